@@ -11,6 +11,7 @@
 
 #include "iolbconv.h"
 #include "kernels.h"
+#include "split_plan.h"
 #include "tune.h"
 #include "wino_mats.h"
 
@@ -43,8 +44,10 @@ struct DeviceState {
 
 // Scratch of the entry point that allocates nothing: the re-laid-out weights of one layer.  Every GPU the
 // library runs on holds its own copy of the array, at its own address, until the process ends.
-constexpr size_t kScratchFloats = (size_t)4 << 20;            // 16 MiB
-static __device__ __align__(256) float scratch[kScratchFloats];
+constexpr size_t kScratchFloats = (size_t)4 << 20;            // largest padded weight tensor conv_direct_noalloc takes
+// room for such a tensor in three bf16 parts
+constexpr size_t kScratchBytes = kScratchFloats * 6;          // 24 MiB
+static __device__ __align__(256) char scratch[kScratchBytes];
 std::mutex g_mutex;
 std::map<int, DeviceState> g_devices;
 
@@ -196,13 +199,106 @@ int check_config(const iolb_shape& s, const iolb_tile_config& cfg)
     return IOLB_EINVAL;
 }
 
+// ---- direct layers on the bf16 matrix cores, operands in three parts ---------------------------
+// Which kernel a layer without a caller-supplied tile runs on.  The choice and the block depend on the layer alone
+// (not on the tensor layout, which changes addresses only, nor on the entry point), so that every entry point gives
+// the same bits for the same layer.
+struct SplitChoice {
+    enum { NONE, CONV, POINT } kind = NONE;
+    iolb::SplitGeom conv{};
+    iolb::SplitPointGeom point{};
+    size_t weight_bytes = 0;
+};
+typedef std::tuple<int, int, int, int, int, int, int, int, int, int, int> SplitKey;
+std::map<SplitKey, SplitChoice> g_split;
+
+SplitChoice split_choice(const iolb_shape& s, int P, int Q, int pad_w, int layout, const iolb_tile_config& tile)
+{
+    const bool hwc = layout == IOLB_LAYOUT_HWC;
+    const SplitKey key(s.N, s.C, s.H, s.W, s.K, s.R, s.S, s.stride, s.pad, pad_w, hwc ? 1 : 0);
+    {
+        std::lock_guard<std::mutex> lock(g_mutex);
+        auto it = g_split.find(key);
+        if (it != g_split.end()) return it->second;
+    }
+    SplitChoice ch;
+    double cycles = 0;
+    if (is_thin(tile)) {
+        // bound by its stores on a kernel of its own
+    } else if (s.R == 1 && s.S == 1 && s.pad == 0 && pad_w == 0) {
+        iolb::SplitPointGeom g{};
+        g.groups = 1; g.images = s.N; g.C = s.C; g.K = g.Ky = s.K; g.HW = g.HWy = P * Q; g.HWin = s.H * s.W; g.Win = s.W; g.Q = Q;
+        g.stride = s.stride; g.hwc = hwc;
+        g.in = hwc ? (s.C % 4 ? iolb::SPLIT_IN_SINGLE : iolb::SPLIT_IN_CHANNELS) : s.stride == 1 ? iolb::SPLIT_IN_PIXELS : iolb::SPLIT_IN_SINGLE;
+        g.vec_out = hwc && s.K % 4 == 0;
+        if (iolb::split_point_plan(&g, &cycles)) {
+            ch.kind = SplitChoice::POINT;
+            ch.point = g;
+            ch.weight_bytes = (size_t)iolb::split_point_weight_bytes(g);
+        }
+    } else {
+        iolb::SplitGeom g{};
+        g.N = s.N; g.C = s.C; g.H = s.H; g.W = s.W; g.K = s.K; g.R = s.R; g.S = s.S; g.stride = s.stride; g.pad = s.pad; g.pad_w = pad_w;
+        g.P = P; g.Q = Q; g.hwc = hwc; g.vec_in = hwc && s.C % 4 == 0; g.vec_out = hwc && s.K % 4 == 0;
+        if (iolb::split_plan(&g, &cycles)) {
+            ch.kind = SplitChoice::CONV;
+            ch.conv = g;
+            ch.weight_bytes = (size_t)iolb::split_weight_bytes(g);
+        }
+    }
+    // conv_direct_noalloc has a fixed room for the kernels and gives the bits of conv_direct: a layer that it takes
+    // (its tile's kernels fit, or it reads them in place) must fit that room in three parts too
+    const long long c_padded = ((long long)s.C + tile.alpha - 1) / tile.alpha * tile.alpha;
+    const bool refused = tile.path == IOLB_PATH_MFMA && (s.K + 31LL) / 32 * 32 * c_padded * s.R * s.S > (long long)kScratchFloats;
+    if (ch.weight_bytes > kScratchBytes && !refused) ch.kind = SplitChoice::NONE;
+    std::lock_guard<std::mutex> lock(g_mutex);
+    g_split[key] = ch;
+    return ch;
+}
+
+int run_split(const float* x, const float* w, float* y, const iolb_shape& s, const SplitChoice& ch, int layout, float* wt_buf)
+{
+    DeviceState* dev = nullptr;
+    int rc = device_state(&dev);
+    if (rc != IOLB_OK) return rc;
+    void* wt = wt_buf;
+    if (!wt) {
+        rc = ensure_workspace(dev, align256(ch.weight_bytes), &wt);
+        if (rc != IOLB_OK) return rc;
+    }
+    hipStream_t st = t_stream;
+    const bool point = ch.kind == SplitChoice::POINT;
+    IOLB_HIP(iolb::launch_split_weights(w, wt, s.K, s.C, s.R, s.S, point ? 4 : ch.conv.ch8, point ? ch.point.Kb16 : ch.conv.Kb16,
+                                        layout == IOLB_LAYOUT_CWH, st));
+    const bool aligned = ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(y)) & 15) == 0;
+    MainKernelTimer timer(st, IOLB_TIME_DIRECT);
+    if (point) {
+        iolb::SplitPointGeom g = ch.point;
+        if (!aligned) { g.vec_out = 0; if (g.in == iolb::SPLIT_IN_CHANNELS) g.in = iolb::SPLIT_IN_SINGLE; }
+        IOLB_HIP(iolb::launch_split_point(x, wt, y, g, st));
+    } else {
+        iolb::SplitGeom g = ch.conv;
+        if (!aligned) g.vec_in = g.vec_out = 0;
+        IOLB_HIP(iolb::launch_split_conv(x, wt, y, g, st));
+    }
+    timer.stop(st);
+    return IOLB_OK;
+}
+
 // layout CWH: s, P, Q describe the transposed layer (H and W, R and S exchanged) and the weights are read
 // transposed; the tensors are then plain CHW tensors of that layer.
 // wt_buf != nullptr: room for the re-laid-out weights (wt_floats floats) given by the caller, so that nothing is
 // allocated; otherwise the library's workspace is used.
+// own_tile: the tile is the library's own choice, not the caller's: the layer may run on the split kernels instead.
 int run_direct(const float* x, const float* w, float* y, const iolb_shape& s, int P, int Q, const iolb_tile_config& cfg,
-               int layout = IOLB_LAYOUT_CHW, int pad_w = -1, float* wt_buf = nullptr, size_t wt_floats = 0)
+               int layout = IOLB_LAYOUT_CHW, int pad_w = -1, float* wt_buf = nullptr, size_t wt_floats = 0, bool own_tile = true)
 {
+    if (own_tile) {
+        const SplitChoice ch = split_choice(s, P, Q, pad_w < 0 ? s.pad : pad_w, layout, cfg);
+        const bool refused = wt_buf && cfg.path == IOLB_PATH_MFMA &&
+                             (size_t)((s.K + 31) / 32 * 32) * ((s.C + cfg.alpha - 1) / cfg.alpha * cfg.alpha) * s.R * s.S > wt_floats;
+        if (ch.kind != SplitChoice::NONE && !refused) return run_split(x, w, y, s, ch, layout, wt_buf);
+    }
     DeviceState* dev = nullptr;
     int rc = device_state(&dev);
     if (rc != IOLB_OK) return rc;
@@ -476,7 +572,7 @@ int conv_direct_cfg(const float* x, const float* w, float* y, int N, int C, int 
     if (rc != IOLB_OK) return rc;
     rc = check_config(s, *cfg);
     if (rc != IOLB_OK) return rc;
-    return run_direct(x, w, y, s, P, Q, *cfg);
+    return run_direct(x, w, y, s, P, Q, *cfg, IOLB_LAYOUT_CHW, -1, nullptr, 0, false);
 }
 
 int conv_direct(const float* x, const float* w, float* y, int N, int C, int H, int W, int K, int R, int S,
@@ -556,7 +652,7 @@ int conv_direct_layout(const float* x, const float* w, float* y, int N, int C, i
         rc = tuned_tile(s, &tile, layout == IOLB_LAYOUT_CHW, layout == IOLB_LAYOUT_CHW);
         if (rc != IOLB_OK) return rc;
     }
-    return run_direct(x, w, y, s, P, Q, tile, layout);
+    return run_direct(x, w, y, s, P, Q, tile, layout, -1, nullptr, 0, cfg == nullptr);
 }
 
 size_t conv_winograd_workspace_bytes(int N, int C, int H, int W, int K, int m)

@@ -1,0 +1,412 @@
+// Direct convolution on the bf16 matrix cores at fp32 precision, dataflow of Sec. 5.2.
+#include "kernels.h"
+#include "split_mfma.h"
+
+#include <type_traits>
+
+namespace iolb {
+
+namespace {
+
+// voffset of an element that does not exist: beyond every buffer's range, so that the load returns zero
+constexpr unsigned OUTSIDE = 0x80000000u;
+
+// Position of the input tile that staged row / column `i` is taken from, relative to the tile's first: with a
+// stride beyond the kernel extent only the rows and columns that some window covers are staged.
+__device__ __forceinline__ int staged_offset(int i, int est, int stride) { return est == stride ? i : i / est * stride + i % est; }
+
+template <int FROM, int TO, class F>
+__device__ __forceinline__ void static_for(F f)
+{
+    if constexpr (FROM < TO) {
+        f(std::integral_constant<int, FROM>{});
+        static_for<FROM + 1, TO>(f);
+    }
+}
+
+template <int MB, int NB, int WM, int WN, bool VEC>
+__global__ void __launch_bounds__(64 * WM * WN, 2)
+split_conv_kernel(const float* __restrict__ x, const u32x4* __restrict__ wt, float* __restrict__ y, SplitGeom g)
+{
+    extern __shared__ u32x4 lds16[];
+    char* const lds = reinterpret_cast<char*>(lds16);
+    constexpr int T = 64 * WM * WN;
+    constexpr int IB = SPLIT_BATCH;
+    const int CH8 = g.ch8;
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, grp = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm_i = wave % WM, wn_i = wave / WM;
+
+    // consecutive workgroup ids are dealt round-robin to the 8 XCDs; remap so that each XCD (one L2) works on a
+    // contiguous range of blocks, whose channel blocks share the same input tile
+    int bid;
+    {
+        const int nblk = gridDim.x, q = nblk >> 3, r = nblk & 7, xcd = blockIdx.x & 7;
+        bid = xcd * q + (xcd < r ? xcd : r) + ((int)blockIdx.x >> 3);
+    }
+    // the divisions run on the vector unit: back to scalars, so that everything derived from them stays scalar
+    const int kb = __builtin_amdgcn_readfirstlane(bid % g.nbk); bid /= g.nbk;
+    const int x0 = __builtin_amdgcn_readfirstlane(bid % g.nbx * g.tx); bid /= g.nbx;
+    const int y0 = __builtin_amdgcn_readfirstlane(bid % g.nby * g.ty);
+    const int n0 = __builtin_amdgcn_readfirstlane(bid / g.nby * g.b);
+
+    const int RS = g.R * g.S;
+    const int steps = (RS * CH8 + 3) >> 2;                  // matrix steps of a chunk: four units each
+    const int items = CH8 * g.halo;
+    const int im_bytes = g.yh * g.rowb, group_bytes = g.b * im_bytes, buf_bytes = CH8 * group_bytes;
+    int* const koff = reinterpret_cast<int*>(lds + g.nbuf * buf_bytes);          // [4 * steps]
+    uint2* const table = reinterpret_cast<uint2*>(koff + ((4 * steps + 1) & ~1));      // [items]
+
+    // LDS byte offset of unit (tap, channel group) relative to a pixel's window corner
+    for (int u = tid; u < 4 * steps; u += T) {
+        const int tap = u / CH8, c8 = u % CH8;
+        int off = 0;
+        if (tap < RS) {
+            const int r = tap / g.S, s = tap % g.S;
+            off = c8 * group_bytes + r * g.rowb + 48 * ((s % g.esx) * g.colw + s / g.esx);
+        }
+        koff[u] = off;
+    }
+    // where the elements of the input tile come from and where they go
+    const int gy0 = y0 * g.stride - g.pad, gx0 = x0 * g.stride - g.pad_w;
+    for (int i = tid; i < items; i += T) {
+        const int c8 = i / g.halo, hp = i % g.halo;
+        const int per = g.yh * g.rowp;
+        const int im = hp / per, rem = hp % per, iy = rem / g.rowp, ix = rem % g.rowp;
+        const int gy = gy0 + staged_offset(iy, g.esy, g.stride), gx = gx0 + staged_offset(ix, g.esx, g.stride);
+        uint2 e;
+        e.x = OUTSIDE;
+        if (n0 + im < g.N && ix < g.xh && gy >= 0 && gy < g.H && gx >= 0 && gx < g.W)
+            e.x = g.hwc ? 4u * (unsigned)(((im * g.H + gy) * g.W + gx) * g.C + c8 * 8)
+                      : 4u * (unsigned)(((im * g.C + c8 * 8) * g.H + gy) * g.W + gx);
+        e.y = (unsigned)(c8 * group_bytes + im * im_bytes + iy * g.rowb + 48 * ((ix % g.esx) * g.colw + ix / g.esx));
+        // c8 in the low bits of the LDS offset (a multiple of 16)
+        e.y |= (unsigned)c8;
+        table[i] = e;
+    }
+
+    // pixels of this lane
+    const int txy = g.tx * g.ty, npix = g.b * txy;
+    int pbase[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        const int slot = (wn_i * NB + nb) * 16 + l16;
+        const int pix = slot < npix ? slot : npix - 1;
+        const int im = pix / txy, rem = pix % txy, py = rem / g.tx, px = rem % g.tx;
+        pbase[nb] = im * im_bytes + py * g.esy * g.rowb + 48 * px;
+    }
+
+    f32x4 acc[MB][NB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    const int nchunks = __builtin_amdgcn_readfirstlane((g.C + 8 * CH8 - 1) / (8 * CH8));
+    // weights of matrix step t: [t][16-channel block][part][lane]
+    const int kb16 = kb * (MB * WM) + wm_i * MB;
+    const size_t wstep = (size_t)g.Kb16 * 192;              // 16-byte pieces per step
+    const u32x4* wp = wt + (size_t)(g.w_per_image ? n0 : 0) * g.w_image + (size_t)kb16 * 192 + lane;
+
+    const unsigned img = (unsigned)((long long)g.C * g.H * g.W * 4);
+    const int images = g.N - n0 < g.b ? g.N - n0 : g.b;
+    const unsigned long long xbase = reinterpret_cast<unsigned long long>(x + (size_t)n0 * g.C * g.H * g.W);
+    const unsigned xlo = __builtin_amdgcn_readfirstlane((unsigned)xbase), xhi = __builtin_amdgcn_readfirstlane((unsigned)(xbase >> 32));
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        reinterpret_cast<void*>((unsigned long long)xhi << 32 | xlo), 0, (int)__builtin_amdgcn_readfirstlane(img * (unsigned)images), 0x00020000);
+    const int cstep = g.hwc ? 4 : 4 * g.H * g.W;
+
+    // staging of chunk ch, batch b (IB items per thread): loads now, split and LDS writes one slot later
+    float xv[IB][8];
+    unsigned xdst[IB];
+    const int batches = __builtin_amdgcn_readfirstlane((items + T * IB - 1) / (T * IB));
+    auto load_batch = [&](int ch, int b) {
+        const int c0 = ch < nchunks ? ch * 8 * CH8 : 0, have = ch < nchunks ? g.C - c0 : 0;
+#pragma unroll
+        for (int i = 0; i < IB; ++i) {
+            const int it = (b * IB + i) * T + tid;
+            uint2 e = {OUTSIDE, ~0u};
+            if (it < items) e = table[it];
+            xdst[i] = e.y;
+            const int left = have - (int)(e.y & 15) * 8;      // channels of this group that exist
+            if constexpr (VEC) {
+                // channels innermost, C a multiple of 4 and x 16-byte aligned: two 16-byte loads
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(rs, left > 4 * h ? (int)e.x + 16 * h : (int)OUTSIDE, c0 * 4, 0);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) xv[i][4 * h + j] = __uint_as_float(q[j]);
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    // the scalar offset stays inside the buffer, whatever the lanes do
+                    const int cj = c0 + j < g.C ? c0 + j : g.C - 1;
+                    xv[i][j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, left > j ? (int)e.x : (int)OUTSIDE, cj * cstep, 0));
+                }
+            }
+        }
+    };
+    auto write_batch = [&](char* buf) {
+#pragma unroll
+        for (int i = 0; i < IB; ++i) {
+            u32x4 h, m, l;
+            split_eight(xv[i], h, m, l);
+            if (xdst[i] != ~0u) {
+                u32x4* d = reinterpret_cast<u32x4*>(buf + (xdst[i] & ~15u));
+                d[0] = h; d[1] = m; d[2] = l;
+            }
+        }
+    };
+    auto barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+
+    barrier();                                              // tables are in place
+    for (int b = 0; b < batches; ++b) {
+        load_batch(0, b);
+        write_batch(lds);
+    }
+    // the order in which a step issues its loads: first the weights, then the inputs
+    u32x4 a[MB * 3];
+#pragma unroll
+    for (int j = 0; j < MB * 3; ++j) a[j] = wp[j * 64];
+    __builtin_amdgcn_sched_barrier(0);
+    if (nchunks > 1) load_batch(1, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    barrier();
+
+    u32x4 bf[2][3];
+    auto fetch = [&](u32x4 (&f)[3], const char* from) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) f[p] = *reinterpret_cast<const u32x4*>(from + 16 * p);
+    };
+    int ch = 0, k = 0;
+    int ko = koff[grp];
+    fetch(bf[0], lds + ko + pbase[0]);
+    // One matrix step: four units (tap, channel group) for every block of the wave.  The weights of the next step are
+    // on their way while this one multiplies; the pixels come from LDS one block ahead, across steps too.
+    for (int left = nchunks * steps; left > 0; --left) {
+        u32x4 an[MB * 3];
+        const bool chunk_end = k + 1 == steps;
+        if (!(chunk_end && ch + 1 == nchunks)) wp += wstep;
+#pragma unroll
+        for (int j = 0; j < MB * 3; ++j) an[j] = wp[j * 64];
+        const char* bp = lds + (ch & 1) * buf_bytes;
+        const int kn = koff[4 * (chunk_end ? 0 : k + 1) + grp];
+        auto block = [&](auto nb_c) {
+            constexpr int nb = decltype(nb_c)::value;
+            if constexpr (nb + 1 < NB) fetch(bf[(nb + 1) & 1], bp + ko + pbase[nb + 1]);
+            else                       fetch(bf[(nb + 1) & 1], bp + kn + pbase[0]);
+            constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};      // small products first
+#pragma unroll
+            for (int q = 0; q < 6; ++q)
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+                    acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        __builtin_bit_cast(bf16x8, a[mb * 3 + PA[q]]), __builtin_bit_cast(bf16x8, bf[nb & 1][PB[q]]), acc[mb][nb], 0, 0, 0);
+        };
+        constexpr int HALF = NB / 2;
+        static_for<0, HALF>(block);
+        // Loads come back in the order they were issued.  Where the paths with and without input loads meet, the
+        // compiler would have to assume the worst and wait for every load at the next use of a weight: the two paths
+        // stay apart until each has waited for its own weights.
+        if (k < batches && ch + 1 < nchunks) {
+            write_batch(lds + ((ch + 1) & 1) * buf_bytes);
+            const bool more = k + 1 < batches;
+            load_batch(more ? ch + 1 : ch + 2, more ? k + 1 : 0);
+            static_for<HALF, NB>(block);
+            constexpr int LOADS = (VEC ? 2 : 8) * IB;
+            __builtin_amdgcn_s_waitcnt(0x0F70 | (LOADS & 15) | (LOADS >> 4) << 14);       // vmcnt(LOADS)
+        } else {
+            static_for<HALF, NB>(block);
+            __builtin_amdgcn_s_waitcnt(0x0F70);                                             // vmcnt(0)
+        }
+        if constexpr (NB & 1) {
+#pragma unroll
+            for (int p = 0; p < 3; ++p) bf[0][p] = bf[1][p];
+        }
+#pragma unroll
+        for (int j = 0; j < MB * 3; ++j) a[j] = an[j];
+        ko = kn;
+        ++k;
+        if (chunk_end) {
+            barrier();
+            k = 0;
+            ++ch;
+            fetch(bf[0], lds + (ch & 1) * buf_bytes + ko + pbase[0]);
+        }
+    }
+
+    // each partial sum is complete: write the block once.  Register i of a 16 x 16 block holds channel 4 grp + i of
+    // pixel l16.  Outputs that are not finite, or so small that parts of their operands may lie below the smallest
+    // bf16, are marked and computed again below.
+    const size_t PQ = (size_t)g.P * g.Q;
+    unsigned long long again = 0;
+    static_assert(MB * NB * 4 <= 64, "one mark per output");
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        const int slot = (wn_i * NB + nb) * 16 + l16;
+        const int im = slot / txy, rem = slot % txy, py = y0 + rem / g.tx, px = x0 + rem % g.tx;
+        if (slot >= npix || n0 + im >= g.N || py >= g.P || px >= g.Q) continue;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            const int k0 = (kb16 + mb) * 16 + 4 * grp;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float v = acc[mb][nb][i], av = __builtin_fabsf(v);
+                if (!(av <= 3.402823466e38f && av >= 1.3e-29f) && av != 0.f) again |= 1ull << ((nb * MB + mb) * 4 + i);
+            }
+            if (g.hwc) {
+                float* yp = y + (((size_t)(n0 + im) * g.P + py) * g.Q + px) * g.K + k0;
+                if (g.vec_out && k0 + 3 < g.K) {
+                    *reinterpret_cast<f32x4*>(yp) = acc[mb][nb];
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (k0 + i < g.K) yp[i] = acc[mb][nb][i];
+                }
+            } else {
+                float* yp = y + ((size_t)(n0 + im) * g.K + k0) * PQ + (size_t)py * g.Q + px;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (k0 + i < g.K) yp[(size_t)i * PQ] = acc[mb][nb][i];
+            }
+        }
+    }
+    while (again) {
+        const int bit = __builtin_ctzll(again);
+        again &= again - 1;
+        const int nb = bit / (4 * MB), mb = bit / 4 % MB, i = bit & 3;
+        const int slot = (wn_i * NB + nb) * 16 + l16;
+        const int im = slot / txy, rem = slot % txy, py = y0 + rem / g.tx, px = x0 + rem % g.tx;
+        const int row = 4 * grp + i, k = (kb16 + mb) * 16 + row;
+        if (k >= g.K) continue;
+        const unsigned short* wk = reinterpret_cast<const unsigned short*>(wt + (size_t)(g.w_per_image ? n0 : 0) * g.w_image + (size_t)(kb16 + mb) * 192);
+        float sum = 0.f;
+        for (int c = 0; c < g.C; ++c)
+            for (int tap = 0; tap < RS; ++tap) {
+                const int gy = py * g.stride - g.pad + tap / g.S, gx = px * g.stride - g.pad_w + tap % g.S;
+                if (gy < 0 || gy >= g.H || gx < 0 || gx >= g.W) continue;
+                const int u = tap * CH8 + c / 8 % CH8, ln = (u & 3) * 16 + row;
+                const unsigned short* q = wk + ((size_t)(c / (8 * CH8)) * steps + (u >> 2)) * wstep * 8 + ln * 8 + c % 8;
+                const float wv = bf16_bits_to_float(q[0]) + (bf16_bits_to_float(q[512]) + bf16_bits_to_float(q[1024]));
+                const size_t xi = g.hwc ? (((size_t)(n0 + im) * g.H + gy) * g.W + gx) * g.C + c
+                                      : (((size_t)(n0 + im) * g.C + c) * g.H + gy) * g.W + gx;
+                sum = __builtin_fmaf(x[xi], wv, sum);
+            }
+        y[g.hwc ? (((size_t)(n0 + im) * g.P + py) * g.Q + px) * g.K + k : ((size_t)(n0 + im) * g.K + k) * PQ + (size_t)py * g.Q + px] = sum;
+    }
+}
+
+// Transformed kernels U[plane][rows][cols] (channel rows, kernel columns) -> the operands of the product's steps,
+// [plane][chunk of 32][16-channel block][part][lane][8 bf16].
+__global__ void __launch_bounds__(256)
+split_planes_kernel(const float* __restrict__ U, u32x4* __restrict__ wt, int K, int C, int rows, int cols, int chunks, int Kb16, long long pieces)
+{
+    const long long id = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (id >= pieces) return;
+    const int lane = (int)(id & 63), kb = (int)((id >> 6) % Kb16), t = (int)((id >> 6) / Kb16);
+    const int plane = t / chunks, k = kb * 16 + (lane & 15), c0 = (t % chunks) * 32 + (lane >> 4) * 8;
+    unsigned short p[3][8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        float v = 0.f;
+        if (k < K && c0 + j < C) v = U[((size_t)plane * rows + c0 + j) * cols + k];
+        split_kept(v, p[0][j], p[1][j], p[2][j]);
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        u32x4 o;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[j] = (unsigned)p[q][2 * j] | ((unsigned)p[q][2 * j + 1] << 16);
+        wt[((size_t)t * Kb16 + kb) * 192 + q * 64 + lane] = o;
+    }
+}
+
+// w[K][C][R][S] -> the operands of the matrix steps, [chunk][step][16-channel block][part][lane][8 bf16].  One
+// thread per 16-byte piece.
+__global__ void __launch_bounds__(256)
+split_weights_kernel(const float* __restrict__ w, u32x4* __restrict__ wt, int K, int C, int R, int S, int ch8, int steps, int Kb16,
+                     long long pieces, int transposed)
+{
+    const long long id = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (id >= pieces) return;
+    const int lane = (int)(id & 63);
+    const int kb = (int)((id >> 6) % Kb16);
+    const int t = (int)((id >> 6) / Kb16);
+    const int RS = R * S;
+    const int k = kb * 16 + (lane & 15), u = (t % steps) * 4 + (lane >> 4);
+    const int tap = u / ch8, c0 = (t / steps * ch8 + u % ch8) * 8;
+    const int tw = transposed ? (tap % S) * R + tap / S : tap;
+    unsigned short p[3][8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        float v = 0.f;
+        if (k < K && tap < RS && c0 + j < C) v = w[((size_t)k * C + c0 + j) * RS + tw];
+        split_kept(v, p[0][j], p[1][j], p[2][j]);
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        u32x4 o;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[j] = (unsigned)p[q][2 * j] | ((unsigned)p[q][2 * j + 1] << 16);
+        wt[((size_t)t * Kb16 + kb) * 192 + q * 64 + lane] = o;
+    }
+}
+
+template <int MB, int NB, int WM, int WN, bool VEC>
+hipError_t launch_one(const float* x, const u32x4* wt, float* y, const SplitGeom& g, hipStream_t st)
+{
+    auto kern = split_conv_kernel<MB, NB, WM, WN, VEC>;
+    const size_t shm = split_lds_bytes(g);
+    if (shm > 64 * 1024) {
+        const hipError_t e = allow_large_lds((const void*)kern);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kern, dim3(g.nbk * g.nbx * g.nby * g.nbn), dim3(64 * WM * WN), shm, st, x, wt, y, g);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_split_weights(const float* w, void* wt, int K, int C, int R, int S, int ch8, int Kb16, bool transposed, hipStream_t st)
+{
+    const int steps = (R * S * ch8 + 3) / 4;
+    const long long pieces = (long long)((C + 8 * ch8 - 1) / (8 * ch8)) * steps * Kb16 * 64;
+    if ((pieces + 255) / 256 > 0x7fffffffLL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(split_weights_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st, w, (u32x4*)wt, K, C, R, S, ch8, steps,
+                       Kb16, pieces, transposed ? 1 : 0);
+    return hipGetLastError();
+}
+
+hipError_t launch_split_planes(const float* U, void* wt, int planes, int K, int C, int rows, int cols, int Kb16, hipStream_t st)
+{
+    const int chunks = (C + 31) / 32;
+    const long long pieces = (long long)planes * chunks * Kb16 * 64;
+    if ((pieces + 255) / 256 > 0x7fffffffLL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(split_planes_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st, U, (u32x4*)wt, K, C, rows, cols, chunks,
+                       Kb16, pieces);
+    return hipGetLastError();
+}
+
+template <bool VEC>
+static hipError_t launch_shape(const float* x, const u32x4* wt, float* y, const SplitGeom& g, hipStream_t st)
+{
+#define IOLB_SPLIT_CASE(M_, N_, A_, B_) \
+    if (g.mb == M_ && g.nb == N_ && g.wm == A_ && g.wn == B_) return launch_one<M_, N_, A_, B_, VEC>(x, wt, y, g, st);
+    IOLB_SPLIT_SHAPES(IOLB_SPLIT_CASE)
+#undef IOLB_SPLIT_CASE
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_split_conv(const float* x, const void* wt, float* y, const SplitGeom& g, hipStream_t st)
+{
+    // what the kernel assumes of its geometry
+    if (g.b * g.tx * g.ty > 16 * g.nb * g.wn || split_lds_bytes(g) > 160 * 1024 || g.Kb16 != g.nbk * g.mb * g.wm ||
+        (split_chunks(g) > 1 && split_batches(g) > split_steps(g)) || (g.nbuf < 2 && split_chunks(g) > 1) || g.ch8 < 1 || g.ch8 > 8 ||
+        4LL * g.b * g.C * g.H * g.W >= (1LL << 31) || (g.w_per_image && g.b != 1) || (g.vec_in && (!g.hwc || g.C % 4)))
+        return hipErrorInvalidValue;
+    const u32x4* w = static_cast<const u32x4*>(wt);
+    return g.vec_in ? launch_shape<true>(x, w, y, g, st) : launch_shape<false>(x, w, y, g, st);
+}
+
+}  // namespace iolb

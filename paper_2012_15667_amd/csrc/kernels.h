@@ -59,6 +59,75 @@ hipError_t launch_direct_mfma(const float* x, const float* wt, float* y, const D
 // The same for the channels-innermost tensor layout (g.hwc = 1).
 hipError_t launch_direct_mfma_hwc(const float* x, const float* wt, float* y, const DirectGeom& g, hipStream_t st);
 
+// Direct convolution on the bf16 matrix cores with operands in three parts (direct_split.hip).
+struct SplitGeom {
+    int N, C, H, W, K, R, S, stride, pad, P, Q;
+    int pad_w;
+    int b, tx, ty;             // output sub-block: b images * ty rows * tx columns, at most 16 * nb * wn pixels
+    int mb, nb, wm, wn;        // wave grid wm x wn, blocks of 16 channels x 16 pixels per wave mb x nb
+    int ch8;                   // channels per chunk / 8, 1 to 8
+    int nbx, nby, nbn, nbk;    // blocks along W_out, H_out, batch, C_out
+    int esy, esx;              // staged stride: min(stride, R), min(stride, S)
+    int yh, xh;                // staged rows and columns per image
+    int colw, rowp;            // columns of one residue class mod esx; elements of a staged row (esx * colw)
+    int rowb;                  // bytes from one staged row to the next in LDS
+    int halo;                  // b * yh * rowp
+    int nbuf;                  // LDS buffers: 1 when the channels fit one chunk
+    int Kb16;                  // 16-channel blocks, whole workgroup blocks
+    int w_per_image;           // every image has kernels of its own (w_image 16-byte pieces apart); b = 1
+    long long w_image;
+    int hwc, vec_in, vec_out;  // channels innermost; with 16-byte loads / stores of four channels
+};
+constexpr int SPLIT_BATCH = 2;          // (pixel, 8 channels) items of the input tile that a thread stages at once
+// The workgroup shapes that exist: blocks per wave (channels, pixels), wave grid (channels, pixels).
+#define IOLB_SPLIT_SHAPES(X) \
+    X(1, 2, 4, 1) X(1, 4, 4, 1) X(1, 8, 4, 1) X(2, 2, 4, 1) X(2, 4, 4, 1) X(2, 5, 4, 1) X(2, 7, 4, 1) X(2, 8, 4, 1) \
+    X(3, 2, 4, 1) X(3, 4, 4, 1) X(3, 5, 4, 1) X(4, 2, 4, 1) X(4, 4, 4, 1)                                           \
+    X(1, 2, 2, 2) X(1, 4, 2, 2) X(1, 7, 2, 2) X(1, 8, 2, 2) X(2, 2, 2, 2) X(2, 4, 2, 2) X(2, 5, 2, 2) X(2, 7, 2, 2) X(2, 8, 2, 2) \
+    X(3, 2, 2, 2) X(3, 4, 2, 2) X(3, 5, 2, 2) X(4, 4, 2, 2)                                                          \
+    X(1, 1, 1, 4) X(1, 2, 1, 4) X(1, 4, 1, 4) X(1, 7, 1, 4) X(2, 1, 1, 4) X(2, 2, 1, 4) X(2, 4, 1, 4) X(2, 7, 1, 4) X(3, 2, 1, 4) X(3, 4, 1, 4)
+inline int split_steps(const SplitGeom& g) { return (g.R * g.S * g.ch8 + 3) / 4; }
+inline int split_chunks(const SplitGeom& g) { return (g.C + 8 * g.ch8 - 1) / (8 * g.ch8); }
+inline int split_batches(const SplitGeom& g)
+{
+    const int per = 64 * g.wm * g.wn * SPLIT_BATCH;
+    return (g.ch8 * g.halo + per - 1) / per;
+}
+// buffers of the input tile, offsets of the matrix steps' units, table of the input tile's elements
+inline long long split_lds_bytes(const SplitGeom& g)
+{
+    return (long long)g.nbuf * g.ch8 * g.b * g.yh * g.rowb + 4 * ((4 * split_steps(g) + 1) & ~1) + 8LL * g.ch8 * g.halo;
+}
+inline long long split_weight_bytes(const SplitGeom& g) { return (long long)split_chunks(g) * split_steps(g) * g.Kb16 * 3072; }
+// Kernels in three parts in the order of the matrix steps, written from w[K][C][R][S] (transposed: w[K][C][S][R]), or
+// for 1 x 1 products from planes U[plane][rows][cols] of transformed kernels (ch8 = 4).
+hipError_t launch_split_weights(const float* w, void* wt, int K, int C, int R, int S, int ch8, int Kb16, bool transposed, hipStream_t st);
+hipError_t launch_split_planes(const float* U, void* wt, int planes, int K, int C, int rows, int cols, int Kb16, hipStream_t st);
+hipError_t launch_split_conv(const float* x, const void* wt, float* y, const SplitGeom& g, hipStream_t st);
+
+// 1 x 1 layers and the Winograd product on the same matrix cores (split_point.hip): per group of images that share
+// kernels (all images of a layer; one transformed plane), y[K][HW] = w[K][C] x[C][HW] over the group's pixels.
+struct SplitPointGeom {
+    int groups, images;        // groups, images per group
+    int C, K, Ky;              // Ky: channel planes per image of y (>= K)
+    int HW, HWy, HWin, Win, Q, stride;   // output pixels per image, pitch of an output plane; input plane, row lengths and stride
+    int mb, nb, wm, wn;        // wave grid wm x wn, blocks of 16 channels x 16 pixels per wave mb x nb
+    int nbk, nbp;              // blocks along the channels, along a group's pixels
+    int Kb16;                  // 16-channel blocks in the re-laid-out kernels
+    long long w_image;         // 16-byte pieces from one group's kernels to the next
+    int hwc, in, vec_out;      // in: how the inputs are read, below
+};
+// Inputs read in single floats; four channels at a time (channels innermost, C a multiple of 4, 16-byte aligned); two or
+// four neighbouring pixels at a time (channels outermost, stride 1; blocks may run on into the next image only where
+// HW is a multiple of that).
+enum { SPLIT_IN_SINGLE = 0, SPLIT_IN_CHANNELS = 1, SPLIT_IN_PIXELS = 2 };
+constexpr int split_point_pixels(int in, int npix) { return in != SPLIT_IN_PIXELS ? 1 : npix >= 96 ? 4 : 2; }
+#define IOLB_SPLIT_POINT_SHAPES(X) \
+    X(1, 2, 4, 1) X(1, 4, 4, 1) X(1, 8, 4, 1) X(2, 2, 4, 1) X(2, 4, 4, 1) X(2, 6, 4, 1) X(2, 8, 4, 1) X(3, 4, 4, 1) X(4, 4, 4, 1) \
+    X(1, 4, 2, 2) X(2, 2, 2, 2) X(2, 4, 2, 2) X(4, 4, 2, 2) X(2, 8, 4, 2) X(4, 4, 4, 2) X(2, 4, 4, 2)
+inline long long split_point_weight_bytes(const SplitPointGeom& g) { return (g.C + 31LL) / 32 * g.Kb16 * 3072; }
+hipError_t launch_split_point(const float* x, const void* wt, float* y, const SplitPointGeom& g, hipStream_t st);
+
 // Thin layers (direct_thin.hip): 3 x 3 kernels, stride 1, C <= 4, plain NCHW tensors.  wk: K rows of
 // direct_thin_row(C) floats (the 9 C elements of a kernel, zero-padded to whole 16-float pieces), 64-byte aligned,
 // written from w by launch_direct_thin_rows.  Of g the layer, P, Q, pad and pad_w are used.

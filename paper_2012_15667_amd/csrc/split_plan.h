@@ -1,0 +1,21 @@
+// Which layers run on the bf16 matrix cores with operands in three parts, and on which workgroup shape.
+#ifndef IOLB_SPLIT_PLAN_H
+#define IOLB_SPLIT_PLAN_H
+
+#include "kernels.h"
+
+namespace iolb {
+
+// Fills the derived fields of g (extents, pitches, block counts) from the layer, the block (b, tx, ty) and the
+// workgroup shape (mb, nb, wm, wn, ch8).  False when the kernel cannot run it.
+bool split_derive(SplitGeom* g);
+// The block and workgroup shape of least modelled time for the layer in g; *cycles gets that time (clock cycles of
+// the chip at full occupation).  False when no shape runs the layer.
+bool split_plan(SplitGeom* g, double* cycles);
+double split_cycles(const SplitGeom& g);
+// The same for 1 x 1 layers: groups, images, C, K, Ky, HW, HWy, HWin, Win, Q, stride, hwc and in describe the layer.
+bool split_point_plan(SplitPointGeom* g, double* cycles);
+
+}  // namespace iolb
+
+#endif

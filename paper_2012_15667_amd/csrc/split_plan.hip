@@ -1,0 +1,146 @@
+// The block of a layer on the split matrix-core kernel (direct_split.hip): host only.
+#include "split_plan.h"
+
+#include <algorithm>
+#include <vector>
+
+namespace iolb {
+
+bool split_derive(SplitGeom* g)
+{
+    g->esy = std::min(g->stride, g->R);
+    g->esx = std::min(g->stride, g->S);
+    const long long yh = (long long)(g->ty - 1) * g->esy + g->R, xh = (long long)(g->tx - 1) * g->esx + g->S;
+    if (yh * xh * g->b > 8192) return false;
+    g->yh = (int)yh;
+    g->xh = (int)xh;
+    g->colw = (g->xh + g->esx - 1) / g->esx;
+    g->rowp = g->colw * g->esx;
+    g->halo = g->b * g->yh * g->rowp;
+    const int z = 16 * g->mb * g->wm;
+    g->nbk = (g->K + z - 1) / z;
+    g->Kb16 = g->nbk * g->mb * g->wm;
+    g->nbx = (g->Q + g->tx - 1) / g->tx;
+    g->nby = (g->P + g->ty - 1) / g->ty;
+    g->nbn = (g->N + g->b - 1) / g->b;
+    if ((long long)g->nbk * g->nbx * g->nby * g->nbn > 0x7fffffffLL) return false;
+    g->nbuf = split_chunks(*g) > 1 ? 2 : 1;
+    if (g->b * g->tx * g->ty > 16 * g->nb * g->wn) return false;
+    if (4LL * g->b * g->C * g->H * g->W >= (1LL << 31)) return false;
+    if (split_chunks(*g) > 1 && split_batches(*g) > split_steps(*g)) return false;
+    // Sixteen lanes read 16 bytes each of consecutive pixels, 48 bytes apart: that covers every LDS bank once.  A row
+    // pitch that is congruent to the bytes of a tile row modulo the 256 bytes of the banks keeps it so across a row
+    // end; taken where it does not cost a resident workgroup.
+    g->rowb = g->rowp * 48;
+    const long long tight = split_lds_bytes(*g);
+    if (g->ty * g->b > 1) {
+        int padded = g->rowb;
+        while ((g->esy * padded - 48 * g->tx) % 256 && padded < g->rowb + 256) padded += 16;
+        if ((g->esy * padded - 48 * g->tx) % 256 == 0) {
+            SplitGeom t = *g;
+            t.rowb = padded;
+            const long long full = 160 * 1024;
+            if (split_lds_bytes(t) <= full && std::min(full / split_lds_bytes(t), 2LL) == std::min(full / tight, 2LL)) g->rowb = padded;
+        }
+    }
+    return split_lds_bytes(*g) <= 160 * 1024;
+}
+
+double split_cycles(const SplitGeom& g)
+{
+    const double steps = split_steps(g), chunks = split_chunks(g);
+    const double T = 64.0 * g.wm * g.wn;
+    const double mfma = 96.0 * g.mb * g.nb;
+    const double items = g.ch8 * g.halo / T;
+    const double wg = chunks * (steps * (mfma + 60) + items * 220 + 200) + 4000 + 60.0 * g.mb * g.nb + items * 900;
+    const double grid = (double)g.nbk * g.nbx * g.nby * g.nbn;
+    const bool two = split_lds_bytes(g) <= 80 * 1024;
+    const double per = grid / 256;
+    const double rounds = per <= 1 ? 1 : per <= 4 ? (double)(long long)(per + 0.999) : per + 0.6;
+    return rounds * wg * (two && per > 1 ? 1.15 : 1.45);
+}
+
+bool split_plan(SplitGeom* g, double* cycles)
+{
+    struct Shape { int mb, nb, wm, wn; };
+    static const Shape shapes[] = {
+#define IOLB_SPLIT_ENTRY(M_, N_, A_, B_) {M_, N_, A_, B_},
+        IOLB_SPLIT_SHAPES(IOLB_SPLIT_ENTRY)
+#undef IOLB_SPLIT_ENTRY
+    };
+    // cuts of an extent into k nearly equal parts
+    auto cuts = [](int extent, int most) {
+        std::vector<int> v;
+        for (int k = 1; k <= extent; ++k) {
+            const int c = (extent + k - 1) / k;
+            if (c > most) continue;
+            if (v.empty() || v.back() != c) v.push_back(c);
+            if (v.size() >= 24) break;
+        }
+        return v;
+    };
+    bool found = false;
+    SplitGeom best = *g;
+    double best_cycles = 0;
+    for (const Shape& sh : shapes) {
+        const int slots = 16 * sh.nb * sh.wn;
+        for (int ch8 : {4, 2, 1}) {
+            if ((ch8 == 4 && g->C <= 16) || (ch8 == 1 && g->C > 8)) continue;
+            SplitGeom t = *g;
+            t.mb = sh.mb; t.nb = sh.nb; t.wm = sh.wm; t.wn = sh.wn; t.ch8 = ch8;
+            for (int tx : cuts(g->Q, slots))
+                for (int ty : cuts(g->P, slots / tx)) {
+                    const int most_b = (tx == g->Q && ty == g->P && !g->w_per_image) ? std::min(g->N, slots / (tx * ty)) : 1;
+                    for (int b = 1; b <= most_b; ++b) {
+                        if (b * tx * ty * 2 < slots) continue;           // a smaller shape does it
+                        t.tx = tx; t.ty = ty; t.b = b;
+                        if (!split_derive(&t)) continue;
+                        const double c = split_cycles(t);
+                        if (!found || c < best_cycles) { found = true; best = t; best_cycles = c; }
+                    }
+                }
+        }
+    }
+    if (found) { *g = best; *cycles = best_cycles; }
+    return found;
+}
+
+bool split_point_plan(SplitPointGeom* g, double* cycles)
+{
+    struct Shape { int mb, nb, wm, wn; };
+    static const Shape shapes[] = {
+#define IOLB_POINT_ENTRY(M_, N_, A_, B_) {M_, N_, A_, B_},
+        IOLB_SPLIT_POINT_SHAPES(IOLB_POINT_ENTRY)
+#undef IOLB_POINT_ENTRY
+    };
+    bool found = false;
+    SplitPointGeom best = *g;
+    double best_cycles = 0;
+    for (const Shape& sh : shapes) {
+        SplitPointGeom t = *g;
+        t.mb = sh.mb; t.nb = sh.nb; t.wm = sh.wm; t.wn = sh.wn;
+        const int npix = 16 * t.nb * t.wn, z = 16 * t.mb * t.wm;
+        // pixels read several at a time must not run on into another image
+        if (t.in == SPLIT_IN_PIXELS && t.images > 1 && t.HW % split_point_pixels(t.in, npix)) {
+            if (t.w_image == 0 && t.HW >= 128) { t.groups *= t.images; t.images = 1; }
+            else t.in = SPLIT_IN_SINGLE;
+        }
+        t.nbk = (t.K + z - 1) / z;
+        t.Kb16 = t.nbk * t.mb * t.wm;
+        const long long nbp = ((long long)t.images * t.HW + npix - 1) / npix, grid = nbp * t.groups * t.nbk;
+        const long long span = std::min<long long>((t.HW - 1 + npix - 1) / t.HW + 1, t.images);
+        if (grid > 0x7fffffffLL || (long long)t.images * t.HW >= (1LL << 31) - 1024 || 4 * span * t.C * t.HWin >= (1LL << 31)) continue;
+        t.nbp = (int)nbp;
+        // a step of a workgroup: z x 32 weights in three parts and 32 channels of npix pixels come in at 19 bytes per
+        // clock and compute unit; alone on its unit a workgroup waits some 3200 clocks for them
+        const double chunks = (t.C + 31) / 32, n = grid / 256.0, rounds = n <= 4 ? (double)((grid + 255) / 256) : n + 0.5;
+        const double step = std::max((192.0 * z + 128.0 * npix) / 19, 96.0 * t.mb * t.nb * (t.wm * t.wn / 4) * 1.4);
+        const double res = t.mb * t.nb <= 4 ? 4 : t.mb * t.nb <= 8 ? 3 : 8.0 / (t.wm * t.wn);
+        const double c = std::max(rounds * chunks * step, (double)(long long)(rounds / res + 0.999) * chunks * 3200) + 6000;
+        if (!found || c < best_cycles) { found = true; best = t; best_cycles = c; }
+    }
+    if (found) { *g = best; *cycles = best_cycles; }
+    return found;
+}
+
+}  // namespace iolb

@@ -1,0 +1,304 @@
+// 1 x 1 convolution, and the product step of unfused Winograd, on the bf16 matrix cores at fp32 precision.
+#include "kernels.h"
+#include "split_mfma.h"
+
+#include <type_traits>
+
+namespace iolb {
+
+namespace {
+
+constexpr unsigned OUTSIDE = 0x80000000u;
+
+template <int FROM, int TO, class F>
+__device__ __forceinline__ void static_for(F f)
+{
+    if constexpr (FROM < TO) {
+        f(std::integral_constant<int, FROM>{});
+        static_for<FROM + 1, TO>(f);
+    }
+}
+
+template <int MB, int NB, int WM, int WN, int IN>
+__global__ void __launch_bounds__(64 * WM * WN, 2)
+split_point_kernel(const float* __restrict__ x, const u32x4* __restrict__ wt, float* __restrict__ y, SplitPointGeom g)
+{
+    constexpr int T = 64 * WM * WN, NPIX = 16 * NB * WN, BUF = 4 * NPIX * 48;
+    // an input item: CH channels of PX neighbouring pixels
+    constexpr int PX = split_point_pixels(IN, NPIX), CH = IN == SPLIT_IN_PIXELS ? 4 : 8;
+    constexpr int ITEMS = 32 / CH * NPIX / PX, IB = (ITEMS + T - 1) / T;
+    extern __shared__ u32x4 lds16[];
+    char* const lds = reinterpret_cast<char*>(lds16);       // two buffers, then 48 bytes that nobody reads
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, grp = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm_i = wave % WM, wn_i = wave / WM;
+
+    int bid;
+    {
+        const int nblk = gridDim.x, q = nblk >> 3, r = nblk & 7, xcd = blockIdx.x & 7;
+        bid = xcd * q + (xcd < r ? xcd : r) + ((int)blockIdx.x >> 3);
+    }
+    const int kb = __builtin_amdgcn_readfirstlane(bid % g.nbk); bid /= g.nbk;
+    const int group = __builtin_amdgcn_readfirstlane(bid / g.nbp);        // images that share kernels
+    const int pix0 = __builtin_amdgcn_readfirstlane(bid % g.nbp) * NPIX;  // first pixel, in the group's images one after the other
+    const int n0 = group * g.images + __builtin_amdgcn_readfirstlane(pix0 / g.HW);
+    const int p0 = __builtin_amdgcn_readfirstlane(pix0 % g.HW);           // ... in image n0
+    const long long left_px = (long long)g.images * g.HW - pix0;          // pixels of the group from there on
+
+    const size_t image = (size_t)g.C * g.HWin;
+    const int span = __builtin_amdgcn_readfirstlane((p0 + NPIX - 1) / g.HW + 1);              // images the block touches
+    const int have = (group + 1) * g.images - n0;
+    const unsigned long long xbase = reinterpret_cast<unsigned long long>(x + (size_t)n0 * image);
+    // (the builtin returns a signed int: the halves have to be unsigned before they are put together)
+    const unsigned xlo = __builtin_amdgcn_readfirstlane((unsigned)xbase), xhi = __builtin_amdgcn_readfirstlane((unsigned)(xbase >> 32));
+    const unsigned range = __builtin_amdgcn_readfirstlane((unsigned)(4 * image * (span < have ? span : have)));
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        reinterpret_cast<void*>((unsigned long long)xhi << 32 | xlo), 0, (int)range, 0x00020000);
+
+    // the input items of this thread
+    unsigned src[IB], dst[IB];
+    int c_in[IB];
+#pragma unroll
+    for (int i = 0; i < IB; ++i) {
+        const int it = i * T + tid, px = it % (NPIX / PX) * PX;
+        c_in[i] = it / (NPIX / PX) * CH;
+        src[i] = OUTSIDE;
+        dst[i] = 2 * BUF;
+        if (it < ITEMS) {
+            dst[i] = (unsigned)(48 * (c_in[i] / 8 * NPIX + px) + (c_in[i] & 4) * 2);
+            if (px < left_px) {
+                const int q = p0 + px, im = q / g.HW, r = q % g.HW;
+                const int in = g.stride == 1 ? r : r / g.Q * g.stride * g.Win + r % g.Q * g.stride;
+                src[i] = g.hwc ? 4u * (unsigned)((im * g.HWin + in) * g.C + c_in[i]) : 4u * (unsigned)((im * g.C + c_in[i]) * g.HWin + in);
+            }
+        }
+    }
+    const int cstep = g.hwc ? 4 : 4 * g.HWin;
+
+    f32x4 acc[MB][NB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    const int nchunks = (g.C + 31) >> 5;
+    const int kb16 = kb * (MB * WM) + wm_i * MB;
+    const size_t wstep = (size_t)g.Kb16 * 192;
+    const u32x4* wp = wt + (size_t)group * g.w_image + (size_t)kb16 * 192 + lane;
+
+    float xv[2][IB][CH * PX];
+    auto load_x = [&](float (&v)[IB][CH * PX], int ch) {
+        const int c0 = ch < nchunks ? 32 * ch : 0, cl = ch < nchunks ? g.C - c0 : 0;
+#pragma unroll
+        for (int i = 0; i < IB; ++i) {
+            const int some = cl - c_in[i];                  // channels of this item that exist
+            if constexpr (IN == SPLIT_IN_CHANNELS) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(rs, some > 4 * h ? (int)src[i] + 16 * h : (int)OUTSIDE, c0 * 4, 0);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) v[i][4 * h + j] = __uint_as_float(q[j]);
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < CH; ++j) {
+                    const int cj = c0 + j < g.C ? c0 + j : g.C - 1, at = some > j ? (int)src[i] : (int)OUTSIDE;
+                    if constexpr (PX == 4) {
+                        const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(rs, at, cj * cstep, 0);
+#pragma unroll
+                        for (int p = 0; p < 4; ++p) v[i][p * CH + j] = __uint_as_float(q[p]);
+                    } else if constexpr (PX == 2) {
+                        const u32x2 q = __builtin_amdgcn_raw_buffer_load_b64(rs, at, cj * cstep, 0);
+                        v[i][j] = __uint_as_float(q[0]);
+                        v[i][CH + j] = __uint_as_float(q[1]);
+                    } else {
+                        v[i][j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, at, cj * cstep, 0));
+                    }
+                }
+            }
+        }
+    };
+    auto write_x = [&](const float (&v)[IB][CH * PX], char* buf) {
+#pragma unroll
+        for (int i = 0; i < IB; ++i) {
+            char* d = (dst[i] == 2 * BUF ? lds : buf) + dst[i];
+            if constexpr (CH == 8) {
+                u32x4 h, m, l;
+                split_eight(v[i], h, m, l);
+                u32x4* d4 = reinterpret_cast<u32x4*>(d);
+                d4[0] = h; d4[1] = m; d4[2] = l;
+            } else {
+#pragma unroll
+                for (int p = 0; p < PX; ++p) {
+                    u32x2 h, m, l;
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        unsigned hj, mj, lj;
+                        split_pair(v[i][p * 4 + 2 * j], v[i][p * 4 + 2 * j + 1], hj, mj, lj);
+                        h[j] = hj; m[j] = mj; l[j] = lj;
+                    }
+                    // (an item that does not exist writes all its pixels to the same spare place)
+                    char* dp = d + (dst[i] == 2 * BUF ? 0 : 48 * p);
+                    *reinterpret_cast<u32x2*>(dp) = h;
+                    *reinterpret_cast<u32x2*>(dp + 16) = m;
+                    *reinterpret_cast<u32x2*>(dp + 32) = l;
+                }
+            }
+        }
+    };
+    auto load_a = [&](u32x4 (&a)[MB * 3]) {
+#pragma unroll
+        for (int j = 0; j < MB * 3; ++j) a[j] = wp[j * 64];
+    };
+    auto barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+    const char* const mine = lds + 48 * (grp * NPIX + wn_i * NB * 16 + l16);
+    u32x4 bf[2][3];
+    auto fetch = [&](u32x4 (&f)[3], const char* from) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) f[p] = *reinterpret_cast<const u32x4*>(from + 16 * p);
+    };
+
+    u32x4 a0[MB * 3], a1[MB * 3];
+    load_x(xv[0], 0);
+    load_x(xv[1], 1);
+    load_a(a0);
+    __builtin_amdgcn_sched_barrier(0);
+    write_x(xv[0], lds);
+    load_x(xv[0], 2);
+    __builtin_amdgcn_sched_barrier(0);
+    barrier();
+    fetch(bf[0], mine);
+
+    // One step = 32 channels.  While chunk t is multiplied, chunk t + 1 is split into its three parts (its loads were
+    // issued two steps ago) and written to the other buffer, and the loads of chunk t + 3 are issued.
+    auto step = [&](int t, u32x4 (&a)[MB * 3], u32x4 (&an)[MB * 3], float (&v)[IB][CH * PX]) {
+        if (t + 1 < nchunks) wp += wstep;
+        load_a(an);
+        const char* cur = mine + (t & 1) * BUF;
+        auto block = [&](auto nb_c) {
+            constexpr int nb = decltype(nb_c)::value;
+            if constexpr (nb + 1 < NB) fetch(bf[(nb + 1) & 1], cur + 48 * 16 * (nb + 1));
+            constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};      // small products first
+#pragma unroll
+            for (int q = 0; q < 6; ++q)
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+                    acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        __builtin_bit_cast(bf16x8, a[mb * 3 + PA[q]]), __builtin_bit_cast(bf16x8, bf[nb & 1][PB[q]]), acc[mb][nb], 0, 0, 0);
+        };
+        constexpr int HALF = NB / 2;
+        static_for<0, HALF>(block);
+        __builtin_amdgcn_sched_barrier(0);
+        write_x(v, lds + ((t + 1) & 1) * BUF);
+        static_for<HALF, NB>(block);
+        // the arithmetic of the split runs in the shadow of the matrix instructions
+#pragma unroll
+        for (int i = 0; i < (NB - HALF) * 6 * MB; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        load_x(v, t + 3);
+        __builtin_amdgcn_sched_barrier(0);
+        barrier();
+        fetch(bf[0], mine + ((t + 1) & 1) * BUF);
+    };
+    for (int t = 0;;) {
+        step(t, a0, a1, xv[1]);
+        if (++t == nchunks) break;
+        step(t, a1, a0, xv[0]);
+        if (++t == nchunks) break;
+    }
+
+    // each partial sum is complete: write the block once.  Register i of a 16 x 16 block holds channel 4 grp + i of
+    // pixel l16.  Outputs that are not finite, or so small that parts of their operands may lie below the smallest
+    // bf16, are marked and computed again below.
+    unsigned long long again = 0;
+    static_assert(MB * NB * 4 <= 64, "one mark per output");
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        const int px = (wn_i * NB + nb) * 16 + l16;
+        if (px >= left_px) continue;
+        const int n = n0 + (p0 + px) / g.HW, r = (p0 + px) % g.HW;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            const int k0 = (kb16 + mb) * 16 + 4 * grp;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float v = acc[mb][nb][i], av = __builtin_fabsf(v);
+                if (!(av <= 3.402823466e38f && av >= 1.3e-29f) && av != 0.f) again |= 1ull << ((nb * MB + mb) * 4 + i);
+            }
+            if (g.hwc) {
+                float* yp = y + ((size_t)n * g.HW + r) * g.K + k0;
+                if (g.vec_out && k0 + 3 < g.K) {
+                    *reinterpret_cast<f32x4*>(yp) = acc[mb][nb];
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (k0 + i < g.K) yp[i] = acc[mb][nb][i];
+                }
+            } else {
+                float* yp = y + ((size_t)n * g.Ky + k0) * g.HWy + r;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (k0 + i < g.K) yp[(size_t)i * g.HWy] = acc[mb][nb][i];
+            }
+        }
+    }
+    while (again) {
+        const int bit = __builtin_ctzll(again);
+        again &= again - 1;
+        const int nb = bit / (4 * MB), mb = bit / 4 % MB, i = bit & 3;
+        const int px = (wn_i * NB + nb) * 16 + l16, n = n0 + (p0 + px) / g.HW, r = (p0 + px) % g.HW;
+        const int in = g.stride == 1 ? r : r / g.Q * g.stride * g.Win + r % g.Q * g.stride;
+        const int row = 4 * grp + i, k = (kb16 + mb) * 16 + row;
+        if (k >= g.K) continue;
+        const unsigned short* wk = reinterpret_cast<const unsigned short*>(wt + (size_t)group * g.w_image + (size_t)(kb16 + mb) * 192);
+        float sum = 0.f;
+        for (int c = 0; c < g.C; ++c) {
+            const unsigned short* q = wk + (size_t)(c >> 5) * wstep * 8 + ((c >> 3 & 3) * 16 + row) * 8 + (c & 7);
+            const float wv = bf16_bits_to_float(q[0]) + (bf16_bits_to_float(q[512]) + bf16_bits_to_float(q[1024]));
+            sum = __builtin_fmaf(x[g.hwc ? ((size_t)n * g.HWin + in) * g.C + c : ((size_t)n * g.C + c) * g.HWin + in], wv, sum);
+        }
+        y[g.hwc ? ((size_t)n * g.HW + r) * g.K + k : ((size_t)n * g.Ky + k) * g.HWy + r] = sum;
+    }
+}
+
+template <int MB, int NB, int WM, int WN, int IN>
+hipError_t launch_one(const float* x, const u32x4* wt, float* y, const SplitPointGeom& g, hipStream_t st)
+{
+    auto kern = split_point_kernel<MB, NB, WM, WN, IN>;
+    constexpr size_t shm = 2 * 4 * 16 * NB * WN * 48 + 48;
+    if (shm > 64 * 1024) {
+        const hipError_t e = allow_large_lds((const void*)kern);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kern, dim3(g.nbk * g.nbp * g.groups), dim3(64 * WM * WN), shm, st, x, wt, y, g);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_split_point(const float* x, const void* wt, float* y, const SplitPointGeom& g, hipStream_t st)
+{
+    // what the kernel assumes of its geometry
+    const long long npix = 16LL * g.nb * g.wn, span = (g.HW - 1 + npix - 1) / g.HW + 1;
+    if (g.Kb16 != g.nbk * g.mb * g.wm || (long long)g.nbp * npix < (long long)g.images * g.HW || (long long)g.images * g.HW >= (1LL << 31) - 1024 ||
+        4 * (span < g.images ? span : g.images) * g.C * g.HWin >= (1LL << 31) || g.Kb16 * 16 < g.K ||
+        (long long)g.nbk * g.nbp * g.groups > 0x7fffffffLL)
+        return hipErrorInvalidValue;
+    if (g.in == SPLIT_IN_CHANNELS && (!g.hwc || g.C % 4)) return hipErrorInvalidValue;
+    if (g.in == SPLIT_IN_PIXELS && (g.hwc || g.stride != 1 || (g.images > 1 && g.HW % split_point_pixels(g.in, (int)npix)))) return hipErrorInvalidValue;
+    const u32x4* w = static_cast<const u32x4*>(wt);
+#define IOLB_POINT_CASE(M_, N_, A_, B_)                                                              \
+    if (g.mb == M_ && g.nb == N_ && g.wm == A_ && g.wn == B_) {                                      \
+        if (g.in == SPLIT_IN_PIXELS) return launch_one<M_, N_, A_, B_, SPLIT_IN_PIXELS>(x, w, y, g, st);      \
+        if (g.in == SPLIT_IN_CHANNELS) return launch_one<M_, N_, A_, B_, SPLIT_IN_CHANNELS>(x, w, y, g, st);  \
+        return launch_one<M_, N_, A_, B_, SPLIT_IN_SINGLE>(x, w, y, g, st);                          \
+    }
+    IOLB_SPLIT_POINT_SHAPES(IOLB_POINT_CASE)
+#undef IOLB_POINT_CASE
+    return hipErrorInvalidValue;
+}
+
+}  // namespace iolb
