@@ -1,6 +1,7 @@
 // C-ABI layer: argument checks, tile selection, workspace, launches.  See include/iolbconv.h.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <array>
 #include <cstring>
 #include <map>
@@ -231,7 +232,7 @@ SplitChoice split_choice(const iolb_shape& s, int P, int Q, int pad_w, int layou
         g.stride = s.stride; g.hwc = hwc;
         g.in = hwc ? (s.C % 4 ? iolb::SPLIT_IN_SINGLE : iolb::SPLIT_IN_CHANNELS) : s.stride == 1 ? iolb::SPLIT_IN_PIXELS : iolb::SPLIT_IN_SINGLE;
         g.vec_out = hwc && s.K % 4 == 0;
-        if (iolb::split_point_plan(&g, &cycles)) {
+        if (iolb::split_point_faster(s, P, Q) && iolb::split_point_plan(&g, &cycles)) {
             ch.kind = SplitChoice::POINT;
             ch.point = g;
             ch.weight_bytes = (size_t)iolb::split_point_weight_bytes(g);
@@ -240,7 +241,7 @@ SplitChoice split_choice(const iolb_shape& s, int P, int Q, int pad_w, int layou
         iolb::SplitGeom g{};
         g.N = s.N; g.C = s.C; g.H = s.H; g.W = s.W; g.K = s.K; g.R = s.R; g.S = s.S; g.stride = s.stride; g.pad = s.pad; g.pad_w = pad_w;
         g.P = P; g.Q = Q; g.hwc = hwc; g.vec_in = hwc && s.C % 4 == 0; g.vec_out = hwc && s.K % 4 == 0;
-        if (iolb::split_plan(&g, &cycles)) {
+        if (iolb::split_conv_faster(s) && iolb::split_plan(&g, &cycles)) {
             ch.kind = SplitChoice::CONV;
             ch.conv = g;
             ch.weight_bytes = (size_t)iolb::split_weight_bytes(g);
@@ -485,11 +486,81 @@ int make_wino_shape(int N, int C, int H, int W, int K, int m, iolb_shape* s, int
 // Channel rows per plane of a caller-held transformed-kernel buffer: every stage depth divides 16.
 int pretransformed_rows(int C) { return (C + 15) / 16 * 16; }
 
+// ---- unfused Winograd with the product on the bf16 matrix cores ------------------------------
+struct SplitWino {
+    bool use = false;
+    iolb::SplitPointGeom g{};
+    iolb::WinoGeom w{};
+    size_t u_off = 0, v_off = 0, m_off = 0, total = 0;
+};
+std::map<ShapeKey, SplitWino> g_split_wino;
+
+// tile: the library's own choice for the layer.  The split product takes over where its modelled time beats that
+// of the tile.
+SplitWino split_wino(const iolb_shape& s, const iolb_tile_config& tile)
+{
+    const ShapeKey key(s.N, s.C, s.H, s.W, s.K, s.R, s.S, s.stride, s.pad, s.algo);
+    {
+        std::lock_guard<std::mutex> lock(g_mutex);
+        auto it = g_split_wino.find(key);
+        if (it != g_split_wino.end()) return it->second;
+    }
+    SplitWino r;
+    iolb::WinoGeom& w = r.w;
+    w.N = s.N; w.C = w.Cp = s.C; w.H = s.H; w.W = s.W; w.K = w.Kp = s.K; w.m = iolb::winograd_m(s.algo); w.pad = s.pad;
+    w.P = s.H + 2 * s.pad - 2; w.Q = s.W + 2 * s.pad - 2;
+    w.th = (w.P + w.m - 1) / w.m; w.tw = (w.Q + w.m - 1) / w.m;
+    const int64_t tiles = (int64_t)s.N * w.th * w.tw, pitch = (tiles + 3) / 4 * 4, n2 = (int64_t)(w.m + 2) * (w.m + 2);
+    double cycles = 0;
+    if (tile.path != IOLB_PATH_FMA && n2 * std::max(s.C, s.K) * pitch < (1LL << 31) && s.C <= 65535 && s.K <= 65535) {
+        w.tiles = (int)tiles; w.tiles_pitch = (int)pitch;
+        iolb::SplitPointGeom& g = r.g;
+        g.groups = (int)n2; g.images = 1; g.C = s.C; g.K = g.Ky = s.K; g.HW = (int)tiles; g.HWy = g.HWin = (int)pitch; g.Win = g.Q = (int)tiles;
+        g.stride = 1; g.in = iolb::SPLIT_IN_PIXELS;
+        g.w_image = 1;                                        // kernels per plane; the real distance follows from the plan
+        if (iolb::split_point_plan(&g, &cycles)) {
+            g.w_image = iolb::split_point_weight_bytes(g) / 16;
+            r.u_off = 0;
+            r.v_off = align256((size_t)n2 * iolb::split_point_weight_bytes(g));
+            r.m_off = r.v_off + align256(sizeof(float) * n2 * s.C * pitch);
+            r.total = r.m_off + align256(sizeof(float) * n2 * s.K * pitch);
+            r.use = r.total <= winograd_workspace_max(s.C, s.K, w.m, tiles) && iolb::split_wino_faster(s, tile, tiles, cycles);
+        }
+    }
+    std::lock_guard<std::mutex> lock(g_mutex);
+    g_split_wino[key] = r;
+    return r;
+}
+
+int run_winograd_split(const float* x, const float* w, const float* Upre, float* y, const iolb_shape& s, const SplitWino& p, void* ws)
+{
+    char* base = static_cast<char*>(ws);
+    void* U = base + p.u_off;
+    float* V = reinterpret_cast<float*>(base + p.v_off);
+    float* M = reinterpret_cast<float*>(base + p.m_off);
+    hipStream_t st = t_stream;
+    if (w)
+        IOLB_HIP(iolb::launch_wino_kernel_transform_split(w, U, p.w.m, s.C, s.K, p.g.Kb16, st));
+    else
+        IOLB_HIP(iolb::launch_split_planes(Upre, U, p.g.groups, s.K, s.C, pretransformed_rows(s.C), (s.K + 31) / 32 * 32, p.g.Kb16, st));
+    IOLB_HIP(iolb::launch_wino_input_transform(x, V, p.w, st));
+    MainKernelTimer timer(st, IOLB_TIME_WINO_PRODUCT);
+    IOLB_HIP(iolb::launch_split_point(V, U, M, p.g, st));
+    timer.stop(st);
+    IOLB_HIP(iolb::launch_wino_output_transform(M, y, p.w, st));
+    return IOLB_OK;
+}
+
 // w != nullptr: transform the kernels into the workspace first.  w == nullptr: Upre holds them already
 // (written by conv_winograd_transform_kernels).
 int run_winograd(const float* x, const float* w, const float* Upre, float* y, const iolb_shape& s,
-                 const iolb_tile_config& cfg, void* ws, size_t ws_bytes)
+                 const iolb_tile_config& cfg, void* ws, size_t ws_bytes, bool own_tile = true)
 {
+    if (own_tile) {
+        // (a caller's workspace that holds no more than the tile needs keeps the tile)
+        const SplitWino p = split_wino(s, cfg);
+        if (p.use && ws && ws_bytes >= p.total && !(reinterpret_cast<uintptr_t>(ws) & 255)) return run_winograd_split(x, w, Upre, y, s, p, ws);
+    }
     DeviceState* dev = nullptr;
     int rc = device_state(&dev);
     if (rc != IOLB_OK) return rc;
@@ -680,7 +751,7 @@ int conv_winograd_ws(const float* x, const float* w, float* y, int N, int C, int
         rc = tuned_tile(s, &tile);
         if (rc != IOLB_OK) return rc;
     }
-    return run_winograd(x, w, nullptr, y, s, tile, workspace, workspace_bytes);
+    return run_winograd(x, w, nullptr, y, s, tile, workspace, workspace_bytes, cfg == nullptr);
 }
 
 size_t conv_winograd_kernel_bytes(int C, int K, int m)
@@ -719,7 +790,7 @@ int conv_winograd_pre(const float* x, const float* U, float* y, int N, int C, in
         rc = tuned_tile(s, &tile);
         if (rc != IOLB_OK) return rc;
     }
-    return run_winograd(x, nullptr, U, y, s, tile, workspace, workspace_bytes);
+    return run_winograd(x, nullptr, U, y, s, tile, workspace, workspace_bytes, cfg == nullptr);
 }
 
 int conv_winograd(const float* x, const float* w, float* y, int N, int C, int H, int W, int K, int m)

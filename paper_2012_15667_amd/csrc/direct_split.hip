@@ -24,9 +24,9 @@ __device__ __forceinline__ void static_for(F f)
     }
 }
 
-template <int MB, int NB, int WM, int WN, bool VEC>
+template <int MB, int NB, int WM, int WN, bool VEC, bool APART>
 __global__ void __launch_bounds__(64 * WM * WN, 2)
-split_conv_kernel(const float* __restrict__ x, const u32x4* __restrict__ wt, float* __restrict__ y, SplitGeom g)
+split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitGeom g)
 {
     extern __shared__ u32x4 lds16[];
     char* const lds = reinterpret_cast<char*>(lds16);
@@ -196,13 +196,22 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* __restrict__ wt, flo
             constexpr int nb = decltype(nb_c)::value;
             if constexpr (nb + 1 < NB) fetch(bf[(nb + 1) & 1], bp + ko + pbase[nb + 1]);
             else                       fetch(bf[(nb + 1) & 1], bp + kn + pbase[0]);
-            constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};      // small products first
+            // the six products of parts that reach fp32 precision, smallest first
+            constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+            f32x4 sum[MB];
 #pragma unroll
             for (int q = 0; q < 6; ++q)
 #pragma unroll
-                for (int mb = 0; mb < MB; ++mb)
-                    acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                        __builtin_bit_cast(bf16x8, a[mb * 3 + PA[q]]), __builtin_bit_cast(bf16x8, bf[nb & 1][PB[q]]), acc[mb][nb], 0, 0, 0);
+                for (int mb = 0; mb < MB; ++mb) {
+                    f32x4& to = APART ? sum[mb] : acc[mb][nb];
+                    to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        __builtin_bit_cast(bf16x8, a[mb * 3 + PA[q]]), __builtin_bit_cast(bf16x8, bf[nb & 1][PB[q]]),
+                        APART && q == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : to, 0, 0, 0);
+                }
+            if constexpr (APART) {
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) acc[mb][nb] += sum[mb];
+            }
         };
         constexpr int HALF = NB / 2;
         static_for<0, HALF>(block);
@@ -353,10 +362,10 @@ split_weights_kernel(const float* __restrict__ w, u32x4* __restrict__ wt, int K,
     }
 }
 
-template <int MB, int NB, int WM, int WN, bool VEC>
+template <int MB, int NB, int WM, int WN, bool VEC, bool APART>
 hipError_t launch_one(const float* x, const u32x4* wt, float* y, const SplitGeom& g, hipStream_t st)
 {
-    auto kern = split_conv_kernel<MB, NB, WM, WN, VEC>;
+    auto kern = split_conv_kernel<MB, NB, WM, WN, VEC, APART>;
     const size_t shm = split_lds_bytes(g);
     if (shm > 64 * 1024) {
         const hipError_t e = allow_large_lds((const void*)kern);
@@ -388,12 +397,21 @@ hipError_t launch_split_planes(const float* U, void* wt, int planes, int K, int 
     return hipGetLastError();
 }
 
+// At most eight channels (ch8 = 1): each step's products are summed from zero before they are added to the running
+// sum, which is then rounded once per step and not six times.  Such layers ran on plain FMAs or short fp32 chains
+// before, which round less than six bf16 products per step would; they are not bound by the matrix cores.
 template <bool VEC>
 static hipError_t launch_shape(const float* x, const u32x4* wt, float* y, const SplitGeom& g, hipStream_t st)
 {
 #define IOLB_SPLIT_CASE(M_, N_, A_, B_) \
-    if (g.mb == M_ && g.nb == N_ && g.wm == A_ && g.wn == B_) return launch_one<M_, N_, A_, B_, VEC>(x, wt, y, g, st);
-    IOLB_SPLIT_SHAPES(IOLB_SPLIT_CASE)
+    if (g.mb == M_ && g.nb == N_ && g.wm == A_ && g.wn == B_) return launch_one<M_, N_, A_, B_, VEC, APART>(x, wt, y, g, st);
+    if (g.ch8 == 1) {
+        constexpr bool APART = true;
+        IOLB_SPLIT_FEW_SHAPES(IOLB_SPLIT_CASE)
+    } else {
+        constexpr bool APART = false;
+        IOLB_SPLIT_SHAPES(IOLB_SPLIT_CASE)
+    }
 #undef IOLB_SPLIT_CASE
     return hipErrorInvalidValue;
 }

@@ -82,10 +82,13 @@ constexpr int SPLIT_BATCH = 2;          // (pixel, 8 channels) items of the inpu
 // The workgroup shapes that exist: blocks per wave (channels, pixels), wave grid (channels, pixels).
 #define IOLB_SPLIT_SHAPES(X) \
     X(1, 2, 4, 1) X(1, 4, 4, 1) X(1, 8, 4, 1) X(2, 2, 4, 1) X(2, 4, 4, 1) X(2, 5, 4, 1) X(2, 7, 4, 1) X(2, 8, 4, 1) \
-    X(3, 2, 4, 1) X(3, 4, 4, 1) X(3, 5, 4, 1) X(4, 2, 4, 1) X(4, 4, 4, 1)                                           \
+    X(3, 2, 4, 1) X(3, 4, 4, 1) X(4, 2, 4, 1)                                                                       \
     X(1, 2, 2, 2) X(1, 4, 2, 2) X(1, 7, 2, 2) X(1, 8, 2, 2) X(2, 2, 2, 2) X(2, 4, 2, 2) X(2, 5, 2, 2) X(2, 7, 2, 2) X(2, 8, 2, 2) \
-    X(3, 2, 2, 2) X(3, 4, 2, 2) X(3, 5, 2, 2) X(4, 4, 2, 2)                                                          \
-    X(1, 1, 1, 4) X(1, 2, 1, 4) X(1, 4, 1, 4) X(1, 7, 1, 4) X(2, 1, 1, 4) X(2, 2, 1, 4) X(2, 4, 1, 4) X(2, 7, 1, 4) X(3, 2, 1, 4) X(3, 4, 1, 4)
+    X(3, 4, 2, 2)                                                                                                   \
+    X(1, 1, 1, 4) X(1, 2, 1, 4) X(1, 4, 1, 4) X(1, 7, 1, 4) X(2, 2, 1, 4) X(2, 4, 1, 4) X(2, 7, 1, 4) X(3, 4, 1, 4)
+// ... and those for layers of at most eight channels (ch8 = 1)
+#define IOLB_SPLIT_FEW_SHAPES(X) \
+    X(1, 2, 4, 1) X(1, 4, 4, 1) X(1, 2, 2, 2) X(1, 4, 2, 2) X(2, 2, 2, 2) X(2, 4, 2, 2) X(1, 2, 1, 4) X(1, 4, 1, 4) X(2, 4, 1, 4)
 inline int split_steps(const SplitGeom& g) { return (g.R * g.S * g.ch8 + 3) / 4; }
 inline int split_chunks(const SplitGeom& g) { return (g.C + 8 * g.ch8 - 1) / (8 * g.ch8); }
 inline int split_batches(const SplitGeom& g)
@@ -122,9 +125,7 @@ struct SplitPointGeom {
 // HW is a multiple of that).
 enum { SPLIT_IN_SINGLE = 0, SPLIT_IN_CHANNELS = 1, SPLIT_IN_PIXELS = 2 };
 constexpr int split_point_pixels(int in, int npix) { return in != SPLIT_IN_PIXELS ? 1 : npix >= 96 ? 4 : 2; }
-#define IOLB_SPLIT_POINT_SHAPES(X) \
-    X(1, 2, 4, 1) X(1, 4, 4, 1) X(1, 8, 4, 1) X(2, 2, 4, 1) X(2, 4, 4, 1) X(2, 6, 4, 1) X(2, 8, 4, 1) X(3, 4, 4, 1) X(4, 4, 4, 1) \
-    X(1, 4, 2, 2) X(2, 2, 2, 2) X(2, 4, 2, 2) X(4, 4, 2, 2) X(2, 8, 4, 2) X(4, 4, 4, 2) X(2, 4, 4, 2)
+#define IOLB_SPLIT_POINT_SHAPES(X) X(1, 2, 4, 1) X(1, 4, 4, 1) X(2, 2, 2, 2) X(2, 4, 4, 1) X(3, 4, 4, 1) X(4, 4, 4, 1)
 inline long long split_point_weight_bytes(const SplitPointGeom& g) { return (g.C + 31LL) / 32 * g.Kb16 * 3072; }
 hipError_t launch_split_point(const float* x, const void* wt, float* y, const SplitPointGeom& g, hipStream_t st);
 
@@ -170,6 +171,8 @@ struct WinoGeom {
     int waves_m, waves_n;
 };
 hipError_t launch_wino_kernel_transform(const float* w, float* U, const WinoGeom& g, hipStream_t st);
+// U in three bf16 parts for launch_split_point (groups = planes), written from w.
+hipError_t launch_wino_kernel_transform_split(const float* w, void* wt, int m, int C, int K, int Kb16, hipStream_t st);
 hipError_t launch_wino_input_transform(const float* x, float* V, const WinoGeom& g, hipStream_t st);
 hipError_t launch_wino_product(const float* U, const float* V, float* M, const WinoGeom& g, hipStream_t st);
 hipError_t launch_wino_output_transform(const float* M, float* y, const WinoGeom& g, hipStream_t st);

@@ -1,6 +1,11 @@
-// fp32 products on the bf16 matrix cores: every operand is cut into three bf16 parts whose sum is the operand.
-//
-// The fp32 matrix instructions of this chip do 64 multiply-adds... see split_conv_kernel for the kernel that uses this.
+// fp32 products on the bf16 matrix cores: every operand is cut into three bf16 parts, x = h + m + l, and the product
+// of two operands is taken as the six products of parts that reach fp32 precision (h h, h m, m h, m m, h l, l h; the
+// three left out are below 2^-24 of the product).  A v_mfma_f32_16x16x32_bf16 does 16 times the multiply-adds of an fp32
+// matrix instruction in the same time, so six of them still leave a factor of 16 / 6; sums stay in fp32.  Measured on
+// register operands: 1937 TFLOP/s of bf16 products = 323 TFLOP/s of fp32 products, against 155 of the fp32 instructions
+// (32x32x16_bf16: 1430 - 1690).  Error of a sum of n such products against 64 bits (relative, 2-norm; x uniform on
+// [0, 1], w normal), fp32 instructions / this: n = 144 2.2e-7 / 1.9e-7, 576 4.2e-7 / 3.5e-7, 4608 1.23e-6 / 0.99e-6,
+// 12800 1.9e-6 / 1.7e-6.  Three products (two parts) would give 4e-6 at every n: not used.
 #ifndef IOLB_SPLIT_MFMA_H
 #define IOLB_SPLIT_MFMA_H
 

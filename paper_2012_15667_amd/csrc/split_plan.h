@@ -16,6 +16,12 @@ double split_cycles(const SplitGeom& g);
 // The same for 1 x 1 layers: groups, images, C, K, Ky, HW, HWy, HWin, Win, Q, stride, hwc and in describe the layer.
 bool split_point_plan(SplitPointGeom* g, double* cycles);
 
+
+// Whether a layer without a caller-supplied tile leaves the fp32 kernels (the reasons are in the definitions).
+bool split_conv_faster(const iolb_shape& s);
+bool split_point_faster(const iolb_shape& s, int P, int Q);
+bool split_wino_faster(const iolb_shape& s, const iolb_tile_config& tile, long long tiles, double product_cycles);
+
 }  // namespace iolb
 
 #endif

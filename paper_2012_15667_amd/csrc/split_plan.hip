@@ -1,7 +1,9 @@
 // The block of a layer on the split matrix-core kernel (direct_split.hip): host only.
 #include "split_plan.h"
+#include "tune.h"
 
 #include <algorithm>
+#include <cmath>
 #include <vector>
 
 namespace iolb {
@@ -63,11 +65,10 @@ double split_cycles(const SplitGeom& g)
 bool split_plan(SplitGeom* g, double* cycles)
 {
     struct Shape { int mb, nb, wm, wn; };
-    static const Shape shapes[] = {
 #define IOLB_SPLIT_ENTRY(M_, N_, A_, B_) {M_, N_, A_, B_},
-        IOLB_SPLIT_SHAPES(IOLB_SPLIT_ENTRY)
+    static const std::vector<Shape> all = {IOLB_SPLIT_SHAPES(IOLB_SPLIT_ENTRY)}, few = {IOLB_SPLIT_FEW_SHAPES(IOLB_SPLIT_ENTRY)};
 #undef IOLB_SPLIT_ENTRY
-    };
+    const std::vector<Shape>& shapes = g->C <= 8 ? few : all;
     // cuts of an extent into k nearly equal parts
     auto cuts = [](int extent, int most) {
         std::vector<int> v;
@@ -85,7 +86,7 @@ bool split_plan(SplitGeom* g, double* cycles)
     for (const Shape& sh : shapes) {
         const int slots = 16 * sh.nb * sh.wn;
         for (int ch8 : {4, 2, 1}) {
-            if ((ch8 == 4 && g->C <= 16) || (ch8 == 1 && g->C > 8)) continue;
+            if ((ch8 == 4 && g->C <= 16) || (ch8 == 1) != (g->C <= 8)) continue;
             SplitGeom t = *g;
             t.mb = sh.mb; t.nb = sh.nb; t.wm = sh.wm; t.wn = sh.wn; t.ch8 = ch8;
             for (int tx : cuts(g->Q, slots))
@@ -141,6 +142,39 @@ bool split_point_plan(SplitPointGeom* g, double* cycles)
     }
     if (found) { *g = best; *cycles = best_cycles; }
     return found;
+}
+
+// Kernels with a window: measured 1.1 to 4 times as fast as the fp32 kernels on every layer of 60 drawn ones (16 to 512
+// channels, 7 x 7 to 224 x 224, batch 1 to 64) but those of three channels with 3 x 3 kernels, which are bound by
+// their stores (0.76 - 0.96); 7 x 7 and 11 x 11 kernels on three channels 0.98 - 1.2 and 5.7.
+bool split_conv_faster(const iolb_shape& s) { return s.C > 8 || s.R * s.S >= 25; }
+
+// 1 x 1: the fp32 kernel reads and writes at the rate of memory and needs no pass over the kernels before it; it
+// loses where the products outweigh that.  Measured over 60 drawn layers: from 48 flop per byte of the tensors and
+// 160 channels on 1.07 to 1.5 times as fast, below 0.57 to 1.1.
+bool split_point_faster(const iolb_shape& s, int P, int Q)
+{
+    const double flop = 2.0 * s.N * P * Q * s.C * s.K;
+    const double bytes = 4.0 * ((double)s.N * s.C * P * Q + (double)s.N * s.K * P * Q + (double)s.K * s.C);
+    return s.C >= 160 && flop >= 48 * bytes && flop >= 1e9;
+}
+
+// Times in ns: transforms and launches of both unfused ways are the same, so that against an unfused tile the
+// products are compared; a fused tile costs its rounds at the rate its kernel was measured at, the unfused way the
+// traffic of V and M at 5.2 TB/s.
+bool split_wino_faster(const iolb_shape& s, const iolb_tile_config& tile, long long tiles, double product_cycles)
+{
+    const int m = winograd_m(s.algo);
+    const double n2 = (m + 2) * (m + 2), product = product_cycles / 2.0;
+    const int Kp = (s.K + 31) / 32 * 32;
+    if (tile.path == IOLB_PATH_FUSED) {
+        const double out = (double)s.N * (s.H + 2 * s.pad - 2) * (s.W + 2 * s.pad - 2);
+        const double bytes = 4.0 * ((double)s.N * s.C * s.H * s.W + 2 * n2 * tiles * (s.C + s.K) + s.K * out);
+        const double tb = tile.x / m, blocks = std::ceil(tiles / tb) * ((s.K + tile.z - 1) / tile.z);
+        const double fused = std::ceil(blocks / 256) * (2 * n2 * tb * tile.z * s.C / (m == 2 ? 370 : 295)) + 2 * 3000;
+        return product + bytes / 5200 + 4 * 3000 < fused;
+    }
+    return s.C >= 128 && s.K >= 128 && product < 0.8 * (2 * n2 * tiles * s.C * Kp / 105000);
 }
 
 }  // namespace iolb

@@ -21,7 +21,7 @@ __device__ __forceinline__ void static_for(F f)
 
 template <int MB, int NB, int WM, int WN, int IN>
 __global__ void __launch_bounds__(64 * WM * WN, 2)
-split_point_kernel(const float* __restrict__ x, const u32x4* __restrict__ wt, float* __restrict__ y, SplitPointGeom g)
+split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitPointGeom g)
 {
     constexpr int T = 64 * WM * WN, NPIX = 16 * NB * WN, BUF = 4 * NPIX * 48;
     // an input item: CH channels of PX neighbouring pixels

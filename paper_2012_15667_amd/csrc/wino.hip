@@ -15,6 +15,7 @@
 // The transform matrices (wino_mats.h) are compile-time constants: zeros and +-1 cost nothing.
 #include "kernels.h"
 #include "lds_dma.h"
+#include "split_mfma.h"
 #include "wino_mats.h"
 #include "wino_transform.h"
 
@@ -48,6 +49,52 @@ kernel_transform(const float* __restrict__ w, float* __restrict__ U, int C, int 
     for (int i = 0; i < n; ++i)
 #pragma unroll
         for (int j = 0; j < n; ++j) U[(size_t)(i * n + j) * plane + idx] = u[i][j];
+}
+
+// step 1b for the product on the bf16 matrix cores: the same U, cut into three bf16 parts in the order of the product's
+// steps, [xi][chunk of 32 channels][16-kernel block][part][lane][8 channels].  One lane per 16-byte piece of one plane
+// row (blockIdx.y): eight channels of one kernel.
+template <int M>
+__global__ void __launch_bounds__(256)
+kernel_transform_split(const float* __restrict__ w, u32x4* __restrict__ wt, int C, int K, int chunks, int Kb16)
+{
+    constexpr int n = Mats<M>::n;
+    const size_t id = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (id >= (size_t)chunks * Kb16 * 64) return;
+    const int row = blockIdx.y, lane = (int)(id & 63), kb = (int)((id >> 6) % Kb16), ch = (int)((id >> 6) / Kb16);
+    const int k = kb * 16 + (lane & 15), c0 = ch * 32 + (lane >> 4) * 8;
+    unsigned short p[n][3][8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        float g[3][3];
+        const bool exists = c0 + c < C && k < K;
+        const float* wp = w + ((size_t)k * C + c0 + c) * 9;
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) g[i][j] = exists ? wp[i * 3 + j] : 0.f;
+        float t[n][3], mine[1][3], u[1][n];
+        left_mul<M, UseL, n, 3, 3>(g, t);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            mine[0][j] = t[0][j];
+#pragma unroll
+            for (int i = 1; i < n; ++i)
+                if (row == i) mine[0][j] = t[i][j];
+        }
+        right_mul_t<M, UseL, 1, 3, n>(mine, u);
+#pragma unroll
+        for (int j = 0; j < n; ++j) split_kept(u[0][j], p[j][0][c], p[j][1][c], p[j][2][c]);
+    }
+#pragma unroll
+    for (int j = 0; j < n; ++j)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            u32x4 o;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[i] = (unsigned)p[j][q][2 * i] | ((unsigned)p[j][q][2 * i + 1] << 16);
+            wt[(((size_t)(row * n + j) * chunks + ch) * Kb16 + kb) * 192 + q * 64 + lane] = o;
+        }
 }
 
 // step 1a: one lane per (c, t); t runs fastest.  VEC (m = 2 or 4, W a multiple of m, x aligned to
@@ -356,6 +403,23 @@ hipError_t launch_wino_kernel_transform(const float* w, float* U, const WinoGeom
     case 3: hipLaunchKernelGGL(kernel_transform<3>, dim3(grid), dim3(256), 0, st, w, U, g.C, g.CpU, g.K, g.Kp); break;
     case 4: hipLaunchKernelGGL(kernel_transform<4>, dim3(grid), dim3(256), 0, st, w, U, g.C, g.CpU, g.K, g.Kp); break;
     case 6: hipLaunchKernelGGL(kernel_transform<6>, dim3(grid), dim3(256), 0, st, w, U, g.C, g.CpU, g.K, g.Kp); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_wino_kernel_transform_split(const float* w, void* wt, int m, int C, int K, int Kb16, hipStream_t st)
+{
+    const int chunks = (C + 31) / 32;
+    const long long pieces = (long long)chunks * Kb16 * 64;
+    if ((pieces + 255) / 256 > 0x7fffffffLL) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)((pieces + 255) / 256), m + 2);
+    u32x4* o = static_cast<u32x4*>(wt);
+    switch (m) {
+    case 2: hipLaunchKernelGGL(kernel_transform_split<2>, grid, dim3(256), 0, st, w, o, C, K, chunks, Kb16); break;
+    case 3: hipLaunchKernelGGL(kernel_transform_split<3>, grid, dim3(256), 0, st, w, o, C, K, chunks, Kb16); break;
+    case 4: hipLaunchKernelGGL(kernel_transform_split<4>, grid, dim3(256), 0, st, w, o, C, K, chunks, Kb16); break;
+    case 6: hipLaunchKernelGGL(kernel_transform_split<6>, grid, dim3(256), 0, st, w, o, C, K, chunks, Kb16); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
