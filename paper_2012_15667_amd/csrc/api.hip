@@ -512,7 +512,7 @@ SplitWino split_wino(const iolb_shape& s, const iolb_tile_config& tile)
     w.th = (w.P + w.m - 1) / w.m; w.tw = (w.Q + w.m - 1) / w.m;
     const int64_t tiles = (int64_t)s.N * w.th * w.tw, pitch = (tiles + 3) / 4 * 4, n2 = (int64_t)(w.m + 2) * (w.m + 2);
     double cycles = 0;
-    if (tile.path != IOLB_PATH_FMA && n2 * std::max(s.C, s.K) * pitch < (1LL << 31) && s.C <= 65535 && s.K <= 65535) {
+    if (tile.path != IOLB_PATH_FMA && n2 * std::max(s.C, s.K) * pitch < (1LL << 31) && s.C <= 32768 && s.K <= 65535) {
         w.tiles = (int)tiles; w.tiles_pitch = (int)pitch;
         iolb::SplitPointGeom& g = r.g;
         g.groups = (int)n2; g.images = 1; g.C = s.C; g.K = g.Ky = s.K; g.HW = (int)tiles; g.HWy = g.HWin = (int)pitch; g.Win = g.Q = (int)tiles;
@@ -539,11 +539,7 @@ int run_winograd_split(const float* x, const float* w, const float* Upre, float*
     float* V = reinterpret_cast<float*>(base + p.v_off);
     float* M = reinterpret_cast<float*>(base + p.m_off);
     hipStream_t st = t_stream;
-    if (w)
-        IOLB_HIP(iolb::launch_wino_kernel_transform_split(w, U, p.w.m, s.C, s.K, p.g.Kb16, st));
-    else
-        IOLB_HIP(iolb::launch_split_planes(Upre, U, p.g.groups, s.K, s.C, pretransformed_rows(s.C), (s.K + 31) / 32 * 32, p.g.Kb16, st));
-    IOLB_HIP(iolb::launch_wino_input_transform(x, V, p.w, st));
+    IOLB_HIP(iolb::launch_wino_transforms(x, V, p.w, w ? w : Upre, U, w ? iolb::WINO_KERNELS_SPLIT : iolb::WINO_KERNELS_GIVEN, p.g.Kb16, st));
     MainKernelTimer timer(st, IOLB_TIME_WINO_PRODUCT);
     IOLB_HIP(iolb::launch_split_point(V, U, M, p.g, st));
     timer.stop(st);
@@ -589,18 +585,17 @@ int run_winograd(const float* x, const float* w, const float* Upre, float* y, co
         timer.stop(st);
         return IOLB_OK;
     }
-    if (w) {
-        IOLB_HIP(iolb::launch_wino_kernel_transform(w, U, g, st));
-    } else {
+    if (!w) {
         g.CpU = pretransformed_rows(s.C);
         Uuse = Upre;
     }
     if (fused) {
+        if (w) IOLB_HIP(iolb::launch_wino_kernel_transform(w, U, g, st));
         IOLB_HIP(iolb::launch_wino_fused_relayout(Uuse, V, g, st));
         IOLB_HIP(iolb::launch_wino_fused(x, V, y, g, st));
         return IOLB_OK;
     }
-    IOLB_HIP(iolb::launch_wino_input_transform(x, V, g, st));
+    IOLB_HIP(iolb::launch_wino_transforms(x, V, g, w, U, w ? iolb::WINO_KERNELS_PLAIN : iolb::WINO_KERNELS_NONE, 0, st));
     MainKernelTimer timer(st, IOLB_TIME_WINO_PRODUCT);
     IOLB_HIP(iolb::launch_wino_product(Uuse, V, M, g, st));
     timer.stop(st);

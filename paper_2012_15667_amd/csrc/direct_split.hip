@@ -306,31 +306,6 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
     }
 }
 
-// Transformed kernels U[plane][rows][cols] (channel rows, kernel columns) -> the operands of the product's steps,
-// [plane][chunk of 32][16-channel block][part][lane][8 bf16].
-__global__ void __launch_bounds__(256)
-split_planes_kernel(const float* __restrict__ U, u32x4* __restrict__ wt, int K, int C, int rows, int cols, int chunks, int Kb16, long long pieces)
-{
-    const long long id = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (id >= pieces) return;
-    const int lane = (int)(id & 63), kb = (int)((id >> 6) % Kb16), t = (int)((id >> 6) / Kb16);
-    const int plane = t / chunks, k = kb * 16 + (lane & 15), c0 = (t % chunks) * 32 + (lane >> 4) * 8;
-    unsigned short p[3][8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        float v = 0.f;
-        if (k < K && c0 + j < C) v = U[((size_t)plane * rows + c0 + j) * cols + k];
-        split_kept(v, p[0][j], p[1][j], p[2][j]);
-    }
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        u32x4 o;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) o[j] = (unsigned)p[q][2 * j] | ((unsigned)p[q][2 * j + 1] << 16);
-        wt[((size_t)t * Kb16 + kb) * 192 + q * 64 + lane] = o;
-    }
-}
-
 // w[K][C][R][S] -> the operands of the matrix steps, [chunk][step][16-channel block][part][lane][8 bf16].  One
 // thread per 16-byte piece.
 __global__ void __launch_bounds__(256)
@@ -384,16 +359,6 @@ hipError_t launch_split_weights(const float* w, void* wt, int K, int C, int R, i
     if ((pieces + 255) / 256 > 0x7fffffffLL) return hipErrorInvalidValue;
     hipLaunchKernelGGL(split_weights_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st, w, (u32x4*)wt, K, C, R, S, ch8, steps,
                        Kb16, pieces, transposed ? 1 : 0);
-    return hipGetLastError();
-}
-
-hipError_t launch_split_planes(const float* U, void* wt, int planes, int K, int C, int rows, int cols, int Kb16, hipStream_t st)
-{
-    const int chunks = (C + 31) / 32;
-    const long long pieces = (long long)planes * chunks * Kb16 * 64;
-    if ((pieces + 255) / 256 > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(split_planes_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st, U, (u32x4*)wt, K, C, rows, cols, chunks,
-                       Kb16, pieces);
     return hipGetLastError();
 }
 

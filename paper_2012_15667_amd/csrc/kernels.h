@@ -102,10 +102,8 @@ inline long long split_lds_bytes(const SplitGeom& g)
     return (long long)g.nbuf * g.ch8 * g.b * g.yh * g.rowb + 4 * ((4 * split_steps(g) + 1) & ~1) + 8LL * g.ch8 * g.halo;
 }
 inline long long split_weight_bytes(const SplitGeom& g) { return (long long)split_chunks(g) * split_steps(g) * g.Kb16 * 3072; }
-// Kernels in three parts in the order of the matrix steps, written from w[K][C][R][S] (transposed: w[K][C][S][R]), or
-// for 1 x 1 products from planes U[plane][rows][cols] of transformed kernels (ch8 = 4).
+// Kernels in three parts in the order of the matrix steps, written from w[K][C][R][S] (transposed: w[K][C][S][R]).
 hipError_t launch_split_weights(const float* w, void* wt, int K, int C, int R, int S, int ch8, int Kb16, bool transposed, hipStream_t st);
-hipError_t launch_split_planes(const float* U, void* wt, int planes, int K, int C, int rows, int cols, int Kb16, hipStream_t st);
 hipError_t launch_split_conv(const float* x, const void* wt, float* y, const SplitGeom& g, hipStream_t st);
 
 // 1 x 1 layers and the Winograd product on the same matrix cores (split_point.hip): per group of images that share
@@ -171,9 +169,11 @@ struct WinoGeom {
     int waves_m, waves_n;
 };
 hipError_t launch_wino_kernel_transform(const float* w, float* U, const WinoGeom& g, hipStream_t st);
-// U in three bf16 parts for launch_split_point (groups = planes), written from w.
-hipError_t launch_wino_kernel_transform_split(const float* w, void* wt, int m, int C, int K, int Kb16, hipStream_t st);
-hipError_t launch_wino_input_transform(const float* x, float* V, const WinoGeom& g, hipStream_t st);
+// Input transform of x into V and, in the same launch, the kernels of the product: NONE (U is there already), PLAIN
+// (U[xi][CpU][Kp] from w), or three bf16 parts for launch_split_point (groups = planes, Kb16 16-kernel blocks) from w
+// (SPLIT) or from a caller's U[xi][C rounded up to 16][K rounded up to 32] in w's place (GIVEN).
+enum { WINO_KERNELS_NONE, WINO_KERNELS_PLAIN, WINO_KERNELS_SPLIT, WINO_KERNELS_GIVEN };
+hipError_t launch_wino_transforms(const float* x, float* V, const WinoGeom& g, const float* w, void* U, int kind, int Kb16, hipStream_t st);
 hipError_t launch_wino_product(const float* U, const float* V, float* M, const WinoGeom& g, hipStream_t st);
 hipError_t launch_wino_output_transform(const float* M, float* y, const WinoGeom& g, hipStream_t st);
 // All four steps in one kernel, for C <= 4 with C * (m+2)^2 <= 128 (wino_fused.hip).  Its kernel-side

@@ -28,11 +28,10 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 // step 1b: one lane per (c, k); k runs fastest so the writes of a wave are contiguous.  U has Cp rows of Kp
 // columns per plane: rows [C, Cp) and columns [K, Kp) are zero.
 template <int M>
-__global__ void __launch_bounds__(256)
-kernel_transform(const float* __restrict__ w, float* __restrict__ U, int C, int Cp, int K, int Kp)
+__device__ __forceinline__ void kernel_transform_block(const float* __restrict__ w, float* __restrict__ U, int C, int Cp, int K, int Kp, size_t block)
 {
     constexpr int n = Mats<M>::n;
-    const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
+    const size_t idx = block * 256 + threadIdx.x;
     if (idx >= (size_t)Cp * Kp) return;
     const int k = idx % Kp, c = idx / Kp;
     float g[3][3];
@@ -50,51 +49,87 @@ kernel_transform(const float* __restrict__ w, float* __restrict__ U, int C, int 
 #pragma unroll
         for (int j = 0; j < n; ++j) U[(size_t)(i * n + j) * plane + idx] = u[i][j];
 }
+template <int M>
+__global__ void __launch_bounds__(256)
+kernel_transform(const float* __restrict__ w, float* __restrict__ U, int C, int Cp, int K, int Kp)
+{
+    kernel_transform_block<M>(w, U, C, Cp, K, Kp, blockIdx.x);
+}
 
 // step 1b for the product on the bf16 matrix cores: the same U, cut into three bf16 parts in the order of the product's
 // steps, [xi][chunk of 32 channels][16-kernel block][part][lane][8 channels].  One lane per 16-byte piece of one plane
-// row (blockIdx.y): eight channels of one kernel.
+// row: eight channels of one kernel.
 template <int M>
-__global__ void __launch_bounds__(256)
-kernel_transform_split(const float* __restrict__ w, u32x4* __restrict__ wt, int C, int K, int chunks, int Kb16)
+__device__ __forceinline__ void kernel_transform_split_block(const float* __restrict__ w, u32x4* __restrict__ wt, int C, int K, int chunks, int Kb16,
+                                                             int block, int row)
 {
     constexpr int n = Mats<M>::n;
-    const size_t id = (size_t)blockIdx.x * 256 + threadIdx.x;
+    const size_t id = (size_t)block * 256 + threadIdx.x;
     if (id >= (size_t)chunks * Kb16 * 64) return;
-    const int row = blockIdx.y, lane = (int)(id & 63), kb = (int)((id >> 6) % Kb16), ch = (int)((id >> 6) / Kb16);
+    const int lane = (int)(id & 63), kb = (int)((id >> 6) % Kb16), ch = (int)((id >> 6) / Kb16);
     const int k = kb * 16 + (lane & 15), c0 = ch * 32 + (lane >> 4) * 8;
-    unsigned short p[n][3][8];
+    float mine[8][3];                                       // this row of L g, for each channel
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
-        float g[3][3];
+        float g[3][3], t[n][3];
         const bool exists = c0 + c < C && k < K;
         const float* wp = w + ((size_t)k * C + c0 + c) * 9;
 #pragma unroll
         for (int i = 0; i < 3; ++i)
 #pragma unroll
             for (int j = 0; j < 3; ++j) g[i][j] = exists ? wp[i * 3 + j] : 0.f;
-        float t[n][3], mine[1][3], u[1][n];
         left_mul<M, UseL, n, 3, 3>(g, t);
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
-            mine[0][j] = t[0][j];
+            mine[c][j] = t[0][j];
 #pragma unroll
             for (int i = 1; i < n; ++i)
-                if (row == i) mine[0][j] = t[i][j];
+                if (row == i) mine[c][j] = t[i][j];
         }
-        right_mul_t<M, UseL, 1, 3, n>(mine, u);
-#pragma unroll
-        for (int j = 0; j < n; ++j) split_kept(u[0][j], p[j][0][c], p[j][1][c], p[j][2][c]);
     }
+    static_for<n>([&](auto j) {
+        unsigned short p[3][8];
 #pragma unroll
-    for (int j = 0; j < n; ++j)
+        for (int c = 0; c < 8; ++c) {
+            float u = 0.f;
+            bool first = true;
+            static_for<3>([&](auto b) { accumulate<M, UseL, decltype(j)::value, decltype(b)::value>(u, first, mine[c][b]); });
+            split_kept(u, p[0][c], p[1][c], p[2][c]);
+        }
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
             u32x4 o;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) o[i] = (unsigned)p[j][q][2 * i] | ((unsigned)p[j][q][2 * i + 1] << 16);
+            for (int i = 0; i < 4; ++i) o[i] = (unsigned)p[q][2 * i] | ((unsigned)p[q][2 * i + 1] << 16);
             wt[(((size_t)(row * n + j) * chunks + ch) * Kb16 + kb) * 192 + q * 64 + lane] = o;
         }
+    });
+}
+
+// Transformed kernels U[plane][rows][cols] (channel rows, kernel columns) -> the same operands.
+__device__ __forceinline__ void split_planes_block(const float* __restrict__ U, u32x4* __restrict__ wt, int K, int C, int rows, int cols, int chunks,
+                                                   int Kb16, int block)
+{
+    const long long per_plane = (long long)chunks * Kb16 * 64;
+    const int blocks_per_plane = (int)((per_plane + 255) / 256), plane = block / blocks_per_plane;
+    const long long in = (long long)(block % blocks_per_plane) * 256 + threadIdx.x;
+    if (in >= per_plane) return;
+    const int lane = (int)(in & 63), kb = (int)((in >> 6) % Kb16), ch = (int)((in >> 6) / Kb16);
+    const int k = kb * 16 + (lane & 15), c0 = ch * 32 + (lane >> 4) * 8;
+    unsigned short p[3][8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        float v = 0.f;
+        if (k < K && c0 + j < C) v = U[((size_t)plane * rows + c0 + j) * cols + k];
+        split_kept(v, p[0][j], p[1][j], p[2][j]);
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        u32x4 o;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[j] = (unsigned)p[q][2 * j] | ((unsigned)p[q][2 * j + 1] << 16);
+        wt[(((size_t)plane * chunks + ch) * Kb16 + kb) * 192 + q * 64 + lane] = o;
+    }
 }
 
 // step 1a: one lane per (c, t); t runs fastest.  VEC (m = 2 or 4, W a multiple of m, x aligned to
@@ -103,12 +138,9 @@ kernel_transform_split(const float* __restrict__ w, u32x4* __restrict__ wt, int 
 // m + 2 strided 4-byte loads per row by one wide one; only the lanes at a wave boundary load their border
 // column themselves.
 template <int M, bool VEC>
-__global__ void __launch_bounds__(256)
-input_transform(const float* __restrict__ x, float* __restrict__ V, WinoGeom g)
+__device__ __forceinline__ void input_transform_block(const float* __restrict__ x, float* __restrict__ V, const WinoGeom& g, int t, int c)
 {
     constexpr int n = Mats<M>::n;
-    const int t = blockIdx.x * 256 + threadIdx.x;
-    const int c = blockIdx.y;
     if (t >= g.tiles) return;
     const int tj = t % g.tw, ti = (t / g.tw) % g.th, img = t / (g.tw * g.th);
     const int h0 = ti * M - g.pad, w0 = tj * M - g.pad;
@@ -185,6 +217,30 @@ input_transform(const float* __restrict__ x, float* __restrict__ V, WinoGeom g)
     for (int i = 0; i < n; ++i)
 #pragma unroll
         for (int j = 0; j < n; ++j) vp[(size_t)(i * n + j) * plane] = v[i][j];
+}
+
+// Steps 1a and 1b in one launch: they do not depend on each other, and on a small layer a launch of its own costs as
+// much as the work.  The first `kernel_blocks` blocks transform kernels, or cut a caller's transformed ones into parts;
+// the others transform inputs, `across` blocks of 256 sub-domains per channel.
+enum { KERNELS_PLAIN, KERNELS_SPLIT, KERNELS_GIVEN };
+template <int M, bool VEC, int KERNELS>
+__global__ void __launch_bounds__(256)
+transforms(const float* __restrict__ x, float* __restrict__ V, WinoGeom g, const float* __restrict__ w, void* __restrict__ U, int chunks, int Kb16,
+           int kernel_blocks, int across)
+{
+    int block = blockIdx.x;
+    if (block >= kernel_blocks) {
+        block -= kernel_blocks;
+        const int c = block / across;
+        input_transform_block<M, VEC>(x, V, g, (block - c * across) * 256 + threadIdx.x, c);
+        return;
+    }
+    if constexpr (KERNELS == KERNELS_PLAIN)
+        kernel_transform_block<M>(w, static_cast<float*>(U), g.C, g.CpU, g.K, g.Kp, block);
+    else if constexpr (KERNELS == KERNELS_SPLIT)
+        kernel_transform_split_block<M>(w, static_cast<u32x4*>(U), g.C, g.K, chunks, Kb16, block / Mats<M>::n, block % Mats<M>::n);
+    else
+        split_planes_block(w, static_cast<u32x4*>(U), g.K, g.C, (g.C + 15) / 16 * 16, (g.K + 31) / 32 * 32, chunks, Kb16, block);
 }
 
 // step 4: one lane per (k, t); t runs fastest.  VEC (m = 2 or 4, W a multiple of m, y aligned to 4m
@@ -408,42 +464,48 @@ hipError_t launch_wino_kernel_transform(const float* w, float* U, const WinoGeom
     return hipGetLastError();
 }
 
-hipError_t launch_wino_kernel_transform_split(const float* w, void* wt, int m, int C, int K, int Kb16, hipStream_t st)
+namespace {
+
+template <int M>
+hipError_t launch_transforms(const float* x, float* V, const WinoGeom& g, const float* w, void* U, int kind, int Kb16, hipStream_t st)
 {
-    const int chunks = (C + 31) / 32;
-    const long long pieces = (long long)chunks * Kb16 * 64;
-    if ((pieces + 255) / 256 > 0x7fffffffLL) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)((pieces + 255) / 256), m + 2);
-    u32x4* o = static_cast<u32x4*>(wt);
-    switch (m) {
-    case 2: hipLaunchKernelGGL(kernel_transform_split<2>, grid, dim3(256), 0, st, w, o, C, K, chunks, Kb16); break;
-    case 3: hipLaunchKernelGGL(kernel_transform_split<3>, grid, dim3(256), 0, st, w, o, C, K, chunks, Kb16); break;
-    case 4: hipLaunchKernelGGL(kernel_transform_split<4>, grid, dim3(256), 0, st, w, o, C, K, chunks, Kb16); break;
-    case 6: hipLaunchKernelGGL(kernel_transform_split<6>, grid, dim3(256), 0, st, w, o, C, K, chunks, Kb16); break;
-    default: return hipErrorInvalidValue;
+    if (g.Cp > 65535) return hipErrorInvalidValue;
+    constexpr int n = Mats<M>::n;
+    const int chunks = (g.C + 31) / 32;
+    const long long pieces = ((long long)chunks * Kb16 * 64 + 255) / 256;
+    const long long blocks = kind == WINO_KERNELS_PLAIN ? ((long long)g.CpU * g.Kp + 255) / 256
+                             : kind == WINO_KERNELS_SPLIT ? pieces * n : kind == WINO_KERNELS_GIVEN ? pieces * n * n : 0;
+    const int across = (g.tiles + 255) / 256;
+    const long long total = blocks + (long long)across * g.Cp;
+    if (total > 0x7fffffffLL) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)total);
+    bool vec = false;
+    if constexpr (M == 2 || M == 4) vec = g.pad == 1 && g.W % M == 0 && (reinterpret_cast<uintptr_t>(x) & (4 * M - 1)) == 0;
+#define IOLB_CASE(KIND_, NAME_)                                                                                               \
+    if (kind == KIND_) {                                                                                                      \
+        if constexpr (M == 2 || M == 4)                                                                                       \
+            if (vec) hipLaunchKernelGGL((transforms<M, true, NAME_>), grid, dim3(256), 0, st, x, V, g, w, U, chunks, Kb16, (int)blocks, across); \
+        if (!vec) hipLaunchKernelGGL((transforms<M, false, NAME_>), grid, dim3(256), 0, st, x, V, g, w, U, chunks, Kb16, (int)blocks, across);   \
     }
+    IOLB_CASE(WINO_KERNELS_PLAIN, KERNELS_PLAIN)
+    IOLB_CASE(WINO_KERNELS_NONE, KERNELS_PLAIN)
+    IOLB_CASE(WINO_KERNELS_SPLIT, KERNELS_SPLIT)
+    IOLB_CASE(WINO_KERNELS_GIVEN, KERNELS_GIVEN)
+#undef IOLB_CASE
     return hipGetLastError();
 }
 
-hipError_t launch_wino_input_transform(const float* x, float* V, const WinoGeom& g, hipStream_t st)
+}  // namespace
+
+hipError_t launch_wino_transforms(const float* x, float* V, const WinoGeom& g, const float* w, void* U, int kind, int Kb16, hipStream_t st)
 {
-    if (g.Cp > 65535) return hipErrorInvalidValue;
-    dim3 grid((g.tiles + 255) / 256, g.Cp);
-    const bool vec = g.pad == 1 && g.W % g.m == 0 && (reinterpret_cast<uintptr_t>(x) & (4 * g.m - 1)) == 0;
     switch (g.m) {
-    case 2:
-        if (vec) hipLaunchKernelGGL((input_transform<2, true>), grid, dim3(256), 0, st, x, V, g);
-        else     hipLaunchKernelGGL((input_transform<2, false>), grid, dim3(256), 0, st, x, V, g);
-        break;
-    case 3: hipLaunchKernelGGL((input_transform<3, false>), grid, dim3(256), 0, st, x, V, g); break;
-    case 4:
-        if (vec) hipLaunchKernelGGL((input_transform<4, true>), grid, dim3(256), 0, st, x, V, g);
-        else     hipLaunchKernelGGL((input_transform<4, false>), grid, dim3(256), 0, st, x, V, g);
-        break;
-    case 6: hipLaunchKernelGGL((input_transform<6, false>), grid, dim3(256), 0, st, x, V, g); break;
+    case 2: return launch_transforms<2>(x, V, g, w, U, kind, Kb16, st);
+    case 3: return launch_transforms<3>(x, V, g, w, U, kind, Kb16, st);
+    case 4: return launch_transforms<4>(x, V, g, w, U, kind, Kb16, st);
+    case 6: return launch_transforms<6>(x, V, g, w, U, kind, Kb16, st);
     default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 hipError_t launch_wino_output_transform(const float* Mp, float* y, const WinoGeom& g, hipStream_t st)
