@@ -106,7 +106,7 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
     // weights of matrix step t: [t][16-channel block][part][lane]
     const int kb16 = kb * (MB * WM) + wm_i * MB;
     const size_t wstep = (size_t)g.Kb16 * 192;              // 16-byte pieces per step
-    const u32x4* wp = wt + (size_t)(g.w_per_image ? n0 : 0) * g.w_image + (size_t)kb16 * 192 + lane;
+    const u32x4* wp = wt + (size_t)kb16 * 192 + lane;
 
     const unsigned img = (unsigned)((long long)g.C * g.H * g.W * 4);
     const int images = g.N - n0 < g.b ? g.N - n0 : g.b;
@@ -165,10 +165,18 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
         load_batch(0, b);
         write_batch(lds);
     }
-    // the order in which a step issues its loads: first the weights, then the inputs
-    u32x4 a[MB * 3];
+    // Weights of the next AHEAD steps are on their way while a step multiplies: a step of a small block is shorter than
+    // the latency of its loads.  The order in which a step issues its loads: first the weights, then the inputs.
+    constexpr int AHEAD = MB == 1 ? 3 : MB * NB <= 8 ? 2 : 1;
+    u32x4 a[AHEAD + 1][MB * 3];
+    const int total = nchunks * steps;
+    auto load_weights = [&](u32x4 (&f)[MB * 3], int t) {
+        if (t > 0 && t < total) wp += wstep;                // past the last step: read again, not used
 #pragma unroll
-    for (int j = 0; j < MB * 3; ++j) a[j] = wp[j * 64];
+        for (int j = 0; j < MB * 3; ++j) f[j] = wp[j * 64];
+    };
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) load_weights(a[i], i);
     __builtin_amdgcn_sched_barrier(0);
     if (nchunks > 1) load_batch(1, 0);
     __builtin_amdgcn_sched_barrier(0);
@@ -179,17 +187,14 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
 #pragma unroll
         for (int p = 0; p < 3; ++p) f[p] = *reinterpret_cast<const u32x4*>(from + 16 * p);
     };
-    int ch = 0, k = 0;
+    int ch = 0, k = 0, t = 0;
     int ko = koff[grp];
     fetch(bf[0], lds + ko + pbase[0]);
-    // One matrix step: four units (tap, channel group) for every block of the wave.  The weights of the next step are
-    // on their way while this one multiplies; the pixels come from LDS one block ahead, across steps too.
-    for (int left = nchunks * steps; left > 0; --left) {
-        u32x4 an[MB * 3];
+    // One matrix step: four units (tap, channel group) for every block of the wave.  The pixels come from LDS one block
+    // ahead, across steps too.
+    auto step = [&](const u32x4 (&w0)[MB * 3], u32x4 (&wn)[MB * 3]) {
         const bool chunk_end = k + 1 == steps;
-        if (!(chunk_end && ch + 1 == nchunks)) wp += wstep;
-#pragma unroll
-        for (int j = 0; j < MB * 3; ++j) an[j] = wp[j * 64];
+        load_weights(wn, t + AHEAD);
         const char* bp = lds + (ch & 1) * buf_bytes;
         const int kn = koff[4 * (chunk_end ? 0 : k + 1) + grp];
         auto block = [&](auto nb_c) {
@@ -205,7 +210,7 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
                 for (int mb = 0; mb < MB; ++mb) {
                     f32x4& to = APART ? sum[mb] : acc[mb][nb];
                     to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                        __builtin_bit_cast(bf16x8, a[mb * 3 + PA[q]]), __builtin_bit_cast(bf16x8, bf[nb & 1][PB[q]]),
+                        __builtin_bit_cast(bf16x8, w0[mb * 3 + PA[q]]), __builtin_bit_cast(bf16x8, bf[nb & 1][PB[q]]),
                         APART && q == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : to, 0, 0, 0);
                 }
             if constexpr (APART) {
@@ -217,24 +222,27 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
         static_for<0, HALF>(block);
         // Loads come back in the order they were issued.  Where the paths with and without input loads meet, the
         // compiler would have to assume the worst and wait for every load at the next use of a weight: the two paths
-        // stay apart until each has waited for its own weights.
+        // stay apart until each has waited for the weights of the next step.
+        constexpr int LATER = MB * 3 * (AHEAD - 1), LOADS = (VEC ? 2 : 8) * IB;
         if (k < batches && ch + 1 < nchunks) {
             write_batch(lds + ((ch + 1) & 1) * buf_bytes);
             const bool more = k + 1 < batches;
             load_batch(more ? ch + 1 : ch + 2, more ? k + 1 : 0);
             static_for<HALF, NB>(block);
-            constexpr int LOADS = (VEC ? 2 : 8) * IB;
-            __builtin_amdgcn_s_waitcnt(0x0F70 | (LOADS & 15) | (LOADS >> 4) << 14);       // vmcnt(LOADS)
+            __builtin_amdgcn_s_waitcnt(0x0F70 | ((LATER + LOADS) & 15) | ((LATER + LOADS) >> 4) << 14);
         } else {
             static_for<HALF, NB>(block);
-            __builtin_amdgcn_s_waitcnt(0x0F70);                                             // vmcnt(0)
+            __builtin_amdgcn_s_waitcnt(0x0F70 | (LATER & 15) | (LATER >> 4) << 14);
         }
         if constexpr (NB & 1) {
 #pragma unroll
             for (int p = 0; p < 3; ++p) bf[0][p] = bf[1][p];
         }
+        if constexpr (AHEAD == 1) {
+            // one copy of the step: two would not fit the registers of the large blocks
 #pragma unroll
-        for (int j = 0; j < MB * 3; ++j) a[j] = an[j];
+            for (int j = 0; j < MB * 3; ++j) a[0][j] = a[1][j];
+        }
         ko = kn;
         ++k;
         if (chunk_end) {
@@ -243,6 +251,18 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
             ++ch;
             fetch(bf[0], lds + (ch & 1) * buf_bytes + ko + pbase[0]);
         }
+        return ++t == total;
+    };
+    if constexpr (AHEAD == 1) {
+        while (!step(a[0], a[1])) {}
+    } else {
+        // AHEAD + 1 copies, so that every step names its registers
+        bool done = false;
+        while (!done)
+            static_for<0, AHEAD + 1>([&](auto i_c) {
+                constexpr int i = decltype(i_c)::value;
+                if (!done) done = step(a[i], a[(i + AHEAD) % (AHEAD + 1)]);
+            });
     }
 
     // each partial sum is complete: write the block once.  Register i of a 16 x 16 block holds channel 4 grp + i of
@@ -289,7 +309,7 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
         const int im = slot / txy, rem = slot % txy, py = y0 + rem / g.tx, px = x0 + rem % g.tx;
         const int row = 4 * grp + i, k = (kb16 + mb) * 16 + row;
         if (k >= g.K) continue;
-        const unsigned short* wk = reinterpret_cast<const unsigned short*>(wt + (size_t)(g.w_per_image ? n0 : 0) * g.w_image + (size_t)(kb16 + mb) * 192);
+        const unsigned short* wk = reinterpret_cast<const unsigned short*>(wt + (size_t)(kb16 + mb) * 192);
         float sum = 0.f;
         for (int c = 0; c < g.C; ++c)
             for (int tap = 0; tap < RS; ++tap) {
@@ -386,7 +406,7 @@ hipError_t launch_split_conv(const float* x, const void* wt, float* y, const Spl
     // what the kernel assumes of its geometry
     if (g.b * g.tx * g.ty > 16 * g.nb * g.wn || split_lds_bytes(g) > 160 * 1024 || g.Kb16 != g.nbk * g.mb * g.wm ||
         (split_chunks(g) > 1 && split_batches(g) > split_steps(g)) || (g.nbuf < 2 && split_chunks(g) > 1) || g.ch8 < 1 || g.ch8 > 8 ||
-        4LL * g.b * g.C * g.H * g.W >= (1LL << 31) || (g.w_per_image && g.b != 1) || (g.vec_in && (!g.hwc || g.C % 4)))
+        4LL * g.b * g.C * g.H * g.W >= (1LL << 31) || (g.vec_in && (!g.hwc || g.C % 4)))
         return hipErrorInvalidValue;
     const u32x4* w = static_cast<const u32x4*>(wt);
     return g.vec_in ? launch_shape<true>(x, w, y, g, st) : launch_shape<false>(x, w, y, g, st);

@@ -74,8 +74,6 @@ struct SplitGeom {
     int halo;                  // b * yh * rowp
     int nbuf;                  // LDS buffers: 1 when the channels fit one chunk
     int Kb16;                  // 16-channel blocks, whole workgroup blocks
-    int w_per_image;           // every image has kernels of its own (w_image 16-byte pieces apart); b = 1
-    long long w_image;
     int hwc, vec_in, vec_out;  // channels innermost; with 16-byte loads / stores of four channels
 };
 constexpr int SPLIT_BATCH = 2;          // (pixel, 8 channels) items of the input tile that a thread stages at once

@@ -91,7 +91,7 @@ bool split_plan(SplitGeom* g, double* cycles)
             t.mb = sh.mb; t.nb = sh.nb; t.wm = sh.wm; t.wn = sh.wn; t.ch8 = ch8;
             for (int tx : cuts(g->Q, slots))
                 for (int ty : cuts(g->P, slots / tx)) {
-                    const int most_b = (tx == g->Q && ty == g->P && !g->w_per_image) ? std::min(g->N, slots / (tx * ty)) : 1;
+                    const int most_b = (tx == g->Q && ty == g->P) ? std::min(g->N, slots / (tx * ty)) : 1;
                     for (int b = 1; b <= most_b; ++b) {
                         if (b * tx * ty * 2 < slots) continue;           // a smaller shape does it
                         t.tx = tx; t.ty = ty; t.b = b;
