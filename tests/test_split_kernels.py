@@ -1,0 +1,195 @@
+"""The kernels that take fp32 products as bf16 products of parts (direct_split.hip, split_point.hip): edges of their
+blocks, remainders, layouts, values whose parts do not fit bf16, and the layers' other entry points."""
+import numpy as np
+import pytest
+
+from oracle.conv_oracle import conv_ref, conv_ref_cwh, conv_ref_hwc
+from paper_2012_15667_amd.inputs import make_inputs
+from tests.conftest import rel_err
+
+pytestmark = pytest.mark.gpu
+
+GUARD_WINO = {2: 5e-5, 4: 5e-4}          # as in test_gpu_parity.py
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU (run with -m 'not gpu' on a CPU box)")
+    from paper_2012_15667_amd import binding
+    binding.lib()
+    return torch, binding
+
+
+def _bound(x, w, stride, pad, ref_of=conv_ref):
+    """Largest error of a sum of products taken in three bf16 parts, per output: a running sum is rounded six times per
+    step of four (tap, eight channels) units and every rounding, inside the instruction too, is at most 2^-23 of the sum
+    of magnitudes so far (twice 2^-24: truncation is allowed for); the products left out add 3 * 2^-24."""
+    C, RS = w.shape[1], w.shape[2] * w.shape[3]
+    steps = -(-C // 8) * RS
+    return (12 * steps + 16) * 2.0 ** -23 * ref_of(np.abs(x), np.abs(w), stride, pad) + 1e-30
+
+
+CASES = [
+    # N, C, H, W, K, R, S, stride, pad
+    (1, 9, 7, 7, 1, 3, 3, 1, 1),            # second channel group nearly empty, one kernel
+    (2, 16, 9, 8, 15, 3, 3, 1, 1),          # exactly one chunk of 16: a single LDS buffer
+    (2, 17, 12, 11, 17, 3, 3, 1, 1),        # one channel and one kernel over a block
+    (1, 33, 5, 6, 130, 3, 3, 1, 0),         # chunk of 32 and one channel; K over 128
+    (3, 40, 14, 14, 64, 3, 3, 1, 1),        # whole images in a block, several images
+    (5, 48, 7, 7, 96, 3, 3, 1, 1),          # batch not a multiple of the images per block
+    (2, 31, 23, 29, 24, 3, 3, 2, 1),        # stride 2: residue classes of odd width
+    (1, 20, 31, 30, 40, 2, 2, 3, 0),        # stride beyond the kernel: rows and columns nobody uses
+    (2, 24, 17, 17, 32, 1, 7, 1, 0),        # one-sided kernels (no padding here)
+    (2, 24, 17, 17, 32, 7, 1, 1, 0),
+    (2, 64, 1, 1, 32, 3, 3, 1, 1),          # a single pixel
+    (2, 12, 35, 20, 20, 5, 5, 1, 2),
+    (2, 3, 51, 47, 30, 11, 11, 4, 0),       # three channels: products summed apart per step
+    (1, 5, 30, 30, 64, 7, 7, 2, 3),
+    (2, 8, 19, 19, 33, 5, 5, 1, 2),
+]
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_split_direct_layouts_within_the_bound(gpu, case):
+    torch, B = gpu
+    N, C, H, W, K, R, S, stride, pad = case
+    x, w = make_inputs(N, C, H, W, K, R, S, "u11", "he", seed=sum(case))
+    ref, lim = conv_ref(x, w, stride, pad), _bound(x, w, stride, pad)
+    wd = torch.from_numpy(w).cuda()
+    y = B.conv_direct(torch.from_numpy(x).cuda(), wd, stride, pad).cpu().numpy()
+    assert (np.abs(y - ref) <= lim).all()
+    # channels innermost: the same sums in the same order
+    xh = np.ascontiguousarray(x.transpose(0, 2, 3, 1))
+    yh = B.conv_direct_layout(torch.from_numpy(xh).cuda(), wd, stride, pad, B.LAYOUT_HWC).cpu().numpy()
+    assert np.array_equal(yh, y.transpose(0, 2, 3, 1))
+    # the transposed image: the taps in another order
+    xt = np.ascontiguousarray(x.transpose(0, 1, 3, 2))
+    yt = B.conv_direct_layout(torch.from_numpy(xt).cuda(), wd, stride, pad, B.LAYOUT_CWH).cpu().numpy()
+    assert (np.abs(yt - conv_ref_cwh(xt, w, stride, pad)) <= lim.transpose(0, 1, 3, 2)).all()
+
+
+@pytest.mark.parametrize("offset", [1, 2, 3])
+def test_split_direct_takes_tensors_off_16_byte_boundaries(gpu, offset):
+    torch, B = gpu
+    x, w = make_inputs(2, 20, 9, 10, 24, 3, 3, "u11", "he", seed=offset)
+    xh = np.ascontiguousarray(x.transpose(0, 2, 3, 1))
+    buf = torch.zeros(xh.size + 4, device="cuda")
+    xd = buf[offset:offset + xh.size].view(xh.shape)
+    xd.copy_(torch.from_numpy(xh))
+    out = torch.full((2 * 9 * 10 * 24 + 8,), 7.0, device="cuda")
+    yd = out[offset:offset + 2 * 9 * 10 * 24].view(2, 9, 10, 24)
+    B.conv_direct_layout(xd, torch.from_numpy(w).cuda(), 1, 1, B.LAYOUT_HWC, y=yd)
+    ref = conv_ref_hwc(xh, w, 1, 1)
+    assert (np.abs(yd.cpu().numpy() - ref) <= _bound(xh, w, 1, 1, conv_ref_hwc)).all()
+    flat = out.cpu().numpy()
+    assert (flat[:offset] == 7).all() and (flat[offset + 2 * 9 * 10 * 24:] == 7).all()
+
+
+# large enough for the split 1 x 1 kernel (at least 160 channels, 1 GFLOP, 48 flop per byte)
+POINT_CASES = [
+    # N, C, H, W, K, stride, layout
+    (9, 768, 17, 17, 192, 1, "chw"),        # 289 pixels: blocks that end inside an image, pairs over its end
+    (2, 161, 64, 65, 400, 1, "chw"),        # ragged channels, K not a multiple of a block
+    (60, 515, 6, 6, 500, 1, "chw"),         # blocks over several images
+    (70, 515, 7, 5, 500, 1, "chw"),         # the same with an odd number of pixels
+    (4, 300, 61, 61, 450, 2, "chw"),        # stride 2: single pixels
+    (9, 768, 17, 17, 192, 1, "hwc"),
+    (9, 770, 17, 17, 191, 1, "hwc"),        # no vector loads or stores
+    (4, 300, 61, 61, 452, 2, "hwc"),
+]
+
+
+@pytest.mark.parametrize("case", POINT_CASES)
+def test_split_pointwise_within_the_bound(gpu, case):
+    torch, B = gpu
+    N, C, H, W, K, stride, layout = case
+    x, w = make_inputs(N, C, H, W, K, 1, 1, "u11", "he", seed=N + C)
+    xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+    xs = xd[:, :, ::stride, ::stride].double().flatten(2).contiguous()
+    wk = wd.double().view(1, K, C).expand(N, K, C).contiguous()
+    P, Q = (H - 1) // stride + 1, (W - 1) // stride + 1
+    ref = torch.bmm(wk, xs).view(N, K, P, Q)
+    lim = (12 * -(-C // 8) + 16) * 2.0 ** -23 * torch.bmm(wk.abs(), xs.abs()).view(N, K, P, Q)
+    if layout == "chw":
+        y = B.conv_direct(xd, wd, stride, 0)
+    else:
+        y = B.conv_direct_layout(xd.permute(0, 2, 3, 1).contiguous(), wd, stride, 0, B.LAYOUT_HWC).permute(0, 3, 1, 2)
+    assert bool(((y.double() - ref).abs() <= lim).all())
+
+
+@pytest.mark.parametrize("shape", [(2, 24, 12, 13, 20, 3, 1), (2, 3, 40, 40, 16, 11, 0), (9, 768, 17, 17, 192, 1, 0)])
+def test_values_whose_parts_are_not_finite_bf16(gpu, shape):
+    """Infinities and NaN spread as in plain fp32 sums (0 * inf only where an operand is 0); finite values that round
+    to an infinite bf16 and sums far below the smallest bf16 keep fp32 precision."""
+    torch, B = gpu
+    N, C, H, W, K, R, pad = shape
+    x, w = make_inputs(N, C, H, W, K, R, R, "u11", "he", seed=5)
+    w[np.abs(w) < 1e-3] = 1e-3
+    x[np.abs(x) < 1e-3] = 1e-3
+    wd = torch.from_numpy(w).cuda()
+    run = lambda a: B.conv_direct(torch.from_numpy(a).cuda(), wd, 1 if R < 11 else 4, pad).cpu().numpy()
+    cpu = lambda a: torch.nn.functional.conv2d(torch.from_numpy(a).double(), torch.from_numpy(w).double(), stride=1 if R < 11 else 4, padding=pad).numpy()
+    a = x.copy()
+    a[0, 1, 3, 4], a[0, 2, 3, 5], a[N - 1, 0, H - 1, W - 1] = np.inf, -np.inf, np.nan
+    got, ref = run(a), cpu(a)
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref))
+    assert (np.sign(got[np.isinf(ref)]) == np.sign(ref[np.isinf(ref)])).all()
+    ok = np.isfinite(ref)
+    assert ok.any() and rel_err(got[ok], ref[ok]) <= 3e-5
+    a = x.copy()
+    a[0, 0, :2, :2] = 3.4e38                                # above the largest bf16
+    w[:] *= 1e-3
+    wd = torch.from_numpy(w).cuda()
+    got, ref = run(a), cpu(a)
+    assert np.isfinite(ref).all() and np.abs(ref).max() < 3e38
+    assert np.array_equal(np.isfinite(got), np.isfinite(ref.astype(np.float32)))
+    assert rel_err(got, ref) <= 3e-5
+    a = (x * np.float32(1e-31)).astype(np.float32)
+    got, ref = run(a), cpu(a)
+    assert rel_err(got, ref) <= 3e-5
+
+
+@pytest.mark.parametrize("m,N,C,H,W,K", [(2, 64, 512, 7, 7, 512), (2, 5, 131, 30, 29, 130), (2, 33, 261, 15, 15, 300), (4, 2, 290, 75, 73, 384)])
+def test_winograd_with_the_split_product(gpu, m, N, C, H, W, K):
+    """Sub-domain counts that are no multiple of four, ragged channels; on the fly, pre-transformed and with a workspace
+    that has only room for the tuned tile."""
+    torch, B = gpu
+    x, w = make_inputs(N, C, H, W, K, 3, 3, "u01", "he", seed=m + C)
+    xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+    ref = torch.zeros(N, K, H, W, dtype=torch.float64, device="cuda")
+    xp = torch.nn.functional.pad(xd.double(), (1, 1, 1, 1))
+    for r in range(3):
+        for s in range(3):
+            win = xp[:, :, r:r + H, s:s + W].reshape(N, C, H * W).contiguous()
+            wk = wd[:, :, r, s].double().view(1, K, C).expand(N, K, C).contiguous()
+            ref += torch.bmm(wk, win).view(N, K, H, W)
+    ref = ref.cpu().numpy()
+    y = B.conv_winograd(xd, wd, m)
+    assert rel_err(y.cpu().numpy(), ref) <= GUARD_WINO[m]
+    U = B.winograd_transform_kernels(wd, m)[0]
+    ws = torch.full((B.winograd_workspace_bytes(N, C, H, W, K, m),), 255, dtype=torch.uint8, device="cuda")    # NaN bits
+    yp = B.conv_winograd_pre(xd, U, K, m, workspace=ws)
+    assert torch.equal(y, yp)
+    ws.fill_(255)
+    assert torch.equal(B.conv_winograd(xd, wd, m, workspace=ws), y)
+
+
+def test_split_layers_through_the_call_that_allocates_nothing(gpu):
+    """The same bits as conv_direct up to its limit on the kernels, in three parts too; beyond it the error stays."""
+    torch, B = gpu
+    for (N, C, H, W, K, R) in ((1, 640, 5, 5, 704, 3), (2, 20, 12, 12, 40, 5), (9, 768, 17, 17, 192, 1)):
+        x, w = make_inputs(N, C, H, W, K, R, R, "u01", "he", seed=C)
+        xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+        y = B.conv_direct(xd, wd, 1, R // 2)
+        z = B.conv_direct_noalloc(xd, wd, 1, R // 2, torch.empty_like(y))
+        assert torch.equal(y, z)
+    x, w = make_inputs(1, 704, 9, 9, 704, 3, 3, "u01", "he", seed=1)      # (4 x 4 would take a tile that needs no room)
+    xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+    y = torch.full((1, 704, 9, 9), 3.0, device="cuda")
+    with pytest.raises(B.IolbError) as e:
+        B.conv_direct_noalloc(xd, wd, 1, 1, y)
+    assert e.value.code == -4 and bool((y == 3.0).all())
+    B.conv_direct(xd, wd, 1, 1, y=y)
+    assert rel_err(y.cpu().numpy(), conv_ref(x, w, 1, 1)) <= 3e-5
