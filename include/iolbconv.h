@@ -92,7 +92,12 @@ typedef struct iolb_bounds_out {
  *   y[n,k,p,q] = sum_{c,r,s} xpad[n,c,p*stride+r-pad,q*stride+s-pad] * w[k,c,r,s]
  * x: [N][C][H][W], w: [K][C][R][S], y: [N][K][P][Q]; cross-correlation, zero padding.
  * y is fully overwritten; x and y must not overlap.  The tile comes from iolb_tune with the
- * default budgets.  May grow the stream's workspace in the library (one allocation, kept). */
+ * default budgets.  May grow the stream's workspace in the library (one allocation, kept).
+ * Without a caller-supplied tile, layers that are bound by the fp32 matrix instructions run on the bf16 ones instead
+ * (this call, conv_direct_layout with cfg NULL, conv_direct_pad2, conv_direct_noalloc; the products of conv_winograd,
+ * conv_winograd_pad, and conv_winograd_ws / _pre with cfg NULL): every operand as the sum of three bf16 parts, six
+ * products of parts, fp32 sums -- no less precise than fp32 products.  Their blocks are not tiles of the enumeration;
+ * a caller-supplied tile always runs on the fp32 kernels. */
 int conv_direct(const float* x, const float* w, float* y,
                 int N, int C, int H, int W, int K, int R, int S, int stride, int pad);
 
@@ -118,8 +123,8 @@ int conv_direct_layout(const float* x, const float* w, float* y,
  * the re-laid-out weights go into a fixed array inside the library instead of the grown workspace: the call
  * makes no hipMalloc / hipFree and no allocating library call, and enqueues kernels only.
  * Limit: K rounded up to 32, times C rounded up to whole stages (at most 16 extra channels), times R * S must
- * not exceed conv_direct_noalloc_max_weight_floats() = 4194304 floats (16 MiB, held by every GPU the library
- * has run this call on until the process ends); beyond it the call returns IOLB_EWORKSPACE and launches
+ * not exceed conv_direct_noalloc_max_weight_floats() = 4194304 floats (the array has room for them in three bf16
+ * parts: 24 MiB, held by every GPU the library has run this call on until the process ends); beyond it the call returns IOLB_EWORKSPACE and launches
  * nothing.  All calls on one GPU share that array: calls that overlap on one GPU (two streams) race, and a
  * captured graph must not replay concurrently with another call of this entry point on the same GPU. */
 int conv_direct_noalloc(const float* x, const float* w, float* y,

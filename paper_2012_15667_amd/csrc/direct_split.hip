@@ -1,4 +1,26 @@
-// Direct convolution on the bf16 matrix cores at fp32 precision, dataflow of Sec. 5.2.
+// Direct convolution on the bf16 matrix cores at fp32 precision (operands in three parts, split_mfma.h), dataflow of
+// Sec. 5.2: a workgroup keeps the partial sums of b images * ty rows * tx columns by 16 MB WM output channels in
+// registers for the whole channel loop and writes them once.
+//
+// The channel loop runs in chunks of 8, 16 or 32 channels (8 ch8).  Of a chunk the input tile is in LDS, per pixel and
+// group of eight channels 48 bytes (three parts of eight bf16), in two buffers: while one chunk is multiplied the next
+// is loaded to registers, split and written to the other buffer, a batch of items per matrix step, with one barrier
+// per chunk.  A matrix step contracts four units of (tap, eight channels) in one v_mfma_f32_16x16x32_bf16 per product
+// of parts: the four lane groups of the instruction read the window pixel of their own unit, whose LDS offset comes
+// from a table, so one kernel serves every kernel extent, stride and padding.  Sixteen lanes read 16 bytes each 48 bytes
+// apart: every LDS bank once.  With a stride the columns are stored by residue class, so that this holds there too.
+// The weights (split once per call, in the order of the steps) go from the L2 straight into registers: each wave has
+// channels of its own, so through LDS they would only be written and read once more.
+//
+// What bounds it: the matrix cores, at the clock the chip's power allows (3x3, C = K = 256, 56 x 56, batch 64, whole
+// call: 1900 us on the fp32 instructions -> 949 us = 250 TFLOP/s of fp32 products; register-only bf16 loop 323; matrix
+// cores busy 0.73 of the cycles).  The rest: LDS reads (56 % of the cycles) and weight loads that meet at the CU's load
+// rate (about 19 bytes per clock).  Measured on that layer: blocks of 32 x 112 per wave 1041 us (kernel), 64 x 64 with the
+// weights read by two waves 1137, eight waves per workgroup 1046, chunks of 16 channels 1123; row pitch in LDS without
+// the padding of split_derive 1068 against 1024; input loads whose descriptor the compiler kept in vector registers
+// (a loop over the lanes per load) 1073 against 1041.  Sums apart per step (APART) for all layers: error 1.8e-7 in
+// place of 7.6e-7, 1129 us: kept for the few-channel layers only.
+// Small layers are bound by the latency of a step's weight loads (about 0.5 us): AHEAD below.
 #include "kernels.h"
 #include "split_mfma.h"
 

@@ -1,4 +1,19 @@
-// 1 x 1 convolution, and the product step of unfused Winograd, on the bf16 matrix cores at fp32 precision.
+// 1 x 1 convolution (no padding), and the product step of unfused Winograd, on the bf16 matrix cores at fp32 precision
+// (operands in three parts, split_mfma.h): per group of images that share kernels y[K][HW] = w[K][C] x[C][HW], a
+// transformed plane of Winograd being such a group of its own.
+//
+// A step is 32 channels.  The inputs of chunk t + 1 are split and written to one LDS buffer while chunk t is multiplied
+// from the other; their loads are issued three chunks ahead and kept in registers, two or four neighbouring pixels per
+// load where the layout has them.  The split's arithmetic is placed between the matrix instructions, three vector
+// instructions after each, where it costs little (a bf16 matrix instruction leaves the vector pipeline free; measured:
+// eight vector instructions per 32-cycle matrix instruction 1433 against 1631 TFLOP/s).  wt is not declared restrict on
+// purpose: loads of memory known not to change were moved down past the barrier to their use, which undid the prefetch.
+//
+// What bounds it: large products the rate at which a compute unit takes operands in, about 19 bytes per clock (a block
+// of z channels by npix pixels needs 192 z + 128 npix bytes per 32 channels), and the power the vector work of the
+// split costs in clock: 16 planes of 512 x 12544 x 512 (F(2x2)) 630 us = 167 TFLOP/s with 128 x 64 blocks (fp32
+// instructions: 840 us), 634 with 256 x 64, 666 - 680 with 128 x 96 and 192 x 64, 700 with 128 x 128, 708 with eight
+// waves on 256 x 128.  Small ones the latency of their steps.  1 x 1, 768 -> 192 at 17 x 17, batch 64: 66 -> 48 us whole call.
 #include "kernels.h"
 #include "split_mfma.h"
 

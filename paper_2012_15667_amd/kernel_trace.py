@@ -46,8 +46,8 @@ def main():
         for key in ("roofline", "roofline_winograd_product", "roofline_winograd_fused"):
             rf = d.get(key)
             if rf:
-                f.write("- %s: avg launch %.4f ms over %d launches, %.2f TFLOP/s (%.3f of the fp32 MFMA peak)\n" %
-                        (rf["kernel"], rf["avg_launch_ms"], rf["launches"], rf["achieved"], rf["frac"]))
+                f.write("- %s: avg launch %.4f ms over %d launches, %.2f TFLOP/s (%.3f of %.1f)\n" %
+                        (rf["kernel"], rf["avg_launch_ms"], rf["launches"], rf["achieved"], rf["frac"], rf["peak"]))
         f.write("- step: %.3f ms, %.1f TFLOP/s direct-equivalent\n\nPer layer (five back-to-back repetitions, outside the timed steps):\n\n" % (d["ms_per_step"], d["value"]))
         f.write("| layer | algo | path | tile b,x,y,z,alpha,threads | ms | TFLOP/s direct-eq. | bound-only pick ms | other Winograd path ms |\n|---|---|---|---|---|---|---|---|\n")
         for l in d["layers"]:

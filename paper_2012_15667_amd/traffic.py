@@ -130,6 +130,7 @@ def main():
         for pname, ctrs in layer_passes:
             tag = "%s_%s_%s_%s" % (layer, algo, path, pname)
             commands.append(_rocprof(ctrs, tag, _bench_args(layer, algo, path)))
+            print("collected " + tag, flush=True)
             for r in _rows(tag):
                 k = r["Kernel_Name"]
                 if "iolb::" not in k or (r["Counter_Name"] not in scale and r["Counter_Name"] not in SQ):
@@ -158,7 +159,7 @@ def main():
     w("convolution that term is below compulsory on every layer, for Winograd it is the printed expression of Sec. 4.3.")
     if args.sq:
         w("Matrix-core figures of a layer's main kernel: MFMA instructions against the algorithmic count (flop / 4096: one")
-        w("v_mfma_f32_32x32x2_f32 is 4096 flop; direct 2 N K P Q C R S, Winograd 2 (m+2)^2 tiles C K) shows the work the kernel")
+        w("v_mfma_f32_32x32x2_f32 is 4096 flop, one 16x16x32_bf16 of the split kernels 16384 / 6; direct 2 N K P Q C R S, Winograd 2 (m+2)^2 tiles C K) shows the work the kernel")
         w("adds (channel padding, idle slots); MFMA busy = SQ_VALU_MFMA_BUSY_CYCLES / (1024 SIMDs x GRBM_GUI_ACTIVE / 8 XCDs);")
         w("LDS conflicts = SQ_LDS_BANK_CONFLICT / SQ_LDS_IDX_ACTIVE.")
     w("")
@@ -183,7 +184,7 @@ def main():
             w("    %-46s read %9.1f MB   written %9.1f MB%s" % (k[:46], rd / 1e6, wr / 1e6, extra))
             tot_r += rd
             tot_w += wr
-            if rd + wr > main_bytes and ("mfma" in k or "product" in k or "rows" in k or "fused" in k or "thin_kernel" in k):
+            if rd + wr > main_bytes and ("mfma" in k or "product" in k or "rows" in k or "fused" in k or "thin_kernel" in k or "split_conv" in k or "split_point" in k):
                 main_bytes, main_name = rd + wr, k
         if args.sq and main_name:
             c = per_kernel[main_name]
@@ -195,9 +196,12 @@ def main():
                 P = (L.H + 2 * L.pad - L.R) // L.stride + 1
                 Q = (L.W + 2 * L.pad - L.S) // L.stride + 1
                 flop = 2.0 * L.N * L.K * P * Q * L.C * L.R * L.S
+            per_instr = 4096.0
+            if "split_" in main_name:                 # six products of parts; one 16x16x32 instruction is 16384 flop
+                per_instr = 16384.0 / 6
             if c["SQ_INSTS_MFMA"] > 0 and c["GRBM_GUI_ACTIVE"] > 0:
                 w("    main kernel: %.0f MFMA instructions = %.3f x algorithmic;  MFMA busy %.3f;  LDS conflicts %.3f" % (
-                    c["SQ_INSTS_MFMA"], c["SQ_INSTS_MFMA"] / (flop / 4096.0),
+                    c["SQ_INSTS_MFMA"], c["SQ_INSTS_MFMA"] / (flop / per_instr),
                     c["SQ_VALU_MFMA_BUSY_CYCLES"] / (1024.0 * c["GRBM_GUI_ACTIVE"] / 8.0),
                     c["SQ_LDS_BANK_CONFLICT"] / max(1.0, c["SQ_LDS_IDX_ACTIVE"])))
         w("    total %9.1f MB read + %9.1f MB written = %9.1f MB;  compulsory %8.1f MB (x %.2f);  bound %8.1f MB (x %.2f)" %
