@@ -67,7 +67,11 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
         bid = xcd * q + (xcd < r ? xcd : r) + ((int)blockIdx.x >> 3);
     }
     // the divisions run on the vector unit: back to scalars, so that everything derived from them stays scalar
-    const int kb = __builtin_amdgcn_readfirstlane(bid % g.nbk); bid /= g.nbk;
+    // ... and channel blocks of the same pixels are neighbours, unless the kernels do not fit an L2 (k_outer): then an XCD
+    // stays with one channel block
+    const int pixel_blocks = g.nbx * g.nby * g.nbn;
+    const int kb = __builtin_amdgcn_readfirstlane(g.k_outer ? bid / pixel_blocks : bid % g.nbk);
+    bid = g.k_outer ? bid % pixel_blocks : bid / g.nbk;
     const int x0 = __builtin_amdgcn_readfirstlane(bid % g.nbx * g.tx); bid /= g.nbx;
     const int y0 = __builtin_amdgcn_readfirstlane(bid % g.nby * g.ty);
     const int n0 = __builtin_amdgcn_readfirstlane(bid / g.nby * g.b);

@@ -74,6 +74,7 @@ struct SplitGeom {
     int halo;                  // b * yh * rowp
     int nbuf;                  // LDS buffers: 1 when the channels fit one chunk
     int Kb16;                  // 16-channel blocks, whole workgroup blocks
+    int k_outer;               // blocks of one channel block are neighbours, not those of the same pixels
     int hwc, vec_in, vec_out;  // channels innermost; with 16-byte loads / stores of four channels
 };
 constexpr int SPLIT_BATCH = 2;          // (pixel, 8 channels) items of the input tile that a thread stages at once

@@ -26,6 +26,10 @@ bool split_derive(SplitGeom* g)
     g->nby = (g->P + g->ty - 1) / g->ty;
     g->nbn = (g->N + g->b - 1) / g->b;
     if ((long long)g->nbk * g->nbx * g->nby * g->nbn > 0x7fffffffLL) return false;
+    // kernels of 3 MiB and more do not stay in an L2 of 4 MiB beside the inputs: then an XCD works on one channel block
+    // at a time (512 -> 512 at 28 x 28, 14 MB of kernels: 1140 -> 1118 us; 256 -> 256 at 56 x 56, 3.5 MB: 1068 -> 1052;
+    // 256 -> 512 at 28 x 28: equal)
+    g->k_outer = g->nbk > 1 && split_weight_bytes(*g) >= (3LL << 20);
     g->nbuf = split_chunks(*g) > 1 ? 2 : 1;
     if (g->b * g->tx * g->ty > 16 * g->nb * g->wn) return false;
     if (4LL * g->b * g->C * g->H * g->W >= (1LL << 31)) return false;
