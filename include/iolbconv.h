@@ -200,6 +200,14 @@ int iolb_tune_bound(const iolb_shape* shape, size_t lds_bytes, int vgpr_budget, 
 int64_t iolb_enumerate(const iolb_shape* shape, size_t lds_bytes, int vgpr_budget, int use_box,
                        iolb_tile_config* out, int64_t capacity);
 
+/* What a call without a caller-supplied tile runs on: IOLB_ROUTE_TILE, the fp32 kernels with the tuned tile, or
+ * IOLB_ROUTE_SPLIT, the bf16 matrix cores (see conv_direct); or a negative code.  It depends on the layer and the layout
+ * alone.  layout: as for conv_direct_layout (IOLB_LAYOUT_CHW for the Winograd algos).  *bytes (may be NULL): on the split
+ * route the bytes of the re-laid-out kernels (direct) or the least workspace that takes it (Winograd), else 0.
+ * conv_direct_noalloc takes the route of conv_direct, within its limit.  Host only. */
+enum { IOLB_ROUTE_TILE = 0, IOLB_ROUTE_SPLIT = 1 };
+int iolb_route(const iolb_shape* shape, int layout, size_t* bytes);
+
 /* Lower-bound figures for a layer at fast-memory size S_f elements.  Host only. */
 int iolb_bounds(const iolb_shape* shape, int64_t S_f_elems, iolb_bounds_out* out);
 

@@ -16,7 +16,7 @@ LAYOUT_CHW, LAYOUT_HWC, LAYOUT_CWH = 0, 1, 2
 
 EXPORTS = ["conv_direct", "conv_direct_noalloc", "conv_direct_noalloc_max_weight_floats", "conv_direct_cfg", "conv_direct_layout", "conv_direct_pad2", "conv_winograd", "conv_winograd_pad", "conv_winograd_workspace_bytes",
            "conv_winograd_ws", "conv_winograd_kernel_bytes", "conv_winograd_transform_kernels", "conv_winograd_pre",
-           "iolb_tune", "iolb_tune_bound", "iolb_enumerate", "iolb_bounds", "iolb_winograd_matrices", "iolb_set_stream",
+           "iolb_tune", "iolb_tune_bound", "iolb_enumerate", "iolb_route", "iolb_bounds", "iolb_winograd_matrices", "iolb_set_stream",
            "iolb_probe_hbm_copy", "iolb_probe_mfma_sink_bytes", "iolb_probe_mfma_f32",
            "iolb_probe_share_scratch_bytes", "iolb_probe_pipeline_share",
            "iolb_timing_enable", "iolb_timing_read", "iolb_release_workspace", "iolb_strerror",
@@ -100,6 +100,8 @@ def lib():
         L.iolb_tune_bound.argtypes = [ctypes.POINTER(Shape), sz, i, ctypes.POINTER(TileConfig)]
         L.iolb_enumerate.restype = ctypes.c_int64
         L.iolb_enumerate.argtypes = [ctypes.POINTER(Shape), sz, i, i, ctypes.POINTER(TileConfig), ctypes.c_int64]
+        L.iolb_route.restype = i
+        L.iolb_route.argtypes = [ctypes.POINTER(Shape), i, ctypes.POINTER(sz)]
         L.iolb_bounds.restype = i
         L.iolb_bounds.argtypes = [ctypes.POINTER(Shape), ctypes.c_int64, ctypes.POINTER(BoundsOut)]
         L.iolb_winograd_matrices.restype = i
@@ -166,6 +168,16 @@ def iolb_enumerate(shape, lds_bytes=0, vgpr_budget=0, use_box=True):
     arr = (TileConfig * max(n, 1))()
     _check(L.iolb_enumerate(ctypes.byref(shape), lds_bytes, vgpr_budget, int(use_box), arr, n))
     return [arr[j].as_dict() for j in range(n)]
+
+
+ROUTE_TILE, ROUTE_SPLIT = 0, 1
+
+
+def iolb_route(shape, layout=LAYOUT_CHW):
+    """(route, bytes) of a call without a tile: ROUTE_TILE or ROUTE_SPLIT, and what the split route needs in scratch."""
+    need = ctypes.c_size_t(0)
+    route = _check(lib().iolb_route(ctypes.byref(shape), layout, ctypes.byref(need)))
+    return route, need.value
 
 
 def iolb_bounds(shape, Sf):

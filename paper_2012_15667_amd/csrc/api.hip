@@ -202,8 +202,8 @@ int check_config(const iolb_shape& s, const iolb_tile_config& cfg)
 
 // ---- direct layers on the bf16 matrix cores, operands in three parts ---------------------------
 // Which kernel a layer without a caller-supplied tile runs on.  The choice and the block depend on the layer alone
-// (not on the tensor layout, which changes addresses only, nor on the entry point), so that every entry point gives
-// the same bits for the same layer.
+// (not on the entry point nor on the tile it was tuned; the tensor layout changes addresses only), so that every entry
+// point gives the same bits for the same layer, whatever was called before.
 struct SplitChoice {
     enum { NONE, CONV, POINT } kind = NONE;
     iolb::SplitGeom conv{};
@@ -213,7 +213,14 @@ struct SplitChoice {
 typedef std::tuple<int, int, int, int, int, int, int, int, int, int, int> SplitKey;
 std::map<SplitKey, SplitChoice> g_split;
 
-SplitChoice split_choice(const iolb_shape& s, int P, int Q, int pad_w, int layout, const iolb_tile_config& tile)
+// Whether conv_direct_noalloc has no room for the kernels of this tile in fp32 (the limit that its header states).
+bool beyond_scratch(const iolb_shape& s, const iolb_tile_config& tile)
+{
+    const long long c_padded = ((long long)s.C + tile.alpha - 1) / tile.alpha * tile.alpha;
+    return tile.path == IOLB_PATH_MFMA && (s.K + 31LL) / 32 * 32 * c_padded * s.R * s.S > (long long)kScratchFloats;
+}
+
+SplitChoice split_choice(const iolb_shape& s, int P, int Q, int pad_w, int layout)
 {
     const bool hwc = layout == IOLB_LAYOUT_HWC;
     const SplitKey key(s.N, s.C, s.H, s.W, s.K, s.R, s.S, s.stride, s.pad, pad_w, hwc ? 1 : 0);
@@ -224,9 +231,7 @@ SplitChoice split_choice(const iolb_shape& s, int P, int Q, int pad_w, int layou
     }
     SplitChoice ch;
     double cycles = 0;
-    if (is_thin(tile)) {
-        // bound by its stores on a kernel of its own
-    } else if (s.R == 1 && s.S == 1 && s.pad == 0 && pad_w == 0) {
+    if (s.R == 1 && s.S == 1 && s.pad == 0 && pad_w == 0) {
         iolb::SplitPointGeom g{};
         g.groups = 1; g.images = s.N; g.C = s.C; g.K = g.Ky = s.K; g.HW = g.HWy = P * Q; g.HWin = s.H * s.W; g.Win = s.W; g.Q = Q;
         g.stride = s.stride; g.hwc = hwc;
@@ -247,18 +252,22 @@ SplitChoice split_choice(const iolb_shape& s, int P, int Q, int pad_w, int layou
             ch.weight_bytes = (size_t)iolb::split_weight_bytes(g);
         }
     }
-    // conv_direct_noalloc has a fixed room for the kernels and gives the bits of conv_direct: a layer that it takes
-    // (its tile's kernels fit, or it reads them in place) must fit that room in three parts too
-    const long long c_padded = ((long long)s.C + tile.alpha - 1) / tile.alpha * tile.alpha;
-    const bool refused = tile.path == IOLB_PATH_MFMA && (s.K + 31LL) / 32 * 32 * c_padded * s.R * s.S > (long long)kScratchFloats;
-    if (ch.weight_bytes > kScratchBytes && !refused) ch.kind = SplitChoice::NONE;
+    // conv_direct_noalloc has a fixed room for the kernels and gives the bits of conv_direct: a layer that it takes (the
+    // kernels of conv_direct's own tile fit, or are read in place) must fit that room in three parts too.  It knows no
+    // layers with another padding per axis.
+    if (ch.weight_bytes > kScratchBytes && pad_w == s.pad) {
+        iolb_tile_config tile;
+        if (tuned_tile(s, &tile) != IOLB_OK || !beyond_scratch(s, tile)) ch = SplitChoice();
+    }
     std::lock_guard<std::mutex> lock(g_mutex);
     g_split[key] = ch;
     return ch;
 }
 
-int run_split(const float* x, const float* w, float* y, const iolb_shape& s, const SplitChoice& ch, int layout, float* wt_buf)
+// wt_buf != nullptr: room of wt_bytes bytes for the kernels in three parts
+int run_split(const float* x, const float* w, float* y, const iolb_shape& s, const SplitChoice& ch, int layout, float* wt_buf, size_t wt_bytes)
 {
+    if (wt_buf && ch.weight_bytes > wt_bytes) return IOLB_EWORKSPACE;
     DeviceState* dev = nullptr;
     int rc = device_state(&dev);
     if (rc != IOLB_OK) return rc;
@@ -288,17 +297,15 @@ int run_split(const float* x, const float* w, float* y, const iolb_shape& s, con
 
 // layout CWH: s, P, Q describe the transposed layer (H and W, R and S exchanged) and the weights are read
 // transposed; the tensors are then plain CHW tensors of that layer.
-// wt_buf != nullptr: room for the re-laid-out weights (wt_floats floats) given by the caller, so that nothing is
-// allocated; otherwise the library's workspace is used.
+// wt_buf != nullptr: room for the re-laid-out weights (wt_floats floats, or wt_floats weights in three bf16 parts) given
+// by the caller, so that nothing is allocated; otherwise the library's workspace is used.
 // own_tile: the tile is the library's own choice, not the caller's: the layer may run on the split kernels instead.
 int run_direct(const float* x, const float* w, float* y, const iolb_shape& s, int P, int Q, const iolb_tile_config& cfg,
                int layout = IOLB_LAYOUT_CHW, int pad_w = -1, float* wt_buf = nullptr, size_t wt_floats = 0, bool own_tile = true)
 {
     if (own_tile) {
-        const SplitChoice ch = split_choice(s, P, Q, pad_w < 0 ? s.pad : pad_w, layout, cfg);
-        const bool refused = wt_buf && cfg.path == IOLB_PATH_MFMA &&
-                             (size_t)((s.K + 31) / 32 * 32) * ((s.C + cfg.alpha - 1) / cfg.alpha * cfg.alpha) * s.R * s.S > wt_floats;
-        if (ch.kind != SplitChoice::NONE && !refused) return run_split(x, w, y, s, ch, layout, wt_buf);
+        const SplitChoice ch = split_choice(s, P, Q, pad_w < 0 ? s.pad : pad_w, layout);
+        if (ch.kind != SplitChoice::NONE && !(wt_buf && beyond_scratch(s, cfg))) return run_split(x, w, y, s, ch, layout, wt_buf, 6 * wt_floats);
     }
     DeviceState* dev = nullptr;
     int rc = device_state(&dev);
@@ -830,6 +837,34 @@ int conv_winograd_pad(const float* x, const float* w, float* y, int N, int C, in
     rc = ensure_workspace(dev, bytes, &ws);
     if (rc != IOLB_OK) return rc;
     return run_winograd(x, w, nullptr, y, s, tile, ws, bytes);
+}
+
+int iolb_route(const iolb_shape* shape, int layout, size_t* bytes)
+{
+    if (!shape) return IOLB_EINVAL;
+    if (layout != IOLB_LAYOUT_CHW && (shape->algo != IOLB_DIRECT || (layout != IOLB_LAYOUT_HWC && layout != IOLB_LAYOUT_CWH)))
+        return IOLB_EUNSUPPORTED;
+    iolb_shape s = *shape;
+    if (layout == IOLB_LAYOUT_CWH) { std::swap(s.H, s.W); std::swap(s.R, s.S); }
+    int P = 0, Q = 0;
+    int rc = iolb::validate_shape(s, &P, &Q);
+    if (rc != IOLB_OK) return rc;
+    bool split;
+    size_t need;
+    if (s.algo == IOLB_DIRECT) {
+        const SplitChoice ch = split_choice(s, P, Q, s.pad, layout);
+        split = ch.kind != SplitChoice::NONE;
+        need = ch.weight_bytes;
+    } else {
+        iolb_tile_config tile;
+        rc = tuned_tile(s, &tile);
+        if (rc != IOLB_OK) return rc;
+        const SplitWino p = split_wino(s, tile);
+        split = p.use;
+        need = p.total;
+    }
+    if (bytes) *bytes = split ? need : 0;
+    return split ? IOLB_ROUTE_SPLIT : IOLB_ROUTE_TILE;
 }
 
 int iolb_winograd_matrices(int m, float* A, float* L, float* B)

@@ -1,0 +1,72 @@
+"""Which kernel a call without a tile runs on (iolb_route): a property of the layer, whatever was asked before, and within
+the fixed room of conv_direct_noalloc.  Host only, except where marked."""
+import json
+import os
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+from paper_2012_15667_amd import binding as B
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SCRATCH_BYTES = 6 * 4194304              # conv_direct_noalloc's array: 4 Mi weights in three bf16 parts
+
+# 1 x 1 layers with more kernels than that array holds: (N, C, H, W, K)
+LARGE_POINT = [(8, 2304, 14, 14, 2304), (8, 2048, 17, 17, 2304), (4, 2560, 16, 16, 2560)]
+
+
+def _routes(order):
+    """iolb_route of every layer in the given layout order, asked in a process of its own (the library remembers)."""
+    code = ("import json; from paper_2012_15667_amd import binding as B\n"
+            "out = {}\n"
+            "for l in %r:\n"
+            "    for lay in %r:\n"
+            "        out['%%s %%s' %% (l, lay)] = B.iolb_route(B.make_shape(*l, 1, 1, 1, 0), lay)\n"
+            "print(json.dumps(out))" % (LARGE_POINT, order))
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, stdout=subprocess.PIPE, text=True, check=True, timeout=100)
+    return json.loads(r.stdout)
+
+
+def test_the_route_does_not_depend_on_what_was_asked_before():
+    a = _routes([B.LAYOUT_CWH, B.LAYOUT_CHW, B.LAYOUT_HWC])
+    assert a == _routes([B.LAYOUT_CHW, B.LAYOUT_HWC, B.LAYOUT_CWH])
+
+
+def _noalloc_takes(shape):
+    """The limit conv_direct_noalloc states, on the tile of conv_direct."""
+    t = B.iolb_tune(shape)
+    padded = -(-shape.K // 32) * 32 * -(-shape.C // t["alpha"]) * t["alpha"] * shape.R * shape.S
+    return t["path"] != B.PATH_MFMA or padded <= 4194304
+
+
+@pytest.mark.parametrize("layer", LARGE_POINT + [(1, 704, 9, 9, 640), (1, 704, 9, 9, 704), (1, 640, 5, 5, 704), (2, 1024, 8, 8, 1024)])
+def test_layers_the_call_without_allocation_takes_fit_its_room(layer):
+    R = 1 if layer in LARGE_POINT else 3
+    shape = B.make_shape(*layer, R, R, 1, R // 2)
+    for layout in (B.LAYOUT_CWH, B.LAYOUT_CHW):                 # another layout's tile first
+        route, need = B.iolb_route(shape, layout)
+        if _noalloc_takes(shape):
+            assert need <= SCRATCH_BYTES, layout
+        if need > SCRATCH_BYTES:
+            assert route == B.ROUTE_SPLIT
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("first", [B.LAYOUT_CWH, B.LAYOUT_CHW])
+def test_large_pointwise_layers_give_the_same_bits_whatever_ran_before(first):
+    """Another layout first, then conv_direct_noalloc: the result of conv_direct, nothing written beside the scratch."""
+    import torch
+    N, C, H, K = (8, 2304, 14, 2304) if first == B.LAYOUT_CWH else (4, 2304, 14, 2304)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.rand((N, C, H, H), generator=g, device="cuda") - 0.5
+    w = torch.randn((K, C, 1, 1), generator=g, device="cuda") * C ** -0.5
+    B.conv_direct_layout(x, w, 1, 0, first)
+    y = torch.full((N, K, H, H), 7.0, device="cuda")
+    B.conv_direct_noalloc(x, w, 1, 0, y)
+    assert torch.equal(y, B.conv_direct(x, w, 1, 0))
+    ref = torch.bmm(w.double().view(1, K, C).expand(N, K, C).contiguous(), x.double().flatten(2).contiguous()).view(N, K, H, H)
+    # sums of C fp32 products: every rounding at most 2^-23 of the magnitudes
+    lim = 2 * C * 2.0 ** -23 * torch.bmm(w.double().abs().view(1, K, C).expand(N, K, C).contiguous(), x.double().abs().flatten(2).contiguous()).view(N, K, H, H)
+    assert bool(((y.double() - ref).abs() <= lim).all())
