@@ -221,7 +221,7 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
     auto step = [&](const u32x4 (&w0)[MB * 3], u32x4 (&wn)[MB * 3]) {
         const bool chunk_end = k + 1 == steps;
         load_weights(wn, t + AHEAD);
-        const char* bp = lds + (ch & 1) * buf_bytes;
+        const char* bp = lds + split_buffer(ch, g.nbuf) * buf_bytes;
         const int kn = koff[4 * (chunk_end ? 0 : k + 1) + grp];
         auto block = [&](auto nb_c) {
             constexpr int nb = decltype(nb_c)::value;
@@ -251,7 +251,7 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
         // stay apart until each has waited for the weights of the next step.
         constexpr int LATER = MB * 3 * (AHEAD - 1), LOADS = (VEC ? 2 : 8) * IB;
         if (k < batches && ch + 1 < nchunks) {
-            write_batch(lds + ((ch + 1) & 1) * buf_bytes);
+            write_batch(lds + split_buffer(ch + 1, g.nbuf) * buf_bytes);
             const bool more = k + 1 < batches;
             load_batch(more ? ch + 1 : ch + 2, more ? k + 1 : 0);
             static_for<HALF, NB>(block);
@@ -271,13 +271,14 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
         }
         ko = kn;
         ++k;
-        if (chunk_end) {
+        const bool done = ++t == total;
+        if (chunk_end && !done) {                           // (one chunk has one buffer: there is no next one to read)
             barrier();
             k = 0;
             ++ch;
-            fetch(bf[0], lds + (ch & 1) * buf_bytes + ko + pbase[0]);
+            fetch(bf[0], lds + split_buffer(ch, g.nbuf) * buf_bytes + ko + pbase[0]);
         }
-        return ++t == total;
+        return done;
     };
     if constexpr (AHEAD == 1) {
         while (!step(a[0], a[1])) {}
@@ -431,7 +432,7 @@ hipError_t launch_split_conv(const float* x, const void* wt, float* y, const Spl
 {
     // what the kernel assumes of its geometry
     if (g.b * g.tx * g.ty > 16 * g.nb * g.wn || split_lds_bytes(g) > 160 * 1024 || g.Kb16 != g.nbk * g.mb * g.wm ||
-        (split_chunks(g) > 1 && split_batches(g) > split_steps(g)) || (g.nbuf < 2 && split_chunks(g) > 1) || g.ch8 < 1 || g.ch8 > 8 ||
+        (split_chunks(g) > 1 && split_batches(g) > split_steps(g)) || g.nbuf < (split_chunks(g) > 1 ? 2 : 1) || g.nbuf > 2 || g.ch8 < 1 || g.ch8 > 8 ||
         4LL * g.b * g.C * g.H * g.W >= (1LL << 31) || (g.vec_in && (!g.hwc || g.C % 4)))
         return hipErrorInvalidValue;
     const u32x4* w = static_cast<const u32x4*>(wt);

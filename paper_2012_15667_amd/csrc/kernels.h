@@ -100,6 +100,10 @@ inline long long split_lds_bytes(const SplitGeom& g)
 {
     return (long long)g.nbuf * g.ch8 * g.b * g.yh * g.rowb + 4 * ((4 * split_steps(g) + 1) & ~1) + 8LL * g.ch8 * g.halo;
 }
+// The input-tile buffer of a chunk: never one that split_lds_bytes does not count.
+__host__ __device__ constexpr int split_buffer(int chunk, int nbuf) { return chunk & (nbuf - 1); }
+static_assert(split_buffer(0, 1) == 0 && split_buffer(1, 1) == 0 && split_buffer(0, 2) == 0 && split_buffer(1, 2) == 1 && split_buffer(2, 2) == 0,
+              "one buffer or two in turn");
 inline long long split_weight_bytes(const SplitGeom& g) { return (long long)split_chunks(g) * split_steps(g) * g.Kb16 * 3072; }
 // Kernels in three parts in the order of the matrix steps, written from w[K][C][R][S] (transposed: w[K][C][S][R]).
 hipError_t launch_split_weights(const float* w, void* wt, int K, int C, int R, int S, int ch8, int Kb16, bool transposed, hipStream_t st);
