@@ -293,8 +293,7 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
     }
 
     // each partial sum is complete: write the block once.  Register i of a 16 x 16 block holds channel 4 grp + i of
-    // pixel l16.  Outputs that are not finite, or so small that parts of their operands may lie below the smallest
-    // bf16, are marked and computed again below.
+    // pixel l16.  Sums that are not finite are marked and computed again below.
     const size_t PQ = (size_t)g.P * g.Q;
     unsigned long long again = 0;
     static_assert(MB * NB * 4 <= 64, "one mark per output");
@@ -308,8 +307,8 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
             const int k0 = (kb16 + mb) * 16 + 4 * grp;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const float v = acc[mb][nb][i], av = __builtin_fabsf(v);
-                if (!(av <= 3.402823466e38f && av >= 1.3e-29f) && av != 0.f) again |= 1ull << ((nb * MB + mb) * 4 + i);
+                if (!(__builtin_fabsf(acc[mb][nb][i]) <= 3.402823466e38f)) again |= 1ull << ((nb * MB + mb) * 4 + i);
+                acc[mb][nb][i] *= SPLIT_UNSCALE;
             }
             if (g.hwc) {
                 float* yp = y + (((size_t)(n0 + im) * g.P + py) * g.Q + px) * g.K + k0;
@@ -340,14 +339,14 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
         float sum = 0.f;
         for (int c = 0; c < g.C; ++c)
             for (int tap = 0; tap < RS; ++tap) {
+                // zeros around the image are operands like others (0 times an infinite weight is NaN)
                 const int gy = py * g.stride - g.pad + tap / g.S, gx = px * g.stride - g.pad_w + tap % g.S;
-                if (gy < 0 || gy >= g.H || gx < 0 || gx >= g.W) continue;
+                const bool inside = gy >= 0 && gy < g.H && gx >= 0 && gx < g.W;
                 const int u = tap * CH8 + c / 8 % CH8, ln = (u & 3) * 16 + row;
                 const unsigned short* q = wk + ((size_t)(c / (8 * CH8)) * steps + (u >> 2)) * wstep * 8 + ln * 8 + c % 8;
-                const float wv = bf16_bits_to_float(q[0]) + (bf16_bits_to_float(q[512]) + bf16_bits_to_float(q[1024]));
                 const size_t xi = g.hwc ? (((size_t)(n0 + im) * g.H + gy) * g.W + gx) * g.C + c
                                       : (((size_t)(n0 + im) * g.C + c) * g.H + gy) * g.W + gx;
-                sum = __builtin_fmaf(x[xi], wv, sum);
+                sum = __builtin_fmaf(inside ? x[xi] : 0.f, kept_value(q[0], q[512], q[1024]), sum);
             }
         y[g.hwc ? (((size_t)(n0 + im) * g.P + py) * g.Q + px) * g.K + k : ((size_t)(n0 + im) * g.K + k) * PQ + (size_t)py * g.Q + px] = sum;
     }

@@ -19,10 +19,20 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
-// x = h + m + l with h, m, l bf16 (8 significant bits each, rounded to nearest, so that the two differences are
+// Both operands are scaled by 2^23 before they are cut: every bit of an fp32 value, down to 2^-149, is then at least the
+// smallest normal bf16, so that the three parts hold any value exactly and no instruction sees a denormal operand.  Sums
+// are scaled back by 2^-46 when they are written.  At the other end operands from 2^105 and sums from 2^82 on overflow,
+// which the sum shows: it is infinite or NaN, as with operands that are not finite, and the output is computed again in
+// plain fp32.
+constexpr float SPLIT_SCALE = 8388608.f;                     // 2^23
+constexpr float SPLIT_UNSCALE = 1.f / SPLIT_SCALE / SPLIT_SCALE;
+
+// 2^23 x = h + m + l with h, m, l bf16 (8 significant bits each, rounded to nearest, so that the two differences are
 // exact): two operands at a time, one packed conversion per part.
 __device__ __forceinline__ void split_pair(float a, float b, unsigned& h, unsigned& m, unsigned& l)
 {
+    a *= SPLIT_SCALE;
+    b *= SPLIT_SCALE;
     const bf16x2 hv = {(__bf16)a, (__bf16)b};
     h = __builtin_bit_cast(unsigned, hv);
     const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xffff0000u);
@@ -44,24 +54,30 @@ __device__ __forceinline__ void split_eight(const float (&v)[8], u32x4& h, u32x4
     }
 }
 
-// For values that are kept (weights): parts whose sum is the value for infinities, NaN and the largest finite
-// values too (h truncated where rounding would overflow, no differences of infinities).
+// For values that are kept (weights): a value beyond the parts' range is kept whole, its two halves in place of m and l,
+// under a NaN that makes every sum it enters NaN.
 __device__ __forceinline__ void split_kept(float a, unsigned short& h, unsigned short& m, unsigned short& l)
 {
-    const unsigned u = __float_as_uint(a);
-    unsigned hu = (unsigned)__builtin_bit_cast(unsigned short, (__bf16)a) << 16;
-    if ((hu & 0x7f800000u) == 0x7f800000u && (u & 0x7f800000u) != 0x7f800000u) hu = u & 0xffff0000u;
-    h = (unsigned short)(hu >> 16);
-    m = l = 0;
-    if ((hu & 0x7f800000u) != 0x7f800000u) {
-        const float r = a - __uint_as_float(hu);
-        const unsigned mu = (unsigned)__builtin_bit_cast(unsigned short, (__bf16)r) << 16;
-        m = (unsigned short)(mu >> 16);
-        l = __builtin_bit_cast(unsigned short, (__bf16)(r - __uint_as_float(mu)));
+    const float v = a * SPLIT_SCALE;
+    h = __builtin_bit_cast(unsigned short, (__bf16)v);
+    if ((h & 0x7f80) == 0x7f80) {
+        const unsigned u = __float_as_uint(a);
+        h = 0x7fc0;
+        m = (unsigned short)(u >> 16);
+        l = (unsigned short)u;
+        return;
     }
+    const float r = v - __uint_as_float((unsigned)h << 16);
+    m = __builtin_bit_cast(unsigned short, (__bf16)r);
+    l = __builtin_bit_cast(unsigned short, (__bf16)(r - __uint_as_float((unsigned)m << 16)));
 }
 
-__device__ __forceinline__ float bf16_bits_to_float(unsigned short b) { return __uint_as_float((unsigned)b << 16); }
+// The value that split_kept was given.
+__device__ __forceinline__ float kept_value(unsigned h, unsigned m, unsigned l)
+{
+    const float parts = __uint_as_float(h << 16) + (__uint_as_float(m << 16) + __uint_as_float(l << 16));
+    return h == 0x7fc0 ? __uint_as_float(m << 16 | l) : parts * (1.f / SPLIT_SCALE);
+}
 
 }  // namespace iolb
 

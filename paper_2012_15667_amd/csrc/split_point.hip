@@ -226,8 +226,7 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
     }
 
     // each partial sum is complete: write the block once.  Register i of a 16 x 16 block holds channel 4 grp + i of
-    // pixel l16.  Outputs that are not finite, or so small that parts of their operands may lie below the smallest
-    // bf16, are marked and computed again below.
+    // pixel l16.  Sums that are not finite are marked and computed again below.
     unsigned long long again = 0;
     static_assert(MB * NB * 4 <= 64, "one mark per output");
 #pragma unroll
@@ -240,8 +239,8 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
             const int k0 = (kb16 + mb) * 16 + 4 * grp;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const float v = acc[mb][nb][i], av = __builtin_fabsf(v);
-                if (!(av <= 3.402823466e38f && av >= 1.3e-29f) && av != 0.f) again |= 1ull << ((nb * MB + mb) * 4 + i);
+                if (!(__builtin_fabsf(acc[mb][nb][i]) <= 3.402823466e38f)) again |= 1ull << ((nb * MB + mb) * 4 + i);
+                acc[mb][nb][i] *= SPLIT_UNSCALE;
             }
             if (g.hwc) {
                 float* yp = y + ((size_t)n * g.HW + r) * g.K + k0;
@@ -272,8 +271,7 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
         float sum = 0.f;
         for (int c = 0; c < g.C; ++c) {
             const unsigned short* q = wk + (size_t)(c >> 5) * wstep * 8 + ((c >> 3 & 3) * 16 + row) * 8 + (c & 7);
-            const float wv = bf16_bits_to_float(q[0]) + (bf16_bits_to_float(q[512]) + bf16_bits_to_float(q[1024]));
-            sum = __builtin_fmaf(x[g.hwc ? ((size_t)n * g.HWin + in) * g.C + c : ((size_t)n * g.C + c) * g.HWin + in], wv, sum);
+            sum = __builtin_fmaf(x[g.hwc ? ((size_t)n * g.HWin + in) * g.C + c : ((size_t)n * g.C + c) * g.HWin + in], kept_value(q[0], q[512], q[1024]), sum);
         }
         y[g.hwc ? ((size_t)n * g.HW + r) * g.K + k : ((size_t)n * g.Ky + k) * g.HWy + r] = sum;
     }

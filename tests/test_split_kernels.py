@@ -28,7 +28,7 @@ def _bound(x, w, stride, pad, ref_of=conv_ref):
     of magnitudes so far (twice 2^-24: truncation is allowed for); the products left out add 3 * 2^-24."""
     C, RS = w.shape[1], w.shape[2] * w.shape[3]
     steps = -(-C // 8) * RS
-    return (12 * steps + 16) * 2.0 ** -23 * ref_of(np.abs(x), np.abs(w), stride, pad) + 1e-30
+    return (12 * steps + 16) * 2.0 ** -23 * ref_of(np.abs(x), np.abs(w), stride, pad)
 
 
 CASES = [
@@ -122,7 +122,7 @@ def test_split_pointwise_within_the_bound(gpu, case):
 @pytest.mark.parametrize("shape", [(2, 24, 12, 13, 20, 3, 1), (2, 3, 40, 40, 16, 11, 0), (9, 768, 17, 17, 192, 1, 0)])
 def test_values_whose_parts_are_not_finite_bf16(gpu, shape):
     """Infinities and NaN spread as in plain fp32 sums (0 * inf only where an operand is 0); finite values that round
-    to an infinite bf16 and sums far below the smallest bf16 keep fp32 precision."""
+    to an infinite bf16 and very small sums keep fp32 precision."""
     torch, B = gpu
     N, C, H, W, K, R, pad = shape
     x, w = make_inputs(N, C, H, W, K, R, R, "u11", "he", seed=5)
@@ -149,6 +149,56 @@ def test_values_whose_parts_are_not_finite_bf16(gpu, shape):
     a = (x * np.float32(1e-31)).astype(np.float32)
     got, ref = run(a), cpu(a)
     assert rel_err(got, ref) <= 3e-5
+
+
+# (operand scales of x and w): each operand near or below the smallest normal number against a large partner, both ways;
+# denormal operands; denormal results; operands and sums beyond what the scaled parts hold (2^105, 2^82)
+SCALES = [(1e-38, 1e30), (1e30, 1e-38), (1e-41, 1e25), (1e25, 1e-41), (1e-30, 1e-11), (1e33, 1e-10), (1e-10, 1e33), (1e15, 1e12)]
+
+
+@pytest.mark.parametrize("scales", SCALES)
+@pytest.mark.parametrize("shape", [(2, 24, 12, 13, 20, 3, 1, 1), (2, 3, 40, 40, 16, 11, 4, 0), (12, 768, 17, 17, 192, 1, 1, 0)])
+def test_operands_over_the_whole_range_keep_fp32_precision(gpu, shape, scales):
+    torch, B = gpu
+    N, C, H, W, K, R, stride, pad = shape
+    assert B.iolb_route(B.make_shape(N, C, H, W, K, R, R, stride, pad))[0] == B.ROUTE_SPLIT
+    x, w = make_inputs(N, C, H, W, K, R, R, "u11", "he", seed=31)
+    x, w = x * np.float32(scales[0]), w * np.float32(scales[1])
+    y = B.conv_direct(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), stride, pad).cpu().numpy()
+    # results below the smallest normal number are multiples of 2^-149: one rounding
+    assert (np.abs(y - conv_ref(x, w, stride, pad)) <= _bound(x, w, stride, pad) + 2.0 ** -149).all()
+
+
+@pytest.mark.parametrize("scales", [(1e-38, 1e30), (1e30, 1e-38), (1e33, 1e-10), (1e-10, 1e33)])
+def test_winograd_product_over_the_whole_range(gpu, scales):
+    torch, B = gpu
+    N, C, H, W, K = 64, 512, 7, 7, 512
+    assert B.iolb_route(B.make_shape(N, C, H, W, K, algo=B.WINO_F2))[0] == B.ROUTE_SPLIT
+    x, w = make_inputs(N, C, H, W, K, 3, 3, "u11", "he", seed=32)
+    x, w = x * np.float32(scales[0]), w * np.float32(scales[1])
+    xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+    # the fp32 product of the tuned tile, asked for by name
+    tile = B.iolb_tune(B.make_shape(N, C, H, W, K, algo=B.WINO_F2))
+    ref = B.conv_winograd(xd, wd, 2, cfg=tile).cpu().numpy()
+    assert rel_err(B.conv_winograd(xd, wd, 2).cpu().numpy(), ref) <= GUARD_WINO[2]
+    U = B.winograd_transform_kernels(wd, 2)[0]
+    assert rel_err(B.conv_winograd_pre(xd, U, K, 2).cpu().numpy(), ref) <= GUARD_WINO[2]
+
+
+def test_zeros_around_the_image_meet_infinite_weights(gpu):
+    """The border is made of zeros that are multiplied like other operands: 0 times an infinite weight is NaN."""
+    torch, B = gpu
+    x, w = make_inputs(1, 24, 9, 9, 20, 3, 3, "u11", "he", seed=33)
+    x = np.abs(x) + np.float32(0.1)
+    w[3, 5, 0, 1], w[7, 2, 2, 2] = np.inf, -np.inf
+    y = B.conv_direct(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), 1, 1).cpu().numpy()
+    assert np.isnan(y[0, 3, 0, :]).all() and (y[0, 3, 1:, :] == np.inf).all()
+    assert np.isnan(y[0, 7, 8, :]).all() and np.isnan(y[0, 7, :, 8]).all() and (y[0, 7, :8, :8] == -np.inf).all()
+    rest = [k for k in range(20) if k not in (3, 7)]
+    assert np.isfinite(y[:, rest]).all()
+    tile = B.iolb_tune(B.make_shape(1, 24, 9, 9, 20))
+    z = B.conv_direct(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), 1, 1, cfg=tile).cpu().numpy()
+    assert np.array_equal(np.isnan(y), np.isnan(z)) and np.array_equal(y[np.isinf(z)], z[np.isinf(z)])
 
 
 @pytest.mark.parametrize("m,N,C,H,W,K", [(2, 64, 512, 7, 7, 512), (2, 5, 131, 30, 29, 130), (2, 33, 261, 15, 15, 300), (4, 2, 290, 75, 73, 384)])
