@@ -46,6 +46,18 @@ __device__ __forceinline__ void static_for(F f)
     }
 }
 
+// Buffer of a block's images, first one n0: loads beyond them return zero.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t image_buffer(const float* x, const SplitGeom& g, int n0)
+{
+    const unsigned img = (unsigned)((long long)g.C * g.H * g.W * 4);
+    const int images = g.N - n0 < g.b ? g.N - n0 : g.b;
+    const unsigned long long xbase = reinterpret_cast<unsigned long long>(x + (size_t)n0 * g.C * g.H * g.W);
+    // (the builtin returns a signed int: the halves have to be unsigned before they are put together)
+    const unsigned xlo = __builtin_amdgcn_readfirstlane((unsigned)xbase), xhi = __builtin_amdgcn_readfirstlane((unsigned)(xbase >> 32));
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>((unsigned long long)xhi << 32 | xlo), 0,
+                                             (int)__builtin_amdgcn_readfirstlane(img * (unsigned)images), 0x00020000);
+}
+
 template <int MB, int NB, int WM, int WN, bool VEC, bool APART>
 __global__ void __launch_bounds__(64 * WM * WN, 2)
 split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitGeom g)
@@ -54,7 +66,9 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
     char* const lds = reinterpret_cast<char*>(lds16);
     constexpr int T = 64 * WM * WN;
     constexpr int IB = SPLIT_BATCH;
-    const int CH8 = g.ch8;
+    // read here, once: loads of their own in the branches of a loop with diverging exits, which the compiler would make of
+    // later uses, would count as values that differ between lanes
+    const int CH8 = g.ch8, C = g.C, cstep = g.cstep;
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, grp = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm_i = wave % WM, wn_i = wave / WM;
@@ -103,8 +117,8 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
         uint2 e;
         e.x = OUTSIDE;
         if (n0 + im < g.N && ix < g.xh && gy >= 0 && gy < g.H && gx >= 0 && gx < g.W)
-            e.x = g.hwc ? 4u * (unsigned)(((im * g.H + gy) * g.W + gx) * g.C + c8 * 8)
-                      : 4u * (unsigned)(((im * g.C + c8 * 8) * g.H + gy) * g.W + gx);
+            e.x = g.hwc ? 4u * (unsigned)(((im * g.H + gy) * g.W + gx) * C + c8 * 8)
+                      : 4u * (unsigned)(((im * C + c8 * 8) * g.H + gy) * g.W + gx);
         e.y = (unsigned)(c8 * group_bytes + im * im_bytes + iy * g.rowb + 48 * ((ix % g.esx) * g.colw + ix / g.esx));
         // c8 in the low bits of the LDS offset (a multiple of 16)
         e.y |= (unsigned)c8;
@@ -128,26 +142,20 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    const int nchunks = __builtin_amdgcn_readfirstlane((g.C + 8 * CH8 - 1) / (8 * CH8));
+    const int nchunks = __builtin_amdgcn_readfirstlane((C + 8 * CH8 - 1) / (8 * CH8));
     // weights of matrix step t: [t][16-channel block][part][lane]
     const int kb16 = kb * (MB * WM) + wm_i * MB;
     const size_t wstep = (size_t)g.Kb16 * 192;              // 16-byte pieces per step
     const u32x4* wp = wt + (size_t)kb16 * 192 + lane;
 
-    const unsigned img = (unsigned)((long long)g.C * g.H * g.W * 4);
-    const int images = g.N - n0 < g.b ? g.N - n0 : g.b;
-    const unsigned long long xbase = reinterpret_cast<unsigned long long>(x + (size_t)n0 * g.C * g.H * g.W);
-    const unsigned xlo = __builtin_amdgcn_readfirstlane((unsigned)xbase), xhi = __builtin_amdgcn_readfirstlane((unsigned)(xbase >> 32));
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        reinterpret_cast<void*>((unsigned long long)xhi << 32 | xlo), 0, (int)__builtin_amdgcn_readfirstlane(img * (unsigned)images), 0x00020000);
-    const int cstep = g.hwc ? 4 : 4 * g.H * g.W;
+    const __amdgpu_buffer_rsrc_t rs = image_buffer(x, g, n0);
 
     // staging of chunk ch, batch b (IB items per thread): loads now, split and LDS writes one slot later
     float xv[IB][8];
     unsigned xdst[IB];
     const int batches = __builtin_amdgcn_readfirstlane((items + T * IB - 1) / (T * IB));
     auto load_batch = [&](int ch, int b) {
-        const int c0 = ch < nchunks ? ch * 8 * CH8 : 0, have = ch < nchunks ? g.C - c0 : 0;
+        const int c0 = ch < nchunks ? ch * 8 * CH8 : 0, have = ch < nchunks ? C - c0 : 0;
 #pragma unroll
         for (int i = 0; i < IB; ++i) {
             const int it = (b * IB + i) * T + tid;
@@ -167,7 +175,7 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
                     // the scalar offset stays inside the buffer, whatever the lanes do
-                    const int cj = c0 + j < g.C ? c0 + j : g.C - 1;
+                    const int cj = c0 + j < C ? c0 + j : C - 1;
                     xv[i][j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, left > j ? (int)e.x : (int)OUTSIDE, cj * cstep, 0));
                 }
             }
@@ -293,63 +301,99 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
     }
 
     // each partial sum is complete: write the block once.  Register i of a 16 x 16 block holds channel 4 grp + i of
-    // pixel l16.  Sums that are not finite are marked and computed again below.
+    // pixel l16.  Sums that are not finite are marked.
     const size_t PQ = (size_t)g.P * g.Q;
     unsigned long long again = 0;
     static_assert(MB * NB * 4 <= 64, "one mark per output");
+    auto write_y = [&](auto marked_c) {
+        constexpr bool MARKED = decltype(marked_c)::value;  // the second time: marked outputs only
+        const int l16 = opaque(lane) & 15, grp = opaque(lane) >> 4;
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        const int slot = (wn_i * NB + nb) * 16 + l16;
-        const int im = slot / txy, rem = slot % txy, py = y0 + rem / g.tx, px = x0 + rem % g.tx;
-        if (slot >= npix || n0 + im >= g.N || py >= g.P || px >= g.Q) continue;
+        for (int nb = 0; nb < NB; ++nb) {
+            const int slot = (wn_i * NB + nb) * 16 + l16;
+            const int im = slot / txy, rem = slot % txy, py = y0 + rem / g.tx, px = x0 + rem % g.tx;
+            if (slot >= npix || n0 + im >= g.N || py >= g.P || px >= g.Q) continue;
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-            const int k0 = (kb16 + mb) * 16 + 4 * grp;
+            for (int mb = 0; mb < MB; ++mb) {
+                const int k0 = (kb16 + mb) * 16 + 4 * grp, bit = (nb * MB + mb) * 4;
+                if constexpr (!MARKED) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if (!(__builtin_fabsf(acc[mb][nb][i]) <= 3.402823466e38f)) again |= 1ull << ((nb * MB + mb) * 4 + i);
-                acc[mb][nb][i] *= SPLIT_UNSCALE;
-            }
-            if (g.hwc) {
-                float* yp = y + (((size_t)(n0 + im) * g.P + py) * g.Q + px) * g.K + k0;
-                if (g.vec_out && k0 + 3 < g.K) {
-                    *reinterpret_cast<f32x4*>(yp) = acc[mb][nb];
+                    for (int i = 0; i < 4; ++i) {
+                        if (!(__builtin_fabsf(acc[mb][nb][i]) <= 3.402823466e38f)) again |= 1ull << (bit + i);
+                        acc[mb][nb][i] *= SPLIT_UNSCALE;
+                    }
+                }
+                if (g.hwc) {
+                    float* yp = y + (((size_t)(n0 + im) * g.P + py) * g.Q + px) * g.K + k0;
+                    if (!MARKED && g.vec_out && k0 + 3 < g.K) {
+                        *reinterpret_cast<f32x4*>(yp) = acc[mb][nb];
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (k0 + i < g.K && (!MARKED || again >> (bit + i) & 1)) yp[i] = acc[mb][nb][i];
+                    }
                 } else {
+                    float* yp = y + ((size_t)(n0 + im) * g.K + k0) * PQ + (size_t)py * g.Q + px;
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
-                        if (k0 + i < g.K) yp[i] = acc[mb][nb][i];
+                        if (k0 + i < g.K && (!MARKED || again >> (bit + i) & 1)) yp[(size_t)i * PQ] = acc[mb][nb][i];
                 }
-            } else {
-                float* yp = y + ((size_t)(n0 + im) * g.K + k0) * PQ + (size_t)py * g.Q + px;
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (k0 + i < g.K) yp[(size_t)i * PQ] = acc[mb][nb][i];
             }
         }
+    };
+    write_y(std::false_type{});
+    if (__builtin_amdgcn_ballot_w64(again != 0) == 0) return;
+
+    // A wave with a marked output takes its whole block again on the fp32 matrix instructions, which hold their sums in
+    // the same registers: in the same steps, four units of eight channels, the inputs from memory, those of the next 16
+    // pixels while the present ones are multiplied.  Bound by the latency of a step's loads, at most once per wave: 64 -> 64
+    // at 56 x 56, batch 8, all inputs NaN 40 -> 89 us (one output at a time in its lane: 3081), one NaN 53 (1234); 256 ->
+    // 256 at 56 x 56, batch 64, all NaN 3516 against 1891 on the fp32 tile.
+    // (a descriptor of its own: kept through the matrix loop, the first one would end in vector registers)
+    const __amdgpu_buffer_rsrc_t rs2 = image_buffer(x, g, __builtin_amdgcn_readfirstlane(opaque(n0)));
+    const int lane2 = opaque(lane), col16 = lane2 & 15, unit0 = lane2 >> 4;
+    int cy[NB], cx[NB], ci[NB];                             // window corner and image of this lane's pixels
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        const int slot = (wn_i * NB + nb) * 16 + col16, pix = slot < npix ? slot : npix - 1, rem = pix % txy;
+        ci[nb] = pix / txy;
+        cy[nb] = gy0 + rem / g.tx * g.stride;
+        cx[nb] = gx0 + rem % g.tx * g.stride;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    while (again) {
-        const int bit = __builtin_ctzll(again);
-        again &= again - 1;
-        const int nb = bit / (4 * MB), mb = bit / 4 % MB, i = bit & 3;
-        const int slot = (wn_i * NB + nb) * 16 + l16;
-        const int im = slot / txy, rem = slot % txy, py = y0 + rem / g.tx, px = x0 + rem % g.tx;
-        const int row = 4 * grp + i, k = (kb16 + mb) * 16 + row;
-        if (k >= g.K) continue;
-        const unsigned short* wk = reinterpret_cast<const unsigned short*>(wt + (size_t)(kb16 + mb) * 192);
-        float sum = 0.f;
-        for (int c = 0; c < g.C; ++c)
-            for (int tap = 0; tap < RS; ++tap) {
-                // zeros around the image are operands like others (0 times an infinite weight is NaN)
-                const int gy = py * g.stride - g.pad + tap / g.S, gx = px * g.stride - g.pad_w + tap % g.S;
-                const bool inside = gy >= 0 && gy < g.H && gx >= 0 && gx < g.W;
-                const int u = tap * CH8 + c / 8 % CH8, ln = (u & 3) * 16 + row;
-                const unsigned short* q = wk + ((size_t)(c / (8 * CH8)) * steps + (u >> 2)) * wstep * 8 + ln * 8 + c % 8;
-                const size_t xi = g.hwc ? (((size_t)(n0 + im) * g.H + gy) * g.W + gx) * g.C + c
-                                      : (((size_t)(n0 + im) * g.C + c) * g.H + gy) * g.W + gx;
-                sum = __builtin_fmaf(inside ? x[xi] : 0.f, kept_value(q[0], q[512], q[1024]), sum);
-            }
-        y[g.hwc ? (((size_t)(n0 + im) * g.P + py) * g.Q + px) * g.K + k : ((size_t)(n0 + im) * g.K + k) * PQ + (size_t)py * g.Q + px] = sum;
+    const u32x4* wq = wt + (size_t)kb16 * 192 + lane2;
+#pragma unroll 1
+    for (int s = 0; s < total; ++s, wq += wstep) {
+        const int unit = s % steps * 4 + unit0, tap = unit / CH8, c0 = (s / steps * CH8 + unit % CH8) * 8;
+        const int r = tap / g.S, col = tap % g.S;
+        float wv[MB][8], v[2][8];
+        auto load_v = [&](float (&to)[8], int cyn, int cxn, int cin) {
+            const int gy = cyn + r, gx = cxn + col;
+            const bool inside = tap < RS && n0 + cin < g.N && gy >= 0 && gy < g.H && gx >= 0 && gx < g.W;
+            const unsigned at = g.hwc ? 4u * (unsigned)(((cin * g.H + gy) * g.W + gx) * C + c0) : 4u * (unsigned)(((cin * C + c0) * g.H + gy) * g.W + gx);
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                to[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs2, inside && c0 + j < C ? (int)(at + j * (unsigned)cstep) : (int)OUTSIDE, 0, 0));
+        };
+        load_v(v[0], cy[0], cx[0], ci[0]);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            kept_eight(wq[mb * 192], wq[mb * 192 + 64], wq[mb * 192 + 128], wv[mb]);
+            if constexpr (MB > 2) __builtin_amdgcn_sched_barrier(0);       // all pieces at once would not fit the registers
+        }
+        static_for<0, NB>([&](auto nb_c) {
+            constexpr int nb = decltype(nb_c)::value;
+            if constexpr (nb + 1 < NB) load_v(v[(nb + 1) & 1], cy[nb + 1], cx[nb + 1], ci[nb + 1]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[mb][j], v[nb & 1][j], acc[mb][nb], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        });
     }
+    write_y(std::true_type{});
 }
 
 // w[K][C][R][S] -> the operands of the matrix steps, [chunk][step][16-channel block][part][lane][8 bf16].  One
@@ -432,7 +476,7 @@ hipError_t launch_split_conv(const float* x, const void* wt, float* y, const Spl
     // what the kernel assumes of its geometry
     if (g.b * g.tx * g.ty > 16 * g.nb * g.wn || split_lds_bytes(g) > 160 * 1024 || g.Kb16 != g.nbk * g.mb * g.wm ||
         (split_chunks(g) > 1 && split_batches(g) > split_steps(g)) || g.nbuf < (split_chunks(g) > 1 ? 2 : 1) || g.nbuf > 2 || g.ch8 < 1 || g.ch8 > 8 ||
-        4LL * g.b * g.C * g.H * g.W >= (1LL << 31) || (g.vec_in && (!g.hwc || g.C % 4)))
+        4LL * g.b * g.C * g.H * g.W >= (1LL << 31) || g.cstep != (g.hwc ? 4 : 4 * g.H * g.W) || (g.vec_in && (!g.hwc || g.C % 4)))
         return hipErrorInvalidValue;
     const u32x4* w = static_cast<const u32x4*>(wt);
     return g.vec_in ? launch_shape<true>(x, w, y, g, st) : launch_shape<false>(x, w, y, g, st);

@@ -76,6 +76,7 @@ struct SplitGeom {
     int Kb16;                  // 16-channel blocks, whole workgroup blocks
     int k_outer;               // blocks of one channel block are neighbours, not those of the same pixels
     int hwc, vec_in, vec_out;  // channels innermost; with 16-byte loads / stores of four channels
+    int cstep;                 // bytes from an input channel to the next
 };
 constexpr int SPLIT_BATCH = 2;          // (pixel, 8 channels) items of the input tile that a thread stages at once
 // The workgroup shapes that exist: blocks per wave (channels, pixels), wave grid (channels, pixels).

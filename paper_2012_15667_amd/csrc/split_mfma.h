@@ -16,6 +16,14 @@ namespace iolb {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+// The same value, of which the compiler does not know that: what is derived from it is computed where it is used and
+// not kept in registers from an equal expression before (here: through the matrix loop).
+__device__ __forceinline__ int opaque(int v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
@@ -77,6 +85,16 @@ __device__ __forceinline__ float kept_value(unsigned h, unsigned m, unsigned l)
 {
     const float parts = __uint_as_float(h << 16) + (__uint_as_float(m << 16) + __uint_as_float(l << 16));
     return h == 0x7fc0 ? __uint_as_float(m << 16 | l) : parts * (1.f / SPLIT_SCALE);
+}
+
+// Eight of them from the three pieces of a lane.
+__device__ __forceinline__ void kept_eight(const u32x4& h, const u32x4& m, const u32x4& l, float (&v)[8])
+{
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        v[2 * j] = kept_value(h[j] & 0xffffu, m[j] & 0xffffu, l[j] & 0xffffu);
+        v[2 * j + 1] = kept_value(h[j] >> 16, m[j] >> 16, l[j] >> 16);
+    }
 }
 
 }  // namespace iolb

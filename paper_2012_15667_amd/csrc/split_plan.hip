@@ -33,6 +33,7 @@ bool split_derive(SplitGeom* g)
     g->nbuf = split_chunks(*g) > 1 ? 2 : 1;
     if (g->b * g->tx * g->ty > 16 * g->nb * g->wn) return false;
     if (4LL * g->b * g->C * g->H * g->W >= (1LL << 31)) return false;
+    g->cstep = g->hwc ? 4 : 4 * g->H * g->W;
     if (split_chunks(*g) > 1 && split_batches(*g) > split_steps(*g)) return false;
     // Sixteen lanes read 16 bytes each of consecutive pixels, 48 bytes apart: that covers every LDS bank once.  A row
     // pitch that is congruent to the bytes of a tile row modulo the 256 bytes of the banks keeps it so across a row

@@ -226,55 +226,82 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
     }
 
     // each partial sum is complete: write the block once.  Register i of a 16 x 16 block holds channel 4 grp + i of
-    // pixel l16.  Sums that are not finite are marked and computed again below.
+    // pixel l16.  Sums that are not finite are marked.
     unsigned long long again = 0;
     static_assert(MB * NB * 4 <= 64, "one mark per output");
+    auto write_y = [&](auto marked_c) {
+        constexpr bool MARKED = decltype(marked_c)::value;  // the second time: marked outputs only
+        const int l16 = opaque(lane) & 15, grp = opaque(lane) >> 4;
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        const int px = (wn_i * NB + nb) * 16 + l16;
-        if (px >= left_px) continue;
-        const int n = n0 + (p0 + px) / g.HW, r = (p0 + px) % g.HW;
+        for (int nb = 0; nb < NB; ++nb) {
+            const int px = (wn_i * NB + nb) * 16 + l16;
+            if (px >= left_px) continue;
+            const int n = n0 + (p0 + px) / g.HW, r = (p0 + px) % g.HW;
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-            const int k0 = (kb16 + mb) * 16 + 4 * grp;
+            for (int mb = 0; mb < MB; ++mb) {
+                const int k0 = (kb16 + mb) * 16 + 4 * grp, bit = (nb * MB + mb) * 4;
+                if constexpr (!MARKED) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if (!(__builtin_fabsf(acc[mb][nb][i]) <= 3.402823466e38f)) again |= 1ull << ((nb * MB + mb) * 4 + i);
-                acc[mb][nb][i] *= SPLIT_UNSCALE;
-            }
-            if (g.hwc) {
-                float* yp = y + ((size_t)n * g.HW + r) * g.K + k0;
-                if (g.vec_out && k0 + 3 < g.K) {
-                    *reinterpret_cast<f32x4*>(yp) = acc[mb][nb];
+                    for (int i = 0; i < 4; ++i) {
+                        if (!(__builtin_fabsf(acc[mb][nb][i]) <= 3.402823466e38f)) again |= 1ull << (bit + i);
+                        acc[mb][nb][i] *= SPLIT_UNSCALE;
+                    }
+                }
+                if (g.hwc) {
+                    float* yp = y + ((size_t)n * g.HW + r) * g.K + k0;
+                    if (!MARKED && g.vec_out && k0 + 3 < g.K) {
+                        *reinterpret_cast<f32x4*>(yp) = acc[mb][nb];
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (k0 + i < g.K && (!MARKED || again >> (bit + i) & 1)) yp[i] = acc[mb][nb][i];
+                    }
                 } else {
+                    float* yp = y + ((size_t)n * g.Ky + k0) * g.HWy + r;
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
-                        if (k0 + i < g.K) yp[i] = acc[mb][nb][i];
+                        if (k0 + i < g.K && (!MARKED || again >> (bit + i) & 1)) yp[(size_t)i * g.HWy] = acc[mb][nb][i];
                 }
-            } else {
-                float* yp = y + ((size_t)n * g.Ky + k0) * g.HWy + r;
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (k0 + i < g.K) yp[(size_t)i * g.HWy] = acc[mb][nb][i];
             }
         }
-    }
-    while (again) {
-        const int bit = __builtin_ctzll(again);
-        again &= again - 1;
-        const int nb = bit / (4 * MB), mb = bit / 4 % MB, i = bit & 3;
-        const int px = (wn_i * NB + nb) * 16 + l16, n = n0 + (p0 + px) / g.HW, r = (p0 + px) % g.HW;
+    };
+    write_y(std::false_type{});
+    if (__builtin_amdgcn_ballot_w64(again != 0) == 0) return;
+
+    // A wave with a marked output takes its whole block again on the fp32 matrix instructions, which hold their sums in
+    // the same registers; the inputs come from memory.
+    const int lane2 = opaque(lane), col16 = lane2 & 15, c0 = 8 * (lane2 >> 4);
+    unsigned at[NB];                                        // this lane's pixels, first channel of its group
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        const int px = (wn_i * NB + nb) * 16 + col16, q = p0 + px, im = q / g.HW, r = q % g.HW;
         const int in = g.stride == 1 ? r : r / g.Q * g.stride * g.Win + r % g.Q * g.stride;
-        const int row = 4 * grp + i, k = (kb16 + mb) * 16 + row;
-        if (k >= g.K) continue;
-        const unsigned short* wk = reinterpret_cast<const unsigned short*>(wt + (size_t)group * g.w_image + (size_t)(kb16 + mb) * 192);
-        float sum = 0.f;
-        for (int c = 0; c < g.C; ++c) {
-            const unsigned short* q = wk + (size_t)(c >> 5) * wstep * 8 + ((c >> 3 & 3) * 16 + row) * 8 + (c & 7);
-            sum = __builtin_fmaf(x[g.hwc ? ((size_t)n * g.HWin + in) * g.C + c : ((size_t)n * g.C + c) * g.HWin + in], kept_value(q[0], q[512], q[1024]), sum);
-        }
-        y[g.hwc ? ((size_t)n * g.HW + r) * g.K + k : ((size_t)n * g.Ky + k) * g.HWy + r] = sum;
+        at[nb] = px >= left_px ? OUTSIDE : g.hwc ? 4u * (unsigned)((im * g.HWin + in) * g.C + c0) : 4u * (unsigned)((im * g.C + c0) * g.HWin + in);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
+    const u32x4* wq = wt + (size_t)group * g.w_image + (size_t)kb16 * 192 + lane2;
+#pragma unroll 1
+    for (int ch = 0; ch < nchunks; ++ch, wq += wstep) {
+        float wv[MB][8];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) kept_eight(wq[mb * 192], wq[mb * 192 + 64], wq[mb * 192 + 128], wv[mb]);
+        static_for<0, NB>([&](auto nb_c) {
+            constexpr int nb = decltype(nb_c)::value;
+            float v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int c = 32 * ch + j;                  // relative to the lane group's first
+                v[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                    rs, at[nb] != OUTSIDE && c + c0 < g.C ? (int)(at[nb] + c * (unsigned)cstep) : (int)OUTSIDE, 0, 0));
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[mb][j], v[j], acc[mb][nb], 0, 0, 0);
+        });
+    }
+    write_y(std::true_type{});
 }
 
 template <int MB, int NB, int WM, int WN, int IN>

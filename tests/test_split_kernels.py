@@ -185,6 +185,47 @@ def test_winograd_product_over_the_whole_range(gpu, scales):
     assert rel_err(B.conv_winograd_pre(xd, U, K, 2).cpu().numpy(), ref) <= GUARD_WINO[2]
 
 
+@pytest.mark.parametrize("case", CASES)
+def test_sums_taken_again_in_every_shape_and_layout(gpu, case):
+    """Operands beyond what the parts hold: every output comes from the second, plain fp32, pass over its block."""
+    torch, B = gpu
+    N, C, H, W, K, R, S, stride, pad = case
+    x, w = make_inputs(N, C, H, W, K, R, S, "u11", "he", seed=sum(case) + 1)
+    x = (x + np.copysign(np.float32(0.5), x)) * np.float32(1e32)
+    ref, lim = conv_ref(x, w, stride, pad), _bound(x, w, stride, pad)
+    wd = torch.from_numpy(w).cuda()
+    y = B.conv_direct(torch.from_numpy(x).cuda(), wd, stride, pad).cpu().numpy()
+    assert (np.abs(y - ref) <= lim).all()
+    xh = np.ascontiguousarray(x.transpose(0, 2, 3, 1))
+    yh = B.conv_direct_layout(torch.from_numpy(xh).cuda(), wd, stride, pad, B.LAYOUT_HWC).cpu().numpy()
+    assert np.array_equal(yh, y.transpose(0, 2, 3, 1))
+    xt = np.ascontiguousarray(x.transpose(0, 1, 3, 2))
+    yt = B.conv_direct_layout(torch.from_numpy(xt).cuda(), wd, stride, pad, B.LAYOUT_CWH).cpu().numpy()
+    assert (np.abs(yt - conv_ref_cwh(xt, w, stride, pad)) <= lim.transpose(0, 1, 3, 2)).all()
+
+
+@pytest.mark.parametrize("case", [(12, 768, 17, 17, 192, 1, "chw"), (2, 161, 64, 65, 400, 1, "chw"), (70, 515, 7, 5, 500, 1, "chw"),
+                                  (4, 300, 61, 61, 450, 2, "chw"), (12, 770, 17, 17, 191, 1, "hwc"), (4, 300, 61, 61, 452, 2, "hwc")])
+def test_pointwise_sums_taken_again(gpu, case):
+    """One image with operands beyond the parts' range: its outputs are taken again, those of its neighbours keep their bits."""
+    torch, B = gpu
+    N, C, H, W, K, stride, layout = case
+    lay = B.LAYOUT_HWC if layout == "hwc" else B.LAYOUT_CHW
+    assert B.iolb_route(B.make_shape(N, C, H, W, K, 1, 1, stride, 0), lay)[0] == B.ROUTE_SPLIT
+    x, w = make_inputs(N, C, H, W, K, 1, 1, "u11", "he", seed=N + C + 1)
+    xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+    big = xd.clone()
+    big[1] = (big[1] + torch.copysign(torch.full_like(big[1], 0.5), big[1])) * 1e32
+    P, Q = (H - 1) // stride + 1, (W - 1) // stride + 1
+    run = lambda a: (B.conv_direct(a, wd, stride, 0) if layout == "chw" else
+                     B.conv_direct_layout(a.permute(0, 2, 3, 1).contiguous(), wd, stride, 0, lay).permute(0, 3, 1, 2))
+    y, z = run(xd), run(big)
+    assert torch.equal(y[0], z[0]) and torch.equal(y[2:], z[2:])
+    xs, wk = big[1, :, ::stride, ::stride].double().flatten(1), wd.double().view(K, C)
+    lim = (12 * -(-C // 8) + 16) * 2.0 ** -23 * (wk.abs() @ xs.abs())
+    assert bool(((z[1].double().flatten(1) - wk @ xs).abs() <= lim).all())
+
+
 def test_zeros_around_the_image_meet_infinite_weights(gpu):
     """The border is made of zeros that are multiplied like other operands: 0 times an infinite weight is NaN."""
     torch, B = gpu
