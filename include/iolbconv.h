@@ -12,7 +12,8 @@
  * library keeps one workspace per (GPU, stream), so calls on different streams do not share scratch memory;
  * calls on one stream are ordered by the stream.  A call that does not have to grow its stream's workspace
  * enqueues kernels only (no allocation, no memset, no synchronisation), so after one eager call for the same
- * layer on the same stream it can be recorded by a stream capture and replayed as a graph.  A workspace that
+ * layer on the same stream it can be recorded by a stream capture and replayed as a graph.  One that has to grow it
+ * while the stream is captured allocates there and then; the graph holds its kernels only.  A workspace that
  * has to grow is replaced, never freed before iolb_release_workspace, so kernels in flight and graphs captured
  * earlier keep valid addresses; iolb_release_workspace invalidates such graphs.
  *
@@ -98,7 +99,7 @@ typedef struct iolb_bounds_out {
  * conv_winograd_pad, and conv_winograd_ws / _pre with cfg NULL): every operand as the sum of three bf16 parts, six
  * products of parts, fp32 sums -- no less precise than fp32 products.  Their blocks are not tiles of the enumeration;
  * a caller-supplied tile always runs on the fp32 kernels.  Infinities, NaN, operands from 4e31 and sums from 5e24
- * on give what fp32 sums give, at up to 3.5 times the layer's time where every output is such. */
+ * on give what fp32 sums give, at about four times the layer's time where every output is such. */
 int conv_direct(const float* x, const float* w, float* y,
                 int N, int C, int H, int W, int K, int R, int S, int stride, int pad);
 

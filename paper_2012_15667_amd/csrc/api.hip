@@ -71,7 +71,13 @@ int ensure_workspace(DeviceState* d, size_t bytes, void** out)
     Workspace& w = d->ws[t_stream];
     if (w.bytes < bytes) {
         void* p = nullptr;
-        IOLB_HIP(hipMalloc(&p, bytes));
+        // also while the stream is being captured (the graph holds kernels only): layers that run in place on the fp32
+        // kernels, without scratch, need some on the split ones, and such a layer's first call may be a captured one
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        IOLB_HIP(hipThreadExchangeStreamCaptureMode(&mode));
+        const hipError_t e = hipMalloc(&p, bytes);
+        IOLB_HIP(hipThreadExchangeStreamCaptureMode(&mode));
+        if (e != hipSuccess) return hip_fail(e);
         if (w.ptr) d->retired.push_back(w.ptr);
         w.ptr = p;
         w.bytes = bytes;

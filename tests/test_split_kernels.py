@@ -284,3 +284,27 @@ def test_split_layers_through_the_call_that_allocates_nothing(gpu):
     assert e.value.code == -4 and bool((y == 3.0).all())
     B.conv_direct(xd, wd, 1, 1, y=y)
     assert rel_err(y.cpu().numpy(), conv_ref(x, w, 1, 1)) <= 3e-5
+
+
+def test_first_call_of_a_pointwise_layer_may_be_a_captured_one(gpu):
+    """A 1 x 1 layer whose fp32 kernel reads the weights in place could always be captured without an eager call before
+    it on the stream; its split kernel needs scratch."""
+    torch, B = gpu
+    N, C, H, K = 12, 768, 17, 192
+    assert B.iolb_route(B.make_shape(N, C, H, H, K, 1, 1, 1, 0))[0] == B.ROUTE_SPLIT
+    x, w = make_inputs(N, C, H, H, K, 1, 1, "u01", "he", seed=8)
+    xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+    y = torch.empty((N, K, H, H), device="cuda")
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    B.release_workspace()                                   # no stream has any
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        B.conv_direct(xd, wd, 1, 0, y=y)
+    for rep in range(3):
+        xd.copy_(torch.rand(xd.shape, device="cuda"))
+        y.fill_(-1.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, B.conv_direct(xd, wd, 1, 0)), rep
+        torch.cuda.synchronize()
