@@ -504,12 +504,12 @@ struct SplitWino {
     bool use = false;
     iolb::SplitPointGeom g{};
     iolb::WinoGeom w{};
-    size_t u_off = 0, v_off = 0, m_off = 0, total = 0;
+    size_t u_off = 0, v_off = 0, m_off = 0, total = 0;        // total: the least workspace, the tile's if that is larger
 };
 std::map<ShapeKey, SplitWino> g_split_wino;
 
-// tile: the library's own choice for the layer.  The split product takes over where its modelled time beats that
-// of the tile.
+// tile: the library's own choice for the layer.  The split product takes over where its modelled time beats that of the
+// tile.  What the tile's path refuses (tensors beyond its 32-bit indexes, a workspace too small for it) stays refused.
 SplitWino split_wino(const iolb_shape& s, const iolb_tile_config& tile)
 {
     const ShapeKey key(s.N, s.C, s.H, s.W, s.K, s.R, s.S, s.stride, s.pad, s.algo);
@@ -518,6 +518,8 @@ SplitWino split_wino(const iolb_shape& s, const iolb_tile_config& tile)
         auto it = g_split_wino.find(key);
         if (it != g_split_wino.end()) return it->second;
     }
+    iolb::WinoGeom t{};
+    const bool tile_runs = winograd_geom(s, tile, &t) == IOLB_OK;
     SplitWino r;
     iolb::WinoGeom& w = r.w;
     w.N = s.N; w.C = w.Cp = s.C; w.H = s.H; w.W = s.W; w.K = w.Kp = s.K; w.m = iolb::winograd_m(s.algo); w.pad = s.pad;
@@ -525,7 +527,7 @@ SplitWino split_wino(const iolb_shape& s, const iolb_tile_config& tile)
     w.th = (w.P + w.m - 1) / w.m; w.tw = (w.Q + w.m - 1) / w.m;
     const int64_t tiles = (int64_t)s.N * w.th * w.tw, pitch = (tiles + 3) / 4 * 4, n2 = (int64_t)(w.m + 2) * (w.m + 2);
     double cycles = 0;
-    if (tile.path != IOLB_PATH_FMA && n2 * std::max(s.C, s.K) * pitch < (1LL << 31) && s.C <= 32768 && s.K <= 65535) {
+    if (tile_runs && tile.path != IOLB_PATH_FMA && n2 * std::max(s.C, s.K) * pitch < (1LL << 31) && s.C <= 32768 && s.K <= 65535) {
         w.tiles = (int)tiles; w.tiles_pitch = (int)pitch;
         iolb::SplitPointGeom& g = r.g;
         g.groups = (int)n2; g.images = 1; g.C = s.C; g.K = g.Ky = s.K; g.HW = (int)tiles; g.HWy = g.HWin = (int)pitch; g.Win = g.Q = (int)tiles;
@@ -537,6 +539,7 @@ SplitWino split_wino(const iolb_shape& s, const iolb_tile_config& tile)
             r.v_off = align256((size_t)n2 * iolb::split_point_weight_bytes(g));
             r.m_off = r.v_off + align256(sizeof(float) * n2 * s.C * pitch);
             r.total = r.m_off + align256(sizeof(float) * n2 * s.K * pitch);
+            r.total = std::max(r.total, winograd_layout(t.Cp, t.Kp, t.m, t.tiles_pitch, tile.path).total);
             r.use = r.total <= winograd_workspace_max(s.C, s.K, w.m, tiles) && iolb::split_wino_faster(s, tile, tiles, cycles);
         }
     }

@@ -308,3 +308,30 @@ def test_first_call_of_a_pointwise_layer_may_be_a_captured_one(gpu):
         torch.cuda.synchronize()
         assert torch.equal(y, B.conv_direct(xd, wd, 1, 0)), rep
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("m,N,C,H,W,K", [(4, 9, 277, 35, 37, 233), (2, 64, 512, 7, 7, 512), (6, 5, 284, 29, 30, 497)])
+def test_a_workspace_too_small_for_the_tuned_tile_stays_refused(gpu, m, N, C, H, W, K):
+    torch, B = gpu
+    shape = B.make_shape(N, C, H, W, K, algo=B.WINO_ALGO[m])
+    route, need = B.iolb_route(shape)
+    assert route == B.ROUTE_SPLIT
+    x, w = torch.rand((N, C, H, W), device="cuda"), torch.randn((K, C, 3, 3), device="cuda")
+    tile = B.iolb_tune(shape)
+    ws = torch.empty(B.winograd_workspace_bytes(N, C, H, W, K, m), dtype=torch.uint8, device="cuda")
+
+    def taken(size, **kw):
+        try:
+            B.conv_winograd(x, w, m, workspace=ws[:size], **kw)
+        except B.IolbError as e:
+            assert e.code == -4
+            return False
+        return True
+
+    # the tile's own size, to 256 bytes
+    lo, hi = 0, ws.numel() // 256
+    while lo + 1 < hi:
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if taken(256 * mid, cfg=tile) else (mid, hi)
+    assert taken(256 * hi) and not taken(256 * lo)
+    assert need >= 256 * hi and taken(need)
