@@ -9,7 +9,7 @@ from tests.conftest import rel_err
 
 pytestmark = pytest.mark.gpu
 
-GUARD_WINO = {2: 5e-5, 4: 5e-4}          # as in test_gpu_parity.py
+GUARD_WINO = {2: 5e-5, 3: 3e-4, 4: 5e-4, 6: 6e-4}          # as in test_gpu_parity.py
 
 
 @pytest.fixture(scope="module")
@@ -36,25 +36,29 @@ CASES = [
     (1, 9, 7, 7, 1, 3, 3, 1, 1),            # second channel group nearly empty, one kernel
     (2, 16, 9, 8, 15, 3, 3, 1, 1),          # exactly one chunk of 16: a single LDS buffer
     (2, 17, 12, 11, 17, 3, 3, 1, 1),        # one channel and one kernel over a block
-    (1, 33, 5, 6, 130, 3, 3, 1, 0),         # chunk of 32 and one channel; K over 128
+    (1, 33, 9, 10, 130, 3, 3, 1, 0),        # chunk of 32 and one channel; K over 128
     (3, 40, 14, 14, 64, 3, 3, 1, 1),        # whole images in a block, several images
     (5, 48, 7, 7, 96, 3, 3, 1, 1),          # batch not a multiple of the images per block
     (2, 31, 23, 29, 24, 3, 3, 2, 1),        # stride 2: residue classes of odd width
     (1, 20, 31, 30, 40, 2, 2, 3, 0),        # stride beyond the kernel: rows and columns nobody uses
     (2, 24, 17, 17, 32, 1, 7, 1, 0),        # one-sided kernels (no padding here)
     (2, 24, 17, 17, 32, 7, 1, 1, 0),
-    (2, 64, 1, 1, 32, 3, 3, 1, 1),          # a single pixel
+    (20, 64, 1, 1, 32, 3, 3, 1, 1),         # a single pixel per image
     (2, 12, 35, 20, 20, 5, 5, 1, 2),
     (2, 3, 51, 47, 30, 11, 11, 4, 0),       # three channels: products summed apart per step
     (1, 5, 30, 30, 64, 7, 7, 2, 3),
     (2, 8, 19, 19, 33, 5, 5, 1, 2),
 ]
+# fewer than 16 pixels in all: no block of the split kernel is half full, the tuned tile stays
+FEW_PIXELS = [(1, 33, 5, 6, 130, 3, 3, 1, 0), (2, 64, 1, 1, 32, 3, 3, 1, 1)]
 
 
-@pytest.mark.parametrize("case", CASES)
+@pytest.mark.parametrize("case", CASES + FEW_PIXELS)
 def test_split_direct_layouts_within_the_bound(gpu, case):
     torch, B = gpu
     N, C, H, W, K, R, S, stride, pad = case
+    for layout in (B.LAYOUT_CHW, B.LAYOUT_HWC, B.LAYOUT_CWH):
+        assert B.iolb_route(B.make_shape(*case), layout)[0] == (B.ROUTE_TILE if case in FEW_PIXELS else B.ROUTE_SPLIT)
     x, w = make_inputs(N, C, H, W, K, R, S, "u11", "he", seed=sum(case))
     ref, lim = conv_ref(x, w, stride, pad), _bound(x, w, stride, pad)
     wd = torch.from_numpy(w).cuda()
@@ -68,6 +72,25 @@ def test_split_direct_layouts_within_the_bound(gpu, case):
     xt = np.ascontiguousarray(x.transpose(0, 1, 3, 2))
     yt = B.conv_direct_layout(torch.from_numpy(xt).cuda(), wd, stride, pad, B.LAYOUT_CWH).cpu().numpy()
     assert (np.abs(yt - conv_ref_cwh(xt, w, stride, pad)) <= lim.transpose(0, 1, 3, 2)).all()
+
+
+@pytest.mark.parametrize("layer", [(4, 24, 18, 18, 40, 3, 1), (4, 3, 24, 24, 40, 7, 3), (12, 768, 17, 17, 192, 1, 0)])
+def test_single_products_have_fp32_precision(gpu, layer):
+    """One channel and one tap are not zero, so that every output is one product x w of full 24-bit operands.  Of its nine
+    products of parts three are left out: m l and l m, each at most 2^-8 2^-16 of it, and l l: 2^-23.  The other six are
+    added in five roundings of at most 2^-23 of the sum (truncation allowed for); the partial sums exceed the product by
+    no more than 2^-7 of it.  A product left out beside these, h l, l h (2^-17 on average) or m m (2^-18), breaks it."""
+    torch, B = gpu
+    N, C, H, W, K, R, pad = layer
+    assert B.iolb_route(B.make_shape(N, C, H, W, K, R, R, 1, pad))[0] == B.ROUTE_SPLIT
+    g = torch.Generator(device="cuda").manual_seed(C)
+    x = torch.zeros((N, C, H, W), device="cuda")
+    w = torch.zeros((K, C, R, R), device="cuda")
+    x[:, C - 1] = (torch.rand((N, H, W), generator=g, device="cuda") + 1) * torch.where(torch.rand((N, H, W), generator=g, device="cuda") < 0.5, -1.0, 1.0)
+    w[:, C - 1, R // 2, R // 2] = torch.rand(K, generator=g, device="cuda") + 1
+    exact = x[:, C - 1].double()[:, None] * w[:, C - 1, R // 2, R // 2].double()[None, :, None, None]
+    err = ((B.conv_direct(x, w, 1, pad).double() - exact) / exact).abs()
+    assert float(err.max()) <= 2.0 ** -23 * (1 + 5 * (1 + 2.0 ** -7)) and float(err.mean()) <= 2.0 ** -24
 
 
 @pytest.mark.parametrize("offset", [1, 2, 3])
@@ -90,13 +113,13 @@ def test_split_direct_takes_tensors_off_16_byte_boundaries(gpu, offset):
 # large enough for the split 1 x 1 kernel (at least 160 channels, 1 GFLOP, 48 flop per byte)
 POINT_CASES = [
     # N, C, H, W, K, stride, layout
-    (9, 768, 17, 17, 192, 1, "chw"),        # 289 pixels: blocks that end inside an image, pairs over its end
+    (12, 768, 17, 17, 192, 1, "chw"),       # 289 pixels: blocks that end inside an image, pairs over its end
     (2, 161, 64, 65, 400, 1, "chw"),        # ragged channels, K not a multiple of a block
     (60, 515, 6, 6, 500, 1, "chw"),         # blocks over several images
     (70, 515, 7, 5, 500, 1, "chw"),         # the same with an odd number of pixels
     (4, 300, 61, 61, 450, 2, "chw"),        # stride 2: single pixels
-    (9, 768, 17, 17, 192, 1, "hwc"),
-    (9, 770, 17, 17, 191, 1, "hwc"),        # no vector loads or stores
+    (12, 768, 17, 17, 192, 1, "hwc"),
+    (12, 770, 17, 17, 191, 1, "hwc"),       # no vector loads or stores
     (4, 300, 61, 61, 452, 2, "hwc"),
 ]
 
@@ -105,6 +128,7 @@ POINT_CASES = [
 def test_split_pointwise_within_the_bound(gpu, case):
     torch, B = gpu
     N, C, H, W, K, stride, layout = case
+    assert B.iolb_route(B.make_shape(N, C, H, W, K, 1, 1, stride, 0), B.LAYOUT_HWC if layout == "hwc" else B.LAYOUT_CHW)[0] == B.ROUTE_SPLIT
     x, w = make_inputs(N, C, H, W, K, 1, 1, "u11", "he", seed=N + C)
     xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
     xs = xd[:, :, ::stride, ::stride].double().flatten(2).contiguous()
@@ -119,12 +143,13 @@ def test_split_pointwise_within_the_bound(gpu, case):
     assert bool(((y.double() - ref).abs() <= lim).all())
 
 
-@pytest.mark.parametrize("shape", [(2, 24, 12, 13, 20, 3, 1), (2, 3, 40, 40, 16, 11, 0), (9, 768, 17, 17, 192, 1, 0)])
+@pytest.mark.parametrize("shape", [(2, 24, 12, 13, 20, 3, 1), (2, 3, 40, 40, 16, 11, 0), (12, 768, 17, 17, 192, 1, 0)])
 def test_values_whose_parts_are_not_finite_bf16(gpu, shape):
     """Infinities and NaN spread as in plain fp32 sums (0 * inf only where an operand is 0); finite values that round
     to an infinite bf16 and very small sums keep fp32 precision."""
     torch, B = gpu
     N, C, H, W, K, R, pad = shape
+    assert B.iolb_route(B.make_shape(N, C, H, W, K, R, R, 1 if R < 11 else 4, pad))[0] == B.ROUTE_SPLIT
     x, w = make_inputs(N, C, H, W, K, R, R, "u11", "he", seed=5)
     w[np.abs(w) < 1e-3] = 1e-3
     x[np.abs(x) < 1e-3] = 1e-3
@@ -242,11 +267,24 @@ def test_zeros_around_the_image_meet_infinite_weights(gpu):
     assert np.array_equal(np.isnan(y), np.isnan(z)) and np.array_equal(y[np.isinf(z)], z[np.isinf(z)])
 
 
-@pytest.mark.parametrize("m,N,C,H,W,K", [(2, 64, 512, 7, 7, 512), (2, 5, 131, 30, 29, 130), (2, 33, 261, 15, 15, 300), (4, 2, 290, 75, 73, 384)])
-def test_winograd_with_the_split_product(gpu, m, N, C, H, W, K):
-    """Sub-domain counts that are no multiple of four, ragged channels; on the fly, pre-transformed and with a workspace
-    that has only room for the tuned tile."""
+# m, N, C, H, W, K, whether the product is a split one.  Split: ragged channels, kernels and sub-domain counts (not
+# multiples of 32, 16, 4) for every m
+WINO_CASES = [
+    (2, 64, 512, 7, 7, 512, True), (2, 33, 342, 9, 11, 235, True), (2, 9, 179, 21, 20, 510, True), (3, 33, 525, 7, 8, 485, True),
+    (4, 5, 187, 35, 34, 489, True), (4, 9, 277, 35, 37, 233, True), (6, 5, 284, 29, 30, 497, True),
+    (2, 5, 131, 30, 29, 130, False), (2, 33, 261, 15, 15, 300, False), (4, 2, 290, 75, 73, 384, False),
+]
+
+
+@pytest.mark.parametrize("m,N,C,H,W,K,split", WINO_CASES)
+def test_winograd_with_the_split_product(gpu, m, N, C, H, W, K, split):
+    """On the fly, pre-transformed, with the least workspace that takes the split product and with the next smaller one,
+    which keeps the tuned tile."""
     torch, B = gpu
+    shape = B.make_shape(N, C, H, W, K, algo=B.WINO_ALGO[m])
+    route, need = B.iolb_route(shape)
+    assert route == (B.ROUTE_SPLIT if split else B.ROUTE_TILE)
+    needs_as_much = (m, N) == (4, 9)                        # the tuned tile has the larger workspace there
     x, w = make_inputs(N, C, H, W, K, 3, 3, "u01", "he", seed=m + C)
     xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
     ref = torch.zeros(N, K, H, W, dtype=torch.float64, device="cuda")
@@ -265,12 +303,21 @@ def test_winograd_with_the_split_product(gpu, m, N, C, H, W, K):
     assert torch.equal(y, yp)
     ws.fill_(255)
     assert torch.equal(B.conv_winograd(xd, wd, m, workspace=ws), y)
+    if split:
+        ws.fill_(255)
+        assert torch.equal(B.conv_winograd(xd, wd, m, workspace=ws[:need]), y)
+        on_tile = B.conv_winograd(xd, wd, m, cfg=B.iolb_tune(shape))
+        assert not torch.equal(on_tile, y)
+        if not needs_as_much:
+            assert torch.equal(B.conv_winograd(xd, wd, m, workspace=ws[:need - 256]), on_tile)
 
 
 def test_split_layers_through_the_call_that_allocates_nothing(gpu):
     """The same bits as conv_direct up to its limit on the kernels, in three parts too; beyond it the error stays."""
     torch, B = gpu
-    for (N, C, H, W, K, R) in ((1, 640, 5, 5, 704, 3), (2, 20, 12, 12, 40, 5), (9, 768, 17, 17, 192, 1)):
+    # (641 channels: the kernels fit in fp32, but not their parts, which take whole chunks of 32)
+    for (N, C, H, W, K, R, split) in ((1, 640, 5, 5, 704, 3, 1), (1, 641, 9, 9, 704, 3, 0), (2, 20, 12, 12, 40, 5, 1), (12, 768, 17, 17, 192, 1, 1)):
+        assert B.iolb_route(B.make_shape(N, C, H, W, K, R, R, 1, R // 2))[0] == split
         x, w = make_inputs(N, C, H, W, K, R, R, "u01", "he", seed=C)
         xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
         y = B.conv_direct(xd, wd, 1, R // 2)
