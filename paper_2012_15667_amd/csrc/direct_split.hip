@@ -30,21 +30,9 @@ namespace iolb {
 
 namespace {
 
-// voffset of an element that does not exist: beyond every buffer's range, so that the load returns zero
-constexpr unsigned OUTSIDE = 0x80000000u;
-
 // Position of the input tile that staged row / column `i` is taken from, relative to the tile's first: with a
 // stride beyond the kernel extent only the rows and columns that some window covers are staged.
 __device__ __forceinline__ int staged_offset(int i, int est, int stride) { return est == stride ? i : i / est * stride + i % est; }
-
-template <int FROM, int TO, class F>
-__device__ __forceinline__ void static_for(F f)
-{
-    if constexpr (FROM < TO) {
-        f(std::integral_constant<int, FROM>{});
-        static_for<FROM + 1, TO>(f);
-    }
-}
 
 // Buffer of a block's images, first one n0: loads beyond them return zero.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t image_buffer(const float* x, const SplitGeom& g, int n0)
@@ -253,7 +241,7 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
             }
         };
         constexpr int HALF = NB / 2;
-        static_for<0, HALF>(block);
+        static_range<0, HALF>(block);
         // Loads come back in the order they were issued.  Where the paths with and without input loads meet, the
         // compiler would have to assume the worst and wait for every load at the next use of a weight: the two paths
         // stay apart until each has waited for the weights of the next step.
@@ -262,10 +250,10 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
             write_batch(lds + split_buffer(ch + 1, g.nbuf) * buf_bytes);
             const bool more = k + 1 < batches;
             load_batch(more ? ch + 1 : ch + 2, more ? k + 1 : 0);
-            static_for<HALF, NB>(block);
+            static_range<HALF, NB>(block);
             __builtin_amdgcn_s_waitcnt(0x0F70 | ((LATER + LOADS) & 15) | ((LATER + LOADS) >> 4) << 14);
         } else {
-            static_for<HALF, NB>(block);
+            static_range<HALF, NB>(block);
             __builtin_amdgcn_s_waitcnt(0x0F70 | (LATER & 15) | (LATER >> 4) << 14);
         }
         if constexpr (NB & 1) {
@@ -294,7 +282,7 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
         // AHEAD + 1 copies, so that every step names its registers
         bool done = false;
         while (!done)
-            static_for<0, AHEAD + 1>([&](auto i_c) {
+            static_range<0, AHEAD + 1>([&](auto i_c) {
                 constexpr int i = decltype(i_c)::value;
                 if (!done) done = step(a[i], a[(i + AHEAD) % (AHEAD + 1)]);
             });
@@ -382,7 +370,7 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
             kept_eight(wq[mb * 192], wq[mb * 192 + 64], wq[mb * 192 + 128], wv[mb]);
             if constexpr (MB > 2) __builtin_amdgcn_sched_barrier(0);       // all pieces at once would not fit the registers
         }
-        static_for<0, NB>([&](auto nb_c) {
+        static_range<0, NB>([&](auto nb_c) {
             constexpr int nb = decltype(nb_c)::value;
             if constexpr (nb + 1 < NB) load_v(v[(nb + 1) & 1], cy[nb + 1], cx[nb + 1], ci[nb + 1]);
             __builtin_amdgcn_sched_barrier(0);

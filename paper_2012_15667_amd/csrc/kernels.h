@@ -79,16 +79,17 @@ struct SplitGeom {
     int cstep;                 // bytes from an input channel to the next
 };
 constexpr int SPLIT_BATCH = 2;          // (pixel, 8 channels) items of the input tile that a thread stages at once
-// The workgroup shapes that exist: blocks per wave (channels, pixels), wave grid (channels, pixels).
+// The workgroup shapes that exist: blocks per wave (channels, pixels), wave grid (channels, pixels).  Of two with the same
+// workgroup block and blocks per wave, which the planner's model cannot tell apart, there is one.
 #define IOLB_SPLIT_SHAPES(X) \
     X(1, 2, 4, 1) X(1, 4, 4, 1) X(1, 8, 4, 1) X(2, 2, 4, 1) X(2, 4, 4, 1) X(2, 5, 4, 1) X(2, 7, 4, 1) X(2, 8, 4, 1) \
     X(3, 2, 4, 1) X(3, 4, 4, 1) X(4, 2, 4, 1)                                                                       \
-    X(1, 2, 2, 2) X(1, 4, 2, 2) X(1, 7, 2, 2) X(1, 8, 2, 2) X(2, 2, 2, 2) X(2, 4, 2, 2) X(2, 5, 2, 2) X(2, 7, 2, 2) X(2, 8, 2, 2) \
+    X(1, 2, 2, 2) X(1, 4, 2, 2) X(1, 7, 2, 2) X(1, 8, 2, 2) X(2, 5, 2, 2) X(2, 7, 2, 2) X(2, 8, 2, 2)             \
     X(3, 4, 2, 2)                                                                                                   \
-    X(1, 1, 1, 4) X(1, 2, 1, 4) X(1, 4, 1, 4) X(1, 7, 1, 4) X(2, 2, 1, 4) X(2, 4, 1, 4) X(2, 7, 1, 4) X(3, 4, 1, 4)
+    X(1, 1, 1, 4) X(1, 2, 1, 4) X(1, 4, 1, 4) X(1, 7, 1, 4) X(2, 7, 1, 4) X(3, 4, 1, 4)
 // ... and those for layers of at most eight channels (ch8 = 1)
 #define IOLB_SPLIT_FEW_SHAPES(X) \
-    X(1, 2, 4, 1) X(1, 4, 4, 1) X(1, 2, 2, 2) X(1, 4, 2, 2) X(2, 2, 2, 2) X(2, 4, 2, 2) X(1, 2, 1, 4) X(1, 4, 1, 4) X(2, 4, 1, 4)
+    X(1, 2, 4, 1) X(1, 4, 4, 1) X(1, 2, 2, 2) X(1, 4, 2, 2) X(2, 4, 2, 2) X(1, 2, 1, 4) X(1, 4, 1, 4) X(2, 4, 1, 4)
 inline int split_steps(const SplitGeom& g) { return (g.R * g.S * g.ch8 + 3) / 4; }
 inline int split_chunks(const SplitGeom& g) { return (g.C + 8 * g.ch8 - 1) / (8 * g.ch8); }
 inline int split_batches(const SplitGeom& g)
@@ -122,12 +123,12 @@ struct SplitPointGeom {
     long long w_image;         // 16-byte pieces from one group's kernels to the next
     int hwc, in, vec_out;      // in: how the inputs are read, below
 };
-// Inputs read in single floats; four channels at a time (channels innermost, C a multiple of 4, 16-byte aligned); two or
-// four neighbouring pixels at a time (channels outermost, stride 1; blocks may run on into the next image only where
-// HW is a multiple of that).
+// Inputs read in single floats; four channels at a time (channels innermost, C a multiple of 4, 16-byte aligned); two
+// neighbouring pixels at a time (channels outermost, stride 1; blocks may run on into the next image only where HW is
+// even).
 enum { SPLIT_IN_SINGLE = 0, SPLIT_IN_CHANNELS = 1, SPLIT_IN_PIXELS = 2 };
-constexpr int split_point_pixels(int in, int npix) { return in != SPLIT_IN_PIXELS ? 1 : npix >= 96 ? 4 : 2; }
-#define IOLB_SPLIT_POINT_SHAPES(X) X(1, 2, 4, 1) X(1, 4, 4, 1) X(2, 2, 2, 2) X(2, 4, 4, 1) X(3, 4, 4, 1) X(4, 4, 4, 1)
+constexpr int split_point_pixels(int in) { return in == SPLIT_IN_PIXELS ? 2 : 1; }
+#define IOLB_SPLIT_POINT_SHAPES(X) X(1, 2, 4, 1) X(1, 4, 4, 1) X(2, 4, 4, 1) X(3, 4, 4, 1) X(4, 4, 4, 1)
 inline long long split_point_weight_bytes(const SplitPointGeom& g) { return (g.C + 31LL) / 32 * g.Kb16 * 3072; }
 hipError_t launch_split_point(const float* x, const void* wt, float* y, const SplitPointGeom& g, hipStream_t st);
 

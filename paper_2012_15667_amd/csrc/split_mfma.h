@@ -11,6 +11,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 namespace iolb {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -23,6 +25,19 @@ __device__ __forceinline__ int opaque(int v)
     asm volatile("" : "+v"(v));
     return v;
 }
+
+// Calls f with the integral constants FROM ... TO - 1.
+template <int FROM, int TO, class F>
+__device__ __forceinline__ void static_range(F f)
+{
+    if constexpr (FROM < TO) {
+        f(std::integral_constant<int, FROM>{});
+        static_range<FROM + 1, TO>(f);
+    }
+}
+
+// voffset of an element that does not exist: beyond every buffer's range, so that the load returns zero
+constexpr unsigned OUTSIDE = 0x80000000u;
 
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));

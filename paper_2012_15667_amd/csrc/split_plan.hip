@@ -132,7 +132,7 @@ bool split_point_plan(SplitPointGeom* g, double* cycles)
         t.mb = sh.mb; t.nb = sh.nb; t.wm = sh.wm; t.wn = sh.wn;
         const int npix = 16 * t.nb * t.wn, z = 16 * t.mb * t.wm;
         // pixels read several at a time must not run on into another image
-        if (t.in == SPLIT_IN_PIXELS && t.images > 1 && t.HW % split_point_pixels(t.in, npix)) {
+        if (t.in == SPLIT_IN_PIXELS && t.images > 1 && t.HW % split_point_pixels(t.in)) {
             if (t.w_image == 0 && t.HW >= 128) { t.groups *= t.images; t.images = 1; }
             else t.in = SPLIT_IN_SINGLE;
         }

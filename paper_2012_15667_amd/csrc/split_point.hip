@@ -3,8 +3,8 @@
 // transformed plane of Winograd being such a group of its own.
 //
 // A step is 32 channels.  The inputs of chunk t + 1 are split and written to one LDS buffer while chunk t is multiplied
-// from the other; their loads are issued three chunks ahead and kept in registers, two or four neighbouring pixels per
-// load where the layout has them.  The split's arithmetic is placed between the matrix instructions, three vector
+// from the other; their loads are issued three chunks ahead and kept in registers, two neighbouring pixels per load where
+// the layout has them.  The split's arithmetic is placed between the matrix instructions, three vector
 // instructions after each, where it costs little (a bf16 matrix instruction leaves the vector pipeline free; measured:
 // eight vector instructions per 32-cycle matrix instruction 1433 against 1631 TFLOP/s).  wt is not declared restrict on
 // purpose: loads of memory known not to change were moved down past the barrier to their use, which undid the prefetch.
@@ -23,24 +23,13 @@ namespace iolb {
 
 namespace {
 
-constexpr unsigned OUTSIDE = 0x80000000u;
-
-template <int FROM, int TO, class F>
-__device__ __forceinline__ void static_for(F f)
-{
-    if constexpr (FROM < TO) {
-        f(std::integral_constant<int, FROM>{});
-        static_for<FROM + 1, TO>(f);
-    }
-}
-
 template <int MB, int NB, int WM, int WN, int IN>
 __global__ void __launch_bounds__(64 * WM * WN, 2)
 split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitPointGeom g)
 {
     constexpr int T = 64 * WM * WN, NPIX = 16 * NB * WN, BUF = 4 * NPIX * 48;
     // an input item: CH channels of PX neighbouring pixels
-    constexpr int PX = split_point_pixels(IN, NPIX), CH = IN == SPLIT_IN_PIXELS ? 4 : 8;
+    constexpr int PX = split_point_pixels(IN), CH = IN == SPLIT_IN_PIXELS ? 4 : 8;
     constexpr int ITEMS = 32 / CH * NPIX / PX, IB = (ITEMS + T - 1) / T;
     extern __shared__ u32x4 lds16[];
     char* const lds = reinterpret_cast<char*>(lds16);       // two buffers, then 48 bytes that nobody reads
@@ -118,11 +107,7 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
 #pragma unroll
                 for (int j = 0; j < CH; ++j) {
                     const int cj = c0 + j < g.C ? c0 + j : g.C - 1, at = some > j ? (int)src[i] : (int)OUTSIDE;
-                    if constexpr (PX == 4) {
-                        const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(rs, at, cj * cstep, 0);
-#pragma unroll
-                        for (int p = 0; p < 4; ++p) v[i][p * CH + j] = __uint_as_float(q[p]);
-                    } else if constexpr (PX == 2) {
+                    if constexpr (PX == 2) {
                         const u32x2 q = __builtin_amdgcn_raw_buffer_load_b64(rs, at, cj * cstep, 0);
                         v[i][j] = __uint_as_float(q[0]);
                         v[i][CH + j] = __uint_as_float(q[1]);
@@ -202,10 +187,10 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
                         __builtin_bit_cast(bf16x8, a[mb * 3 + PA[q]]), __builtin_bit_cast(bf16x8, bf[nb & 1][PB[q]]), acc[mb][nb], 0, 0, 0);
         };
         constexpr int HALF = NB / 2;
-        static_for<0, HALF>(block);
+        static_range<0, HALF>(block);
         __builtin_amdgcn_sched_barrier(0);
         write_x(v, lds + ((t + 1) & 1) * BUF);
-        static_for<HALF, NB>(block);
+        static_range<HALF, NB>(block);
         // the arithmetic of the split runs in the shadow of the matrix instructions
 #pragma unroll
         for (int i = 0; i < (NB - HALF) * 6 * MB; ++i) {
@@ -286,7 +271,7 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
         float wv[MB][8];
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) kept_eight(wq[mb * 192], wq[mb * 192 + 64], wq[mb * 192 + 128], wv[mb]);
-        static_for<0, NB>([&](auto nb_c) {
+        static_range<0, NB>([&](auto nb_c) {
             constexpr int nb = decltype(nb_c)::value;
             float v[8];
 #pragma unroll
@@ -309,10 +294,7 @@ hipError_t launch_one(const float* x, const u32x4* wt, float* y, const SplitPoin
 {
     auto kern = split_point_kernel<MB, NB, WM, WN, IN>;
     constexpr size_t shm = 2 * 4 * 16 * NB * WN * 48 + 48;
-    if (shm > 64 * 1024) {
-        const hipError_t e = allow_large_lds((const void*)kern);
-        if (e != hipSuccess) return e;
-    }
+    static_assert(shm <= 64 * 1024, "dynamic LDS without an opt-in");
     hipLaunchKernelGGL(kern, dim3(g.nbk * g.nbp * g.groups), dim3(64 * WM * WN), shm, st, x, wt, y, g);
     return hipGetLastError();
 }
@@ -328,7 +310,7 @@ hipError_t launch_split_point(const float* x, const void* wt, float* y, const Sp
         (long long)g.nbk * g.nbp * g.groups > 0x7fffffffLL)
         return hipErrorInvalidValue;
     if (g.in == SPLIT_IN_CHANNELS && (!g.hwc || g.C % 4)) return hipErrorInvalidValue;
-    if (g.in == SPLIT_IN_PIXELS && (g.hwc || g.stride != 1 || (g.images > 1 && g.HW % split_point_pixels(g.in, (int)npix)))) return hipErrorInvalidValue;
+    if (g.in == SPLIT_IN_PIXELS && (g.hwc || g.stride != 1 || (g.images > 1 && g.HW % split_point_pixels(g.in)))) return hipErrorInvalidValue;
     const u32x4* w = static_cast<const u32x4*>(wt);
 #define IOLB_POINT_CASE(M_, N_, A_, B_)                                                              \
     if (g.mb == M_ && g.nb == N_ && g.wm == A_ && g.wn == B_) {                                      \
