@@ -50,6 +50,15 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 constexpr float SPLIT_SCALE = 8388608.f;                     // 2^23
 constexpr float SPLIT_UNSCALE = 1.f / SPLIT_SCALE / SPLIT_SCALE;
 
+// The two as one register, which the compiler takes apart with a shift and a mask; it would convert the first one a
+// second time otherwise.
+__device__ __forceinline__ unsigned packed(bf16x2 v)
+{
+    unsigned u = __builtin_bit_cast(unsigned, v);
+    asm("" : "+v"(u));
+    return u;
+}
+
 // 2^23 x = h + m + l with h, m, l bf16 (8 significant bits each, rounded to nearest, so that the two differences are
 // exact): two operands at a time, one packed conversion per part.
 __device__ __forceinline__ void split_pair(float a, float b, unsigned& h, unsigned& m, unsigned& l)
@@ -57,10 +66,10 @@ __device__ __forceinline__ void split_pair(float a, float b, unsigned& h, unsign
     a *= SPLIT_SCALE;
     b *= SPLIT_SCALE;
     const bf16x2 hv = {(__bf16)a, (__bf16)b};
-    h = __builtin_bit_cast(unsigned, hv);
+    h = packed(hv);
     const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xffff0000u);
     const bf16x2 mv = {(__bf16)ra, (__bf16)rb};
-    m = __builtin_bit_cast(unsigned, mv);
+    m = packed(mv);
     const float sa = ra - __uint_as_float(m << 16), sb = rb - __uint_as_float(m & 0xffff0000u);
     const bf16x2 lv = {(__bf16)sa, (__bf16)sb};
     l = __builtin_bit_cast(unsigned, lv);
