@@ -91,17 +91,15 @@ __device__ __forceinline__ void split_eight(const float (&v)[8], u32x4& h, u32x4
 __device__ __forceinline__ void split_kept(float a, unsigned short& h, unsigned short& m, unsigned short& l)
 {
     const float v = a * SPLIT_SCALE;
+    const unsigned u = __float_as_uint(a);
     h = __builtin_bit_cast(unsigned short, (__bf16)v);
-    if ((h & 0x7f80) == 0x7f80) {
-        const unsigned u = __float_as_uint(a);
-        h = 0x7fc0;
-        m = (unsigned short)(u >> 16);
-        l = (unsigned short)u;
-        return;
-    }
     const float r = v - __uint_as_float((unsigned)h << 16);
     m = __builtin_bit_cast(unsigned short, (__bf16)r);
     l = __builtin_bit_cast(unsigned short, (__bf16)(r - __uint_as_float((unsigned)m << 16)));
+    const bool beyond = (h & 0x7f80) == 0x7f80;
+    h = beyond ? (unsigned short)0x7fc0 : h;
+    m = beyond ? (unsigned short)(u >> 16) : m;
+    l = beyond ? (unsigned short)u : l;
 }
 
 // The value that split_kept was given.
