@@ -229,22 +229,41 @@ def main():
     def tile_of(L, a):
         return B.iolb_tune(shape_of(L, a))
 
-    # direct layers whose tile runs the matrix-core kernel (thin layers run a plain-FMA kernel of their own, which the
-    # library does not time with them)
-    def on_matrix_cores(j):
-        return j[1] == "direct" and (forced[id(j)] or tile_of(j[0], "direct"))["path"] == B.PATH_MFMA
-    direct_alg_flops = sum(direct_flops(j[0]) for j in jobs if on_matrix_cores(j))
+    # What a call of a layer runs on: "split" (bf16 matrix cores, operands in three parts) or the path of its tile.  Thin
+    # layers ("fma") run plain-FMA kernels, which the library does not time with the matrix-core ones.
+    path_names = {B.PATH_FMA: "fma", B.PATH_MFMA: "mfma", B.PATH_FUSED: "fused", B.PATH_POINT: "pointwise"}
 
-    # Winograd layers by the kernel their tuned tile runs: unfused product, fused matrix-core kernel, or the thin
-    # one-kernel FMA path (no matrix-core launch: nothing added to a roofline)
-    wino_alg_flops = sum(wino_product_flops(j[0], int(j[1][4:])) for j in jobs
-                         if j[1] != "direct" and tile_of(j[0], j[1])["path"] == B.PATH_MFMA)
-    fused_alg_flops = sum(wino_product_flops(j[0], int(j[1][4:])) for j in jobs
-                          if j[1] != "direct" and tile_of(j[0], j[1])["path"] == B.PATH_FUSED)
+    def runs_on(L, a, tile=None):
+        if tile is None and B.iolb_route(shape_of(L, a))[0] == B.ROUTE_SPLIT:
+            return "split"
+        return path_names[(tile or tile_of(L, a))["path"]]
+
+    def alg_flops(j):
+        return direct_flops(j[0]) if j[1] == "direct" else wino_product_flops(j[0], int(j[1][4:]))
+
+    # per timed kind of kernel, the algorithmic flop of a step on the split kernels and on the fp32 instructions
+    kinds = {"direct": [0.0, 0.0], "product": [0.0, 0.0], "fused": [0.0, 0.0]}
+    for j in jobs:
+        on = runs_on(j[0], j[1], forced[id(j)])
+        if on != "fma":
+            kind = "direct" if j[1] == "direct" else "fused" if on == "fused" else "product"
+            kinds[kind][0 if on == "split" else 1] += alg_flops(j)
+
+    def roofline_of(kind, kernel, launches, ms):
+        """Rate of one kind of kernel over the timed steps.  peak: what the step's flop would run at with each part at the
+        peak of the instructions that it runs on (the split kernels' or the fp32 ones')."""
+        split, fp32 = kinds[kind]
+        if not launches or split + fp32 == 0:
+            return None
+        peak = (split + fp32) / (split / PEAK_SPLIT_MFMA_TFLOPS + fp32 / PEAK_FP32_MFMA_TFLOPS)
+        achieved = (split + fp32) * args.steps / (ms * 1e-3) / 1e12
+        return {"bound": "mfma", "kernel": kernel, "achieved": round(achieved, 2), "peak": round(peak, 1), "unit": "TFLOP/s",
+                "frac": round(achieved / peak, 4), "split_share_of_flop": round(split / (split + fp32), 4),
+                "over_measured_fp32_mfma_loop": round(achieved / ceilings["mfma_f32_TFLOPs"], 4),
+                "avg_launch_ms": round(ms / launches, 4), "launches": launches}
 
     # ---- per-layer figures (outside the timed region) ------------------------------------------
     traffic = read_traffic_table()
-    path_names = {B.PATH_FMA: "fma", B.PATH_MFMA: "mfma", B.PATH_FUSED: "fused", B.PATH_POINT: "pointwise"}
 
     def timed(job, tile, reps=5):
         run(job, tile)
@@ -263,26 +282,28 @@ def main():
         shape = shape_of(L, a)
         tile = B.iolb_tune(shape)
         bound_tile = B.iolb_tune_bound(shape)
+        on = runs_on(L, a)
         ms = timed(job, None)
-        ms_bound = ms if bound_tile == tile else timed(job, bound_tile)
+        ms_tile = ms if on != "split" else timed(job, tile)           # the tuned tile, where the call does not take it
+        ms_bound = ms_tile if bound_tile == tile else timed(job, bound_tile)
         bnd = B.iolb_bounds(shape, 40960)
         keys = ("b", "x", "y", "z", "alpha", "threads", "path")
         rec = {
-            "layer": L.name, "algo": a, "ms": round(ms, 4),
+            "layer": L.name, "algo": a, "ms": round(ms, 4), "runs_on": on,
             "tflops_direct_equiv": round(direct_flops(L) / ms / 1e9, 2),
-            "tile": {k: tile[k] for k in keys},
+            "tuned_tile": {"tile": {k: tile[k] for k in keys}, "ms": round(ms_tile, 4), "taken": on != "split",
+                           "modelled_read_MB": round(4 * tile["q_read_elems"] / 1e6, 2)},
             "bound_pick": {"tile": {k: bound_tile[k] for k in keys}, "ms": round(ms_bound, 4),
                            "read_volume_over_tuned": round(bound_tile["q_read_elems"] / tile["q_read_elems"], 3)},
             "compulsory_MB": round(4 * bnd["compulsory_elems"] / 1e6, 2),
             "io_lower_bound_lead_MB_at_160KB": round(4 * bnd["q_lower_lead"] / 1e6, 2),
-            "modelled_read_MB": round(4 * tile["q_read_elems"] / 1e6, 2),
         }
         if a != "direct":
-            # the other Winograd path beside the tuned one (fused against unfused)
-            other = pick_tile(L, a, "unfused" if tile["path"] == B.PATH_FUSED else "fused")
+            # the other Winograd path beside the one taken (fused against unfused)
+            other = pick_tile(L, a, "unfused" if on == "fused" else "fused")
             if other is not None and tile["path"] != B.PATH_FMA:
                 rec["other_path"] = {"path": path_names[other["path"]], "ms": round(timed(job, other), 4)}
-        t = traffic.get((L.name, a, path_names[tile["path"]]))
+        t = traffic.get((L.name, a, on))
         if t:
             denom = max(4 * bnd["compulsory_elems"], 4 * bnd["q_lower_lead"] if a != "direct" else 0)
             rec["hbm_MB_measured"] = round((t["read"] + t["written"]) / 1e6, 1)
@@ -296,34 +317,16 @@ def main():
 
     ms_step = 1e3 * elapsed / args.steps
     value = flops_step / (elapsed / args.steps) / 1e12
-    roofline = None
-    if n_direct:
-        achieved = direct_alg_flops * args.steps / (ms_direct * 1e-3) / 1e12
-        roofline = {"bound": "mfma", "kernel": "split_conv_kernel (all instantiations in the step; fp32 products as six bf16 products)",
-                    "achieved": round(achieved, 2), "peak": PEAK_SPLIT_MFMA_TFLOPS, "unit": "TFLOP/s",
-                    "frac": round(achieved / PEAK_SPLIT_MFMA_TFLOPS, 4),
-                    "over_measured_fp32_mfma_loop": round(achieved / ceilings["mfma_f32_TFLOPs"], 4),
-                    "avg_launch_ms": round(ms_direct / n_direct, 4), "launches": n_direct}
-        per = [traffic[k]["main_kernel"] for k in traffic if k[1] == "direct" and any(j[0].name == k[0] and on_matrix_cores(j) for j in jobs)]
+    roofline = roofline_of("direct", "split_conv_kernel (all instantiations in the step; fp32 products as six bf16 products)" if kinds["direct"][0]
+                           else "direct_mfma_kernel (all instantiations in the step)", n_direct, ms_direct)
+    if roofline:
+        per = [traffic[k]["main_kernel"] for k in ((j[0].name, j[1], runs_on(j[0], j[1], forced[id(j)])) for j in jobs)
+               if k in traffic and k[1] == "direct" and k[2] != "fma"]
         roofline["traffic"] = round(sum(per) / len(per)) if per else None
         roofline["traffic_source"] = ("recorded: %s (rocprofv3 FETCH_SIZE + WRITE_SIZE of an earlier run of the same "
                                       "kernels, average over the direct launches of a step), not measured in this run" % TRAFFIC_FILE) if per else None
-    wino_roofline = None
-    if n_wino:
-        achieved_w = wino_alg_flops * args.steps / (ms_wino * 1e-3) / 1e12
-        wino_roofline = {"bound": "mfma", "kernel": "split_point_kernel (large products) / wino_product_kernel (fp32 instructions), all launches of the step",
-                         "achieved": round(achieved_w, 2), "peak": PEAK_SPLIT_MFMA_TFLOPS, "unit": "TFLOP/s",
-                         "frac": round(achieved_w / PEAK_SPLIT_MFMA_TFLOPS, 4),
-                         "over_measured_fp32_mfma_loop": round(achieved_w / ceilings["mfma_f32_TFLOPs"], 4),
-                         "avg_launch_ms": round(ms_wino / n_wino, 4), "launches": n_wino}
-
-    fused_roofline = None
-    if n_fused:
-        achieved_f = fused_alg_flops * args.steps / (ms_fused * 1e-3) / 1e12
-        fused_roofline = {"bound": "mfma", "kernel": "wino_fused_mfma_kernel / wino_rows_kernel (fused Winograd layers of the step)",
-                          "achieved": round(achieved_f, 2), "peak": PEAK_FP32_MFMA_TFLOPS, "unit": "TFLOP/s",
-                          "frac": round(achieved_f / PEAK_FP32_MFMA_TFLOPS, 4),
-                          "avg_launch_ms": round(ms_fused / n_fused, 4), "launches": n_fused}
+    wino_roofline = roofline_of("product", "split_point_kernel (large products) and wino_product_kernel (fp32 instructions), all launches of the step", n_wino, ms_wino)
+    fused_roofline = roofline_of("fused", "wino_fused_mfma_kernel / wino_rows_kernel (fused Winograd layers of the step)", n_fused, ms_fused)
 
     out = {
         "metric": "TFLOP/s per conv layer (direct & Winograd) + HBM bytes / I/O lower bound",

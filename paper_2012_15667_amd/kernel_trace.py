@@ -49,13 +49,14 @@ def main():
                 f.write("- %s: avg launch %.4f ms over %d launches, %.2f TFLOP/s (%.3f of %.1f)\n" %
                         (rf["kernel"], rf["avg_launch_ms"], rf["launches"], rf["achieved"], rf["frac"], rf["peak"]))
         f.write("- step: %.3f ms, %.1f TFLOP/s direct-equivalent\n\nPer layer (five back-to-back repetitions, outside the timed steps):\n\n" % (d["ms_per_step"], d["value"]))
-        f.write("| layer | algo | path | tile b,x,y,z,alpha,threads | ms | TFLOP/s direct-eq. | bound-only pick ms | other Winograd path ms |\n|---|---|---|---|---|---|---|---|\n")
+        f.write("| layer | algo | runs on | ms | TFLOP/s direct-eq. | tuned tile b,x,y,z,alpha,threads | its ms | bound-only pick ms | other Winograd path ms |\n|---|---|---|---|---|---|---|---|---|\n")
         for l in d["layers"]:
-            t = l["tile"]
+            t = l["tuned_tile"]["tile"]
             other = l.get("other_path")
-            f.write("| %s | %s | %s | %d,%d,%d,%d,%d,%d | %.4f | %.1f | %.4f | %s |\n" % (
-                l["layer"], l["algo"], {0: "fma", 1: "mfma", 2: "fused"}[t["path"]], t["b"], t["x"], t["y"], t["z"], t["alpha"], t["threads"],
-                l["ms"], l["tflops_direct_equiv"], l["bound_pick"]["ms"], "%s %.4f" % (other["path"], other["ms"]) if other else ""))
+            f.write("| %s | %s | %s | %.4f | %.1f | %d,%d,%d,%d,%d,%d %s | %.4f | %.4f | %s |\n" % (
+                l["layer"], l["algo"], l["runs_on"], l["ms"], l["tflops_direct_equiv"], t["b"], t["x"], t["y"], t["z"], t["alpha"], t["threads"],
+                {0: "fma", 1: "mfma", 2: "fused", 3: "pointwise"}[t["path"]], l["tuned_tile"]["ms"], l["bound_pick"]["ms"],
+                "%s %.4f" % (other["path"], other["ms"]) if other else ""))
     print("wrote " + out)
 
 

@@ -194,7 +194,7 @@ def report(path, reps=5):
     w.append("# Layer sets on one MI355X: whole networks' convolution layers, batch sweep, figure sweep\n")
     w.append("Written by `python -m paper_2012_15667_amd.layersets --report profiles/layer_sets.md` (run from the repository root")
     w.append("on the GPU box).  Timed with `torch.cuda.Event` around at least %d calls (about 2 ms of work for short layers) after warm-up calls, inputs resident in HBM, fp32;" % reps)
-    w.append("TFLOP/s are direct-convolution-equivalent (2 N K P Q C R S / time); every call goes through the tuned tile.\n")
+    w.append("TFLOP/s are direct-convolution-equivalent (2 N K P Q C R S / time); every call leaves the kernel to the library.\n")
     w.append("## Networks (batch 64; distinct convolution shapes x how often the network runs them)\n")
     w.append("| network | conv layers | GFLOP | best algorithm per layer: ms / TFLOP/s | direct only: ms / TFLOP/s |")
     w.append("|---|---|---|---|---|")

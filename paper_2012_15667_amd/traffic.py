@@ -27,13 +27,15 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 OUT_DIR = os.path.join("rocprof_out", "traffic")
 STEPS = 2
 
-# (layer, algo, path): path "tuned"/"bound" for direct; "fused"/"unfused" for Winograd (thin layers: "tuned")
+# (layer, algo, path): path "tuned" (the call without a tile) / "bound" for direct; "fused"/"unfused" for Winograd, and
+# "tuned" for thin layers and for those whose call without a tile takes the split product
 DEFAULT_RUNS = (
     [(l, "direct", "tuned") for l in ("cfg3", "cfg5a", "cfg5b", "cfg5c", "cfg5d")] +
     [("cfg2", "wino2", p) for p in ("unfused", "fused")] +
     [("cfg4", "wino4", p) for p in ("unfused", "fused")] +
     [("cfg5a", a, "tuned") for a in ("wino2", "wino4")] +
-    [(l, a, p) for l in ("cfg5b", "cfg5c", "cfg5d") for a in ("wino2", "wino4") for p in ("unfused", "fused")]
+    [(l, a, p) for l in ("cfg5b", "cfg5c", "cfg5d") for a in ("wino2", "wino4") for p in ("unfused", "fused")] +
+    [("cfg5c", "wino4", "tuned"), ("cfg5d", "wino2", "tuned"), ("cfg5d", "wino4", "tuned")]
 )
 
 
@@ -65,24 +67,24 @@ def _bench_args(layer, algo, path):
     args = ["--profile", "--warmup", "0", "--steps", str(STEPS), "--layers", layer, "--algos", algo]
     if algo == "direct":
         args += ["--direct-pick", path]
-    elif path != "tuned":
+    elif path != "tuned":                             # (bench.py's default is the call without a tile)
         args += ["--wino-path", path]
     return args
 
 
 def _path_label(layer, algo, path):
-    """The path name bench.py looks a layer up under: the kernel path of the tile that ran."""
+    """The path name bench.py looks a layer up under: what the call ran on."""
     from . import binding as B
     from .inputs import CONFIGS
     L = CONFIGS[layer]
-    names = {B.PATH_FMA: "fma", B.PATH_MFMA: "mfma", B.PATH_FUSED: "fused", B.PATH_POINT: "pointwise"}
-    if algo == "direct":
-        if path != "tuned":
-            return "bound"
-        return names[B.iolb_tune(B.make_shape(L.N, L.C, L.H, L.W, L.K, L.R, L.S, L.stride, L.pad))["path"]]
     if path == "tuned":
-        sh = B.make_shape(L.N, L.C, L.H, L.W, L.K, algo={"wino2": B.WINO_F2, "wino4": B.WINO_F4}[algo])
+        algo_id = {"direct": B.DIRECT, "wino2": B.WINO_F2, "wino4": B.WINO_F4}[algo]
+        sh = B.make_shape(L.N, L.C, L.H, L.W, L.K, L.R, L.S, L.stride, L.pad, algo_id)
+        if B.iolb_route(sh)[0] == B.ROUTE_SPLIT:
+            return "split"
         return {B.PATH_FMA: "fma", B.PATH_MFMA: "mfma", B.PATH_FUSED: "fused", B.PATH_POINT: "pointwise"}[B.iolb_tune(sh)["path"]]
+    if algo == "direct":
+        return "bound"
     return {"unfused": "mfma", "fused": "fused"}[path]
 
 
@@ -147,7 +149,7 @@ def main():
     w("which runs, each counter in a run of its own:")
     w("  " + commands[0])
     w("  rocprofv3 --pmc <counter> --output-format csv -d rocprof_out/traffic -o <tag> -- python3 bench.py --profile --warmup 0 "
-      "--steps %d --layers <layer> --algos <algo> [--wino-path fused|unfused] [--direct-pick tuned]" % STEPS)
+      "--steps %d --layers <layer> --algos <algo> [--wino-path fused|unfused|tuned] [--direct-pick tuned]" % STEPS)
     w("")
     w("Calibration: a plain 1 GiB device copy (1048576 KiB each way) reads FETCH_SIZE = %.0f and WRITE_SIZE = %.0f," % (raw["FETCH_SIZE"], raw["WRITE_SIZE"]))
     w("so FETCH_SIZE is scaled by %.4f and WRITE_SIZE by %.4f.  The counters sit between L2 and the fabric: reads" % (scale["FETCH_SIZE"], scale["WRITE_SIZE"]))
