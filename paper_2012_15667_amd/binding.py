@@ -200,9 +200,13 @@ def iolb_winograd_matrices(m):
 
 def _use_current_stream():
     # the handle itself: building torch's stream object for it takes 2.5 us, a quarter of a small layer's whole call
-    # (one image of 16 channels at 14 x 14: 13.4 -> 10.6 us a call)
+    # (one image of 16 channels at 14 x 14: 13.4 -> 10.6 us a call).  The function is not part of torch's public
+    # interface; a torch without it goes the public way.
     import torch
-    _check(lib().iolb_set_stream(ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))))
+    device = torch.cuda.current_device()
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    handle = raw(device) if raw is not None else torch.cuda.current_stream(device).cuda_stream
+    _check(lib().iolb_set_stream(ctypes.c_void_p(handle)))
 
 
 def _dev_f32(t, name):

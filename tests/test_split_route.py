@@ -70,3 +70,24 @@ def test_large_pointwise_layers_give_the_same_bits_whatever_ran_before(first):
     # sums of C fp32 products: every rounding at most 2^-23 of the magnitudes
     lim = 2 * C * 2.0 ** -23 * torch.bmm(w.double().abs().view(1, K, C).expand(N, K, C).contiguous(), x.double().abs().flatten(2).contiguous()).view(N, K, H, H)
     assert bool(((y.double() - ref).abs() <= lim).all())
+
+
+@pytest.mark.gpu
+def test_calls_follow_the_current_stream_with_and_without_the_raw_handle(monkeypatch):
+    """Graphs record what is enqueued on the capture's stream: a call on another one would leave y as it was."""
+    import torch
+    x, w = torch.rand((2, 24, 9, 9), device="cuda"), torch.randn((20, 24, 3, 3), device="cuda")
+    want = B.conv_direct(x, w, 1, 1)
+    for without in (False, True):
+        if without:
+            monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+        y = torch.zeros_like(want)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+            B.conv_direct(x, w, 1, 1, y=y)
+        for _ in range(2):
+            y.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(y, want), without
