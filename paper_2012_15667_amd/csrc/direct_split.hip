@@ -13,13 +13,13 @@
 // channels of its own, so through LDS they would only be written and read once more.
 //
 // What bounds it: the matrix cores, at the clock the chip's power allows (3x3, C = K = 256, 56 x 56, batch 64, whole
-// call: 1900 us on the fp32 instructions -> 949 us = 250 TFLOP/s of fp32 products; register-only bf16 loop 323; matrix
-// cores busy 0.73 of the cycles).  The rest: LDS reads (56 % of the cycles) and weight loads that meet at the CU's load
-// rate (about 19 bytes per clock).  Measured on that layer: blocks of 32 x 112 per wave 1041 us (kernel), 64 x 64 with the
-// weights read by two waves 1137, eight waves per workgroup 1046, chunks of 16 channels 1123; row pitch in LDS without
-// the padding of split_derive 1068 against 1024; input loads whose descriptor the compiler kept in vector registers
-// (a loop over the lanes per load) 1073 against 1041.  Sums apart per step (APART) for all layers: error 1.8e-7 in
-// place of 7.6e-7, 1129 us: kept for the few-channel layers only.
+// call: 1900 us on the fp32 instructions -> 940 - 996 us over several boxes = 252 - 238 TFLOP/s of fp32 products;
+// register-only bf16 loop 323; matrix cores busy 0.72 of the cycles).  The rest: LDS reads (56 % of the cycles) and weight
+// loads (16 bytes per clock and unit through the L2).  Measured on that layer: blocks of 32 x 112 per wave 1041 us (kernel),
+// 64 x 64 with the weights read by two waves 1137, eight waves per workgroup 1046, chunks of 16 channels 1123; row pitch in
+// LDS without the padding of split_derive 1068 against 1024; input loads whose descriptor or offset the compiler kept in
+// vector registers (a loop over the lanes per load) 1073 against 1041.  Sums apart per step (APART) for all layers: error
+// 1.8e-7 in place of 7.6e-7, 1129 us: kept for the few-channel layers only.
 // Small layers are bound by the latency of a step's weight loads (about 0.5 us): AHEAD below.
 #include "kernels.h"
 #include "split_mfma.h"

@@ -1,6 +1,6 @@
 // fp32 products on the bf16 matrix cores: every operand is cut into three bf16 parts, x = h + m + l, and the product
 // of two operands is taken as the six products of parts that reach fp32 precision (h h, h m, m h, m m, h l, l h; the
-// three left out are below 2^-24 of the product).  A v_mfma_f32_16x16x32_bf16 does 16 times the multiply-adds of an fp32
+// three left out are each below 2^-24 of the product).  A v_mfma_f32_16x16x32_bf16 does 16 times the multiply-adds of an fp32
 // matrix instruction in the same time, so six of them still leave a factor of 16 / 6; sums stay in fp32.  Measured on
 // register operands: 1937 TFLOP/s of bf16 products = 323 TFLOP/s of fp32 products, against 155 of the fp32 instructions
 // (32x32x16_bf16: 1430 - 1690).  Error of a sum of n such products against 64 bits (relative, 2-norm; x uniform on

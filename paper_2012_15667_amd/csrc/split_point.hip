@@ -9,11 +9,12 @@
 // eight vector instructions per 32-cycle matrix instruction 1433 against 1631 TFLOP/s).  wt is not declared restrict on
 // purpose: loads of memory known not to change were moved down past the barrier to their use, which undid the prefetch.
 //
-// What bounds it: large products the rate at which a compute unit takes operands in, about 19 bytes per clock (a block
-// of z channels by npix pixels needs 192 z + 128 npix bytes per 32 channels), and the power the vector work of the
-// split costs in clock: 16 planes of 512 x 12544 x 512 (F(2x2)) 630 us = 167 TFLOP/s with 128 x 64 blocks (fp32
-// instructions: 840 us), 634 with 256 x 64, 666 - 680 with 128 x 96 and 192 x 64, 700 with 128 x 128, 708 with eight
-// waves on 256 x 128.  Small ones the latency of their steps.  1 x 1, 768 -> 192 at 17 x 17, batch 64: 66 -> 48 us whole call.
+// What bounds it: large products the rate at which a compute unit takes operands in, about 20 bytes per clock (6.05 GB
+// through the L2s in 1.15 M clocks on the product below; a block of z channels by npix pixels needs 192 z + 128 npix bytes
+// per 32 channels), and the power the vector work of the split costs in clock: 16 planes of 512 x 12544 x 512 (F(2x2))
+// 630 us = 167 TFLOP/s with 128 x 64 blocks (fp32 instructions: 840 us), 634 with 256 x 64, 666 - 680 with 128 x 96 and
+// 192 x 64, 700 with 128 x 128, 708 with eight waves on 256 x 128.  Small ones the latency of their steps.  1 x 1,
+// 768 -> 192 at 17 x 17, batch 64: 66 -> 45 - 47 us whole call.
 #include "kernels.h"
 #include "split_mfma.h"
 
