@@ -12,9 +12,13 @@
 // What bounds it: large products the rate at which a compute unit takes operands in, about 20 bytes per clock (6.05 GB
 // through the L2s in 1.15 M clocks on the product below; a block of z channels by npix pixels needs 192 z + 128 npix bytes
 // per 32 channels), and the power the vector work of the split costs in clock: 16 planes of 512 x 12544 x 512 (F(2x2))
-// 630 us = 167 TFLOP/s with 128 x 64 blocks (fp32 instructions: 840 us), 634 with 256 x 64, 666 - 680 with 128 x 96 and
-// 192 x 64, 700 with 128 x 128, 708 with eight waves on 256 x 128.  Small ones the latency of their steps.  1 x 1,
-// 768 -> 192 at 17 x 17, batch 64: 66 -> 45 - 47 us whole call.
+// 545 us = 193 TFLOP/s with 256 x 64 blocks (fp32 instructions: 840 us; with single stores 580), larger blocks were slower.
+// Small ones the latency of their steps.  1 x 1, 768 -> 192 at 17 x 17, batch 64: 66 -> 45 - 47 us whole call.
+// Measured and taken back: the weights of chunk t + 2 loaded before the inputs of chunk t + 3, so that these have two steps
+// to arrive (the same product 545 -> 573 us).
+//
+// A column of a wave's 16 x 16 blocks is 16 pixels; block nb of the wave takes every NB-th pixel from nb on (VPX), so that a
+// lane holds NB neighbours of each output channel and stores them at once.
 #include "kernels.h"
 #include "split_mfma.h"
 
@@ -24,7 +28,7 @@ namespace iolb {
 
 namespace {
 
-template <int MB, int NB, int WM, int WN, int IN>
+template <int MB, int NB, int WM, int WN, int IN, bool VPX>
 __global__ void __launch_bounds__(64 * WM * WN, 2)
 split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitPointGeom g)
 {
@@ -61,6 +65,10 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
         reinterpret_cast<void*>((unsigned long long)xhi << 32 | xlo), 0, (int)range, 0x00020000);
 
     // the input items of this thread
+    // Column l16 of a wave's block nb is pixel 16 nb + l16, or, for vector stores, NB l16 + nb: pixels are kept in LDS in the
+    // order in which the blocks read them.
+    auto slot_of = [&](int px) { return VPX ? px / (16 * NB) * (16 * NB) + px % NB * 16 + px % (16 * NB) / NB : px; };
+    auto pixel_of = [&](int nb, int l) { return wn_i * NB * 16 + (VPX ? NB * l + nb : 16 * nb + l); };
     unsigned src[IB], dst[IB];
     int c_in[IB];
 #pragma unroll
@@ -70,7 +78,7 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
         src[i] = OUTSIDE;
         dst[i] = 2 * BUF;
         if (it < ITEMS) {
-            dst[i] = (unsigned)(48 * (c_in[i] / 8 * NPIX + px) + (c_in[i] & 4) * 2);
+            dst[i] = (unsigned)(48 * (c_in[i] / 8 * NPIX + slot_of(px)) + (c_in[i] & 4) * 2);
             if (px < left_px) {
                 const int q = p0 + px, im = q / g.HW, r = q % g.HW;
                 const int in = g.stride == 1 ? r : r / g.Q * g.stride * g.Win + r % g.Q * g.stride;
@@ -79,6 +87,7 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
         }
     }
     const int cstep = g.hwc ? 4 : 4 * g.HWin;
+    constexpr int NEXT_PX = VPX ? 48 * 16 : 48;             // LDS bytes from a pixel to the next of its item
 
     f32x4 acc[MB][NB];
 #pragma unroll
@@ -139,7 +148,7 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
                         h[j] = hj; m[j] = mj; l[j] = lj;
                     }
                     // (an item that does not exist writes all its pixels to the same spare place)
-                    char* dp = d + (dst[i] == 2 * BUF ? 0 : 48 * p);
+                    char* dp = d + (dst[i] == 2 * BUF ? 0 : NEXT_PX * p);
                     *reinterpret_cast<u32x2*>(dp) = h;
                     *reinterpret_cast<u32x2*>(dp + 16) = m;
                     *reinterpret_cast<u32x2*>(dp + 32) = l;
@@ -218,9 +227,31 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
     auto write_y = [&](auto marked_c) {
         constexpr bool MARKED = decltype(marked_c)::value;  // the second time: marked outputs only
         const int l16 = opaque(lane) & 15, grp = opaque(lane) >> 4;
+        if constexpr (VPX && !MARKED) {
+            typedef float vec __attribute__((ext_vector_type(NB)));
+            const int px = pixel_of(0, l16);                // ... and the next NB - 1, in the same row of y
+            if (px >= left_px) return;
+            const int n = n0 + (p0 + px) / g.HW, r = (p0 + px) % g.HW;
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) {
+                const int k0 = (kb16 + mb) * 16 + 4 * grp;
+                float* yp = y + ((size_t)n * g.Ky + k0) * g.HWy + r;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    vec q;
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) {
+                        if (!(__builtin_fabsf(acc[mb][nb][i]) <= 3.402823466e38f)) again |= 1ull << ((nb * MB + mb) * 4 + i);
+                        q[nb] = acc[mb][nb][i] * SPLIT_UNSCALE;
+                    }
+                    if (k0 + i < g.K) *reinterpret_cast<vec*>(yp + (size_t)i * g.HWy) = q;
+                }
+            }
+            return;
+        }
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
-            const int px = (wn_i * NB + nb) * 16 + l16;
+            const int px = pixel_of(nb, l16);
             if (px >= left_px) continue;
             const int n = n0 + (p0 + px) / g.HW, r = (p0 + px) % g.HW;
 #pragma unroll
@@ -260,7 +291,7 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
     unsigned at[NB];                                        // this lane's pixels, first channel of its group
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-        const int px = (wn_i * NB + nb) * 16 + col16, q = p0 + px, im = q / g.HW, r = q % g.HW;
+        const int px = pixel_of(nb, col16), q = p0 + px, im = q / g.HW, r = q % g.HW;
         const int in = g.stride == 1 ? r : r / g.Q * g.stride * g.Win + r % g.Q * g.stride;
         at[nb] = px >= left_px ? OUTSIDE : g.hwc ? 4u * (unsigned)((im * g.HWin + in) * g.C + c0) : 4u * (unsigned)((im * g.C + c0) * g.HWin + in);
 #pragma unroll
@@ -290,10 +321,10 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
     write_y(std::true_type{});
 }
 
-template <int MB, int NB, int WM, int WN, int IN>
+template <int MB, int NB, int WM, int WN, int IN, bool VPX>
 hipError_t launch_one(const float* x, const u32x4* wt, float* y, const SplitPointGeom& g, hipStream_t st)
 {
-    auto kern = split_point_kernel<MB, NB, WM, WN, IN>;
+    auto kern = split_point_kernel<MB, NB, WM, WN, IN, VPX>;
     constexpr size_t shm = 2 * 4 * 16 * NB * WN * 48 + 48;
     static_assert(shm <= 64 * 1024, "dynamic LDS without an opt-in");
     hipLaunchKernelGGL(kern, dim3(g.nbk * g.nbp * g.groups), dim3(64 * WM * WN), shm, st, x, wt, y, g);
@@ -313,11 +344,19 @@ hipError_t launch_split_point(const float* x, const void* wt, float* y, const Sp
     if (g.in == SPLIT_IN_CHANNELS && (!g.hwc || g.C % 4)) return hipErrorInvalidValue;
     if (g.in == SPLIT_IN_PIXELS && (g.hwc || g.stride != 1 || (g.images > 1 && g.HW % split_point_pixels(g.in)))) return hipErrorInvalidValue;
     const u32x4* w = static_cast<const u32x4*>(wt);
-#define IOLB_POINT_CASE(M_, N_, A_, B_)                                                              \
-    if (g.mb == M_ && g.nb == N_ && g.wm == A_ && g.wn == B_) {                                      \
-        if (g.in == SPLIT_IN_PIXELS) return launch_one<M_, N_, A_, B_, SPLIT_IN_PIXELS>(x, w, y, g, st);      \
-        if (g.in == SPLIT_IN_CHANNELS) return launch_one<M_, N_, A_, B_, SPLIT_IN_CHANNELS>(x, w, y, g, st);  \
-        return launch_one<M_, N_, A_, B_, SPLIT_IN_SINGLE>(x, w, y, g, st);                          \
+    // Whole groups of nb pixels that lie in one row of y, on 4 nb bytes: stores of nb floats.  (Where a group is the last
+    // one of a row that is padded, the padding is written too.)  16 planes of 512 x 12544 x 512: 580 -> 545 us, 36 of 256 x
+    // 12544 x 256 386 -> 350, 16 of 512 x 1024 x 512 47.9 -> 44.1.
+    const bool vec = !g.hwc && g.HWy % g.nb == 0 && (reinterpret_cast<uintptr_t>(y) & (4 * g.nb - 1)) == 0 &&
+                     (g.images == 1 ? (g.HW + g.nb - 1) / g.nb * g.nb <= g.HWy : g.HW % g.nb == 0);
+#define IOLB_POINT_CASE(M_, N_, A_, B_)                                                                          \
+    if (g.mb == M_ && g.nb == N_ && g.wm == A_ && g.wn == B_) {                                                  \
+        if (g.in == SPLIT_IN_CHANNELS) return launch_one<M_, N_, A_, B_, SPLIT_IN_CHANNELS, false>(x, w, y, g, st);  \
+        if (g.in == SPLIT_IN_PIXELS)                                                                             \
+            return vec ? launch_one<M_, N_, A_, B_, SPLIT_IN_PIXELS, true>(x, w, y, g, st)                       \
+                       : launch_one<M_, N_, A_, B_, SPLIT_IN_PIXELS, false>(x, w, y, g, st);                     \
+        return vec ? launch_one<M_, N_, A_, B_, SPLIT_IN_SINGLE, true>(x, w, y, g, st)                           \
+                   : launch_one<M_, N_, A_, B_, SPLIT_IN_SINGLE, false>(x, w, y, g, st);                         \
     }
     IOLB_SPLIT_POINT_SHAPES(IOLB_POINT_CASE)
 #undef IOLB_POINT_CASE

@@ -252,6 +252,35 @@ def test_pointwise_sums_taken_again(gpu, case):
     assert bool(((z[1].double().flatten(1) - wk @ xs).abs() <= lim).all())
 
 
+def _framed(torch, values, at):
+    """The same values `at` floats after the start of a buffer that is NaN before and after them."""
+    frame = torch.full((values.numel() + 80,), float("nan"), device="cuda")
+    inside = frame[at:at + values.numel()].view(values.shape)
+    inside.copy_(values)
+    return frame, inside
+
+
+def _outside_is_untouched(torch, frame, at, n):
+    return bool(torch.isnan(frame[:at]).all()) and bool(torch.isnan(frame[at + n:]).all())
+
+
+@pytest.mark.parametrize("case", [(64, 256, 14, 14, 256), (50, 260, 12, 15, 261), (50, 300, 10, 13, 300), (12, 768, 17, 17, 192), (9, 256, 30, 34, 250)])
+@pytest.mark.parametrize("at", [4, 5, 6])
+def test_pointwise_stores_of_several_pixels(gpu, case, at):
+    """Planes of a multiple of four pixels leave in vector stores where y allows it, others one by one."""
+    torch, B = gpu
+    N, C, H, W, K = case
+    assert B.iolb_route(B.make_shape(N, C, H, W, K, 1, 1, 1, 0))[0] == B.ROUTE_SPLIT
+    x, w = make_inputs(N, C, H, W, K, 1, 1, "u11", "he", seed=N + K)
+    xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+    frame, y = _framed(torch, torch.zeros((N, K, H, W), device="cuda"), at)
+    B.conv_direct(xd, wd, 1, 0, y=y)
+    assert _outside_is_untouched(torch, frame, at, y.numel())
+    xs, wk = xd.double().flatten(2), wd.double().view(1, K, C).expand(N, K, C).contiguous()
+    lim = (12 * -(-C // 8) + 16) * 2.0 ** -23 * torch.bmm(wk.abs(), xs.abs())
+    assert bool(((y.double().flatten(2) - torch.bmm(wk, xs)).abs() <= lim).all())
+
+
 def test_zeros_around_the_image_meet_infinite_weights(gpu):
     """The border is made of zeros that are multiplied like other operands: 0 times an infinite weight is NaN."""
     torch, B = gpu
