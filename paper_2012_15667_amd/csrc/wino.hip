@@ -16,6 +16,7 @@
 #include "kernels.h"
 #include "lds_dma.h"
 #include "split_mfma.h"
+#include "split_weights.h"
 #include "wino_mats.h"
 #include "wino_transform.h"
 
@@ -57,53 +58,32 @@ kernel_transform(const float* __restrict__ w, float* __restrict__ U, int C, int 
 }
 
 // step 1b for the product on the bf16 matrix cores: the same U, cut into three bf16 parts in the order of the product's
-// steps, [xi][chunk of 32 channels][16-kernel block][part][lane][8 channels].  One lane per 16-byte piece of one plane
-// row: eight channels of one kernel.
+// steps, [xi][chunk of 32 channels][16-kernel block][part][lane][8 channels].  One workgroup per 32 channels of 16 kernels, a
+// wave per row of the planes in turn.  Bound by its stores once the rows of w come through LDS: 512 x 512 kernels in F(2 x 2)
+// (25 MB) 30 -> 8 us; gathered by their lanes they cost a cache line per lane and load, in every row of the planes again.
+constexpr int SPLIT_ROW = 32 * 9, SPLIT_ROW_PITCH = SPLIT_ROW + 1;
 template <int M>
 __device__ __forceinline__ void kernel_transform_split_block(const float* __restrict__ w, u32x4* __restrict__ wt, int C, int K, int chunks, int Kb16,
-                                                             int block, int row)
+                                                             int block, float* rows)
 {
     constexpr int n = Mats<M>::n;
-    const size_t id = (size_t)block * 256 + threadIdx.x;
-    if (id >= (size_t)chunks * Kb16 * 64) return;
-    const int lane = (int)(id & 63), kb = (int)((id >> 6) % Kb16), ch = (int)((id >> 6) / Kb16);
-    const int k = kb * 16 + (lane & 15), c0 = ch * 32 + (lane >> 4) * 8;
-    float mine[8][3];                                       // this row of L g, for each channel
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int kb = block % Kb16, ch = block / Kb16;
+    const int have = C - ch * 32 < 32 ? (C - ch * 32) * 9 : SPLIT_ROW;
+    stage_kernels<16, 4, 5>(K > kb * 16 ? w + ((size_t)kb * 16 * C + ch * 32) * 9 : w, rows, wave, lane, C * 9LL, K - kb * 16, have, SPLIT_ROW, SPLIT_ROW_PITCH);
+    __syncthreads();
+    const float* mine = rows + (lane & 15) * SPLIT_ROW_PITCH + (lane >> 4) * 72;
+#pragma unroll 1
+    for (int row = wave; row < n; row += 4) {
+        float lg[8][3];                                     // this row of L g, for each channel
+        kernel_row<M>(row, mine, lg);
+        static_for<n>([&](auto j) {
+            unsigned short p[3][8];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        float g[3][3], t[n][3];
-        const bool exists = c0 + c < C && k < K;
-        const float* wp = w + ((size_t)k * C + c0 + c) * 9;
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) g[i][j] = exists ? wp[i * 3 + j] : 0.f;
-        left_mul<M, UseL, n, 3, 3>(g, t);
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            mine[c][j] = t[0][j];
-#pragma unroll
-            for (int i = 1; i < n; ++i)
-                if (row == i) mine[c][j] = t[i][j];
-        }
+            for (int c = 0; c < 8; ++c) split_kept(kernel_element<M, decltype(j)::value>(lg[c]), p[0][c], p[1][c], p[2][c]);
+            store_parts(wt + (((size_t)(row * n + j) * chunks + ch) * Kb16 + kb) * 192 + lane, p);
+        });
     }
-    static_for<n>([&](auto j) {
-        unsigned short p[3][8];
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            float u = 0.f;
-            bool first = true;
-            static_for<3>([&](auto b) { accumulate<M, UseL, decltype(j)::value, decltype(b)::value>(u, first, mine[c][b]); });
-            split_kept(u, p[0][c], p[1][c], p[2][c]);
-        }
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            u32x4 o;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) o[i] = (unsigned)p[q][2 * i] | ((unsigned)p[q][2 * i + 1] << 16);
-            wt[(((size_t)(row * n + j) * chunks + ch) * Kb16 + kb) * 192 + q * 64 + lane] = o;
-        }
-    });
 }
 
 // Transformed kernels U[plane][rows][cols] (channel rows, kernel columns) -> the same operands.
@@ -123,13 +103,7 @@ __device__ __forceinline__ void split_planes_block(const float* __restrict__ U, 
         if (k < K && c0 + j < C) v = U[((size_t)plane * rows + c0 + j) * cols + k];
         split_kept(v, p[0][j], p[1][j], p[2][j]);
     }
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        u32x4 o;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) o[j] = (unsigned)p[q][2 * j] | ((unsigned)p[q][2 * j + 1] << 16);
-        wt[(((size_t)plane * chunks + ch) * Kb16 + kb) * 192 + q * 64 + lane] = o;
-    }
+    store_parts(wt + (((size_t)plane * chunks + ch) * Kb16 + kb) * 192 + lane, p);
 }
 
 // step 1a: one lane per (c, t); t runs fastest.  VEC (m = 2 or 4, W a multiple of m, x aligned to
@@ -237,9 +211,10 @@ transforms(const float* __restrict__ x, float* __restrict__ V, WinoGeom g, const
     }
     if constexpr (KERNELS == KERNELS_PLAIN)
         kernel_transform_block<M>(w, static_cast<float*>(U), g.C, g.CpU, g.K, g.Kp, block);
-    else if constexpr (KERNELS == KERNELS_SPLIT)
-        kernel_transform_split_block<M>(w, static_cast<u32x4*>(U), g.C, g.K, chunks, Kb16, block / Mats<M>::n, block % Mats<M>::n);
-    else
+    else if constexpr (KERNELS == KERNELS_SPLIT) {
+        __shared__ float rows[16 * SPLIT_ROW_PITCH];
+        kernel_transform_split_block<M>(w, static_cast<u32x4*>(U), g.C, g.K, chunks, Kb16, block, rows);
+    } else
         split_planes_block(w, static_cast<u32x4*>(U), g.K, g.C, (g.C + 15) / 16 * 16, (g.K + 31) / 32 * 32, chunks, Kb16, block);
 }
 
@@ -474,7 +449,7 @@ hipError_t launch_transforms(const float* x, float* V, const WinoGeom& g, const 
     const int chunks = (g.C + 31) / 32;
     const long long pieces = ((long long)chunks * Kb16 * 64 + 255) / 256;
     const long long blocks = kind == WINO_KERNELS_PLAIN ? ((long long)g.CpU * g.Kp + 255) / 256
-                             : kind == WINO_KERNELS_SPLIT ? pieces * n : kind == WINO_KERNELS_GIVEN ? pieces * n * n : 0;
+                             : kind == WINO_KERNELS_SPLIT ? (long long)chunks * Kb16 : kind == WINO_KERNELS_GIVEN ? pieces * n * n : 0;
     const int across = (g.tiles + 255) / 256;
     const long long total = blocks + (long long)across * g.Cp;
     if (total > 0x7fffffffLL) return hipErrorInvalidValue;
