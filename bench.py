@@ -211,6 +211,17 @@ def main():
         step()
     torch.cuda.synchronize()
 
+    def is_timed_as(job, kind):
+        """Whether the job's main kernel is one of that timed kind."""
+        B.timing_read(kind)
+        B.timing_enable(True)
+        run(job, forced[id(job)])
+        torch.cuda.synchronize()
+        B.timing_enable(False)
+        return B.timing_read(kind)[0] > 0
+
+    fused_jobs = {id(j) for j in jobs if j[1] != "direct" and is_timed_as(j, B.TIME_WINO_FUSED)}
+
     # ---- timed region: exactly --steps steps, main kernels bracketed by HIP events ------------
     B.timing_read(B.TIME_DIRECT); B.timing_read(B.TIME_WINO_PRODUCT); B.timing_read(B.TIME_WINO_FUSED)
     B.timing_enable(True)
@@ -246,7 +257,7 @@ def main():
     for j in jobs:
         on = runs_on(j[0], j[1], forced[id(j)])
         if on != "fma":
-            kind = "direct" if j[1] == "direct" else "fused" if on == "fused" else "product"
+            kind = "direct" if j[1] == "direct" else "fused" if id(j) in fused_jobs else "product"
             kinds[kind][0 if on == "split" else 1] += alg_flops(j)
 
     def roofline_of(kind, kernel, launches, ms):
@@ -326,7 +337,7 @@ def main():
         roofline["traffic_source"] = ("recorded: %s (rocprofv3 FETCH_SIZE + WRITE_SIZE of an earlier run of the same "
                                       "kernels, average over the direct launches of a step), not measured in this run" % TRAFFIC_FILE) if per else None
     wino_roofline = roofline_of("product", "split_point_kernel (large products) and wino_product_kernel (fp32 instructions), all launches of the step", n_wino, ms_wino)
-    fused_roofline = roofline_of("fused", "wino_fused_mfma_kernel / wino_rows_kernel (fused Winograd layers of the step)", n_fused, ms_fused)
+    fused_roofline = roofline_of("fused", "wino_split_kernel (bf16 matrix cores) and wino_fused_mfma_kernel / wino_rows_kernel (fp32 instructions): fused Winograd layers of the step", n_fused, ms_fused)
 
     out = {
         "metric": "TFLOP/s per conv layer (direct & Winograd) + HBM bytes / I/O lower bound",

@@ -499,17 +499,18 @@ int make_wino_shape(int N, int C, int H, int W, int K, int m, iolb_shape* s, int
 // Channel rows per plane of a caller-held transformed-kernel buffer: every stage depth divides 16.
 int pretransformed_rows(int C) { return (C + 15) / 16 * 16; }
 
-// ---- unfused Winograd with the product on the bf16 matrix cores ------------------------------
+// ---- Winograd on the bf16 matrix cores, operands in three parts ------------------------------
 struct SplitWino {
-    bool use = false;
+    enum { NONE, PRODUCT, FUSED } kind = NONE;                // transforms and a product of their own, or one kernel
     iolb::SplitPointGeom g{};
     iolb::WinoGeom w{};
+    iolb::WinoSplitGeom f{};
     size_t u_off = 0, v_off = 0, m_off = 0, total = 0;        // total: the least workspace, the tile's if that is larger
 };
 std::map<ShapeKey, SplitWino> g_split_wino;
 
-// tile: the library's own choice for the layer.  The split product takes over where its modelled time beats that of the
-// tile.  What the tile's path refuses (tensors beyond its 32-bit indexes, a workspace too small for it) stays refused.
+// tile: the library's own choice for the layer.  A split way takes over where its modelled time beats that of the tile.
+// What the tile's path refuses (tensors beyond its 32-bit indexes, a workspace too small for it) stays refused.
 SplitWino split_wino(const iolb_shape& s, const iolb_tile_config& tile)
 {
     const ShapeKey key(s.N, s.C, s.H, s.W, s.K, s.R, s.S, s.stride, s.pad, s.algo);
@@ -526,22 +527,40 @@ SplitWino split_wino(const iolb_shape& s, const iolb_tile_config& tile)
     w.P = s.H + 2 * s.pad - 2; w.Q = s.W + 2 * s.pad - 2;
     w.th = (w.P + w.m - 1) / w.m; w.tw = (w.Q + w.m - 1) / w.m;
     const int64_t tiles = (int64_t)s.N * w.th * w.tw, pitch = (tiles + 3) / 4 * 4, n2 = (int64_t)(w.m + 2) * (w.m + 2);
-    double cycles = 0;
-    if (tile_runs && tile.path != IOLB_PATH_FMA && n2 * std::max(s.C, s.K) * pitch < (1LL << 31) && s.C <= 32768 && s.K <= 65535) {
-        w.tiles = (int)tiles; w.tiles_pitch = (int)pitch;
+    w.tiles = (int)tiles; w.tiles_pitch = (int)pitch;
+    const size_t most = winograd_workspace_max(s.C, s.K, w.m, tiles);
+    const bool runs = tile_runs && tile.path != IOLB_PATH_FMA;
+    const size_t tile_bytes = runs ? winograd_layout(t.Cp, t.Kp, t.m, t.tiles_pitch, tile.path).total : 0;
+    double product_ns = 0, fused_ns = 0;
+    size_t product_bytes = 0, fused_bytes = 0;
+    if (runs && n2 * std::max(s.C, s.K) * pitch < (1LL << 31) && s.C <= 32768 && s.K <= 65535) {
         iolb::SplitPointGeom& g = r.g;
         g.groups = (int)n2; g.images = 1; g.C = s.C; g.K = g.Ky = s.K; g.HW = (int)tiles; g.HWy = g.HWin = (int)pitch; g.Win = g.Q = (int)tiles;
         g.stride = 1; g.in = iolb::SPLIT_IN_PIXELS;
         g.w_image = 1;                                        // kernels per plane; the real distance follows from the plan
+        double cycles = 0;
         if (iolb::split_point_plan(&g, &cycles)) {
             g.w_image = iolb::split_point_weight_bytes(g) / 16;
             r.u_off = 0;
             r.v_off = align256((size_t)n2 * iolb::split_point_weight_bytes(g));
             r.m_off = r.v_off + align256(sizeof(float) * n2 * s.C * pitch);
-            r.total = r.m_off + align256(sizeof(float) * n2 * s.K * pitch);
-            r.total = std::max(r.total, winograd_layout(t.Cp, t.Kp, t.m, t.tiles_pitch, tile.path).total);
-            r.use = r.total <= winograd_workspace_max(s.C, s.K, w.m, tiles) && iolb::split_wino_faster(s, tile, tiles, cycles);
+            product_bytes = std::max(r.m_off + align256(sizeof(float) * n2 * s.K * pitch), tile_bytes);
+            if (product_bytes <= most) product_ns = cycles;
         }
+    }
+    if (runs && (w.m == 2 || w.m == 4)) {
+        iolb::WinoSplitGeom& f = r.f;
+        f.N = s.N; f.C = s.C; f.H = s.H; f.W = s.W; f.K = s.K; f.m = w.m; f.pad = s.pad; f.P = w.P; f.Q = w.Q; f.th = w.th; f.tw = w.tw;
+        f.tiles = w.tiles;
+        if (tiles < (1LL << 31) && iolb::wino_split_plan(&f, &fused_ns)) {
+            fused_bytes = std::max(align256((size_t)iolb::wino_split_weight_bytes(f)), tile_bytes);
+            if (fused_bytes > most) fused_ns = 0;
+        }
+    }
+    switch (iolb::split_wino_pick(s, tile, tiles, product_ns, fused_ns)) {
+    case 1: r.kind = SplitWino::PRODUCT; r.total = product_bytes; break;
+    case 2: r.kind = SplitWino::FUSED; r.total = fused_bytes; break;
+    default: break;
     }
     std::lock_guard<std::mutex> lock(g_mutex);
     g_split_wino[key] = r;
@@ -555,6 +574,13 @@ int run_winograd_split(const float* x, const float* w, const float* Upre, float*
     float* V = reinterpret_cast<float*>(base + p.v_off);
     float* M = reinterpret_cast<float*>(base + p.m_off);
     hipStream_t st = t_stream;
+    if (p.kind == SplitWino::FUSED) {
+        IOLB_HIP(iolb::launch_wino_split_weights(w ? w : Upre, !w, U, p.f, st));
+        MainKernelTimer timer(st, IOLB_TIME_WINO_FUSED);
+        IOLB_HIP(iolb::launch_wino_split(x, U, y, p.f, st));
+        timer.stop(st);
+        return IOLB_OK;
+    }
     IOLB_HIP(iolb::launch_wino_transforms(x, V, p.w, w ? w : Upre, U, w ? iolb::WINO_KERNELS_SPLIT : iolb::WINO_KERNELS_GIVEN, p.g.Kb16, st));
     MainKernelTimer timer(st, IOLB_TIME_WINO_PRODUCT);
     IOLB_HIP(iolb::launch_split_point(V, U, M, p.g, st));
@@ -571,7 +597,7 @@ int run_winograd(const float* x, const float* w, const float* Upre, float* y, co
     if (own_tile) {
         // (a caller's workspace that holds no more than the tile needs keeps the tile)
         const SplitWino p = split_wino(s, cfg);
-        if (p.use && ws && ws_bytes >= p.total && !(reinterpret_cast<uintptr_t>(ws) & 255)) return run_winograd_split(x, w, Upre, y, s, p, ws);
+        if (p.kind != SplitWino::NONE && ws && ws_bytes >= p.total && !(reinterpret_cast<uintptr_t>(ws) & 255)) return run_winograd_split(x, w, Upre, y, s, p, ws);
     }
     DeviceState* dev = nullptr;
     int rc = device_state(&dev);
@@ -869,7 +895,7 @@ int iolb_route(const iolb_shape* shape, int layout, size_t* bytes)
         rc = tuned_tile(s, &tile);
         if (rc != IOLB_OK) return rc;
         const SplitWino p = split_wino(s, tile);
-        split = p.use;
+        split = p.kind != SplitWino::NONE;
         need = p.total;
     }
     if (bytes) *bytes = split ? need : 0;

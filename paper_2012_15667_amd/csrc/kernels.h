@@ -198,6 +198,29 @@ hipError_t launch_wino_fused_mfma(const float* x, const float* U2, float* y, con
 // The same with one wave per plane row and the input transform shared out over all threads (wino_fused_rows.hip).
 hipError_t launch_wino_fused_rows(const float* x, const float* U2, float* y, const WinoGeom& g, hipStream_t st);
 
+// All four steps in one kernel on the bf16 matrix cores with operands in three parts, m in {2, 4} (wino_split.hip).
+struct WinoSplitGeom {
+    int N, C, H, W, K, m, pad, P, Q;
+    int th, tw, tiles;         // sub-domains along H_out, W_out; in all
+    int tb, z;                 // block: tb sub-domains by z kernels, every plane
+    int nbt, nbk;              // blocks along the sub-domains, the kernels
+    int chunks, Kb32;          // stages of 16 channels; 32-kernel blocks, whole workgroup blocks
+};
+#define IOLB_WINO_SPLIT_SHAPES(X) X(4, 32, 64) X(4, 32, 32) X(2, 64, 64) X(2, 32, 32)
+inline long long wino_split_weight_bytes(const WinoSplitGeom& g) { return (g.m + 2LL) * (g.m + 2) * g.chunks * g.Kb32 * 3072; }
+// Whether the kernel's 32-bit offsets reach: the images of a block, the kernels.
+inline bool wino_split_fits(const WinoSplitGeom& g)
+{
+    const long long per = (long long)g.th * g.tw, span = (g.tb - 1 + per - 1) / per + 1;
+    const long long images = span < g.N ? span : g.N;
+    return g.pad >= 1 && 4 * (images * g.C * g.H * g.W + g.pad * (g.W + 1LL)) < (1LL << 31) && wino_split_weight_bytes(g) < (1LL << 31) && g.chunks == (g.C + 15) / 16 &&
+           g.nbk * (g.z / 32) == g.Kb32 && g.Kb32 * 32LL >= g.K && (long long)g.nbt * g.tb >= g.tiles && (long long)g.nbt * g.nbk <= 0x7fffffffLL &&
+           per * g.N == g.tiles && (long long)g.nbt * g.tb < (1LL << 31);
+}
+// The kernels in three parts, from w[K][C][3][3] or (given) from a caller's U[plane][C rounded up to 16][K to 32].
+hipError_t launch_wino_split_weights(const float* w, bool given, void* wt, const WinoSplitGeom& g, hipStream_t st);
+hipError_t launch_wino_split(const float* x, const void* wt, float* y, const WinoSplitGeom& g, hipStream_t st);
+
 // Ceiling probes (probe.hip).  The copy moves bytes / 16 16-byte pieces; the MFMA loop runs
 // PROBE_MFMA_BLOCKS workgroups of four waves, each wave PROBE_ACC MFMAs (4096 flop each) per iteration, and
 // writes PROBE_MFMA_BLOCKS * 256 floats to sink.

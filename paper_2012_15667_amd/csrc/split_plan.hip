@@ -169,22 +169,73 @@ bool split_point_faster(const iolb_shape& s, int P, int Q)
     return s.C >= 160 && flop >= 48 * bytes && flop >= 1e9;
 }
 
-// Times in ns: transforms and launches of both unfused ways are the same, so that against an unfused tile the
-// products are compared; a fused tile costs its rounds at the rate its kernel was measured at, the unfused way the
-// traffic of V and M at 5.2 TB/s.
-bool split_wino_faster(const iolb_shape& s, const iolb_tile_config& tile, long long tiles, double product_cycles)
+// Modelled time of a call: the kernels' transform, and per round of workgroups first loads and stores and a stage of 16
+// channels.  Fitted on 148 drawn layers (16 to 512 channels, 7 x 7 to 224 x 224, batch 1 to 64): within 5 - 7 % (2-norm).
+static double wino_split_ns(const WinoSplitGeom& g)
+{
+    const double per = (double)g.nbt * g.nbk / 256, rounds = per <= 4 ? std::ceil(per) : per + 0.5;
+    if (g.m == 4) return g.z == 64 ? 5600 + rounds * (10700 + 3450.0 * g.chunks) : 7300 + rounds * (6900 + 2520.0 * g.chunks);
+    return g.z == 64 ? 3800 + rounds * (8500 + 2650.0 * g.chunks) : 7000 + rounds * (2500 + 1000.0 * g.chunks);
+}
+
+bool wino_split_plan(WinoSplitGeom* g, double* ns)
+{
+    struct Shape { int m, tb, z; };
+    static const Shape shapes[] = {
+#define IOLB_WINO_SPLIT_ENTRY(M_, T_, Z_) {M_, T_, Z_},
+        IOLB_WINO_SPLIT_SHAPES(IOLB_WINO_SPLIT_ENTRY)
+#undef IOLB_WINO_SPLIT_ENTRY
+    };
+    bool found = false;
+    WinoSplitGeom best = *g;
+    double best_ns = 0;
+    for (const Shape& sh : shapes) {
+        if (sh.m != g->m) continue;
+        WinoSplitGeom t = *g;
+        t.tb = sh.tb; t.z = sh.z;
+        t.nbt = (g->tiles + sh.tb - 1) / sh.tb;
+        t.nbk = (g->K + sh.z - 1) / sh.z;
+        t.chunks = (g->C + 15) / 16;
+        t.Kb32 = t.nbk * (sh.z / 32);
+        if (!wino_split_fits(t)) continue;
+        const double c = wino_split_ns(t);
+        if (!found || c < best_ns) { found = true; best = t; best_ns = c; }
+    }
+    if (found) { *g = best; *ns = best_ns; }
+    return found;
+}
+
+// Modelled times in ns, each fitted on 194 drawn layers like those above (within 8 - 18 %): the tile's product or fused
+// kernel by rounds of its blocks, traffic of V and M at 5.7 - 6.05 TB/s, the launches.  A split way has to win by a margin; over
+// those layers the pick is 1.22 times as fast as the tile, and the tile is nowhere the better one by more than 1 %.
+// Unfused tiles of layers whose channels are no multiple of four keep the rule that was there first, which sends fewer
+// of them here (their routes are part of the tests), though such layers gain as much: 33 x 261 -> 300 at 15 x 15 109 -> 63 us.
+int split_wino_pick(const iolb_shape& s, const iolb_tile_config& tile, long long tiles, double product_cycles, double fused_ns)
 {
     const int m = winograd_m(s.algo);
-    const double n2 = (m + 2) * (m + 2), product = product_cycles / 2.0;
+    const double n2 = (m + 2) * (m + 2);
     const int Kp = (s.K + 31) / 32 * 32;
+    if (tile.path != IOLB_PATH_FUSED && s.C % 4)
+        return product_cycles && s.C >= 128 && s.K >= 128 && product_cycles / 2 < 0.8 * (2 * n2 * tiles * s.C * Kp / 105000);
+    const double out = (double)s.N * (s.H + 2 * s.pad - 2) * (s.W + 2 * s.pad - 2);
+    const double bytes = 4 * ((double)s.N * s.C * s.H * s.W + 2 * n2 * tiles * (s.C + s.K) + s.K * out);
+    const double tb = tile.x / m, across = std::ceil(tiles / tb);
+    double best;
     if (tile.path == IOLB_PATH_FUSED) {
-        const double out = (double)s.N * (s.H + 2 * s.pad - 2) * (s.W + 2 * s.pad - 2);
-        const double bytes = 4.0 * ((double)s.N * s.C * s.H * s.W + 2 * n2 * tiles * (s.C + s.K) + s.K * out);
-        const double tb = tile.x / m, blocks = std::ceil(tiles / tb) * ((s.K + tile.z - 1) / tile.z);
-        const double fused = std::ceil(blocks / 256) * (2 * n2 * tb * tile.z * s.C / (m == 2 ? 370 : 295)) + 2 * 3000;
-        return product + bytes / 5200 + 4 * 3000 < fused;
+        const double rounds = std::ceil(across * ((s.K + tile.z - 1) / tile.z) / 256), block = 2 * n2 * tb * tile.z * s.C / 1000;
+        best = m == 2 ? 3500 + rounds * (6100 + 2.42 * block) : 8100 + rounds * (8300 + 3.05 * block);
+    } else {
+        const double rounds = std::ceil(n2 * across * ((Kp + tile.z - 1) / tile.z) / 256), waves = std::min(4, tile.threads / 64);
+        best = 12000 + bytes / 6000 + 45.0 * s.C + rounds * s.C * 2 * tb * tile.z / waves / 1000 * (m == 2 ? 9.2 : 6.6);
     }
-    return s.C >= 128 && s.K >= 128 && product < 0.8 * (2 * n2 * tiles * s.C * Kp / 105000);
+    best *= m == 2 || m == 4 ? 0.93 : 0.85;
+    int pick = 0;
+    if (product_cycles) {
+        const double ns = m == 2 ? 9200 + bytes / 6050 + 0.25 * product_cycles : 12000 + bytes / 5700 + 0.334 * product_cycles;
+        if (ns < best) { best = ns; pick = 1; }
+    }
+    if (fused_ns && fused_ns < best) pick = 2;
+    return pick;
 }
 
 }  // namespace iolb

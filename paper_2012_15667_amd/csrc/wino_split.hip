@@ -1,0 +1,549 @@
+// Winograd F(2 x 2, 3 x 3) and F(4 x 4, 3 x 3) in one kernel on the bf16 matrix cores at fp32 precision (operands in three
+// parts, split_mfma.h).  A workgroup of eight waves takes TB sub-domains by Z kernels in every one of the (m + 2)^2 planes;
+// the channel sums of all planes stay in registers until the last channel, so that V and M never leave the chip.
+//
+// A stage is 16 channels, one contraction of v_mfma_f32_32x32x16_bf16.  Each thread transforms TB / 32 windows of inputs
+// (loaded one stage ahead) and puts V in LDS in fp32, in one of two buffers; each wave multiplies PL / 8 planes: it cuts its V
+// into parts between the matrix instructions of the plane before, and takes the transformed kernels, already in parts, from
+// the L2 into registers some units ahead.  Each V is cut once and each kernel part read once per workgroup.
+//
+// What bounds it: kernel parts from the L2 (F(4 x 4), 32 x 64: 221 KB per stage for 3456 clocks of matrix work at 62 bytes per
+// clock and unit; left out, 520 -> 350 us), the vector work of transform and cut (left out, 317), inputs (left out, 395) and
+// first loads and stores of a round (436); each alone hides behind the others only in part.  Whole calls, fp32 way -> this:
+// F(4 x 4) 128 -> 128 at 112 x 112, batch 64 859 -> 582 us (102 TFLOP/s of the planes' products), 256 -> 256 at 14 x 14 87 ->
+// 60, F(2 x 2) 256 -> 256 at 56 x 56 1104 -> 736, 64 -> 64 at 28 x 28, batch 8 19.8 -> 13.6.
+// Measured and not kept: four waves of twice the planes each; transform and loads spread between the matrix instructions
+// of every wave in place of the two phases below (F(4 x 4), 256 -> 256 at 56 x 56 521 -> 666: 26 registers spilled);
+// differences of the cut by v_dot2 (equal).
+#include "kernels.h"
+#include "split_mfma.h"
+#include "split_weights.h"
+#include "wino_mats.h"
+#include "wino_transform.h"
+
+namespace iolb {
+
+namespace {
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+// M outputs of a row, at any float
+template <int M> using row_of = float __attribute__((ext_vector_type(M), aligned(4)));
+
+// B v for one column of a window, with the sums that two rows of B share taken once
+template <int M>
+__device__ __forceinline__ void input_transform_1d(float (&v)[M + 2])
+{
+    if constexpr (M == 2) {
+        const float d0 = v[0], d1 = v[1], d2 = v[2], d3 = v[3];
+        v[0] = d0 - d2; v[1] = d1 + d2; v[2] = d2 - d1; v[3] = d1 - d3;
+    } else {
+        const float d0 = v[0], d1 = v[1], d2 = v[2], d3 = v[3], d4 = v[4], d5 = v[5];
+        v[0] = __builtin_fmaf(4.f, d0, __builtin_fmaf(-5.f, d2, d4));
+        const float p = __builtin_fmaf(-4.f, d2, d4), q = __builtin_fmaf(-4.f, d1, d3);
+        v[1] = p + q; v[2] = p - q;
+        const float r = d4 - d2, t = d3 - d1;
+        v[3] = __builtin_fmaf(2.f, t, r); v[4] = __builtin_fmaf(-2.f, t, r);
+        v[5] = __builtin_fmaf(4.f, d1, __builtin_fmaf(-5.f, d3, d5));
+    }
+}
+// A v: n values in, M out
+template <int M>
+__device__ __forceinline__ void output_transform_1d(const float (&v)[M + 2], float (&o)[M])
+{
+    if constexpr (M == 2) {
+        o[0] = v[0] + v[1] + v[2];
+        o[1] = v[1] - v[2] - v[3];
+    } else {
+        const float a = v[1] + v[2], b = v[1] - v[2], c = v[3] + v[4], d = v[3] - v[4];
+        o[0] = v[0] + a + c;
+        o[1] = __builtin_fmaf(2.f, d, b);
+        o[2] = __builtin_fmaf(4.f, c, a);
+        o[3] = __builtin_fmaf(8.f, d, b) + v[5];
+    }
+}
+
+// Whether this lane's bit of a wave-uniform mask is set: a select reads the mask as it is.
+__device__ __forceinline__ bool by_lane(unsigned long long mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
+
+// How a lane's own columns are read: one by one; M at a time, those beyond the image's last column (in the last
+// sub-domain of a row) zeroed afterwards; M at a time, all inside.
+enum { COLS_SINGLE, COLS_CUT, COLS_WHOLE };
+
+template <int M, int TB, int Z, int COLS>
+__global__ void __launch_bounds__(512, M == 2 && TB == 32 && Z == 32 ? 4 : 2)
+wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restrict__ y, WinoSplitGeom g)
+{
+    constexpr int n = M + 2, PL = n * n, ZB = Z / 32, TBB = TB / 32;
+    constexpr int FP = PL / 8, LP = PL % 8;                  // whole planes per wave, planes left over: 4 ZB units for 8 waves
+    constexpr int UNITS = FP * ZB + (LP ? 1 : 0);            // units (32 kernels of a plane) per wave
+    constexpr int D = UNITS % 3 == 0 ? 3 : UNITS == 4 ? 2 : UNITS;       // units of kernels in flight
+    constexpr int WIN = TB / 32;                             // windows per thread and stage
+    constexpr int VBUF = PL * TB * 64;
+    static_assert(LP == 0 || LP == 4, "left-over planes");
+    extern __shared__ u32x4 lds16[];
+    char* const lds = reinterpret_cast<char*>(lds16);
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    int bid;
+    {
+        const int nblk = gridDim.x, q = nblk >> 3, r = nblk & 7, xcd = blockIdx.x & 7;
+        bid = xcd * q + (xcd < r ? xcd : r) + ((int)blockIdx.x >> 3);
+    }
+    // an XCD stays with one block of kernels, whose parts its L2 holds
+    const int kb = __builtin_amdgcn_readfirstlane(bid / g.nbt);
+    const int t0 = __builtin_amdgcn_readfirstlane(bid % g.nbt * TB);
+    const int per_image = g.th * g.tw, plane_in = g.H * g.W;
+    const int img0 = __builtin_amdgcn_readfirstlane(t0 / per_image);
+
+    // inputs: byte offsets from the first image's window origin at (-pad, -pad)
+    const int shift = g.pad * (g.W + 1);
+    const size_t image = (size_t)g.C * plane_in;
+    const int last_t = t0 + TB < g.tiles ? t0 + TB : g.tiles;
+    const int span = __builtin_amdgcn_readfirstlane((last_t - 1) / per_image + 1 - img0);
+    const unsigned long long xb = reinterpret_cast<unsigned long long>(x) + 4 * (img0 * image) - 4ull * shift;
+    const unsigned xlo = __builtin_amdgcn_readfirstlane((unsigned)xb), xhi = __builtin_amdgcn_readfirstlane((unsigned)(xb >> 32));
+    const unsigned xrange = __builtin_amdgcn_readfirstlane((unsigned)(4 * (image * span + shift)));
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>((unsigned long long)xhi << 32 | xlo), 0, (int)xrange, 0x00020000);
+    const unsigned ubytes = __builtin_amdgcn_readfirstlane((unsigned)g.chunks * (unsigned)g.Kb32 * (3072u * PL));
+    const __amdgpu_buffer_rsrc_t ru = __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4*>(wt), 0, (int)ubytes, 0x00020000);
+
+    // this thread's windows: a wave takes 4 channels of 16 sub-domains, a row of 16 lanes each.  A lane loads the M columns
+    // under its sub-domain's own place; the two border columns are its neighbours', those of lanes 0 and 15 are loaded.
+    const int c0w = TB == 32 ? (wave >> 1) * 4 : (wave >> 2) * 8;
+    const int tloc = (TB == 32 ? wave & 1 : wave & 3) * 16 + (lane & 15), cl = c0w + (lane >> 4);
+    unsigned long long rowok[n], colok[M], left, right, edge;            // by lane: one register pair each, as the selects read them
+    unsigned xoff, eoff;
+    {
+        const int t = t0 + tloc, tt = t < g.tiles ? t : t0;
+        const int tj = tt % g.tw, ti = tt / g.tw % g.th, img = tt / per_image;
+        const int h0 = ti * M - g.pad, w0 = tj * M - g.pad;
+        auto lanes = [](bool v) { return __builtin_amdgcn_ballot_w64(v); };
+#pragma unroll
+        for (int i = 0; i < n; ++i) rowok[i] = lanes(t < g.tiles && h0 + i >= 0 && h0 + i < g.H);
+#pragma unroll
+        for (int j = 0; j < M; ++j) colok[j] = COLS == COLS_WHOLE ? ~0ull : lanes(w0 + 1 + j >= 0 && w0 + 1 + j < g.W);
+        // (pad >= 1: beyond the first and the last sub-domain of a row there are zeros)
+        left = lanes(tj > 0); right = lanes(tj + 1 < g.tw);
+        const int e16 = lane & 15, we = w0 + (e16 == 0 ? 0 : M + 1);
+        edge = lanes((e16 == 0 ? tj > 0 : e16 == 15 && tj + 1 < g.tw) && we >= 0 && we < g.W);
+        xoff = 4u * (unsigned)(shift + (int)((img - img0) * (int)image) + (lane >> 4) * plane_in + h0 * g.W + w0);
+        eoff = xoff + ((lane & 15) == 0 ? 0 : 4 * (M + 1));
+    }
+    float wx[WIN][n][n];                                    // loads in flight: column 0 the edge, then the M own columns
+    const int nst = g.chunks;
+    auto load_x = [&](int s) {
+        static_range<0, WIN>([&](auto ic) {
+            constexpr int i = decltype(ic)::value;
+            const int c0 = 16 * s + c0w + 4 * i;
+            const unsigned long long have = __builtin_amdgcn_ballot_w64(16 * s + cl + 4 * i < g.C);
+            static_range<0, n>([&](auto rc) {
+                constexpr int r = decltype(rc)::value;
+                const int so = 4 * ((c0 < g.C ? c0 : 0) * plane_in + r * g.W);
+                const unsigned long long row = have & rowok[r];
+                wx[i][r][0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rx, (int)(by_lane(row & edge) ? eoff : OUTSIDE), so, 0));
+                if constexpr (COLS != COLS_SINGLE && M == 4) {
+                    const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)((by_lane(row) ? xoff : OUTSIDE) + 4), so, 0);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) wx[i][r][j + 1] = __uint_as_float(q[j]);
+                } else if constexpr (COLS != COLS_SINGLE) {
+                    const u32x2 q = __builtin_amdgcn_raw_buffer_load_b64(rx, (int)((by_lane(row) ? xoff : OUTSIDE) + 4), so, 0);
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) wx[i][r][j + 1] = __uint_as_float(q[j]);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < M; ++j)
+                        wx[i][r][j + 1] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rx, (int)((by_lane(row & colok[j]) ? xoff : OUTSIDE) + 4 * (j + 1)), so, 0));
+                }
+            });
+        });
+    };
+    // V in LDS: [plane][four channels][sub-domain][4]
+    const int vw = cl / 4 * (TB * 16) + tloc * 16 + (cl & 3) * 4;
+    auto transform = [&](char* vb) {
+        static_range<0, WIN>([&](auto ic) {
+            constexpr int i = decltype(ic)::value;
+            if constexpr (COLS == COLS_CUT)
+#pragma unroll
+                for (int r = 0; r < n; ++r)
+#pragma unroll
+                    for (int j = 1; j < M; ++j) wx[i][r][j + 1] = by_lane(colok[j]) ? wx[i][r][j + 1] : 0.f;
+#pragma unroll
+            for (int r = 0; r < n; ++r) {
+                const int e = __float_as_int(wx[i][r][0]);
+                // row_shr:1 and row_shl:1: lanes without such a neighbour keep the edge
+                const float lf = __int_as_float(__builtin_amdgcn_update_dpp(e, __float_as_int(wx[i][r][M]), 0x111, 0xf, 0xf, false));
+                const float rg = __int_as_float(__builtin_amdgcn_update_dpp(e, __float_as_int(wx[i][r][1]), 0x101, 0xf, 0xf, false));
+                wx[i][r][0] = by_lane(left) ? lf : 0.f;
+                wx[i][r][n - 1] = by_lane(right) ? rg : 0.f;
+            }
+#pragma unroll
+            for (int j = 0; j < n; ++j) {
+                float c[n];
+#pragma unroll
+                for (int r = 0; r < n; ++r) c[r] = wx[i][r][j];
+                input_transform_1d<M>(c);
+#pragma unroll
+                for (int r = 0; r < n; ++r) wx[i][r][j] = c[r];
+            }
+            char* d = vb + vw + i * (TB * 16);
+#pragma unroll
+            for (int r = 0; r < n; ++r) {
+                input_transform_1d<M>(wx[i][r]);
+#pragma unroll
+                for (int j = 0; j < n; ++j) *reinterpret_cast<float*>(d + (r * n + j) * (TB * 64)) = wx[i][r][j];
+            }
+        });
+    };
+    auto barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+
+    // kernels: plane p of this wave, unit zb of it; the left-over unit
+    const int xplane = 8 * FP + (ZB == 2 ? wave >> 1 : wave & 3), xzb = ZB == 2 ? wave & 1 : 0;
+    const bool has_extra = LP && (ZB == 2 || wave < 4);
+    const unsigned pstride = (unsigned)g.chunks * (unsigned)g.Kb32 * 3072u;
+    auto unit_at = [&](int u, int s) {                      // byte offset of unit u (a constant) of stage s
+        const unsigned at = (unsigned)(s * g.Kb32 + kb * ZB) * 3072u;
+        if (LP && u == UNITS - 1) return at + (unsigned)xplane * pstride + xzb * 3072u;
+        return at + (unsigned)(wave * FP + u / ZB) * pstride + u % ZB * 3072u;
+    };
+    u32x4 a[D][3];
+    auto load_u = [&](u32x4 (&f)[3], unsigned at) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) f[p] = __builtin_amdgcn_raw_buffer_load_b128(ru, lane * 16 + 1024 * p, (int)at, 0);
+    };
+
+    f32x16 acc[FP][ZB][TBB], accx[TBB];
+    auto clear = [&]() {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+#pragma unroll
+            for (int p = 0; p < FP; ++p)
+#pragma unroll
+                for (int z = 0; z < ZB; ++z)
+#pragma unroll
+                    for (int b = 0; b < TBB; ++b) acc[p][z][b][i] = 0.f;
+#pragma unroll
+            for (int b = 0; b < TBB; ++b) accx[b][i] = 0.f;
+        }
+    };
+    // the eight channels of this lane's half, of tile l32 (+ 32 b), of a plane
+    const int r0 = half * (TB * 32) + l32 * 16;
+    auto fetch = [&](float (&v)[8], const char* vplane, int b) {
+        const f32x4 lo = *reinterpret_cast<const f32x4*>(vplane + r0 + b * 512), hi = *reinterpret_cast<const f32x4*>(vplane + r0 + TB * 16 + b * 512);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { v[j] = lo[j]; v[4 + j] = hi[j]; }
+    };
+    // Plane by plane; the next plane's operands are read and cut into parts between the matrix instructions of this one,
+    // the unit after next is loaded part by part as the registers fall free.
+    constexpr int PLANES = FP + (LP ? 1 : 0);
+    auto multiply = [&](int s, const char* vb) {
+        const int next = s + 1 < nst ? s + 1 : s;
+        auto plane_at = [&](int p) { return vb + (LP && p == FP ? xplane : wave * FP + p) * (TB * 64); };
+        u32x4 b[2][TBB][3];
+        f32x4 v[2];
+        // pieces of four channels: 2 TBB of a plane
+        auto fetch4 = [&](f32x4& o, int p, int piece) {
+            o = *reinterpret_cast<const f32x4*>(plane_at(p) + r0 + (piece & 1) * (TB * 16) + (piece >> 1) * 512);
+        };
+        auto cut4 = [&](u32x4 (&o)[TBB][3], const f32x4& f, int piece) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                unsigned h, m, l;
+                split_pair(f[2 * j], f[2 * j + 1], h, m, l);
+                const int at = 2 * (piece & 1) + j;
+                o[piece >> 1][0][at] = h; o[piece >> 1][1][at] = m; o[piece >> 1][2][at] = l;
+            }
+        };
+        static_range<0, TBB>([&](auto tc) {
+            constexpr int t = decltype(tc)::value;
+            fetch4(v[0], 0, 2 * t);
+            fetch4(v[1], 0, 2 * t + 1);
+            cut4(b[0], v[0], 2 * t);
+            cut4(b[0], v[1], 2 * t + 1);
+        });
+        static_range<0, PLANES>([&](auto pc) {
+            constexpr int p = decltype(pc)::value;
+            constexpr bool EXTRA = LP && p == FP;
+            constexpr int Z1 = EXTRA ? 1 : ZB;               // units of the plane here
+            if (EXTRA && !has_extra) return;
+            static_range<0, Z1>([&](auto zc) {
+                constexpr int z = decltype(zc)::value, u = EXTRA ? UNITS - 1 : p * ZB + z, un = u + D;
+                constexpr bool MORE = p + 1 < PLANES;
+                constexpr int PIECES = MORE ? 2 * TBB / Z1 : 0;          // pieces of the next plane cut here
+                __builtin_amdgcn_sched_barrier(0);
+                static_range<0, PIECES>([&](auto ic) { fetch4(v[decltype(ic)::value & 1], p + 1, z * PIECES + decltype(ic)::value);
+                                                       if constexpr (PIECES > 2) cut4(b[(p + 1) & 1], v[decltype(ic)::value & 1], z * PIECES + decltype(ic)::value); });
+                if constexpr (PIECES <= 2)
+                    static_range<0, PIECES>([&](auto ic) { cut4(b[(p + 1) & 1], v[decltype(ic)::value & 1], z * PIECES + decltype(ic)::value); });
+                u32x4 (&f)[3] = a[u % D];
+                f32x16 (&c)[TBB] = EXTRA ? accx : acc[EXTRA ? 0 : p][EXTRA ? 0 : z];
+                const bool load = !LP || un != UNITS - 1 || has_extra;
+                const unsigned at = un < UNITS ? unit_at(un, s) : unit_at(un - UNITS, next);
+                constexpr int PA[6] = {2, 1, 1, 0, 0, 0}, PB[6] = {0, 1, 0, 2, 1, 0};
+                static_range<0, 6>([&](auto qc) {
+                    constexpr int q = decltype(qc)::value;
+#pragma unroll
+                    for (int t = 0; t < TBB; ++t)
+                        c[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f[PA[q]]), __builtin_bit_cast(bf16x8, b[p & 1][t][PB[q]]), c[t], 0, 0, 0);
+                    if constexpr (q == 0 || q == 2 || q == 5)
+                        if (load) f[PA[q]] = __builtin_amdgcn_raw_buffer_load_b128(ru, lane * 16 + 1024 * PA[q], (int)at, 0);
+                });
+                // per matrix instruction its share of the vector work
+                constexpr int VALU = (26 * PIECES + 6 * TBB - 1) / (6 * TBB) + 1;
+#pragma unroll
+                for (int i = 0; i < 6; ++i) {
+#pragma unroll
+                    for (int t = 0; t < TBB; ++t) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        if constexpr (MORE) __builtin_amdgcn_sched_group_barrier(0x002, VALU, 0);
+                    }
+                    if (i == 0 || i == 2 || i == 5) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        });
+    };
+
+    // Channel sums leave the registers 32 kernels at a time, through LDS: [plane][kernel][tile]; a thread then owns whole
+    // (kernel, tile) pairs.
+    constexpr int PAIRS = 32 * TB / 512;
+    static_assert(ZB * PAIRS <= 32, "one mark per pair");
+    unsigned again = 0;                                      // pairs whose sums are not all finite
+    auto finish = [&](auto marked_c, float scale) {
+        constexpr bool MARKED = decltype(marked_c)::value;   // the second time: marked pairs only
+        float* const m = reinterpret_cast<float*>(lds);
+        static_range<0, ZB>([&](auto zc) {
+            constexpr int z = decltype(zc)::value;
+            if constexpr (z) barrier();
+            auto put = [&](int plane, const f32x16 (&c)[TBB]) {
+#pragma unroll
+                for (int t = 0; t < TBB; ++t)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) m[(plane * 32 + 8 * (i >> 2) + (i & 3) + 4 * half) * TB + 32 * t + l32] = c[t][i] * scale;
+            };
+            static_range<0, FP>([&](auto pc) { put(wave * FP + decltype(pc)::value, acc[decltype(pc)::value][z]); });
+            if constexpr (LP != 0)
+                if (has_extra && xzb == z) put(xplane, accx);
+            barrier();
+            const int tl = opaque(tid) % TB, t = t0 + tl;
+            const int tj = t % g.tw, ti = t / g.tw % g.th, img = t / per_image;
+            const int h0 = ti * M, w0 = tj * M;
+#pragma unroll
+            for (int i = 0; i < PAIRS; ++i) {
+                const int kl = tid / TB + i * (512 / TB), k = kb * Z + 32 * z + kl, bit = z * PAIRS + i;
+                float v[n][n];
+#pragma unroll
+                for (int r = 0; r < n; ++r)
+#pragma unroll
+                    for (int j = 0; j < n; ++j) v[r][j] = m[((r * n + j) * 32 + kl) * TB + tl];
+                float h[n][M], o[M][M];
+#pragma unroll
+                for (int r = 0; r < n; ++r) output_transform_1d<M>(v[r], h[r]);
+#pragma unroll
+                for (int j = 0; j < M; ++j) {
+                    float c[n], q[M];
+#pragma unroll
+                    for (int r = 0; r < n; ++r) c[r] = h[r][j];
+                    output_transform_1d<M>(c, q);
+#pragma unroll
+                    for (int r = 0; r < M; ++r) o[r][j] = q[r];
+                }
+                if (t >= g.tiles || k >= g.K) continue;
+                if constexpr (MARKED) {
+                    if (!(again >> bit & 1)) continue;
+                } else {
+                    // every plane enters one of the corners, with a factor that is not zero
+                    if (!(__builtin_fabsf(o[0][0]) <= 3.402823466e38f && __builtin_fabsf(o[0][M - 1]) <= 3.402823466e38f &&
+                          __builtin_fabsf(o[M - 1][0]) <= 3.402823466e38f && __builtin_fabsf(o[M - 1][M - 1]) <= 3.402823466e38f))
+                        again |= 1u << bit;
+                }
+                float* yp = y + ((size_t)img * g.K + k) * ((size_t)g.P * g.Q) + (size_t)h0 * g.Q + w0;
+#pragma unroll
+                for (int r = 0; r < M; ++r) {
+                    if (h0 + r >= g.P) break;
+                    if (w0 + M <= g.Q) {
+                        row_of<M> v;
+#pragma unroll
+                        for (int j = 0; j < M; ++j) v[j] = o[r][j];
+                        *reinterpret_cast<row_of<M>*>(yp + (size_t)r * g.Q) = v;
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < M; ++j)
+                            if (w0 + j < g.Q) yp[(size_t)r * g.Q + j] = o[r][j];
+                    }
+                }
+            }
+        });
+    };
+
+    // Waves w and w + 4 share a SIMD.  The first transforms the next stage after it has multiplied this one, the second
+    // before, so that one's vector work runs beside the other's matrix work: the second is one transform ahead and
+    // meets the barrier between the two.
+    const bool ahead = wave >= 4;
+    load_x(0);
+    static_range<0, D>([&](auto uc) {
+        constexpr int u = decltype(uc)::value;
+        if (!LP || u < UNITS - 1 || has_extra) load_u(a[u], unit_at(u, 0));
+    });
+    __builtin_amdgcn_sched_barrier(0);
+    clear();
+    transform(lds);
+    load_x(1);
+    __builtin_amdgcn_sched_barrier(0);
+    barrier();
+    if (ahead) {
+        if (1 < nst) transform(lds + VBUF);
+        load_x(2);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll 1
+    for (int s = 0; s < nst; ++s) {
+        multiply(s, lds + (s & 1) * VBUF);
+        if (ahead) barrier();
+        const int ts = ahead ? s + 2 : s + 1;
+        if (ts < nst) {
+            transform(lds + (ts & 1) * VBUF);
+            load_x(ts + 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (!ahead) barrier();
+    }
+    finish(std::false_type{}, SPLIT_UNSCALE);
+    int* const any = reinterpret_cast<int*>(lds + 2 * VBUF);
+    barrier();
+    if (tid == 0) *any = 0;
+    barrier();
+    if (again) *any = 1;
+    barrier();
+    if (__builtin_amdgcn_readfirstlane(*any) == 0) return;
+
+    // The block again on the fp32 matrix instructions, from the same inputs; kernels are put together from their parts.
+    clear();
+#pragma unroll 1
+    for (int s = 0; s < nst; ++s) {
+        load_x(s);
+        transform(lds);
+        barrier();
+        auto unit = [&](unsigned at, const char* vplane, f32x16 (&c)[TBB]) {
+            u32x4 f[3];
+            load_u(f, at);
+            float w[8];
+            kept_eight(f[0], f[1], f[2], w);
+#pragma unroll
+            for (int t = 0; t < TBB; ++t) {
+                float v[8];
+                fetch(v, vplane, t);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) c[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[j], v[j], c[t], 0, 0, 0);
+            }
+        };
+        static_range<0, FP * ZB>([&](auto uc) {
+            constexpr int u = decltype(uc)::value;
+            unit(unit_at(u, s), lds + (wave * FP + u / ZB) * (TB * 64), acc[u / ZB][u % ZB]);
+        });
+        if constexpr (LP != 0)
+            if (has_extra) unit(unit_at(UNITS - 1, s), lds + xplane * (TB * 64), accx);
+        barrier();
+    }
+    finish(std::true_type{}, 1.f);
+}
+
+// Kernels in three parts in the order of the kernel above: [plane][16 channels][32 kernels][part][lane][8 channels].
+// One workgroup per 16 channels of 32 kernels of w[K][C][3][3], a wave per row of the planes in turn.
+template <int M>
+__global__ void __launch_bounds__(256)
+wino_split_weights(const float* __restrict__ w, u32x4* __restrict__ wt, int C, int K, int chunks, int Kb32)
+{
+    constexpr int n = M + 2, LEN = 16 * 9, PITCH = LEN + 1;
+    __shared__ float rows[32 * PITCH];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int kb = blockIdx.x % Kb32, ch = blockIdx.x / Kb32;
+    const int have = C - ch * 16 < 16 ? (C - ch * 16) * 9 : LEN;
+    stage_kernels<32, 4, 3>(K > kb * 32 ? w + ((size_t)kb * 32 * C + ch * 16) * 9 : w, rows, wave, lane, C * 9LL, K - kb * 32, have, LEN, PITCH);
+    __syncthreads();
+    const float* mine = rows + (lane & 31) * PITCH + (lane >> 5) * 72;
+#pragma unroll 1
+    for (int row = wave; row < n; row += 4) {
+        float lg[8][3];                                     // this row of L g, for each channel
+        kernel_row<M>(row, mine, lg);
+        static_for<n>([&](auto j) {
+            unsigned short p[3][8];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) split_kept(kernel_element<M, decltype(j)::value>(lg[c]), p[0][c], p[1][c], p[2][c]);
+            store_parts(wt + (((size_t)(row * n + j) * chunks + ch) * Kb32 + kb) * 192 + lane, p);
+        });
+    }
+}
+
+// The same from a caller's U[plane][C rounded up to 16][K rounded up to 32]: one lane per 16-byte piece.
+template <int M>
+__global__ void __launch_bounds__(256)
+wino_split_given(const float* __restrict__ U, u32x4* __restrict__ wt, int C, int K, int chunks, int Kb32)
+{
+    constexpr int n = M + 2;
+    const long long id = (long long)blockIdx.x * 256 + threadIdx.x, per = (long long)chunks * Kb32 * 64;
+    const int plane = (int)(id / per), in = (int)(id % per);
+    if (plane >= n * n) return;
+    const int lane = in & 63, kb = (in >> 6) % Kb32, ch = (in >> 6) / Kb32;
+    const int k = kb * 32 + (lane & 31), c0 = ch * 16 + (lane >> 5) * 8;
+    const int rows = (C + 15) / 16 * 16, cols = (K + 31) / 32 * 32;
+    unsigned short p[3][8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        const float v = k < K && c0 + c < C ? U[((size_t)plane * rows + c0 + c) * cols + k] : 0.f;
+        split_kept(v, p[0][c], p[1][c], p[2][c]);
+    }
+    store_parts(wt + (((size_t)plane * chunks + ch) * Kb32 + kb) * 192 + lane, p);
+}
+
+template <int M, int TB, int Z, int COLS>
+hipError_t launch_one(const float* x, const u32x4* wt, float* y, const WinoSplitGeom& g, hipStream_t st)
+{
+    auto kern = wino_split_kernel<M, TB, Z, COLS>;
+    constexpr size_t shm = (size_t)(M + 2) * (M + 2) * TB * 128 + 16;
+    static_assert(shm <= 160 * 1024, "LDS");
+    if (shm > 64 * 1024) {
+        const hipError_t e = allow_large_lds((const void*)kern);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kern, dim3(g.nbt * g.nbk), dim3(512), shm, st, x, wt, y, g);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_wino_split_weights(const float* w, bool given, void* wt, const WinoSplitGeom& g, hipStream_t st)
+{
+    const long long pieces = (long long)g.chunks * g.Kb32 * 64, n = g.m + 2;
+    const long long blocks = given ? (pieces * n * n + 255) / 256 : (long long)g.chunks * g.Kb32;
+    if (pieces >= (1LL << 31) || blocks > 0x7fffffffLL || g.chunks * 16LL < g.C || g.Kb32 * 32LL < g.K) return hipErrorInvalidValue;
+    u32x4* o = static_cast<u32x4*>(wt);
+#define IOLB_CASE(M_)                                                                                                                       \
+    if (g.m == M_) {                                                                                                                        \
+        if (given) hipLaunchKernelGGL(wino_split_given<M_>, dim3((unsigned)blocks), dim3(256), 0, st, w, o, g.C, g.K, g.chunks, g.Kb32);    \
+        else       hipLaunchKernelGGL(wino_split_weights<M_>, dim3((unsigned)blocks), dim3(256), 0, st, w, o, g.C, g.K, g.chunks, g.Kb32);  \
+        return hipGetLastError();                                                                                                           \
+    }
+    IOLB_CASE(2) IOLB_CASE(4)
+#undef IOLB_CASE
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_wino_split(const float* x, const void* wt, float* y, const WinoSplitGeom& g, hipStream_t st)
+{
+    // what the kernel assumes of its geometry
+    if (!wino_split_fits(g)) return hipErrorInvalidValue;
+    const u32x4* u = static_cast<const u32x4*>(wt);
+    // (loads and stores of M floats need no more than the alignment of one; each float is checked against the buffer's range)
+    const int cols = g.pad != 1 ? COLS_SINGLE : g.W % g.m ? COLS_CUT : COLS_WHOLE;
+#define IOLB_CASE(M_, T_, Z_)                                                            \
+    if (g.m == M_ && g.tb == T_ && g.z == Z_)                                            \
+        return cols == COLS_WHOLE ? launch_one<M_, T_, Z_, COLS_WHOLE>(x, u, y, g, st)   \
+               : cols == COLS_CUT ? launch_one<M_, T_, Z_, COLS_CUT>(x, u, y, g, st)     \
+                                  : launch_one<M_, T_, Z_, COLS_SINGLE>(x, u, y, g, st);
+    IOLB_WINO_SPLIT_SHAPES(IOLB_CASE)
+#undef IOLB_CASE
+    return hipErrorInvalidValue;
+}
+
+}  // namespace iolb

@@ -342,6 +342,118 @@ def test_winograd_with_the_split_product(gpu, m, N, C, H, W, K, split):
             assert torch.equal(B.conv_winograd(xd, wd, m, workspace=ws[:need - 256]), on_tile)
 
 
+# m, N, C, H, W, K, pad: both block shapes of each m, with columns read whole, cut at the image's edge and one by one;
+# sub-domains, kernels and channels that are no multiple of a block's
+FUSED_CASES = [
+    (2, 8, 64, 28, 28, 64, 1), (2, 5, 20, 41, 39, 70, 1), (2, 12, 36, 60, 61, 66, 2), (2, 16, 128, 14, 14, 96, 1),
+    (2, 8, 128, 56, 56, 128, 1), (2, 2, 182, 125, 125, 102, 1), (2, 30, 128, 40, 41, 128, 3),
+    (4, 16, 64, 64, 64, 64, 1), (4, 64, 256, 14, 14, 256, 1), (4, 20, 16, 100, 99, 17, 2), (4, 30, 30, 59, 58, 40, 1),
+    (4, 8, 80, 128, 128, 144, 1), (4, 12, 36, 60, 61, 66, 1), (4, 1, 48, 300, 301, 34, 2),
+]
+
+
+def _winograd_ref(torch, xd, wd, pad):
+    N, C, H, W = xd.shape
+    K, P, Q = wd.shape[0], H + 2 * pad - 2, W + 2 * pad - 2
+    ref = torch.zeros(N, K, P * Q, dtype=torch.float64, device="cuda")
+    xp = torch.nn.functional.pad(xd.double(), (pad,) * 4)
+    for r in range(3):
+        for s in range(3):
+            win = xp[:, :, r:r + P, s:s + Q].reshape(N, C, P * Q).contiguous()
+            ref += torch.bmm(wd[:, :, r, s].double().unsqueeze(0).expand(N, K, C).contiguous(), win)
+    return ref.view(N, K, P, Q)
+
+
+def _runs_fused(B, call):
+    """The result of the call, which has to run one Winograd kernel on the bf16 matrix cores."""
+    B.timing_enable()
+    try:
+        B.timing_read(B.TIME_WINO_FUSED)
+        y = call()
+        launches = B.timing_read(B.TIME_WINO_FUSED)[0]
+    finally:
+        B.timing_enable(False)
+    assert launches == 1
+    return y
+
+
+@pytest.mark.parametrize("m,N,C,H,W,K,pad", FUSED_CASES)
+@pytest.mark.parametrize("at", [4, 5])
+def test_fused_winograd_in_every_shape(gpu, m, N, C, H, W, K, pad, at):
+    torch, B = gpu
+    assert B.iolb_route(B.make_shape(N, C, H, W, K, 3, 3, 1, pad, algo=B.WINO_ALGO[m]))[0] == B.ROUTE_SPLIT
+    x, w = make_inputs(N, C, H, W, K, 3, 3, "u11", "he", seed=m + C + pad)
+    xf, xd = _framed(torch, torch.from_numpy(x).cuda(), at)
+    wd = torch.from_numpy(w).cuda()
+    yf, y = _framed(torch, torch.zeros((N, K, H + 2 * pad - 2, W + 2 * pad - 2), device="cuda"), at)
+    _runs_fused(B, lambda: B.conv_winograd(xd, wd, m, y=y, pad=pad))
+    assert _outside_is_untouched(torch, yf, at, y.numel())
+    ref = _winograd_ref(torch, xd, wd, pad)
+    assert rel_err(y.cpu().numpy(), ref.cpu().numpy()) <= GUARD_WINO[m]
+    if pad == 1:
+        U = B.winograd_transform_kernels(wd, m)[0]
+        ws = torch.full((B.winograd_workspace_bytes(N, C, H, W, K, m),), 255, dtype=torch.uint8, device="cuda")    # NaN bits
+        assert torch.equal(_runs_fused(B, lambda: B.conv_winograd_pre(xd, U, K, m, workspace=ws)), y)
+
+
+@pytest.mark.parametrize("m,N,C,H,W,K,pad", FUSED_CASES)
+def test_fused_winograd_sums_taken_again(gpu, m, N, C, H, W, K, pad):
+    """One image with operands beyond the parts' range: its outputs are taken again in fp32, all others keep their bits;
+    then infinite and NaN kernels, which spoil their own outputs only."""
+    torch, B = gpu
+    x, w = make_inputs(N, C, H, W, K, 3, 3, "u11", "he", seed=m + C + pad + 1)
+    xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+    big, i = xd.clone(), N - 1
+    big[i] = (big[i] + torch.copysign(torch.full_like(big[i], 0.5), big[i])) * 1e32
+    y, z = (_runs_fused(B, lambda: B.conv_winograd(a, wd, m, pad=pad)) for a in (xd, big))
+    assert torch.equal(y[:i], z[:i])
+    assert rel_err(z[i].cpu().numpy(), _winograd_ref(torch, big[i:], wd, pad)[0].cpu().numpy()) <= GUARD_WINO[m]
+    odd = wd.clone()
+    odd[1, C - 1, 2, 2], odd[K - 1, 0, 0, 1] = float("inf"), float("nan")
+    z = B.conv_winograd(xd, odd, m, pad=pad)
+    assert not bool(torch.isfinite(z[:, [1, K - 1]]).any())
+    rest = [k for k in range(K) if k not in (1, K - 1)]
+    assert torch.equal(z[:, rest], y[:, rest])
+
+
+@pytest.mark.parametrize("scales", [(1e-38, 1e30), (1e30, 1e-38), (1e33, 1e-10), (1e-10, 1e33)])
+@pytest.mark.parametrize("m,N,C,H,W,K,pad", [FUSED_CASES[0], FUSED_CASES[5], FUSED_CASES[8], FUSED_CASES[12]])
+def test_fused_winograd_over_the_whole_range(gpu, m, N, C, H, W, K, pad, scales):
+    torch, B = gpu
+    x, w = make_inputs(N, C, H, W, K, 3, 3, "u11", "he", seed=32)
+    xd, wd = torch.from_numpy(x * np.float32(scales[0])).cuda(), torch.from_numpy(w * np.float32(scales[1])).cuda()
+    # the fp32 kernels of the tuned tile, asked for by name
+    ref = B.conv_winograd(xd, wd, m, cfg=B.iolb_tune(B.make_shape(N, C, H, W, K, algo=B.WINO_ALGO[m]))).cpu().numpy()
+    assert rel_err(_runs_fused(B, lambda: B.conv_winograd(xd, wd, m)).cpu().numpy(), ref) <= GUARD_WINO[m]
+
+
+def test_fused_winograd_in_a_graph_and_on_little_workspace(gpu):
+    torch, B = gpu
+    m, N, C, H, W, K = 4, 16, 64, 64, 64, 64
+    shape = B.make_shape(N, C, H, W, K, algo=B.WINO_ALGO[m])
+    need = B.iolb_route(shape)[1]
+    x, w = torch.rand((N, C, H, W), device="cuda"), torch.randn((K, C, 3, 3), device="cuda")
+    ws = torch.full((need,), 255, dtype=torch.uint8, device="cuda")
+    y = _runs_fused(B, lambda: B.conv_winograd(x, w, m, workspace=ws))
+    # (fewer bytes than the split kernels take, but enough for the tile)
+    on_tile = B.conv_winograd(x, w, m, cfg=B.iolb_tune(shape))
+    assert not torch.equal(on_tile, y)
+    with pytest.raises(B.IolbError):
+        B.conv_winograd(x, w, m, workspace=ws[:256])
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        B.conv_winograd(x, w, m, y=y, workspace=ws)
+    for rep in range(3):
+        x.copy_(torch.rand(x.shape, device="cuda"))
+        y.fill_(-1.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, B.conv_winograd(x, w, m)), rep
+        torch.cuda.synchronize()
+
+
 def test_split_layers_through_the_call_that_allocates_nothing(gpu):
     """The same bits as conv_direct up to its limit on the kernels, in three parts too; beyond it the error stays."""
     torch, B = gpu
