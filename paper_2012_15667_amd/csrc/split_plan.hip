@@ -53,12 +53,12 @@ bool split_derive(SplitGeom* g)
     return split_lds_bytes(*g) <= 160 * 1024;
 }
 
-// Modelled clock cycles of a layer.  Per matrix step a wave keeps its SIMD busy for 96 cycles per 16 x 16 block (six
+// Modelled clock cycles of a layer, by rounds of workgroups.  Per matrix step a wave keeps its SIMD busy for 96 cycles per 16 x 16 block (six
 // instructions of 16) plus some 60; an input item costs 220 cycles of loads, split and LDS writes per chunk.  One
 // workgroup per compute unit leaves latencies open (1.45), two hide most of them (1.15).  Up to four rounds count whole.
 // Fitted on ten layers by timing the best block of every workgroup shape (74 variants each): the pick is the fastest or
 // within 4 % on six, within 15 % on the others.
-static double split_cycles(const SplitGeom& g)
+static double split_rounds(const SplitGeom& g)
 {
     const double steps = split_steps(g), chunks = split_chunks(g);
     const double T = 64.0 * g.wm * g.wn;
@@ -70,6 +70,39 @@ static double split_cycles(const SplitGeom& g)
     const double per = grid / 256;
     const double rounds = per <= 1 ? 1 : per <= 4 ? (double)(long long)(per + 0.999) : per + 0.6;
     return rounds * wg * (two && per > 1 ? 1.15 : 1.45);
+}
+
+// Workgroups that share a compute unit: by registers (of the shapes as compiled) and LDS.
+static int split_resident(const SplitGeom& g)
+{
+    const int regs = g.mb == 1 ? (g.nb <= 2 ? 4 : 3) : g.mb == 2 && g.nb == 2 ? 3 : 2;
+    return (int)std::min<long long>(regs, 160 * 1024 / split_lds_bytes(g));
+}
+
+// The same by what a workgroup does alone and what several on a compute unit share.  Alone it takes the sum of what its
+// chunks do one after the other: per matrix step 96 cycles per 16 x 16 block (six instructions of 16) and 170 of waiting,
+// 507 per input item of a thread (loads, split, LDS writes; more where rows are narrow), 1120 at the chunk's end; then its
+// stores.  Several hide each other's waiting until they meet in what they share: the matrix cores, the rate of the weights
+// through the L2 (16 channels per wave and step: 69 cycles, and 159 where they are read at all), 730 per item.  The two
+// times and the traffic of inputs and outputs are joined by norms.
+// Fitted on 187 layers (drawn over 9 to 512 channels, 7 x 7 to 224 x 224, batch 1 to 64, and the networks'), on the best
+// three blocks of every workgroup shape: within 7 % (2-norm).  Its picks take 1.030 times the best block timed, those of
+// split_rounds 1.072; on 266 other layers 130 picks differ, 1.064 times as fast, but seven of them 5 - 14 % slower.  Where
+// it promises 8 % over the pick of split_rounds, 76 of 366 further layers, that is 1.127 times as fast, one 7 % slower, one 3 %:
+// those leave it (5 x 5, 96 -> 256 at 27 x 27, batch 16: 82.7 -> 78.5 us; 180 -> 35 at 124 x 124, stride 2: 158 -> 122).
+constexpr double PROMISE = 1.08;
+static double split_cycles(const SplitGeom& g)
+{
+    const double steps = split_steps(g), chunks = split_chunks(g);
+    const double mfma = 96.0 * g.mb * g.nb, narrow = 1 + 0.8 / g.xh, items = g.ch8 * g.halo / (64.0 * g.wm * g.wn) * narrow;
+    const double alone = 390.0 * g.mb * g.nb + 1520 * std::ceil(items / narrow) * narrow + chunks * (steps * (mfma + 170) + 507 * items + 1120);
+    const double shared = 1010 + 357.0 * g.mb * g.nb + chunks * (steps * std::pow(std::pow(1.13 * mfma, 4) + std::pow(g.mb * (17.2 * g.wm + 159), 4), 0.25) + 730 * items);
+    auto group = [&](double n) { return n > 0 ? std::pow(std::pow(alone, 3.13) + std::pow(n * shared, 3.13), 1 / 3.13) : 0; };
+    const int most = split_resident(g);
+    const double n = (double)g.nbk * g.nbx * g.nby * g.nbn / 256, full = std::floor(n / most);
+    const double cycles = n <= 4 * most ? full * group(most) + group(std::ceil(n - full * most)) : (n / most + 0.5) * group(most);
+    const double bytes = 4.0 * g.N * ((double)g.C * g.H * g.W + (double)g.K * g.P * g.Q);
+    return std::pow(std::pow(cycles, 4) + std::pow(bytes / 990, 4), 0.25);
 }
 
 bool split_plan(SplitGeom* g, double* cycles)
@@ -91,8 +124,8 @@ bool split_plan(SplitGeom* g, double* cycles)
         return v;
     };
     bool found = false;
-    SplitGeom best = *g;
-    double best_cycles = 0;
+    SplitGeom best = *g, other = *g;                        // of least split_rounds, of least split_cycles
+    double best_rounds = 0, best_cycles = 0;
     for (const Shape& sh : shapes) {
         const int slots = 16 * sh.nb * sh.wn;
         for (int ch8 : {4, 2, 1}) {
@@ -106,14 +139,20 @@ bool split_plan(SplitGeom* g, double* cycles)
                         if (b * tx * ty * 2 < slots) continue;           // a smaller shape does it
                         t.tx = tx; t.ty = ty; t.b = b;
                         if (!split_derive(&t)) continue;
-                        const double c = split_cycles(t);
-                        if (!found || c < best_cycles) { found = true; best = t; best_cycles = c; }
+                        const double r = split_rounds(t), c = split_cycles(t);
+                        if (!found || r < best_rounds) { best = t; best_rounds = r; }
+                        if (!found || c < best_cycles) { other = t; best_cycles = c; }
+                        found = true;
                     }
                 }
         }
     }
-    if (found) { *g = best; *cycles = best_cycles; }
-    return found;
+    if (!found) return false;
+    const double c = split_cycles(best);
+    const bool leave = c > PROMISE * best_cycles;
+    *g = leave ? other : best;
+    *cycles = leave ? best_cycles : c;
+    return true;
 }
 
 bool split_point_plan(SplitPointGeom* g, double* cycles)
