@@ -65,8 +65,8 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
         reinterpret_cast<void*>((unsigned long long)xhi << 32 | xlo), 0, (int)range, 0x00020000);
 
     // the input items of this thread
-    // Column l16 of a wave's block nb is pixel 16 nb + l16, or, for vector stores, NB l16 + nb: pixels are kept in LDS in the
-    // order in which the blocks read them.
+    // Column l16 of a wave's block nb is pixel 16 nb + l16, or NB l16 + nb (VPX): pixels are kept in LDS in the order in which
+    // the blocks read them.  Pairs of pixels are then written with half the bank conflicts (48 bytes from lane to lane, not 96).
     auto slot_of = [&](int px) { return VPX ? px / (16 * NB) * (16 * NB) + px % NB * 16 + px % (16 * NB) / NB : px; };
     auto pixel_of = [&](int nb, int l) { return wn_i * NB * 16 + (VPX ? NB * l + nb : 16 * nb + l); };
     unsigned src[IB], dst[IB];
@@ -228,10 +228,12 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
         constexpr bool MARKED = decltype(marked_c)::value;  // the second time: marked outputs only
         const int l16 = opaque(lane) & 15, grp = opaque(lane) >> 4;
         if constexpr (VPX && !MARKED) {
-            typedef float vec __attribute__((ext_vector_type(NB)));
-            const int px = pixel_of(0, l16);                // ... and the next NB - 1, in the same row of y
+            typedef float vec __attribute__((ext_vector_type(NB), aligned(4)));
+            const int px = pixel_of(0, l16);                // ... and the next NB - 1
             if (px >= left_px) return;
             const int n = n0 + (p0 + px) / g.HW, r = (p0 + px) % g.HW;
+            // at once where they lie in the row of y: beyond the image's pixels is its padding then
+            const bool whole = r + NB <= g.HWy;
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) {
                 const int k0 = (kb16 + mb) * 16 + 4 * grp;
@@ -244,7 +246,14 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
                         if (!(__builtin_fabsf(acc[mb][nb][i]) <= 3.402823466e38f)) again |= 1ull << ((nb * MB + mb) * 4 + i);
                         q[nb] = acc[mb][nb][i] * SPLIT_UNSCALE;
                     }
-                    if (k0 + i < g.K) *reinterpret_cast<vec*>(yp + (size_t)i * g.HWy) = q;
+                    if (k0 + i >= g.K) continue;
+                    if (whole) {
+                        *reinterpret_cast<vec*>(yp + (size_t)i * g.HWy) = q;
+                    } else {
+#pragma unroll
+                        for (int nb = 0; nb < NB; ++nb)
+                            if (px + nb < left_px) yp[(size_t)i * g.HWy + nb] = q[nb];
+                    }
                 }
             }
             return;
@@ -344,19 +353,18 @@ hipError_t launch_split_point(const float* x, const void* wt, float* y, const Sp
     if (g.in == SPLIT_IN_CHANNELS && (!g.hwc || g.C % 4)) return hipErrorInvalidValue;
     if (g.in == SPLIT_IN_PIXELS && (g.hwc || g.stride != 1 || (g.images > 1 && g.HW % split_point_pixels(g.in)))) return hipErrorInvalidValue;
     const u32x4* w = static_cast<const u32x4*>(wt);
-    // Whole groups of nb pixels that lie in one row of y, on 4 nb bytes: stores of nb floats.  (Where a group is the last
-    // one of a row that is padded, the padding is written too.)  16 planes of 512 x 12544 x 512: 580 -> 545 us, 36 of 256 x
-    // 12544 x 256 386 -> 350, 16 of 512 x 1024 x 512 47.9 -> 44.1.
-    const bool vec = !g.hwc && g.HWy % g.nb == 0 && (reinterpret_cast<uintptr_t>(y) & (4 * g.nb - 1)) == 0 &&
-                     (g.images == 1 ? (g.HW + g.nb - 1) / g.nb * g.nb <= g.HWy : g.HW % g.nb == 0);
-#define IOLB_POINT_CASE(M_, N_, A_, B_)                                                                          \
-    if (g.mb == M_ && g.nb == N_ && g.wm == A_ && g.wn == B_) {                                                  \
+    // NB neighbouring pixels per lane (VPX) unless they can cross into another image.  16 planes of 512 x 12544 x 512: 580 ->
+    // 545 us, 16 of 512 x 1024 x 512 47.9 -> 44.1, 64 images of 17 x 17, 768 -> 192: 46.1 -> 41.9; with the crossing groups
+    // taken apart 64 images of 49 pixels, 512 -> 512, 19.7 -> 22.6, of 90 pixels 27.2 -> 29.4.
+    const bool vec = !g.hwc && (g.images == 1 || g.HW % g.nb == 0);
+#define IOLB_POINT_CASE(M_, N_, A_, B_)                                                                              \
+    if (g.mb == M_ && g.nb == N_ && g.wm == A_ && g.wn == B_) {                                                      \
         if (g.in == SPLIT_IN_CHANNELS) return launch_one<M_, N_, A_, B_, SPLIT_IN_CHANNELS, false>(x, w, y, g, st);  \
-        if (g.in == SPLIT_IN_PIXELS)                                                                             \
-            return vec ? launch_one<M_, N_, A_, B_, SPLIT_IN_PIXELS, true>(x, w, y, g, st)                       \
-                       : launch_one<M_, N_, A_, B_, SPLIT_IN_PIXELS, false>(x, w, y, g, st);                     \
-        return vec ? launch_one<M_, N_, A_, B_, SPLIT_IN_SINGLE, true>(x, w, y, g, st)                           \
-                   : launch_one<M_, N_, A_, B_, SPLIT_IN_SINGLE, false>(x, w, y, g, st);                         \
+        if (g.in == SPLIT_IN_PIXELS)                                                                                 \
+            return vec ? launch_one<M_, N_, A_, B_, SPLIT_IN_PIXELS, true>(x, w, y, g, st)                           \
+                       : launch_one<M_, N_, A_, B_, SPLIT_IN_PIXELS, false>(x, w, y, g, st);                         \
+        return vec ? launch_one<M_, N_, A_, B_, SPLIT_IN_SINGLE, true>(x, w, y, g, st)                               \
+                   : launch_one<M_, N_, A_, B_, SPLIT_IN_SINGLE, false>(x, w, y, g, st);                             \
     }
     IOLB_SPLIT_POINT_SHAPES(IOLB_POINT_CASE)
 #undef IOLB_POINT_CASE
