@@ -20,7 +20,13 @@
 // LDS without the padding of split_derive 1068 against 1024; input loads whose descriptor or offset the compiler kept in
 // vector registers (a loop over the lanes per load) 1073 against 1041.  Sums apart per step (APART) for all layers: error
 // 1.8e-7 in place of 7.6e-7, 1129 us: kept for the few-channel layers only.
-// Small layers are bound by the latency of a step's weight loads (about 0.5 us): AHEAD below.
+// Loads come back in the order they were issued, so a step that waits for weights waits for the inputs issued before them
+// too, which come from further away: weights two or three steps ahead (AHEAD) give those as many steps to arrive.  One step
+// ahead on blocks of more than eight 16 x 16 per wave: 64 -> 64 at 56 x 56, batch 32 48.5 us (two: 47.5, whole calls), 256 ->
+// 256 at 56 x 56, batch 64 943 (908).
+// Layers of one round of workgroups start and end together: of the 44 us a workgroup of 64 -> 64, batch 32, lives, 5.4
+// pass before its first matrix step and 4.7 at its stores.  So the first loads go out before anything is waited for, and
+// extents are divided by with a multiplication (64 -> 64 49.7 -> 48.5 us; 128 -> 256, stride 2 58.4 -> 55.6).
 #include "kernels.h"
 #include "split_mfma.h"
 
@@ -48,7 +54,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t image_buffer(const float* x, c
 
 template <int MB, int NB, int WM, int WN, bool VEC, bool APART>
 __global__ void __launch_bounds__(64 * WM * WN, 2)
-split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitGeom g)
+split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitGeom g, SplitDivisors dv)
 {
     extern __shared__ u32x4 lds16[];
     char* const lds = reinterpret_cast<char*>(lds16);
@@ -68,15 +74,30 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
         const int nblk = gridDim.x, q = nblk >> 3, r = nblk & 7, xcd = blockIdx.x & 7;
         bid = xcd * q + (xcd < r ? xcd : r) + ((int)blockIdx.x >> 3);
     }
-    // the divisions run on the vector unit: back to scalars, so that everything derived from them stays scalar
-    // ... and channel blocks of the same pixels are neighbours, unless the kernels do not fit an L2 (k_outer): then an XCD
-    // stays with one channel block
+    // channel blocks of the same pixels are neighbours, unless the kernels do not fit an L2 (k_outer): then an XCD stays with
+    // one channel block
     const int pixel_blocks = g.nbx * g.nby * g.nbn;
-    const int kb = __builtin_amdgcn_readfirstlane(g.k_outer ? bid / pixel_blocks : bid % g.nbk);
-    bid = g.k_outer ? bid % pixel_blocks : bid / g.nbk;
-    const int x0 = __builtin_amdgcn_readfirstlane(bid % g.nbx * g.tx); bid /= g.nbx;
-    const int y0 = __builtin_amdgcn_readfirstlane(bid % g.nby * g.ty);
-    const int n0 = __builtin_amdgcn_readfirstlane(bid / g.nby * g.b);
+    int kb, x0, y0, n0;
+    if (dv.small) {
+        const int a = g.k_outer ? dv.pixel_blocks.of(bid) : dv.nbk.of(bid);
+        kb = g.k_outer ? a : bid - a * g.nbk;
+        bid = g.k_outer ? bid - a * pixel_blocks : a;
+        const int b = dv.nbx.of(bid), c = dv.nby.of(b);
+        x0 = (bid - b * g.nbx) * g.tx;
+        y0 = (b - c * g.nby) * g.ty;
+        n0 = c * g.b;
+    } else {
+        kb = g.k_outer ? bid / pixel_blocks : bid % g.nbk;
+        bid = g.k_outer ? bid % pixel_blocks : bid / g.nbk;
+        x0 = bid % g.nbx * g.tx; bid /= g.nbx;
+        y0 = bid % g.nby * g.ty;
+        n0 = bid / g.nby * g.b;
+    }
+    // (divisions run on the vector unit: back to scalars, so that everything derived from them stays scalar)
+    kb = __builtin_amdgcn_readfirstlane(kb);
+    x0 = __builtin_amdgcn_readfirstlane(x0);
+    y0 = __builtin_amdgcn_readfirstlane(y0);
+    n0 = __builtin_amdgcn_readfirstlane(n0);
 
     const int RS = g.R * g.S;
     const int steps = (RS * CH8 + 3) >> 2;                  // matrix steps of a chunk: four units each
@@ -84,51 +105,6 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
     const int im_bytes = g.yh * g.rowb, group_bytes = g.b * im_bytes, buf_bytes = CH8 * group_bytes;
     int* const koff = reinterpret_cast<int*>(lds + g.nbuf * buf_bytes);          // [4 * steps]
     uint2* const table = reinterpret_cast<uint2*>(koff + ((4 * steps + 1) & ~1));      // [items]
-
-    // LDS byte offset of unit (tap, channel group) relative to a pixel's window corner
-    for (int u = tid; u < 4 * steps; u += T) {
-        const int tap = u / CH8, c8 = u % CH8;
-        int off = 0;
-        if (tap < RS) {
-            const int r = tap / g.S, s = tap % g.S;
-            off = c8 * group_bytes + r * g.rowb + 48 * ((s % g.esx) * g.colw + s / g.esx);
-        }
-        koff[u] = off;
-    }
-    // where the elements of the input tile come from and where they go
-    const int gy0 = y0 * g.stride - g.pad, gx0 = x0 * g.stride - g.pad_w;
-    for (int i = tid; i < items; i += T) {
-        const int c8 = i / g.halo, hp = i % g.halo;
-        const int per = g.yh * g.rowp;
-        const int im = hp / per, rem = hp % per, iy = rem / g.rowp, ix = rem % g.rowp;
-        const int gy = gy0 + staged_offset(iy, g.esy, g.stride), gx = gx0 + staged_offset(ix, g.esx, g.stride);
-        uint2 e;
-        e.x = OUTSIDE;
-        if (n0 + im < g.N && ix < g.xh && gy >= 0 && gy < g.H && gx >= 0 && gx < g.W)
-            e.x = g.hwc ? 4u * (unsigned)(((im * g.H + gy) * g.W + gx) * C + c8 * 8)
-                      : 4u * (unsigned)(((im * C + c8 * 8) * g.H + gy) * g.W + gx);
-        e.y = (unsigned)(c8 * group_bytes + im * im_bytes + iy * g.rowb + 48 * ((ix % g.esx) * g.colw + ix / g.esx));
-        // c8 in the low bits of the LDS offset (a multiple of 16)
-        e.y |= (unsigned)c8;
-        table[i] = e;
-    }
-
-    // pixels of this lane
-    const int txy = g.tx * g.ty, npix = g.b * txy;
-    int pbase[NB];
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        const int slot = (wn_i * NB + nb) * 16 + l16;
-        const int pix = slot < npix ? slot : npix - 1;
-        const int im = pix / txy, rem = pix % txy, py = rem / g.tx, px = rem % g.tx;
-        pbase[nb] = im * im_bytes + py * g.esy * g.rowb + 48 * px;
-    }
-
-    f32x4 acc[MB][NB];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     const int nchunks = __builtin_amdgcn_readfirstlane((C + 8 * CH8 - 1) / (8 * CH8));
     // weights of matrix step t: [t][16-channel block][part][lane]
@@ -138,58 +114,98 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
 
     const __amdgpu_buffer_rsrc_t rs = image_buffer(x, g, n0);
 
-    // staging of chunk ch, batch b (IB items per thread): loads now, split and LDS writes one slot later
+    // where item `it` of the input tile comes from and where it goes
+    const int gy0 = y0 * g.stride - g.pad, gx0 = x0 * g.stride - g.pad_w;
+    auto place = [&](int it) {
+        const int per = g.yh * g.rowp;
+        const int c8 = dv.halo.of(it), hp = it - c8 * g.halo, im = dv.per.of(hp), rem = hp - im * per;
+        const int iy = dv.rowp.of(rem), ix = rem - iy * g.rowp, ix_col = dv.esx.of(ix);
+        const int gy = gy0 + staged_offset(iy, g.esy, g.stride), gx = gx0 + staged_offset(ix, g.esx, g.stride);
+        uint2 e;
+        e.x = OUTSIDE;
+        if (n0 + im < g.N && ix < g.xh && gy >= 0 && gy < g.H && gx >= 0 && gx < g.W)
+            e.x = g.hwc ? 4u * (unsigned)(((im * g.H + gy) * g.W + gx) * C + c8 * 8)
+                      : 4u * (unsigned)(((im * C + c8 * 8) * g.H + gy) * g.W + gx);
+        e.y = (unsigned)(c8 * group_bytes + im * im_bytes + iy * g.rowb + 48 * ((ix - ix_col * g.esx) * g.colw + ix_col));
+        // c8 in the low bits of the LDS offset (a multiple of 16)
+        e.y |= (unsigned)c8;
+        return e;
+    };
+
+    // staging of chunk ch: an item's eight channels to registers, later its parts to LDS
+    auto load_item = [&](float (&v)[8], uint2 e, int ch) {
+        const int c0 = ch < nchunks ? ch * 8 * CH8 : 0, have = ch < nchunks ? C - c0 : 0;
+        const int left = have - (int)(e.y & 15) * 8;          // channels of this group that exist
+        if constexpr (VEC) {
+            // channels innermost, C a multiple of 4 and x 16-byte aligned: two 16-byte loads
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(rs, left > 4 * h ? (int)e.x + 16 * h : (int)OUTSIDE, c0 * 4, 0);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[4 * h + j] = __uint_as_float(q[j]);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                // the scalar offset stays inside the buffer, whatever the lanes do
+                const int cj = c0 + j < C ? c0 + j : C - 1;
+                v[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, left > j ? (int)e.x : (int)OUTSIDE, cj * cstep, 0));
+            }
+        }
+    };
+    auto write_item = [&](const float (&v)[8], unsigned dst, char* buf) {
+        u32x4 h, m, l;
+        split_eight(v, h, m, l);
+        if (dst != ~0u) {
+            u32x4* d = reinterpret_cast<u32x4*>(buf + (dst & ~15u));
+            d[0] = h; d[1] = m; d[2] = l;
+        }
+    };
+    // a batch: IB items per thread, loads now, split and LDS writes one slot later.  A thread's own items: it alone reads
+    // what it put in the table.
     float xv[IB][8];
     unsigned xdst[IB];
     const int batches = __builtin_amdgcn_readfirstlane((items + T * IB - 1) / (T * IB));
     auto load_batch = [&](int ch, int b) {
-        const int c0 = ch < nchunks ? ch * 8 * CH8 : 0, have = ch < nchunks ? C - c0 : 0;
 #pragma unroll
         for (int i = 0; i < IB; ++i) {
             const int it = (b * IB + i) * T + tid;
             uint2 e = {OUTSIDE, ~0u};
             if (it < items) e = table[it];
             xdst[i] = e.y;
-            const int left = have - (int)(e.y & 15) * 8;      // channels of this group that exist
-            if constexpr (VEC) {
-                // channels innermost, C a multiple of 4 and x 16-byte aligned: two 16-byte loads
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(rs, left > 4 * h ? (int)e.x + 16 * h : (int)OUTSIDE, c0 * 4, 0);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) xv[i][4 * h + j] = __uint_as_float(q[j]);
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    // the scalar offset stays inside the buffer, whatever the lanes do
-                    const int cj = c0 + j < C ? c0 + j : C - 1;
-                    xv[i][j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, left > j ? (int)e.x : (int)OUTSIDE, cj * cstep, 0));
-                }
-            }
+            load_item(xv[i], e, ch);
         }
     };
     auto write_batch = [&](char* buf) {
 #pragma unroll
-        for (int i = 0; i < IB; ++i) {
-            u32x4 h, m, l;
-            split_eight(xv[i], h, m, l);
-            if (xdst[i] != ~0u) {
-                u32x4* d = reinterpret_cast<u32x4*>(buf + (xdst[i] & ~15u));
-                d[0] = h; d[1] = m; d[2] = l;
-            }
-        }
+        for (int i = 0; i < IB; ++i) write_item(xv[i], xdst[i], buf);
     };
     auto barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
 
-    barrier();                                              // tables are in place
-    for (int b = 0; b < batches; ++b) {
-        load_batch(0, b);
-        write_batch(lds);
-    }
+    // Everything the first steps need is on its way before the first of it is waited for: the first FIRST batches of chunk 0
+    // as their places in the table are computed, the weights, chunk 1.  The rest of the tables is computed meanwhile.
+    constexpr int FIRST = MB * NB >= 8 ? 2 : 1;
+    float fv[FIRST][IB][8];
+    unsigned fdst[FIRST][IB];
+    auto place_batch = [&](float (&v)[IB][8], unsigned (&dst)[IB], int b) {
+#pragma unroll
+        for (int i = 0; i < IB; ++i) {
+            const int it = (b * IB + i) * T + tid;
+            uint2 e = {OUTSIDE, ~0u};
+            if (it < items) {
+                e = place(it);
+                table[it] = e;
+            }
+            dst[i] = e.y;
+            load_item(v[i], e, 0);
+        }
+    };
+#pragma unroll
+    for (int f = 0; f < FIRST; ++f) place_batch(fv[f], fdst[f], f);
+    __builtin_amdgcn_sched_barrier(0);
     // Weights of the next AHEAD steps are on their way while a step multiplies: a step of a small block is shorter than
-    // the latency of its loads.  The order in which a step issues its loads: first the weights, then the inputs.
-    constexpr int AHEAD = MB == 1 ? 3 : MB * NB <= 8 ? 2 : 1;
+    // the latency of its loads.  A step issues first the weights, then the inputs.
+    constexpr int AHEAD = MB == 1 ? 3 : 2;
     u32x4 a[AHEAD + 1][MB * 3];
     const int total = nchunks * steps;
     auto load_weights = [&](u32x4 (&f)[MB * 3], int t) {
@@ -200,9 +216,47 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
 #pragma unroll
     for (int i = 0; i < AHEAD; ++i) load_weights(a[i], i);
     __builtin_amdgcn_sched_barrier(0);
-    if (nchunks > 1) load_batch(1, 0);
+    load_batch(1, 0);                                       // (of a chunk that does not exist: zeros, no access)
     __builtin_amdgcn_sched_barrier(0);
+
+    // LDS byte offset of unit (tap, channel group) relative to a pixel's window corner
+    for (int u = tid; u < 4 * steps; u += T) {
+        const int tap = dv.ch8.of(u), c8 = u - tap * CH8;
+        int off = 0;
+        if (tap < RS) {
+            const int r = dv.S.of(tap), s = tap - r * g.S, s_col = dv.esx.of(s);
+            off = c8 * group_bytes + r * g.rowb + 48 * ((s - s_col * g.esx) * g.colw + s_col);
+        }
+        koff[u] = off;
+    }
+    // pixels of this lane
+    const int txy = g.tx * g.ty, npix = g.b * txy;
+    int pbase[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        const int slot = (wn_i * NB + nb) * 16 + l16;
+        const int pix = slot < npix ? slot : npix - 1;
+        const int im = dv.txy.of(pix), rem = pix - im * txy, py = dv.tx.of(rem), px = rem - py * g.tx;
+        pbase[nb] = im * im_bytes + py * g.esy * g.rowb + 48 * px;
+    }
+
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int f = 0; f < FIRST; ++f)
+#pragma unroll
+        for (int i = 0; i < IB; ++i) write_item(fv[f][i], fdst[f][i], lds);
+    for (int b = FIRST; b < batches; ++b) {
+        place_batch(fv[0], fdst[0], b);
+#pragma unroll
+        for (int i = 0; i < IB; ++i) write_item(fv[0][i], fdst[0][i], lds);
+    }
     barrier();
+
+    f32x4 acc[MB][NB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     u32x4 bf[2][3];
     auto fetch = [&](u32x4 (&f)[3], const char* from) {
@@ -260,11 +314,6 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
 #pragma unroll
             for (int p = 0; p < 3; ++p) bf[0][p] = bf[1][p];
         }
-        if constexpr (AHEAD == 1) {
-            // one copy of the step: two would not fit the registers of the large blocks
-#pragma unroll
-            for (int j = 0; j < MB * 3; ++j) a[0][j] = a[1][j];
-        }
         ko = kn;
         ++k;
         const bool done = ++t == total;
@@ -276,17 +325,13 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
         }
         return done;
     };
-    if constexpr (AHEAD == 1) {
-        while (!step(a[0], a[1])) {}
-    } else {
-        // AHEAD + 1 copies, so that every step names its registers
-        bool done = false;
-        while (!done)
-            static_range<0, AHEAD + 1>([&](auto i_c) {
-                constexpr int i = decltype(i_c)::value;
-                if (!done) done = step(a[i], a[(i + AHEAD) % (AHEAD + 1)]);
-            });
-    }
+    // AHEAD + 1 copies, so that every step names its registers
+    bool done = false;
+    while (!done)
+        static_range<0, AHEAD + 1>([&](auto i_c) {
+            constexpr int i = decltype(i_c)::value;
+            if (!done) done = step(a[i], a[(i + AHEAD) % (AHEAD + 1)]);
+        });
 
     // each partial sum is complete: write the block once.  Register i of a 16 x 16 block holds channel 4 grp + i of
     // pixel l16.  Sums that are not finite are marked.
@@ -299,7 +344,7 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
             const int slot = (wn_i * NB + nb) * 16 + l16;
-            const int im = slot / txy, rem = slot % txy, py = y0 + rem / g.tx, px = x0 + rem % g.tx;
+            const int im = dv.txy.of(slot), rem = slot - im * txy, row = dv.tx.of(rem), py = y0 + row, px = x0 + rem - row * g.tx;
             if (slot >= npix || n0 + im >= g.N || py >= g.P || px >= g.Q) continue;
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) {
@@ -416,7 +461,7 @@ split_weights_kernel(const float* __restrict__ w, u32x4* __restrict__ wt, int K,
 }
 
 template <int MB, int NB, int WM, int WN, bool VEC, bool APART>
-hipError_t launch_one(const float* x, const u32x4* wt, float* y, const SplitGeom& g, hipStream_t st)
+hipError_t launch_one(const float* x, const u32x4* wt, float* y, const SplitGeom& g, const SplitDivisors& dv, hipStream_t st)
 {
     auto kern = split_conv_kernel<MB, NB, WM, WN, VEC, APART>;
     const size_t shm = split_lds_bytes(g);
@@ -424,7 +469,7 @@ hipError_t launch_one(const float* x, const u32x4* wt, float* y, const SplitGeom
         const hipError_t e = allow_large_lds((const void*)kern);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kern, dim3(g.nbk * g.nbx * g.nby * g.nbn), dim3(64 * WM * WN), shm, st, x, wt, y, g);
+    hipLaunchKernelGGL(kern, dim3(g.nbk * g.nbx * g.nby * g.nbn), dim3(64 * WM * WN), shm, st, x, wt, y, g, dv);
     return hipGetLastError();
 }
 
@@ -444,10 +489,10 @@ hipError_t launch_split_weights(const float* w, void* wt, int K, int C, int R, i
 // sum, which is then rounded once per step and not six times.  Such layers ran on plain FMAs or short fp32 chains
 // before, which round less than six bf16 products per step would; they are not bound by the matrix cores.
 template <bool VEC>
-static hipError_t launch_shape(const float* x, const u32x4* wt, float* y, const SplitGeom& g, hipStream_t st)
+static hipError_t launch_shape(const float* x, const u32x4* wt, float* y, const SplitGeom& g, const SplitDivisors& dv, hipStream_t st)
 {
 #define IOLB_SPLIT_CASE(M_, N_, A_, B_) \
-    if (g.mb == M_ && g.nb == N_ && g.wm == A_ && g.wn == B_) return launch_one<M_, N_, A_, B_, VEC, APART>(x, wt, y, g, st);
+    if (g.mb == M_ && g.nb == N_ && g.wm == A_ && g.wn == B_) return launch_one<M_, N_, A_, B_, VEC, APART>(x, wt, y, g, dv, st);
     if (g.ch8 == 1) {
         constexpr bool APART = true;
         IOLB_SPLIT_FEW_SHAPES(IOLB_SPLIT_CASE)
@@ -467,7 +512,14 @@ hipError_t launch_split_conv(const float* x, const void* wt, float* y, const Spl
         4LL * g.b * g.C * g.H * g.W >= (1LL << 31) || g.cstep != (g.hwc ? 4 : 4 * g.H * g.W) || (g.vec_in && (!g.hwc || g.C % 4)))
         return hipErrorInvalidValue;
     const u32x4* w = static_cast<const u32x4*>(wt);
-    return g.vec_in ? launch_shape<true>(x, w, y, g, st) : launch_shape<false>(x, w, y, g, st);
+    // Divided are items, units and pixels of a block (what is in LDS per item and unit bounds them by 2^15, their divisors too),
+    // and workgroup ids.
+    const unsigned pixel_blocks = (unsigned)(g.nbx * g.nby * g.nbn);
+    const bool small = (long long)pixel_blocks * g.nbk <= 32768;
+    if ((long long)g.ch8 * g.halo > 32768 || split_steps(g) * 4LL > 32768 || g.S > 32768) return hipErrorInvalidValue;
+    const SplitDivisors dv = {Divisor(g.ch8), Divisor(g.halo), Divisor(g.yh * g.rowp), Divisor(g.rowp), Divisor(g.S), Divisor(g.esx), Divisor(g.tx * g.ty),
+                              Divisor(g.tx), Divisor(g.nbk), Divisor(pixel_blocks), Divisor(g.nbx), Divisor(g.nby), small};
+    return g.vec_in ? launch_shape<true>(x, w, y, g, dv, st) : launch_shape<false>(x, w, y, g, dv, st);
 }
 
 }  // namespace iolb

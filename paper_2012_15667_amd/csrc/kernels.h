@@ -78,6 +78,19 @@ struct SplitGeom {
     int hwc, vec_in, vec_out;  // channels innermost; with 16-byte loads / stores of four channels
     int cstep;                 // bytes from an input channel to the next
 };
+// Division by a number known on the host: exact for n * d < 2^31.  (The compiler's division takes some 40 instructions.)
+struct Divisor {
+    unsigned m;                // 2^31 / d, rounded down, + 1
+    Divisor() = default;
+    explicit Divisor(unsigned d) : m((1u << 31) / d + 1) {}
+    __device__ __forceinline__ int of(int n) const { return (int)__umulhi((unsigned)n << 1, m); }
+};
+// ... by the extents that the kernel divides by
+struct SplitDivisors {
+    Divisor ch8, halo, per, rowp, S, esx, txy, tx;          // per: yh * rowp
+    Divisor nbk, pixel_blocks, nbx, nby;                    // of workgroup ids, where small says that they are exact
+    int small;
+};
 constexpr int SPLIT_BATCH = 2;          // (pixel, 8 channels) items of the input tile that a thread stages at once
 // The workgroup shapes that exist: blocks per wave (channels, pixels), wave grid (channels, pixels).  Of two with the same
 // workgroup block and blocks per wave, which the planner's model cannot tell apart, there is one.
