@@ -29,6 +29,7 @@
 // extents are divided by with a multiplication (64 -> 64 49.7 -> 48.5 us; 128 -> 256, stride 2 58.4 -> 55.6).
 #include "kernels.h"
 #include "split_mfma.h"
+#include "split_weights.h"
 
 #include <type_traits>
 
@@ -429,35 +430,52 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
     write_y(std::true_type{});
 }
 
-// w[K][C][R][S] -> the operands of the matrix steps, [chunk][step][16-channel block][part][lane][8 bf16].  One
-// thread per 16-byte piece.
+// w[K][C][R][S] -> the operands of the matrix steps, [chunk][step][16-channel block][part][lane][8 bf16].  A workgroup per 16
+// kernels, `octets` groups of eight channels and up to 16 taps (all of them, or slices of 16), whose pieces its threads take
+// one each: rows of w are read as they lie, 16 floats and more at a time, and go through LDS.  Bound by latency: a load, an
+// LDS pass and a store one after the other (gathered in single floats, 256 -> 256 kernels of 3 x 3 took 7.4 us, now 5.7; 7 x
+// 7 and 11 x 11 on three channels 62 -> 58 and 49.2 -> 46.8 whole calls).
+constexpr int SLICE = 16, ROW = 8 * SLICE;                 // taps of a slice; floats of a kernel in LDS
 __global__ void __launch_bounds__(256)
 split_weights_kernel(const float* __restrict__ w, u32x4* __restrict__ wt, int K, int C, int R, int S, int ch8, int steps, int Kb16,
-                     long long pieces, int transposed)
+                     int octets, int all_octets, int slices, int transposed)
 {
-    const long long id = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (id >= pieces) return;
-    const int lane = (int)(id & 63);
-    const int kb = (int)((id >> 6) % Kb16);
-    const int t = (int)((id >> 6) / Kb16);
-    const int RS = R * S;
-    const int k = kb * 16 + (lane & 15), u = (t % steps) * 4 + (lane >> 4);
-    const int tap = u / ch8, c0 = (t / steps * ch8 + u % ch8) * 8;
-    const int tw = transposed ? (tap % S) * R + tap / S : tap;
+    constexpr int PITCH = ROW + 1, ROWS = 16, MINE = ROWS / 4;
+    __shared__ float rows[ROWS * PITCH];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kb = blockIdx.x % Kb16, rest = blockIdx.x / Kb16, first = rest / slices * octets, t0 = rest % slices * SLICE;
+    const int RS = R * S, taps = 4 * steps / ch8, k0 = kb * 16;
+    const int ts = slices > 1 ? SLICE : RS;                 // taps of a channel in LDS
+    const int channels = C - first * 8 < octets * 8 ? C - first * 8 : octets * 8;
+    const long long from0 = (long long)k0 * C * RS + (long long)first * 8 * RS + t0;
+    float v[2][MINE];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const int e = lane + 64 * c, row = slices > 1 ? e / SLICE * RS + e % SLICE : e;
+        // (kernels, channels and taps that only fill a block up are not there to be read)
+        const bool here = slices > 1 ? e / SLICE < channels && t0 + e % SLICE < RS : e < channels * RS;
+#pragma unroll
+        for (int j = 0; j < MINE; ++j) {
+            const int k = wave * MINE + j;
+            const bool exists = here && k0 + k < K;
+            v[c][j] = w[exists ? from0 + (long long)k * C * RS + row : 0];
+            v[c][j] = exists ? v[c][j] : 0.f;
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int j = 0; j < MINE; ++j) rows[(wave * MINE + j) * PITCH + lane + 64 * c] = v[c][j];
+    __syncthreads();
+    const int k = tid & 15, mine = slices > 1 ? SLICE : taps, t = t0 + (tid >> 4) % mine, o = (tid >> 4) / mine, octet = first + o;
+    if (o >= octets || octet >= all_octets || t >= taps) return;
+    const float* from = rows + k * PITCH + o * 8 * ts + t - t0;
     unsigned short p[3][8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        float v = 0.f;
-        if (k < K && tap < RS && c0 + j < C) v = w[((size_t)k * C + c0 + j) * RS + tw];
-        split_kept(v, p[0][j], p[1][j], p[2][j]);
-    }
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        u32x4 o;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) o[j] = (unsigned)p[q][2 * j] | ((unsigned)p[q][2 * j + 1] << 16);
-        wt[((size_t)t * Kb16 + kb) * 192 + q * 64 + lane] = o;
-    }
+    for (int j = 0; j < 8; ++j) split_kept(t < RS ? from[j * ts] : 0.f, p[0][j], p[1][j], p[2][j]);
+    const int tap = transposed && t < RS ? t % R * S + t / R : t;
+    const int unit = tap * ch8 + octet % ch8;
+    store_parts(wt + ((size_t)(octet / ch8 * steps + (unit >> 2)) * Kb16 + kb) * 192 + (unit & 3) * 16 + k, p);
 }
 
 template <int MB, int NB, int WM, int WN, bool VEC, bool APART>
@@ -477,11 +495,13 @@ hipError_t launch_one(const float* x, const u32x4* wt, float* y, const SplitGeom
 
 hipError_t launch_split_weights(const float* w, void* wt, int K, int C, int R, int S, int ch8, int Kb16, bool transposed, hipStream_t st)
 {
-    const int steps = (R * S * ch8 + 3) / 4;
-    const long long pieces = (long long)((C + 8 * ch8 - 1) / (8 * ch8)) * steps * Kb16 * 64;
-    if ((pieces + 255) / 256 > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(split_weights_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st, w, (u32x4*)wt, K, C, R, S, ch8, steps,
-                       Kb16, pieces, transposed ? 1 : 0);
+    if (ch8 != 1 && ch8 != 2 && ch8 != 4) return hipErrorInvalidValue;
+    const int steps = (R * S * ch8 + 3) / 4, octets = (C + 8 * ch8 - 1) / (8 * ch8) * ch8, taps = 4 * steps / ch8;
+    const int per = taps < SLICE ? SLICE / taps : 1, slices = (taps + SLICE - 1) / SLICE;
+    const long long blocks = (octets + per - 1LL) / per * slices * Kb16;
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(split_weights_kernel, dim3((unsigned)blocks), dim3(256), 0, st, w, (u32x4*)wt, K, C, R, S, ch8, steps, Kb16, per, octets,
+                       slices, transposed ? 1 : 0);
     return hipGetLastError();
 }
 

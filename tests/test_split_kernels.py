@@ -74,6 +74,37 @@ def test_split_direct_layouts_within_the_bound(gpu, case):
     assert (np.abs(yt - conv_ref_cwh(xt, w, stride, pad)) <= lim.transpose(0, 1, 3, 2)).all()
 
 
+@pytest.mark.parametrize("taps", [(1, 2), (1, 15), (4, 4), (1, 17), (5, 5), (4, 8), (3, 11), (7, 9), (1, 65)])
+@pytest.mark.parametrize("C,K", [(3, 16), (9, 17), (17, 5), (40, 130)])
+def test_kernels_reach_their_steps_for_every_window(gpu, taps, C, K):
+    """Kernels go to the matrix steps in slices of 16 taps, and the first steps of the input tile are loaded ahead:
+    windows around the slices' edges, channels and kernels beyond a block's, whole numbers (every sum is exact)."""
+    torch, B = gpu
+    R, S = taps
+    case = (3, C, R + 8, S + 12, K, R, S, 1, 0)
+    if C > 8 or R * S >= 25:
+        assert B.iolb_route(B.make_shape(*case), B.LAYOUT_CHW)[0] == B.ROUTE_SPLIT
+    rng = np.random.default_rng(R * 100 + S + C)
+    x = rng.integers(-4, 5, (3, C, R + 8, S + 12)).astype(np.float32)
+    w = rng.integers(-4, 5, (K, C, R, S)).astype(np.float32)
+    y = B.conv_direct(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), 1, 0).cpu().numpy()
+    assert np.array_equal(y, conv_ref(x, w, 1, 0))
+    xt = np.ascontiguousarray(x.transpose(0, 1, 3, 2))
+    yt = B.conv_direct_layout(torch.from_numpy(xt).cuda(), torch.from_numpy(w).cuda(), 1, 0, B.LAYOUT_CWH).cpu().numpy()
+    assert np.array_equal(yt, y.transpose(0, 1, 3, 2))
+
+
+def test_more_blocks_than_ids_divided_by_multiplication(gpu):
+    """Beyond 32768 workgroups (34816 here, of 112 pixels by 128 kernels) their ids are divided as integers; parts of the batch
+    stay below.  Whole numbers: every sum is exact, whatever the block."""
+    torch, B = gpu
+    x = torch.randint(-4, 5, (4352, 9, 14, 14), device="cuda", dtype=torch.float32)
+    w = torch.randint(-4, 5, (512, 9, 3, 3), device="cuda", dtype=torch.float32)
+    y = B.conv_direct(x, w, 1, 1)
+    for i in range(0, 4352, 1088):
+        assert torch.equal(y[i:i + 1088], B.conv_direct(x[i:i + 1088].contiguous(), w, 1, 1))
+
+
 @pytest.mark.parametrize("layer", [(4, 24, 18, 18, 40, 3, 1), (4, 3, 24, 24, 40, 7, 3), (12, 768, 17, 17, 192, 1, 0)])
 def test_single_products_have_fp32_precision(gpu, layer):
     """One channel and one tap are not zero, so that every output is one product x w of full 24-bit operands.  Of its nine
