@@ -219,6 +219,11 @@ struct WinoSplitGeom {
     int nbt, nbk;              // blocks along the sub-domains, the kernels
     int chunks, Kb32;          // stages of 16 channels; 32-kernel blocks, whole workgroup blocks
 };
+// ... and what it divides workgroup ids and sub-domains by, where small says that this is exact (per_image: th * tw)
+struct WinoSplitDivisors {
+    Divisor nbt, per_image, tw;
+    int small;
+};
 #define IOLB_WINO_SPLIT_SHAPES(X) X(4, 32, 64) X(4, 32, 32) X(2, 64, 64) X(2, 32, 32)
 inline long long wino_split_weight_bytes(const WinoSplitGeom& g) { return (g.m + 2LL) * (g.m + 2) * g.chunks * g.Kb32 * 3072; }
 // Whether the kernel's 32-bit offsets reach: the images of a block, the kernels.

@@ -71,7 +71,7 @@ enum { COLS_SINGLE, COLS_CUT, COLS_WHOLE };
 
 template <int M, int TB, int Z, int COLS>
 __global__ void __launch_bounds__(512, M == 2 && TB == 32 && Z == 32 ? 4 : 2)
-wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restrict__ y, WinoSplitGeom g)
+wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restrict__ y, WinoSplitGeom g, WinoSplitDivisors dv)
 {
     constexpr int n = M + 2, PL = n * n, ZB = Z / 32, TBB = TB / 32;
     constexpr int FP = PL / 8, LP = PL % 8;                  // whole planes per wave, planes left over: 4 ZB units for 8 waves
@@ -91,16 +91,24 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
         bid = xcd * q + (xcd < r ? xcd : r) + ((int)blockIdx.x >> 3);
     }
     // an XCD stays with one block of kernels, whose parts its L2 holds
-    const int kb = __builtin_amdgcn_readfirstlane(bid / g.nbt);
-    const int t0 = __builtin_amdgcn_readfirstlane(bid % g.nbt * TB);
+    const int kb = __builtin_amdgcn_readfirstlane(dv.small ? dv.nbt.of(bid) : bid / g.nbt);
+    const int t0 = (bid - kb * g.nbt) * TB;
     const int per_image = g.th * g.tw, plane_in = g.H * g.W;
-    const int img0 = __builtin_amdgcn_readfirstlane(t0 / per_image);
+    auto image_of = [&](int t) { return dv.small ? dv.per_image.of(t) : t / per_image; };
+    // a sub-domain's image, row and column
+    auto place = [&](int t, int& img, int& ti, int& tj) {
+        img = image_of(t);
+        const int in = t - img * per_image;
+        ti = dv.small ? dv.tw.of(in) : in / g.tw;
+        tj = in - ti * g.tw;
+    };
+    const int img0 = __builtin_amdgcn_readfirstlane(image_of(t0));
 
     // inputs: byte offsets from the first image's window origin at (-pad, -pad)
     const int shift = g.pad * (g.W + 1);
     const size_t image = (size_t)g.C * plane_in;
     const int last_t = t0 + TB < g.tiles ? t0 + TB : g.tiles;
-    const int span = __builtin_amdgcn_readfirstlane((last_t - 1) / per_image + 1 - img0);
+    const int span = __builtin_amdgcn_readfirstlane(image_of(last_t - 1) + 1 - img0);
     const unsigned long long xb = reinterpret_cast<unsigned long long>(x) + 4 * (img0 * image) - 4ull * shift;
     const unsigned xlo = __builtin_amdgcn_readfirstlane((unsigned)xb), xhi = __builtin_amdgcn_readfirstlane((unsigned)(xb >> 32));
     const unsigned xrange = __builtin_amdgcn_readfirstlane((unsigned)(4 * (image * span + shift)));
@@ -116,7 +124,8 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
     unsigned xoff, eoff;
     {
         const int t = t0 + tloc, tt = t < g.tiles ? t : t0;
-        const int tj = tt % g.tw, ti = tt / g.tw % g.th, img = tt / per_image;
+        int img, ti, tj;
+        place(tt, img, ti, tj);
         const int h0 = ti * M - g.pad, w0 = tj * M - g.pad;
         auto lanes = [](bool v) { return __builtin_amdgcn_ballot_w64(v); };
 #pragma unroll
@@ -130,9 +139,9 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
         xoff = 4u * (unsigned)(shift + (int)((img - img0) * (int)image) + (lane >> 4) * plane_in + h0 * g.W + w0);
         eoff = xoff + ((lane & 15) == 0 ? 0 : 4 * (M + 1));
     }
-    float wx[WIN][n][n];                                    // loads in flight: column 0 the edge, then the M own columns
+    typedef float Windows[WIN][n][n];                       // loads in flight: column 0 the edge, then the M own columns
     const int nst = g.chunks;
-    auto load_x = [&](int s) {
+    auto load_x = [&](Windows& wx, int s) {
         static_range<0, WIN>([&](auto ic) {
             constexpr int i = decltype(ic)::value;
             const int c0 = 16 * s + c0w + 4 * i;
@@ -160,7 +169,7 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
     };
     // V in LDS: [plane][four channels][sub-domain][4]
     const int vw = cl / 4 * (TB * 16) + tloc * 16 + (cl & 3) * 4;
-    auto transform = [&](char* vb) {
+    auto transform = [&](Windows& wx, char* vb) {
         static_range<0, WIN>([&](auto ic) {
             constexpr int i = decltype(ic)::value;
             if constexpr (COLS == COLS_CUT)
@@ -326,7 +335,8 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
                 if (has_extra && xzb == z) put(xplane, accx);
             barrier();
             const int tl = opaque(tid) % TB, t = t0 + tl;
-            const int tj = t % g.tw, ti = t / g.tw % g.th, img = t / per_image;
+            int img, ti, tj;
+            place(t, img, ti, tj);
             const int h0 = ti * M, w0 = tj * M;
 #pragma unroll
             for (int i = 0; i < PAIRS; ++i) {
@@ -380,30 +390,35 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
     // before, so that one's vector work runs beside the other's matrix work: the second is one transform ahead and
     // meets the barrier between the two.
     const bool ahead = wave >= 4;
-    load_x(0);
-    static_range<0, D>([&](auto uc) {
-        constexpr int u = decltype(uc)::value;
-        if (!LP || u < UNITS - 1 || has_extra) load_u(a[u], unit_at(u, 0));
-    });
-    __builtin_amdgcn_sched_barrier(0);
-    clear();
-    transform(lds);
-    load_x(1);
+    Windows wx;
+    {
+        // before there are sums the registers hold two stages' windows: both are on their way before the first is waited for
+        Windows first;
+        load_x(first, 0);
+        static_range<0, D>([&](auto uc) {
+            constexpr int u = decltype(uc)::value;
+            if (!LP || u < UNITS - 1 || has_extra) load_u(a[u], unit_at(u, 0));
+        });
+        load_x(wx, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        transform(first, lds);
+    }
     __builtin_amdgcn_sched_barrier(0);
     barrier();
     if (ahead) {
-        if (1 < nst) transform(lds + VBUF);
-        load_x(2);
+        if (1 < nst) transform(wx, lds + VBUF);
+        load_x(wx, 2);
         __builtin_amdgcn_sched_barrier(0);
     }
+    clear();
 #pragma unroll 1
     for (int s = 0; s < nst; ++s) {
         multiply(s, lds + (s & 1) * VBUF);
         if (ahead) barrier();
         const int ts = ahead ? s + 2 : s + 1;
         if (ts < nst) {
-            transform(lds + (ts & 1) * VBUF);
-            load_x(ts + 1);
+            transform(wx, lds + (ts & 1) * VBUF);
+            load_x(wx, ts + 1);
         }
         __builtin_amdgcn_sched_barrier(0);
         if (!ahead) barrier();
@@ -421,8 +436,8 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
     clear();
 #pragma unroll 1
     for (int s = 0; s < nst; ++s) {
-        load_x(s);
-        transform(lds);
+        load_x(wx, s);
+        transform(wx, lds);
         barrier();
         auto unit = [&](unsigned at, const char* vplane, f32x16 (&c)[TBB]) {
             u32x4 f[3];
@@ -506,7 +521,10 @@ hipError_t launch_one(const float* x, const u32x4* wt, float* y, const WinoSplit
         const hipError_t e = allow_large_lds((const void*)kern);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kern, dim3(g.nbt * g.nbk), dim3(512), shm, st, x, wt, y, g);
+    const int per_image = g.th * g.tw;
+    const bool small = (g.tiles + 64LL) * per_image < (1LL << 31) && (long long)g.nbt * g.nbk * g.nbt < (1LL << 31);
+    const WinoSplitDivisors dv = {Divisor(g.nbt), Divisor(per_image), Divisor(g.tw), small};
+    hipLaunchKernelGGL(kern, dim3(g.nbt * g.nbk), dim3(512), shm, st, x, wt, y, g, dv);
     return hipGetLastError();
 }
 
