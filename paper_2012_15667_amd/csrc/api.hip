@@ -213,6 +213,7 @@ int check_config(const iolb_shape& s, const iolb_tile_config& cfg)
 struct SplitChoice {
     enum { NONE, CONV, POINT } kind = NONE;
     iolb::SplitGeom conv{};
+    bool own = false;                      // conv: its workgroups prepare their own kernels
     iolb::SplitPointGeom point{};
     size_t weight_bytes = 0;
 };
@@ -255,6 +256,7 @@ SplitChoice split_choice(const iolb_shape& s, int P, int Q, int pad_w, int layou
         if (iolb::split_conv_faster(s) && iolb::split_plan(&g, &cycles)) {
             ch.kind = SplitChoice::CONV;
             ch.conv = g;
+            ch.own = iolb::split_own(g);
             ch.weight_bytes = (size_t)iolb::split_weight_bytes(g);
         }
     }
@@ -277,25 +279,28 @@ int run_split(const float* x, const float* w, float* y, const iolb_shape& s, con
     DeviceState* dev = nullptr;
     int rc = device_state(&dev);
     if (rc != IOLB_OK) return rc;
-    void* wt = wt_buf;
-    if (!wt) {
-        rc = ensure_workspace(dev, align256(ch.weight_bytes), &wt);
-        if (rc != IOLB_OK) return rc;
-    }
+    const bool point = ch.kind == SplitChoice::POINT, own = !point && ch.own, transposed = layout == IOLB_LAYOUT_CWH;
+    const void* kernels = w;
     hipStream_t st = t_stream;
-    const bool point = ch.kind == SplitChoice::POINT;
-    IOLB_HIP(iolb::launch_split_weights(w, wt, s.K, s.C, s.R, s.S, point ? 4 : ch.conv.ch8, point ? ch.point.Kb16 : ch.conv.Kb16,
-                                        layout == IOLB_LAYOUT_CWH, st));
+    if (!own) {
+        void* wt = wt_buf;
+        if (!wt) {
+            rc = ensure_workspace(dev, align256(ch.weight_bytes), &wt);
+            if (rc != IOLB_OK) return rc;
+        }
+        IOLB_HIP(iolb::launch_split_weights(w, wt, s.K, s.C, s.R, s.S, point ? 4 : ch.conv.ch8, point ? ch.point.Kb16 : ch.conv.Kb16, transposed, st));
+        kernels = wt;
+    }
     const bool aligned = ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(y)) & 15) == 0;
     MainKernelTimer timer(st, IOLB_TIME_DIRECT);
     if (point) {
         iolb::SplitPointGeom g = ch.point;
         if (!aligned) { g.vec_out = 0; if (g.in == iolb::SPLIT_IN_CHANNELS) g.in = iolb::SPLIT_IN_SINGLE; }
-        IOLB_HIP(iolb::launch_split_point(x, wt, y, g, st));
+        IOLB_HIP(iolb::launch_split_point(x, kernels, y, g, st));
     } else {
         iolb::SplitGeom g = ch.conv;
         if (!aligned) g.vec_in = g.vec_out = 0;
-        IOLB_HIP(iolb::launch_split_conv(x, wt, y, g, st));
+        IOLB_HIP(iolb::launch_split_conv(x, kernels, y, g, own, transposed, st));
     }
     timer.stop(st);
     return IOLB_OK;

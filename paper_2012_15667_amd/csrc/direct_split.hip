@@ -27,6 +27,9 @@
 // Layers of one round of workgroups start and end together: of the 44 us a workgroup of 64 -> 64, batch 32, lives, 5.4
 // pass before its first matrix step and 4.7 at its stores.  So the first loads go out before anything is waited for, and
 // extents are divided by with a multiplication (64 -> 64 49.7 -> 48.5 us; 128 -> 256, stride 2 58.4 -> 55.6).
+// Small layers (split_own) take no weights kernel before them: each workgroup reads the rows of its channels as they lie, cuts
+// them into parts in LDS and multiplies from there (OWN; 16 -> 16 at 14 x 14, one image, 10.6 -> 8.2 us a call, 6.6 of them
+// the GPU's).
 #include "kernels.h"
 #include "split_mfma.h"
 #include "split_weights.h"
@@ -53,9 +56,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t image_buffer(const float* x, c
                                              (int)__builtin_amdgcn_readfirstlane(img * (unsigned)images), 0x00020000);
 }
 
-template <int MB, int NB, int WM, int WN, bool VEC, bool APART>
+template <int MB, int NB, int WM, int WN, bool VEC, bool APART, bool OWN>
 __global__ void __launch_bounds__(64 * WM * WN, 2)
-split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitGeom g, SplitDivisors dv)
+split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitGeom g, SplitDivisors dv, SplitOwn own)
 {
     extern __shared__ u32x4 lds16[];
     char* const lds = reinterpret_cast<char*>(lds16);
@@ -204,18 +207,27 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
 #pragma unroll
     for (int f = 0; f < FIRST; ++f) place_batch(fv[f], fdst[f], f);
     __builtin_amdgcn_sched_barrier(0);
+    u32x4* const parts = reinterpret_cast<u32x4*>(lds + split_tables_bytes(g));     // a workgroup's own kernels (OWN)
     // Weights of the next AHEAD steps are on their way while a step multiplies: a step of a small block is shorter than
     // the latency of its loads.  A step issues first the weights, then the inputs.
-    constexpr int AHEAD = MB == 1 ? 3 : 2;
+    constexpr int AHEAD = OWN ? 1 : MB == 1 ? 3 : 2;
     u32x4 a[AHEAD + 1][MB * 3];
     const int total = nchunks * steps;
     auto load_weights = [&](u32x4 (&f)[MB * 3], int t) {
+        if constexpr (OWN) {
+            const u32x4* from = parts + ((t < total ? t : 0) * (MB * WM) + wm_i * MB) * 192 + lane;
+#pragma unroll
+            for (int j = 0; j < MB * 3; ++j) f[j] = from[j * 64];
+            return;
+        }
         if (t > 0 && t < total) wp += wstep;                // past the last step: read again, not used
 #pragma unroll
         for (int j = 0; j < MB * 3; ++j) f[j] = wp[j * 64];
     };
+    if constexpr (!OWN) {
 #pragma unroll
-    for (int i = 0; i < AHEAD; ++i) load_weights(a[i], i);
+        for (int i = 0; i < AHEAD; ++i) load_weights(a[i], i);
+    }
     __builtin_amdgcn_sched_barrier(0);
     load_batch(1, 0);                                       // (of a chunk that does not exist: zeros, no access)
     __builtin_amdgcn_sched_barrier(0);
@@ -230,6 +242,41 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
         }
         koff[u] = off;
     }
+    // its own kernels (OWN): from w, whose rows for these channels are one stretch, to LDS, one float between rows; from there
+    // the parts, in the order of the steps
+    const int row_w = C * RS;
+    if constexpr (OWN) {
+        float* const rows = reinterpret_cast<float*>(parts + nchunks * steps * (MB * WM * 192));
+        constexpr int Z = 16 * MB * WM, PER = 8;
+        const float* w = reinterpret_cast<const float*>(wt);
+        const int k0 = kb * Z, have = (g.K - k0 < Z ? g.K - k0 : Z) * row_w;
+        for (int e0 = tid; e0 < Z * row_w + tid; e0 += T * PER) {
+            float v[PER];
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const int e = e0 + i * T;
+                v[i] = w[e < have ? (size_t)k0 * row_w + e : 0];
+                v[i] = e < have ? v[i] : 0.f;
+            }
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const int e = e0 + i * T;
+                if (e < Z * row_w) rows[e + own.row.of(e)] = v[i];
+            }
+        }
+        barrier();
+        for (int p = tid; p < nchunks * steps * (MB * WM * 64); p += T) {
+            const int block = (p >> 6) % (MB * WM), t = (p >> 6) / (MB * WM), ch = own.steps.of(t);
+            const int unit = (t - ch * steps) * 4 + (p >> 4 & 3), tap = dv.ch8.of(unit), c0 = (ch * CH8 + unit - tap * CH8) * 8;
+            const int r = dv.S.of(tap), tw = own.transposed ? (tap - r * g.S) * g.R + r : tap;
+            const float* from = rows + (block * 16 + (p & 15)) * (row_w + 1) + c0 * RS + tw;
+            unsigned short q[3][8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) split_kept(tap < RS && c0 + j < C ? from[j * RS] : 0.f, q[0][j], q[1][j], q[2][j]);
+            store_parts(parts + (p >> 6) * 192 + (p & 63), q);
+        }
+    }
+
     // pixels of this lane
     const int txy = g.tx * g.ty, npix = g.b * txy;
     int pbase[NB];
@@ -252,6 +299,7 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
         for (int i = 0; i < IB; ++i) write_item(fv[0][i], fdst[0][i], lds);
     }
     barrier();
+    if constexpr (OWN) load_weights(a[0], 0);
 
     f32x4 acc[MB][NB];
 #pragma unroll
@@ -306,10 +354,10 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
             const bool more = k + 1 < batches;
             load_batch(more ? ch + 1 : ch + 2, more ? k + 1 : 0);
             static_range<HALF, NB>(block);
-            __builtin_amdgcn_s_waitcnt(0x0F70 | ((LATER + LOADS) & 15) | ((LATER + LOADS) >> 4) << 14);
+            if constexpr (!OWN) __builtin_amdgcn_s_waitcnt(0x0F70 | ((LATER + LOADS) & 15) | ((LATER + LOADS) >> 4) << 14);
         } else {
             static_range<HALF, NB>(block);
-            __builtin_amdgcn_s_waitcnt(0x0F70 | (LATER & 15) | (LATER >> 4) << 14);
+            if constexpr (!OWN) __builtin_amdgcn_s_waitcnt(0x0F70 | (LATER & 15) | (LATER >> 4) << 14);
         }
         if constexpr (NB & 1) {
 #pragma unroll
@@ -396,9 +444,10 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    const u32x4* wq = wt + (size_t)kb16 * 192 + lane2;
+    const u32x4* wq = OWN ? parts + wm_i * (MB * 192) + lane2 : wt + (size_t)kb16 * 192 + lane2;
+    const size_t next_w = OWN ? MB * WM * 192 : wstep;
 #pragma unroll 1
-    for (int s = 0; s < total; ++s, wq += wstep) {
+    for (int s = 0; s < total; ++s, wq += next_w) {
         const int unit = s % steps * 4 + unit0, tap = unit / CH8, c0 = (s / steps * CH8 + unit % CH8) * 8;
         const int r = tap / g.S, col = tap % g.S;
         float wv[MB][8], v[2][8];
@@ -478,16 +527,16 @@ split_weights_kernel(const float* __restrict__ w, u32x4* __restrict__ wt, int K,
     store_parts(wt + ((size_t)(octet / ch8 * steps + (unit >> 2)) * Kb16 + kb) * 192 + (unit & 3) * 16 + k, p);
 }
 
-template <int MB, int NB, int WM, int WN, bool VEC, bool APART>
-hipError_t launch_one(const float* x, const u32x4* wt, float* y, const SplitGeom& g, const SplitDivisors& dv, hipStream_t st)
+template <int MB, int NB, int WM, int WN, bool VEC, bool APART, bool OWN>
+hipError_t launch_one(const float* x, const u32x4* wt, float* y, const SplitGeom& g, const SplitDivisors& dv, const SplitOwn& own, hipStream_t st)
 {
-    auto kern = split_conv_kernel<MB, NB, WM, WN, VEC, APART>;
-    const size_t shm = split_lds_bytes(g);
+    auto kern = split_conv_kernel<MB, NB, WM, WN, VEC, APART, OWN>;
+    const size_t shm = split_lds_bytes(g, OWN);
     if (shm > 64 * 1024) {
         const hipError_t e = allow_large_lds((const void*)kern);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kern, dim3(g.nbk * g.nbx * g.nby * g.nbn), dim3(64 * WM * WN), shm, st, x, wt, y, g, dv);
+    hipLaunchKernelGGL(kern, dim3(g.nbk * g.nbx * g.nby * g.nbn), dim3(64 * WM * WN), shm, st, x, wt, y, g, dv, own);
     return hipGetLastError();
 }
 
@@ -509,25 +558,30 @@ hipError_t launch_split_weights(const float* w, void* wt, int K, int C, int R, i
 // sum, which is then rounded once per step and not six times.  Such layers ran on plain FMAs or short fp32 chains
 // before, which round less than six bf16 products per step would; they are not bound by the matrix cores.
 template <bool VEC>
-static hipError_t launch_shape(const float* x, const u32x4* wt, float* y, const SplitGeom& g, const SplitDivisors& dv, hipStream_t st)
+static hipError_t launch_shape(const float* x, const u32x4* wt, float* y, const SplitGeom& g, const SplitDivisors& dv, const SplitOwn* own, hipStream_t st)
 {
 #define IOLB_SPLIT_CASE(M_, N_, A_, B_) \
-    if (g.mb == M_ && g.nb == N_ && g.wm == A_ && g.wn == B_) return launch_one<M_, N_, A_, B_, VEC, APART>(x, wt, y, g, dv, st);
+    if (!own && g.mb == M_ && g.nb == N_ && g.wm == A_ && g.wn == B_) return launch_one<M_, N_, A_, B_, VEC, APART, false>(x, wt, y, g, dv, SplitOwn(), st);
+#define IOLB_SPLIT_OWN_CASE(M_, N_, A_, B_) \
+    if (own && g.mb == M_ && g.nb == N_ && g.wm == A_ && g.wn == B_) return launch_one<M_, N_, A_, B_, VEC, APART, true>(x, wt, y, g, dv, *own, st);
     if (g.ch8 == 1) {
         constexpr bool APART = true;
         IOLB_SPLIT_FEW_SHAPES(IOLB_SPLIT_CASE)
+        IOLB_SPLIT_OWN_FEW_SHAPES(IOLB_SPLIT_OWN_CASE)
     } else {
         constexpr bool APART = false;
         IOLB_SPLIT_SHAPES(IOLB_SPLIT_CASE)
+        IOLB_SPLIT_OWN_SHAPES(IOLB_SPLIT_OWN_CASE)
     }
+#undef IOLB_SPLIT_OWN_CASE
 #undef IOLB_SPLIT_CASE
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_split_conv(const float* x, const void* wt, float* y, const SplitGeom& g, hipStream_t st)
+hipError_t launch_split_conv(const float* x, const void* wt, float* y, const SplitGeom& g, bool own, bool transposed, hipStream_t st)
 {
     // what the kernel assumes of its geometry
-    if (g.b * g.tx * g.ty > 16 * g.nb * g.wn || split_lds_bytes(g) > 160 * 1024 || g.Kb16 != g.nbk * g.mb * g.wm ||
+    if (g.b * g.tx * g.ty > 16 * g.nb * g.wn || split_lds_bytes(g, own) > 160 * 1024 || g.Kb16 != g.nbk * g.mb * g.wm ||
         (split_chunks(g) > 1 && split_batches(g) > split_steps(g)) || g.nbuf < (split_chunks(g) > 1 ? 2 : 1) || g.nbuf > 2 || g.ch8 < 1 || g.ch8 > 8 ||
         4LL * g.b * g.C * g.H * g.W >= (1LL << 31) || g.cstep != (g.hwc ? 4 : 4 * g.H * g.W) || (g.vec_in && (!g.hwc || g.C % 4)))
         return hipErrorInvalidValue;
@@ -539,7 +593,8 @@ hipError_t launch_split_conv(const float* x, const void* wt, float* y, const Spl
     if ((long long)g.ch8 * g.halo > 32768 || split_steps(g) * 4LL > 32768 || g.S > 32768) return hipErrorInvalidValue;
     const SplitDivisors dv = {Divisor(g.ch8), Divisor(g.halo), Divisor(g.yh * g.rowp), Divisor(g.rowp), Divisor(g.S), Divisor(g.esx), Divisor(g.tx * g.ty),
                               Divisor(g.tx), Divisor(g.nbk), Divisor(pixel_blocks), Divisor(g.nbx), Divisor(g.nby), small};
-    return g.vec_in ? launch_shape<true>(x, w, y, g, dv, st) : launch_shape<false>(x, w, y, g, dv, st);
+    const SplitOwn o = {Divisor(split_steps(g)), Divisor(g.C * g.R * g.S), transposed ? 1 : 0};
+    return g.vec_in ? launch_shape<true>(x, w, y, g, dv, own ? &o : nullptr, st) : launch_shape<false>(x, w, y, g, dv, own ? &o : nullptr, st);
 }
 
 }  // namespace iolb

@@ -91,6 +91,11 @@ struct SplitDivisors {
     Divisor nbk, pixel_blocks, nbx, nby;                    // of workgroup ids, where small says that they are exact
     int small;
 };
+// ... and where workgroups prepare their own kernels (row: C * R * S; transposed: w[K][C][S][R])
+struct SplitOwn {
+    Divisor steps, row;
+    int transposed;
+};
 constexpr int SPLIT_BATCH = 2;          // (pixel, 8 channels) items of the input tile that a thread stages at once
 // The workgroup shapes that exist: blocks per wave (channels, pixels), wave grid (channels, pixels).  Of two with the same
 // workgroup block and blocks per wave, which the planner's model cannot tell apart, there is one.
@@ -103,6 +108,9 @@ constexpr int SPLIT_BATCH = 2;          // (pixel, 8 channels) items of the inpu
 // ... and those for layers of at most eight channels (ch8 = 1)
 #define IOLB_SPLIT_FEW_SHAPES(X) \
     X(1, 2, 4, 1) X(1, 4, 4, 1) X(1, 2, 2, 2) X(1, 4, 2, 2) X(2, 4, 2, 2) X(1, 2, 1, 4) X(1, 4, 1, 4) X(2, 4, 1, 4)
+// ... and those with workgroups that prepare their own kernels
+#define IOLB_SPLIT_OWN_SHAPES(X) X(1, 1, 1, 4) X(1, 2, 1, 4) X(1, 4, 1, 4) X(1, 2, 2, 2) X(1, 2, 4, 1)
+#define IOLB_SPLIT_OWN_FEW_SHAPES(X) X(1, 2, 1, 4) X(1, 4, 1, 4) X(1, 2, 2, 2) X(1, 2, 4, 1)
 inline int split_steps(const SplitGeom& g) { return (g.R * g.S * g.ch8 + 3) / 4; }
 inline int split_chunks(const SplitGeom& g) { return (g.C + 8 * g.ch8 - 1) / (8 * g.ch8); }
 inline int split_batches(const SplitGeom& g)
@@ -110,10 +118,21 @@ inline int split_batches(const SplitGeom& g)
     const int per = 64 * g.wm * g.wn * SPLIT_BATCH;
     return (g.ch8 * g.halo + per - 1) / per;
 }
-// buffers of the input tile, offsets of the matrix steps' units, table of the input tile's elements
-inline long long split_lds_bytes(const SplitGeom& g)
+// buffers of the input tile, offsets of the matrix steps' units, table of the input tile's elements, whole 16 bytes
+__host__ __device__ inline int split_tables_bytes(const SplitGeom& g)
 {
-    return (long long)g.nbuf * g.ch8 * g.b * g.yh * g.rowb + 4 * ((4 * split_steps(g) + 1) & ~1) + 8LL * g.ch8 * g.halo;
+    const int steps = (g.R * g.S * g.ch8 + 3) / 4;
+    return (g.nbuf * g.ch8 * g.b * g.yh * g.rowb + 4 * ((4 * steps + 1) & ~1) + 8 * g.ch8 * g.halo + 15) & ~15;
+}
+// ... and the parts and rows of a workgroup's own kernels
+inline long long split_own_bytes(const SplitGeom& g)
+{
+    return (long long)split_chunks(g) * split_steps(g) * g.mb * g.wm * 3072 + 64LL * g.mb * g.wm * (g.C * g.R * g.S + 1LL);
+}
+inline long long split_lds_bytes(const SplitGeom& g, bool own = false)
+{
+    const long long tables = ((long long)g.nbuf * g.ch8 * g.b * g.yh * g.rowb + 4 * ((4 * split_steps(g) + 1) & ~1) + 8LL * g.ch8 * g.halo + 15) & ~15LL;
+    return tables + (own ? split_own_bytes(g) : 0);
 }
 // The input-tile buffer of a chunk: never one that split_lds_bytes does not count.
 __host__ __device__ constexpr int split_buffer(int chunk, int nbuf) { return chunk & (nbuf - 1); }
@@ -122,7 +141,8 @@ static_assert(split_buffer(0, 1) == 0 && split_buffer(1, 1) == 0 && split_buffer
 inline long long split_weight_bytes(const SplitGeom& g) { return (long long)split_chunks(g) * split_steps(g) * g.Kb16 * 3072; }
 // Kernels in three parts in the order of the matrix steps, written from w[K][C][R][S] (transposed: w[K][C][S][R]).
 hipError_t launch_split_weights(const float* w, void* wt, int K, int C, int R, int S, int ch8, int Kb16, bool transposed, hipStream_t st);
-hipError_t launch_split_conv(const float* x, const void* wt, float* y, const SplitGeom& g, hipStream_t st);
+// (own: the kernels themselves, transposed as above, in place of wt)
+hipError_t launch_split_conv(const float* x, const void* wt, float* y, const SplitGeom& g, bool own, bool transposed, hipStream_t st);
 
 // 1 x 1 layers and the Winograd product on the same matrix cores (split_point.hip): per group of images that share
 // kernels (all images of a layer; one transformed plane), y[K][HW] = w[K][C] x[C][HW] over the group's pixels.

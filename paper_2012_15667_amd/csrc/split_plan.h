@@ -12,6 +12,8 @@ bool split_derive(SplitGeom* g);
 // The block and workgroup shape of least modelled time for the layer in g; *cycles gets that time (clock cycles of
 // the chip at full occupation).  False when no shape runs the layer.
 bool split_plan(SplitGeom* g, double* cycles);
+// Whether the workgroups of a planned layer prepare their own kernels (no launch before the convolution).
+bool split_own(const SplitGeom& g);
 // The same for 1 x 1 layers: groups, images, C, K, Ky, HW, HWy, HWin, Win, Q, stride, hwc and in describe the layer.
 bool split_point_plan(SplitPointGeom* g, double* cycles);
 // The block of the fused Winograd kernel for the layer in g (N, C, H, W, K, m, pad, P, Q, th, tw, tiles); *ns gets the

@@ -155,6 +155,23 @@ bool split_plan(SplitGeom* g, double* cycles)
     return true;
 }
 
+// Layers of few workgroups and small kernels: a launch before the convolution takes longer (some 2.3 us of the host's time
+// and 3 us of the GPU's) than every workgroup cutting the same kernels once more, about 1 us for 2304 floats.  The line lies
+// where both are even: 16 -> 16 at 14 x 14, one image, 10.6 -> 8.2 us a call, 3 x 32 -> 32 at 15 x 15 (4608 floats) 10.4 ->
+// 8.5; beyond it 20 x 32 -> 64 at 17 x 17, 7 x 1 (14336 floats) 10.6 -> 13.9, 3 x 20 -> 24 at 206 x 206, stride 2 (5760, 500
+// workgroups) 14.3 -> 25.6.
+constexpr long long OWN_FLOATS = 4800, OWN_ALL_FLOATS = 256 * OWN_FLOATS;
+bool split_own(const SplitGeom& g)
+{
+    bool shape = false;
+#define IOLB_SPLIT_OWN_ENTRY(M_, N_, A_, B_) shape = shape || (g.mb == M_ && g.nb == N_ && g.wm == A_ && g.wn == B_);
+    if (g.ch8 == 1) { IOLB_SPLIT_OWN_FEW_SHAPES(IOLB_SPLIT_OWN_ENTRY) } else { IOLB_SPLIT_OWN_SHAPES(IOLB_SPLIT_OWN_ENTRY) }
+#undef IOLB_SPLIT_OWN_ENTRY
+    const long long floats = 16LL * g.mb * g.wm * g.C * g.R * g.S;
+    const long long grid = (long long)g.nbk * g.nbx * g.nby * g.nbn;
+    return shape && floats <= OWN_FLOATS && grid * floats <= OWN_ALL_FLOATS && split_lds_bytes(g, true) <= 160 * 1024;
+}
+
 bool split_point_plan(SplitPointGeom* g, double* cycles)
 {
     struct Shape { int mb, nb, wm, wn; };

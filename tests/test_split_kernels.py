@@ -94,6 +94,42 @@ def test_kernels_reach_their_steps_for_every_window(gpu, taps, C, K):
     assert np.array_equal(yt, y.transpose(0, 1, 3, 2))
 
 
+@pytest.mark.parametrize("case", [
+    # N, C, H, W, K, R, S, stride, pad: 4608 and 4320 kernel floats a workgroup, the next ones beyond 4800; many workgroups
+    (3, 32, 15, 15, 32, 3, 3, 1, 1), (2, 30, 14, 15, 17, 3, 3, 2, 1), (1, 34, 15, 15, 32, 3, 3, 1, 1), (3, 9, 12, 13, 100, 4, 4, 1, 2),
+    (40, 16, 14, 14, 16, 3, 3, 1, 1), (400, 16, 14, 14, 16, 3, 3, 1, 1), (7, 16, 114, 114, 16, 3, 3, 1, 1), (2, 3, 60, 60, 7, 7, 7, 2, 3),
+])
+def test_small_layers_prepare_their_own_kernels(gpu, case):
+    """Workgroups of small layers prepare their own kernels: within the bound, with an infinite input and a weight beyond the
+    parts' range, and replayed in a graph."""
+    torch, B = gpu
+    N, C, H, W, K, R, S, stride, pad = case
+    x, w = make_inputs(N, C, H, W, K, R, S, "u11", "he", seed=sum(case))
+    ref, lim = conv_ref(x, w, stride, pad), _bound(x, w, stride, pad)
+    xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+    y = B.conv_direct(xd, wd, stride, pad)
+    assert (np.abs(y.cpu().numpy() - ref) <= lim).all()
+    x[0, C - 1, H // 2, W // 2] = np.inf
+    w[K - 1, 0, 0, 0] = -1e35
+    ref = conv_ref(x, w, stride, pad)
+    xi, wi = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+    z = B.conv_direct(xi, wi, stride, pad).cpu().numpy()
+    fine = np.isfinite(ref)
+    assert np.array_equal(np.isnan(z), np.isnan(ref)) and np.array_equal(z[~fine], ref[~fine], equal_nan=True)
+    assert (np.abs(z[fine] - ref[fine]) <= _bound(np.where(np.isfinite(x), x, 0), w, stride, pad)[fine]).all()
+    out = torch.empty_like(y)
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        B.conv_direct(xd, wd, stride, pad, y=out)
+    for _ in range(3):
+        out.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, y)
+
+
 def test_more_blocks_than_ids_divided_by_multiplication(gpu):
     """Beyond 32768 workgroups (34816 here, of 112 pixels by 128 kernels) their ids are divided as integers; parts of the batch
     stay below.  Whole numbers: every sum is exact, whatever the block."""
