@@ -198,28 +198,39 @@ def iolb_winograd_matrices(m):
             [[Bm[i * n + j] for j in range(n)] for i in range(n)])
 
 
+_torch = None
+
+
+def _load_torch():
+    # once: an import statement in every function of a call is a look-up under the import lock each
+    global _torch
+    import torch
+    _torch = torch
+    return torch
+
+
 def _use_current_stream():
     # the handle itself: building torch's stream object for it takes 2.5 us, a quarter of a small layer's whole call
     # (one image of 16 channels at 14 x 14: 13.4 -> 10.6 us a call).  The function is not part of torch's public
     # interface; a torch without it goes the public way.
-    import torch
+    torch = _torch or _load_torch()
     device = torch.cuda.current_device()
     raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
     handle = raw(device) if raw is not None else torch.cuda.current_stream(device).cuda_stream
-    _check(lib().iolb_set_stream(ctypes.c_void_p(handle)))
+    _check(lib().iolb_set_stream(handle))
 
 
 def _dev_f32(t, name):
-    import torch
+    torch = _torch or _load_torch()
     if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == torch.float32 and t.is_contiguous()):
         raise TypeError(name + " must be a contiguous float32 tensor on the GPU")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()                        # (an address: the functions' argtypes make pointers of it)
 
 
 def conv_direct(x, w, stride=1, pad=0, y=None, cfg=None):
     """y = direct convolution of x [N][C][H][W] with w [K][C][R][S] on the current stream.  pad: zeros per
     side, or (pad_h, pad_w) for a padding of its own per axis (tuned tile only)."""
-    import torch
+    torch = _torch or _load_torch()
     N, C, H, W = x.shape
     K, C2, R, S = w.shape
     if C2 != C:
@@ -262,7 +273,7 @@ def conv_direct_layout(x, w, stride=1, pad=0, layout=LAYOUT_HWC, y=None, cfg=Non
     """Direct convolution with the tensor layout given: LAYOUT_CHW as conv_direct; LAYOUT_HWC takes
     x [N][H][W][C] and returns y [N][P][Q][K]; LAYOUT_CWH takes x [N][C][W][H] and returns y [N][K][Q][P].
     w is [K][C][R][S] for all."""
-    import torch
+    torch = _torch or _load_torch()
     if layout == LAYOUT_HWC:
         N, H, W, C = x.shape
     elif layout == LAYOUT_CWH:
@@ -306,7 +317,7 @@ def conv_direct_noalloc(x, w, stride, pad, y):
 def conv_winograd(x, w, m, y=None, cfg=None, workspace=None, pad=1):
     """y = Winograd F(m x m, 3 x 3) convolution (stride 1, pad 1 unless `pad` says otherwise) on the current
     stream.  Another padding runs with the tuned tile and the library's workspace only."""
-    import torch
+    torch = _torch or _load_torch()
     N, C, H, W = x.shape
     K, C2, R, S = w.shape
     if C2 != C or R != 3 or S != 3:
@@ -349,7 +360,7 @@ def conv_winograd(x, w, m, y=None, cfg=None, workspace=None, pad=1):
 def winograd_transform_kernels(w, m):
     """U = L g L^T for w [K][C][3][3], in a new device buffer the Winograd calls can reuse (see
     conv_winograd_pre); returns (U, C, K)."""
-    import torch
+    torch = _torch or _load_torch()
     K, C, R, S = w.shape
     if R != 3 or S != 3:
         raise ValueError("Winograd path needs 3x3 kernels")
@@ -364,7 +375,7 @@ def winograd_transform_kernels(w, m):
 
 def conv_winograd_pre(x, U, K, m, y=None, cfg=None, workspace=None):
     """conv_winograd with kernels transformed beforehand by winograd_transform_kernels."""
-    import torch
+    torch = _torch or _load_torch()
     N, C, H, W = x.shape
     if y is None:
         y = torch.empty((N, K, H, W), dtype=torch.float32, device=x.device)
@@ -435,7 +446,7 @@ PROBE_ROLE_MFMA, PROBE_ROLE_VALU = 0, 1
 def probe_pipeline_share(roles, iters=2000):
     """(milliseconds, [average clock ticks of a wave of each slot]) of one launch in which every SIMD holds
     len(roles) waves, slot s running roles[s] (PROBE_ROLE_MFMA / PROBE_ROLE_VALU)."""
-    import torch
+    torch = _torch or _load_torch()
     _use_current_stream()
     scratch = torch.zeros(lib().iolb_probe_share_scratch_bytes() // 4 + 1, dtype=torch.float32, device="cuda")
     arr = (ctypes.c_int * len(roles))(*roles)
