@@ -53,6 +53,20 @@ def test_layers_the_call_without_allocation_takes_fit_its_room(layer):
             assert route == B.ROUTE_SPLIT
 
 
+def test_division_by_multiplication_is_exact_in_its_range():
+    """n / d as the high half of 2 n times 2^31 / d + 1, in 32 bits, for every n d < 2^31: around the multiples of d and at
+    the largest n, where it would be wrong first."""
+    rng = np.random.default_rng(0)
+    for d in list(range(1, 600)) + rng.integers(600, 1 << 20, 400).tolist() + [32767, 32768, 32769, (1 << 30) + 1, (1 << 31) - 1]:
+        m = (1 << 31) // d + 1
+        assert m < 1 << 32
+        most = ((1 << 31) - 1) // d
+        k = np.unique(np.concatenate([np.arange(0, 200), rng.integers(0, most // d + 1, 200), [most // d]]))
+        n = np.unique(np.concatenate([k * d - 1, k * d, k * d + 1, [most]]))
+        n = n[(n >= 0) & (n <= most)].astype(np.uint64)
+        assert np.array_equal((n * np.uint64(2) * np.uint64(m)) >> np.uint64(32), n // np.uint64(d)), d
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("first", [B.LAYOUT_CWH, B.LAYOUT_CHW])
 def test_large_pointwise_layers_give_the_same_bits_whatever_ran_before(first):
