@@ -586,14 +586,9 @@ hipError_t launch_split_conv(const float* x, const void* wt, float* y, const Spl
         4LL * g.b * g.C * g.H * g.W >= (1LL << 31) || g.cstep != (g.hwc ? 4 : 4 * g.H * g.W) || (g.vec_in && (!g.hwc || g.C % 4)))
         return hipErrorInvalidValue;
     const u32x4* w = static_cast<const u32x4*>(wt);
-    // Divided are items, units and pixels of a block (what is in LDS per item and unit bounds them by 2^15, their divisors too),
-    // and workgroup ids.
-    const unsigned pixel_blocks = (unsigned)(g.nbx * g.nby * g.nbn);
-    const bool small = (long long)pixel_blocks * g.nbk <= 32768;
-    if ((long long)g.ch8 * g.halo > 32768 || split_steps(g) * 4LL > 32768 || g.S > 32768) return hipErrorInvalidValue;
-    const SplitDivisors dv = {Divisor(g.ch8), Divisor(g.halo), Divisor(g.yh * g.rowp), Divisor(g.rowp), Divisor(g.S), Divisor(g.esx), Divisor(g.tx * g.ty),
-                              Divisor(g.tx), Divisor(g.nbk), Divisor(pixel_blocks), Divisor(g.nbx), Divisor(g.nby), small};
-    const SplitOwn o = {Divisor(split_steps(g)), Divisor(g.C * g.R * g.S), transposed ? 1 : 0};
+    SplitDivisors dv;
+    SplitOwn o;
+    if (!split_divisors(g, transposed, &dv, &o)) return hipErrorInvalidValue;
     return g.vec_in ? launch_shape<true>(x, w, y, g, dv, own ? &o : nullptr, st) : launch_shape<false>(x, w, y, g, dv, own ? &o : nullptr, st);
 }
 

@@ -83,7 +83,7 @@ struct Divisor {
     unsigned m;                // 2^31 / d, rounded down, + 1
     Divisor() = default;
     explicit Divisor(unsigned d) : m((1u << 31) / d + 1) {}
-    __device__ __forceinline__ int of(int n) const { return (int)__umulhi((unsigned)n << 1, m); }
+    __host__ __device__ int of(int n) const { return (int)((unsigned long long)((unsigned)n << 1) * m >> 32); }
 };
 // ... by the extents that the kernel divides by
 struct SplitDivisors {
@@ -133,6 +133,18 @@ inline long long split_lds_bytes(const SplitGeom& g, bool own = false)
 {
     const long long tables = ((long long)g.nbuf * g.ch8 * g.b * g.yh * g.rowb + 4 * ((4 * split_steps(g) + 1) & ~1) + 8LL * g.ch8 * g.halo + 15) & ~15LL;
     return tables + (own ? split_own_bytes(g) : 0);
+}
+// What the kernel divides by.  Divided are items, units and pixels of a block (what is in LDS per item and unit bounds them by 2^15,
+// their divisors too), and workgroup ids, where there are few enough.  False for a geometry beyond that.
+inline bool split_divisors(const SplitGeom& g, bool transposed, SplitDivisors* dv, SplitOwn* own)
+{
+    if ((long long)g.ch8 * g.halo > 32768 || split_steps(g) * 4LL > 32768 || g.S > 32768) return false;
+    const unsigned pixel_blocks = (unsigned)(g.nbx * g.nby * g.nbn);
+    const bool small = (long long)pixel_blocks * g.nbk <= 32768;
+    *dv = {Divisor(g.ch8), Divisor(g.halo), Divisor(g.yh * g.rowp), Divisor(g.rowp), Divisor(g.S), Divisor(g.esx), Divisor(g.tx * g.ty),
+           Divisor(g.tx), Divisor(g.nbk), Divisor(pixel_blocks), Divisor(g.nbx), Divisor(g.nby), small};
+    *own = {Divisor(split_steps(g)), Divisor(g.C * g.R * g.S), transposed ? 1 : 0};
+    return true;
 }
 // The input-tile buffer of a chunk: never one that split_lds_bytes does not count.
 __host__ __device__ constexpr int split_buffer(int chunk, int nbuf) { return chunk & (nbuf - 1); }
@@ -244,6 +256,13 @@ struct WinoSplitDivisors {
     Divisor nbt, per_image, tw;
     int small;
 };
+inline WinoSplitDivisors wino_split_divisors(const WinoSplitGeom& g)
+{
+    const int per_image = g.th * g.tw;
+    // (sub-domains of the last block may not exist: less than 64 of them)
+    const bool small = (g.tiles + 64LL) * per_image < (1LL << 31) && (long long)g.nbt * g.nbk * g.nbt < (1LL << 31);
+    return {Divisor(g.nbt), Divisor(per_image), Divisor(g.tw), small};
+}
 #define IOLB_WINO_SPLIT_SHAPES(X) X(4, 32, 64) X(4, 32, 32) X(2, 64, 64) X(2, 32, 32)
 inline long long wino_split_weight_bytes(const WinoSplitGeom& g) { return (g.m + 2LL) * (g.m + 2) * g.chunks * g.Kb32 * 3072; }
 // Whether the kernel's 32-bit offsets reach: the images of a block, the kernels.

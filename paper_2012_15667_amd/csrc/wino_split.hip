@@ -521,10 +521,7 @@ hipError_t launch_one(const float* x, const u32x4* wt, float* y, const WinoSplit
         const hipError_t e = allow_large_lds((const void*)kern);
         if (e != hipSuccess) return e;
     }
-    const int per_image = g.th * g.tw;
-    const bool small = (g.tiles + 64LL) * per_image < (1LL << 31) && (long long)g.nbt * g.nbk * g.nbt < (1LL << 31);
-    const WinoSplitDivisors dv = {Divisor(g.nbt), Divisor(per_image), Divisor(g.tw), small};
-    hipLaunchKernelGGL(kern, dim3(g.nbt * g.nbk), dim3(512), shm, st, x, wt, y, g, dv);
+    hipLaunchKernelGGL(kern, dim3(g.nbt * g.nbk), dim3(512), shm, st, x, wt, y, g, wino_split_divisors(g));
     return hipGetLastError();
 }
 

@@ -1,5 +1,6 @@
 """Which kernel a call without a tile runs on (iolb_route): a property of the layer, whatever was asked before, and within
 the fixed room of conv_direct_noalloc.  Host only, except where marked."""
+import ctypes
 import json
 import os
 import subprocess
@@ -9,6 +10,7 @@ import numpy as np
 import pytest
 
 from paper_2012_15667_amd import binding as B
+from tests import plan_host
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SCRATCH_BYTES = 6 * 4194304              # conv_direct_noalloc's array: 4 Mi weights in three bf16 parts
@@ -54,17 +56,41 @@ def test_layers_the_call_without_allocation_takes_fit_its_room(layer):
 
 
 def test_division_by_multiplication_is_exact_in_its_range():
-    """n / d as the high half of 2 n times 2^31 / d + 1, in 32 bits, for every n d < 2^31: around the multiples of d and at
-    the largest n, where it would be wrong first."""
+    """The library's Divisor for every n d < 2^31: around the multiples of d and at the largest n, where it would be wrong first."""
     rng = np.random.default_rng(0)
     for d in list(range(1, 600)) + rng.integers(600, 1 << 20, 400).tolist() + [32767, 32768, 32769, (1 << 30) + 1, (1 << 31) - 1]:
-        m = (1 << 31) // d + 1
-        assert m < 1 << 32
         most = ((1 << 31) - 1) // d
         k = np.unique(np.concatenate([np.arange(0, 200), rng.integers(0, most // d + 1, 200), [most // d]]))
         n = np.unique(np.concatenate([k * d - 1, k * d, k * d + 1, [most]]))
-        n = n[(n >= 0) & (n <= most)].astype(np.uint64)
-        assert np.array_equal((n * np.uint64(2) * np.uint64(m)) >> np.uint64(32), n // np.uint64(d)), d
+        n = np.ascontiguousarray(n[(n >= 0) & (n <= most)].astype(np.int32))
+        q = np.empty_like(n)
+        plan_host.lib().divide(n.ctypes.data, len(n), d, q.ctypes.data)
+        assert np.array_equal(q, n // d), d
+
+
+@pytest.mark.parametrize("layer", [
+    # N, C, H, W, K, R, S, stride, pad
+    (1, 16, 14, 14, 16, 3, 3, 1, 1), (64, 256, 56, 56, 256, 3, 3, 1, 1), (2, 3, 60, 60, 7, 7, 7, 2, 3), (1, 8, 224, 224, 64, 11, 11, 4, 0),
+    (3, 17, 40, 300, 40, 1, 65, 1, 0), (2, 9, 33, 35, 17, 2, 2, 5, 0), (600, 40, 14, 14, 2000, 3, 3, 1, 1), (4352, 9, 14, 14, 512, 3, 3, 1, 1),
+    (64, 64, 224, 224, 512, 3, 3, 1, 1), (8192, 9, 7, 7, 512, 3, 3, 1, 1),
+])
+def test_what_the_direct_kernel_divides_is_in_that_range(layer):
+    facts = (ctypes.c_int * 4)()
+    assert plan_host.lib().split_facts(*layer, facts) == 1
+    assert facts[3] == 1 and facts[2] == (facts[0] <= 32768), list(facts)
+
+
+@pytest.mark.parametrize("layer", [
+    # N, C, H, W, K, m, pad: tiles times the tiles of an image on both sides of 2^31
+    (1, 8, 180, 180, 8, 2, 1), (1, 5, 430, 430, 32, 2, 1), (1, 5, 432, 432, 32, 2, 1), (64, 16, 99, 101, 64, 4, 1), (200, 5, 129, 131, 40, 4, 2),
+    (1, 5, 4000, 4001, 32, 2, 1), (20000, 5, 7, 7, 100, 2, 1),
+])
+def test_what_the_fused_winograd_kernel_divides_is_in_that_range(layer):
+    N, C, H, W, K, m, pad = layer
+    facts = (ctypes.c_int * 3)()
+    assert plan_host.lib().wino_split_facts(*layer, facts) == 1
+    per = -(-(H + 2 * pad - 2) // m) * -(-(W + 2 * pad - 2) // m)
+    assert facts[2] == 1 and (facts[1] == 1 or (N * per + 64) * per >= 1 << 31 or facts[0] ** 2 >= 1 << 31)
 
 
 @pytest.mark.gpu
