@@ -274,6 +274,19 @@ inline bool wino_split_fits(const WinoSplitGeom& g)
            g.nbk * (g.z / 32) == g.Kb32 && g.Kb32 * 32LL >= g.K && (long long)g.nbt * g.tb >= g.tiles && (long long)g.nbt * g.nbk <= 0x7fffffffLL &&
            per * g.N == g.tiles && (long long)g.nbt * g.tb < (1LL << 31);
 }
+// Bytes of the buffer that a block's inputs are read from, `images` of them, from the first window's origin at (-pad, -pad) on.
+__host__ __device__ inline unsigned wino_split_range(const WinoSplitGeom& g, int images)
+{
+    return 4u * ((unsigned)images * (unsigned)(g.C * g.H * g.W) + (unsigned)(g.pad * (g.W + 1)));
+}
+// The scalar byte offset at which channel c0 (and the next three) and row r of the windows are loaded.  Never beyond the range of
+// even one image: the hardware checks a lane's own offset against the range less this one, which must not wrap.  Rows that lie
+// below every window's image (r >= H + pad) and channels that do not exist are masked in every lane.
+__host__ __device__ inline int wino_split_offset(const WinoSplitGeom& g, int c0, int r)
+{
+    const int last = g.H + g.pad - 1;
+    return 4 * ((c0 < g.C ? c0 : 0) * (g.H * g.W) + (r < last ? r : last) * g.W);
+}
 // The kernels in three parts, from w[K][C][3][3] or (given) from a caller's U[plane][C rounded up to 16][K to 32].
 hipError_t launch_wino_split_weights(const float* w, bool given, void* wt, const WinoSplitGeom& g, hipStream_t st);
 hipError_t launch_wino_split(const float* x, const void* wt, float* y, const WinoSplitGeom& g, hipStream_t st);

@@ -111,7 +111,7 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
     const int span = __builtin_amdgcn_readfirstlane(image_of(last_t - 1) + 1 - img0);
     const unsigned long long xb = reinterpret_cast<unsigned long long>(x) + 4 * (img0 * image) - 4ull * shift;
     const unsigned xlo = __builtin_amdgcn_readfirstlane((unsigned)xb), xhi = __builtin_amdgcn_readfirstlane((unsigned)(xb >> 32));
-    const unsigned xrange = __builtin_amdgcn_readfirstlane((unsigned)(4 * (image * span + shift)));
+    const unsigned xrange = __builtin_amdgcn_readfirstlane(wino_split_range(g, span));
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>((unsigned long long)xhi << 32 | xlo), 0, (int)xrange, 0x00020000);
     const unsigned ubytes = __builtin_amdgcn_readfirstlane((unsigned)g.chunks * (unsigned)g.Kb32 * (3072u * PL));
     const __amdgpu_buffer_rsrc_t ru = __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4*>(wt), 0, (int)ubytes, 0x00020000);
@@ -148,7 +148,7 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
             const unsigned long long have = __builtin_amdgcn_ballot_w64(16 * s + cl + 4 * i < g.C);
             static_range<0, n>([&](auto rc) {
                 constexpr int r = decltype(rc)::value;
-                const int so = 4 * ((c0 < g.C ? c0 : 0) * plane_in + r * g.W);
+                const int so = wino_split_offset(g, c0, r);
                 const unsigned long long row = have & rowok[r];
                 wx[i][r][0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rx, (int)(by_lane(row & edge) ? eoff : OUTSIDE), so, 0));
                 if constexpr (COLS != COLS_SINGLE && M == 4) {
@@ -549,7 +549,8 @@ hipError_t launch_wino_split(const float* x, const void* wt, float* y, const Win
     // what the kernel assumes of its geometry
     if (!wino_split_fits(g)) return hipErrorInvalidValue;
     const u32x4* u = static_cast<const u32x4*>(wt);
-    // (loads and stores of M floats need no more than the alignment of one; each float is checked against the buffer's range)
+    // (loads and stores of M floats need no more than the alignment of one; each float is checked against the buffer's range, the
+    // scalar offset included: measured with loads across the end of a range inside a larger buffer)
     const int cols = g.pad != 1 ? COLS_SINGLE : g.W % g.m ? COLS_CUT : COLS_WHOLE;
 #define IOLB_CASE(M_, T_, Z_)                                                            \
     if (g.m == M_ && g.tb == T_ && g.z == Z_)                                            \

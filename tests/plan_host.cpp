@@ -29,6 +29,18 @@ extern "C" int plan_wino_split(int N, int C, int H, int W, int K, int m, int pad
     return wino_split_plan(g, &ns);
 }
 
+// Of the input loads of such a layer: the greatest scalar offset less the buffer's range of one image.
+extern "C" long long wino_split_beyond_range(int N, int C, int H, int W, int K, int m, int pad)
+{
+    WinoSplitGeom g;
+    if (!plan_wino_split(N, C, H, W, K, m, pad, &g)) return -1;
+    long long most = 0;
+    for (int c0 = 0; c0 < 16 * (g.chunks + 2); c0 += 4)                   // (stages are loaded up to two ahead)
+        for (int r = 0; r < m + 2; ++r)
+            if (wino_split_offset(g, c0, r) > most) most = wino_split_offset(g, c0, r);
+    return most - (long long)wino_split_range(g, 1);
+}
+
 // The direct kernel's block for a layer (H x W padded by pad on both axes), and its workgroups.
 extern "C" int plan_split(int N, int C, int H, int W, int K, int R, int S, int stride, int pad, SplitGeom* g)
 {

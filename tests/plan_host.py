@@ -21,4 +21,5 @@ def lib():
         L = ctypes.CDLL(out)
     L.divide.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_uint, ctypes.c_void_p]
     L.divide.restype = None
+    L.wino_split_beyond_range.restype = ctypes.c_longlong
     return L

@@ -416,6 +416,9 @@ FUSED_CASES = [
     (2, 8, 128, 56, 56, 128, 1), (2, 2, 182, 125, 125, 102, 1), (2, 30, 128, 40, 41, 128, 3),
     (4, 16, 64, 64, 64, 64, 1), (4, 64, 256, 14, 14, 256, 1), (4, 20, 16, 100, 99, 17, 2), (4, 30, 30, 59, 58, 40, 1),
     (4, 8, 80, 128, 128, 144, 1), (4, 12, 36, 60, 61, 66, 1), (4, 1, 48, 300, 301, 34, 2),
+    # images of fewer rows than a window has, channels no multiple of the four that are loaded together
+    (4, 4, 5, 3, 100, 512, 1), (4, 16, 17, 1, 224, 128, 1), (4, 64, 23, 2, 224, 64, 1), (4, 30, 33, 1, 225, 40, 3),
+    (2, 64, 17, 1, 120, 64, 1), (2, 64, 21, 1, 33, 40, 2),
 ]
 
 

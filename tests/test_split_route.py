@@ -93,6 +93,19 @@ def test_what_the_fused_winograd_kernel_divides_is_in_that_range(layer):
     assert facts[2] == 1 and (facts[1] == 1 or (N * per + 64) * per >= 1 << 31 or facts[0] ** 2 >= 1 << 31)
 
 
+@pytest.mark.parametrize("m", [2, 4])
+@pytest.mark.parametrize("pad", [1, 2, 3])
+def test_scalar_offsets_of_the_fused_winograd_loads_stay_inside_one_image(m, pad):
+    """The hardware checks a lane's offset against the buffer's range less the scalar offset: that must not wrap, whatever
+    the lanes' masks say.  Images of fewer rows than a window has, every remainder of C by the four channels loaded together."""
+    for H in range(1, 8):
+        for W in (1, 2, 3, 5, 100, 224):
+            for C in list(range(5, 36)) + [100, 101, 102, 103]:
+                for N, K in ((1, 64), (4, 512)):
+                    beyond = plan_host.lib().wino_split_beyond_range(N, C, H, W, K, m, pad)
+                    assert beyond <= 0, (N, C, H, W, K, beyond)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("first", [B.LAYOUT_CWH, B.LAYOUT_CHW])
 def test_large_pointwise_layers_give_the_same_bits_whatever_ran_before(first):
