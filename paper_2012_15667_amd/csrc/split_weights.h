@@ -46,27 +46,25 @@ __device__ __forceinline__ void store_parts(u32x4* to, const unsigned short (&p)
     }
 }
 
-// Row `row` of L g for eight channels, g[3][3] one after the other from `from` on.
+// Row `row` (the same in every lane of a wave) of L g for eight channels, g[3][3] one after the other from `from` on.  A branch per
+// row, two channels' loads at a time: with every row computed and one selected, all channels' loads ahead, the launch that the input
+// transform shares took 254 registers in F(3 x 3), 210 in F(4 x 4) (now 66 and 61 - 112, as without), which left two waves per SIMD
+// (382 -> 132 at 121 x 121, batch 9, F(3 x 3): 633 us, now 579).
 template <int M>
 __device__ __forceinline__ void kernel_row(int row, const float* from, float (&lg)[8][3])
 {
-    constexpr int n = M + 2;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        float g[3][3], t[n][3];
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) g[i][j] = from[c * 9 + i * 3 + j];
-        left_mul<M, UseL, n, 3, 3>(g, t);
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            lg[c][j] = t[0][j];
-#pragma unroll
-            for (int i = 1; i < n; ++i)
-                if (row == i) lg[c][j] = t[i][j];
-        }
-    }
+    static_for<M + 2>([&](auto r) {
+        if (row != decltype(r)::value) return;
+        static_for<8>([&](auto c) {
+            static_for<3>([&](auto j) {
+                float u = 0.f;
+                bool first = true;
+                static_for<3>([&](auto i) { accumulate<M, UseL, decltype(r)::value, decltype(i)::value>(u, first, from[c * 9 + i * 3 + j]); });
+                lg[c][j] = u;
+            });
+            if constexpr (decltype(c)::value % 2) __builtin_amdgcn_sched_barrier(0);
+        });
+    });
 }
 // Element J of that row of L g L^T.
 template <int M, int J>
