@@ -110,7 +110,7 @@ constexpr int SPLIT_BATCH = 2;          // (pixel, 8 channels) items of the inpu
     X(1, 2, 4, 1) X(1, 4, 4, 1) X(1, 2, 2, 2) X(1, 4, 2, 2) X(2, 4, 2, 2) X(1, 2, 1, 4) X(1, 4, 1, 4) X(2, 4, 1, 4)
 // ... and those with workgroups that prepare their own kernels
 #define IOLB_SPLIT_OWN_SHAPES(X) X(1, 1, 1, 4) X(1, 2, 1, 4) X(1, 4, 1, 4) X(1, 2, 2, 2) X(1, 2, 4, 1)
-#define IOLB_SPLIT_OWN_FEW_SHAPES(X) X(1, 2, 1, 4) X(1, 4, 1, 4) X(1, 2, 2, 2) X(1, 2, 4, 1)
+#define IOLB_SPLIT_OWN_FEW_SHAPES(X) X(1, 2, 1, 4) X(1, 4, 1, 4)
 inline int split_steps(const SplitGeom& g) { return (g.R * g.S * g.ch8 + 3) / 4; }
 inline int split_chunks(const SplitGeom& g) { return (g.C + 8 * g.ch8 - 1) / (8 * g.ch8); }
 inline int split_batches(const SplitGeom& g)

@@ -156,20 +156,22 @@ bool split_plan(SplitGeom* g, double* cycles)
 }
 
 // Layers of few workgroups and small kernels: a launch before the convolution takes longer (some 2.3 us of the host's time
-// and 3 us of the GPU's) than every workgroup cutting the same kernels once more, about 1 us for 2304 floats.  The line lies
-// where both are even: 16 -> 16 at 14 x 14, one image, 10.6 -> 8.2 us a call, 3 x 32 -> 32 at 15 x 15 (4608 floats) 10.4 ->
-// 8.5; beyond it 20 x 32 -> 64 at 17 x 17, 7 x 1 (14336 floats) 10.6 -> 13.9, 3 x 20 -> 24 at 206 x 206, stride 2 (5760, 500
-// workgroups) 14.3 -> 25.6.
-constexpr long long OWN_FLOATS = 4800, OWN_ALL_FLOATS = 256 * OWN_FLOATS;
+// and 3 us of the GPU's) than every workgroup cutting the same kernels once more, about 1 us for 2304 values.  Counted are the
+// values that it cuts: eight channels per unit whether they exist or not, four units per step.  The line lies where both are even,
+// found on 340 drawn layers of up to 20500 values: up to 5400, and 256 workgroups of those, own kernels are the faster way on all 174,
+// by 1.25 in the mean (16 -> 16 at 14 x 14, one image, 10.6 -> 8.2 us a call; 3 x 32 -> 32 at 15 x 15, 4608 values, 10.4 -> 8.5);
+// at 6144 to 6656 it is 1.0, and 0.5 - 0.8 on more than 256 workgroups (3 -> 48 at 148 x 148, batch 6, 7 x 7, stride 2: 6656
+// values, 2352 of them of channels and taps that exist, 504 workgroups, 19.4 us with a launch before it, 29.0 without).
+constexpr long long OWN_VALUES = 5400, OWN_ALL_VALUES = 256 * OWN_VALUES;
 bool split_own(const SplitGeom& g)
 {
     bool shape = false;
 #define IOLB_SPLIT_OWN_ENTRY(M_, N_, A_, B_) shape = shape || (g.mb == M_ && g.nb == N_ && g.wm == A_ && g.wn == B_);
     if (g.ch8 == 1) { IOLB_SPLIT_OWN_FEW_SHAPES(IOLB_SPLIT_OWN_ENTRY) } else { IOLB_SPLIT_OWN_SHAPES(IOLB_SPLIT_OWN_ENTRY) }
 #undef IOLB_SPLIT_OWN_ENTRY
-    const long long floats = 16LL * g.mb * g.wm * g.C * g.R * g.S;
+    const long long values = 16LL * g.mb * g.wm * split_chunks(g) * split_steps(g) * 32;
     const long long grid = (long long)g.nbk * g.nbx * g.nby * g.nbn;
-    return shape && floats <= OWN_FLOATS && grid * floats <= OWN_ALL_FLOATS && split_lds_bytes(g, true) <= 160 * 1024;
+    return shape && values <= OWN_VALUES && grid * values <= OWN_ALL_VALUES && split_lds_bytes(g, true) <= 160 * 1024;
 }
 
 bool split_point_plan(SplitPointGeom* g, double* cycles)

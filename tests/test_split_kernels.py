@@ -94,14 +94,24 @@ def test_kernels_reach_their_steps_for_every_window(gpu, taps, C, K):
     assert np.array_equal(yt, y.transpose(0, 1, 3, 2))
 
 
-@pytest.mark.parametrize("case", [
-    # N, C, H, W, K, R, S, stride, pad: 4608 and 4320 kernel floats a workgroup, the next ones beyond 4800; many workgroups
-    (3, 32, 15, 15, 32, 3, 3, 1, 1), (2, 30, 14, 15, 17, 3, 3, 2, 1), (1, 34, 15, 15, 32, 3, 3, 1, 1), (3, 9, 12, 13, 100, 4, 4, 1, 2),
-    (40, 16, 14, 14, 16, 3, 3, 1, 1), (400, 16, 14, 14, 16, 3, 3, 1, 1), (7, 16, 114, 114, 16, 3, 3, 1, 1), (2, 3, 60, 60, 7, 7, 7, 2, 3),
-])
+# N, C, H, W, K, R, S, stride, pad of layers whose workgroups prepare their own kernels, up to 5400 values each: few and many
+# channels and workgroups, kernels beyond the last block ...
+OWN_LAYERS = [
+    (3, 32, 15, 15, 32, 3, 3, 1, 1), (2, 30, 14, 15, 17, 3, 3, 2, 1), (3, 9, 12, 13, 100, 4, 4, 1, 2), (40, 16, 14, 14, 16, 3, 3, 1, 1),
+    (400, 16, 14, 14, 16, 3, 3, 1, 1), (7, 16, 114, 114, 16, 3, 3, 1, 1), (2, 3, 100, 100, 16, 5, 5, 1, 1), (2, 5, 100, 100, 15, 6, 6, 1, 1),
+]
+# ... and of layers beyond that, in values or in workgroups
+NOT_OWN_LAYERS = [
+    (1, 34, 15, 15, 32, 3, 3, 1, 1), (2, 3, 60, 60, 7, 7, 7, 2, 3), (6, 3, 148, 148, 48, 7, 7, 2, 3), (2, 48, 13, 13, 16, 3, 3, 1, 1),
+    (64, 16, 114, 114, 16, 3, 3, 1, 1),
+]
+MANY_BLOCKS = (4352, 9, 14, 14, 512, 3, 3, 1, 1)
+
+
+@pytest.mark.parametrize("case", OWN_LAYERS + NOT_OWN_LAYERS[:4])
 def test_small_layers_prepare_their_own_kernels(gpu, case):
-    """Workgroups of small layers prepare their own kernels: within the bound, with an infinite input and a weight beyond the
-    parts' range, and replayed in a graph."""
+    """Workgroups of small layers prepare their own kernels (which do: a test of the planner, by the same lists): within the bound,
+    with an infinite input and a weight beyond the parts' range, and replayed in a graph."""
     torch, B = gpu
     N, C, H, W, K, R, S, stride, pad = case
     x, w = make_inputs(N, C, H, W, K, R, S, "u11", "he", seed=sum(case))
@@ -134,10 +144,11 @@ def test_more_blocks_than_ids_divided_by_multiplication(gpu):
     """Beyond 32768 workgroups (34816 here, of 112 pixels by 128 kernels) their ids are divided as integers; parts of the batch
     stay below.  Whole numbers: every sum is exact, whatever the block."""
     torch, B = gpu
-    x = torch.randint(-4, 5, (4352, 9, 14, 14), device="cuda", dtype=torch.float32)
-    w = torch.randint(-4, 5, (512, 9, 3, 3), device="cuda", dtype=torch.float32)
-    y = B.conv_direct(x, w, 1, 1)
-    for i in range(0, 4352, 1088):
+    N, C, H, W, K, R, S, stride, pad = MANY_BLOCKS
+    x = torch.randint(-4, 5, (N, C, H, W), device="cuda", dtype=torch.float32)
+    w = torch.randint(-4, 5, (K, C, R, S), device="cuda", dtype=torch.float32)
+    y = B.conv_direct(x, w, stride, pad)
+    for i in range(0, N, 1088):
         assert torch.equal(y[i:i + 1088], B.conv_direct(x[i:i + 1088].contiguous(), w, 1, 1))
 
 

@@ -11,6 +11,7 @@ import pytest
 
 from paper_2012_15667_amd import binding as B
 from tests import plan_host
+from tests.test_split_kernels import MANY_BLOCKS, NOT_OWN_LAYERS, OWN_LAYERS
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SCRATCH_BYTES = 6 * 4194304              # conv_direct_noalloc's array: 4 Mi weights in three bf16 parts
@@ -78,6 +79,14 @@ def test_what_the_direct_kernel_divides_is_in_that_range(layer):
     facts = (ctypes.c_int * 4)()
     assert plan_host.lib().split_facts(*layer, facts) == 1
     assert facts[3] == 1 and facts[2] == (facts[0] <= 32768), list(facts)
+
+
+@pytest.mark.parametrize("layer,own", [(l, 1) for l in OWN_LAYERS] + [(l, 0) for l in NOT_OWN_LAYERS] + [(MANY_BLOCKS, 0)])
+def test_which_layers_prepare_their_own_kernels(layer, own):
+    facts = (ctypes.c_int * 4)()
+    assert plan_host.lib().split_facts(*layer, facts) == 1 and facts[3] == 1
+    assert facts[1] == own
+    assert (facts[0] > 32768) == (layer == MANY_BLOCKS)         # workgroups: where ids are divided as integers
 
 
 @pytest.mark.parametrize("layer", [
