@@ -536,7 +536,7 @@ SplitWino split_wino(const iolb_shape& s, const iolb_tile_config& tile)
     const size_t most = winograd_workspace_max(s.C, s.K, w.m, tiles);
     const bool runs = tile_runs && tile.path != IOLB_PATH_FMA;
     const size_t tile_bytes = runs ? winograd_layout(t.Cp, t.Kp, t.m, t.tiles_pitch, tile.path).total : 0;
-    double product_ns = 0, fused_ns = 0;
+    double product_cycles = 0, fused_ns = 0;                  // (clock cycles of the product alone; ns of the fused call)
     size_t product_bytes = 0, fused_bytes = 0;
     if (runs && n2 * std::max(s.C, s.K) * pitch < (1LL << 31) && s.C <= 32768 && s.K <= 65535) {
         iolb::SplitPointGeom& g = r.g;
@@ -550,7 +550,7 @@ SplitWino split_wino(const iolb_shape& s, const iolb_tile_config& tile)
             r.v_off = align256((size_t)n2 * iolb::split_point_weight_bytes(g));
             r.m_off = r.v_off + align256(sizeof(float) * n2 * s.C * pitch);
             product_bytes = std::max(r.m_off + align256(sizeof(float) * n2 * s.K * pitch), tile_bytes);
-            if (product_bytes <= most) product_ns = cycles;
+            if (product_bytes <= most) product_cycles = cycles;
         }
     }
     if (runs && (w.m == 2 || w.m == 4)) {
@@ -562,7 +562,7 @@ SplitWino split_wino(const iolb_shape& s, const iolb_tile_config& tile)
             if (fused_bytes > most) fused_ns = 0;
         }
     }
-    switch (iolb::split_wino_pick(s, tile, tiles, product_ns, fused_ns)) {
+    switch (iolb::split_wino_pick(s, tile, tiles, product_cycles, fused_ns)) {
     case 1: r.kind = SplitWino::PRODUCT; r.total = product_bytes; break;
     case 2: r.kind = SplitWino::FUSED; r.total = fused_bytes; break;
     default: break;
