@@ -243,7 +243,8 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
                     vec q;
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb) {
-                        if (!(__builtin_fabsf(acc[mb][nb][i]) <= 3.402823466e38f)) again |= 1ull << ((nb * MB + mb) * 4 + i);
+                        // (beyond the pixels that exist the inputs are what follows them: not a reason to do anything again)
+                        if (px + nb < left_px && !(__builtin_fabsf(acc[mb][nb][i]) <= 3.402823466e38f)) again |= 1ull << ((nb * MB + mb) * 4 + i);
                         q[nb] = acc[mb][nb][i] * SPLIT_UNSCALE;
                     }
                     if (k0 + i >= g.K) continue;

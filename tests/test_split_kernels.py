@@ -345,7 +345,8 @@ def _outside_is_untouched(torch, frame, at, n):
 @pytest.mark.parametrize("case", [(64, 256, 14, 14, 256), (50, 260, 12, 15, 261), (50, 300, 10, 13, 300), (12, 768, 17, 17, 192), (9, 256, 30, 34, 250)])
 @pytest.mark.parametrize("at", [4, 5, 6])
 def test_pointwise_stores_of_several_pixels(gpu, case, at):
-    """Planes of a multiple of four pixels leave in vector stores where y allows it, others one by one."""
+    """Neighbouring pixels leave in one store, at any alignment of y, where they cannot run on into another image (planes of a multiple
+    of the pixels per lane, or one image per group); the last ones of a plane may be fewer.  Nothing is written beyond y."""
     torch, B = gpu
     N, C, H, W, K = case
     assert B.iolb_route(B.make_shape(N, C, H, W, K, 1, 1, 1, 0))[0] == B.ROUTE_SPLIT
@@ -357,6 +358,31 @@ def test_pointwise_stores_of_several_pixels(gpu, case, at):
     xs, wk = xd.double().flatten(2), wd.double().view(1, K, C).expand(N, K, C).contiguous()
     lim = (12 * -(-C // 8) + 16) * 2.0 ** -23 * torch.bmm(wk.abs(), xs.abs())
     assert bool(((y.double().flatten(2) - torch.bmm(wk, xs)).abs() <= lim).all())
+
+
+def test_what_lies_beyond_the_pixels_is_no_reason_to_take_sums_again(gpu):
+    """An odd number of sub-domains: a pair of pixels is read where the plane of inputs ends, and the other half is what the workspace
+    held before.  With NaN there the result has the same bits, and no wave takes its block a second time (73 us, 33 without)."""
+    torch, B = gpu
+    m, N, C, H, W, K = 2, 9, 512, 10, 10, 512                     # 225 sub-domains
+    route, need = B.iolb_route(B.make_shape(N, C, H, W, K, algo=B.WINO_ALGO[m]))
+    assert route == B.ROUTE_SPLIT and need > 16 * 4 * (C + K) * 225         # (V and M in the workspace: the product)
+    x, w = torch.rand((N, C, H, W), device="cuda"), torch.randn((K, C, 3, 3), device="cuda")
+    took, out = [], []
+    for fill in (0, 255):
+        ws = torch.full((need,), fill, dtype=torch.uint8, device="cuda")
+        out.append(B.conv_winograd(x, w, m, workspace=ws))
+        took.append(1e9)
+        for _ in range(10):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                B.conv_winograd(x, w, m, y=out[-1], workspace=ws)
+            b.record()
+            b.synchronize()
+            took[-1] = min(took[-1], a.elapsed_time(b))
+    assert torch.equal(out[0], out[1])
+    assert took[1] < 1.5 * took[0], took
 
 
 def test_zeros_around_the_image_meet_infinite_weights(gpu):
