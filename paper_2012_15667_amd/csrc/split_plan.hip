@@ -228,16 +228,13 @@ bool split_point_faster(const iolb_shape& s, int P, int Q)
 }
 
 // Modelled time of a call: the kernels' transform, and per round of workgroups first loads and stores and a stage of 16
-// channels, each somewhat longer the more rounds there are (share).  Fitted on whole calls of 2862 drawn layers (16 to 512
-// channels, 7 x 7 to 224 x 224, batch 1 to 64): within 5 (F(2 x 2), 64 x 64), 7 (32 x 32), 6 (F(4 x 4), 32 x 64) and 10 %
-// (32 x 32) in the 2-norm, 4 - 9 % above 200 us.
+// channels.  Fitted on 148 drawn layers (16 to 512 channels, 7 x 7 to 224 x 224, batch 1 to 64); on 2862 others within 9 (F(2 x 2))
+// and 12 % (F(4 x 4)) in the 2-norm, above 200 us 9 and 11 % too low (128 -> 128 at 112 x 112, batch 64, F(4 x 4) 494 us for 570).
 static double wino_split_ns(const WinoSplitGeom& g)
 {
-    struct Fit { double call, round, stage, share, last; };
-    const Fit f = g.m == 4 ? (g.z == 64 ? Fit{10200, 8630, 3750, 0.119, 0.53} : Fit{8800, 4400, 2515, 0.295, 0.58})
-                           : (g.z == 64 ? Fit{7900, 6300, 2840, 0.113, 0.56} : Fit{8000, 960, 1057, 0.143, 0.39});
-    const double per = (double)g.nbt * g.nbk / 256, rounds = per <= 4 ? std::ceil(per) : per + f.last;
-    return f.call + rounds * (f.round + f.stage * g.chunks) * (1 + f.share * std::max(0.0, 1 - 1 / per));
+    const double per = (double)g.nbt * g.nbk / 256, rounds = per <= 4 ? std::ceil(per) : per + 0.5;
+    if (g.m == 4) return g.z == 64 ? 5600 + rounds * (10700 + 3450.0 * g.chunks) : 7300 + rounds * (6900 + 2520.0 * g.chunks);
+    return g.z == 64 ? 3800 + rounds * (8500 + 2650.0 * g.chunks) : 7000 + rounds * (2500 + 1000.0 * g.chunks);
 }
 
 bool wino_split_plan(WinoSplitGeom* g, double* ns)
@@ -267,17 +264,15 @@ bool wino_split_plan(WinoSplitGeom* g, double* ns)
     return found;
 }
 
-// Modelled times in ns: of the tile's product or fused kernel by rounds of its blocks, traffic of V and M at 6 TB/s, the launches
-// (fitted on 194 drawn layers; on 8000 others within 9 % in the 2-norm for F(2 x 2) and 14 for F(4 x 4) where the tile is fused, 15 -
-// 29 where it is not); of the split product by its modelled cycles, traffic, its kernels' parts (11 - 14 % there).  A split way has
-// to win by a margin.  Over those 8000 layers against the rule that was there first (only a product, by the ratio below): 1.38
-// times as fast for F(2 x 2), 1.24 for F(4 x 4), 1.09 and 1.03 for F(3 x 3) and F(6 x 6); eight are 3 - 9 % slower.
-//   Unfused tiles where that rule took the product: it still runs unless the fused kernel is modelled faster.  By the tile's model
-// alone some went back to the tile (128 -> 304 at 77 x 77, batch 8, F(3 x 3) 150 -> 197 us).
-//   Unfused tiles of one wave: their model is off by 27 %, other tiles' by 8 - 19 (76 -> 26 at 81 x 81, batch 53, F(6 x 6) went to the
-// product, 176 -> 205 us); at 0.93 thirteen more layers of the 8000 are slower, by up to 17 %.
-//   Fused F(2 x 2) tiles of up to 32 channels: one or two stages, which both kernels spend on first loads and stores; at 0.95 ten
-// of 1149 layers were 3 - 10 % slower.
+// Modelled times in ns, each fitted on 194 drawn layers like those above (within 8 - 18 %; on 8000 others 9 - 14 where the tile is
+// fused, 15 - 29 where it is not, the split product 14 - 21): the tile's product or fused kernel by rounds of its blocks, traffic of V
+// and M at 5.7 - 6.05 TB/s, the launches.  A split way has to win by a margin.  Over those 8000 layers against the rule that was there
+// first (only a product, by the ratio below): 1.37 times as fast for F(2 x 2), 1.23 for F(4 x 4), 1.05 and 1.04 for F(3 x 3) and
+// F(6 x 6); 40 of them are 3 - 17 % slower, 35 of those below 30 us.  Models of fewer percent (residency of the tile's blocks, a cache of 400
+// MB before memory: 5 - 10 %) gained 1 - 4 % more in the mean and lost more than 3 % on twice as many.
+//   Unfused tiles where the first rule took the product: that runs, or the fused kernel where it is modelled faster by a margin too.
+// By the tile's model some went back to the tile (128 -> 304 at 77 x 77, batch 8, F(3 x 3) 150 -> 197 us; 128 -> 176 at 128 x
+// 128, batch 4, F(6 x 6) 101 -> 137), without the margin some to a slower fused kernel (512 -> 336 at 140 x 140, F(4 x 4) 143 -> 152).
 //   Layers whose channels are no multiple of four keep the first rule altogether.  The routes of three of them (130 and more channels)
 // are part of the tests; the kernels take such channels as well (33 x 261 -> 300 at 15 x 15 109 us, the product 63), and of those below
 // 128 channels, which no split way runs, nothing has been measured.
@@ -291,13 +286,8 @@ int split_wino_pick(const iolb_shape& s, const iolb_tile_config& tile, long long
     if (!fused_tile && s.C % 4) return product_first;
     const double out = (double)s.N * (s.H + 2 * s.pad - 2) * (s.W + 2 * s.pad - 2);
     const double bytes = 4 * ((double)s.N * s.C * s.H * s.W + 2 * n2 * tiles * (s.C + s.K) + s.K * out);
-    double product = 0;
-    if (product_cycles) {
-        struct Fit { double call, rate, cycle, parts; };
-        const Fit f = m == 2 ? Fit{10600, 4890, 0.144, 2480} : m == 3 ? Fit{11800, 4600, 0.134, 2080} : m == 4 ? Fit{12500, 4610, 0.154, 2200} : Fit{16400, 4240, 0.153, 2570};
-        product = f.call + bytes / f.rate + f.cycle * product_cycles + n2 * ((s.C + 31) / 32) * ((s.K + 15) / 16) * 3072 / f.parts;
-    }
-    if (product_first) return fused_ns && fused_ns < product ? 2 : 1;
+    const double product = m == 2 ? 9200 + bytes / 6050 + 0.25 * product_cycles : 12000 + bytes / 5700 + 0.334 * product_cycles;
+    if (product_first) return fused_ns && fused_ns < (m == 4 ? 0.92 : 1) * product ? 2 : 1;
     const double tb = tile.x / m, across = std::ceil(tiles / tb);
     double best;
     if (fused_tile) {
@@ -307,11 +297,11 @@ int split_wino_pick(const iolb_shape& s, const iolb_tile_config& tile, long long
         const double rounds = std::ceil(n2 * across * ((Kp + tile.z - 1) / tile.z) / 256), waves = std::min(4, tile.threads / 64);
         best = 12000 + bytes / 6000 + 45.0 * s.C + rounds * s.C * 2 * tb * tile.z / waves / 1000 * (m == 2 ? 9.2 : 6.6);
     }
-    const double fused_margin = !fused_tile ? 0.93 : m == 2 && s.C <= 32 ? 0.8 : 0.95;
-    const bool by_product = product && product < (!fused_tile && tile.threads == 64 ? 0.75 : 0.93) * best;
-    const double other = by_product ? std::min(product, fused_margin * best) : fused_margin * best;
-    if (fused_ns && fused_ns < other) return 2;
-    return by_product ? 1 : 0;
+    best *= m == 2 || m == 4 ? 0.93 : 0.85;
+    int pick = 0;
+    if (product_cycles && product < best) { best = product; pick = 1; }
+    if (fused_ns && fused_ns < best) pick = 2;
+    return pick;
 }
 
 }  // namespace iolb

@@ -102,15 +102,15 @@ def test_what_the_fused_winograd_kernel_divides_is_in_that_range(layer):
     assert facts[2] == 1 and (facts[1] == 1 or (N * per + 64) * per >= 1 << 31 or facts[0] ** 2 >= 1 << 31)
 
 
-@pytest.mark.parametrize("m,layer,route", [
-    # the product by 4 / 3 of the tile's speed and more, which a model of the tile alone sends back ...
-    (3, (8, 128, 77, 77, 304), B.ROUTE_SPLIT), (3, (23, 128, 47, 65, 336), B.ROUTE_SPLIT), (6, (4, 128, 128, 128, 176), B.ROUTE_SPLIT),
-    # ... and tiles of one wave, 1.1 - 1.2 times as fast as the product
-    (3, (8, 48, 46, 46, 80), B.ROUTE_TILE), (6, (53, 76, 81, 81, 26), B.ROUTE_TILE),
-    (4, (2, 48, 24, 24, 336), B.ROUTE_TILE),
+@pytest.mark.parametrize("m,layer", [
+    (3, (8, 128, 77, 77, 304)), (3, (23, 128, 47, 65, 336)), (6, (4, 128, 128, 128, 176)), (6, (14, 256, 104, 104, 160)),
 ])
-def test_winograd_layers_take_the_faster_way(m, layer, route):
-    assert B.iolb_route(B.make_shape(*layer, algo=B.WINO_ALGO[m]))[0] == route
+def test_winograd_layers_of_many_channels_keep_the_product(m, layer):
+    """It is 1.1 - 1.35 times as fast there as the tile, to which its modelled time sends them."""
+    N, C, H, W, K = layer
+    route, need = B.iolb_route(B.make_shape(*layer, algo=B.WINO_ALGO[m]))
+    assert route == B.ROUTE_SPLIT and need > 4 * (m + 2) ** 2 * (C + K) * N * -(-H // m) * -(-W // m)      # V and M in the workspace
+
 
 
 @pytest.mark.parametrize("m", [2, 4])
