@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <limits>
 #include <vector>
 
 namespace iolb {
@@ -88,21 +89,27 @@ static int split_resident(const SplitGeom& g)
 // Fitted on 187 layers (drawn over 9 to 512 channels, 7 x 7 to 224 x 224, batch 1 to 64, and the networks'), on the best
 // three blocks of every workgroup shape: within 7 % (2-norm).  Its picks take 1.030 times the best block timed, those of
 // split_rounds 1.072; on 266 other layers 130 picks differ, 1.064 times as fast, but seven of them 5 - 14 % slower.  Where
-// it promises 8 % over the pick of split_rounds, 76 of 366 further layers, that is 1.127 times as fast, one 7 % slower, one 3 %:
-// those leave it (5 x 5, 96 -> 256 at 27 x 27, batch 16: 82.7 -> 78.5 us; 180 -> 35 at 124 x 124, stride 2: 158 -> 122).
+// it promises 8 % over the pick of split_rounds, 355 of 2000 further layers, that is 1.118 times as fast, 11 of them 3 - 13 % slower (at
+// 12 % 4 of 214, but 1.03 - 1.05 times as fast is lost on the others; 338 -> 385 at 17 x 17, 1 x 3, 25.4 -> 27.8 us is promised 17): those
+// leave it (5 x 5, 96 -> 256 at 27 x 27, batch 16: 82.7 -> 78.5 us; 180 -> 35 at 124 x 124, stride 2: 158 -> 122).
 constexpr double PROMISE = 1.08;
-static double split_cycles(const SplitGeom& g)
+static double norm4(double a, double b) { return std::sqrt(std::sqrt((a * a) * (a * a) + (b * b) * (b * b))); }
+// limit: a result that is not below it may be any such number (the planner asks for the least of some thousand blocks, and a bound
+// without powers decides most of them: 0.69 -> 0.34 ms on a layer's first call, in the mean of 4000).
+static double split_cycles(const SplitGeom& g, double limit)
 {
     const double steps = split_steps(g), chunks = split_chunks(g);
     const double mfma = 96.0 * g.mb * g.nb, narrow = 1 + 0.8 / g.xh, items = g.ch8 * g.halo / (64.0 * g.wm * g.wn) * narrow;
     const double alone = 390.0 * g.mb * g.nb + 1520 * std::ceil(items / narrow) * narrow + chunks * (steps * (mfma + 170) + 507 * items + 1120);
-    const double shared = 1010 + 357.0 * g.mb * g.nb + chunks * (steps * std::pow(std::pow(1.13 * mfma, 4) + std::pow(g.mb * (17.2 * g.wm + 159), 4), 0.25) + 730 * items);
-    auto group = [&](double n) { return n > 0 ? std::pow(std::pow(alone, 3.13) + std::pow(n * shared, 3.13), 1 / 3.13) : 0; };
+    const double shared = 1010 + 357.0 * g.mb * g.nb + chunks * (steps * norm4(1.13 * mfma, g.mb * (17.2 * g.wm + 159)) + 730 * items);
     const int most = split_resident(g);
-    const double n = (double)g.nbk * g.nbx * g.nby * g.nbn / 256, full = std::floor(n / most);
-    const double cycles = n <= 4 * most ? full * group(most) + group(std::ceil(n - full * most)) : (n / most + 0.5) * group(most);
+    const double n = (double)g.nbk * g.nbx * g.nby * g.nbn / 256, full = std::floor(n / most), rest = std::ceil(n - full * most);
     const double bytes = 4.0 * g.N * ((double)g.C * g.H * g.W + (double)g.K * g.P * g.Q);
-    return std::pow(std::pow(cycles, 4) + std::pow(bytes / 990, 4), 0.25);
+    auto rounds = [&](auto group) { return n <= 4 * most ? full * group(most) + (rest > 0 ? group(rest) : 0) : (n / most + 0.5) * group(most); };
+    const double least = rounds([&](double w) { return std::max(alone, w * shared); });
+    if (least >= limit) return least;
+    const double cycles = rounds([&](double w) { return std::pow(std::pow(alone, 3.13) + std::pow(w * shared, 3.13), 1 / 3.13); });
+    return norm4(cycles, bytes / 990);
 }
 
 bool split_plan(SplitGeom* g, double* cycles)
@@ -139,7 +146,7 @@ bool split_plan(SplitGeom* g, double* cycles)
                         if (b * tx * ty * 2 < slots) continue;           // a smaller shape does it
                         t.tx = tx; t.ty = ty; t.b = b;
                         if (!split_derive(&t)) continue;
-                        const double r = split_rounds(t), c = split_cycles(t);
+                        const double r = split_rounds(t), c = split_cycles(t, found ? best_cycles : std::numeric_limits<double>::infinity());
                         if (!found || r < best_rounds) { best = t; best_rounds = r; }
                         if (!found || c < best_cycles) { other = t; best_cycles = c; }
                         found = true;
@@ -148,7 +155,7 @@ bool split_plan(SplitGeom* g, double* cycles)
         }
     }
     if (!found) return false;
-    const double c = split_cycles(best);
+    const double c = split_cycles(best, std::numeric_limits<double>::infinity());
     const bool leave = c > PROMISE * best_cycles;
     *g = leave ? other : best;
     *cycles = leave ? best_cycles : c;
