@@ -582,7 +582,7 @@ hipError_t launch_split_conv(const float* x, const void* wt, float* y, const Spl
 {
     // what the kernel assumes of its geometry
     if (g.b * g.tx * g.ty > 16 * g.nb * g.wn || split_lds_bytes(g, own) > 160 * 1024 || g.Kb16 != g.nbk * g.mb * g.wm ||
-        (split_chunks(g) > 1 && split_batches(g) > split_steps(g)) || g.nbuf < (split_chunks(g) > 1 ? 2 : 1) || g.nbuf > 2 || g.ch8 < 1 || g.ch8 > 8 ||
+        (split_chunks(g) > 1 && split_batches(g) > split_steps(g)) || g.nbuf < (split_chunks(g) > 1 ? 2 : 1) || g.nbuf > 2 || (g.ch8 != 1 && g.ch8 != 2 && g.ch8 != 4) ||
         4LL * g.b * g.C * g.H * g.W >= (1LL << 31) || g.cstep != (g.hwc ? 4 : 4 * g.H * g.W) || (g.vec_in && (!g.hwc || g.C % 4)))
         return hipErrorInvalidValue;
     const u32x4* w = static_cast<const u32x4*>(wt);

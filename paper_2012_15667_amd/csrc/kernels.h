@@ -65,7 +65,7 @@ struct SplitGeom {
     int pad_w;
     int b, tx, ty;             // output sub-block: b images * ty rows * tx columns, at most 16 * nb * wn pixels
     int mb, nb, wm, wn;        // wave grid wm x wn, blocks of 16 channels x 16 pixels per wave mb x nb
-    int ch8;                   // channels per chunk / 8, 1 to 8
+    int ch8;                   // channels per chunk / 8: 1, 2 or 4
     int nbx, nby, nbn, nbk;    // blocks along W_out, H_out, batch, C_out
     int esy, esx;              // staged stride: min(stride, R), min(stride, S)
     int yh, xh;                // staged rows and columns per image
