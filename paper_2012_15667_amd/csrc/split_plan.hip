@@ -165,11 +165,12 @@ bool split_plan(SplitGeom* g, double* cycles)
 // Layers of few workgroups and small kernels: a launch before the convolution takes longer (some 2.3 us of the host's time
 // and 3 us of the GPU's) than every workgroup cutting the same kernels once more, about 1 us for 2304 values.  Counted are the
 // values that it cuts: eight channels per unit whether they exist or not, four units per step.  The line lies where both are even,
-// found on 340 drawn layers of up to 20500 values: up to 5400, and 256 workgroups of those, own kernels are the faster way on all 174,
-// by 1.25 in the mean (16 -> 16 at 14 x 14, one image, 10.6 -> 8.2 us a call; 3 x 32 -> 32 at 15 x 15, 4608 values, 10.4 -> 8.5);
-// at 6144 to 6656 it is 1.0, and 0.5 - 0.8 on more than 256 workgroups (3 -> 48 at 148 x 148, batch 6, 7 x 7, stride 2: 6656
-// values, 2352 of them of channels and taps that exist, 504 workgroups, 19.4 us with a launch before it, 29.0 without).
-constexpr long long OWN_VALUES = 5400, OWN_ALL_VALUES = 256 * OWN_VALUES;
+// found on 340 drawn layers of up to 20500 values: up to 6144, and 256 workgroups of those, own kernels are the faster way by 1.23 in
+// the mean on 202, none below 0.99 (16 -> 16 at 14 x 14, one image, 10.6 -> 8.2 us a call; 3 x 32 -> 32 at 15 x 15, 4608 values,
+// 10.4 -> 8.5); at 6656 it is 0.96 - 1.07, at 7680 0.91 - 0.96, and 0.5 - 0.8 on more than 256 workgroups (3 -> 48 at 148 x 148, batch 6,
+// 7 x 7, stride 2: 6656 values, 2352 of them of channels and taps that exist, 504 workgroups, 19.4 us with a launch before it,
+// 29.0 without).
+constexpr long long OWN_VALUES = 6144, OWN_ALL_VALUES = 256 * OWN_VALUES;
 bool split_own(const SplitGeom& g)
 {
     bool shape = false;

@@ -94,11 +94,12 @@ def test_kernels_reach_their_steps_for_every_window(gpu, taps, C, K):
     assert np.array_equal(yt, y.transpose(0, 1, 3, 2))
 
 
-# N, C, H, W, K, R, S, stride, pad of layers whose workgroups prepare their own kernels, up to 5400 values each: few and many
+# N, C, H, W, K, R, S, stride, pad of layers whose workgroups prepare their own kernels, up to 6144 values each: few and many
 # channels and workgroups, kernels beyond the last block ...
 OWN_LAYERS = [
     (3, 32, 15, 15, 32, 3, 3, 1, 1), (2, 30, 14, 15, 17, 3, 3, 2, 1), (3, 9, 12, 13, 100, 4, 4, 1, 2), (40, 16, 14, 14, 16, 3, 3, 1, 1),
     (400, 16, 14, 14, 16, 3, 3, 1, 1), (7, 16, 114, 114, 16, 3, 3, 1, 1), (2, 3, 100, 100, 16, 5, 5, 1, 1), (2, 5, 100, 100, 15, 6, 6, 1, 1),
+    (7, 21, 9, 9, 306, 3, 1, 1, 0),
 ]
 # ... and of layers beyond that, in values or in workgroups
 NOT_OWN_LAYERS = [
