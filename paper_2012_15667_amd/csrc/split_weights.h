@@ -47,9 +47,9 @@ __device__ __forceinline__ void store_parts(u32x4* to, const unsigned short (&p)
 }
 
 // Row `row` (the same in every lane of a wave) of L g for eight channels, g[3][3] one after the other from `from` on.  A branch per
-// row, two channels' loads at a time: with every row computed and one selected, all channels' loads ahead, the launch that the input
-// transform shares took 254 registers in F(3 x 3), 210 in F(4 x 4) (now 66 and 61 - 112, as without), which left two waves per SIMD
-// (382 -> 132 at 121 x 121, batch 9, F(3 x 3): 633 us, now 579).
+// row: with every row computed and one selected, the launch that the input transform shares took 254 registers in F(3 x 3), 210 in
+// F(4 x 4) (now 66 and 61 - 112, as without), which left two waves per SIMD (382 -> 132 at 121 x 121, batch 9, F(3 x 3): 633 us,
+// now 579).
 template <int M>
 __device__ __forceinline__ void kernel_row(int row, const float* from, float (&lg)[8][3])
 {
@@ -62,7 +62,6 @@ __device__ __forceinline__ void kernel_row(int row, const float* from, float (&l
                 static_for<3>([&](auto i) { accumulate<M, UseL, decltype(r)::value, decltype(i)::value>(u, first, from[c * 9 + i * 3 + j]); });
                 lg[c][j] = u;
             });
-            if constexpr (decltype(c)::value % 2) __builtin_amdgcn_sched_barrier(0);
         });
     });
 }

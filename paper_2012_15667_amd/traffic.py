@@ -28,14 +28,15 @@ OUT_DIR = os.path.join("rocprof_out", "traffic")
 STEPS = 2
 
 # (layer, algo, path): path "tuned" (the call without a tile) / "bound" for direct; "fused"/"unfused" for Winograd, and
-# "tuned" for thin layers and for those whose call without a tile takes the split product
+# "tuned" for thin layers and for those whose call without a tile takes a split way
 DEFAULT_RUNS = (
     [(l, "direct", "tuned") for l in ("cfg3", "cfg5a", "cfg5b", "cfg5c", "cfg5d")] +
     [("cfg2", "wino2", p) for p in ("unfused", "fused")] +
     [("cfg4", "wino4", p) for p in ("unfused", "fused")] +
     [("cfg5a", a, "tuned") for a in ("wino2", "wino4")] +
     [(l, a, p) for l in ("cfg5b", "cfg5c", "cfg5d") for a in ("wino2", "wino4") for p in ("unfused", "fused")] +
-    [("cfg5c", "wino4", "tuned"), ("cfg5d", "wino2", "tuned"), ("cfg5d", "wino4", "tuned")]
+    [("cfg2", "wino2", "tuned"), ("cfg4", "wino4", "tuned")] +
+    [(l, a, "tuned") for l in ("cfg5b", "cfg5c", "cfg5d") for a in ("wino2", "wino4")]
 )
 
 
