@@ -279,13 +279,23 @@ __host__ __device__ inline unsigned wino_split_range(const WinoSplitGeom& g, int
 {
     return 4u * ((unsigned)images * (unsigned)(g.C * g.H * g.W) + (unsigned)(g.pad * (g.W + 1)));
 }
+// How a lane's own columns are read: one by one; M at a time, those beyond the image's last column (in the last sub-domain of
+// a row) zeroed afterwards; M at a time, all inside.  Images of so few rows that the last ones of every window lie below them are read
+// one by one, too.  (Loads and stores of M floats need no more than the alignment of one; each float is checked against the buffer's
+// range, the scalar offset included: measured with loads across the end of a range inside a larger buffer.)
+enum { WINO_COLS_SINGLE, WINO_COLS_CUT, WINO_COLS_WHOLE };
+inline int wino_split_cols(const WinoSplitGeom& g)
+{
+    return g.pad != 1 || g.H + g.pad < g.m + 2 ? WINO_COLS_SINGLE : g.W % g.m ? WINO_COLS_CUT : WINO_COLS_WHOLE;
+}
 // The scalar byte offset at which channel c0 (and the next three) and row r of the windows are loaded.  Never beyond the range of
 // even one image: the hardware checks a lane's own offset against the range less this one, which must not wrap.  Rows that lie
-// below every window's image (r >= H + pad) and channels that do not exist are masked in every lane.
+// below every window's image (r >= H + pad; only read one by one) and channels that do not exist are masked in every lane.
+template <int COLS>
 __host__ __device__ inline int wino_split_offset(const WinoSplitGeom& g, int c0, int r)
 {
-    const int last = g.H + g.pad - 1;
-    return 4 * ((c0 < g.C ? c0 : 0) * (g.H * g.W) + (r < last ? r : last) * g.W);
+    const int last = g.H + g.pad - 1, row = COLS == WINO_COLS_SINGLE && r > last ? last : r;
+    return 4 * ((c0 < g.C ? c0 : 0) * (g.H * g.W) + row * g.W);
 }
 // The kernels in three parts, from w[K][C][3][3] or (given) from a caller's U[plane][C rounded up to 16][K to 32].
 hipError_t launch_wino_split_weights(const float* w, bool given, void* wt, const WinoSplitGeom& g, hipStream_t st);

@@ -65,10 +65,6 @@ __device__ __forceinline__ void output_transform_1d(const float (&v)[M + 2], flo
 // Whether this lane's bit of a wave-uniform mask is set: a select reads the mask as it is.
 __device__ __forceinline__ bool by_lane(unsigned long long mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
 
-// How a lane's own columns are read: one by one; M at a time, those beyond the image's last column (in the last
-// sub-domain of a row) zeroed afterwards; M at a time, all inside.
-enum { COLS_SINGLE, COLS_CUT, COLS_WHOLE };
-
 template <int M, int TB, int Z, int COLS>
 __global__ void __launch_bounds__(512, M == 2 && TB == 32 && Z == 32 ? 4 : 2)
 wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restrict__ y, WinoSplitGeom g, WinoSplitDivisors dv)
@@ -131,7 +127,7 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
 #pragma unroll
         for (int i = 0; i < n; ++i) rowok[i] = lanes(t < g.tiles && h0 + i >= 0 && h0 + i < g.H);
 #pragma unroll
-        for (int j = 0; j < M; ++j) colok[j] = COLS == COLS_WHOLE ? ~0ull : lanes(w0 + 1 + j >= 0 && w0 + 1 + j < g.W);
+        for (int j = 0; j < M; ++j) colok[j] = COLS == WINO_COLS_WHOLE ? ~0ull : lanes(w0 + 1 + j >= 0 && w0 + 1 + j < g.W);
         // (pad >= 1: beyond the first and the last sub-domain of a row there are zeros)
         left = lanes(tj > 0); right = lanes(tj + 1 < g.tw);
         const int e16 = lane & 15, we = w0 + (e16 == 0 ? 0 : M + 1);
@@ -148,14 +144,14 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
             const unsigned long long have = __builtin_amdgcn_ballot_w64(16 * s + cl + 4 * i < g.C);
             static_range<0, n>([&](auto rc) {
                 constexpr int r = decltype(rc)::value;
-                const int so = wino_split_offset(g, c0, r);
+                const int so = wino_split_offset<COLS>(g, c0, r);
                 const unsigned long long row = have & rowok[r];
                 wx[i][r][0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rx, (int)(by_lane(row & edge) ? eoff : OUTSIDE), so, 0));
-                if constexpr (COLS != COLS_SINGLE && M == 4) {
+                if constexpr (COLS != WINO_COLS_SINGLE && M == 4) {
                     const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)((by_lane(row) ? xoff : OUTSIDE) + 4), so, 0);
 #pragma unroll
                     for (int j = 0; j < 4; ++j) wx[i][r][j + 1] = __uint_as_float(q[j]);
-                } else if constexpr (COLS != COLS_SINGLE) {
+                } else if constexpr (COLS != WINO_COLS_SINGLE) {
                     const u32x2 q = __builtin_amdgcn_raw_buffer_load_b64(rx, (int)((by_lane(row) ? xoff : OUTSIDE) + 4), so, 0);
 #pragma unroll
                     for (int j = 0; j < 2; ++j) wx[i][r][j + 1] = __uint_as_float(q[j]);
@@ -172,7 +168,7 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
     auto transform = [&](Windows& wx, char* vb) {
         static_range<0, WIN>([&](auto ic) {
             constexpr int i = decltype(ic)::value;
-            if constexpr (COLS == COLS_CUT)
+            if constexpr (COLS == WINO_COLS_CUT)
 #pragma unroll
                 for (int r = 0; r < n; ++r)
 #pragma unroll
@@ -549,14 +545,12 @@ hipError_t launch_wino_split(const float* x, const void* wt, float* y, const Win
     // what the kernel assumes of its geometry
     if (!wino_split_fits(g)) return hipErrorInvalidValue;
     const u32x4* u = static_cast<const u32x4*>(wt);
-    // (loads and stores of M floats need no more than the alignment of one; each float is checked against the buffer's range, the
-    // scalar offset included: measured with loads across the end of a range inside a larger buffer)
-    const int cols = g.pad != 1 ? COLS_SINGLE : g.W % g.m ? COLS_CUT : COLS_WHOLE;
-#define IOLB_CASE(M_, T_, Z_)                                                            \
-    if (g.m == M_ && g.tb == T_ && g.z == Z_)                                            \
-        return cols == COLS_WHOLE ? launch_one<M_, T_, Z_, COLS_WHOLE>(x, u, y, g, st)   \
-               : cols == COLS_CUT ? launch_one<M_, T_, Z_, COLS_CUT>(x, u, y, g, st)     \
-                                  : launch_one<M_, T_, Z_, COLS_SINGLE>(x, u, y, g, st);
+    const int cols = wino_split_cols(g);
+#define IOLB_CASE(M_, T_, Z_)                                                                 \
+    if (g.m == M_ && g.tb == T_ && g.z == Z_)                                                 \
+        return cols == WINO_COLS_WHOLE ? launch_one<M_, T_, Z_, WINO_COLS_WHOLE>(x, u, y, g, st) \
+               : cols == WINO_COLS_CUT ? launch_one<M_, T_, Z_, WINO_COLS_CUT>(x, u, y, g, st)   \
+                                       : launch_one<M_, T_, Z_, WINO_COLS_SINGLE>(x, u, y, g, st);
     IOLB_WINO_SPLIT_SHAPES(IOLB_CASE)
 #undef IOLB_CASE
     return hipErrorInvalidValue;

@@ -34,10 +34,13 @@ extern "C" long long wino_split_beyond_range(int N, int C, int H, int W, int K, 
 {
     WinoSplitGeom g;
     if (!plan_wino_split(N, C, H, W, K, m, pad, &g)) return -1;
+    const bool single = wino_split_cols(g) == WINO_COLS_SINGLE;
     long long most = 0;
     for (int c0 = 0; c0 < 16 * (g.chunks + 2); c0 += 4)                   // (stages are loaded up to two ahead)
-        for (int r = 0; r < m + 2; ++r)
-            if (wino_split_offset(g, c0, r) > most) most = wino_split_offset(g, c0, r);
+        for (int r = 0; r < m + 2; ++r) {
+            const int at = single ? wino_split_offset<WINO_COLS_SINGLE>(g, c0, r) : wino_split_offset<WINO_COLS_WHOLE>(g, c0, r);
+            if (at > most) most = at;
+        }
     return most - (long long)wino_split_range(g, 1);
 }
 
