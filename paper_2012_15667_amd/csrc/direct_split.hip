@@ -229,7 +229,11 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
         for (int i = 0; i < AHEAD; ++i) load_weights(a[i], i);
     }
     __builtin_amdgcn_sched_barrier(0);
-    load_batch(1, 0);                                       // (of a chunk that does not exist: zeros, no access)
+    // (Asked for in any case, as zeros where there is no second chunk, these loads let the first steps wait for fewer of them; that cost
+    // layers of one chunk 1 - 4 %, and inputs in single floats with channels innermost up to 6: 411 -> 22 at 129 x 90, stride 2, batch 43
+    // 706 us, 753 so; 17 -> 249 at 58 x 58 57.0 and 58.4.  Over 2500 drawn layers the branch is 0.7 % the better one, 3 - 4 % the worse
+    // on 20; only the narrow blocks that read four channels at a time, 0.5 % the other way, go without.)
+    if (nchunks > 1 || (VEC && MB * NB <= 2)) load_batch(1, 0);
     __builtin_amdgcn_sched_barrier(0);
 
     // LDS byte offset of unit (tap, channel group) relative to a pixel's window corner
