@@ -13,8 +13,8 @@
 // channels of its own, so through LDS they would only be written and read once more.
 //
 // What bounds it: the matrix cores, at the clock the chip's power allows (3x3, C = K = 256, 56 x 56, batch 64, whole
-// call: 1900 us on the fp32 instructions -> 889 - 934 us over several boxes = 266 - 253 TFLOP/s of fp32 products;
-// register-only bf16 loop 323; matrix cores busy 0.75 of the cycles).  The rest: LDS reads (56 % of the cycles) and weight
+// call: 1900 us on the fp32 instructions, 934 - 953 on three cards = 254 - 249 TFLOP/s of fp32 products; register-only
+// bf16 loop 323; matrix cores busy 0.76 of the cycles).  The rest: LDS reads (56 % of the cycles) and weight
 // loads (16 bytes per clock and unit through the L2).  Measured on that layer: blocks of 32 x 112 per wave 1041 us (kernel),
 // 64 x 64 with the weights read by two waves 1137, eight waves per workgroup 1046, chunks of 16 channels 1123; row pitch in
 // LDS without the padding of split_derive 1068 against 1024; input loads whose descriptor or offset the compiler kept in

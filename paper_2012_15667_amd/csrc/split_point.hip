@@ -9,11 +9,12 @@
 // eight vector instructions per 32-cycle matrix instruction 1433 against 1631 TFLOP/s).  wt is not declared restrict on
 // purpose: loads of memory known not to change were moved down past the barrier to their use, which undid the prefetch.
 //
-// What bounds it: large products the rate at which a compute unit takes operands in, about 20 bytes per clock (6.05 GB
-// through the L2s in 1.15 M clocks on the product below; a block of z channels by npix pixels needs 192 z + 128 npix bytes
-// per 32 channels), and the power the vector work of the split costs in clock: 16 planes of 512 x 12544 x 512 (F(2x2))
-// 545 us = 193 TFLOP/s with 256 x 64 blocks (fp32 instructions: 840 us; with single stores 580), larger blocks were slower.
-// Small ones the latency of their steps.  1 x 1, 768 -> 192 at 17 x 17, batch 64: 66 -> 45 - 47 us whole call.
+// What bounds it: of large products nothing found yet. Matrix cores are busy 0.57 of the cycles; a compute unit takes in 20 bytes
+// of operands per clock (6.05 GB through the L2s in 1.15 M clocks on the product below; a block of z channels by npix pixels
+// needs 192 z + 128 npix bytes per 32 channels), while other kernels take 24 to 36 through the same L2s; the vector work of the split
+// costs clock. 16 planes of 512 x 12544 x 512 (F(2x2)) 545 us = 193 TFLOP/s with 256 x 64 blocks (fp32 instructions: 840 us; with
+// single stores 580), larger blocks were slower.  Small ones the latency of their steps.  1 x 1, 768 -> 192 at 17 x 17, batch 64,
+// whole call: 66 us on the fp32 instructions, 46.4 with single stores, 43.5.
 // Measured and taken back: the weights of chunk t + 2 loaded before the inputs of chunk t + 3, so that these have two steps
 // to arrive (the same product 545 -> 573 us).
 //

@@ -9,9 +9,17 @@
 //
 // What bounds it: kernel parts from the L2 (F(4 x 4), 32 x 64: 221 KB per stage for 3456 clocks of matrix work at 62 bytes per
 // clock and unit; left out, 520 -> 350 us), the vector work of transform and cut (left out, 317), inputs (left out, 395) and
-// first loads and stores of a round (436); each alone hides behind the others only in part.  Whole calls, fp32 way -> this:
+// first loads and stores of a round (436); each alone hides behind the others only in part.  Matrix cores are busy 0.24 - 0.25 of the
+// cycles there, 0.34 - 0.39 on F(2 x 2), 64 x 64 (counters of whole layers).  Whole calls, fp32 way -> this:
 // F(4 x 4) 128 -> 128 at 112 x 112, batch 64 859 -> 582 us (102 TFLOP/s of the planes' products), 256 -> 256 at 14 x 14 87 ->
-// 60, F(2 x 2) 256 -> 256 at 56 x 56 1104 -> 736, 64 -> 64 at 28 x 28, batch 8 19.8 -> 13.6.
+// 59, F(2 x 2) 256 -> 256 at 56 x 56 1104 -> 736, 64 -> 64 at 28 x 28, batch 8 19.8 -> 13.2.
+// Registers: F(4 x 4), 32 x 64 has 256 and spills 5 (24 bytes a lane; 14 and 44 where columns are read one by one), the other blocks
+// none.
+// A block with a sum that is not finite is taken again by all its waves, stage by stage without overlap: one NaN adds the time of one
+// such block (256 -> 256 at 14 x 14 64 -> 155 us, 64 -> 64 at 28 x 28, batch 8 14.9 -> 25.5, where the fp32 kernels took 94 and 20.5 whatever the
+// values), all NaN takes 2.1 - 2.8 times as long (128 -> 128 at 112 x 112 600 -> 1690 us, fp32 kernel 860).  With the next stage's inputs
+// and the next unit's kernels on their way that was 133, 24.1 and 1427, but one or two more registers were spilled and large finite layers took 0.5 %
+// longer: not kept.
 // Measured and not kept: four waves of twice the planes each; transform and loads spread between the matrix instructions
 // of every wave in place of the two phases below (F(4 x 4), 256 -> 256 at 56 x 56 521 -> 666: 26 registers spilled);
 // differences of the cut by v_dot2 (equal).
