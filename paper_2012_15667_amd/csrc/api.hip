@@ -288,7 +288,7 @@ int run_split(const float* x, const float* w, float* y, const iolb_shape& s, con
             rc = ensure_workspace(dev, align256(ch.weight_bytes), &wt);
             if (rc != IOLB_OK) return rc;
         }
-        IOLB_HIP(iolb::launch_split_weights(w, wt, s.K, s.C, s.R, s.S, point ? 4 : ch.conv.ch8, point ? ch.point.Kb16 : ch.conv.Kb16, transposed, st));
+        IOLB_HIP(iolb::launch_split_weights(w, wt, s.K, s.C, s.R, s.S, point ? 4 : ch.conv.ch8, point ? ch.point.Kb16 : ch.conv.Kb16, point ? 3 : ch.conv.parts, transposed, st));
         kernels = wt;
     }
     const bool aligned = ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(y)) & 15) == 0;
@@ -300,7 +300,7 @@ int run_split(const float* x, const float* w, float* y, const iolb_shape& s, con
     } else {
         iolb::SplitGeom g = ch.conv;
         if (!aligned) g.vec_in = g.vec_out = 0;
-        IOLB_HIP(iolb::launch_split_conv(x, kernels, y, g, own, transposed, st));
+        IOLB_HIP(iolb::launch_split_conv(x, kernels, w, y, g, own, transposed, st));
     }
     timer.stop(st);
     return IOLB_OK;

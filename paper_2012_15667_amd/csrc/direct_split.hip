@@ -1,21 +1,27 @@
-// Direct convolution on the bf16 matrix cores at fp32 precision (operands in three parts, split_mfma.h), dataflow of
-// Sec. 5.2: a workgroup keeps the partial sums of b images * ty rows * tx columns by 16 MB WM output channels in
+// Direct convolution on the 16-bit matrix cores at fp32 precision (operands in two fp16 parts, of few channels and small layers in
+// three of bf16: split_mfma.h), dataflow of Sec. 5.2: a workgroup keeps the partial sums of b images * ty rows * tx columns by 16 MB WM output channels in
 // registers for the whole channel loop and writes them once.
 //
 // The channel loop runs in chunks of 8, 16 or 32 channels (8 ch8).  Of a chunk the input tile is in LDS, per pixel and
-// group of eight channels 48 bytes (three parts of eight bf16), in two buffers: while one chunk is multiplied the next
+// group of eight channels 16 bytes per part (two parts in planes of their own, three one after the other), in two buffers: while one chunk is multiplied the next
 // is loaded to registers, split and written to the other buffer, a batch of items per matrix step, with one barrier
-// per chunk.  A matrix step contracts four units of (tap, eight channels) in one v_mfma_f32_16x16x32_bf16 per product
+// per chunk.  A matrix step contracts four units of (tap, eight channels) in one v_mfma_f32_16x16x32 per product
 // of parts: the four lane groups of the instruction read the window pixel of their own unit, whose LDS offset comes
-// from a table, so one kernel serves every kernel extent, stride and padding.  Sixteen lanes read 16 bytes each 48 bytes
-// apart: every LDS bank once.  With a stride the columns are stored by residue class, so that this holds there too.
+// from a table, so one kernel serves every kernel extent, stride and padding.  Sixteen lanes read 16 bytes each 16 or 48
+// bytes apart: every LDS bank once.  With a stride the columns are stored by residue class, so that this holds there too.
 // The weights (split once per call, in the order of the steps) go from the L2 straight into registers: each wave has
 // channels of its own, so through LDS they would only be written and read once more.
 //
-// What bounds it: the matrix cores, at the clock the chip's power allows (3x3, C = K = 256, 56 x 56, batch 64, whole
-// call: 1900 us on the fp32 instructions, 934 - 953 on three cards = 254 - 249 TFLOP/s of fp32 products; register-only
-// bf16 loop 323; matrix cores busy 0.76 of the cycles).  The rest: LDS reads (56 % of the cycles) and weight
-// loads (16 bytes per clock and unit through the L2).  Measured on that layer: blocks of 32 x 112 per wave 1041 us (kernel),
+// Two parts: the scales (split_mfma.h) are of a kernel, and of an image in a block, from a sample of its first loads and 64 values
+// spread over the channels, known before the first of them is split.  What the split finds of each pixel's largest value is kept in
+// LDS; after the last step every wave looks through it for pixels that are too small for the scale, and takes its block again on the
+// fp32 instructions for their images.  That and one barrier more cost 1.2 us of a workgroup's life.  Measured whole calls, three
+// bf16 parts / two fp16 parts: 3x3, 256 -> 256 at 56 x 56, batch 64 927 / 605 us (392 TFLOP/s of fp32 products; register-only 646),
+// 64 -> 64 at 56 x 56, batch 32 50 / 38, 128 -> 256 at 28 x 28, stride 2 57 / 42, 5x5, 96 -> 256 at 27 x 27, batch 16, channels
+// innermost 76 / 58; 80 drawn layers 1.17 in the mean.
+// What bounds it: the matrix cores are busy 0.6 of the cycles; the rest is LDS reads (85 bytes per clock and unit), weight loads (24
+// through the L2) and the first loads and last stores of a round.  Twice the items per batch of staging: equal.
+// With three parts (whole call on the fp32 instructions 1900 us, 934 - 953) measured on that layer: blocks of 32 x 112 per wave 1041 us (kernel),
 // 64 x 64 with the weights read by two waves 1137, eight waves per workgroup 1046, chunks of 16 channels 1123; row pitch in
 // LDS without the padding of split_derive 1068 against 1024; input loads whose descriptor or offset the compiler kept in
 // vector registers (a loop over the lanes per load) 1073 against 1041.  Sums apart per step (APART) for all layers: error
@@ -40,10 +46,6 @@ namespace iolb {
 
 namespace {
 
-// Position of the input tile that staged row / column `i` is taken from, relative to the tile's first: with a
-// stride beyond the kernel extent only the rows and columns that some window covers are staged.
-__device__ __forceinline__ int staged_offset(int i, int est, int stride) { return est == stride ? i : i / est * stride + i % est; }
-
 // Buffer of a block's images, first one n0: loads beyond them return zero.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t image_buffer(const float* x, const SplitGeom& g, int n0)
 {
@@ -56,7 +58,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t image_buffer(const float* x, c
                                              (int)__builtin_amdgcn_readfirstlane(img * (unsigned)images), 0x00020000);
 }
 
-template <int MB, int NB, int WM, int WN, bool VEC, bool APART, bool OWN>
+template <int MB, int NB, int WM, int WN, bool VEC, bool APART, bool OWN, bool TWO>
 __global__ void __launch_bounds__(64 * WM * WN, 2)
 split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitGeom g, SplitDivisors dv, SplitOwn own)
 {
@@ -64,6 +66,8 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
     char* const lds = reinterpret_cast<char*>(lds16);
     constexpr int T = 64 * WM * WN;
     constexpr int IB = SPLIT_BATCH;
+    static_assert(!TWO || (!APART && !OWN), "two fp16 parts, or three of bf16");
+    constexpr int PARTS = TWO ? 2 : 3, PX = split_pixel_bytes(PARTS), WBLOCK = 64 * PARTS;
     // read here, once: loads of their own in the branches of a loop with diverging exits, which the compiler would make of
     // later uses, would count as values that differ between lanes
     const int CH8 = g.ch8, C = g.C, cstep = g.cstep;
@@ -106,15 +110,22 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
     const int RS = g.R * g.S;
     const int steps = (RS * CH8 + 3) >> 2;                  // matrix steps of a chunk: four units each
     const int items = CH8 * g.halo;
-    const int im_bytes = g.yh * g.rowb, group_bytes = g.b * im_bytes, buf_bytes = CH8 * group_bytes;
-    int* const koff = reinterpret_cast<int*>(lds + g.nbuf * buf_bytes);          // [4 * steps]
+    const int im_bytes = g.yh * g.rowb, plane = g.b * im_bytes, group_bytes = split_planes(PARTS) * plane, buf_bytes = CH8 * group_bytes;
+    // (two parts: l lies `plane` bytes after h)
+    float* const kback = reinterpret_cast<float*>(lds + g.nbuf * buf_bytes);     // TWO: what undoes the scales of the block's kernels
+    int* const koff = reinterpret_cast<int*>(kback + (TWO ? 16 * MB * WM : 0));  // [4 * steps]
     uint2* const table = reinterpret_cast<uint2*>(koff + ((4 * steps + 1) & ~1));      // [items]
+    // TWO: the largest value of each staged pixel over the channels, scaled; of each image in the sample (one image: of each wave);
+    // whether an image is taken again
+    unsigned* const most = reinterpret_cast<unsigned*>(table + items);
+    unsigned* const sample = most + g.halo;
+    unsigned* const lost = sample + (g.b > 1 ? g.b : WM * WN);
 
     const int nchunks = __builtin_amdgcn_readfirstlane((C + 8 * CH8 - 1) / (8 * CH8));
     // weights of matrix step t: [t][16-channel block][part][lane]
     const int kb16 = kb * (MB * WM) + wm_i * MB;
-    const size_t wstep = (size_t)g.Kb16 * 192;              // 16-byte pieces per step
-    const u32x4* wp = wt + (size_t)kb16 * 192 + lane;
+    const size_t wstep = (size_t)g.Kb16 * WBLOCK;           // 16-byte pieces per step
+    const u32x4* wp = wt + (size_t)kb16 * WBLOCK + lane;
 
     const __amdgpu_buffer_rsrc_t rs = image_buffer(x, g, n0);
 
@@ -124,15 +135,17 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
         const int per = g.yh * g.rowp;
         const int c8 = dv.halo.of(it), hp = it - c8 * g.halo, im = dv.per.of(hp), rem = hp - im * per;
         const int iy = dv.rowp.of(rem), ix = rem - iy * g.rowp, ix_col = dv.esx.of(ix);
-        const int gy = gy0 + staged_offset(iy, g.esy, g.stride), gx = gx0 + staged_offset(ix, g.esx, g.stride);
+        // with a stride beyond the kernel's extent only the rows and columns that some window covers are staged
+        const int gy = gy0 + iy + dv.esy.of(iy) * (g.stride - g.esy), gx = gx0 + ix + ix_col * (g.stride - g.esx);
         uint2 e;
-        e.x = OUTSIDE;
-        if (n0 + im < g.N && ix < g.xh && gy >= 0 && gy < g.H && gx >= 0 && gx < g.W)
-            e.x = g.hwc ? 4u * (unsigned)(((im * g.H + gy) * g.W + gx) * C + c8 * 8)
-                      : 4u * (unsigned)(((im * C + c8 * 8) * g.H + gy) * g.W + gx);
-        e.y = (unsigned)(c8 * group_bytes + im * im_bytes + iy * g.rowb + 48 * ((ix - ix_col * g.esx) * g.colw + ix_col));
-        // c8 in the low bits of the LDS offset (a multiple of 16)
+        // (no branches: five of these stand between a workgroup's start and its last first load)
+        const bool inside = (n0 + im < g.N) & (ix < g.xh) & ((unsigned)gy < (unsigned)g.H) & ((unsigned)gx < (unsigned)g.W);
+        const int pixel = gy * g.W + gx;
+        e.x = inside ? 4u * (unsigned)(g.hwc ? (im * g.H * g.W + pixel) * C + c8 * 8 : (im * C + c8 * 8) * g.H * g.W + pixel) : OUTSIDE;
+        e.y = (unsigned)(c8 * group_bytes + im * im_bytes + iy * g.rowb + PX * ((ix - ix_col * g.esx) * g.colw + ix_col));
+        // c8 in the low bits of the LDS offset (a multiple of 16, below 2^18); of two parts the image above, later its scale, a float
         e.y |= (unsigned)c8;
+        if constexpr (TWO) e.y |= (unsigned)im << 23;
         return e;
     };
 
@@ -157,7 +170,31 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
             }
         }
     };
-    auto write_item = [&](const float (&v)[8], unsigned dst, char* buf) {
+    static_assert(16 * NB * WN < 511, "images of a block, in nine bits beside no item");
+    auto largest = [&]() {                                  // of a block's only image
+        unsigned m = sample[0];
+#pragma unroll
+        for (int i = 1; i < WM * WN; ++i) m = sample[i] > m ? sample[i] : m;
+        return m;
+    };
+    unsigned only = 0;                                      // its scale
+    auto with_scale = [&](unsigned dst) {
+        unsigned scale = only;
+        if (g.b > 1) scale = half_scale_bits(sample[dst == ~0u ? 0 : dst >> 23]);
+        return dst == ~0u ? dst : (dst & 0x7fffffu) | scale;
+    };
+    auto write_item = [&](const float (&v)[8], unsigned dst, char* buf, int it) {
+        if constexpr (TWO) {
+            u32x4 h, l;
+            const float m = half_eight(v, __uint_as_float(dst & 0x7f800000u), h, l);
+            if (dst != ~0u) {
+                char* d = buf + (dst & 0x7ffff0u);
+                *reinterpret_cast<u32x4*>(d) = h;
+                *reinterpret_cast<u32x4*>(d + plane) = l;
+                atomicMax(most + (it - (int)(dst & 15) * g.halo), __float_as_uint(m));
+            }
+            return;
+        }
         u32x4 h, m, l;
         split_eight(v, h, m, l);
         if (dst != ~0u) {
@@ -180,9 +217,9 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
             load_item(xv[i], e, ch);
         }
     };
-    auto write_batch = [&](char* buf) {
+    auto write_batch = [&](char* buf, int b) {
 #pragma unroll
-        for (int i = 0; i < IB; ++i) write_item(xv[i], xdst[i], buf);
+        for (int i = 0; i < IB; ++i) write_item(xv[i], xdst[i], buf, (b * IB + i) * T + tid);
     };
     auto barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
 
@@ -207,22 +244,46 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
 #pragma unroll
     for (int f = 0; f < FIRST; ++f) place_batch(fv[f], fdst[f], f);
     __builtin_amdgcn_sched_barrier(0);
+    // Two parts: for the sample that sets the inputs' scales, beside the first batches, some values spread over the channels, of the
+    // pixels of the first items, of several images over all of them; what undoes the kernels' scales.
+    float spread = 0.f, my_kback = 0.f;
+    unsigned spread_image = 0;
+    if constexpr (TWO) {
+        static_assert(16 * MB * WM <= T, "one kernel per thread");
+        if (g.b > 1 || wave == 0) {
+            uint2 e = {OUTSIDE, 0};
+            if (g.b > 1) e = place(tid * items / T);
+            else if (tid < items) e = table[tid];
+            const int c = ((tid & 15) * nchunks >> 4) * 8 * CH8 + (tid >> 4 & 7);
+            spread_image = e.y >> 23;
+            const bool exists = e.x != OUTSIDE && c + (int)(e.y & 15) * 8 < C;
+            spread = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, exists ? (int)(e.x + (unsigned)c * (unsigned)cstep) : (int)OUTSIDE, 0, 0));
+        }
+        for (int i = tid; i < g.halo; i += T) most[i] = 0;
+        if (g.b > 1) {
+            for (int i = tid; i < 2 * g.b; i += T) sample[i] = 0;                // (lost follows)
+        } else if (tid == 0) {
+            lost[0] = 0;
+        }
+        if (tid < 16 * MB * WM) my_kback = reinterpret_cast<const float*>(wt + (size_t)nchunks * steps * wstep)[kb * (16 * MB * WM) + tid];
+        __builtin_amdgcn_sched_barrier(0);
+    }
     u32x4* const parts = reinterpret_cast<u32x4*>(lds + split_tables_bytes(g));     // a workgroup's own kernels (OWN)
     // Weights of the next AHEAD steps are on their way while a step multiplies: a step of a small block is shorter than
     // the latency of its loads.  A step issues first the weights, then the inputs.
     constexpr int AHEAD = OWN ? 1 : MB == 1 ? 3 : 2;
-    u32x4 a[AHEAD + 1][MB * 3];
+    u32x4 a[AHEAD + 1][MB * PARTS];
     const int total = nchunks * steps;
-    auto load_weights = [&](u32x4 (&f)[MB * 3], int t) {
+    auto load_weights = [&](u32x4 (&f)[MB * PARTS], int t) {
         if constexpr (OWN) {
             const u32x4* from = parts + ((t < total ? t : 0) * (MB * WM) + wm_i * MB) * 192 + lane;
 #pragma unroll
-            for (int j = 0; j < MB * 3; ++j) f[j] = from[j * 64];
+            for (int j = 0; j < MB * PARTS; ++j) f[j] = from[j * 64];
             return;
         }
         if (t > 0 && t < total) wp += wstep;                // past the last step: read again, not used
 #pragma unroll
-        for (int j = 0; j < MB * 3; ++j) f[j] = wp[j * 64];
+        for (int j = 0; j < MB * PARTS; ++j) f[j] = wp[j * 64];
     };
     if constexpr (!OWN) {
 #pragma unroll
@@ -242,7 +303,7 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
         int off = 0;
         if (tap < RS) {
             const int r = dv.S.of(tap), s = tap - r * g.S, s_col = dv.esx.of(s);
-            off = c8 * group_bytes + r * g.rowb + 48 * ((s - s_col * g.esx) * g.colw + s_col);
+            off = c8 * group_bytes + r * g.rowb + PX * ((s - s_col * g.esx) * g.colw + s_col);
         }
         koff[u] = off;
     }
@@ -289,18 +350,64 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
         const int slot = (wn_i * NB + nb) * 16 + l16;
         const int pix = slot < npix ? slot : npix - 1;
         const int im = dv.txy.of(pix), rem = pix - im * txy, py = dv.tx.of(rem), px = rem - py * g.tx;
-        pbase[nb] = im * im_bytes + py * g.esy * g.rowb + 48 * px;
+        pbase[nb] = im * im_bytes + py * g.esy * g.rowb + PX * px;
     }
 
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (TWO) {
+        // scales of the images, from the first batches and the spread values
+        unsigned mine[FIRST][IB];
+#pragma unroll
+        for (int f = 0; f < FIRST; ++f)
+#pragma unroll
+            for (int i = 0; i < IB; ++i) mine[f][i] = largest_of(fv[f][i]);
+        unsigned all = finite_bits(spread);
+        if (g.b > 1) {
+            barrier();
+            if (all) atomicMax(sample + spread_image, all);
+#pragma unroll
+            for (int f = 0; f < FIRST; ++f)
+#pragma unroll
+                for (int i = 0; i < IB; ++i)
+                    if (mine[f][i]) atomicMax(sample + (fdst[f][i] >> 23), mine[f][i]);      // (an item that does not exist is zeros)
+        } else {
+#pragma unroll
+            for (int f = 0; f < FIRST; ++f)
+#pragma unroll
+                for (int i = 0; i < IB; ++i) all = mine[f][i] > all ? mine[f][i] : all;
+            all = wave_max(all);
+            if (lane == 0) sample[wave] = all;
+        }
+        barrier();
+        only = half_scale_bits(largest());
+#pragma unroll
+        for (int f = 0; f < FIRST; ++f)
+#pragma unroll
+            for (int i = 0; i < IB; ++i) {
+                fdst[f][i] = with_scale(fdst[f][i]);
+                if (fdst[f][i] != ~0u) table[(f * IB + i) * T + tid].y = fdst[f][i];
+            }
+#pragma unroll
+        for (int i = 0; i < IB; ++i) xdst[i] = fdst[0][i];                       // (those of the second chunk's first batch, if there is one)
+    }
 #pragma unroll
     for (int f = 0; f < FIRST; ++f)
 #pragma unroll
-        for (int i = 0; i < IB; ++i) write_item(fv[f][i], fdst[f][i], lds);
+        for (int i = 0; i < IB; ++i) write_item(fv[f][i], fdst[f][i], lds, (f * IB + i) * T + tid);
     for (int b = FIRST; b < batches; ++b) {
         place_batch(fv[0], fdst[0], b);
 #pragma unroll
-        for (int i = 0; i < IB; ++i) write_item(fv[0][i], fdst[0][i], lds);
+        for (int i = 0; i < IB; ++i) {
+            const int it = (b * IB + i) * T + tid;
+            if constexpr (TWO) {
+                fdst[0][i] = with_scale(fdst[0][i]);
+                if (fdst[0][i] != ~0u) table[it].y = fdst[0][i];
+            }
+            write_item(fv[0][i], fdst[0][i], lds, it);
+        }
+    }
+    if constexpr (TWO) {
+        if (tid < 16 * MB * WM) kback[tid] = my_kback;
     }
     barrier();
     if constexpr (OWN) load_weights(a[0], 0);
@@ -311,17 +418,17 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    u32x4 bf[2][3];
-    auto fetch = [&](u32x4 (&f)[3], const char* from) {
+    u32x4 bf[2][PARTS];
+    auto fetch = [&](u32x4 (&f)[PARTS], const char* from) {
 #pragma unroll
-        for (int p = 0; p < 3; ++p) f[p] = *reinterpret_cast<const u32x4*>(from + 16 * p);
+        for (int p = 0; p < PARTS; ++p) f[p] = *reinterpret_cast<const u32x4*>(from + (TWO ? plane : 16) * p);
     };
     int ch = 0, k = 0, t = 0;
     int ko = koff[grp];
     fetch(bf[0], lds + ko + pbase[0]);
     // One matrix step: four units (tap, channel group) for every block of the wave.  The pixels come from LDS one block
     // ahead, across steps too.
-    auto step = [&](const u32x4 (&w0)[MB * 3], u32x4 (&wn)[MB * 3]) {
+    auto step = [&](const u32x4 (&w0)[MB * PARTS], u32x4 (&wn)[MB * PARTS]) {
         const bool chunk_end = k + 1 == steps;
         load_weights(wn, t + AHEAD);
         const char* bp = lds + split_buffer(ch, g.nbuf) * buf_bytes;
@@ -330,16 +437,21 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
             constexpr int nb = decltype(nb_c)::value;
             if constexpr (nb + 1 < NB) fetch(bf[(nb + 1) & 1], bp + ko + pbase[nb + 1]);
             else                       fetch(bf[(nb + 1) & 1], bp + kn + pbase[0]);
-            // the six products of parts that reach fp32 precision, smallest first
+            // the products of parts that reach fp32 precision, smallest first: six, of two parts three
             constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
             f32x4 sum[MB];
 #pragma unroll
-            for (int q = 0; q < 6; ++q)
+            for (int q = TWO ? 3 : 0; q < 6; ++q)
 #pragma unroll
                 for (int mb = 0; mb < MB; ++mb) {
+                    if constexpr (TWO) {
+                        acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                            __builtin_bit_cast(f16x8, w0[mb * PARTS + PA[q]]), __builtin_bit_cast(f16x8, bf[nb & 1][PB[q]]), acc[mb][nb], 0, 0, 0);
+                        continue;
+                    }
                     f32x4& to = APART ? sum[mb] : acc[mb][nb];
                     to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                        __builtin_bit_cast(bf16x8, w0[mb * 3 + PA[q]]), __builtin_bit_cast(bf16x8, bf[nb & 1][PB[q]]),
+                        __builtin_bit_cast(bf16x8, w0[mb * PARTS + PA[q]]), __builtin_bit_cast(bf16x8, bf[nb & 1][PB[q]]),
                         APART && q == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : to, 0, 0, 0);
                 }
             if constexpr (APART) {
@@ -352,9 +464,9 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
         // Loads come back in the order they were issued.  Where the paths with and without input loads meet, the
         // compiler would have to assume the worst and wait for every load at the next use of a weight: the two paths
         // stay apart until each has waited for the weights of the next step.
-        constexpr int LATER = MB * 3 * (AHEAD - 1), LOADS = (VEC ? 2 : 8) * IB;
+        constexpr int LATER = MB * PARTS * (AHEAD - 1), LOADS = (VEC ? 2 : 8) * IB;
         if (k < batches && ch + 1 < nchunks) {
-            write_batch(lds + split_buffer(ch + 1, g.nbuf) * buf_bytes);
+            write_batch(lds + split_buffer(ch + 1, g.nbuf) * buf_bytes, k);
             const bool more = k + 1 < batches;
             load_batch(more ? ch + 1 : ch + 2, more ? k + 1 : 0);
             static_range<HALF, NB>(block);
@@ -365,7 +477,7 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
         }
         if constexpr (NB & 1) {
 #pragma unroll
-            for (int p = 0; p < 3; ++p) bf[0][p] = bf[1][p];
+            for (int p = 0; p < PARTS; ++p) bf[0][p] = bf[1][p];
         }
         ko = kn;
         ++k;
@@ -390,23 +502,63 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
     // pixel l16.  Sums that are not finite are marked.
     const size_t PQ = (size_t)g.P * g.Q;
     unsigned long long again = 0;
+    // what undoes the scales (one image in a block: its own)
+    float back = 1.f;
+    f32x4 kb4[MB];
+    bool image_lost = false, finite = false;
+    if constexpr (TWO) {
+        // (most waves have no sum that is not finite: 0 times it is NaN, and so is the sum of those)
+        f32x4 z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) z[i] = __builtin_fmaf(acc[mb][nb][i], 0.f, z[i]);
+        back = half_unscale(half_scale_bits(largest()));
+        // Images with a pixel whose channels are all too small for their scale, and not all zeros.  (Every wave looks through all
+        // pixels: what it marks it needs no barrier to see.)
+        bool small = false;
+        for (int i = lane; i < g.halo; i += 64) {
+            const unsigned m = most[i];
+            if (m - 1 < __float_as_uint(HALF_LEAST) - 1) {
+                lost[dv.per.of(i)] = 1;
+                small = true;
+            }
+        }
+        finite = __builtin_amdgcn_ballot_w64(small || z[0] + z[1] + z[2] + z[3] != 0.f) == 0;
+        image_lost = lost[0] != 0;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) kb4[mb] = *reinterpret_cast<const f32x4*>(kback + (wm_i * MB + mb) * 16 + 4 * (lane >> 4));
+    }
     static_assert(MB * NB * 4 <= 64, "one mark per output");
-    auto write_y = [&](auto marked_c) {
-        constexpr bool MARKED = decltype(marked_c)::value;  // the second time: marked outputs only
+    // once without looking at them where all are finite; or once, marking those that are not, and then those marked
+    enum { PLAIN, MARKING, MARKED_ONLY };
+    auto write_y = [&](auto mode_c) {
+        constexpr int MODE = decltype(mode_c)::value;
+        constexpr bool MARKED = MODE == MARKED_ONLY;
         const int l16 = opaque(lane) & 15, grp = opaque(lane) >> 4;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
             const int slot = (wn_i * NB + nb) * 16 + l16;
             const int im = dv.txy.of(slot), rem = slot - im * txy, row = dv.tx.of(rem), py = y0 + row, px = x0 + rem - row * g.tx;
             if (slot >= npix || n0 + im >= g.N || py >= g.P || px >= g.Q) continue;
+            if constexpr (TWO && !MARKED) {
+                if (g.b > 1) {
+                    back = half_unscale(half_scale_bits(sample[im]));
+                    if (MODE == MARKING) image_lost = lost[im] != 0;
+                }
+                if (MODE == MARKING && image_lost) again |= ((1ull << (4 * MB - 1) << 1) - 1) << (nb * MB * 4);
+            }
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) {
                 const int k0 = (kb16 + mb) * 16 + 4 * grp, bit = (nb * MB + mb) * 4;
                 if constexpr (!MARKED) {
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        if (!(__builtin_fabsf(acc[mb][nb][i]) <= 3.402823466e38f)) again |= 1ull << (bit + i);
-                        acc[mb][nb][i] *= SPLIT_UNSCALE;
+                        if (MODE == MARKING && !(__builtin_fabsf(acc[mb][nb][i]) <= 3.402823466e38f)) again |= 1ull << (bit + i);
+                        if constexpr (TWO) acc[mb][nb][i] = acc[mb][nb][i] * back * kb4[mb][i];
+                        else               acc[mb][nb][i] *= SPLIT_UNSCALE;
                     }
                 }
                 if (g.hwc) {
@@ -427,7 +579,11 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
             }
         }
     };
-    write_y(std::false_type{});
+    if (finite) {
+        write_y(std::integral_constant<int, PLAIN>{});
+        return;
+    }
+    write_y(std::integral_constant<int, MARKING>{});
     if (__builtin_amdgcn_ballot_w64(again != 0) == 0) return;
 
     // A wave with a marked output takes its whole block again on the fp32 matrix instructions, which hold their sums in
@@ -466,7 +622,18 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
         load_v(v[0], cy[0], cx[0], ci[0]);
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
-            kept_eight(wq[mb * 192], wq[mb * 192 + 64], wq[mb * 192 + 128], wv[mb]);
+            if constexpr (TWO) {
+                // the kernels as the caller holds them: their two parts are not always all of them
+                const int k0 = (kb16 + mb) * 16 + col16, tw = own.transposed ? col * g.R + r : tap;
+                const float* from = own.w + ((size_t)(k0 < g.K ? k0 : 0) * C + c0) * RS + tw;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const bool exists = tap < RS && k0 < g.K && c0 + j < C;
+                    wv[mb][j] = exists ? from[(size_t)j * RS] : 0.f;
+                }
+            } else {
+                kept_eight(wq[mb * 192], wq[mb * 192 + 64], wq[mb * 192 + 128], wv[mb]);
+            }
             if constexpr (MB > 2) __builtin_amdgcn_sched_barrier(0);       // all pieces at once would not fit the registers
         }
         static_range<0, NB>([&](auto nb_c) {
@@ -480,7 +647,7 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
             __builtin_amdgcn_sched_barrier(0);
         });
     }
-    write_y(std::true_type{});
+    write_y(std::integral_constant<int, MARKED_ONLY>{});
 }
 
 // w[K][C][R][S] -> the operands of the matrix steps, [chunk][step][16-channel block][part][lane][8 bf16].  A workgroup per 16
@@ -489,11 +656,13 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
 // LDS pass and a store one after the other (gathered in single floats, 256 -> 256 kernels of 3 x 3 took 7.4 us, now 5.7; 7 x
 // 7 and 11 x 11 on three channels 62 -> 58 and 49.2 -> 46.8 whole calls).
 constexpr int SLICE = 16, ROW = 8 * SLICE;                 // taps of a slice; floats of a kernel in LDS
+template <bool TWO>
 __global__ void __launch_bounds__(256)
 split_weights_kernel(const float* __restrict__ w, u32x4* __restrict__ wt, int K, int C, int R, int S, int ch8, int steps, int Kb16,
                      int octets, int all_octets, int slices, int transposed)
 {
     constexpr int PITCH = ROW + 1, ROWS = 16, MINE = ROWS / 4;
+    __shared__ unsigned scales[ROWS];                       // TWO: scale of each kernel, lowest bit: too small for it here
     __shared__ float rows[ROWS * PITCH];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kb = blockIdx.x % Kb16, rest = blockIdx.x / Kb16, first = rest / slices * octets, t0 = rest % slices * SLICE;
@@ -501,7 +670,17 @@ split_weights_kernel(const float* __restrict__ w, u32x4* __restrict__ wt, int K,
     const int ts = slices > 1 ? SLICE : RS;                 // taps of a channel in LDS
     const int channels = C - first * 8 < octets * 8 ? C - first * 8 : octets * 8;
     const long long from0 = (long long)k0 * C * RS + (long long)first * 8 * RS + t0;
-    float v[2][MINE];
+    float v[2][MINE], some[MINE];
+    if constexpr (TWO) {
+        const int row = C * RS, at = (int)((long long)row * (lane >> 2) >> 4) + (lane & 3);
+#pragma unroll
+        for (int j = 0; j < MINE; ++j) {
+            const int k = k0 + wave * MINE + j;
+            const bool exists = k < K && at < row;
+            some[j] = w[exists ? (size_t)k * row + at : 0];
+            some[j] = exists ? some[j] : 0.f;
+        }
+    }
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
         const int e = lane + 64 * c, row = slices > 1 ? e / SLICE * RS + e % SLICE : e;
@@ -515,6 +694,23 @@ split_weights_kernel(const float* __restrict__ w, u32x4* __restrict__ wt, int K,
             v[c][j] = exists ? v[c][j] : 0.f;
         }
     }
+    if constexpr (TWO) {
+        // A kernel's scale follows from 64 of its values, 16 runs of four spread over it: the same in each of its workgroups.
+        float* const kback = reinterpret_cast<float*>(wt + (size_t)steps * (all_octets / ch8) * Kb16 * 128);
+#pragma unroll
+        for (int j = 0; j < MINE; ++j) {
+            const int k = wave * MINE + j;
+            unsigned here = __float_as_uint(__builtin_fabsf(v[0][j])), there = __float_as_uint(__builtin_fabsf(v[1][j]));
+            here = here > there ? here : there;
+            const unsigned scale = half_scale_bits(wave_max(finite_bits(some[j])));
+            here = wave_max(here);
+            if (lane == 0) {
+                // (of fewer than 32 values here some are all small now and then: not judged)
+                scales[k] = scale + (here != 0 && channels * ts >= 32 && __uint_as_float(here) * __uint_as_float(scale) < HALF_LEAST);
+                if (first == 0 && t0 == 0) kback[k0 + k] = half_unscale(scale);
+            }
+        }
+    }
 #pragma unroll
     for (int c = 0; c < 2; ++c)
 #pragma unroll
@@ -523,6 +719,23 @@ split_weights_kernel(const float* __restrict__ w, u32x4* __restrict__ wt, int K,
     const int k = tid & 15, mine = slices > 1 ? SLICE : taps, t = t0 + (tid >> 4) % mine, o = (tid >> 4) / mine, octet = first + o;
     if (o >= octets || octet >= all_octets || t >= taps) return;
     const float* from = rows + k * PITCH + o * 8 * ts + t - t0;
+    if constexpr (TWO) {
+        // (a kernel too small for its scale: NaN in place of its parts here, which every sum of it shows)
+        const float scale = __uint_as_float(scales[k] & ~1u);
+        const unsigned poison = scales[k] & 1 ? 0x7e007e00u : 0u;
+        float g8[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) g8[j] = t < RS ? from[j * ts] : 0.f;
+        u32x4 h, l;
+        half_eight(g8, scale, h, l);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) h[j] |= poison;
+        const int tap = transposed && t < RS ? t % R * S + t / R : t, unit = tap * ch8 + octet % ch8;
+        u32x4* to = wt + ((size_t)(octet / ch8 * steps + (unit >> 2)) * Kb16 + kb) * 128 + (unit & 3) * 16 + k;
+        to[0] = h;
+        to[64] = l;
+        return;
+    }
     unsigned short p[3][8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) split_kept(t < RS ? from[j * ts] : 0.f, p[0][j], p[1][j], p[2][j]);
@@ -531,10 +744,10 @@ split_weights_kernel(const float* __restrict__ w, u32x4* __restrict__ wt, int K,
     store_parts(wt + ((size_t)(octet / ch8 * steps + (unit >> 2)) * Kb16 + kb) * 192 + (unit & 3) * 16 + k, p);
 }
 
-template <int MB, int NB, int WM, int WN, bool VEC, bool APART, bool OWN>
+template <int MB, int NB, int WM, int WN, bool VEC, bool APART, bool OWN, bool TWO>
 hipError_t launch_one(const float* x, const u32x4* wt, float* y, const SplitGeom& g, const SplitDivisors& dv, const SplitOwn& own, hipStream_t st)
 {
-    auto kern = split_conv_kernel<MB, NB, WM, WN, VEC, APART, OWN>;
+    auto kern = split_conv_kernel<MB, NB, WM, WN, VEC, APART, OWN, TWO>;
     const size_t shm = split_lds_bytes(g, OWN);
     if (shm > 64 * 1024) {
         const hipError_t e = allow_large_lds((const void*)kern);
@@ -546,14 +759,14 @@ hipError_t launch_one(const float* x, const u32x4* wt, float* y, const SplitGeom
 
 }  // namespace
 
-hipError_t launch_split_weights(const float* w, void* wt, int K, int C, int R, int S, int ch8, int Kb16, bool transposed, hipStream_t st)
+hipError_t launch_split_weights(const float* w, void* wt, int K, int C, int R, int S, int ch8, int Kb16, int parts, bool transposed, hipStream_t st)
 {
     if (ch8 != 1 && ch8 != 2 && ch8 != 4) return hipErrorInvalidValue;
     const int steps = (R * S * ch8 + 3) / 4, octets = (C + 8 * ch8 - 1) / (8 * ch8) * ch8, taps = 4 * steps / ch8;
     const int per = taps < SLICE ? SLICE / taps : 1, slices = (taps + SLICE - 1) / SLICE;
     const long long blocks = (octets + per - 1LL) / per * slices * Kb16;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(split_weights_kernel, dim3((unsigned)blocks), dim3(256), 0, st, w, (u32x4*)wt, K, C, R, S, ch8, steps, Kb16, per, octets,
+    hipLaunchKernelGGL(parts == 2 ? split_weights_kernel<true> : split_weights_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, st, w, (u32x4*)wt, K, C, R, S, ch8, steps, Kb16, per, octets,
                        slices, transposed ? 1 : 0);
     return hipGetLastError();
 }
@@ -562,38 +775,45 @@ hipError_t launch_split_weights(const float* w, void* wt, int K, int C, int R, i
 // sum, which is then rounded once per step and not six times.  Such layers ran on plain FMAs or short fp32 chains
 // before, which round less than six bf16 products per step would; they are not bound by the matrix cores.
 template <bool VEC>
-static hipError_t launch_shape(const float* x, const u32x4* wt, float* y, const SplitGeom& g, const SplitDivisors& dv, const SplitOwn* own, hipStream_t st)
+static hipError_t launch_shape(const float* x, const u32x4* wt, float* y, const SplitGeom& g, const SplitDivisors& dv, bool own, const SplitOwn& o, hipStream_t st)
 {
+#define IOLB_SPLIT_IS(M_, N_, A_, B_) (g.mb == M_ && g.nb == N_ && g.wm == A_ && g.wn == B_)
+#define IOLB_SPLIT_TWO_CASE(M_, N_, A_, B_) \
+    if (g.parts == 2 && IOLB_SPLIT_IS(M_, N_, A_, B_)) return launch_one<M_, N_, A_, B_, VEC, false, false, true>(x, wt, y, g, dv, o, st);
 #define IOLB_SPLIT_CASE(M_, N_, A_, B_) \
-    if (!own && g.mb == M_ && g.nb == N_ && g.wm == A_ && g.wn == B_) return launch_one<M_, N_, A_, B_, VEC, APART, false>(x, wt, y, g, dv, SplitOwn(), st);
+    if (g.parts == 3 && !own && IOLB_SPLIT_IS(M_, N_, A_, B_)) return launch_one<M_, N_, A_, B_, VEC, APART, false, false>(x, wt, y, g, dv, o, st);
 #define IOLB_SPLIT_OWN_CASE(M_, N_, A_, B_) \
-    if (own && g.mb == M_ && g.nb == N_ && g.wm == A_ && g.wn == B_) return launch_one<M_, N_, A_, B_, VEC, APART, true>(x, wt, y, g, dv, *own, st);
+    if (own && IOLB_SPLIT_IS(M_, N_, A_, B_)) return launch_one<M_, N_, A_, B_, VEC, APART, true, false>(x, wt, y, g, dv, o, st);
     if (g.ch8 == 1) {
         constexpr bool APART = true;
         IOLB_SPLIT_FEW_SHAPES(IOLB_SPLIT_CASE)
         IOLB_SPLIT_OWN_FEW_SHAPES(IOLB_SPLIT_OWN_CASE)
     } else {
         constexpr bool APART = false;
-        IOLB_SPLIT_SHAPES(IOLB_SPLIT_CASE)
+        IOLB_SPLIT_SHAPES(IOLB_SPLIT_TWO_CASE)
+        IOLB_SPLIT_SMALL_SHAPES(IOLB_SPLIT_CASE)
         IOLB_SPLIT_OWN_SHAPES(IOLB_SPLIT_OWN_CASE)
     }
 #undef IOLB_SPLIT_OWN_CASE
 #undef IOLB_SPLIT_CASE
+#undef IOLB_SPLIT_TWO_CASE
+#undef IOLB_SPLIT_IS
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_split_conv(const float* x, const void* wt, float* y, const SplitGeom& g, bool own, bool transposed, hipStream_t st)
+hipError_t launch_split_conv(const float* x, const void* wt, const float* w_given, float* y, const SplitGeom& g, bool own, bool transposed, hipStream_t st)
 {
     // what the kernel assumes of its geometry
     if (g.b * g.tx * g.ty > 16 * g.nb * g.wn || split_lds_bytes(g, own) > 160 * 1024 || g.Kb16 != g.nbk * g.mb * g.wm ||
         (split_chunks(g) > 1 && split_batches(g) > split_steps(g)) || g.nbuf < (split_chunks(g) > 1 ? 2 : 1) || g.nbuf > 2 || (g.ch8 != 1 && g.ch8 != 2 && g.ch8 != 4) ||
-        4LL * g.b * g.C * g.H * g.W >= (1LL << 31) || g.cstep != (g.hwc ? 4 : 4 * g.H * g.W) || (g.vec_in && (!g.hwc || g.C % 4)))
+        4LL * g.b * g.C * g.H * g.W >= (1LL << 31) || g.cstep != (g.hwc ? 4 : 4 * g.H * g.W) || (g.vec_in && (!g.hwc || g.C % 4)) || (g.parts != 2 && g.parts != 3) || (g.parts == 2 && (g.ch8 == 1 || own)))
         return hipErrorInvalidValue;
     const u32x4* w = static_cast<const u32x4*>(wt);
     SplitDivisors dv;
     SplitOwn o;
     if (!split_divisors(g, transposed, &dv, &o)) return hipErrorInvalidValue;
-    return g.vec_in ? launch_shape<true>(x, w, y, g, dv, own ? &o : nullptr, st) : launch_shape<false>(x, w, y, g, dv, own ? &o : nullptr, st);
+    o.w = w_given;
+    return g.vec_in ? launch_shape<true>(x, w, y, g, dv, own, o, st) : launch_shape<false>(x, w, y, g, dv, own, o, st);
 }
 
 }  // namespace iolb

@@ -77,6 +77,7 @@ struct SplitGeom {
     int k_outer;               // blocks of one channel block are neighbours, not those of the same pixels
     int hwc, vec_in, vec_out;  // channels innermost; with 16-byte loads / stores of four channels
     int cstep;                 // bytes from an input channel to the next
+    int parts;                 // of an operand: 3 of bf16, 2 of fp16
 };
 // Division by a number known on the host: exact for n * d < 2^31.  (The compiler's division takes some 40 instructions.)
 struct Divisor {
@@ -87,7 +88,7 @@ struct Divisor {
 };
 // ... by the extents that the kernel divides by
 struct SplitDivisors {
-    Divisor ch8, halo, per, rowp, S, esx, txy, tx;          // per: yh * rowp
+    Divisor ch8, halo, per, rowp, S, esx, esy, txy, tx;     // per: yh * rowp
     Divisor nbk, pixel_blocks, nbx, nby;                    // of workgroup ids, where small says that they are exact
     int small;
 };
@@ -95,6 +96,7 @@ struct SplitDivisors {
 struct SplitOwn {
     Divisor steps, row;
     int transposed;
+    const float* w;            // the kernels as the caller holds them, for blocks that are taken again
 };
 constexpr int SPLIT_BATCH = 2;          // (pixel, 8 channels) items of the input tile that a thread stages at once
 // The workgroup shapes that exist: blocks per wave (channels, pixels), wave grid (channels, pixels).  Of two with the same
@@ -103,8 +105,12 @@ constexpr int SPLIT_BATCH = 2;          // (pixel, 8 channels) items of the inpu
     X(1, 2, 4, 1) X(1, 4, 4, 1) X(1, 8, 4, 1) X(2, 2, 4, 1) X(2, 4, 4, 1) X(2, 5, 4, 1) X(2, 7, 4, 1) X(2, 8, 4, 1) \
     X(3, 2, 4, 1) X(3, 4, 4, 1) X(4, 2, 4, 1)                                                                       \
     X(1, 2, 2, 2) X(1, 4, 2, 2) X(1, 7, 2, 2) X(1, 8, 2, 2) X(2, 5, 2, 2) X(2, 7, 2, 2) X(2, 8, 2, 2)             \
-    X(3, 4, 2, 2)                                                                                                   \
+    X(3, 4, 2, 2) X(3, 5, 4, 1) X(3, 5, 2, 2)                                                                       \
     X(1, 1, 1, 4) X(1, 2, 1, 4) X(1, 4, 1, 4) X(1, 7, 1, 4) X(2, 7, 1, 4) X(3, 4, 1, 4)
+// ... and those of them that small layers and short sums run in three parts
+#define IOLB_SPLIT_SMALL_SHAPES(X) \
+    X(1, 2, 4, 1) X(1, 4, 4, 1) X(2, 2, 4, 1) X(2, 4, 4, 1) X(2, 7, 4, 1) X(1, 2, 2, 2) X(1, 4, 2, 2) X(1, 8, 2, 2) X(1, 1, 1, 4)  \
+    X(1, 2, 1, 4) X(1, 4, 1, 4) X(2, 8, 4, 1) X(3, 4, 4, 1) X(3, 4, 2, 2)
 // ... and those for layers of at most eight channels (ch8 = 1)
 #define IOLB_SPLIT_FEW_SHAPES(X) \
     X(1, 2, 4, 1) X(1, 4, 4, 1) X(1, 2, 2, 2) X(1, 4, 2, 2) X(2, 4, 2, 2) X(1, 2, 1, 4) X(1, 4, 1, 4) X(2, 4, 1, 4)
@@ -118,11 +124,15 @@ inline int split_batches(const SplitGeom& g)
     const int per = 64 * g.wm * g.wn * SPLIT_BATCH;
     return (g.ch8 * g.halo + per - 1) / per;
 }
-// buffers of the input tile, offsets of the matrix steps' units, table of the input tile's elements, whole 16 bytes
+// bytes in LDS of a pixel's eight channels: three parts one after the other; two in planes of their own, sixteen each
+__host__ __device__ constexpr int split_pixel_bytes(int parts) { return parts == 2 ? 16 : 48; }
+__host__ __device__ constexpr int split_planes(int parts) { return parts == 2 ? 2 : 1; }
+// buffers of the input tile, offsets of the matrix steps' units, table of the input tile's elements, whole 16 bytes; of two parts
+// also the kernels' scales, the pixels' largest values, the images' and whether they are taken again
 __host__ __device__ inline int split_tables_bytes(const SplitGeom& g)
 {
-    const int steps = (g.R * g.S * g.ch8 + 3) / 4;
-    return (g.nbuf * g.ch8 * g.b * g.yh * g.rowb + 4 * ((4 * steps + 1) & ~1) + 8 * g.ch8 * g.halo + 15) & ~15;
+    const int steps = (g.R * g.S * g.ch8 + 3) / 4, more = g.parts == 2 ? 64 * g.mb * g.wm + 4 * g.halo + 4 * g.b + 4 * (g.b > 4 ? g.b : 4) : 0;
+    return (g.nbuf * g.ch8 * split_planes(g.parts) * g.b * g.yh * g.rowb + 4 * ((4 * steps + 1) & ~1) + 8 * g.ch8 * g.halo + more + 15) & ~15;
 }
 // ... and the parts and rows of a workgroup's own kernels
 inline long long split_own_bytes(const SplitGeom& g)
@@ -131,7 +141,9 @@ inline long long split_own_bytes(const SplitGeom& g)
 }
 inline long long split_lds_bytes(const SplitGeom& g, bool own = false)
 {
-    const long long tables = ((long long)g.nbuf * g.ch8 * g.b * g.yh * g.rowb + 4 * ((4 * split_steps(g) + 1) & ~1) + 8LL * g.ch8 * g.halo + 15) & ~15LL;
+    const long long more = g.parts == 2 ? 64LL * g.mb * g.wm + 4LL * g.halo + 4 * g.b + 4 * (g.b > 4 ? g.b : 4) : 0;
+    const long long tables = ((long long)g.nbuf * g.ch8 * split_planes(g.parts) * g.b * g.yh * g.rowb + 4 * ((4 * split_steps(g) + 1) & ~1) +
+                              8LL * g.ch8 * g.halo + more + 15) & ~15LL;
     return tables + (own ? split_own_bytes(g) : 0);
 }
 // What the kernel divides by.  Divided are items, units and pixels of a block (what is in LDS per item and unit bounds them by 2^15,
@@ -141,20 +153,22 @@ inline bool split_divisors(const SplitGeom& g, bool transposed, SplitDivisors* d
     if ((long long)g.ch8 * g.halo > 32768 || split_steps(g) * 4LL > 32768 || g.S > 32768) return false;
     const unsigned pixel_blocks = (unsigned)(g.nbx * g.nby * g.nbn);
     const bool small = (long long)pixel_blocks * g.nbk <= 32768;
-    *dv = {Divisor(g.ch8), Divisor(g.halo), Divisor(g.yh * g.rowp), Divisor(g.rowp), Divisor(g.S), Divisor(g.esx), Divisor(g.tx * g.ty),
+    *dv = {Divisor(g.ch8), Divisor(g.halo), Divisor(g.yh * g.rowp), Divisor(g.rowp), Divisor(g.S), Divisor(g.esx), Divisor(g.esy), Divisor(g.tx * g.ty),
            Divisor(g.tx), Divisor(g.nbk), Divisor(pixel_blocks), Divisor(g.nbx), Divisor(g.nby), small};
-    *own = {Divisor(split_steps(g)), Divisor(g.C * g.R * g.S), transposed ? 1 : 0};
+    *own = {Divisor(split_steps(g)), Divisor(g.C * g.R * g.S), transposed ? 1 : 0, nullptr};
     return true;
 }
 // The input-tile buffer of a chunk: never one that split_lds_bytes does not count.
 __host__ __device__ constexpr int split_buffer(int chunk, int nbuf) { return chunk & (nbuf - 1); }
 static_assert(split_buffer(0, 1) == 0 && split_buffer(1, 1) == 0 && split_buffer(0, 2) == 0 && split_buffer(1, 2) == 1 && split_buffer(2, 2) == 0,
               "one buffer or two in turn");
+// Room for the kernels, of which two parts with their exponents use less.  (What conv_direct_noalloc has room for follows from it.)
 inline long long split_weight_bytes(const SplitGeom& g) { return (long long)split_chunks(g) * split_steps(g) * g.Kb16 * 3072; }
-// Kernels in three parts in the order of the matrix steps, written from w[K][C][R][S] (transposed: w[K][C][S][R]).
-hipError_t launch_split_weights(const float* w, void* wt, int K, int C, int R, int S, int ch8, int Kb16, bool transposed, hipStream_t st);
+// Kernels in two or three parts in the order of the matrix steps, written from w[K][C][R][S] (transposed: w[K][C][S][R]); of two parts
+// what undoes the scales of 16 Kb16 kernels follows.
+hipError_t launch_split_weights(const float* w, void* wt, int K, int C, int R, int S, int ch8, int Kb16, int parts, bool transposed, hipStream_t st);
 // (own: the kernels themselves, transposed as above, in place of wt)
-hipError_t launch_split_conv(const float* x, const void* wt, float* y, const SplitGeom& g, bool own, bool transposed, hipStream_t st);
+hipError_t launch_split_conv(const float* x, const void* wt, const float* w, float* y, const SplitGeom& g, bool own, bool transposed, hipStream_t st);
 
 // 1 x 1 layers and the Winograd product on the same matrix cores (split_point.hip): per group of images that share
 // kernels (all images of a layer; one transformed plane), y[K][HW] = w[K][C] x[C][HW] over the group's pixels.

@@ -119,6 +119,87 @@ __device__ __forceinline__ void kept_eight(const u32x4& h, const u32x4& m, const
     }
 }
 
+// ---- two fp16 parts -----------------------------------------------------------------------------
+// An operand in two fp16 parts, 2^e v = h + l (11 significant bits each, rounded to nearest: what is left is at most one unit of
+// the 24th bit), its products as three: l h, h l, h h; l l, at most 2^-22 of the product, is left out.  Half the matrix work of
+// three bf16 parts at a smaller error, since a running sum is rounded half as often (against 64 bits, as above, three bf16 / two fp16
+// parts: n = 576 3.6e-7 / 2.7e-7, 1152 5.0e-7 / 3.7e-7, 2304 7.2e-7 / 5.2e-7); single products 0.8 * 2^-24 in the mean.  The instruction
+// takes denormal fp16 operands as they are and rounds each sum once, to nearest even (measured bit by bit).
+//   fp16 has 5 bits of exponent, so e follows the data: a sample's largest value goes to [2^8, 2^9).  Seven bits are left above it;
+// a value beyond them gives infinite or NaN parts, sums that show it, and the output is computed again in plain fp32.  Below 2^-2 parts
+// lose bits to the smallest denormal, 2^-24: an operand is off by up to 2^-25 then, which is nothing beside a larger operand of
+// the same sum.  So a group of operands that enter the same sums together (a pixel's channels, a kernel's taps and channels) has to
+// hold at least one of 2^-2, or only zeros; where one does not, its outputs are computed again, too.  That is slow, and what networks
+// compute does not come near it: single values 128 times, or whole pixels a thousandth of, what a sample of some thousand values has
+// as its largest.
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+constexpr int HALF_TOP = 9;                                  // sample below 2^9
+constexpr float HALF_LEAST = 0.25f;                          // least largest value of a group
+// (operands are scaled down by at most 2^23, so that none that is not denormal vanishes; up by what a float holds)
+constexpr int HALF_DOWN = -23, HALF_UP = 126;
+
+// Bits of |v|; those of what is not finite come after all others.
+__device__ __forceinline__ unsigned magnitude(float v) { return __float_as_uint(v) & 0x7fffffffu; }
+// The same, 0 in place of what is not finite.
+__device__ __forceinline__ unsigned finite_bits(float v)
+{
+    const unsigned u = magnitude(v);
+    return u < 0x7f800000u ? u : 0u;
+}
+// 2^e for a sample whose largest value has these bits, as that of a float and as it is; a sample of zeros counts as one up to 1.
+__device__ __forceinline__ unsigned half_scale_bits(unsigned largest)
+{
+    const int e = HALF_TOP + 126 - (int)(largest >> 23);
+    const int kept = e < HALF_DOWN ? HALF_DOWN : e > HALF_UP ? HALF_UP : e;
+    return (unsigned)(127 + (largest == 0 ? HALF_TOP - 1 : kept)) << 23;
+}
+__device__ __forceinline__ float half_unscale(unsigned scale_bits) { return __uint_as_float((254u << 23) - scale_bits); }
+// The largest magnitude of eight values, 0 where one of them is not finite.
+__device__ __forceinline__ unsigned largest_of(const float (&v)[8])
+{
+    unsigned m = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) m = magnitude(v[j]) > m ? magnitude(v[j]) : m;
+    return m < 0x7f800000u ? m : 0u;
+}
+// The largest of a wave's values; every lane takes part.
+__device__ __forceinline__ unsigned wave_max(unsigned v)
+{
+    auto take = [&](unsigned o) { v = o > v ? o : v; };
+    take(__builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false));             // row_shr:1, 2, 4, 8: a row's last lane has the row's
+    take(__builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false));
+    take(__builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false));
+    take(__builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false));
+    take(__builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false));             // row_bcast:15, 31
+    take(__builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false));
+    return __builtin_amdgcn_readlane(v, 63);
+}
+// Two values, scaled already.
+__device__ __forceinline__ void half_pair(float a, float b, unsigned& h, unsigned& l)
+{
+    const f16x2 hv = {(_Float16)a, (_Float16)b};
+    h = __builtin_bit_cast(unsigned, hv);
+    asm("" : "+v"(h));                                       // (not converted a second time)
+    const f16x2 hb = __builtin_bit_cast(f16x2, h);
+    const f16x2 lv = {(_Float16)(a - (float)hb[0]), (_Float16)(b - (float)hb[1])};
+    l = __builtin_bit_cast(unsigned, lv);
+}
+// Eight, scaled here; returns the largest of them, scaled.
+__device__ __forceinline__ float half_eight(const float (&v)[8], float scale, u32x4& h, u32x4& l)
+{
+    float most = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const float a = v[2 * j] * scale, b = v[2 * j + 1] * scale;
+        unsigned hj, lj;
+        half_pair(a, b, hj, lj);
+        h[j] = hj; l[j] = lj;
+        most = __builtin_fmaxf(__builtin_fmaxf(most, __builtin_fabsf(a)), __builtin_fabsf(b));
+    }
+    return most;
+}
+
 }  // namespace iolb
 
 #endif

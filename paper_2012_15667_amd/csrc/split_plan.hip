@@ -39,12 +39,13 @@ bool split_derive(SplitGeom* g)
     // Sixteen lanes read 16 bytes each of consecutive pixels, 48 bytes apart: that covers every LDS bank once.  A row
     // pitch that is congruent to the bytes of a tile row modulo the 256 bytes of the banks keeps it so across a row
     // end; taken where it does not cost a resident workgroup.
-    g->rowb = g->rowp * 48;
+    const int px = split_pixel_bytes(g->parts);
+    g->rowb = g->rowp * px;
     const long long tight = split_lds_bytes(*g);
     if (g->ty * g->b > 1) {
         int padded = g->rowb;
-        while ((g->esy * padded - 48 * g->tx) % 256 && padded < g->rowb + 256) padded += 16;
-        if ((g->esy * padded - 48 * g->tx) % 256 == 0) {
+        while ((g->esy * padded - px * g->tx) % 256 && padded < g->rowb + 256) padded += 16;
+        if ((g->esy * padded - px * g->tx) % 256 == 0) {
             SplitGeom t = *g;
             t.rowb = padded;
             const long long full = 160 * 1024;
@@ -76,7 +77,8 @@ static double split_rounds(const SplitGeom& g)
 // Workgroups that share a compute unit: by registers (of the shapes as compiled) and LDS.
 static int split_resident(const SplitGeom& g)
 {
-    const int regs = g.mb == 1 ? (g.nb <= 2 ? 4 : 3) : g.mb == 2 && g.nb == 2 ? 3 : 2;
+    const int two = g.mb == 1 && g.nb <= 2 ? 5 : g.mb * g.nb <= 4 ? 4 : g.mb == 1 || (g.mb == 2 && g.nb <= 4) || (g.mb == 3 && g.nb == 2) ? 3 : 2;
+    const int regs = g.parts == 2 ? two : g.mb == 1 ? (g.nb <= 2 ? 4 : 3) : g.mb == 2 && g.nb == 2 ? 3 : 2;
     return (int)std::min<long long>(regs, 160 * 1024 / split_lds_bytes(g));
 }
 
@@ -112,13 +114,36 @@ static double split_cycles(const SplitGeom& g, double limit)
     return norm4(cycles, bytes / 990);
 }
 
-bool split_plan(SplitGeom* g, double* cycles)
+// The same of operands in two parts, which take half the matrix time, 48 cycles per block and step.  What workgroups on a unit share
+// is the sum of the matrix cores' time, the weights' through the L2 (per 16 channels of a wave) and the pixels' out of LDS (per 16);
+// an item costs as a mean of those that exist and of whole batches of the threads.  Fitted like that one, on 12300 blocks of 200
+// layers: within 7 % (those within 25 % of a layer's best 6 %), its picks 1.015 times the best block timed in the mean (0.05 of them
+// above 1.06, the worst 1.24: 22 -> 412 at 25 x 27, batch 14, 26 us for 21).
+static double split_cycles_two(const SplitGeom& g, double limit)
+{
+    const double steps = split_steps(g), chunks = split_chunks(g), blocks = g.mb * g.nb, narrow = 1 + 0.97 / g.xh;
+    const double threads = 64.0 * g.wm * g.wn, each = g.ch8 * g.halo / threads, items = (0.5 * SPLIT_BATCH * split_batches(g) + 0.5 * each) * narrow;
+    const double alone = 248 * blocks + 614 * std::ceil(each) * narrow + chunks * (steps * (48 * blocks + 230) + 717 * items + 302);
+    const double shared = 112 + 434 * blocks + chunks * (steps * (18.4 * blocks + 86.6 * g.mb + 39.1 * g.nb) + 274 * items);
+    const int most = split_resident(g);
+    const double n = (double)g.nbk * g.nbx * g.nby * g.nbn / 256, full = std::floor(n / most), rest = std::ceil(n - full * most);
+    const double bytes = 4.0 * g.N * ((double)g.C * g.H * g.W + (double)g.K * g.P * g.Q);
+    auto rounds = [&](auto group) { return n <= 4 * most ? full * group(most) + (rest > 0 ? group(rest) : 0) : (n / most + 0.5) * group(most); };
+    const double least = rounds([&](double w) { return std::max(alone, w * shared); });
+    if (least >= limit) return least;
+    return norm4(rounds([&](double w) { return std::sqrt(alone * alone + w * shared * w * shared); }), bytes / 1245);
+}
+
+constexpr long long OWN_VALUES = 6144;
+static bool split_plan_parts(SplitGeom* g, bool small, double* cycles)
 {
     struct Shape { int mb, nb, wm, wn; };
 #define IOLB_SPLIT_ENTRY(M_, N_, A_, B_) {M_, N_, A_, B_},
-    static const std::vector<Shape> all = {IOLB_SPLIT_SHAPES(IOLB_SPLIT_ENTRY)}, few = {IOLB_SPLIT_FEW_SHAPES(IOLB_SPLIT_ENTRY)};
+    static const std::vector<Shape> all = {IOLB_SPLIT_SHAPES(IOLB_SPLIT_ENTRY)}, few = {IOLB_SPLIT_FEW_SHAPES(IOLB_SPLIT_ENTRY)},
+                                    little = {IOLB_SPLIT_SMALL_SHAPES(IOLB_SPLIT_ENTRY)};
 #undef IOLB_SPLIT_ENTRY
-    const std::vector<Shape>& shapes = g->C <= 8 ? few : all;
+    const std::vector<Shape>& shapes = g->C <= 8 ? few : small ? little : all;
+    const bool two = g->parts == 2;
     // cuts of an extent into k nearly equal parts
     auto cuts = [](int extent, int most) {
         std::vector<int> v;
@@ -146,7 +171,8 @@ bool split_plan(SplitGeom* g, double* cycles)
                         if (b * tx * ty * 2 < slots) continue;           // a smaller shape does it
                         t.tx = tx; t.ty = ty; t.b = b;
                         if (!split_derive(&t)) continue;
-                        const double r = split_rounds(t), c = split_cycles(t, found ? best_cycles : std::numeric_limits<double>::infinity());
+                        const double limit = found ? best_cycles : std::numeric_limits<double>::infinity();
+                        const double c = two ? split_cycles_two(t, limit) : split_cycles(t, limit), r = two ? c : split_rounds(t);
                         if (!found || r < best_rounds) { best = t; best_rounds = r; }
                         if (!found || c < best_cycles) { other = t; best_cycles = c; }
                         found = true;
@@ -155,7 +181,7 @@ bool split_plan(SplitGeom* g, double* cycles)
         }
     }
     if (!found) return false;
-    const double c = split_cycles(best, std::numeric_limits<double>::infinity());
+    const double c = two ? best_cycles : split_cycles(best, std::numeric_limits<double>::infinity());
     const bool leave = c > PROMISE * best_cycles;
     *g = leave ? other : best;
     *cycles = leave ? best_cycles : c;
@@ -170,7 +196,7 @@ bool split_plan(SplitGeom* g, double* cycles)
 // 10.4 -> 8.5); at 6656 it is 0.96 - 1.07, at 7680 0.91 - 0.96, and 0.5 - 0.8 on more than 256 workgroups (3 -> 48 at 148 x 148, batch 6,
 // 7 x 7, stride 2: 6656 values, 2352 of them of channels and taps that exist, 504 workgroups, 19.4 us with a launch before it,
 // 29.0 without).
-constexpr long long OWN_VALUES = 6144, OWN_ALL_VALUES = 256 * OWN_VALUES;
+constexpr long long OWN_ALL_VALUES = 256 * OWN_VALUES;
 bool split_own(const SplitGeom& g)
 {
     bool shape = false;
@@ -179,7 +205,38 @@ bool split_own(const SplitGeom& g)
 #undef IOLB_SPLIT_OWN_ENTRY
     const long long values = 16LL * g.mb * g.wm * split_chunks(g) * split_steps(g) * 32;
     const long long grid = (long long)g.nbk * g.nbx * g.nby * g.nbn;
-    return shape && values <= OWN_VALUES && grid * values <= OWN_ALL_VALUES && split_lds_bytes(g, true) <= 160 * 1024;
+    return g.parts == 3 && shape && values <= OWN_VALUES && grid * values <= OWN_ALL_VALUES && split_lds_bytes(g, true) <= 160 * 1024;
+}
+
+// Three bf16 parts: at most eight channels, workgroups that prepare their own kernels, sums of fewer than 96 products (of 27 - 48 their
+// error is 7.5e-8, that of two fp16 parts 8.9e-8; from 96 on two parts have the smaller one), and layers so small that what two fp16 parts take
+// besides the products (the samples their scales come from; some 1.2 us) outweighs them, by both models.  Measured on 200 layers: where
+// the models part them two parts are 0.88 - 1.05 times as fast below 15 us, 1.1 - 1.7 above 25; the picks of this rule take 1.025 times the
+// best block of both, those of two parts alone 1.035.
+// (Cycles: that of two parts more than of three; up to which of three nothing is gained; beyond which two always win.)
+constexpr double TWO_MORE = 2300, THREE_SMALL = 16000, THREE_MOST = 40000;
+bool split_plan(SplitGeom* g, double* cycles)
+{
+    const bool few = g->C <= 8, maybe_own = 16LL * g->C * g->R * g->S <= OWN_VALUES;
+    SplitGeom three = *g;
+    three.parts = 3;
+    double c3 = 0;
+    if ((few || maybe_own) && split_plan_parts(&three, false, &c3) && (few || split_own(three))) {
+        *g = three;
+        *cycles = c3;
+        return true;
+    }
+    g->parts = 2;
+    if (few || !split_plan_parts(g, false, cycles)) return false;
+    three = *g;
+    three.parts = 3;
+    const bool thin = (long long)g->C * g->R * g->S < 96;
+    if (thin && !split_plan_parts(&three, true, &c3)) return false;
+    if (thin || (*cycles < THREE_MOST && split_plan_parts(&three, true, &c3) && c3 < std::max(THREE_SMALL, *cycles + TWO_MORE))) {
+        *g = three;
+        *cycles = c3;
+    }
+    return true;
 }
 
 bool split_point_plan(SplitPointGeom* g, double* cycles)

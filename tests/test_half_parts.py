@@ -1,0 +1,68 @@
+"""Operands in two fp16 parts (split_mfma.h): what their scales, taken from samples, do not fit is computed again in fp32, image by
+image and kernel by kernel, and every output keeps the error bound of a sum in fp32."""
+import numpy as np
+import pytest
+
+from oracle.conv_oracle import conv_ref
+from paper_2012_15667_amd.inputs import make_inputs
+from tests.test_split_kernels import _bound, gpu  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+# N, C, H, W, K, R, stride, pad: whole images in a block, parts of one, a window of one row and of one pixel, chunks of 16 and 32
+LAYERS = [(6, 48, 7, 7, 40, 3, 1, 1), (3, 72, 30, 31, 64, 3, 1, 1), (5, 64, 16, 15, 130, 3, 2, 1), (2, 40, 40, 40, 24, 5, 1, 2)]
+
+
+def _images_apart(x, w):
+    """A scale per image, over 2^80; zeros in the first one."""
+    for i in range(x.shape[0]):
+        x[i] *= np.float32(2.0) ** ((i * 37) % 80 - 50)
+    x[0] = 0
+
+
+def _dark_corner(x, w):
+    """Pixels far below the rest of their image: sums of them alone; one of them not zero at all, one channel of it not tiny."""
+    x[:, :, :5, :5] *= np.float32(1e-6)
+    x[:, :, 6:, :2] *= np.float32(1e-12)
+    x[:, 1:, 1, 1] = 0
+    x[-1, 3, 2, 2] = 1
+
+
+def _outliers(x, w):
+    """Single values far above the sample, of inputs and of kernels."""
+    x[:, x.shape[1] // 2, -1, -1] = 3e5
+    x[-1, -1, 2, 2] = -2e30
+    w[-1, -1, 0, 0] = 1e7
+
+
+def _tiny_kernels(x, w):
+    """Kernels far below 1, one of zeros; channels of one that are far below its others, met by inputs in those channels alone."""
+    w[0] *= np.float32(1e-25)
+    w[1] = 0
+    w[2, :8] *= np.float32(1e-9)
+    w[3, 1:] = 0
+    x[:, 8:] = 0
+
+
+def _sparse(x, w):
+    """Nine in ten inputs are zero, most of the others small."""
+    rng = np.random.default_rng(x.size)
+    x *= (rng.random(x.shape) < 0.1) * np.exp2(-12 * rng.random(x.shape)).astype(np.float32)
+
+
+@pytest.mark.parametrize("layer", LAYERS)
+@pytest.mark.parametrize("change", [_images_apart, _dark_corner, _outliers, _tiny_kernels, _sparse])
+def test_direct_outputs_keep_the_bound_of_fp32(gpu, layer, change):  # noqa: F811
+    torch, B = gpu
+    N, C, H, W, K, R, stride, pad = layer
+    assert B.iolb_route(B.make_shape(N, C, H, W, K, R, R, stride, pad))[0] == B.ROUTE_SPLIT
+    x, w = make_inputs(N, C, H, W, K, R, R, "u11", "he", seed=C + K)
+    x, w = x + np.copysign(np.float32(2.0 ** -6), x), w.copy()
+    change(x, w)
+    run = lambda a: B.conv_direct(torch.from_numpy(a).cuda(), torch.from_numpy(w).cuda(), stride, pad).cpu().numpy()  # noqa: E731
+    y = run(x)
+    assert (np.abs(y - conv_ref(x, w, stride, pad)) <= _bound(x, w, stride, pad) + 2.0 ** -149).all()
+    # what another image holds does not change an image's bits
+    other = x.copy()
+    other[N - 1] *= np.float32(1e-20)
+    assert np.array_equal(run(other)[:N - 1], y[:N - 1])
