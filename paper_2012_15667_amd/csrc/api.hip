@@ -288,7 +288,7 @@ int run_split(const float* x, const float* w, float* y, const iolb_shape& s, con
             rc = ensure_workspace(dev, align256(ch.weight_bytes), &wt);
             if (rc != IOLB_OK) return rc;
         }
-        IOLB_HIP(iolb::launch_split_weights(w, wt, s.K, s.C, s.R, s.S, point ? 4 : ch.conv.ch8, point ? ch.point.Kb16 : ch.conv.Kb16, point ? 3 : ch.conv.parts, transposed, st));
+        IOLB_HIP(iolb::launch_split_weights(w, wt, s.K, s.C, s.R, s.S, point ? 4 : ch.conv.ch8, point ? ch.point.Kb16 : ch.conv.Kb16, point ? 2 : ch.conv.parts, transposed, st));
         kernels = wt;
     }
     const bool aligned = ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(y)) & 15) == 0;
@@ -296,7 +296,7 @@ int run_split(const float* x, const float* w, float* y, const iolb_shape& s, con
     if (point) {
         iolb::SplitPointGeom g = ch.point;
         if (!aligned) { g.vec_out = 0; if (g.in == iolb::SPLIT_IN_CHANNELS) g.in = iolb::SPLIT_IN_SINGLE; }
-        IOLB_HIP(iolb::launch_split_point(x, kernels, y, g, st));
+        IOLB_HIP(iolb::launch_split_point(x, kernels, w, y, g, st));
     } else {
         iolb::SplitGeom g = ch.conv;
         if (!aligned) g.vec_in = g.vec_out = 0;
@@ -587,8 +587,11 @@ int run_winograd_split(const float* x, const float* w, const float* Upre, float*
         return IOLB_OK;
     }
     IOLB_HIP(iolb::launch_wino_transforms(x, V, p.w, w ? w : Upre, U, w ? iolb::WINO_KERNELS_SPLIT : iolb::WINO_KERNELS_GIVEN, p.g.Kb16, st));
+    iolb::SplitPointGeom g = p.g;
+    g.raw = w ? iolb::SPLIT_RAW_TAPS : iolb::SPLIT_RAW_PLANES;
+    g.m = p.w.m;
     MainKernelTimer timer(st, IOLB_TIME_WINO_PRODUCT);
-    IOLB_HIP(iolb::launch_split_point(V, U, M, p.g, st));
+    IOLB_HIP(iolb::launch_split_point(V, U, w ? w : Upre, M, g, st));
     timer.stop(st);
     IOLB_HIP(iolb::launch_wino_output_transform(M, y, p.w, st));
     return IOLB_OK;

@@ -181,15 +181,21 @@ struct SplitPointGeom {
     int Kb16;                  // 16-channel blocks in the re-laid-out kernels
     long long w_image;         // 16-byte pieces from one group's kernels to the next
     int hwc, in, vec_out;      // in: how the inputs are read, below
+    int raw, m;                // the kernels as the caller holds them, below; tile edge where they are transformed
 };
 // Inputs read in single floats; four channels at a time (channels innermost, C a multiple of 4, 16-byte aligned); two
 // neighbouring pixels at a time (channels outermost, stride 1; blocks may run on into the next image only where HW is
 // even).
+// (the caller's kernels: w[K][C]; transformed w[plane][C rounded up to 16][K rounded up to 32]; w[K][C][3][3], to be transformed)
+enum { SPLIT_RAW_ROWS = 0, SPLIT_RAW_PLANES = 1, SPLIT_RAW_TAPS = 2 };
 enum { SPLIT_IN_SINGLE = 0, SPLIT_IN_CHANNELS = 1, SPLIT_IN_PIXELS = 2 };
 constexpr int split_point_pixels(int in) { return in == SPLIT_IN_PIXELS ? 2 : 1; }
 #define IOLB_SPLIT_POINT_SHAPES(X) X(1, 2, 4, 1) X(1, 4, 4, 1) X(2, 4, 4, 1) X(3, 4, 4, 1) X(4, 4, 4, 1)
+// Room for a group's kernels in two parts, which they and what undoes their scales do not fill.
 inline long long split_point_weight_bytes(const SplitPointGeom& g) { return (g.C + 31LL) / 32 * g.Kb16 * 3072; }
-hipError_t launch_split_point(const float* x, const void* wt, float* y, const SplitPointGeom& g, hipStream_t st);
+// wt: the kernels in two parts, per group [chunk][16-kernel block][part][lane] and behind them what undoes the scales of 16 Kb16 kernels;
+// w: as the caller holds them (g.raw), for blocks that are taken again.
+hipError_t launch_split_point(const float* x, const void* wt, const float* w, float* y, const SplitPointGeom& g, hipStream_t st);
 
 // Thin layers (direct_thin.hip): 3 x 3 kernels, stride 1, C <= 4, plain NCHW tensors.  wk: K rows of
 // direct_thin_row(C) floats (the 9 C elements of a kernel, zero-padded to whole 16-float pieces), 64-byte aligned,
@@ -234,7 +240,7 @@ struct WinoGeom {
 };
 hipError_t launch_wino_kernel_transform(const float* w, float* U, const WinoGeom& g, hipStream_t st);
 // Input transform of x into V and, in the same launch, the kernels of the product: NONE (U is there already), PLAIN
-// (U[xi][CpU][Kp] from w), or three bf16 parts for launch_split_point (groups = planes, Kb16 16-kernel blocks) from w
+// (U[xi][CpU][Kp] from w), or two fp16 parts for launch_split_point (groups = planes, Kb16 16-kernel blocks) from w
 // (SPLIT) or from a caller's U[xi][C rounded up to 16][K rounded up to 32] in w's place (GIVEN).
 enum { WINO_KERNELS_NONE, WINO_KERNELS_PLAIN, WINO_KERNELS_SPLIT, WINO_KERNELS_GIVEN };
 hipError_t launch_wino_transforms(const float* x, float* V, const WinoGeom& g, const float* w, void* U, int kind, int Kb16, hipStream_t st);

@@ -1,27 +1,28 @@
-// 1 x 1 convolution (no padding), and the product step of unfused Winograd, on the bf16 matrix cores at fp32 precision
-// (operands in three parts, split_mfma.h): per group of images that share kernels y[K][HW] = w[K][C] x[C][HW], a
+// 1 x 1 convolution (no padding), and the product step of unfused Winograd, on the 16-bit matrix cores at fp32 precision
+// (operands in two fp16 parts, split_mfma.h): per group of images that share kernels y[K][HW] = w[K][C] x[C][HW], a
 // transformed plane of Winograd being such a group of its own.
 //
 // A step is 32 channels.  The inputs of chunk t + 1 are split and written to one LDS buffer while chunk t is multiplied
 // from the other; their loads are issued three chunks ahead and kept in registers, two neighbouring pixels per load where
-// the layout has them.  The split's arithmetic is placed between the matrix instructions, three vector
-// instructions after each, where it costs little (a bf16 matrix instruction leaves the vector pipeline free; measured:
+// the layout has them.  Every pixel has a scale of its own, from the first 32 of its channels and a few more.  The split's arithmetic is
+// placed between the matrix instructions, three vector
+// instructions after each, where it costs little (a 16-bit matrix instruction leaves the vector pipeline free; measured:
 // eight vector instructions per 32-cycle matrix instruction 1433 against 1631 TFLOP/s).  wt is not declared restrict on
 // purpose: loads of memory known not to change were moved down past the barrier to their use, which undid the prefetch.
 //
-// What bounds it: of large products nothing found yet. Matrix cores are busy 0.57 of the cycles; a compute unit takes in 20 bytes
-// of operands per clock (6.05 GB through the L2s in 1.15 M clocks on the product below; a block of z channels by npix pixels
-// needs 192 z + 128 npix bytes per 32 channels), while other kernels take 24 to 36 through the same L2s; the vector work of the split
-// costs clock. 16 planes of 512 x 12544 x 512 (F(2x2)) 545 us = 193 TFLOP/s with 256 x 64 blocks (fp32 instructions: 840 us; with
-// single stores 580), larger blocks were slower.  Small ones the latency of their steps.  1 x 1, 768 -> 192 at 17 x 17, batch 64,
-// whole call: 66 us on the fp32 instructions, 46.4 with single stores, 43.5.
-// Measured and taken back: the weights of chunk t + 2 loaded before the inputs of chunk t + 3, so that these have two steps
+// What bounds it: operands on their way in, about 20 bytes per clock and compute unit (a block of z channels by npix pixels needs
+// 128 z + 128 npix bytes per 32 channels), and the latency of small layers' steps.  16 planes of 512 x 12544 x 512 (F(2x2)), 256 x 64
+// blocks: 840 us on the fp32 instructions, 541 in three bf16 parts, 396 = 266 TFLOP/s in two fp16 parts.  1 x 1, 768 -> 192 at 17 x 17,
+// batch 64, whole call: 66, 43.4, 36.8 us; 320 -> 224 at 170 x 170, batch 22 578 -> 454.  Zero pixels that each looked for their image's
+// largest value cost 12 us of the 17 x 17 layer: now a wave does it once.
+// Measured with three parts and taken back: the weights of chunk t + 2 loaded before the inputs of chunk t + 3, so that these have two steps
 // to arrive (the same product 545 -> 573 us).
 //
 // A column of a wave's 16 x 16 blocks is 16 pixels; block nb of the wave takes every NB-th pixel from nb on (VPX), so that a
 // lane holds NB neighbours of each output channel and stores them at once.
 #include "kernels.h"
 #include "split_mfma.h"
+#include "wino_mats.h"
 
 #include <type_traits>
 
@@ -29,16 +30,27 @@ namespace iolb {
 
 namespace {
 
+// Element j of row `row` of the kernel transform's L.
+__device__ __forceinline__ float kernel_coefficient(int m, int row, int j)
+{
+    return m == 2 ? Mats<2>::L[row][j] : m == 3 ? Mats<3>::L[row][j] : m == 4 ? Mats<4>::L[row][j] : Mats<6>::L[row][j];
+}
+
 template <int MB, int NB, int WM, int WN, int IN, bool VPX>
 __global__ void __launch_bounds__(64 * WM * WN, 2)
-split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitPointGeom g)
+split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitPointGeom g, const float* __restrict__ w)
 {
-    constexpr int T = 64 * WM * WN, NPIX = 16 * NB * WN, BUF = 4 * NPIX * 48;
+    constexpr int T = 64 * WM * WN, NPIX = 16 * NB * WN, PLANE = 4 * NPIX * 16, BUF = 2 * PLANE;
     // an input item: CH channels of PX neighbouring pixels
     constexpr int PX = split_point_pixels(IN), CH = IN == SPLIT_IN_PIXELS ? 4 : 8;
     constexpr int ITEMS = 32 / CH * NPIX / PX, IB = (ITEMS + T - 1) / T;
     extern __shared__ u32x4 lds16[];
-    char* const lds = reinterpret_cast<char*>(lds16);       // two buffers, then 48 bytes that nobody reads
+    // two buffers, each the h of all pixels and then the l; room that nobody reads; per pixel the largest value in the sample that sets
+    // its scale, and of all its channels, scaled; what undoes the kernels' scales
+    char* const lds = reinterpret_cast<char*>(lds16);
+    unsigned* const sample = reinterpret_cast<unsigned*>(lds + 2 * BUF + PLANE + 16);
+    unsigned* const most = sample + NPIX;
+    float* const kback = reinterpret_cast<float*>(most + NPIX);
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, grp = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm_i = wave % WM, wn_i = wave / WM;
@@ -67,7 +79,7 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
 
     // the input items of this thread
     // Column l16 of a wave's block nb is pixel 16 nb + l16, or NB l16 + nb (VPX): pixels are kept in LDS in the order in which
-    // the blocks read them.  Pairs of pixels are then written with half the bank conflicts (48 bytes from lane to lane, not 96).
+    // the blocks read them.  Pairs of pixels are then written with half the bank conflicts (16 bytes from lane to lane, not 32).
     auto slot_of = [&](int px) { return VPX ? px / (16 * NB) * (16 * NB) + px % NB * 16 + px % (16 * NB) / NB : px; };
     auto pixel_of = [&](int nb, int l) { return wn_i * NB * 16 + (VPX ? NB * l + nb : 16 * nb + l); };
     unsigned src[IB], dst[IB];
@@ -79,7 +91,7 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
         src[i] = OUTSIDE;
         dst[i] = 2 * BUF;
         if (it < ITEMS) {
-            dst[i] = (unsigned)(48 * (c_in[i] / 8 * NPIX + slot_of(px)) + (c_in[i] & 4) * 2);
+            dst[i] = (unsigned)(16 * (c_in[i] / 8 * NPIX + slot_of(px)) + (c_in[i] & 4) * 2);
             if (px < left_px) {
                 const int q = p0 + px, im = q / g.HW, r = q % g.HW;
                 const int in = g.stride == 1 ? r : r / g.Q * g.stride * g.Win + r % g.Q * g.stride;
@@ -88,7 +100,7 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
         }
     }
     const int cstep = g.hwc ? 4 : 4 * g.HWin;
-    constexpr int NEXT_PX = VPX ? 48 * 16 : 48;             // LDS bytes from a pixel to the next of its item
+    constexpr int NEXT_PX = VPX ? 16 * 16 : 16;             // LDS bytes from a pixel to the next of its item
 
     f32x4 acc[MB][NB];
 #pragma unroll
@@ -98,8 +110,9 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
 
     const int nchunks = (g.C + 31) >> 5;
     const int kb16 = kb * (MB * WM) + wm_i * MB;
-    const size_t wstep = (size_t)g.Kb16 * 192;
-    const u32x4* wp = wt + (size_t)group * g.w_image + (size_t)kb16 * 192 + lane;
+    const size_t wstep = (size_t)g.Kb16 * 128;
+    const u32x4* const group_w = wt + (size_t)group * g.w_image;
+    const u32x4* wp = group_w + (size_t)kb16 * 128 + lane;
 
     float xv[2][IB][CH * PX];
     auto load_x = [&](float (&v)[IB][CH * PX], int ch) {
@@ -129,50 +142,104 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
             }
         }
     };
+    float scale[IB][PX], top[IB][PX];                       // of the items' pixels: the scale; the largest value so far, scaled
     auto write_x = [&](const float (&v)[IB][CH * PX], char* buf) {
 #pragma unroll
         for (int i = 0; i < IB; ++i) {
             char* d = (dst[i] == 2 * BUF ? lds : buf) + dst[i];
             if constexpr (CH == 8) {
-                u32x4 h, m, l;
-                split_eight(v[i], h, m, l);
-                u32x4* d4 = reinterpret_cast<u32x4*>(d);
-                d4[0] = h; d4[1] = m; d4[2] = l;
+                u32x4 h, l;
+                top[i][0] = __builtin_fmaxf(top[i][0], half_eight(v[i], scale[i][0], h, l));
+                *reinterpret_cast<u32x4*>(d) = h;
+                *reinterpret_cast<u32x4*>(d + PLANE) = l;
             } else {
 #pragma unroll
                 for (int p = 0; p < PX; ++p) {
-                    u32x2 h, m, l;
+                    u32x2 h, l;
 #pragma unroll
                     for (int j = 0; j < 2; ++j) {
-                        unsigned hj, mj, lj;
-                        split_pair(v[i][p * 4 + 2 * j], v[i][p * 4 + 2 * j + 1], hj, mj, lj);
-                        h[j] = hj; m[j] = mj; l[j] = lj;
+                        const float a = v[i][p * 4 + 2 * j] * scale[i][p], b = v[i][p * 4 + 2 * j + 1] * scale[i][p];
+                        unsigned hj, lj;
+                        half_pair(a, b, hj, lj);
+                        h[j] = hj; l[j] = lj;
+                        top[i][p] = __builtin_fmaxf(__builtin_fmaxf(top[i][p], __builtin_fabsf(a)), __builtin_fabsf(b));
                     }
                     // (an item that does not exist writes all its pixels to the same spare place)
                     char* dp = d + (dst[i] == 2 * BUF ? 0 : NEXT_PX * p);
                     *reinterpret_cast<u32x2*>(dp) = h;
-                    *reinterpret_cast<u32x2*>(dp + 16) = m;
-                    *reinterpret_cast<u32x2*>(dp + 32) = l;
+                    *reinterpret_cast<u32x2*>(dp + PLANE) = l;
                 }
             }
         }
     };
-    auto load_a = [&](u32x4 (&a)[MB * 3]) {
+    auto load_a = [&](u32x4 (&a)[MB * 2]) {
 #pragma unroll
-        for (int j = 0; j < MB * 3; ++j) a[j] = wp[j * 64];
+        for (int j = 0; j < MB * 2; ++j) a[j] = wp[j * 64];
     };
     auto barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
-    const char* const mine = lds + 48 * (grp * NPIX + wn_i * NB * 16 + l16);
-    u32x4 bf[2][3];
-    auto fetch = [&](u32x4 (&f)[3], const char* from) {
-#pragma unroll
-        for (int p = 0; p < 3; ++p) f[p] = *reinterpret_cast<const u32x4*>(from + 16 * p);
+    const char* const mine = lds + 16 * (grp * NPIX + wn_i * NB * 16 + l16);
+    u32x4 bf[2][2];
+    auto fetch = [&](u32x4 (&f)[2], const char* from) {
+        f[0] = *reinterpret_cast<const u32x4*>(from);
+        f[1] = *reinterpret_cast<const u32x4*>(from + PLANE);
     };
 
-    u32x4 a0[MB * 3], a1[MB * 3];
+    u32x4 a0[MB * 2], a1[MB * 2];
     load_x(xv[0], 0);
+    // for the sample beside the first 32 channels one more value per item, from the others
+    float spread[IB];
+#pragma unroll
+    for (int i = 0; i < IB; ++i) {
+        const int c = 32 * (int)((unsigned)(37 * (i * T + tid) & 63) * (unsigned)nchunks >> 6);
+        spread[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, src[i] != OUTSIDE && c + c_in[i] < g.C ? (int)(src[i] + (unsigned)c * (unsigned)cstep) : (int)OUTSIDE, 0, 0));
+    }
+    static_assert(16 * MB * WM <= T && 2 * NPIX <= T, "one kernel, one of the pixels' two values per thread");
+    float my_kback = 0.f;
+    if (tid < 16 * MB * WM) my_kback = reinterpret_cast<const float*>(group_w + (size_t)nchunks * wstep)[kb * (16 * MB * WM) + tid];
     load_x(xv[1], 1);
     load_a(a0);
+    if (tid < 2 * NPIX) sample[tid] = 0;                    // (most follows)
+    __builtin_amdgcn_sched_barrier(0);
+    barrier();
+    // A pixel's scale follows from its own values, so that neither its neighbours nor other images change its outputs.
+    auto item_px = [&](int i) { return (i * T + tid) % (NPIX / PX) * PX; };
+    auto exists = [&](int i) { return i * T + tid < ITEMS; };
+#pragma unroll
+    for (int i = 0; i < IB; ++i)
+#pragma unroll
+        for (int p = 0; p < PX; ++p) {
+            unsigned m = p == 0 ? finite_bits(spread[i]) : 0u;
+#pragma unroll
+            for (int j = 0; j < CH; ++j) {
+                const unsigned a = finite_bits(xv[0][i][p * CH + j]);
+                m = a > m ? a : m;
+            }
+            if (exists(i) && m && item_px(i) + p < left_px) atomicMax(sample + item_px(i) + p, m);
+        }
+    if (tid < 16 * MB * WM) kback[tid] = my_kback;
+    barrier();
+    // ... of its image's pixels in the block where those are all zeros.
+    static_assert(NPIX <= 64, "a lane per pixel");
+    const unsigned all = wave_max(lane < NPIX ? sample[lane] : 0u);
+    auto scale_of = [&](int px) {
+        unsigned m = sample[px];
+        if (m == 0 && px < left_px) {
+            m = all;
+            if (span > 1) {
+                m = 0;
+                for (int q = 0, image = (p0 + px) / g.HW; q < NPIX; ++q)
+                    if (q < left_px && (p0 + q) / g.HW == image && sample[q] > m) m = sample[q];
+            }
+        }
+        return half_scale_bits(m);
+    };
+#pragma unroll
+    for (int i = 0; i < IB; ++i)
+#pragma unroll
+        for (int p = 0; p < PX; ++p) {
+            scale[i][p] = __uint_as_float(scale_of(item_px(i) + p));
+            top[i][p] = 0.f;
+        }
     __builtin_amdgcn_sched_barrier(0);
     write_x(xv[0], lds);
     load_x(xv[0], 2);
@@ -182,20 +249,20 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
 
     // One step = 32 channels.  While chunk t is multiplied, chunk t + 1 is split into its three parts (its loads were
     // issued two steps ago) and written to the other buffer, and the loads of chunk t + 3 are issued.
-    auto step = [&](int t, u32x4 (&a)[MB * 3], u32x4 (&an)[MB * 3], float (&v)[IB][CH * PX]) {
+    auto step = [&](int t, u32x4 (&a)[MB * 2], u32x4 (&an)[MB * 2], float (&v)[IB][CH * PX]) {
         if (t + 1 < nchunks) wp += wstep;
         load_a(an);
         const char* cur = mine + (t & 1) * BUF;
         auto block = [&](auto nb_c) {
             constexpr int nb = decltype(nb_c)::value;
-            if constexpr (nb + 1 < NB) fetch(bf[(nb + 1) & 1], cur + 48 * 16 * (nb + 1));
-            constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};      // small products first
+            if constexpr (nb + 1 < NB) fetch(bf[(nb + 1) & 1], cur + 16 * 16 * (nb + 1));
+            constexpr int PA[3] = {1, 0, 0}, PB[3] = {0, 1, 0};      // small products first
 #pragma unroll
-            for (int q = 0; q < 6; ++q)
+            for (int q = 0; q < 3; ++q)
 #pragma unroll
                 for (int mb = 0; mb < MB; ++mb)
-                    acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                        __builtin_bit_cast(bf16x8, a[mb * 3 + PA[q]]), __builtin_bit_cast(bf16x8, bf[nb & 1][PB[q]]), acc[mb][nb], 0, 0, 0);
+                    acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                        __builtin_bit_cast(f16x8, a[mb * 2 + PA[q]]), __builtin_bit_cast(f16x8, bf[nb & 1][PB[q]]), acc[mb][nb], 0, 0, 0);
         };
         constexpr int HALF = NB / 2;
         static_range<0, HALF>(block);
@@ -204,7 +271,7 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
         static_range<HALF, NB>(block);
         // the arithmetic of the split runs in the shadow of the matrix instructions
 #pragma unroll
-        for (int i = 0; i < (NB - HALF) * 6 * MB; ++i) {
+        for (int i = 0; i < (NB - HALF) * 3 * MB; ++i) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
             __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
         }
@@ -222,11 +289,38 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
     }
 
     // each partial sum is complete: write the block once.  Register i of a 16 x 16 block holds channel 4 grp + i of
-    // pixel l16.  Sums that are not finite are marked.
+    // pixel l16.  Where all sums are finite, and no pixel is too small for its scale, they are only written; otherwise those that
+    // are not, and such a pixel's, are marked, and written a second time.
+#pragma unroll
+    for (int i = 0; i < IB; ++i)
+#pragma unroll
+        for (int p = 0; p < PX; ++p)
+            if (exists(i)) atomicMax(most + item_px(i) + p, __float_as_uint(top[i][p]));
+    barrier();
     unsigned long long again = 0;
     static_assert(MB * NB * 4 <= 64, "one mark per output");
-    auto write_y = [&](auto marked_c) {
-        constexpr bool MARKED = decltype(marked_c)::value;  // the second time: marked outputs only
+    float back[NB];
+    f32x4 kb4[MB];
+    bool lost[NB], any_lost = false;
+    f32x4 zero = {0.f, 0.f, 0.f, 0.f};                      // 0 times a sum that is not finite is NaN
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        const int px = pixel_of(nb, l16);
+        back[nb] = half_unscale(scale_of(px));
+        lost[nb] = px < left_px && most[px] - 1 < __float_as_uint(HALF_LEAST) - 1;
+        any_lost |= lost[nb];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) zero[i] = __builtin_fmaf(px < left_px ? acc[mb][nb][i] : 0.f, 0.f, zero[i]);
+    }
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) kb4[mb] = *reinterpret_cast<const f32x4*>(kback + (wm_i * MB + mb) * 16 + 4 * grp);
+    const bool finite = __builtin_amdgcn_ballot_w64(any_lost || zero[0] + zero[1] + zero[2] + zero[3] != 0.f) == 0;
+    enum { PLAIN, MARKING, MARKED_ONLY };
+    auto write_y = [&](auto mode_c) {
+        constexpr int MODE = decltype(mode_c)::value;
+        constexpr bool MARKED = MODE == MARKED_ONLY;
         const int l16 = opaque(lane) & 15, grp = opaque(lane) >> 4;
         if constexpr (VPX && !MARKED) {
             typedef float vec __attribute__((ext_vector_type(NB), aligned(4)));
@@ -245,8 +339,9 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb) {
                         // (beyond the pixels that exist the inputs are what follows them: not a reason to do anything again)
-                        if (px + nb < left_px && !(__builtin_fabsf(acc[mb][nb][i]) <= 3.402823466e38f)) again |= 1ull << ((nb * MB + mb) * 4 + i);
-                        q[nb] = acc[mb][nb][i] * SPLIT_UNSCALE;
+                        if (MODE == MARKING && px + nb < left_px && (lost[nb] || !(__builtin_fabsf(acc[mb][nb][i]) <= 3.402823466e38f)))
+                            again |= 1ull << ((nb * MB + mb) * 4 + i);
+                        q[nb] = acc[mb][nb][i] * back[nb] * kb4[mb][i];
                     }
                     if (k0 + i >= g.K) continue;
                     if (whole) {
@@ -271,8 +366,8 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
                 if constexpr (!MARKED) {
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        if (!(__builtin_fabsf(acc[mb][nb][i]) <= 3.402823466e38f)) again |= 1ull << (bit + i);
-                        acc[mb][nb][i] *= SPLIT_UNSCALE;
+                        if (MODE == MARKING && (lost[nb] || !(__builtin_fabsf(acc[mb][nb][i]) <= 3.402823466e38f))) again |= 1ull << (bit + i);
+                        acc[mb][nb][i] = acc[mb][nb][i] * back[nb] * kb4[mb][i];
                     }
                 }
                 if (g.hwc) {
@@ -293,7 +388,11 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
             }
         }
     };
-    write_y(std::false_type{});
+    if (finite) {
+        write_y(std::integral_constant<int, PLAIN>{});
+        return;
+    }
+    write_y(std::integral_constant<int, MARKING>{});
     if (__builtin_amdgcn_ballot_w64(again != 0) == 0) return;
 
     // A wave with a marked output takes its whole block again on the fp32 matrix instructions, which hold their sums in
@@ -308,12 +407,33 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    const u32x4* wq = wt + (size_t)group * g.w_image + (size_t)kb16 * 192 + lane2;
+    // The kernels as the caller holds them: their two parts are not always all of them.
+    float li[3] = {0.f, 0.f, 0.f}, lj[3] = {0.f, 0.f, 0.f};
+    if (g.raw == SPLIT_RAW_TAPS) {
+        const int n = g.m + 2;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            li[j] = kernel_coefficient(g.m, group / n, j);
+            lj[j] = kernel_coefficient(g.m, group % n, j);
+        }
+    }
+    auto kernel_value = [&](int k, int c) {
+        if (k >= g.K || c >= g.C) return 0.f;
+        if (g.raw == SPLIT_RAW_ROWS) return w[(size_t)k * g.C + c];
+        if (g.raw == SPLIT_RAW_PLANES) return w[((size_t)group * ((g.C + 15) / 16 * 16) + c) * ((g.K + 31) / 32 * 32) + k];
+        const float* t = w + ((size_t)k * g.C + c) * 9;
+        float u = 0.f;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) u += lj[j] * (li[0] * t[j] + (li[1] * t[3 + j] + li[2] * t[6 + j]));
+        return u;
+    };
 #pragma unroll 1
-    for (int ch = 0; ch < nchunks; ++ch, wq += wstep) {
+    for (int ch = 0; ch < nchunks; ++ch) {
         float wv[MB][8];
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) kept_eight(wq[mb * 192], wq[mb * 192 + 64], wq[mb * 192 + 128], wv[mb]);
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) wv[mb][j] = kernel_value((kb16 + mb) * 16 + col16, 32 * ch + c0 + j);
         static_range<0, NB>([&](auto nb_c) {
             constexpr int nb = decltype(nb_c)::value;
             float v[8];
@@ -329,22 +449,22 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
                 for (int mb = 0; mb < MB; ++mb) acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[mb][j], v[j], acc[mb][nb], 0, 0, 0);
         });
     }
-    write_y(std::true_type{});
+    write_y(std::integral_constant<int, MARKED_ONLY>{});
 }
 
 template <int MB, int NB, int WM, int WN, int IN, bool VPX>
-hipError_t launch_one(const float* x, const u32x4* wt, float* y, const SplitPointGeom& g, hipStream_t st)
+hipError_t launch_one(const float* x, const u32x4* wt, const float* w, float* y, const SplitPointGeom& g, hipStream_t st)
 {
     auto kern = split_point_kernel<MB, NB, WM, WN, IN, VPX>;
-    constexpr size_t shm = 2 * 4 * 16 * NB * WN * 48 + 48;
+    constexpr size_t NPIX = 16 * NB * WN, shm = 5 * 4 * NPIX * 16 + 16 + 8 * NPIX + 64 * MB * WM;
     static_assert(shm <= 64 * 1024, "dynamic LDS without an opt-in");
-    hipLaunchKernelGGL(kern, dim3(g.nbk * g.nbp * g.groups), dim3(64 * WM * WN), shm, st, x, wt, y, g);
+    hipLaunchKernelGGL(kern, dim3(g.nbk * g.nbp * g.groups), dim3(64 * WM * WN), shm, st, x, wt, y, g, w);
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_split_point(const float* x, const void* wt, float* y, const SplitPointGeom& g, hipStream_t st)
+hipError_t launch_split_point(const float* x, const void* wt, const float* w_given, float* y, const SplitPointGeom& g, hipStream_t st)
 {
     // what the kernel assumes of its geometry
     const long long npix = 16LL * g.nb * g.wn, span = (g.HW - 1 + npix - 1) / g.HW + 1;
@@ -361,12 +481,12 @@ hipError_t launch_split_point(const float* x, const void* wt, float* y, const Sp
     const bool vec = !g.hwc && (g.images == 1 || g.HW % g.nb == 0);
 #define IOLB_POINT_CASE(M_, N_, A_, B_)                                                                              \
     if (g.mb == M_ && g.nb == N_ && g.wm == A_ && g.wn == B_) {                                                      \
-        if (g.in == SPLIT_IN_CHANNELS) return launch_one<M_, N_, A_, B_, SPLIT_IN_CHANNELS, false>(x, w, y, g, st);  \
+        if (g.in == SPLIT_IN_CHANNELS) return launch_one<M_, N_, A_, B_, SPLIT_IN_CHANNELS, false>(x, w, w_given, y, g, st);  \
         if (g.in == SPLIT_IN_PIXELS)                                                                                 \
-            return vec ? launch_one<M_, N_, A_, B_, SPLIT_IN_PIXELS, true>(x, w, y, g, st)                           \
-                       : launch_one<M_, N_, A_, B_, SPLIT_IN_PIXELS, false>(x, w, y, g, st);                         \
-        return vec ? launch_one<M_, N_, A_, B_, SPLIT_IN_SINGLE, true>(x, w, y, g, st)                               \
-                   : launch_one<M_, N_, A_, B_, SPLIT_IN_SINGLE, false>(x, w, y, g, st);                             \
+            return vec ? launch_one<M_, N_, A_, B_, SPLIT_IN_PIXELS, true>(x, w, w_given, y, g, st)                           \
+                       : launch_one<M_, N_, A_, B_, SPLIT_IN_PIXELS, false>(x, w, w_given, y, g, st);                         \
+        return vec ? launch_one<M_, N_, A_, B_, SPLIT_IN_SINGLE, true>(x, w, w_given, y, g, st)                               \
+                   : launch_one<M_, N_, A_, B_, SPLIT_IN_SINGLE, false>(x, w, w_given, y, g, st);                             \
     }
     IOLB_SPLIT_POINT_SHAPES(IOLB_POINT_CASE)
 #undef IOLB_POINT_CASE

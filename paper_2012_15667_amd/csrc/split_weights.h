@@ -46,6 +46,25 @@ __device__ __forceinline__ void store_parts(u32x4* to, const unsigned short (&p)
     }
 }
 
+// The piece of eight transformed kernel elements in two fp16 parts, scaled already, of kernel lane & 15 and the channels of lane >> 4; the
+// four lanes that share a kernel judge it together (of `channels` < 16 some are all small now and then: not judged).  NaN in place
+// of a kernel too small for its scale.
+__device__ __forceinline__ void store_halves(u32x4* to, const float (&u)[8], int channels)
+{
+    u32x4 h, l;
+    float most = half_eight(u, 1.f, h, l);
+    most = __builtin_fmaxf(most, __shfl_xor(most, 16));
+    most = __builtin_fmaxf(most, __shfl_xor(most, 32));
+    const unsigned poison = channels >= 16 && most != 0.f && most < HALF_LEAST ? 0x7e007e00u : 0u;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) h[i] |= poison;
+    to[0] = h;
+    to[64] = l;
+}
+// The channel of spot 0 ... 15 at which kernels are sampled for their scale: two elements of each, g[0][0] and g[2][2], which are also
+// elements of the transformed kernel, times a power of two.
+__device__ __forceinline__ int sampled_channel(int spot, int C) { return (int)((long long)C * spot >> 4); }
+
 // Row `row` (the same in every lane of a wave) of L g for eight channels, g[3][3] one after the other from `from` on.  A branch per
 // row: with every row computed and one selected, the launch that the input transform shares took 254 registers in F(3 x 3), 210 in
 // F(4 x 4) (now 66 and 61 - 112, as without), which left two waves per SIMD (382 -> 132 at 121 x 121, batch 9, F(3 x 3): 633 us,

@@ -66,6 +66,25 @@ template <> struct Mats<6> {
                                       {0, 1, -1, 32, -32, 0.03125f, -0.03125f, 1}};
 };
 
+// Transformed kernels have elements of very different size from plane to plane (F(6 x 6): 0.003 to 1 of the kernel's).  Powers of
+// two that bring a plane's to the kernel's: 2^(kernel_up(i) + kernel_up(j)) for row i and column j.
+template <int M>
+constexpr int kernel_up(int row)
+{
+    float norm = 0.f;
+    for (int j = 0; j < 3; ++j) norm += Mats<M>::L[row][j] * Mats<M>::L[row][j];
+    int up = 0;
+    for (; norm < 0.5f; norm *= 4.f) ++up;
+    return up;
+}
+constexpr float power_of_two(int e)
+{
+    float p = 1.f;
+    for (; e > 0; --e) p *= 2.f;
+    for (; e < 0; ++e) p *= 0.5f;
+    return p;
+}
+
 }  // namespace iolb
 
 #endif

@@ -36,12 +36,14 @@ def _outliers(x, w):
 
 
 def _tiny_kernels(x, w):
-    """Kernels far below 1, one of zeros; channels of one that are far below its others, met by inputs in those channels alone."""
+    """Kernels far below 1, one of zeros; channels of one that are far below its others, met by inputs in those channels alone: as many
+    as are judged together, eight with a window, 128 without."""
+    n = 8 if w.shape[2] > 1 else 128
     w[0] *= np.float32(1e-25)
     w[1] = 0
-    w[2, :8] *= np.float32(1e-9)
+    w[2, :n] *= np.float32(1e-9)
     w[3, 1:] = 0
-    x[:, 8:] = 0
+    x[:, n:] = 0
 
 
 def _sparse(x, w):
@@ -66,3 +68,62 @@ def test_direct_outputs_keep_the_bound_of_fp32(gpu, layer, change):  # noqa: F81
     other = x.copy()
     other[N - 1] *= np.float32(1e-20)
     assert np.array_equal(run(other)[:N - 1], y[:N - 1])
+
+
+def _relative(torch, y, ref, lim):
+    return float(((y.double() - ref).abs() / (lim + 2.0 ** -149)).max())
+
+
+@pytest.mark.parametrize("layer", [(12, 768, 17, 17, 192, 1), (70, 515, 7, 5, 500, 1), (4, 300, 61, 61, 450, 2)])
+@pytest.mark.parametrize("layout", ["chw", "hwc"])
+@pytest.mark.parametrize("change", [_images_apart, _dark_corner, _outliers, _tiny_kernels, _sparse])
+def test_pointwise_outputs_keep_the_bound_of_fp32(gpu, layer, layout, change):  # noqa: F811
+    torch, B = gpu
+    N, C, H, W, K, stride = layer
+    lay = B.LAYOUT_HWC if layout == "hwc" else B.LAYOUT_CHW
+    assert B.iolb_route(B.make_shape(N, C, H, W, K, 1, 1, stride, 0), lay)[0] == B.ROUTE_SPLIT
+    x, w = make_inputs(N, C, H, W, K, 1, 1, "u11", "he", seed=C + K)
+    x, w = x + np.copysign(np.float32(2.0 ** -6), x), w.copy()
+    change(x, w)
+    wd = torch.from_numpy(w).cuda()
+
+    def run(a):
+        a = torch.from_numpy(a).cuda()
+        if layout == "chw":
+            return B.conv_direct(a, wd, stride, 0)
+        return B.conv_direct_layout(a.permute(0, 2, 3, 1).contiguous(), wd, stride, 0, lay).permute(0, 3, 1, 2)
+
+    y = run(x)
+    xs = torch.from_numpy(x).cuda()[:, :, ::stride, ::stride].double().flatten(2).contiguous()
+    wk = wd.double().view(1, K, C).expand(N, K, C).contiguous()
+    lim = (12 * -(-C // 8) + 16) * 2.0 ** -23 * torch.bmm(wk.abs(), xs.abs())
+    assert _relative(torch, y.flatten(2), torch.bmm(wk, xs), lim) <= 1
+    other = x.copy()
+    other[N - 1] *= np.float32(1e-20)
+    assert torch.equal(run(other)[:N - 1], y[:N - 1])
+
+
+# products of their own between the transforms, every m
+@pytest.mark.parametrize("m,N,C,H,W,K", [(2, 64, 512, 7, 7, 512), (3, 33, 525, 7, 8, 485), (4, 9, 277, 35, 37, 233), (6, 5, 284, 29, 30, 497)])
+def test_winograd_product_with_kernels_the_scales_do_not_fit(gpu, m, N, C, H, W, K):  # noqa: F811
+    """Images and kernels of very different scale, channels of one kernel far below its others, an outlier: from w and from kernels
+    transformed before, within the guard of each image and kernel by itself."""
+    torch, B = gpu
+    from tests.test_split_kernels import GUARD_WINO, _winograd_ref
+    assert B.iolb_route(B.make_shape(N, C, H, W, K, algo=B.WINO_ALGO[m]))[0] == B.ROUTE_SPLIT
+    x, w = make_inputs(N, C, H, W, K, 3, 3, "u11", "he", seed=m + C)
+    x, w = x.copy(), w.copy()
+    x[1] *= np.float32(1e-9)
+    x[2] *= np.float32(1e12)
+    x[3, :, 1, 1] *= np.float32(1e4)
+    w[1] *= np.float32(1e-20)
+    w[2] *= np.float32(1e15)
+    w[3, :64] *= np.float32(1e-8)
+    w[4] = 0
+    xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+    ref, U = _winograd_ref(torch, xd, wd, 1), B.winograd_transform_kernels(wd, m)[0]
+    for y in (B.conv_winograd(xd, wd, m), B.conv_winograd_pre(xd, U, K, m)):
+        for i in range(5):
+            for k in range(6):
+                r = ref[i, k].cpu().numpy()
+                assert np.abs(y[i, k].cpu().numpy() - r).max() <= GUARD_WINO[m] * max(np.sqrt(np.mean(r * r)), 1e-300), (i, k)
