@@ -582,7 +582,7 @@ int run_winograd_split(const float* x, const float* w, const float* Upre, float*
     if (p.kind == SplitWino::FUSED) {
         IOLB_HIP(iolb::launch_wino_split_weights(w ? w : Upre, !w, U, p.f, st));
         MainKernelTimer timer(st, IOLB_TIME_WINO_FUSED);
-        IOLB_HIP(iolb::launch_wino_split(x, U, y, p.f, st));
+        IOLB_HIP(iolb::launch_wino_split(x, U, w ? w : Upre, !w, y, p.f, st));
         timer.stop(st);
         return IOLB_OK;
     }

@@ -263,13 +263,14 @@ hipError_t launch_wino_fused_mfma(const float* x, const float* U2, float* y, con
 // The same with one wave per plane row and the input transform shared out over all threads (wino_fused_rows.hip).
 hipError_t launch_wino_fused_rows(const float* x, const float* U2, float* y, const WinoGeom& g, hipStream_t st);
 
-// All four steps in one kernel on the bf16 matrix cores with operands in three parts, m in {2, 4} (wino_split.hip).
+// All four steps in one kernel on the 16-bit matrix cores m in {2, 4} (wino_split.hip).
 struct WinoSplitGeom {
     int N, C, H, W, K, m, pad, P, Q;
     int th, tw, tiles;         // sub-domains along H_out, W_out; in all
     int tb, z;                 // block: tb sub-domains by z kernels, every plane
     int nbt, nbk;              // blocks along the sub-domains, the kernels
     int chunks, Kb32;          // stages of 16 channels; 32-kernel blocks, whole workgroup blocks
+    int parts;                 // of an operand: 3 of bf16, 2 of fp16
 };
 // ... and what it divides workgroup ids and sub-domains by, where small says that this is exact (per_image: th * tw)
 struct WinoSplitDivisors {
@@ -283,6 +284,8 @@ inline WinoSplitDivisors wino_split_divisors(const WinoSplitGeom& g)
     const bool small = (g.tiles + 64LL) * per_image < (1LL << 31) && (long long)g.nbt * g.nbk * g.nbt < (1LL << 31);
     return {Divisor(g.nbt), Divisor(per_image), Divisor(g.tw), small};
 }
+// LDS of its buffers: two of V, 64 bytes per plane and sub-domain, or the channel sums of 32 kernels, 34 floats
+constexpr int wino_split_buffers(int m, int tb) { return (m + 2) * (m + 2) * tb * (34 * 4); }
 #define IOLB_WINO_SPLIT_SHAPES(X) X(4, 32, 64) X(4, 32, 32) X(2, 64, 64) X(2, 32, 32)
 inline long long wino_split_weight_bytes(const WinoSplitGeom& g) { return (g.m + 2LL) * (g.m + 2) * g.chunks * g.Kb32 * 3072; }
 // Whether the kernel's 32-bit offsets reach: the images of a block, the kernels.
@@ -317,9 +320,10 @@ __host__ __device__ inline int wino_split_offset(const WinoSplitGeom& g, int c0,
     const int last = g.H + g.pad - 1, row = COLS == WINO_COLS_SINGLE && r > last ? last : r;
     return 4 * ((c0 < g.C ? c0 : 0) * (g.H * g.W) + row * g.W);
 }
-// The kernels in three parts, from w[K][C][3][3] or (given) from a caller's U[plane][C rounded up to 16][K to 32].
+// The kernels in two (which do not fill their room) or three parts, from w[K][C][3][3] or (given) from a caller's U[plane][C rounded up to 16][K to 32].
 hipError_t launch_wino_split_weights(const float* w, bool given, void* wt, const WinoSplitGeom& g, hipStream_t st);
-hipError_t launch_wino_split(const float* x, const void* wt, float* y, const WinoSplitGeom& g, hipStream_t st);
+// (w, given: what they were made from, for blocks that are taken again)
+hipError_t launch_wino_split(const float* x, const void* wt, const float* w, bool given, float* y, const WinoSplitGeom& g, hipStream_t st);
 
 // Ceiling probes (probe.hip).  The copy moves bytes / 16 16-byte pieces; the MFMA loop runs
 // PROBE_MFMA_BLOCKS workgroups of four waves, each wave PROBE_ACC MFMAs (4096 flop each) per iteration, and

@@ -148,11 +148,13 @@ __device__ __forceinline__ unsigned finite_bits(float v)
     return u < 0x7f800000u ? u : 0u;
 }
 // 2^e for a sample whose largest value has these bits, as that of a float and as it is; a sample of zeros counts as one up to 1.
+// (TOP: the sample's largest value goes below 2^TOP)
+template <int TOP = HALF_TOP>
 __device__ __forceinline__ unsigned half_scale_bits(unsigned largest)
 {
-    const int e = HALF_TOP + 126 - (int)(largest >> 23);
+    const int e = TOP + 126 - (int)(largest >> 23);
     const int kept = e < HALF_DOWN ? HALF_DOWN : e > HALF_UP ? HALF_UP : e;
-    return (unsigned)(127 + (largest == 0 ? HALF_TOP - 1 : kept)) << 23;
+    return (unsigned)(127 + (largest == 0 ? TOP - 1 : kept)) << 23;
 }
 __device__ __forceinline__ float half_unscale(unsigned scale_bits) { return __uint_as_float((254u << 23) - scale_bits); }
 // The largest magnitude of eight values, 0 where one of them is not finite.

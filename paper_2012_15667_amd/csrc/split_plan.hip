@@ -292,6 +292,12 @@ bool split_point_faster(const iolb_shape& s, int P, int Q)
     return s.C >= 160 && flop >= 48 * bytes && flop >= 1e9;
 }
 
+// Sums of fewer channels keep three bf16 parts, whose error is smaller there (F(2 x 2), 16 channels 1.0e-7 against 1.3e-7, 48 1.7e-7 and
+// 1.9e-7; F(4 x 4) 3.7e-7 and 5.4e-7, 1.2e-6 and 1.3e-6; from 64 on that of two fp16 parts is), and which are up to 12 % faster there;
+// so do a few more in a single round of workgroups, where the sample of two parts costs more than its products save (64 -> 64 at 28 x 28,
+// batch 8, F(2 x 2) 13.1 and 13.3 us).
+constexpr int WINO_TWO_LEAST = 64, WINO_TWO_SMALL = 96;
+
 // Modelled time of a call: the kernels' transform, and per round of workgroups first loads and stores and a stage of 16
 // channels.  Fitted on 148 drawn layers (16 to 512 channels, 7 x 7 to 224 x 224, batch 1 to 64); on 2862 others within 9 (F(2 x 2))
 // and 12 % (F(4 x 4)) in the 2-norm, above 200 us 9 and 11 % too low (128 -> 128 at 112 x 112, batch 64, F(4 x 4) 494 us for 570).
@@ -321,6 +327,7 @@ bool wino_split_plan(WinoSplitGeom* g, double* ns)
         t.nbk = (g->K + sh.z - 1) / sh.z;
         t.chunks = (g->C + 15) / 16;
         t.Kb32 = t.nbk * (sh.z / 32);
+        t.parts = g->C < WINO_TWO_LEAST || (g->C < WINO_TWO_SMALL && (long long)t.nbt * t.nbk <= 256) ? 3 : 2;
         if (!wino_split_fits(t)) continue;
         const double c = wino_split_ns(t);
         if (!found || c < best_ns) { found = true; best = t; best_ns = c; }
@@ -364,7 +371,7 @@ int split_wino_pick(const iolb_shape& s, const iolb_tile_config& tile, long long
     }
     best *= m == 2 || m == 4 ? 0.93 : 0.85;
     int pick = 0;
-    if (product_cycles && product < best) { best = product; pick = 1; }
+    if (product_cycles && s.C >= WINO_TWO_LEAST && product < best) { best = product; pick = 1; }
     if (fused_ns && fused_ns < best) pick = 2;
     return pick;
 }

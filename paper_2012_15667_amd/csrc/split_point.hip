@@ -22,19 +22,13 @@
 // lane holds NB neighbours of each output channel and stores them at once.
 #include "kernels.h"
 #include "split_mfma.h"
-#include "wino_mats.h"
+#include "split_weights.h"
 
 #include <type_traits>
 
 namespace iolb {
 
 namespace {
-
-// Element j of row `row` of the kernel transform's L.
-__device__ __forceinline__ float kernel_coefficient(int m, int row, int j)
-{
-    return m == 2 ? Mats<2>::L[row][j] : m == 3 ? Mats<3>::L[row][j] : m == 4 ? Mats<4>::L[row][j] : Mats<6>::L[row][j];
-}
 
 template <int MB, int NB, int WM, int WN, int IN, bool VPX>
 __global__ void __launch_bounds__(64 * WM * WN, 2)
@@ -407,33 +401,14 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    // The kernels as the caller holds them: their two parts are not always all of them.
-    float li[3] = {0.f, 0.f, 0.f}, lj[3] = {0.f, 0.f, 0.f};
-    if (g.raw == SPLIT_RAW_TAPS) {
-        const int n = g.m + 2;
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            li[j] = kernel_coefficient(g.m, group / n, j);
-            lj[j] = kernel_coefficient(g.m, group % n, j);
-        }
-    }
-    auto kernel_value = [&](int k, int c) {
-        if (k >= g.K || c >= g.C) return 0.f;
-        if (g.raw == SPLIT_RAW_ROWS) return w[(size_t)k * g.C + c];
-        if (g.raw == SPLIT_RAW_PLANES) return w[((size_t)group * ((g.C + 15) / 16 * 16) + c) * ((g.K + 31) / 32 * 32) + k];
-        const float* t = w + ((size_t)k * g.C + c) * 9;
-        float u = 0.f;
-#pragma unroll
-        for (int j = 0; j < 3; ++j) u += lj[j] * (li[0] * t[j] + (li[1] * t[3 + j] + li[2] * t[6 + j]));
-        return u;
-    };
+    const RawKernels raw(w, g.raw, g.m, group, g.C, g.K);
 #pragma unroll 1
     for (int ch = 0; ch < nchunks; ++ch) {
         float wv[MB][8];
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int j = 0; j < 8; ++j) wv[mb][j] = kernel_value((kb16 + mb) * 16 + col16, 32 * ch + c0 + j);
+            for (int j = 0; j < 8; ++j) wv[mb][j] = raw.at((kb16 + mb) * 16 + col16, 32 * ch + c0 + j);
         static_range<0, NB>([&](auto nb_c) {
             constexpr int nb = decltype(nb_c)::value;
             float v[8];

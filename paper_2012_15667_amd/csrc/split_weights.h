@@ -4,7 +4,9 @@
 #ifndef IOLB_SPLIT_WEIGHTS_H
 #define IOLB_SPLIT_WEIGHTS_H
 
+#include "kernels.h"
 #include "split_mfma.h"
+#include "wino_mats.h"
 #include "wino_transform.h"
 
 namespace iolb {
@@ -46,15 +48,16 @@ __device__ __forceinline__ void store_parts(u32x4* to, const unsigned short (&p)
     }
 }
 
-// The piece of eight transformed kernel elements in two fp16 parts, scaled already, of kernel lane & 15 and the channels of lane >> 4; the
-// four lanes that share a kernel judge it together (of `channels` < 16 some are all small now and then: not judged).  NaN in place
-// of a kernel too small for its scale.
+// The piece of eight transformed kernel elements in two fp16 parts, scaled already, of kernel lane % KERNELS and the channels of lane / KERNELS; the
+// lanes that share a kernel, lane % KERNELS, judge it together (of `channels` < 16 some are all small now and then: not judged).  NaN in
+// place of a kernel too small for its scale.
+template <int KERNELS>
 __device__ __forceinline__ void store_halves(u32x4* to, const float (&u)[8], int channels)
 {
     u32x4 h, l;
     float most = half_eight(u, 1.f, h, l);
-    most = __builtin_fmaxf(most, __shfl_xor(most, 16));
-    most = __builtin_fmaxf(most, __shfl_xor(most, 32));
+#pragma unroll
+    for (int d = KERNELS; d < 64; d *= 2) most = __builtin_fmaxf(most, __shfl_xor(most, d));
     const unsigned poison = channels >= 16 && most != 0.f && most < HALF_LEAST ? 0x7e007e00u : 0u;
 #pragma unroll
     for (int i = 0; i < 4; ++i) h[i] |= poison;
@@ -64,6 +67,92 @@ __device__ __forceinline__ void store_halves(u32x4* to, const float (&u)[8], int
 // The channel of spot 0 ... 15 at which kernels are sampled for their scale: two elements of each, g[0][0] and g[2][2], which are also
 // elements of the transformed kernel, times a power of two.
 __device__ __forceinline__ int sampled_channel(int spot, int C) { return (int)((long long)C * spot >> 4); }
+// The sample of kernel k from w[K][C][3][3]: one value in each of lanes 0 ... 31.
+__device__ __forceinline__ float sampled_value(const float* __restrict__ w, int k, int K, int C, int lane)
+{
+    const bool exists = lane < 32 && k < K;
+    const float v = w[exists ? ((size_t)k * C + sampled_channel(lane >> 1, C)) * 9 + 8 * (lane & 1) : 0];
+    return exists ? v : 0.f;
+}
+// The scale of kernel k from U[plane][rows][cols]; the 64 / KERNELS lanes that share it take their part of the channels each.
+template <int M, int KERNELS>
+__device__ __forceinline__ unsigned scale_of_given(const float* __restrict__ U, int k, int K, int C, int rows, int cols, int lane)
+{
+    constexpr int n = M + 2, SPOTS = 16 * KERNELS / 64;
+    // L begins and ends with a row of one element, a power of two
+    static_assert(Mats<M>::L[n - 1][2] == 1.f && Mats<M>::L[0][1] == 0.f && Mats<M>::L[0][2] == 0.f && Mats<M>::L[n - 1][0] == 0.f && Mats<M>::L[n - 1][1] == 0.f);
+    constexpr float first = 1.f / (Mats<M>::L[0][0] * Mats<M>::L[0][0]);
+    float s0[SPOTS], s1[SPOTS];
+    const int kc = k < K ? k : 0;
+#pragma unroll
+    for (int j = 0; j < SPOTS; ++j) {
+        const size_t c = sampled_channel(lane / KERNELS * SPOTS + j, C);
+        s0[j] = U[c * cols + kc];
+        s1[j] = U[((size_t)(n * n - 1) * rows + c) * cols + kc];
+    }
+    unsigned some = 0;
+#pragma unroll
+    for (int j = 0; j < SPOTS; ++j) {
+        const unsigned a = finite_bits(s0[j] * first), b = finite_bits(s1[j]);
+        some = a > some ? a : some;
+        some = b > some ? b : some;
+    }
+    some = k < K ? some : 0u;
+#pragma unroll
+    for (int d = KERNELS; d < 64; d *= 2) {
+        const unsigned o = __shfl_xor(some, d);
+        some = o > some ? o : some;
+    }
+    return half_scale_bits(some);
+}
+// What brings row `row` of a transformed kernel to the size of the kernel.
+template <int M>
+__device__ __forceinline__ float row_up(int row)
+{
+    float up = 1.f;
+    static_for<M + 2>([&](auto r) { if (row == decltype(r)::value) up = power_of_two(kernel_up<M>(decltype(r)::value)); });
+    return up;
+}
+// ... and back.
+template <int M>
+__device__ __forceinline__ float row_down(int row)
+{
+    float down = 1.f;
+    static_for<M + 2>([&](auto r) { if (row == decltype(r)::value) down = power_of_two(-kernel_up<M>(decltype(r)::value)); });
+    return down;
+}
+
+// A transformed kernel element as the caller's kernels give it, for blocks that are taken again (their two parts are not always all of it):
+// from w[K][C] (no transform), U[plane][C rounded up to 16][K rounded up to 32] or w[K][C][3][3].
+struct RawKernels {
+    const float* w;
+    int raw, plane, C, K;
+    float li[3], lj[3];
+    __device__ __forceinline__ RawKernels(const float* from, int kind, int m, int which, int channels, int kernels) : w(from), raw(kind), plane(which), C(channels), K(kernels)
+    {
+        const int n = m + 2, row = kind == SPLIT_RAW_TAPS ? plane / n : 0, col = kind == SPLIT_RAW_TAPS ? plane % n : 0;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            li[j] = kind == SPLIT_RAW_TAPS ? coefficient(m, row, j) : 0.f;
+            lj[j] = kind == SPLIT_RAW_TAPS ? coefficient(m, col, j) : 0.f;
+        }
+    }
+    static __device__ __forceinline__ float coefficient(int m, int row, int j)
+    {
+        return m == 2 ? Mats<2>::L[row][j] : m == 3 ? Mats<3>::L[row][j] : m == 4 ? Mats<4>::L[row][j] : Mats<6>::L[row][j];
+    }
+    __device__ __forceinline__ float at(int k, int c) const
+    {
+        if (k >= K || c >= C) return 0.f;
+        if (raw == SPLIT_RAW_ROWS) return w[(size_t)k * C + c];
+        if (raw == SPLIT_RAW_PLANES) return w[((size_t)plane * ((C + 15) / 16 * 16) + c) * ((K + 31) / 32 * 32) + k];
+        const float* t = w + ((size_t)k * C + c) * 9;
+        float u = 0.f;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) u += lj[j] * (li[0] * t[j] + (li[1] * t[3 + j] + li[2] * t[6 + j]));
+        return u;
+    }
+};
 
 // Row `row` (the same in every lane of a wave) of L g for eight channels, g[3][3] one after the other from `from` on.  A branch per
 // row: with every row computed and one selected, the launch that the input transform shares took 254 registers in F(3 x 3), 210 in

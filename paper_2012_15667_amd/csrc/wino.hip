@@ -61,13 +61,6 @@ kernel_transform(const float* __restrict__ w, float* __restrict__ U, int C, int 
 // steps, [xi][chunk of 32 channels][16-kernel block][part][lane][8 channels].  One workgroup per 32 channels of 16 kernels, a
 // wave per row of the planes in turn.  Bound by its stores once the rows of w come through LDS: 512 x 512 kernels in F(2 x 2)
 // (in three parts 25 MB) 30 -> 8 us; gathered by their lanes they cost a cache line per lane and load, in every row of the planes again.
-template <int M>
-__device__ __forceinline__ float row_up(int row)
-{
-    float up = 1.f;
-    static_for<Mats<M>::n>([&](auto r) { if (row == decltype(r)::value) up = power_of_two(kernel_up<M>(decltype(r)::value)); });
-    return up;
-}
 constexpr int SPLIT_ROW = 32 * 9, SPLIT_ROW_PITCH = SPLIT_ROW + 1;
 template <int M>
 __device__ __forceinline__ void kernel_transform_split_block(const float* __restrict__ w, u32x4* __restrict__ wt, int C, int K, int chunks, int Kb16,
@@ -80,12 +73,7 @@ __device__ __forceinline__ void kernel_transform_split_block(const float* __rest
     // each kernel's scale, the same in all of its workgroups
     float some[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int k = kb * 16 + wave * 4 + j;
-        const bool exists = lane < 32 && k < K;
-        some[j] = w[exists ? ((size_t)k * C + sampled_channel(lane >> 1, C)) * 9 + 8 * (lane & 1) : 0];
-        some[j] = exists ? some[j] : 0.f;
-    }
+    for (int j = 0; j < 4; ++j) some[j] = sampled_value(w, kb * 16 + wave * 4 + j, K, C, lane);
     stage_kernels<16, 4, 5>(K > kb * 16 ? w + ((size_t)kb * 16 * C + ch * 32) * 9 : w, rows, wave, lane, C * 9LL, K - kb * 16, have, SPLIT_ROW, SPLIT_ROW_PITCH);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -100,7 +88,7 @@ __device__ __forceinline__ void kernel_transform_split_block(const float* __rest
         for (int e = threadIdx.x; e < n * n * 16; e += 256) {
             const int plane = e >> 4;
             float* back = reinterpret_cast<float*>(wt + ((size_t)plane * 192 + 128) * chunks * Kb16);
-            back[kb * 16 + (e & 15)] = half_unscale(scales[e & 15]) / (row_up<M>(plane / n) * row_up<M>(plane % n));
+            back[kb * 16 + (e & 15)] = half_unscale(scales[e & 15]) * (row_down<M>(plane / n) * row_down<M>(plane % n));
         }
 #pragma unroll 1
     for (int row = wave; row < n; row += 4) {
@@ -113,7 +101,7 @@ __device__ __forceinline__ void kernel_transform_split_block(const float* __rest
             const float up = scale * this_up * power_of_two(kernel_up<M>(J));
 #pragma unroll
             for (int c = 0; c < 8; ++c) u[c] = kernel_element<M, J>(lg[c]) * up;
-            store_halves(wt + (size_t)(row * n + J) * chunks * Kb16 * 192 + ((size_t)ch * Kb16 + kb) * 128 + lane, u, C - ch * 32);
+            store_halves<16>(wt + (size_t)(row * n + J) * chunks * Kb16 * 192 + ((size_t)ch * Kb16 + kb) * 128 + lane, u, C - ch * 32);
         });
     }
 }
@@ -130,43 +118,20 @@ __device__ __forceinline__ void split_planes_block(const float* __restrict__ U, 
     const int lane = (int)(in & 63), kb = (int)((in >> 6) % Kb16), ch = (int)((in >> 6) / Kb16);
     const int k = kb * 16 + (lane & 15), c0 = ch * 32 + (lane >> 4) * 8;
     constexpr int n = Mats<M>::n;
-    float u[8], s0[4], s1[4];
-    const int kc = k < K ? k : 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const size_t c = sampled_channel((lane >> 4) * 4 + j, C);
-        s0[j] = U[c * cols + kc];
-        s1[j] = U[((size_t)(n * n - 1) * rows + c) * cols + kc];
-    }
+    const unsigned scale = scale_of_given<M, 16>(U, k, K, C, rows, cols, lane);
+    float u[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         const bool exists = k < K && c0 + j < C;
         u[j] = U[exists ? ((size_t)plane * rows + c0 + j) * cols + k : 0];
         u[j] = exists ? u[j] : 0.f;
     }
-    // (g[0][0] and g[2][2] of the sampled channels: L begins and ends with a row of one element, a power of two)
-    constexpr float first = 1.f / (Mats<M>::L[0][0] * Mats<M>::L[0][0]);
-    static_assert(Mats<M>::L[n - 1][2] == 1.f && Mats<M>::L[0][1] == 0.f && Mats<M>::L[0][2] == 0.f && Mats<M>::L[n - 1][0] == 0.f && Mats<M>::L[n - 1][1] == 0.f);
-    unsigned some = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const unsigned a = finite_bits(s0[j] * first), b = finite_bits(s1[j]);
-        some = a > some ? a : some;
-        some = b > some ? b : some;
-    }
-    some = k < K ? some : 0u;
-#pragma unroll
-    for (int d = 16; d < 64; d *= 2) {
-        const unsigned o = __shfl_xor(some, d);
-        some = o > some ? o : some;
-    }
-    const unsigned scale = half_scale_bits(some);
     const float up = row_up<M>(plane / n) * row_up<M>(plane % n);
     u32x4* const to = wt + (size_t)plane * chunks * Kb16 * 192;
-    if (ch == 0 && lane < 16) reinterpret_cast<float*>(to + (size_t)128 * chunks * Kb16)[k] = half_unscale(scale) / up;
+    if (ch == 0 && lane < 16) reinterpret_cast<float*>(to + (size_t)128 * chunks * Kb16)[k] = half_unscale(scale) * (row_down<M>(plane / n) * row_down<M>(plane % n));
 #pragma unroll
     for (int j = 0; j < 8; ++j) u[j] *= __uint_as_float(scale) * up;
-    store_halves(to + ((size_t)ch * Kb16 + kb) * 128 + lane, u, C - ch * 32);
+    store_halves<16>(to + ((size_t)ch * Kb16 + kb) * 128 + lane, u, C - ch * 32);
 }
 
 // step 1a: one lane per (c, t); t runs fastest.  VEC (m = 2 or 4, W a multiple of m, x aligned to

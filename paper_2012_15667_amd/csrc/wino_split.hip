@@ -1,20 +1,23 @@
-// Winograd F(2 x 2, 3 x 3) and F(4 x 4, 3 x 3) in one kernel on the bf16 matrix cores at fp32 precision (operands in three
-// parts, split_mfma.h).  A workgroup of eight waves takes TB sub-domains by Z kernels in every one of the (m + 2)^2 planes;
-// the channel sums of all planes stay in registers until the last channel, so that V and M never leave the chip.
+// Winograd F(2 x 2, 3 x 3) and F(4 x 4, 3 x 3) in one kernel on the 16-bit matrix cores at fp32 precision (operands in two
+// fp16 parts, of few channels in three of bf16: split_mfma.h).  A workgroup of eight waves takes TB sub-domains by Z kernels in every one
+// of the (m + 2)^2 planes; the channel sums of all planes stay in registers until the last channel, so that V and M never leave the chip.
 //
-// A stage is 16 channels, one contraction of v_mfma_f32_32x32x16_bf16.  Each thread transforms TB / 32 windows of inputs
+// A stage is 16 channels, one contraction of a 32x32x16 matrix instruction.  Each thread transforms TB / 32 windows of inputs
 // (loaded one stage ahead) and puts V in LDS in fp32, in one of two buffers; each wave multiplies PL / 8 planes: it cuts its V
 // into parts between the matrix instructions of the plane before, and takes the transformed kernels, already in parts, from
 // the L2 into registers some units ahead.  Each V is cut once and each kernel part read once per workgroup.
 //
-// What bounds it: kernel parts from the L2 (F(4 x 4), 32 x 64: 221 KB per stage for 3456 clocks of matrix work at 62 bytes per
-// clock and unit; left out, 520 -> 350 us), the vector work of transform and cut (left out, 317), inputs (left out, 395) and
-// first loads and stores of a round (436); each alone hides behind the others only in part.  Matrix cores are busy 0.24 - 0.25 of the
-// cycles there, 0.34 - 0.39 on F(2 x 2), 64 x 64 (counters of whole layers).  Whole calls, fp32 way -> this:
-// F(4 x 4) 128 -> 128 at 112 x 112, batch 64 859 -> 582 us (102 TFLOP/s of the planes' products), 256 -> 256 at 14 x 14 87 ->
-// 59, F(2 x 2) 256 -> 256 at 56 x 56 1104 -> 736, 64 -> 64 at 28 x 28, batch 8 19.8 -> 13.2.
-// Registers: F(4 x 4), 32 x 64 has 256 and spills 5 (24 bytes a lane; 14 and 44 where columns are read one by one), the other blocks
-// none.
+// Two parts: inputs are scaled before their transform, per image of the block by a sample of its first stage and a few channels more;
+// kernels per kernel, their planes brought to the same size.  A sub-domain whose windows are all too small for the scale, like a sum that
+// is not finite, has its block taken again.
+//
+// What bounds it, F(4 x 4), 32 x 64, 128 -> 128 at 112 x 112, batch 64: of the 46 us that a block lives, 10 pass before its first product
+// and 9 after its last, with one block on a unit; a stage takes 3.4, 1.7 of them products and waiting for kernel parts (147 KB from the L2), the rest
+// the transform.  (Kernel parts from one place in place of the L2's: 2 % less; no scales: 1 %.)  Whole calls, fp32 way / three
+// bf16 parts / this: that layer 859 / 581 / 496 us (119 TFLOP/s of the planes' products), F(4 x 4) 256 -> 256 at 14 x 14 87 / 60 / 52,
+// F(2 x 2) 64 -> 64 at 28 x 28, batch 8 (three parts) 19.8 / 13.2.
+// Channel sums through LDS two at a time, and no division by the planes' scales: 506 -> 496.
+// Registers: F(4 x 4), 32 x 64 has 251, three parts 256 and spill 5 (24 bytes a lane; 13 and 44 where columns are read one by one).
 // A block with a sum that is not finite is taken again by all its waves, stage by stage without overlap: one NaN adds the time of one
 // such block (256 -> 256 at 14 x 14 64 -> 155 us, 64 -> 64 at 28 x 28, batch 8 14.9 -> 25.5, where the fp32 kernels took 94 and 20.5 whatever the
 // values), all NaN takes 2.1 - 2.8 times as long (128 -> 128 at 112 x 112 600 -> 1690 us, fp32 kernel 860).  With the next stage's inputs
@@ -34,6 +37,7 @@ namespace iolb {
 namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 // M outputs of a row, at any float
 template <int M> using row_of = float __attribute__((ext_vector_type(M), aligned(4)));
 
@@ -73,9 +77,10 @@ __device__ __forceinline__ void output_transform_1d(const float (&v)[M + 2], flo
 // Whether this lane's bit of a wave-uniform mask is set: a select reads the mask as it is.
 __device__ __forceinline__ bool by_lane(unsigned long long mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
 
-template <int M, int TB, int Z, int COLS>
+template <int M, int TB, int Z, int COLS, int PARTS>
 __global__ void __launch_bounds__(512, M == 2 && TB == 32 && Z == 32 ? 4 : 2)
-wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restrict__ y, WinoSplitGeom g, WinoSplitDivisors dv)
+wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restrict__ y, WinoSplitGeom g, WinoSplitDivisors dv, const float* __restrict__ w_raw,
+                  int raw)
 {
     constexpr int n = M + 2, PL = n * n, ZB = Z / 32, TBB = TB / 32;
     constexpr int FP = PL / 8, LP = PL % 8;                  // whole planes per wave, planes left over: 4 ZB units for 8 waves
@@ -83,9 +88,21 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
     constexpr int D = UNITS % 3 == 0 ? 3 : UNITS == 4 ? 2 : UNITS;       // units of kernels in flight
     constexpr int WIN = TB / 32;                             // windows per thread and stage
     constexpr int VBUF = PL * TB * 64;
+    constexpr bool TWO = PARTS == 2;                         // operands in two fp16 parts, else in three of bf16
+    constexpr unsigned UNIT = 1024u * PARTS;                 // bytes of a unit
     static_assert(LP == 0 || LP == 4, "left-over planes");
+    // Inputs are scaled so that V, up to 100 and 4 times as large in F(4 x 4) and F(2 x 2), has the room above it that other operands have.
+    // What a transform rounds off is at least 2^-25 of V's parts where a window has a value of 2^-4 and 2^-2.
+    constexpr int TOP = M == 4 ? 4 : 7;
+    constexpr float LEAST = M == 4 ? 0.0625f : 0.25f;
     extern __shared__ u32x4 lds16[];
     char* const lds = reinterpret_cast<char*>(lds16);
+    // behind the buffers: whether a block is taken again; what undoes the kernels' scales; per image of the block the largest value of the
+    // sample that sets its scale; per sub-domain the largest value of its windows, scaled
+    int* const any = reinterpret_cast<int*>(lds + wino_split_buffers(M, TB));
+    float* const kback = reinterpret_cast<float*>(any + 4);
+    unsigned* const sample = reinterpret_cast<unsigned*>(kback + Z);
+    unsigned* const most = sample + TB;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
@@ -117,7 +134,7 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
     const unsigned xlo = __builtin_amdgcn_readfirstlane((unsigned)xb), xhi = __builtin_amdgcn_readfirstlane((unsigned)(xb >> 32));
     const unsigned xrange = __builtin_amdgcn_readfirstlane(wino_split_range(g, span));
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>((unsigned long long)xhi << 32 | xlo), 0, (int)xrange, 0x00020000);
-    const unsigned ubytes = __builtin_amdgcn_readfirstlane((unsigned)g.chunks * (unsigned)g.Kb32 * (3072u * PL));
+    const unsigned ubytes = __builtin_amdgcn_readfirstlane((unsigned)g.chunks * (unsigned)g.Kb32 * (UNIT * PL));
     const __amdgpu_buffer_rsrc_t ru = __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4*>(wt), 0, (int)ubytes, 0x00020000);
 
     // this thread's windows: a wave takes 4 channels of 16 sub-domains, a row of 16 lanes each.  A lane loads the M columns
@@ -126,10 +143,14 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
     const int tloc = (TB == 32 ? wave & 1 : wave & 3) * 16 + (lane & 15), cl = c0w + (lane >> 4);
     unsigned long long rowok[n], colok[M], left, right, edge;            // by lane: one register pair each, as the selects read them
     unsigned xoff, eoff;
+    int image_in;                                           // of the block
+    bool tile_exists;
     {
         const int t = t0 + tloc, tt = t < g.tiles ? t : t0;
         int img, ti, tj;
         place(tt, img, ti, tj);
+        image_in = img - img0;
+        tile_exists = t < g.tiles;
         const int h0 = ti * M - g.pad, w0 = tj * M - g.pad;
         auto lanes = [](bool v) { return __builtin_amdgcn_ballot_w64(v); };
 #pragma unroll
@@ -173,6 +194,7 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
     };
     // V in LDS: [plane][four channels][sub-domain][4]
     const int vw = cl / 4 * (TB * 16) + tloc * 16 + (cl & 3) * 4;
+    float xs = 1.f, top = 0.f;                              // this thread's image's scale; the largest value of its windows, scaled
     auto transform = [&](Windows& wx, char* vb) {
         static_range<0, WIN>([&](auto ic) {
             constexpr int i = decltype(ic)::value;
@@ -181,6 +203,11 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
                 for (int r = 0; r < n; ++r)
 #pragma unroll
                     for (int j = 1; j < M; ++j) wx[i][r][j + 1] = by_lane(colok[j]) ? wx[i][r][j + 1] : 0.f;
+            if constexpr (TWO)
+#pragma unroll
+                for (int r = 0; r < n; ++r)
+#pragma unroll
+                    for (int j = 0; j <= M; ++j) wx[i][r][j] *= xs;
 #pragma unroll
             for (int r = 0; r < n; ++r) {
                 const int e = __float_as_int(wx[i][r][0]);
@@ -189,6 +216,9 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
                 const float rg = __int_as_float(__builtin_amdgcn_update_dpp(e, __float_as_int(wx[i][r][1]), 0x101, 0xf, 0xf, false));
                 wx[i][r][0] = by_lane(left) ? lf : 0.f;
                 wx[i][r][n - 1] = by_lane(right) ? rg : 0.f;
+                if constexpr (TWO)
+#pragma unroll
+                    for (int j = 0; j < n; ++j) top = __builtin_fmaxf(top, __builtin_fabsf(wx[i][r][j]));
             }
 #pragma unroll
             for (int j = 0; j < n; ++j) {
@@ -213,16 +243,16 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
     // kernels: plane p of this wave, unit zb of it; the left-over unit
     const int xplane = 8 * FP + (ZB == 2 ? wave >> 1 : wave & 3), xzb = ZB == 2 ? wave & 1 : 0;
     const bool has_extra = LP && (ZB == 2 || wave < 4);
-    const unsigned pstride = (unsigned)g.chunks * (unsigned)g.Kb32 * 3072u;
+    const unsigned pstride = (unsigned)g.chunks * (unsigned)g.Kb32 * UNIT;
     auto unit_at = [&](int u, int s) {                      // byte offset of unit u (a constant) of stage s
-        const unsigned at = (unsigned)(s * g.Kb32 + kb * ZB) * 3072u;
-        if (LP && u == UNITS - 1) return at + (unsigned)xplane * pstride + xzb * 3072u;
-        return at + (unsigned)(wave * FP + u / ZB) * pstride + u % ZB * 3072u;
+        const unsigned at = (unsigned)(s * g.Kb32 + kb * ZB) * UNIT;
+        if (LP && u == UNITS - 1) return at + (unsigned)xplane * pstride + xzb * UNIT;
+        return at + (unsigned)(wave * FP + u / ZB) * pstride + u % ZB * UNIT;
     };
-    u32x4 a[D][3];
-    auto load_u = [&](u32x4 (&f)[3], unsigned at) {
+    u32x4 a[D][PARTS];
+    auto load_u = [&](u32x4 (&f)[PARTS], unsigned at) {
 #pragma unroll
-        for (int p = 0; p < 3; ++p) f[p] = __builtin_amdgcn_raw_buffer_load_b128(ru, lane * 16 + 1024 * p, (int)at, 0);
+        for (int p = 0; p < PARTS; ++p) f[p] = __builtin_amdgcn_raw_buffer_load_b128(ru, lane * 16 + 1024 * p, (int)at, 0);
     };
 
     f32x16 acc[FP][ZB][TBB], accx[TBB];
@@ -252,19 +282,20 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
     auto multiply = [&](int s, const char* vb) {
         const int next = s + 1 < nst ? s + 1 : s;
         auto plane_at = [&](int p) { return vb + (LP && p == FP ? xplane : wave * FP + p) * (TB * 64); };
-        u32x4 b[2][TBB][3];
+        u32x4 b[2][TBB][PARTS];
         f32x4 v[2];
         // pieces of four channels: 2 TBB of a plane
         auto fetch4 = [&](f32x4& o, int p, int piece) {
             o = *reinterpret_cast<const f32x4*>(plane_at(p) + r0 + (piece & 1) * (TB * 16) + (piece >> 1) * 512);
         };
-        auto cut4 = [&](u32x4 (&o)[TBB][3], const f32x4& f, int piece) {
+        auto cut4 = [&](u32x4 (&o)[TBB][PARTS], const f32x4& f, int piece) {
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                unsigned h, m, l;
-                split_pair(f[2 * j], f[2 * j + 1], h, m, l);
-                const int at = 2 * (piece & 1) + j;
-                o[piece >> 1][0][at] = h; o[piece >> 1][1][at] = m; o[piece >> 1][2][at] = l;
+                unsigned part[3];
+                if constexpr (TWO) half_pair(f[2 * j], f[2 * j + 1], part[0], part[1]);
+                else               split_pair(f[2 * j], f[2 * j + 1], part[0], part[1], part[2]);
+#pragma unroll
+                for (int q = 0; q < PARTS; ++q) o[piece >> 1][q][2 * (piece & 1) + j] = part[q];
             }
         };
         static_range<0, TBB>([&](auto tc) {
@@ -288,51 +319,58 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
                                                        if constexpr (PIECES > 2) cut4(b[(p + 1) & 1], v[decltype(ic)::value & 1], z * PIECES + decltype(ic)::value); });
                 if constexpr (PIECES <= 2)
                     static_range<0, PIECES>([&](auto ic) { cut4(b[(p + 1) & 1], v[decltype(ic)::value & 1], z * PIECES + decltype(ic)::value); });
-                u32x4 (&f)[3] = a[u % D];
+                u32x4 (&f)[PARTS] = a[u % D];
                 f32x16 (&c)[TBB] = EXTRA ? accx : acc[EXTRA ? 0 : p][EXTRA ? 0 : z];
                 const bool load = !LP || un != UNITS - 1 || has_extra;
                 const unsigned at = un < UNITS ? unit_at(un, s) : unit_at(un - UNITS, next);
-                constexpr int PA[6] = {2, 1, 1, 0, 0, 0}, PB[6] = {0, 1, 0, 2, 1, 0};
-                static_range<0, 6>([&](auto qc) {
+                // the products, small ones first; each part of the kernels is loaded again after its last
+                constexpr int PRODUCTS = TWO ? 3 : 6, PA[6] = {TWO ? 1 : 2, TWO ? 0 : 1, TWO ? 0 : 1, 0, 0, 0}, PB[6] = {0, 1, 0, 2, 1, 0};
+                constexpr auto last = [](int q) { return q == 0 || q == 2 || q == 5; };
+                static_range<0, PRODUCTS>([&](auto qc) {
                     constexpr int q = decltype(qc)::value;
 #pragma unroll
                     for (int t = 0; t < TBB; ++t)
-                        c[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f[PA[q]]), __builtin_bit_cast(bf16x8, b[p & 1][t][PB[q]]), c[t], 0, 0, 0);
-                    if constexpr (q == 0 || q == 2 || q == 5)
+                        if constexpr (TWO)
+                            c[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, f[PA[q]]), __builtin_bit_cast(f16x8, b[p & 1][t][PB[q]]), c[t], 0, 0, 0);
+                        else
+                            c[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f[PA[q]]), __builtin_bit_cast(bf16x8, b[p & 1][t][PB[q]]), c[t], 0, 0, 0);
+                    if constexpr (last(q))
                         if (load) f[PA[q]] = __builtin_amdgcn_raw_buffer_load_b128(ru, lane * 16 + 1024 * PA[q], (int)at, 0);
                 });
                 // per matrix instruction its share of the vector work
-                constexpr int VALU = (26 * PIECES + 6 * TBB - 1) / (6 * TBB) + 1;
+                constexpr int VALU = ((TWO ? 6 : 26) * PIECES + PRODUCTS * TBB - 1) / (PRODUCTS * TBB) + 1;
 #pragma unroll
-                for (int i = 0; i < 6; ++i) {
+                for (int i = 0; i < PRODUCTS; ++i) {
 #pragma unroll
                     for (int t = 0; t < TBB; ++t) {
                         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                         if constexpr (MORE) __builtin_amdgcn_sched_group_barrier(0x002, VALU, 0);
                     }
-                    if (i == 0 || i == 2 || i == 5) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+                    if (last(i)) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             });
         });
     };
 
-    // Channel sums leave the registers 32 kernels at a time, through LDS: [plane][kernel][tile]; a thread then owns whole
-    // (kernel, tile) pairs.
+    // Channel sums leave the registers 32 kernels at a time, through LDS: [plane][tile][kernel], 34 floats from tile to tile, so that a lane
+    // writes and reads two kernels at once and 32 tiles reach every bank once; a thread then owns whole (kernel, tile) pairs.
     constexpr int PAIRS = 32 * TB / 512;
     static_assert(ZB * PAIRS <= 32, "one mark per pair");
     unsigned again = 0;                                      // pairs whose sums are not all finite
-    auto finish = [&](auto marked_c, float scale) {
+    auto finish = [&](auto marked_c) {
         constexpr bool MARKED = decltype(marked_c)::value;   // the second time: marked pairs only
         float* const m = reinterpret_cast<float*>(lds);
         static_range<0, ZB>([&](auto zc) {
             constexpr int z = decltype(zc)::value;
             if constexpr (z) barrier();
             auto put = [&](int plane, const f32x16 (&c)[TBB]) {
+                const float scale = MARKED ? 1.f : TWO ? row_down<M>(plane / n) * row_down<M>(plane % n) : SPLIT_UNSCALE;
 #pragma unroll
                 for (int t = 0; t < TBB; ++t)
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) m[(plane * 32 + 8 * (i >> 2) + (i & 3) + 4 * half) * TB + 32 * t + l32] = c[t][i] * scale;
+                    for (int i = 0; i < 16; i += 2)
+                        *reinterpret_cast<f32x2*>(m + (plane * TB + 32 * t + l32) * 34 + 8 * (i >> 2) + (i & 3) + 4 * half) = f32x2{c[t][i] * scale, c[t][i + 1] * scale};
             };
             static_range<0, FP>([&](auto pc) { put(wave * FP + decltype(pc)::value, acc[decltype(pc)::value][z]); });
             if constexpr (LP != 0)
@@ -342,48 +380,70 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
             int img, ti, tj;
             place(t, img, ti, tj);
             const int h0 = ti * M, w0 = tj * M;
+            float back = 1.f;
+            bool lost = false;
+            if constexpr (TWO) {
+                back = half_unscale(half_scale_bits<TOP>(sample[t < g.tiles ? img - img0 : 0]));
+                lost = most[tl] - 1 < __float_as_uint(LEAST) - 1;
+            }
 #pragma unroll
-            for (int i = 0; i < PAIRS; ++i) {
-                const int kl = tid / TB + i * (512 / TB), k = kb * Z + 32 * z + kl, bit = z * PAIRS + i;
-                float v[n][n];
+            for (int i2 = 0; i2 < PAIRS / 2; ++i2) {
+                const int kl2 = 2 * (tid / TB + i2 * (512 / TB));
+                f32x2 both[n][n];
 #pragma unroll
                 for (int r = 0; r < n; ++r)
 #pragma unroll
-                    for (int j = 0; j < n; ++j) v[r][j] = m[((r * n + j) * 32 + kl) * TB + tl];
-                float h[n][M], o[M][M];
+                    for (int j = 0; j < n; ++j) both[r][j] = *reinterpret_cast<const f32x2*>(m + ((r * n + j) * TB + tl) * 34 + kl2);
 #pragma unroll
-                for (int r = 0; r < n; ++r) output_transform_1d<M>(v[r], h[r]);
+                for (int q2 = 0; q2 < 2; ++q2) {
+                    const int kl = kl2 + q2, k = kb * Z + 32 * z + kl, bit = z * PAIRS + 2 * i2 + q2;
+                    float v[n][n];
 #pragma unroll
-                for (int j = 0; j < M; ++j) {
-                    float c[n], q[M];
+                    for (int r = 0; r < n; ++r)
 #pragma unroll
-                    for (int r = 0; r < n; ++r) c[r] = h[r][j];
-                    output_transform_1d<M>(c, q);
+                        for (int j = 0; j < n; ++j) v[r][j] = both[r][j][q2];
+                    float h[n][M], o[M][M];
 #pragma unroll
-                    for (int r = 0; r < M; ++r) o[r][j] = q[r];
-                }
-                if (t >= g.tiles || k >= g.K) continue;
-                if constexpr (MARKED) {
-                    if (!(again >> bit & 1)) continue;
-                } else {
-                    // every plane enters one of the corners, with a factor that is not zero
-                    if (!(__builtin_fabsf(o[0][0]) <= 3.402823466e38f && __builtin_fabsf(o[0][M - 1]) <= 3.402823466e38f &&
-                          __builtin_fabsf(o[M - 1][0]) <= 3.402823466e38f && __builtin_fabsf(o[M - 1][M - 1]) <= 3.402823466e38f))
-                        again |= 1u << bit;
-                }
-                float* yp = y + ((size_t)img * g.K + k) * ((size_t)g.P * g.Q) + (size_t)h0 * g.Q + w0;
+                    for (int r = 0; r < n; ++r) output_transform_1d<M>(v[r], h[r]);
 #pragma unroll
-                for (int r = 0; r < M; ++r) {
-                    if (h0 + r >= g.P) break;
-                    if (w0 + M <= g.Q) {
-                        row_of<M> v;
+                    for (int j = 0; j < M; ++j) {
+                        float c[n], q[M];
 #pragma unroll
-                        for (int j = 0; j < M; ++j) v[j] = o[r][j];
-                        *reinterpret_cast<row_of<M>*>(yp + (size_t)r * g.Q) = v;
+                        for (int r = 0; r < n; ++r) c[r] = h[r][j];
+                        output_transform_1d<M>(c, q);
+#pragma unroll
+                        for (int r = 0; r < M; ++r) o[r][j] = q[r];
+                    }
+                    if (t >= g.tiles || k >= g.K) continue;
+                    if constexpr (MARKED) {
+                        if (!(again >> bit & 1)) continue;
                     } else {
+                        // every plane enters one of the corners, with a factor that is not zero
+                        if (lost || !(__builtin_fabsf(o[0][0]) <= 3.402823466e38f && __builtin_fabsf(o[0][M - 1]) <= 3.402823466e38f &&
+                              __builtin_fabsf(o[M - 1][0]) <= 3.402823466e38f && __builtin_fabsf(o[M - 1][M - 1]) <= 3.402823466e38f))
+                            again |= 1u << bit;
+                        if constexpr (TWO) {
+                            const float kscale = kback[32 * z + kl];
 #pragma unroll
-                        for (int j = 0; j < M; ++j)
-                            if (w0 + j < g.Q) yp[(size_t)r * g.Q + j] = o[r][j];
+                            for (int r = 0; r < M; ++r)
+#pragma unroll
+                                for (int j = 0; j < M; ++j) o[r][j] = o[r][j] * back * kscale;
+                        }
+                    }
+                    float* yp = y + ((size_t)img * g.K + k) * ((size_t)g.P * g.Q) + (size_t)h0 * g.Q + w0;
+#pragma unroll
+                    for (int r = 0; r < M; ++r) {
+                        if (h0 + r >= g.P) break;
+                        if (w0 + M <= g.Q) {
+                            row_of<M> v;
+#pragma unroll
+                            for (int j = 0; j < M; ++j) v[j] = o[r][j];
+                            *reinterpret_cast<row_of<M>*>(yp + (size_t)r * g.Q) = v;
+                        } else {
+#pragma unroll
+                            for (int j = 0; j < M; ++j)
+                                if (w0 + j < g.Q) yp[(size_t)r * g.Q + j] = o[r][j];
+                        }
                     }
                 }
             }
@@ -399,12 +459,44 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
         // before there are sums the registers hold two stages' windows: both are on their way before the first is waited for
         Windows first;
         load_x(first, 0);
+        // for the sample beside the first stage a value of each sub-domain from other channels, a wave four of them; the kernels' scales
+        float spread = 0.f, my_kback = 0.f;
+        if constexpr (TWO) {
+            const int sc = wave * g.C >> 3;
+            const unsigned long long have = __builtin_amdgcn_ballot_w64(sc + (lane >> 4) < g.C) & rowok[1] & colok[0];
+            spread = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rx, (int)((by_lane(have) ? xoff : OUTSIDE) + 4), wino_split_offset<COLS>(g, sc, 1), 0));
+            if (tid < Z) my_kback = reinterpret_cast<const float*>(reinterpret_cast<const char*>(wt) + (size_t)PL * pstride)[kb * Z + tid];
+        }
         static_range<0, D>([&](auto uc) {
             constexpr int u = decltype(uc)::value;
             if (!LP || u < UNITS - 1 || has_extra) load_u(a[u], unit_at(u, 0));
         });
         load_x(wx, 1);
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (TWO) {
+            if (tid < 2 * TB) sample[tid] = 0;                  // (most follows)
+            barrier();
+            unsigned largest = finite_bits(spread);
+            static_range<0, WIN>([&](auto ic) {
+                constexpr int i = decltype(ic)::value;
+#pragma unroll
+                for (int r = 0; r < n; ++r)
+#pragma unroll
+                    for (int j = 0; j < M; ++j) {
+                        const unsigned m = COLS == WINO_COLS_CUT && !by_lane(colok[j]) ? 0u : finite_bits(first[i][r][j + 1]);
+                        largest = m > largest ? m : largest;
+                    }
+            });
+            if (span == 1) {
+                largest = wave_max(largest);
+                if (lane == 0) atomicMax(sample, largest);
+            } else if (tile_exists && largest) {
+                atomicMax(sample + image_in, largest);
+            }
+            if (tid < Z) kback[tid] = my_kback;
+            barrier();
+            xs = __uint_as_float(half_scale_bits<TOP>(sample[image_in]));
+        }
         transform(first, lds);
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -427,27 +519,38 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
         __builtin_amdgcn_sched_barrier(0);
         if (!ahead) barrier();
     }
-    finish(std::false_type{}, SPLIT_UNSCALE);
-    int* const any = reinterpret_cast<int*>(lds + 2 * VBUF);
-    barrier();
+    if constexpr (TWO)
+        if (tile_exists) atomicMax(most + tloc, __float_as_uint(top));
     if (tid == 0) *any = 0;
+    barrier();
+    finish(std::false_type{});
     barrier();
     if (again) *any = 1;
     barrier();
     if (__builtin_amdgcn_readfirstlane(*any) == 0) return;
 
-    // The block again on the fp32 matrix instructions, from the same inputs; kernels are put together from their parts.
+    // The block again on the fp32 matrix instructions, from the same inputs; three parts hold all of a kernel, in place of two the
+    // caller's own is read.
     clear();
+    xs = 1.f;
 #pragma unroll 1
     for (int s = 0; s < nst; ++s) {
         load_x(wx, s);
         transform(wx, lds);
         barrier();
-        auto unit = [&](unsigned at, const char* vplane, f32x16 (&c)[TBB]) {
-            u32x4 f[3];
-            load_u(f, at);
+        auto unit = [&](int u, int plane, int z, f32x16 (&c)[TBB]) {
+            const char* vplane = lds + plane * (TB * 64);
             float w[8];
-            kept_eight(f[0], f[1], f[2], w);
+            if constexpr (TWO) {
+                // (opaque: nothing of it is computed, and kept in scalar registers, through the loop above)
+                const RawKernels kernels(w_raw, raw, M, opaque(plane), opaque(g.C), opaque(g.K));
+#pragma unroll
+                for (int j = 0; j < 8; ++j) w[j] = kernels.at(kb * Z + 32 * z + l32, 16 * s + 8 * half + j);
+            } else {
+                u32x4 f[PARTS];
+                load_u(f, unit_at(u, s));
+                kept_eight(f[0], f[1], f[PARTS - 1], w);
+            }
 #pragma unroll
             for (int t = 0; t < TBB; ++t) {
                 float v[8];
@@ -458,18 +561,19 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
         };
         static_range<0, FP * ZB>([&](auto uc) {
             constexpr int u = decltype(uc)::value;
-            unit(unit_at(u, s), lds + (wave * FP + u / ZB) * (TB * 64), acc[u / ZB][u % ZB]);
+            unit(u, wave * FP + u / ZB, u % ZB, acc[u / ZB][u % ZB]);
         });
         if constexpr (LP != 0)
-            if (has_extra) unit(unit_at(UNITS - 1, s), lds + xplane * (TB * 64), accx);
+            if (has_extra) unit(UNITS - 1, xplane, xzb, accx);
         barrier();
     }
-    finish(std::true_type{}, 1.f);
+    finish(std::true_type{});
 }
 
-// Kernels in three parts in the order of the kernel above: [plane][16 channels][32 kernels][part][lane][8 channels].
+// Kernels in two or three parts in the order of the kernel above: [plane][16 channels][32 kernels][part][lane][8 channels], and behind two
+// parts what undoes the scales of 32 Kb32 kernels.
 // One workgroup per 16 channels of 32 kernels of w[K][C][3][3], a wave per row of the planes in turn.
-template <int M>
+template <int M, int PARTS>
 __global__ void __launch_bounds__(256)
 wino_split_weights(const float* __restrict__ w, u32x4* __restrict__ wt, int C, int K, int chunks, int Kb32)
 {
@@ -478,24 +582,45 @@ wino_split_weights(const float* __restrict__ w, u32x4* __restrict__ wt, int C, i
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int kb = blockIdx.x % Kb32, ch = blockIdx.x / Kb32;
     const int have = C - ch * 16 < 16 ? (C - ch * 16) * 9 : LEN;
+    __shared__ unsigned scales[32];
+    float some[8];                                          // each kernel's scale, the same in all of its workgroups
+#pragma unroll
+    for (int j = 0; j < 8; ++j) some[j] = PARTS == 2 ? sampled_value(w, kb * 32 + wave * 8 + j, K, C, lane) : 0.f;
     stage_kernels<32, 4, 3>(K > kb * 32 ? w + ((size_t)kb * 32 * C + ch * 16) * 9 : w, rows, wave, lane, C * 9LL, K - kb * 32, have, LEN, PITCH);
+#pragma unroll
+    for (int j = 0; j < (PARTS == 2 ? 8 : 0); ++j) {
+        const unsigned s = half_scale_bits(wave_max(finite_bits(some[j])));
+        if (lane == 0) scales[wave * 8 + j] = s;
+    }
     __syncthreads();
     const float* mine = rows + (lane & 31) * PITCH + (lane >> 5) * 72;
+    const unsigned scale = PARTS == 2 ? scales[lane & 31] : 0u;
+    if (PARTS == 2 && ch == 0 && threadIdx.x < 32) reinterpret_cast<float*>(wt + (size_t)n * n * chunks * Kb32 * 128)[kb * 32 + threadIdx.x] = half_unscale(scale);
 #pragma unroll 1
     for (int row = wave; row < n; row += 4) {
         float lg[8][3];                                     // this row of L g, for each channel
         kernel_row<M>(row, mine, lg);
+        const float this_up = row_up<M>(row);
         static_for<n>([&](auto j) {
-            unsigned short p[3][8];
+            constexpr int J = decltype(j)::value;
+            if constexpr (PARTS == 3) {
+                unsigned short p[3][8];
 #pragma unroll
-            for (int c = 0; c < 8; ++c) split_kept(kernel_element<M, decltype(j)::value>(lg[c]), p[0][c], p[1][c], p[2][c]);
-            store_parts(wt + (((size_t)(row * n + j) * chunks + ch) * Kb32 + kb) * 192 + lane, p);
+                for (int c = 0; c < 8; ++c) split_kept(kernel_element<M, J>(lg[c]), p[0][c], p[1][c], p[2][c]);
+                store_parts(wt + (((size_t)(row * n + J) * chunks + ch) * Kb32 + kb) * 192 + lane, p);
+                return;
+            }
+            const float up = __uint_as_float(scale) * this_up * power_of_two(kernel_up<M>(J));
+            float u[8];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) u[c] = kernel_element<M, J>(lg[c]) * up;
+            store_halves<32>(wt + (((size_t)(row * n + J) * chunks + ch) * Kb32 + kb) * 128 + lane, u, C - ch * 16);
         });
     }
 }
 
-// The same from a caller's U[plane][C rounded up to 16][K rounded up to 32]: one lane per 16-byte piece.
-template <int M>
+// The same, to the same bits, from a caller's U[plane][C rounded up to 16][K rounded up to 32]: one lane per 16-byte piece.
+template <int M, int PARTS>
 __global__ void __launch_bounds__(256)
 wino_split_given(const float* __restrict__ U, u32x4* __restrict__ wt, int C, int K, int chunks, int Kb32)
 {
@@ -506,26 +631,40 @@ wino_split_given(const float* __restrict__ U, u32x4* __restrict__ wt, int C, int
     const int lane = in & 63, kb = (in >> 6) % Kb32, ch = (in >> 6) / Kb32;
     const int k = kb * 32 + (lane & 31), c0 = ch * 16 + (lane >> 5) * 8;
     const int rows = (C + 15) / 16 * 16, cols = (K + 31) / 32 * 32;
-    unsigned short p[3][8];
+    if constexpr (PARTS == 3) {
+        unsigned short p[3][8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const float v = k < K && c0 + c < C ? U[((size_t)plane * rows + c0 + c) * cols + k] : 0.f;
+            split_kept(v, p[0][c], p[1][c], p[2][c]);
+        }
+        store_parts(wt + (((size_t)plane * chunks + ch) * Kb32 + kb) * 192 + lane, p);
+        return;
+    }
+    const unsigned scale = scale_of_given<M, 32>(U, k, K, C, rows, cols, lane);
+    if (plane == 0 && ch == 0 && lane < 32) reinterpret_cast<float*>(wt + (size_t)n * n * chunks * Kb32 * 128)[k] = half_unscale(scale);
+    const float up = __uint_as_float(scale) * row_up<M>(plane / n) * row_up<M>(plane % n);
+    float u[8];
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
-        const float v = k < K && c0 + c < C ? U[((size_t)plane * rows + c0 + c) * cols + k] : 0.f;
-        split_kept(v, p[0][c], p[1][c], p[2][c]);
+        const bool exists = k < K && c0 + c < C;
+        u[c] = U[exists ? ((size_t)plane * rows + c0 + c) * cols + k : 0];
+        u[c] = exists ? u[c] * up : 0.f;
     }
-    store_parts(wt + (((size_t)plane * chunks + ch) * Kb32 + kb) * 192 + lane, p);
+    store_halves<32>(wt + (((size_t)plane * chunks + ch) * Kb32 + kb) * 128 + lane, u, C - ch * 16);
 }
 
-template <int M, int TB, int Z, int COLS>
-hipError_t launch_one(const float* x, const u32x4* wt, float* y, const WinoSplitGeom& g, hipStream_t st)
+template <int M, int TB, int Z, int COLS, int PARTS>
+hipError_t launch_one(const float* x, const u32x4* wt, const float* w, int raw, float* y, const WinoSplitGeom& g, hipStream_t st)
 {
-    auto kern = wino_split_kernel<M, TB, Z, COLS>;
-    constexpr size_t shm = (size_t)(M + 2) * (M + 2) * TB * 128 + 16;
+    auto kern = wino_split_kernel<M, TB, Z, COLS, PARTS>;
+    constexpr size_t shm = wino_split_buffers(M, TB) + 16 + 4 * Z + 8 * TB;
     static_assert(shm <= 160 * 1024, "LDS");
     if (shm > 64 * 1024) {
         const hipError_t e = allow_large_lds((const void*)kern);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kern, dim3(g.nbt * g.nbk), dim3(512), shm, st, x, wt, y, g, wino_split_divisors(g));
+    hipLaunchKernelGGL(kern, dim3(g.nbt * g.nbk), dim3(512), shm, st, x, wt, y, g, wino_split_divisors(g), w, raw);
     return hipGetLastError();
 }
 
@@ -537,29 +676,31 @@ hipError_t launch_wino_split_weights(const float* w, bool given, void* wt, const
     const long long blocks = given ? (pieces * n * n + 255) / 256 : (long long)g.chunks * g.Kb32;
     if (pieces >= (1LL << 31) || blocks > 0x7fffffffLL || g.chunks * 16LL < g.C || g.Kb32 * 32LL < g.K) return hipErrorInvalidValue;
     u32x4* o = static_cast<u32x4*>(wt);
-#define IOLB_CASE(M_)                                                                                                                       \
-    if (g.m == M_) {                                                                                                                        \
-        if (given) hipLaunchKernelGGL(wino_split_given<M_>, dim3((unsigned)blocks), dim3(256), 0, st, w, o, g.C, g.K, g.chunks, g.Kb32);    \
-        else       hipLaunchKernelGGL(wino_split_weights<M_>, dim3((unsigned)blocks), dim3(256), 0, st, w, o, g.C, g.K, g.chunks, g.Kb32);  \
-        return hipGetLastError();                                                                                                           \
+#define IOLB_CASE(M_, P_)                                                                                                                       \
+    if (g.m == M_ && g.parts == P_) {                                                                                                           \
+        if (given) hipLaunchKernelGGL((wino_split_given<M_, P_>), dim3((unsigned)blocks), dim3(256), 0, st, w, o, g.C, g.K, g.chunks, g.Kb32);  \
+        else       hipLaunchKernelGGL((wino_split_weights<M_, P_>), dim3((unsigned)blocks), dim3(256), 0, st, w, o, g.C, g.K, g.chunks, g.Kb32); \
+        return hipGetLastError();                                                                                                               \
     }
-    IOLB_CASE(2) IOLB_CASE(4)
+    IOLB_CASE(2, 2) IOLB_CASE(2, 3) IOLB_CASE(4, 2) IOLB_CASE(4, 3)
 #undef IOLB_CASE
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_wino_split(const float* x, const void* wt, float* y, const WinoSplitGeom& g, hipStream_t st)
+hipError_t launch_wino_split(const float* x, const void* wt, const float* w, bool given, float* y, const WinoSplitGeom& g, hipStream_t st)
 {
     // what the kernel assumes of its geometry
     if (!wino_split_fits(g)) return hipErrorInvalidValue;
     const u32x4* u = static_cast<const u32x4*>(wt);
-    const int cols = wino_split_cols(g);
-#define IOLB_CASE(M_, T_, Z_)                                                                 \
-    if (g.m == M_ && g.tb == T_ && g.z == Z_)                                                 \
-        return cols == WINO_COLS_WHOLE ? launch_one<M_, T_, Z_, WINO_COLS_WHOLE>(x, u, y, g, st) \
-               : cols == WINO_COLS_CUT ? launch_one<M_, T_, Z_, WINO_COLS_CUT>(x, u, y, g, st)   \
-                                       : launch_one<M_, T_, Z_, WINO_COLS_SINGLE>(x, u, y, g, st);
+    const int cols = wino_split_cols(g), raw = given ? SPLIT_RAW_PLANES : SPLIT_RAW_TAPS;
+#define IOLB_PARTS_CASE(M_, T_, Z_, P_)                                                                      \
+    if (g.m == M_ && g.tb == T_ && g.z == Z_ && g.parts == P_)                                               \
+        return cols == WINO_COLS_WHOLE ? launch_one<M_, T_, Z_, WINO_COLS_WHOLE, P_>(x, u, w, raw, y, g, st) \
+               : cols == WINO_COLS_CUT ? launch_one<M_, T_, Z_, WINO_COLS_CUT, P_>(x, u, w, raw, y, g, st)   \
+                                       : launch_one<M_, T_, Z_, WINO_COLS_SINGLE, P_>(x, u, w, raw, y, g, st);
+#define IOLB_CASE(M_, T_, Z_) IOLB_PARTS_CASE(M_, T_, Z_, 2) IOLB_PARTS_CASE(M_, T_, Z_, 3)
     IOLB_WINO_SPLIT_SHAPES(IOLB_CASE)
+#undef IOLB_PARTS_CASE
 #undef IOLB_CASE
     return hipErrorInvalidValue;
 }

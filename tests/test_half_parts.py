@@ -127,3 +127,36 @@ def test_winograd_product_with_kernels_the_scales_do_not_fit(gpu, m, N, C, H, W,
             for k in range(6):
                 r = ref[i, k].cpu().numpy()
                 assert np.abs(y[i, k].cpu().numpy() - r).max() <= GUARD_WINO[m] * max(np.sqrt(np.mean(r * r)), 1e-300), (i, k)
+
+
+# one kernel, both tiles and blocks, columns read in every way; 64 channels and more, a batch of small images in a block
+@pytest.mark.parametrize("m,N,C,H,W,K,pad", [(2, 8, 128, 56, 56, 128, 1), (2, 6, 182, 125, 125, 102, 1), (2, 30, 128, 40, 41, 128, 3), (4, 16, 100, 64, 64, 64, 1),
+                                             (4, 64, 256, 14, 14, 256, 1), (4, 8, 80, 126, 126, 144, 1), (4, 64, 128, 15, 14, 96, 1), (4, 20, 64, 100, 99, 17, 2)])
+def test_fused_winograd_with_values_the_scales_do_not_fit(gpu, m, N, C, H, W, K, pad):  # noqa: F811
+    torch, B = gpu
+    from tests.test_split_kernels import GUARD_WINO, _runs_fused, _winograd_ref
+    x, w = make_inputs(N, C, H, W, K, 3, 3, "u11", "he", seed=m + C)
+    x, w = x.copy(), w.copy()
+    x[1] *= np.float32(1e-9)
+    x[2] *= np.float32(1e12)
+    x[3, :, 1, 1] *= np.float32(1e4)
+    x[4, :, :8, :8] *= np.float32(1e-7)
+    w[1] *= np.float32(1e-20)
+    w[2] *= np.float32(1e15)
+    w[3, :64] *= np.float32(1e-8)
+    w[4] = 0
+    xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+    ref = _winograd_ref(torch, xd, wd, pad)
+    y = _runs_fused(B, lambda: B.conv_winograd(xd, wd, m, pad=pad))
+    for i in range(5):
+        for k in range(6):
+            r = ref[i, k].cpu().numpy()
+            assert np.abs(y[i, k].cpu().numpy() - r).max() <= GUARD_WINO[m] * max(np.sqrt(np.mean(r * r)), 1e-300), (i, k)
+    # the dark corner by itself
+    e = 8 - m - 2 + pad
+    r = ref[4, 0, :e, :e].cpu().numpy()
+    assert np.abs(y[4, 0, :e, :e].cpu().numpy() - r).max() <= 8 * GUARD_WINO[m] * np.sqrt(np.mean(r * r))
+    # an image's bits do not depend on what another one holds
+    other = xd.clone()
+    other[N - 1] *= 1e-20
+    assert torch.equal(_runs_fused(B, lambda: B.conv_winograd(other, wd, m, pad=pad))[:N - 1], y[:N - 1])
