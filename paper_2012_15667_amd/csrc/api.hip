@@ -244,7 +244,7 @@ SplitChoice split_choice(const iolb_shape& s, int P, int Q, int pad_w, int layou
         g.stride = s.stride; g.hwc = hwc;
         g.in = hwc ? (s.C % 4 ? iolb::SPLIT_IN_SINGLE : iolb::SPLIT_IN_CHANNELS) : s.stride == 1 ? iolb::SPLIT_IN_PIXELS : iolb::SPLIT_IN_SINGLE;
         g.vec_out = hwc && s.K % 4 == 0;
-        if (iolb::split_point_faster(s, P, Q) && iolb::split_point_plan(&g, &cycles)) {
+        if (iolb::split_point_faster(s, P, Q, hwc) && iolb::split_point_plan(&g, &cycles)) {
             ch.kind = SplitChoice::POINT;
             ch.point = g;
             ch.weight_bytes = (size_t)iolb::split_point_weight_bytes(g);

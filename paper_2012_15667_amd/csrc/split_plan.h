@@ -22,7 +22,7 @@ bool wino_split_plan(WinoSplitGeom* g, double* ns);
 
 // Whether a layer without a caller-supplied tile leaves the fp32 kernels (the reasons are in the definitions).
 bool split_conv_faster(const iolb_shape& s);
-bool split_point_faster(const iolb_shape& s, int P, int Q);
+bool split_point_faster(const iolb_shape& s, int P, int Q, bool hwc);
 // 0: the tile, 1: the split product between transforms of their own, 2: the fused split kernel.  (A time of 0: does not run.)
 int split_wino_pick(const iolb_shape& s, const iolb_tile_config& tile, long long tiles, double product_cycles, double fused_ns);
 

@@ -282,14 +282,24 @@ bool split_point_plan(SplitPointGeom* g, double* cycles)
 // their stores (0.76 - 0.96); 7 x 7 and 11 x 11 kernels on three channels 0.98 - 1.2 and 5.7.
 bool split_conv_faster(const iolb_shape& s) { return s.C > 8 || s.R * s.S >= 25; }
 
-// 1 x 1: the fp32 kernel reads and writes at the rate of memory and needs no pass over the kernels before it; it
-// loses where the products outweigh that.  Measured over 60 drawn layers: from 48 flop per byte of the tensors and
-// 160 channels on 1.07 to 1.5 times as fast, below 0.57 to 1.1.
-bool split_point_faster(const iolb_shape& s, int P, int Q)
+// 1 x 1, channels outermost: the fp32 kernel reads and writes at the rate of memory and needs no pass over the kernels before it; it loses
+// where its chain over the channels or the products outweigh that.  Modelled times in us, fitted on 260 drawn layers (16 to 2048
+// channels; within 14 and 19 % in the 2-norm); where the split way wins by a margin it is 1.6 times as fast in the mean
+// (1536 -> 32 at 13 x 15, batch 6 46 -> 24 us; 684 -> 127 at 8 x 8, batch 53 24 -> 16), one of those 13 % slower; the others it
+// would make up to 1.7 times slower (128 -> 352 at 25 x 25, batch 3 6.9 -> 11.9).
+//   Channels innermost: that kernel does not exist, and the general one reads a channel group of a pixel at a time.  On all of 40 drawn layers
+// of 16 channels and more the split way was the faster one, by 2.3 in the mean (16 -> 32 at 84 x 90, batch 11 14.6 -> 14.3 us, 151 -> 224
+// at 73 x 73, batch 33 950 -> 107), at a smaller error (16 channels 7.7e-8 -> 7.0e-8, 256 2.8e-7 -> 1.7e-7).
+bool split_point_faster(const iolb_shape& s, int P, int Q, bool hwc)
 {
-    const double flop = 2.0 * s.N * P * Q * s.C * s.K;
-    const double bytes = 4.0 * ((double)s.N * s.C * P * Q + (double)s.N * s.K * P * Q + (double)s.K * s.C);
-    return s.C >= 160 && flop >= 48 * bytes && flop >= 1e9;
+    if (s.C < 16) return false;
+    if (hwc) return true;
+    const double pixels = (double)s.N * P * Q, flop = 2 * pixels * s.C * s.K;
+    const double bytes = 4 * (pixels * s.C + pixels * s.K + (double)s.K * s.C);
+    const double waves = std::ceil(pixels / 256 * std::ceil(s.K / 64.0) / 512);
+    const double tile = 5.04 + norm4(bytes / 7.47e6, flop / 1.08e8) + 0.0220 * s.C * std::max(1.0, waves);
+    const double split = 8.65 + norm4(bytes / 4.48e6, flop / 2.20e8) + 0.0087 * s.C;
+    return split + 1 < 0.94 * tile;
 }
 
 // Sums of fewer channels keep three bf16 parts, whose error is smaller there (F(2 x 2), 16 channels 1.0e-7 against 1.3e-7, 48 1.7e-7 and

@@ -160,3 +160,26 @@ def test_fused_winograd_with_values_the_scales_do_not_fit(gpu, m, N, C, H, W, K,
     other = xd.clone()
     other[N - 1] *= 1e-20
     assert torch.equal(_runs_fused(B, lambda: B.conv_winograd(other, wd, m, pad=pad))[:N - 1], y[:N - 1])
+
+
+@pytest.mark.parametrize("layer", [(3, 16, 9, 8, 5, 1), (2, 17, 13, 11, 33, 2), (1, 21, 40, 41, 70, 1), (4, 40, 23, 23, 257, 1), (5, 151, 1, 30, 64, 1), (2, 64, 30, 31, 48, 3)])
+def test_small_pointwise_layers_with_channels_innermost(gpu, layer):  # noqa: F811
+    """From 16 channels on, whatever their size: fewer channels than a chunk, fewer pixels and kernels than a block, strides."""
+    torch, B = gpu
+    N, C, H, W, K, stride = layer
+    shape = B.make_shape(N, C, H, W, K, 1, 1, stride, 0)
+    assert B.iolb_route(shape, B.LAYOUT_HWC)[0] == B.ROUTE_SPLIT
+    x, w = make_inputs(N, C, H, W, K, 1, 1, "u11", "he", seed=C + K)
+    xh = np.ascontiguousarray(x.transpose(0, 2, 3, 1))
+    wd = torch.from_numpy(w).cuda()
+    y = B.conv_direct_layout(torch.from_numpy(xh).cuda(), wd, stride, 0, B.LAYOUT_HWC).cpu().numpy().transpose(0, 3, 1, 2)
+    assert (np.abs(y - conv_ref(x, w, stride, 0)) <= _bound(x, w, stride, 0)).all()
+    # inputs and outputs off 16 bytes
+    buf = torch.zeros(xh.size + 1, device="cuda")
+    xo = buf[1:].view(xh.shape)
+    xo.copy_(torch.from_numpy(xh))
+    out = torch.full((y.size + 2,), 7.0, device="cuda")
+    P, Q = y.shape[2:]
+    yo = out[1:-1].view(N, P, Q, K)
+    B.conv_direct_layout(xo, wd, stride, 0, B.LAYOUT_HWC, y=yo)
+    assert np.array_equal(yo.cpu().numpy().transpose(0, 3, 1, 2), y) and float(out[0]) == 7 and float(out[-1]) == 7
