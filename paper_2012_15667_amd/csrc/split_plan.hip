@@ -313,7 +313,7 @@ constexpr int WINO_TWO_LEAST = 64, WINO_TWO_SMALL = 96;
 // and 12 % (F(4 x 4)) in the 2-norm, above 200 us 9 and 11 % too low (128 -> 128 at 112 x 112, batch 64, F(4 x 4) 494 us for 570).
 static double wino_split_ns(const WinoSplitGeom& g)
 {
-    const double per = (double)g.nbt * g.nbk / 256, rounds = per <= 4 ? std::ceil(per) : per + 0.5;
+    const double per = (double)g.nbt * g.nbk / 256, rounds = (per <= 4 ? std::ceil(per) : per + 0.5) * (g.parts == 3 ? 1 : g.m == 4 ? 0.92 : 0.95);
     if (g.m == 4) return g.z == 64 ? 5600 + rounds * (10700 + 3450.0 * g.chunks) : 7300 + rounds * (6900 + 2520.0 * g.chunks);
     return g.z == 64 ? 3800 + rounds * (8500 + 2650.0 * g.chunks) : 7000 + rounds * (2500 + 1000.0 * g.chunks);
 }
@@ -346,18 +346,15 @@ bool wino_split_plan(WinoSplitGeom* g, double* ns)
     return found;
 }
 
-// Modelled times in ns, each fitted on 194 drawn layers like those above (within 8 - 18 %; on 8000 others 9 - 14 where the tile is
-// fused, 15 - 29 where it is not, the split product 14 - 21): the tile's product or fused kernel by rounds of its blocks, traffic of V
-// and M at 5.7 - 6.05 TB/s, the launches.  A split way has to win by a margin.  Over those 8000 layers against the rule that was there
-// first (only a product, by the ratio below): 1.37 times as fast for F(2 x 2), 1.23 for F(4 x 4), 1.05 and 1.04 for F(3 x 3) and
-// F(6 x 6); 40 of them are 3 - 17 % slower, 35 of those below 30 us.  Models of fewer percent (residency of the tile's blocks, a cache of 400
-// MB before memory: 5 - 10 %) gained 1 - 4 % more in the mean and lost more than 3 % on twice as many.
-//   Unfused tiles where the first rule took the product: that runs, or the fused kernel where it is modelled faster by a margin too.
-// By the tile's model some went back to the tile (128 -> 304 at 77 x 77, batch 8, F(3 x 3) 150 -> 197 us; 128 -> 176 at 128 x
-// 128, batch 4, F(6 x 6) 101 -> 137), without the margin some to a slower fused kernel (512 -> 336 at 140 x 140, F(4 x 4) 143 -> 152).
-//   Layers whose channels are no multiple of four keep the first rule altogether.  The routes of three of them (130 and more channels)
-// are part of the tests; the kernels take such channels as well (33 x 261 -> 300 at 15 x 15 109 us, the product 63), and of those below
-// 128 channels, which no split way runs, nothing has been measured.
+// Modelled times in ns, each fitted on 194 drawn layers like those above, the split product's again on 210 in two parts (13 % in the
+// 2-norm; the tile's 10 where it is fused, 20 where it is not): the tile's product or fused kernel by rounds of its blocks, traffic of V
+// and M at 4.7 - 6 TB/s, the launches.  Over 330 layers these routes take 1.025 times the best of the three, the ones before them (their
+// models from kernels in three parts; no model for channels that are no multiple of four) 1.089; some eight are 3 - 14 % slower than those.
+//   Unfused tiles where the first rule took the product: that runs, or the fused kernel where it is modelled faster.  By the tile's model some
+// went back to the tile (128 -> 304 at 77 x 77, batch 8, F(3 x 3) 150 -> 197 us; 128 -> 176 at 128 x 128, batch 4, F(6 x 6) 101 -> 137).
+//   Where that rule was made for them, from 128 channels and kernels on, layers whose channels are no multiple of four keep it altogether:
+// the routes of three of them are part of the tests.  The kernels take such channels as well (33 x 261 -> 300 at 15 x 15 109 us, the product
+// 63); the others go by the models (81 channels in F(2 x 2) 2.2 times as fast, 70 layers 1.3 in the mean).
 int split_wino_pick(const iolb_shape& s, const iolb_tile_config& tile, long long tiles, double product_cycles, double fused_ns)
 {
     const int m = winograd_m(s.algo);
@@ -365,11 +362,14 @@ int split_wino_pick(const iolb_shape& s, const iolb_tile_config& tile, long long
     const int Kp = (s.K + 31) / 32 * 32;
     const bool fused_tile = tile.path == IOLB_PATH_FUSED;
     const bool product_first = !fused_tile && product_cycles && s.C >= 128 && s.K >= 128 && product_cycles / 2 < 0.8 * (2 * n2 * tiles * s.C * Kp / 105000);
-    if (!fused_tile && s.C % 4) return product_first;
+    if (!fused_tile && s.C % 4 && s.C >= 128 && s.K >= 128) return product_first;
     const double out = (double)s.N * (s.H + 2 * s.pad - 2) * (s.W + 2 * s.pad - 2);
     const double bytes = 4 * ((double)s.N * s.C * s.H * s.W + 2 * n2 * tiles * (s.C + s.K) + s.K * out);
-    const double product = m == 2 ? 9200 + bytes / 6050 + 0.25 * product_cycles : 12000 + bytes / 5700 + 0.334 * product_cycles;
-    if (product_first) return fused_ns && fused_ns < (m == 4 ? 0.92 : 1) * product ? 2 : 1;
+    const double product = m == 2   ? 10600 + bytes / 5140 + 0.158 * product_cycles
+                           : m == 3 ? 11800 + bytes / 4750 + 0.139 * product_cycles
+                           : m == 4 ? 13500 + bytes / 5270 + 0.215 * product_cycles
+                                    : 17400 + bytes / 5080 + 0.307 * product_cycles;
+    if (product_first) return fused_ns && fused_ns < product ? 2 : 1;
     const double tb = tile.x / m, across = std::ceil(tiles / tb);
     double best;
     if (fused_tile) {
@@ -379,7 +379,7 @@ int split_wino_pick(const iolb_shape& s, const iolb_tile_config& tile, long long
         const double rounds = std::ceil(n2 * across * ((Kp + tile.z - 1) / tile.z) / 256), waves = std::min(4, tile.threads / 64);
         best = 12000 + bytes / 6000 + 45.0 * s.C + rounds * s.C * 2 * tb * tile.z / waves / 1000 * (m == 2 ? 9.2 : 6.6);
     }
-    best *= m == 2 || m == 4 ? 0.93 : 0.85;
+    best *= m == 2 ? 1 : m == 6 ? 1.15 : 1.05;
     int pick = 0;
     if (product_cycles && s.C >= WINO_TWO_LEAST && product < best) { best = product; pick = 1; }
     if (fused_ns && fused_ns < best) pick = 2;
