@@ -15,7 +15,7 @@
 // Two parts: the scales (split_mfma.h) are of a kernel, and of an image in a block, from a sample of its first loads and 64 values
 // spread over the channels, known before the first of them is split.  What the split finds of each pixel's largest value is kept in
 // LDS; after the last step every wave looks through it for pixels that are too small for the scale, and takes its block again on the
-// fp32 instructions for their images.  That and one barrier more cost 1.2 us of a workgroup's life.  Measured whole calls, three
+// fp32 instructions for outputs whose window has no others.  That and one barrier more cost 1.2 us of a workgroup's life.  Measured whole calls, three
 // bf16 parts / two fp16 parts: 3x3, 256 -> 256 at 56 x 56, batch 64 927 / 605 us (392 TFLOP/s of fp32 products; register-only 646),
 // 64 -> 64 at 56 x 56, batch 32 50 / 38, 128 -> 256 at 28 x 28, stride 2 57 / 42, 5x5, 96 -> 256 at 27 x 27, batch 16, channels
 // innermost 76 / 58; 80 drawn layers 1.17 in the mean.
@@ -115,11 +115,9 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
     float* const kback = reinterpret_cast<float*>(lds + g.nbuf * buf_bytes);     // TWO: what undoes the scales of the block's kernels
     int* const koff = reinterpret_cast<int*>(kback + (TWO ? 16 * MB * WM : 0));  // [4 * steps]
     uint2* const table = reinterpret_cast<uint2*>(koff + ((4 * steps + 1) & ~1));      // [items]
-    // TWO: the largest value of each staged pixel over the channels, scaled; of each image in the sample (one image: of each wave);
-    // whether an image is taken again
+    // TWO: the largest value of each staged pixel over the channels, scaled; of each image in the sample (one image: of each wave)
     unsigned* const most = reinterpret_cast<unsigned*>(table + items);
     unsigned* const sample = most + g.halo;
-    unsigned* const lost = sample + (g.b > 1 ? g.b : WM * WN);
 
     const int nchunks = __builtin_amdgcn_readfirstlane((C + 8 * CH8 - 1) / (8 * CH8));
     // weights of matrix step t: [t][16-channel block][part][lane]
@@ -261,9 +259,7 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
         }
         for (int i = tid; i < g.halo; i += T) most[i] = 0;
         if (g.b > 1) {
-            for (int i = tid; i < 2 * g.b; i += T) sample[i] = 0;                // (lost follows)
-        } else if (tid == 0) {
-            lost[0] = 0;
+            for (int i = tid; i < g.b; i += T) sample[i] = 0;
         }
         if (tid < 16 * MB * WM) my_kback = reinterpret_cast<const float*>(wt + (size_t)nchunks * steps * wstep)[kb * (16 * MB * WM) + tid];
         __builtin_amdgcn_sched_barrier(0);
@@ -505,7 +501,7 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
     // what undoes the scales (one image in a block: its own)
     float back = 1.f;
     f32x4 kb4[MB];
-    bool image_lost = false, finite = false;
+    bool finite = false;
     if constexpr (TWO) {
         // (most waves have no sum that is not finite: 0 times it is NaN, and so is the sum of those)
         f32x4 z = {0.f, 0.f, 0.f, 0.f};
@@ -516,18 +512,10 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
 #pragma unroll
                 for (int i = 0; i < 4; ++i) z[i] = __builtin_fmaf(acc[mb][nb][i], 0.f, z[i]);
         back = half_unscale(half_scale_bits(largest()));
-        // Images with a pixel whose channels are all too small for their scale, and not all zeros.  (Every wave looks through all
-        // pixels: what it marks it needs no barrier to see.)
+        // pixels whose channels are all too small for their scale, and not all zeros: the windows they are in are looked at below
         bool small = false;
-        for (int i = lane; i < g.halo; i += 64) {
-            const unsigned m = most[i];
-            if (m - 1 < __float_as_uint(HALF_LEAST) - 1) {
-                lost[dv.per.of(i)] = 1;
-                small = true;
-            }
-        }
+        for (int i = lane; i < g.halo; i += 64) small |= most[i] - 1 < __float_as_uint(HALF_LEAST) - 1;
         finite = __builtin_amdgcn_ballot_w64(small || z[0] + z[1] + z[2] + z[3] != 0.f) == 0;
-        image_lost = lost[0] != 0;
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) kb4[mb] = *reinterpret_cast<const f32x4*>(kback + (wm_i * MB + mb) * 16 + 4 * (lane >> 4));
     }
@@ -544,11 +532,16 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
             const int im = dv.txy.of(slot), rem = slot - im * txy, row = dv.tx.of(rem), py = y0 + row, px = x0 + rem - row * g.tx;
             if (slot >= npix || n0 + im >= g.N || py >= g.P || px >= g.Q) continue;
             if constexpr (TWO && !MARKED) {
-                if (g.b > 1) {
-                    back = half_unscale(half_scale_bits(sample[im]));
-                    if (MODE == MARKING) image_lost = lost[im] != 0;
-                }
-                if (MODE == MARKING && image_lost) again |= ((1ull << (4 * MB - 1) << 1) - 1) << (nb * MB * 4);
+                if (g.b > 1) back = half_unscale(half_scale_bits(sample[im]));
+                // no value of this output's window large enough, and not all of them zero
+                unsigned window = 0;
+                if constexpr (MODE == MARKING)
+                    for (int r = 0; r < g.R; ++r)
+                        for (int s = 0; s < g.S; ++s) {
+                            const unsigned m = most[(im * g.yh + row * g.esy + r) * g.rowp + (rem - row * g.tx) * g.esx + s];
+                            window = m > window ? m : window;
+                        }
+                if (MODE == MARKING && window - 1 < __float_as_uint(HALF_LEAST) - 1) again |= ((1ull << (4 * MB - 1) << 1) - 1) << (nb * MB * 4);
             }
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) {

@@ -128,10 +128,10 @@ inline int split_batches(const SplitGeom& g)
 __host__ __device__ constexpr int split_pixel_bytes(int parts) { return parts == 2 ? 16 : 48; }
 __host__ __device__ constexpr int split_planes(int parts) { return parts == 2 ? 2 : 1; }
 // buffers of the input tile, offsets of the matrix steps' units, table of the input tile's elements, whole 16 bytes; of two parts
-// also the kernels' scales, the pixels' largest values, the images' and whether they are taken again
+// also the kernels' scales, the pixels' largest values and the images'
 __host__ __device__ inline int split_tables_bytes(const SplitGeom& g)
 {
-    const int steps = (g.R * g.S * g.ch8 + 3) / 4, more = g.parts == 2 ? 64 * g.mb * g.wm + 4 * g.halo + 4 * g.b + 4 * (g.b > 4 ? g.b : 4) : 0;
+    const int steps = (g.R * g.S * g.ch8 + 3) / 4, more = g.parts == 2 ? 64 * g.mb * g.wm + 4 * g.halo + 4 * (g.b > 4 ? g.b : 4) : 0;
     return (g.nbuf * g.ch8 * split_planes(g.parts) * g.b * g.yh * g.rowb + 4 * ((4 * steps + 1) & ~1) + 8 * g.ch8 * g.halo + more + 15) & ~15;
 }
 // ... and the parts and rows of a workgroup's own kernels
@@ -141,7 +141,7 @@ inline long long split_own_bytes(const SplitGeom& g)
 }
 inline long long split_lds_bytes(const SplitGeom& g, bool own = false)
 {
-    const long long more = g.parts == 2 ? 64LL * g.mb * g.wm + 4LL * g.halo + 4 * g.b + 4 * (g.b > 4 ? g.b : 4) : 0;
+    const long long more = g.parts == 2 ? 64LL * g.mb * g.wm + 4LL * g.halo + 4 * (g.b > 4 ? g.b : 4) : 0;
     const long long tables = ((long long)g.nbuf * g.ch8 * split_planes(g.parts) * g.b * g.yh * g.rowb + 4 * ((4 * split_steps(g) + 1) & ~1) +
                               8LL * g.ch8 * g.halo + more + 15) & ~15LL;
     return tables + (own ? split_own_bytes(g) : 0);

@@ -4,7 +4,7 @@
 //
 // A step is 32 channels.  The inputs of chunk t + 1 are split and written to one LDS buffer while chunk t is multiplied
 // from the other; their loads are issued three chunks ahead and kept in registers, two neighbouring pixels per load where
-// the layout has them.  Every pixel has a scale of its own, from the first 32 of its channels and a few more.  The split's arithmetic is
+// the layout has them.  Every pixel has a scale of its own, from the first 32 of its channels and a few more, and what they are for its neighbours.  The split's arithmetic is
 // placed between the matrix instructions, three vector
 // instructions after each, where it costs little (a 16-bit matrix instruction leaves the vector pipeline free; measured:
 // eight vector instructions per 32-cycle matrix instruction 1433 against 1631 TFLOP/s).  wt is not declared restrict on
@@ -40,11 +40,12 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
     constexpr int ITEMS = 32 / CH * NPIX / PX, IB = (ITEMS + T - 1) / T;
     extern __shared__ u32x4 lds16[];
     // two buffers, each the h of all pixels and then the l; room that nobody reads; per pixel the largest value in the sample that sets
-    // its scale, and of all its channels, scaled; what undoes the kernels' scales
+    // its scale, and of all its channels, scaled, and that of its image; what undoes the kernels' scales
     char* const lds = reinterpret_cast<char*>(lds16);
     unsigned* const sample = reinterpret_cast<unsigned*>(lds + 2 * BUF + PLANE + 16);
     unsigned* const most = sample + NPIX;
-    float* const kback = reinterpret_cast<float*>(most + NPIX);
+    unsigned* const images = most + NPIX;
+    float* const kback = reinterpret_cast<float*>(images + NPIX);
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, grp = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm_i = wave % WM, wn_i = wave / WM;
@@ -187,15 +188,16 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
         const int c = 32 * (int)((unsigned)(37 * (i * T + tid) & 63) * (unsigned)nchunks >> 6);
         spread[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, src[i] != OUTSIDE && c + c_in[i] < g.C ? (int)(src[i] + (unsigned)c * (unsigned)cstep) : (int)OUTSIDE, 0, 0));
     }
-    static_assert(16 * MB * WM <= T && 2 * NPIX <= T, "one kernel, one of the pixels' two values per thread");
+    static_assert(16 * MB * WM <= T && 3 * NPIX <= T, "one kernel, one of the pixels' three values per thread");
     float my_kback = 0.f;
     if (tid < 16 * MB * WM) my_kback = reinterpret_cast<const float*>(group_w + (size_t)nchunks * wstep)[kb * (16 * MB * WM) + tid];
     load_x(xv[1], 1);
     load_a(a0);
-    if (tid < 2 * NPIX) sample[tid] = 0;                    // (most follows)
+    if (tid < 3 * NPIX) sample[tid] = 0;                    // (most and images follow)
     __builtin_amdgcn_sched_barrier(0);
     barrier();
-    // A pixel's scale follows from its own values, so that neither its neighbours nor other images change its outputs.
+    // A pixel's scale follows from the largest value of its image's pixels in the block (a few channels of sparse data say little about the
+    // others), but is at most 512 times its own (so that it is never too small for it).  Other images do not change its outputs.
     auto item_px = [&](int i) { return (i * T + tid) % (NPIX / PX) * PX; };
     auto exists = [&](int i) { return i * T + tid < ITEMS; };
 #pragma unroll
@@ -212,20 +214,19 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
         }
     if (tid < 16 * MB * WM) kback[tid] = my_kback;
     barrier();
-    // ... of its image's pixels in the block where those are all zeros.
     static_assert(NPIX <= 64, "a lane per pixel");
-    const unsigned all = wave_max(lane < NPIX ? sample[lane] : 0u);
+    unsigned all = 0;
+    if (span == 1) {
+        all = wave_max(lane < NPIX ? sample[lane] : 0u);
+    } else {
+        if (tid < NPIX && tid < left_px) atomicMax(images + (p0 + tid) / g.HW, sample[tid]);
+        barrier();
+    }
     auto scale_of = [&](int px) {
-        unsigned m = sample[px];
-        if (m == 0 && px < left_px) {
-            m = all;
-            if (span > 1) {
-                m = 0;
-                for (int q = 0, image = (p0 + px) / g.HW; q < NPIX; ++q)
-                    if (q < left_px && (p0 + q) / g.HW == image && sample[q] > m) m = sample[q];
-            }
-        }
-        return half_scale_bits(m);
+        const unsigned m = sample[px], image = span == 1 ? all : images[(p0 + px) / g.HW];
+        // (bits of floats: 3 << 23 less is an eighth, 9 << 23 more is 512 times)
+        const unsigned eighth = image < 4u << 23 ? 0u : image - (3u << 23), most_m = m + (9u << 23);
+        return half_scale_bits(m == 0 ? eighth : image < m ? m : image < most_m ? image : most_m);
     };
 #pragma unroll
     for (int i = 0; i < IB; ++i)
@@ -431,7 +432,7 @@ template <int MB, int NB, int WM, int WN, int IN, bool VPX>
 hipError_t launch_one(const float* x, const u32x4* wt, const float* w, float* y, const SplitPointGeom& g, hipStream_t st)
 {
     auto kern = split_point_kernel<MB, NB, WM, WN, IN, VPX>;
-    constexpr size_t NPIX = 16 * NB * WN, shm = 5 * 4 * NPIX * 16 + 16 + 8 * NPIX + 64 * MB * WM;
+    constexpr size_t NPIX = 16 * NB * WN, shm = 5 * 4 * NPIX * 16 + 16 + 12 * NPIX + 64 * MB * WM;
     static_assert(shm <= 64 * 1024, "dynamic LDS without an opt-in");
     hipLaunchKernelGGL(kern, dim3(g.nbk * g.nbp * g.groups), dim3(64 * WM * WN), shm, st, x, wt, y, g, w);
     return hipGetLastError();

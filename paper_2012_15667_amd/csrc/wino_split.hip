@@ -92,9 +92,9 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
     constexpr unsigned UNIT = 1024u * PARTS;                 // bytes of a unit
     static_assert(LP == 0 || LP == 4, "left-over planes");
     // Inputs are scaled so that V, up to 100 and 4 times as large in F(4 x 4) and F(2 x 2), has the room above it that other operands have.
-    // What a transform rounds off is at least 2^-25 of V's parts where a window has a value of 2^-4 and 2^-2.
-    constexpr int TOP = M == 4 ? 4 : 7;
-    constexpr float LEAST = M == 4 ? 0.0625f : 0.25f;
+    // What a transform rounds off is not less than what V's parts lose, at most 2^-25, where a window has a value of 2^-5 and 2^-2.
+    constexpr int TOP = M == 4 ? 3 : 7;
+    constexpr float LEAST = M == 4 ? 0.03125f : 0.25f;
     extern __shared__ u32x4 lds16[];
     char* const lds = reinterpret_cast<char*>(lds16);
     // behind the buffers: whether a block is taken again; what undoes the kernels' scales; per image of the block the largest value of the
@@ -529,8 +529,8 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
     barrier();
     if (__builtin_amdgcn_readfirstlane(*any) == 0) return;
 
-    // The block again on the fp32 matrix instructions, from the same inputs; three parts hold all of a kernel, in place of two the
-    // caller's own is read.
+    // The block again on the fp32 matrix instructions, from the same inputs; three parts hold all of a kernel, two do
+    // unless they are not finite: then the caller's own is read.
     clear();
     xs = 1.f;
 #pragma unroll 1
@@ -542,10 +542,22 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
             const char* vplane = lds + plane * (TB * 64);
             float w[8];
             if constexpr (TWO) {
-                // (opaque: nothing of it is computed, and kept in scalar registers, through the loop above)
-                const RawKernels kernels(w_raw, raw, M, opaque(plane), opaque(g.C), opaque(g.K));
+                u32x4 f[PARTS];
+                load_u(f, unit_at(u, s));
+                const f16x8 h = __builtin_bit_cast(f16x8, f[0]), l = __builtin_bit_cast(f16x8, f[1]);
+                const float back = kback[32 * z + l32] * (row_down<M>(plane / n) * row_down<M>(plane % n));
+                bool whole = true;
 #pragma unroll
-                for (int j = 0; j < 8; ++j) w[j] = kernels.at(kb * Z + 32 * z + l32, 16 * s + 8 * half + j);
+                for (int j = 0; j < 8; ++j) {
+                    w[j] = ((float)h[j] + (float)l[j]) * back;
+                    whole = whole && __builtin_fabsf(w[j]) <= 3.402823466e38f;
+                }
+                if (!whole) {
+                    // (opaque: nothing of it is computed, and kept in scalar registers, through the loop above)
+                    const RawKernels kernels(w_raw, raw, M, opaque(plane), opaque(g.C), opaque(g.K));
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) w[j] = kernels.at(kb * Z + 32 * z + l32, 16 * s + 8 * half + j);
+                }
             } else {
                 u32x4 f[PARTS];
                 load_u(f, unit_at(u, s));
