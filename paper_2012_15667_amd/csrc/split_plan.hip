@@ -265,15 +265,20 @@ bool split_point_plan(SplitPointGeom* g, double* cycles)
         const long long span = std::min<long long>((t.HW - 1 + npix - 1) / t.HW + 1, t.images);
         if (grid > 0x7fffffffLL || (long long)t.images * t.HW >= (1LL << 31) - 1024 || 4 * span * t.C * t.HWin >= (1LL << 31)) continue;
         t.nbp = (int)nbp;
-        // a step of a workgroup: z x 32 weights in three parts and 32 channels of npix pixels come in at 19 bytes per
-        // clock and compute unit; alone on its unit a workgroup waits some 3200 clocks for them
+        // A step of a workgroup: 32 channels of npix pixels come in at 12 bytes per clock and compute unit, and those of z kernels in two
+        // parts at 16; alone on its unit a workgroup waits some 2800 clocks for them.  (Fitted on all blocks of 37 drawn layers, two of
+        // which do better with another, by 1 and 2 %.  By the bytes of three parts 768 -> 192 at 17 x 17, batch 64, took 64 kernels a block,
+        // 37 us, and not 192, 35.  Blocks of 128 pixels and 128, 192 or 256 kernels on eight waves: 0.8 - 1.02 on 36 of them.)
         const double chunks = (t.C + 31) / 32, n = grid / 256.0, rounds = n <= 4 ? (double)((grid + 255) / 256) : n + 0.5;
-        const double step = std::max((192.0 * z + 128.0 * npix) / 19, 96.0 * t.mb * t.nb * (t.wm * t.wn / 4) * 1.4);
+        const double step = std::max((96.0 * z + 128.0 * npix) / 12, 48.0 * t.mb * t.nb * (t.wm * t.wn / 4) * 1.4);
+        // (the time that is told is the one that split_wino_pick's models were fitted with: three parts at 19 bytes per clock)
+        const double told = std::max((192.0 * z + 128.0 * npix) / 19, 96.0 * t.mb * t.nb * (t.wm * t.wn / 4) * 1.4);
         const double res = t.mb * t.nb <= 4 ? 4 : t.mb * t.nb <= 8 ? 3 : 8.0 / (t.wm * t.wn);
-        const double c = std::max(rounds * chunks * step, (double)(long long)(rounds / res + 0.999) * chunks * 3200) + 6000;
-        if (!found || c < best_cycles) { found = true; best = t; best_cycles = c; }
+        auto time = [&](double per_step, double alone) { return std::max(rounds * chunks * per_step, (double)(long long)(rounds / res + 0.999) * chunks * alone) + 6000; };
+        const double c = time(step, 2800);
+        if (!found || c < best_cycles) { found = true; best = t; best_cycles = c; *cycles = time(told, 3200); }
     }
-    if (found) { *g = best; *cycles = best_cycles; }
+    if (found) *g = best;
     return found;
 }
 
@@ -352,16 +357,17 @@ bool wino_split_plan(WinoSplitGeom* g, double* ns)
 // models from kernels in three parts; no model for channels that are no multiple of four) 1.089; some eight are 3 - 14 % slower than those.
 //   Unfused tiles where the first rule took the product: that runs, or the fused kernel where it is modelled faster.  By the tile's model some
 // went back to the tile (128 -> 304 at 77 x 77, batch 8, F(3 x 3) 150 -> 197 us; 128 -> 176 at 128 x 128, batch 4, F(6 x 6) 101 -> 137).
-//   Where that rule was made for them, from 128 channels and kernels on, layers whose channels are no multiple of four keep it altogether:
-// the routes of three of them are part of the tests.  The kernels take such channels as well (33 x 261 -> 300 at 15 x 15 109 us, the product
-// 63); the others go by the models (81 channels in F(2 x 2) 2.2 times as fast, 70 layers 1.3 in the mean).
+//   Where that rule was made for them, from 128 channels and kernels on, layers whose channels are no multiple of four keep it altogether,
+// with a wider line: 53 drawn layers between 0.8 and 0.9 are 1.05 to 3.4 times as fast on the product (365 -> 227 at 35 x 35, batch 3, F(2 x 2)
+// 57 -> 32 us; 507 -> 299 at 42 x 42, batch 11, F(4 x 4) 333 -> 120).  Beyond it the routes of three are part of the tests (33 x 261 -> 300
+// at 15 x 15 109 us, the product 63).  The others go by the models (81 channels in F(2 x 2) 2.2 times as fast, 70 layers 1.3 in the mean).
 int split_wino_pick(const iolb_shape& s, const iolb_tile_config& tile, long long tiles, double product_cycles, double fused_ns)
 {
     const int m = winograd_m(s.algo);
     const double n2 = (m + 2) * (m + 2);
     const int Kp = (s.K + 31) / 32 * 32;
     const bool fused_tile = tile.path == IOLB_PATH_FUSED;
-    const bool product_first = !fused_tile && product_cycles && s.C >= 128 && s.K >= 128 && product_cycles / 2 < 0.8 * (2 * n2 * tiles * s.C * Kp / 105000);
+    const bool product_first = !fused_tile && product_cycles && s.C >= 128 && s.K >= 128 && product_cycles / 2 < (s.C % 4 ? 0.9 : 0.8) * (2 * n2 * tiles * s.C * Kp / 105000);
     if (!fused_tile && s.C % 4 && s.C >= 128 && s.K >= 128) return product_first;
     const double out = (double)s.N * (s.H + 2 * s.pad - 2) * (s.W + 2 * s.pad - 2);
     const double bytes = 4 * ((double)s.N * s.C * s.H * s.W + 2 * n2 * tiles * (s.C + s.K) + s.K * out);

@@ -104,7 +104,8 @@ def test_pointwise_outputs_keep_the_bound_of_fp32(gpu, layer, layout, change):  
 
 
 # products of their own between the transforms, every m
-@pytest.mark.parametrize("m,N,C,H,W,K", [(2, 64, 512, 7, 7, 512), (3, 33, 525, 7, 8, 485), (4, 9, 277, 35, 37, 233), (6, 5, 284, 29, 30, 497)])
+@pytest.mark.parametrize("m,N,C,H,W,K", [(2, 64, 512, 7, 7, 512), (3, 33, 525, 7, 8, 485), (4, 9, 277, 35, 37, 233), (6, 5, 284, 29, 30, 497),
+                                          (2, 5, 365, 33, 34, 227), (4, 5, 365, 33, 35, 227)])
 def test_winograd_product_with_kernels_the_scales_do_not_fit(gpu, m, N, C, H, W, K):  # noqa: F811
     """Images and kernels of very different scale, channels of one kernel far below its others, an outlier: from w and from kernels
     transformed before, within the guard of each image and kernel by itself."""
