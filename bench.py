@@ -17,8 +17,8 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 PEAK_FP32_MFMA_TFLOPS = 157.3     # MI355X dense fp32 matrix peak
-# fp32 products taken as six bf16 products of parts: a sixth of the dense bf16 matrix peak (2.5 PFLOP/s)
-PEAK_SPLIT_MFMA_TFLOPS = 416.7
+# fp32 products taken as three fp16 products of parts: a third of the dense fp16 matrix peak (2.5 PFLOP/s)
+PEAK_SPLIT_MFMA_TFLOPS = 833.3
 PEAK_HBM_GBS = 8000.0
 
 # (config name, algorithms run in a step)
@@ -240,7 +240,7 @@ def main():
     def tile_of(L, a):
         return B.iolb_tune(shape_of(L, a))
 
-    # What a call of a layer runs on: "split" (bf16 matrix cores, operands in three parts) or the path of its tile.  Thin
+    # What a call of a layer runs on: "split" (fp16 or bf16 matrix cores, operands in parts) or the path of its tile.  Thin
     # layers ("fma") run plain-FMA kernels, which the library does not time with the matrix-core ones.
     path_names = {B.PATH_FMA: "fma", B.PATH_MFMA: "mfma", B.PATH_FUSED: "fused", B.PATH_POINT: "pointwise"}
 
@@ -328,7 +328,7 @@ def main():
 
     ms_step = 1e3 * elapsed / args.steps
     value = flops_step / (elapsed / args.steps) / 1e12
-    roofline = roofline_of("direct", "split_conv_kernel (all instantiations in the step; fp32 products as six bf16 products)" if kinds["direct"][0]
+    roofline = roofline_of("direct", "split_conv_kernel (all instantiations in the step; fp32 products as three fp16 products)" if kinds["direct"][0]
                            else "direct_mfma_kernel (all instantiations in the step)", n_direct, ms_direct)
     if roofline:
         per = [traffic[k]["main_kernel"] for k in ((j[0].name, j[1], runs_on(j[0], j[1], forced[id(j)])) for j in jobs)
@@ -337,7 +337,7 @@ def main():
         roofline["traffic_source"] = ("recorded: %s (rocprofv3 FETCH_SIZE + WRITE_SIZE of an earlier run of the same "
                                       "kernels, average over the direct launches of a step), not measured in this run" % TRAFFIC_FILE) if per else None
     wino_roofline = roofline_of("product", "split_point_kernel (large products) and wino_product_kernel (fp32 instructions), all launches of the step", n_wino, ms_wino)
-    fused_roofline = roofline_of("fused", "wino_split_kernel (bf16 matrix cores) and wino_fused_mfma_kernel / wino_rows_kernel (fp32 instructions): fused Winograd layers of the step", n_fused, ms_fused)
+    fused_roofline = roofline_of("fused", "wino_split_kernel (fp16 matrix cores; fewer than 64 channels bf16) and wino_fused_mfma_kernel / wino_rows_kernel (fp32 instructions): fused Winograd layers of the step", n_fused, ms_fused)
 
     out = {
         "metric": "TFLOP/s per conv layer (direct & Winograd) + HBM bytes / I/O lower bound",

@@ -94,12 +94,14 @@ typedef struct iolb_bounds_out {
  * x: [N][C][H][W], w: [K][C][R][S], y: [N][K][P][Q]; cross-correlation, zero padding.
  * y is fully overwritten; x and y must not overlap.  The tile comes from iolb_tune with the
  * default budgets.  May grow the stream's workspace in the library (one allocation, kept).
- * Without a caller-supplied tile, layers that are bound by the fp32 matrix instructions run on the bf16 ones instead
+ * Without a caller-supplied tile, layers that are bound by the fp32 matrix instructions run on the 16-bit ones instead
  * (this call, conv_direct_layout with cfg NULL, conv_direct_pad2, conv_direct_noalloc; the products of conv_winograd,
- * conv_winograd_pad, and conv_winograd_ws / _pre with cfg NULL): every operand as the sum of three bf16 parts, six
- * products of parts, fp32 sums -- no less precise than fp32 products.  Their blocks are not tiles of the enumeration;
- * a caller-supplied tile always runs on the fp32 kernels.  Infinities, NaN, operands from 4e31 and sums from 5e24
- * on give what fp32 sums give, at about four times the layer's time where every output is such. */
+ * conv_winograd_pad, and conv_winograd_ws / _pre with cfg NULL): every operand as the sum of two fp16 parts under a
+ * scale taken from the data, three products of parts, or, for few channels and small layers, as the sum of three bf16 parts,
+ * six products; fp32 sums -- no less precise than fp32 products.  Their blocks are not tiles of the enumeration;
+ * a caller-supplied tile always runs on the fp32 kernels.  Outputs that the parts cannot hold (infinities, NaN, operands or
+ * sums near the end of the range, values far from what a sample of the image has as its largest) are computed again in fp32: what
+ * fp32 sums give, in up to ten times the layer's time where many are such. */
 int conv_direct(const float* x, const float* w, float* y,
                 int N, int C, int H, int W, int K, int R, int S, int stride, int pad);
 
@@ -203,7 +205,7 @@ int64_t iolb_enumerate(const iolb_shape* shape, size_t lds_bytes, int vgpr_budge
                        iolb_tile_config* out, int64_t capacity);
 
 /* What a call without a caller-supplied tile runs on: IOLB_ROUTE_TILE, the fp32 kernels with the tuned tile, or
- * IOLB_ROUTE_SPLIT, the bf16 matrix cores (see conv_direct); or a negative code.  It depends on the layer and the layout
+ * IOLB_ROUTE_SPLIT, the 16-bit matrix cores (see conv_direct); or a negative code.  It depends on the layer and the layout
  * alone.  layout: as for conv_direct_layout (IOLB_LAYOUT_CHW for the Winograd algos).  *bytes (may be NULL): on the split
  * route the bytes of the re-laid-out kernels (direct) or the least workspace that takes it (Winograd), else 0.
  * conv_direct_noalloc takes the route of conv_direct, within its limit.  Host only. */

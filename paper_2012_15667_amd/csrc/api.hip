@@ -46,7 +46,7 @@ struct DeviceState {
 // Scratch of the entry point that allocates nothing: the re-laid-out weights of one layer.  Every GPU the
 // library runs on holds its own copy of the array, at its own address, until the process ends.
 constexpr size_t kScratchFloats = (size_t)4 << 20;            // largest padded weight tensor conv_direct_noalloc takes
-// room for such a tensor in three bf16 parts
+// room for such a tensor in three bf16 parts (two fp16 parts take less, and are given the same)
 constexpr size_t kScratchBytes = kScratchFloats * 6;          // 24 MiB
 static __device__ __align__(256) char scratch[kScratchBytes];
 std::mutex g_mutex;
@@ -206,7 +206,7 @@ int check_config(const iolb_shape& s, const iolb_tile_config& cfg)
     return IOLB_EINVAL;
 }
 
-// ---- direct layers on the bf16 matrix cores, operands in three parts ---------------------------
+// ---- direct layers on the 16-bit matrix cores, operands in parts -------------------------------
 // Which kernel a layer without a caller-supplied tile runs on.  The choice and the block depend on the layer alone
 // (not on the entry point nor on the tile it was tuned; the tensor layout changes addresses only), so that every entry
 // point gives the same bits for the same layer, whatever was called before.
@@ -261,7 +261,7 @@ SplitChoice split_choice(const iolb_shape& s, int P, int Q, int pad_w, int layou
         }
     }
     // conv_direct_noalloc has a fixed room for the kernels and gives the bits of conv_direct: a layer that it takes (the
-    // kernels of conv_direct's own tile fit, or are read in place) must fit that room in three parts too.  It knows no
+    // kernels of conv_direct's own tile fit, or are read in place) must fit that room in parts too.  It knows no
     // layers with another padding per axis.
     if (ch.weight_bytes > kScratchBytes && pad_w == s.pad) {
         iolb_tile_config tile;
@@ -272,7 +272,7 @@ SplitChoice split_choice(const iolb_shape& s, int P, int Q, int pad_w, int layou
     return ch;
 }
 
-// wt_buf != nullptr: room of wt_bytes bytes for the kernels in three parts
+// wt_buf != nullptr: room of wt_bytes bytes for the kernels in parts
 int run_split(const float* x, const float* w, float* y, const iolb_shape& s, const SplitChoice& ch, int layout, float* wt_buf, size_t wt_bytes)
 {
     if (wt_buf && ch.weight_bytes > wt_bytes) return IOLB_EWORKSPACE;
@@ -504,7 +504,7 @@ int make_wino_shape(int N, int C, int H, int W, int K, int m, iolb_shape* s, int
 // Channel rows per plane of a caller-held transformed-kernel buffer: every stage depth divides 16.
 int pretransformed_rows(int C) { return (C + 15) / 16 * 16; }
 
-// ---- Winograd on the bf16 matrix cores, operands in three parts ------------------------------
+// ---- Winograd on the 16-bit matrix cores, operands in parts ----------------------------------
 struct SplitWino {
     enum { NONE, PRODUCT, FUSED } kind = NONE;                // transforms and a product of their own, or one kernel
     iolb::SplitPointGeom g{};

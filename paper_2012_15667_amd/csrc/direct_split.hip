@@ -643,7 +643,7 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
     write_y(std::integral_constant<int, MARKED_ONLY>{});
 }
 
-// w[K][C][R][S] -> the operands of the matrix steps, [chunk][step][16-channel block][part][lane][8 bf16].  A workgroup per 16
+// w[K][C][R][S] -> the operands of the matrix steps, [chunk][step][16-channel block][part][lane][8 values].  A workgroup per 16
 // kernels, `octets` groups of eight channels and up to 16 taps (all of them, or slices of 16), whose pieces its threads take
 // one each: rows of w are read as they lie, 16 floats and more at a time, and go through LDS.  Bound by latency: a load, an
 // LDS pass and a store one after the other (gathered in single floats, 256 -> 256 kernels of 3 x 3 took 7.4 us, now 5.7; 7 x

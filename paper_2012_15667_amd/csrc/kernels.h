@@ -59,7 +59,7 @@ hipError_t launch_direct_mfma(const float* x, const float* wt, float* y, const D
 // The same for the channels-innermost tensor layout (g.hwc = 1).
 hipError_t launch_direct_mfma_hwc(const float* x, const float* wt, float* y, const DirectGeom& g, hipStream_t st);
 
-// Direct convolution on the bf16 matrix cores with operands in three parts (direct_split.hip).
+// Direct convolution on the 16-bit matrix cores with operands in parts (direct_split.hip).
 struct SplitGeom {
     int N, C, H, W, K, R, S, stride, pad, P, Q;
     int pad_w;

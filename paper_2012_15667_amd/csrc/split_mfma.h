@@ -1,11 +1,12 @@
-// fp32 products on the bf16 matrix cores: every operand is cut into three bf16 parts, x = h + m + l, and the product
+// fp32 products on the 16-bit matrix cores, in three bf16 parts or, from some sixty channels on, in two fp16 parts (further down).
+// Three bf16 parts: every operand is cut into x = h + m + l, and the product
 // of two operands is taken as the six products of parts that reach fp32 precision (h h, h m, m h, m m, h l, l h; the
 // three left out are each below 2^-24 of the product).  A v_mfma_f32_16x16x32_bf16 does 16 times the multiply-adds of an fp32
 // matrix instruction in the same time, so six of them still leave a factor of 16 / 6; sums stay in fp32.  Measured on
 // register operands: 1937 TFLOP/s of bf16 products = 323 TFLOP/s of fp32 products, against 155 of the fp32 instructions
 // (32x32x16_bf16: 1430 - 1690).  Error of a sum of n such products against 64 bits (relative, 2-norm; x uniform on
 // [0, 1], w normal), fp32 instructions / this: n = 144 2.2e-7 / 1.9e-7, 576 4.2e-7 / 3.5e-7, 4608 1.23e-6 / 0.99e-6,
-// 12800 1.9e-6 / 1.7e-6.  Three products (two parts) would give 4e-6 at every n: not used.
+// 12800 1.9e-6 / 1.7e-6.  Two bf16 parts would give 4e-6 at every n: not used.
 #ifndef IOLB_SPLIT_MFMA_H
 #define IOLB_SPLIT_MFMA_H
 
@@ -128,10 +129,10 @@ __device__ __forceinline__ void kept_eight(const u32x4& h, const u32x4& m, const
 //   fp16 has 5 bits of exponent, so e follows the data: a sample's largest value goes to [2^8, 2^9).  Seven bits are left above it;
 // a value beyond them gives infinite or NaN parts, sums that show it, and the output is computed again in plain fp32.  Below 2^-2 parts
 // lose bits to the smallest denormal, 2^-24: an operand is off by up to 2^-25 then, which is nothing beside a larger operand of
-// the same sum.  So a group of operands that enter the same sums together (a pixel's channels, a kernel's taps and channels) has to
-// hold at least one of 2^-2, or only zeros; where one does not, its outputs are computed again, too.  That is slow, and what networks
-// compute does not come near it: single values 128 times, or whole pixels a thousandth of, what a sample of some thousand values has
-// as its largest.
+// the same sum.  So a group of operands that enter the same sums together (an output's window, a kernel's taps and channels) has to
+// hold at least one of 2^-2, or only zeros; where one does not, its outputs are computed again, too.  That is slow where it
+// happens: 64 -> 64 at 56 x 56, batch 32, with one value of each image 1e5 times the others 35 -> 176 us, with a quarter of each image
+// 1e-5 of the rest 175, nine in ten values zero 36 (in three bf16 parts, whatever the finite values, 51).
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 constexpr int HALF_TOP = 9;                                  // sample below 2^9

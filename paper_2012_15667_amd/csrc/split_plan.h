@@ -1,4 +1,4 @@
-// Which layers run on the bf16 matrix cores with operands in three parts, and on which workgroup shape.
+// Which layers run on the 16-bit matrix cores with operands in parts, and on which workgroup shape.
 #ifndef IOLB_SPLIT_PLAN_H
 #define IOLB_SPLIT_PLAN_H
 

@@ -4,7 +4,8 @@
 //
 // A step is 32 channels.  The inputs of chunk t + 1 are split and written to one LDS buffer while chunk t is multiplied
 // from the other; their loads are issued three chunks ahead and kept in registers, two neighbouring pixels per load where
-// the layout has them.  Every pixel has a scale of its own, from the first 32 of its channels and a few more, and what they are for its neighbours.  The split's arithmetic is
+// the layout has them.  Every pixel has a scale of its own: its image's largest value in the block, from the first 32 channels and a few more, but at
+// most 512 times the largest of the pixel's own sample.  The split's arithmetic is
 // placed between the matrix instructions, three vector
 // instructions after each, where it costs little (a 16-bit matrix instruction leaves the vector pipeline free; measured:
 // eight vector instructions per 32-cycle matrix instruction 1433 against 1631 TFLOP/s).  wt is not declared restrict on
@@ -13,7 +14,7 @@
 // What bounds it: operands on their way in, about 20 bytes per clock and compute unit (a block of z channels by npix pixels needs
 // 128 z + 128 npix bytes per 32 channels), and the latency of small layers' steps.  16 planes of 512 x 12544 x 512 (F(2x2)), 256 x 64
 // blocks: 840 us on the fp32 instructions, 541 in three bf16 parts, 396 = 266 TFLOP/s in two fp16 parts.  1 x 1, 768 -> 192 at 17 x 17,
-// batch 64, whole call: 66, 43.4, 36.8 us; 320 -> 224 at 170 x 170, batch 22 578 -> 454.  Zero pixels that each looked for their image's
+// batch 64, whole call: 66, 43.4, 35.6 us; 320 -> 224 at 170 x 170, batch 22 578 -> 454.  Zero pixels that each looked for their image's
 // largest value cost 12 us of the 17 x 17 layer: now a wave does it once.
 // Measured with three parts and taken back: the weights of chunk t + 2 loaded before the inputs of chunk t + 3, so that these have two steps
 // to arrive (the same product 545 -> 573 us).
@@ -242,7 +243,7 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
     barrier();
     fetch(bf[0], mine);
 
-    // One step = 32 channels.  While chunk t is multiplied, chunk t + 1 is split into its three parts (its loads were
+    // One step = 32 channels.  While chunk t is multiplied, chunk t + 1 is split into its parts (its loads were
     // issued two steps ago) and written to the other buffer, and the loads of chunk t + 3 are issued.
     auto step = [&](int t, u32x4 (&a)[MB * 2], u32x4 (&an)[MB * 2], float (&v)[IB][CH * PX]) {
         if (t + 1 < nchunks) wp += wstep;

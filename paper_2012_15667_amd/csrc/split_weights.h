@@ -36,7 +36,7 @@ __device__ __forceinline__ void stage_kernels(const float* __restrict__ w, float
     }
 }
 
-// A piece of eight values: its three parts, each to its 64 lanes.
+// A piece of eight values: its three bf16 parts, each to its 64 lanes.
 __device__ __forceinline__ void store_parts(u32x4* to, const unsigned short (&p)[3][8])
 {
 #pragma unroll

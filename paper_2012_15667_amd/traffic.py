@@ -162,7 +162,8 @@ def main():
     w("convolution that term is below compulsory on every layer, for Winograd it is the printed expression of Sec. 4.3.")
     if args.sq:
         w("Matrix-core figures of a layer's main kernel: MFMA instructions against the algorithmic count (flop / 4096: one")
-        w("v_mfma_f32_32x32x2_f32 is 4096 flop, one 16x16x32_bf16 of the split kernels 16384 / 6, one 32x32x16_bf16 of the fused one 32768 / 6; direct 2 N K P Q C R S, Winograd 2 (m+2)^2 tiles C K) shows the work the kernel")
+        w("v_mfma_f32_32x32x2_f32 is 4096 flop, one 16x16x32 of the split kernels 16384 / 3 in two fp16 parts and 16384 / 6 in three bf16")
+        w("parts, one 32x32x16 of the fused one twice that; direct 2 N K P Q C R S, Winograd 2 (m+2)^2 tiles C K) shows the work the kernel")
         w("adds (channel padding, idle slots); MFMA busy = SQ_VALU_MFMA_BUSY_CYCLES / (1024 SIMDs x GRBM_GUI_ACTIVE / 8 XCDs);")
         w("LDS conflicts = SQ_LDS_BANK_CONFLICT / SQ_LDS_IDX_ACTIVE.")
     w("")
@@ -200,8 +201,10 @@ def main():
                 Q = (L.W + 2 * L.pad - L.S) // L.stride + 1
                 flop = 2.0 * L.N * L.K * P * Q * L.C * L.R * L.S
             per_instr = 4096.0
-            if "split_" in main_name:                 # six products of parts; one 16x16x32 instruction is 16384 flop
-                per_instr = (32768.0 if "wino_split" in main_name else 16384.0) / 6          # (32x32x16 there)
+            if "split_" in main_name:                 # three products of two parts or six of three; one 16x16x32 instruction is 16384 flop
+                last = main_name.rstrip("> ").split(",")[-1].strip() if "<" in main_name else ""
+                three = ("split_conv" in main_name and last == "false") or ("wino_split" in main_name and last == "3")
+                per_instr = (32768.0 if "wino_split" in main_name else 16384.0) / (6 if three else 3)          # (32x32x16 there)
             if c["SQ_INSTS_MFMA"] > 0 and c["GRBM_GUI_ACTIVE"] > 0:
                 w("    main kernel: %.0f MFMA instructions = %.3f x algorithmic;  MFMA busy %.3f;  LDS conflicts %.3f" % (
                     c["SQ_INSTS_MFMA"], c["SQ_INSTS_MFMA"] / (flop / per_instr),
