@@ -14,8 +14,13 @@
 //
 // Two parts: the scales (split_mfma.h) are of a kernel, and of an image in a block, from a sample of its first loads and 64 values
 // spread over the channels, known before the first of them is split.  What the split finds of each pixel's largest value is kept in
-// LDS; after the last step every wave looks through it for pixels that are too small for the scale, and takes its block again on the
-// fp32 instructions for outputs whose window has no others.  That and one barrier more cost 1.2 us of a workgroup's life.  Measured whole calls, three
+// LDS; after the last step every wave looks through it for pixels that are too small for the scale, and at the largest of each
+// kernel's sums over a lane's pixels, and computes outputs again whose window has no larger values, or whose kernel's sums are
+// too small for what its operands may have lost: few of an image as fp32 sums of their own, more by taking the wave's block again on the
+// fp32 instructions.  Nearly always all is well by one line for all kernels, from bounds; only otherwise is each kernel's own line
+// computed, from what the weights' launch tells of it.  The scales and one barrier more cost 1.2 us of a workgroup's life, the look at
+// the kernels' sums 0.3 - 0.5 (64 -> 64 at 56 x 56, batch 32 33.4 and 34.3 us, 256 -> 256, batch 64 602 and 605; with each kernel's own line
+// there always, by v_dot2 beside the matrix instructions, 36.3 and 609).  Measured whole calls, three
 // bf16 parts / two fp16 parts: 3x3, 256 -> 256 at 56 x 56, batch 64 927 / 605 us (392 TFLOP/s of fp32 products; register-only 646),
 // 64 -> 64 at 56 x 56, batch 32 50 / 38, 128 -> 256 at 28 x 28, stride 2 57 / 42, 5x5, 96 -> 256 at 27 x 27, batch 16, channels
 // innermost 76 / 58; 80 drawn layers 1.17 in the mean.
@@ -60,8 +65,13 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t image_buffer(const float* x, c
 
 template <int MB, int NB, int WM, int WN, bool VEC, bool APART, bool OWN, bool TWO>
 __global__ void __launch_bounds__(64 * WM * WN, 2)
-split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitGeom g, SplitDivisors dv, SplitOwn own)
+split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitGeom given, SplitDivisors dv, SplitOwn own)
 {
+    // All of it is read here.  The compiler would otherwise read field by field where they are used, one wait after the other (33 scalar loads
+    // before the first matrix step, and not 17: 64 -> 64 at 56 x 56, batch 32, 33.9 us and 33.5).
+    SplitGeom g = given;
+#pragma unroll
+    for (unsigned i = 0; i < (TWO ? sizeof(g) / 4 : 0); ++i) reinterpret_cast<int*>(&g)[i] = __builtin_amdgcn_readfirstlane(reinterpret_cast<const int*>(&given)[i]);
     extern __shared__ u32x4 lds16[];
     char* const lds = reinterpret_cast<char*>(lds16);
     constexpr int T = 64 * WM * WN;
@@ -120,6 +130,7 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
     unsigned* const sample = most + g.halo;
 
     const int nchunks = __builtin_amdgcn_readfirstlane((C + 8 * CH8 - 1) / (8 * CH8));
+    const int total = nchunks * steps;
     // weights of matrix step t: [t][16-channel block][part][lane]
     const int kb16 = kb * (MB * WM) + wm_i * MB;
     const size_t wstep = (size_t)g.Kb16 * WBLOCK;           // 16-byte pieces per step
@@ -246,8 +257,9 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
     // pixels of the first items, of several images over all of them; what undoes the kernels' scales.
     float spread = 0.f, my_kback = 0.f;
     unsigned spread_image = 0;
+    constexpr int Z = 16 * MB * WM;
     if constexpr (TWO) {
-        static_assert(16 * MB * WM <= T, "one kernel per thread");
+        static_assert(Z <= T, "one kernel per thread");
         if (g.b > 1 || wave == 0) {
             uint2 e = {OUTSIDE, 0};
             if (g.b > 1) e = place(tid * items / T);
@@ -261,7 +273,7 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
         if (g.b > 1) {
             for (int i = tid; i < g.b; i += T) sample[i] = 0;
         }
-        if (tid < 16 * MB * WM) my_kback = reinterpret_cast<const float*>(wt + (size_t)nchunks * steps * wstep)[kb * (16 * MB * WM) + tid];
+        if (tid < Z) my_kback = reinterpret_cast<const float*>(wt + (size_t)total * wstep)[kb * Z + tid];
         __builtin_amdgcn_sched_barrier(0);
     }
     u32x4* const parts = reinterpret_cast<u32x4*>(lds + split_tables_bytes(g));     // a workgroup's own kernels (OWN)
@@ -269,7 +281,6 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
     // the latency of its loads.  A step issues first the weights, then the inputs.
     constexpr int AHEAD = OWN ? 1 : MB == 1 ? 3 : 2;
     u32x4 a[AHEAD + 1][MB * PARTS];
-    const int total = nchunks * steps;
     auto load_weights = [&](u32x4 (&f)[MB * PARTS], int t) {
         if constexpr (OWN) {
             const u32x4* from = parts + ((t < total ? t : 0) * (MB * WM) + wm_i * MB) * 192 + lane;
@@ -308,7 +319,7 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
     const int row_w = C * RS;
     if constexpr (OWN) {
         float* const rows = reinterpret_cast<float*>(parts + nchunks * steps * (MB * WM * 192));
-        constexpr int Z = 16 * MB * WM, PER = 8;
+        constexpr int PER = 8;
         const float* w = reinterpret_cast<const float*>(wt);
         const int k0 = kb * Z, have = (g.K - k0 < Z ? g.K - k0 : Z) * row_w;
         for (int e0 = tid; e0 < Z * row_w + tid; e0 += T * PER) {
@@ -403,7 +414,7 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
         }
     }
     if constexpr (TWO) {
-        if (tid < 16 * MB * WM) kback[tid] = my_kback;
+        if (tid < Z) kback[tid] = my_kback;
     }
     barrier();
     if constexpr (OWN) load_weights(a[0], 0);
@@ -495,61 +506,161 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
         });
 
     // each partial sum is complete: write the block once.  Register i of a 16 x 16 block holds channel 4 grp + i of
-    // pixel l16.  Sums that are not finite are marked.
+    // pixel l16.
     const size_t PQ = (size_t)g.P * g.Q;
-    unsigned long long again = 0;
+    unsigned long long again = 0;                           // outputs that are computed once more
+    static_assert(MB * NB * 4 <= 64, "one mark per output");
     // what undoes the scales (one image in a block: its own)
     float back = 1.f;
     f32x4 kb4[MB];
-    bool finite = false;
+    bool fine;
+    // The largest of the sums of a kernel, acc[mb][.][i], that are judged together: a lane's, and those of its three neighbours where it has
+    // fewer than four; of several images in a block the neighbours' of the same image, at the same nb.
+    // (maximum: NaN where one of them is)
+    auto together = [&](float v, int im) {
+        auto take = [&](auto bit_c) {
+            const float o = __uint_as_float(quad_other<decltype(bit_c)::value>(__float_as_uint(v)));
+            v = (int)quad_other<decltype(bit_c)::value>((unsigned)im) == im ? __builtin_elementwise_maximum(v, o) : v;
+        };
+        take(std::integral_constant<int, 0>{});
+        take(std::integral_constant<int, 1>{});
+        return v;
+    };
+    auto largest_sum = [&](int mb, int i) {
+        float m = 0.f;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) m = __builtin_elementwise_maximum(m, __builtin_fabsf(acc[mb][nb][i]));
+        return NB < 4 ? together(m, 0) : m;
+    };
+    constexpr float MOST = 3.402823466e38f;                 // a sum beyond it is not finite
+    auto image_of = [&](int nb) {
+        const int slot = (wn_i * NB + nb) * 16 + (opaque(lane) & 15);
+        return dv.txy.of(slot < npix ? slot : npix - 1);
+    };
     if constexpr (TWO) {
-        // (most waves have no sum that is not finite: 0 times it is NaN, and so is the sum of those)
-        f32x4 z = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) z[i] = __builtin_fmaf(acc[mb][nb][i], 0.f, z[i]);
         back = half_unscale(half_scale_bits(largest()));
         // pixels whose channels are all too small for their scale, and not all zeros: the windows they are in are looked at below
         bool small = false;
-        for (int i = lane; i < g.halo; i += 64) small |= most[i] - 1 < __float_as_uint(HALF_LEAST) - 1;
-        finite = __builtin_amdgcn_ballot_w64(small || z[0] + z[1] + z[2] + z[3] != 0.f) == 0;
+        unsigned brightest = 0;
+        for (int i = lane; i < g.halo; i += 64) {
+            small |= most[i] - 1 < __float_as_uint(HALF_LEAST) - 1;
+            brightest = most[i] > brightest ? most[i] : brightest;
+        }
+        const float inputs = __uint_as_float(wave_max(brightest));
+        // Whether all sums are finite and no kernel's too small, by the largest of kernels and inputs: mostly so, and then they are only written.
+        const float line = half_line(own.facts * HALF_PIECE, (float)(C * RS), inputs);
+        float least = MOST, greatest = 0.f;
+        // (not those of a lane all of whose pixels lie beyond the image or the batch)
+        bool outputs = true;
+        if ((y0 + g.ty > g.P) | (x0 + g.tx > g.Q) | (n0 + g.b > g.N)) {
+            outputs = false;
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) kb4[mb] = *reinterpret_cast<const f32x4*>(kback + (wm_i * MB + mb) * 16 + 4 * (lane >> 4));
+            for (int nb = 0; nb < NB; ++nb) {
+                const int slot = (wn_i * NB + nb) * 16 + l16, im = dv.txy.of(slot), rem = slot - im * txy, row = dv.tx.of(rem);
+                outputs |= (slot < npix) & (n0 + im < g.N) & (y0 + row < g.P) & (x0 + rem - row * g.tx < g.Q);
+            }
+        }
+        auto see = [&](float m, int mb, int i) {
+            greatest = __builtin_elementwise_maximum(greatest, m);
+            least = __builtin_fminf(least, outputs && (kb16 + mb) * 16 + 4 * grp + i < g.K ? m : MOST);
+        };
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) kb4[mb] = *reinterpret_cast<const f32x4*>(kback + (wm_i * MB + mb) * 16 + 4 * grp);
+        if (g.b > 1) {
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                const int im = image_of(nb);
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) see(together(__builtin_fabsf(acc[mb][nb][i]), im), mb, i);
+            }
+        } else {
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) see(largest_sum(mb, i), mb, i);
+        }
+        small |= !(least >= line) | !(greatest <= MOST);
+        fine = __builtin_amdgcn_ballot_w64(small) == 0;
+    } else {
+        float m = 0.f;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) m = __builtin_elementwise_maximum(m, __builtin_fabsf(acc[mb][nb][i]));
+        fine = __builtin_amdgcn_ballot_w64(!(m <= MOST)) == 0;
     }
-    static_assert(MB * NB * 4 <= 64, "one mark per output");
-    // once without looking at them where all are finite; or once, marking those that are not, and then those marked
-    enum { PLAIN, MARKING, MARKED_ONLY };
-    auto write_y = [&](auto mode_c) {
-        constexpr int MODE = decltype(mode_c)::value;
-        constexpr bool MARKED = MODE == MARKED_ONLY;
+    // Otherwise each output for itself: sums that are not finite; those whose window has no value that is large enough, and not only
+    // zeros; those of kernels whose sums are too small for it.
+    if (__builtin_expect(!fine, 0)) {
+        float m1[MB][4];
+        KernelFacts facts[MB][4];
+        if constexpr (TWO)
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) {
+                const KernelFacts* from = reinterpret_cast<const KernelFacts*>(reinterpret_cast<const float*>(wt + (size_t)total * wstep) + 16 * g.Kb16) +
+                                          (kb16 + mb) * 16 + 4 * (opaque(lane) >> 4);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    m1[mb][i] = largest_sum(mb, i);
+                    facts[mb][i] = {0.f, 0.f};
+                }
+                for (int p = 0; p < own.facts; ++p, from += 16 * g.Kb16)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        facts[mb][i].squares += from[i].squares;
+                        facts[mb][i].small += from[i].small;
+                    }
+            }
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            const int slot = (wn_i * NB + nb) * 16 + (opaque(lane) & 15);
+            const int im = dv.txy.of(slot), rem = slot - im * txy, row = dv.tx.of(rem), col = rem - row * g.tx;
+            const bool exists = slot < npix && n0 + im < g.N && y0 + row < g.P && x0 + col < g.Q;
+            unsigned window = 0;
+            if constexpr (TWO)
+                if (exists)
+                    for (int r = 0; r < g.R; ++r)
+                        for (int s = 0; s < g.S; ++s) {
+                            const unsigned m = most[(im * g.yh + row * g.esy + r) * g.rowp + col * g.esx + s];
+                            window = m > window ? m : window;
+                        }
+            const bool lost = TWO && window - 1 < __float_as_uint(HALF_LEAST) - 1;
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float own_sum = __builtin_fabsf(acc[mb][nb][i]);
+                    bool bad = lost || !(own_sum <= MOST);
+                    if constexpr (TWO) {
+                        // (a NaN among them: not this output's, whose own sum is finite)
+                        const float m = g.b > 1 ? together(own_sum, image_of(nb)) : m1[mb][i];
+                        bad |= window != 0 && (m < half_line(facts[mb][i].squares, facts[mb][i].small, __uint_as_float(window)) || !(facts[mb][i].squares <= MOST));
+                    }
+                    if (bad && exists && (kb16 + mb) * 16 + 4 * (opaque(lane) >> 4) + i < g.K) again |= 1ull << ((nb * MB + mb) * 4 + i);
+                }
+        }
+    }
+    // all of them; the second time those that were marked
+    auto write_y = [&](auto marked_c) {
+        constexpr bool MARKED = decltype(marked_c)::value;
         const int l16 = opaque(lane) & 15, grp = opaque(lane) >> 4;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
             const int slot = (wn_i * NB + nb) * 16 + l16;
             const int im = dv.txy.of(slot), rem = slot - im * txy, row = dv.tx.of(rem), py = y0 + row, px = x0 + rem - row * g.tx;
             if (slot >= npix || n0 + im >= g.N || py >= g.P || px >= g.Q) continue;
-            if constexpr (TWO && !MARKED) {
+            if constexpr (TWO && !MARKED)
                 if (g.b > 1) back = half_unscale(half_scale_bits(sample[im]));
-                // no value of this output's window large enough, and not all of them zero
-                unsigned window = 0;
-                if constexpr (MODE == MARKING)
-                    for (int r = 0; r < g.R; ++r)
-                        for (int s = 0; s < g.S; ++s) {
-                            const unsigned m = most[(im * g.yh + row * g.esy + r) * g.rowp + (rem - row * g.tx) * g.esx + s];
-                            window = m > window ? m : window;
-                        }
-                if (MODE == MARKING && window - 1 < __float_as_uint(HALF_LEAST) - 1) again |= ((1ull << (4 * MB - 1) << 1) - 1) << (nb * MB * 4);
-            }
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) {
                 const int k0 = (kb16 + mb) * 16 + 4 * grp, bit = (nb * MB + mb) * 4;
                 if constexpr (!MARKED) {
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        if (MODE == MARKING && !(__builtin_fabsf(acc[mb][nb][i]) <= 3.402823466e38f)) again |= 1ull << (bit + i);
                         if constexpr (TWO) acc[mb][nb][i] = acc[mb][nb][i] * back * kb4[mb][i];
                         else               acc[mb][nb][i] *= SPLIT_UNSCALE;
                     }
@@ -572,12 +683,46 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
             }
         }
     };
-    if (finite) {
-        write_y(std::integral_constant<int, PLAIN>{});
-        return;
+    write_y(std::false_type{});
+    if (__builtin_expect(fine || __builtin_amdgcn_ballot_w64(again != 0) == 0, 1)) return;
+
+    // Few marked outputs of an image are sums of their own, a wave's lanes one channel each: so single sums that are small by chance, where
+    // few are judged together, or windows of one small value cost 1 - 2 us and not a block.  (Image by image: what other images hold
+    // decides nothing.)
+    if constexpr (TWO) {
+        constexpr int FEW = 16;
+        unsigned long long many = 0;
+        while (const unsigned long long lanes = __builtin_amdgcn_ballot_w64(again != 0)) {
+            const int src = __builtin_ctzll(lanes);
+            const int nb0 = __builtin_amdgcn_readlane((int)(__builtin_ctzll(again | 1ull << 63) / (4 * MB)), src);
+            const int image = dv.txy.of((wn_i * NB + nb0) * 16 + (src & 15));
+            unsigned long long mine = 0;
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) mine |= image_of(nb) == image ? again & (((1ull << (4 * MB - 1) << 1) - 1) << (nb * MB * 4)) : 0;
+            again &= ~mine;
+            if (wave_sum((float)__popcll(mine)) > FEW) { many |= mine; continue; }
+            while (const unsigned long long left = __builtin_amdgcn_ballot_w64(mine != 0)) {
+                const int at = __builtin_ctzll(left);
+                const int bit = __builtin_amdgcn_readlane(__builtin_ctzll(mine | 1ull << 63), at);
+                if (lane == at) mine &= mine - 1;
+                const int nb = bit / (4 * MB), k = (kb16 + bit / 4 % MB) * 16 + 4 * (at >> 4) + (bit & 3);
+                const int rem = (wn_i * NB + nb) * 16 + (at & 15) - image * txy, row = rem / g.tx, n = n0 + image, py = y0 + row, px = x0 + rem % g.tx;
+                float sum = 0.f;
+                for (int r = 0; r < g.R; ++r)
+                    for (int s = 0; s < g.S; ++s) {
+                        const int gy = py * g.stride - g.pad + r, gx = px * g.stride - g.pad_w + s;
+                        if (gy < 0 || gy >= g.H || gx < 0 || gx >= g.W) continue;
+                        const float* xp = x + (size_t)n * C * g.H * g.W + (g.hwc ? ((size_t)gy * g.W + gx) * C : (size_t)gy * g.W + gx);
+                        const float* wp1 = own.w + (size_t)k * C * RS + (own.transposed ? s * g.R + r : r * g.S + s);
+                        for (int c = lane; c < C; c += 64) sum = __builtin_fmaf(xp[(size_t)c * (cstep / 4)], wp1[(size_t)c * RS], sum);
+                    }
+                sum = wave_sum(sum);
+                if (lane == at) y[g.hwc ? (((size_t)n * g.P + py) * g.Q + px) * g.K + k : ((size_t)n * g.K + k) * PQ + (size_t)py * g.Q + px] = sum;
+            }
+        }
+        again = many;
+        if (__builtin_amdgcn_ballot_w64(again != 0) == 0) return;
     }
-    write_y(std::integral_constant<int, MARKING>{});
-    if (__builtin_amdgcn_ballot_w64(again != 0) == 0) return;
 
     // A wave with a marked output takes its whole block again on the fp32 matrix instructions, which hold their sums in
     // the same registers: in the same steps, four units of eight channels, the inputs from memory, those of the next 16
@@ -640,7 +785,7 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
             __builtin_amdgcn_sched_barrier(0);
         });
     }
-    write_y(std::integral_constant<int, MARKED_ONLY>{});
+    write_y(std::true_type{});
 }
 
 // w[K][C][R][S] -> the operands of the matrix steps, [chunk][step][16-channel block][part][lane][8 values].  A workgroup per 16
@@ -655,7 +800,7 @@ split_weights_kernel(const float* __restrict__ w, u32x4* __restrict__ wt, int K,
                      int octets, int all_octets, int slices, int transposed)
 {
     constexpr int PITCH = ROW + 1, ROWS = 16, MINE = ROWS / 4;
-    __shared__ unsigned scales[ROWS];                       // TWO: scale of each kernel, lowest bit: too small for it here
+    __shared__ unsigned scales[ROWS];                       // TWO: scale of each kernel, lowest bit: too small or too large for it here
     __shared__ float rows[ROWS * PITCH];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kb = blockIdx.x % Kb16, rest = blockIdx.x / Kb16, first = rest / slices * octets, t0 = rest % slices * SLICE;
@@ -690,6 +835,7 @@ split_weights_kernel(const float* __restrict__ w, u32x4* __restrict__ wt, int K,
     if constexpr (TWO) {
         // A kernel's scale follows from 64 of its values, 16 runs of four spread over it: the same in each of its workgroups.
         float* const kback = reinterpret_cast<float*>(wt + (size_t)steps * (all_octets / ch8) * Kb16 * 128);
+        KernelFacts* const facts = reinterpret_cast<KernelFacts*>(kback + 16 * Kb16) + (size_t)rest * 16 * Kb16 + k0;
 #pragma unroll
         for (int j = 0; j < MINE; ++j) {
             const int k = wave * MINE + j;
@@ -697,9 +843,14 @@ split_weights_kernel(const float* __restrict__ w, u32x4* __restrict__ wt, int K,
             here = here > there ? here : there;
             const unsigned scale = half_scale_bits(wave_max(finite_bits(some[j])));
             here = wave_max(here);
+            const float a = v[0][j] * __uint_as_float(scale), b = v[1][j] * __uint_as_float(scale);
+            const float squares = wave_sum(__builtin_fmaf(a, a, b * b));
+            const int small = __popcll(__builtin_amdgcn_ballot_w64(v[0][j] != 0.f && __builtin_fabsf(a) < HALF_LEAST)) +
+                              __popcll(__builtin_amdgcn_ballot_w64(v[1][j] != 0.f && __builtin_fabsf(b) < HALF_LEAST));
             if (lane == 0) {
-                // (of fewer than 32 values here some are all small now and then: not judged)
-                scales[k] = scale + (here != 0 && channels * ts >= 32 && __uint_as_float(here) * __uint_as_float(scale) < HALF_LEAST);
+                facts[k] = {squares, (float)small};
+                // (of fewer than 32 values here some are all small now and then: left to the sums)
+                scales[k] = scale + ((here != 0 && channels * ts >= 32 && __uint_as_float(here) * __uint_as_float(scale) < HALF_LEAST) || !(squares <= HALF_PIECE));
                 if (first == 0 && t0 == 0) kback[k0 + k] = half_unscale(scale);
             }
         }
@@ -713,7 +864,7 @@ split_weights_kernel(const float* __restrict__ w, u32x4* __restrict__ wt, int K,
     if (o >= octets || octet >= all_octets || t >= taps) return;
     const float* from = rows + k * PITCH + o * 8 * ts + t - t0;
     if constexpr (TWO) {
-        // (a kernel too small for its scale: NaN in place of its parts here, which every sum of it shows)
+        // (a kernel that does not fit its scale: NaN in place of its parts here, which every sum of it shows)
         const float scale = __uint_as_float(scales[k] & ~1u);
         const unsigned poison = scales[k] & 1 ? 0x7e007e00u : 0u;
         float g8[8];
@@ -755,12 +906,14 @@ hipError_t launch_one(const float* x, const u32x4* wt, float* y, const SplitGeom
 hipError_t launch_split_weights(const float* w, void* wt, int K, int C, int R, int S, int ch8, int Kb16, int parts, bool transposed, hipStream_t st)
 {
     if (ch8 != 1 && ch8 != 2 && ch8 != 4) return hipErrorInvalidValue;
-    const int steps = (R * S * ch8 + 3) / 4, octets = (C + 8 * ch8 - 1) / (8 * ch8) * ch8, taps = 4 * steps / ch8;
-    const int per = taps < SLICE ? SLICE / taps : 1, slices = (taps + SLICE - 1) / SLICE;
-    const long long blocks = (octets + per - 1LL) / per * slices * Kb16;
+    const SplitPieces p = split_pieces(C, R * S, ch8);
+    const long long blocks = (long long)p.pieces * Kb16;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(parts == 2 ? split_weights_kernel<true> : split_weights_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, st, w, (u32x4*)wt, K, C, R, S, ch8, steps, Kb16, per, octets,
-                       slices, transposed ? 1 : 0);
+    // the room of three parts, 3072 bytes per unit, holds two, the scales and the facts
+    static_assert(SLICE == 16);
+    if (parts == 2 && 2048LL * (p.octets / ch8) * p.steps + 64 + 128LL * p.pieces > 3072LL * (p.octets / ch8) * p.steps) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(parts == 2 ? split_weights_kernel<true> : split_weights_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, st, w, (u32x4*)wt, K, C, R, S, ch8, p.steps,
+                       Kb16, p.per, p.octets, p.slices, transposed ? 1 : 0);
     return hipGetLastError();
 }
 

@@ -97,6 +97,7 @@ struct SplitOwn {
     Divisor steps, row;
     int transposed;
     const float* w;            // the kernels as the caller holds them, for blocks that are taken again
+    int facts;                 // pieces that a kernel's facts come in
 };
 constexpr int SPLIT_BATCH = 2;          // (pixel, 8 channels) items of the input tile that a thread stages at once
 // The workgroup shapes that exist: blocks per wave (channels, pixels), wave grid (channels, pixels).  Of two with the same
@@ -129,10 +130,14 @@ __host__ __device__ constexpr int split_pixel_bytes(int parts) { return parts ==
 __host__ __device__ constexpr int split_planes(int parts) { return parts == 2 ? 2 : 1; }
 // buffers of the input tile, offsets of the matrix steps' units, table of the input tile's elements, whole 16 bytes; of two parts
 // also the kernels' scales, the pixels' largest values and the images'
+__host__ __device__ inline int split_two_bytes(const SplitGeom& g)
+{
+    return g.parts == 2 ? 64 * g.mb * g.wm + 4 * g.halo + 4 * (g.b > 4 ? g.b : 4) : 0;
+}
 __host__ __device__ inline int split_tables_bytes(const SplitGeom& g)
 {
-    const int steps = (g.R * g.S * g.ch8 + 3) / 4, more = g.parts == 2 ? 64 * g.mb * g.wm + 4 * g.halo + 4 * (g.b > 4 ? g.b : 4) : 0;
-    return (g.nbuf * g.ch8 * split_planes(g.parts) * g.b * g.yh * g.rowb + 4 * ((4 * steps + 1) & ~1) + 8 * g.ch8 * g.halo + more + 15) & ~15;
+    const int steps = (g.R * g.S * g.ch8 + 3) / 4;
+    return (g.nbuf * g.ch8 * split_planes(g.parts) * g.b * g.yh * g.rowb + 4 * ((4 * steps + 1) & ~1) + 8 * g.ch8 * g.halo + split_two_bytes(g) + 15) & ~15;
 }
 // ... and the parts and rows of a workgroup's own kernels
 inline long long split_own_bytes(const SplitGeom& g)
@@ -141,11 +146,25 @@ inline long long split_own_bytes(const SplitGeom& g)
 }
 inline long long split_lds_bytes(const SplitGeom& g, bool own = false)
 {
-    const long long more = g.parts == 2 ? 64LL * g.mb * g.wm + 4LL * g.halo + 4 * (g.b > 4 ? g.b : 4) : 0;
     const long long tables = ((long long)g.nbuf * g.ch8 * split_planes(g.parts) * g.b * g.yh * g.rowb + 4 * ((4 * split_steps(g) + 1) & ~1) +
-                              8LL * g.ch8 * g.halo + more + 15) & ~15LL;
+                              8LL * g.ch8 * g.halo + split_two_bytes(g) + 15) & ~15LL;
     return tables + (own ? split_own_bytes(g) : 0);
 }
+// The kernels' parts are written by workgroups of 16 kernels, some groups of eight channels and up to 16 taps: the pieces that what they tell
+// of a kernel comes in (C in chunks of 8 ch8).
+struct SplitPieces { int steps, octets, per, slices, pieces; };
+inline SplitPieces split_pieces(int C, int RS, int ch8)
+{
+    SplitPieces p;
+    p.steps = (RS * ch8 + 3) / 4;
+    p.octets = (C + 8 * ch8 - 1) / (8 * ch8) * ch8;
+    const int taps = 4 * p.steps / ch8;
+    p.per = taps < 16 ? 16 / taps : 1;
+    p.slices = (taps + 15) / 16;
+    p.pieces = (p.octets + p.per - 1) / p.per * p.slices;
+    return p;
+}
+inline int split_facts(int C, int RS, int ch8) { return split_pieces(C, RS, ch8).pieces; }
 // What the kernel divides by.  Divided are items, units and pixels of a block (what is in LDS per item and unit bounds them by 2^15,
 // their divisors too), and workgroup ids, where there are few enough.  False for a geometry beyond that.
 inline bool split_divisors(const SplitGeom& g, bool transposed, SplitDivisors* dv, SplitOwn* own)
@@ -155,7 +174,7 @@ inline bool split_divisors(const SplitGeom& g, bool transposed, SplitDivisors* d
     const bool small = (long long)pixel_blocks * g.nbk <= 32768;
     *dv = {Divisor(g.ch8), Divisor(g.halo), Divisor(g.yh * g.rowp), Divisor(g.rowp), Divisor(g.S), Divisor(g.esx), Divisor(g.esy), Divisor(g.tx * g.ty),
            Divisor(g.tx), Divisor(g.nbk), Divisor(pixel_blocks), Divisor(g.nbx), Divisor(g.nby), small};
-    *own = {Divisor(split_steps(g)), Divisor(g.C * g.R * g.S), transposed ? 1 : 0, nullptr};
+    *own = {Divisor(split_steps(g)), Divisor(g.C * g.R * g.S), transposed ? 1 : 0, nullptr, split_facts(g.C, g.R * g.S, g.ch8)};
     return true;
 }
 // The input-tile buffer of a chunk: never one that split_lds_bytes does not count.
@@ -165,7 +184,7 @@ static_assert(split_buffer(0, 1) == 0 && split_buffer(1, 1) == 0 && split_buffer
 // Room for the kernels, of which two parts with their exponents use less.  (What conv_direct_noalloc has room for follows from it.)
 inline long long split_weight_bytes(const SplitGeom& g) { return (long long)split_chunks(g) * split_steps(g) * g.Kb16 * 3072; }
 // Kernels in two or three parts in the order of the matrix steps, written from w[K][C][R][S] (transposed: w[K][C][S][R]); of two parts
-// what undoes the scales of 16 Kb16 kernels follows.
+// what undoes the scales of 16 Kb16 kernels follows, and their facts, [piece][kernel].
 hipError_t launch_split_weights(const float* w, void* wt, int K, int C, int R, int S, int ch8, int Kb16, int parts, bool transposed, hipStream_t st);
 // (own: the kernels themselves, transposed as above, in place of wt)
 hipError_t launch_split_conv(const float* x, const void* wt, const float* w, float* y, const SplitGeom& g, bool own, bool transposed, hipStream_t st);

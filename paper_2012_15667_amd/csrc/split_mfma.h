@@ -129,8 +129,9 @@ __device__ __forceinline__ void kept_eight(const u32x4& h, const u32x4& m, const
 //   fp16 has 5 bits of exponent, so e follows the data: a sample's largest value goes to [2^8, 2^9).  Seven bits are left above it;
 // a value beyond them gives infinite or NaN parts, sums that show it, and the output is computed again in plain fp32.  Below 2^-2 parts
 // lose bits to the smallest denormal, 2^-24: an operand is off by up to 2^-25 then, which is nothing beside a larger operand of
-// the same sum.  So a group of operands that enter the same sums together (an output's window, a kernel's taps and channels) has to
-// hold at least one of 2^-2, or only zeros; where one does not, its outputs are computed again, too.  That is slow where it
+// the same sum, if that one's partner is not far smaller than its own.  So a group of operands that enter the same sums together (an
+// output's window, a kernel's taps and channels) has to hold at least one of 2^-2, or only zeros, and a kernel's sums have to
+// reach a line (below) that tells whether what counts in them was cut; where they do not, outputs are computed again, too.  That is slow where it
 // happens: 64 -> 64 at 56 x 56, batch 32, with one value of each image 1e5 times the others 35 -> 176 us, with a quarter of each image
 // 1e-5 of the rest 175, nine in ten values zero 36 (in three bf16 parts, whatever the finite values, 51).
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
@@ -178,6 +179,41 @@ __device__ __forceinline__ unsigned wave_max(unsigned v)
     take(__builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false));
     return __builtin_amdgcn_readlane(v, 63);
 }
+// The sum over a wave, in a fixed order; every lane takes part.
+__device__ __forceinline__ float wave_sum(float v)
+{
+    auto take = [&](int o) { v += __int_as_float(o); };
+    take(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x111, 0xf, 0xf, false));
+    take(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x112, 0xf, 0xf, false));
+    take(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x114, 0xf, 0xf, false));
+    take(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x118, 0xf, 0xf, false));
+    take(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x142, 0xa, 0xf, false));
+    take(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x143, 0xc, 0xf, false));
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+// v of the lane whose number differs in bit 0 or 1.
+template <int BIT>
+__device__ __forceinline__ unsigned quad_other(unsigned v)
+{
+    return __builtin_amdgcn_update_dpp(0, v, BIT == 0 ? 0xB1 : 0x4E, 0xf, 0xf, false);      // quad_perm 1 0 3 2, 2 3 0 1
+}
+
+// What parts of two lose of operands that a larger one of the same sum does not make good: where that one meets a small or a zero partner,
+// the lost ones may be all of the sum.  So sums are judged when they are there, per kernel.  Scaled, an operand below HALF_LEAST is off by up to
+// 2^-25: those of the inputs by the kernel's elements, those of the kernel (`small` of them) by up to the largest input add an error of
+// 2^-25 (|kernel| + sqrt(small) inputs), |.| the 2-norm, in the root mean square and sqrt(n) times that at worst.  Sums of a kernel of which
+// none is 2^21 times that (a few pixels' of one image: one sum alone may be small by chance) are computed again: unmarked errors
+// of this kind are 2^-21 of the largest of those sums, and no more than sqrt(n) 2^-21, which is less than the n 2^-24 of n sums in fp32 from 64 products on.
+// Sums of uniform, normal, sparse and lognormal inputs by normal, Laplace, sparse and lognormal kernels are 2^4 to 2^12 above the line, whatever n.
+struct KernelFacts { float squares; float small; };          // sum of the scaled elements' squares; how many are small and not zero
+constexpr float HALF_LINE = 0.0625f;
+// A piece of a kernel, up to 128 elements, has at most these squares; where one has more (a few elements far above the sample), its parts are NaN.
+constexpr float HALF_PIECE = 0x1p27f;
+__device__ __forceinline__ float half_line(float squares, float small, float inputs)
+{
+    return HALF_LINE * (__builtin_amdgcn_sqrtf(squares) + (small > 0.f ? __builtin_amdgcn_sqrtf(small) * inputs : 0.f));
+}
+
 // Two values, scaled already.
 __device__ __forceinline__ void half_pair(float a, float b, unsigned& h, unsigned& l)
 {

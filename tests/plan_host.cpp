@@ -53,6 +53,15 @@ extern "C" int plan_split(int N, int C, int H, int W, int K, int R, int S, int s
     double cycles = 0;
     return split_plan(g, &cycles);
 }
+// {parts of an operand, images of a block, channel blocks of a wave, its pixel blocks, chunks, waves beside each other in kernels and pixels}
+extern "C" int split_block(int N, int C, int H, int W, int K, int R, int S, int stride, int pad, int* block)
+{
+    SplitGeom g;
+    if (!plan_split(N, C, H, W, K, R, S, stride, pad, &g)) return 0;
+    const int of[7] = {g.parts, g.b, g.mb, g.nb, (int)split_chunks(g), g.wm, g.wn};
+    for (int i = 0; i < 7; ++i) block[i] = of[i];
+    return 1;
+}
 // {workgroups, whether they prepare their own kernels, whether ids are divided by multiplication, whether all divisions are exact}
 extern "C" int split_facts(int N, int C, int H, int W, int K, int R, int S, int stride, int pad, int* facts)
 {

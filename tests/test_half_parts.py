@@ -1,10 +1,13 @@
 """Operands in two fp16 parts (split_mfma.h): what their scales, taken from samples, do not fit is computed again in fp32, image by
 image and kernel by kernel, and every output keeps the error bound of a sum in fp32."""
+import ctypes
+
 import numpy as np
 import pytest
 
 from oracle.conv_oracle import conv_ref
 from paper_2012_15667_amd.inputs import make_inputs
+from tests import plan_host
 from tests.test_split_kernels import _bound, gpu  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -184,3 +187,124 @@ def test_small_pointwise_layers_with_channels_innermost(gpu, layer):  # noqa: F8
     yo = out[1:-1].view(N, P, Q, K)
     B.conv_direct_layout(xo, wd, stride, 0, B.LAYOUT_HWC, y=yo)
     assert np.array_equal(yo.cpu().numpy().transpose(0, 3, 1, 2), y) and float(out[0]) == 7 and float(out[-1]) == 7
+
+
+# ---- operands of one sum that differ in size ------------------------------------------------------
+# What a kernel's parts and a pixel's cannot hold beside a larger operand may be all of an output, where that operand meets a small or a
+# zero partner.  The groups do not follow those that the kernels judge together: single channels, parts of eight, the last ones.
+def _identity(x, w):
+    w[:] = 0
+    for k in range(w.shape[0]):
+        w[k, k % w.shape[1], w.shape[2] // 2, w.shape[3] // 2] = 1
+    x *= np.float32(2.0) ** -(np.arange(x.shape[1]) % 64)[None, :, None, None].astype(np.float32)
+
+
+def _balanced(r):
+    def change(x, w):
+        x[:, 3] *= np.float32(r)
+        w[:, 3] /= np.float32(r)
+    return change
+
+
+def _pruned(s):
+    def change(x, w):
+        w[:, 0] = 0
+        x[:, 1:] *= np.float32(s)
+    return change
+
+
+def _some_small_kernels(n):
+    def change(x, w):
+        m = min(n, w.shape[1] - 1)
+        w[2::3, :m] *= np.float32(1e-8)
+        x[:, m:] = 0
+    return change
+
+
+def _last_channels(x, w):
+    n = w.shape[1] % 16 or 3
+    w[::2, -n:] *= np.float32(1e-9)
+    x[:, :-n] = 0
+
+
+def _halves(x, w):
+    w[:, ::2] *= np.float32(1e-8)
+    x[:, 1::2] *= np.float32(1e-8)
+
+
+def _one_image_of_it(x, w):
+    """In one image of the batch only, the others as they are: they do not speak for it."""
+    w[:, 0] = 0
+    x[1, 1:] *= np.float32(1e-9)
+
+
+APART = {"identity": _identity, "balanced_1e3": _balanced(1e3), "balanced_1e5": _balanced(1e5), "balanced_1e7": _balanced(1e7), "balanced_1e9": _balanced(1e9),
+         "pruned_1e-8": _pruned(1e-8), "pruned_1e-12": _pruned(1e-12), "small_1": _some_small_kernels(1), "small_4": _some_small_kernels(4),
+         "small_7": _some_small_kernels(7), "small_100": _some_small_kernels(100), "last": _last_channels, "halves": _halves, "one_image": _one_image_of_it}
+
+
+def _conv64(torch, xd, wd, stride, pad):
+    """The layer in 64 bits, [N][K][P Q]."""
+    (N, C, H, W), (K, _, R, S) = xd.shape, wd.shape
+    P, Q = (H + 2 * pad - R) // stride + 1, (W + 2 * pad - S) // stride + 1
+    xp = torch.nn.functional.pad(xd.double(), (pad,) * 4)
+    y = torch.zeros(N, K, P * Q, dtype=torch.float64, device="cuda")
+    for r in range(R):
+        for s in range(S):
+            win = xp[:, :, r:r + stride * (P - 1) + 1:stride, s:s + stride * (Q - 1) + 1:stride].reshape(N, C, P * Q).contiguous()
+            y += torch.bmm(wd[:, :, r, s].double().unsqueeze(0).expand(N, K, C).contiguous(), win)
+    return y.view(N, K, P, Q)
+
+
+def _each_kernel_by_itself(torch, y, xd, wd, stride, pad):
+    """Error per image and kernel against the size of its sums (the root of the sum of squared products, which no cancellation makes
+    small).  Sums of n products in fp32, four products before each rounding of a running sum of about that size, are off by some
+    sqrt(n / 4) 2^-24 of it: three times that, for images of one or six outputs, and what goes unmarked, 2^-21; one output four
+    times both.  A cut that is not taken again was 1e-4 and more."""
+    ref, size = _conv64(torch, xd, wd, stride, pad), _conv64(torch, xd.double() ** 2, wd.double() ** 2, stride, pad).sqrt()
+    err, lim = (y.double() - ref).abs(), 1.5 * wd[0].numel() ** 0.5 * 2.0 ** -24 + 2.0 ** -21
+    rms = lambda a: (a * a).mean((2, 3)).sqrt()  # noqa: E731
+    tiny = 2.0 ** -149
+    assert bool((rms(err) <= lim * rms(size) + tiny).all()), float((rms(err) / (lim * rms(size) + tiny)).max())
+    assert bool((err.amax((2, 3)) <= 4 * lim * size.amax((2, 3)) + tiny).all()), float((err.amax((2, 3)) / (lim * size.amax((2, 3)) + tiny)).max())
+
+
+# N, C, H, W, K, R, stride, pad of layers that run in two parts (asserted): one image and several in a block, stride 2, 5 x 5, channels
+# and kernels that fill no block, one pixel, every kind of workgroup they get
+TWO_PARTS = [(12, 72, 30, 31, 64, 3, 1, 1), (8, 129, 28, 28, 130, 3, 2, 1), (2, 96, 27, 27, 256, 5, 1, 2), (64, 128, 4, 4, 512, 3, 1, 1),
+             (200, 130, 3, 2, 257, 3, 1, 1), (2, 604, 9, 9, 600, 3, 1, 1), (20, 64, 1, 1, 32, 3, 1, 1), (20, 64, 56, 56, 64, 3, 1, 1)]
+
+
+def _two_parts(N, C, H, W, K, R, stride, pad):
+    block = (ctypes.c_int * 7)()
+    return plan_host.lib().split_block(N, C, H, W, K, R, R, stride, pad, block) == 1 and block[0] == 2
+
+
+def _in_every_layout(torch, B, xd, wd, stride, pad):
+    """The layer in [N][K][P][Q], from every layout and from channels innermost off 16 bytes."""
+    yield B.conv_direct(xd, wd, stride, pad)
+    xh = xd.permute(0, 2, 3, 1).contiguous()
+    yield B.conv_direct_layout(xh, wd, stride, pad, B.LAYOUT_HWC).permute(0, 3, 1, 2)
+    off = torch.zeros(xh.numel() + 1, device="cuda")[1:].view(xh.shape)
+    off.copy_(xh)
+    yield B.conv_direct_layout(off, wd, stride, pad, B.LAYOUT_HWC).permute(0, 3, 1, 2)
+    yield B.conv_direct_layout(xd.permute(0, 1, 3, 2).contiguous(), wd, stride, pad, B.LAYOUT_CWH).permute(0, 1, 3, 2)
+
+
+@pytest.mark.parametrize("layer", TWO_PARTS)
+@pytest.mark.parametrize("change", list(APART))
+def test_direct_kernels_whose_operands_differ_in_size(gpu, layer, change):  # noqa: F811
+    torch, B = gpu
+    N, C, H, W, K, R, stride, pad = layer
+    assert _two_parts(*layer) and _two_parts(N, C, W, H, K, R, stride, pad)
+    x, w = (a.copy() for a in make_inputs(N, C, H, W, K, R, R, "u11", "he", seed=C + K))
+    APART[change](x, w)
+    xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+    for y in _in_every_layout(torch, B, xd, wd, stride, pad):
+        _each_kernel_by_itself(torch, y, xd, wd, stride, pad)
+    # what another image holds does not change an image's bits
+    y = B.conv_direct(xd, wd, stride, pad)
+    other = xd.clone()
+    other[N - 1] *= 1e-20
+    other[N - 1, 1:] = 0
+    assert torch.equal(B.conv_direct(other, wd, stride, pad)[:N - 1], y[:N - 1])
