@@ -69,9 +69,10 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
 {
     // All of it is read here.  The compiler would otherwise read field by field where they are used, one wait after the other (33 scalar loads
     // before the first matrix step, and not 17: 64 -> 64 at 56 x 56, batch 32, 33.9 us and 33.5).
-    SplitGeom g = given;
+    SplitGeom read;
 #pragma unroll
-    for (unsigned i = 0; i < (TWO ? sizeof(g) / 4 : 0); ++i) reinterpret_cast<int*>(&g)[i] = __builtin_amdgcn_readfirstlane(reinterpret_cast<const int*>(&given)[i]);
+    for (unsigned i = 0; i < (TWO ? sizeof(read) / 4 : 0); ++i) reinterpret_cast<int*>(&read)[i] = __builtin_amdgcn_readfirstlane(reinterpret_cast<const int*>(&given)[i]);
+    const SplitGeom& g = TWO ? read : given;
     extern __shared__ u32x4 lds16[];
     char* const lds = reinterpret_cast<char*>(lds16);
     constexpr int T = 64 * WM * WN;
@@ -514,25 +515,8 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
     float back = 1.f;
     f32x4 kb4[MB];
     bool fine;
-    // The largest of the sums of a kernel, acc[mb][.][i], that are judged together: a lane's, and those of its three neighbours where it has
-    // fewer than four; of several images in a block the neighbours' of the same image, at the same nb.
-    // (maximum: NaN where one of them is)
-    auto together = [&](float v, int im) {
-        auto take = [&](auto bit_c) {
-            const float o = __uint_as_float(quad_other<decltype(bit_c)::value>(__float_as_uint(v)));
-            v = (int)quad_other<decltype(bit_c)::value>((unsigned)im) == im ? __builtin_elementwise_maximum(v, o) : v;
-        };
-        take(std::integral_constant<int, 0>{});
-        take(std::integral_constant<int, 1>{});
-        return v;
-    };
-    auto largest_sum = [&](int mb, int i) {
-        float m = 0.f;
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) m = __builtin_elementwise_maximum(m, __builtin_fabsf(acc[mb][nb][i]));
-        return NB < 4 ? together(m, 0) : m;
-    };
-    constexpr float MOST = 3.402823466e38f;                 // a sum beyond it is not finite
+    int image[NB], first_image = 0, last_image = 0, judging = JUDGE_LANE;
+    bool ragged = false;                                    // some pixels of the block are no outputs
     auto image_of = [&](int nb) {
         const int slot = (wn_i * NB + nb) * 16 + (opaque(lane) & 15);
         return dv.txy.of(slot < npix ? slot : npix - 1);
@@ -548,40 +532,50 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
         }
         const float inputs = __uint_as_float(wave_max(brightest));
         // Whether all sums are finite and no kernel's too small, by the largest of kernels and inputs: mostly so, and then they are only written.
-        const float line = half_line(own.facts * HALF_PIECE, (float)(C * RS), inputs);
-        float least = MOST, greatest = 0.f;
-        // (not those of a lane all of whose pixels lie beyond the image or the batch)
-        bool outputs = true;
-        if ((y0 + g.ty > g.P) | (x0 + g.tx > g.Q) | (n0 + g.b > g.N)) {
-            outputs = false;
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                const int slot = (wn_i * NB + nb) * 16 + l16, im = dv.txy.of(slot), rem = slot - im * txy, row = dv.tx.of(rem);
-                outputs |= (slot < npix) & (n0 + im < g.N) & (y0 + row < g.P) & (x0 + rem - row * g.tx < g.Q);
-            }
-        }
-        auto see = [&](float m, int mb, int i) {
-            greatest = __builtin_elementwise_maximum(greatest, m);
-            least = __builtin_fminf(least, outputs && (kb16 + mb) * 16 + 4 * grp + i < g.K ? m : MOST);
-        };
+        const float line = half_line(__builtin_amdgcn_sqrtf(own.facts * HALF_PIECE), __builtin_amdgcn_sqrtf((float)(C * RS)), inputs);
+        float least = FINITE, greatest = 0.f;
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) kb4[mb] = *reinterpret_cast<const f32x4*>(kback + (wm_i * MB + mb) * 16 + 4 * grp);
-        if (g.b > 1) {
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                const int im = image_of(nb);
-#pragma unroll
-                for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) see(together(__builtin_fabsf(acc[mb][nb][i]), im), mb, i);
-            }
-        } else {
+        ragged = (y0 + g.ty > g.P) | (x0 + g.tx > g.Q) | (n0 + g.b > g.N);
+        // (The way of most workgroups lies by itself: instructions come from memory here.  Slots beyond the pixels of a whole block of one image
+        // hold the last of them again.)
+        if (__builtin_expect((g.b == 1) & !ragged, 1)) {
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) see(largest_sum(mb, i), mb, i);
+                for (int i = 0; i < 4; ++i) {
+                    float m = 0.f;
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) m = __builtin_elementwise_maximum(m, __builtin_fabsf(acc[mb][nb][i]));
+                    if constexpr (NB < 4) m = quad_largest(m, 0);
+                    greatest = __builtin_elementwise_maximum(greatest, m);
+                    least = __builtin_fminf(least, (kb16 + mb) * 16 + 4 * grp + i < g.K ? m : FINITE);
+                }
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) image[nb] = 0;
+        } else {
+            first_image = dv.txy.of(wn_i * NB * 16 < npix ? wn_i * NB * 16 : npix - 1);
+            last_image = dv.txy.of((wn_i + 1) * NB * 16 < npix ? (wn_i + 1) * NB * 16 - 1 : npix - 1);
+            judging = g.b == 1 ? JUDGE_LANE : last_image - first_image < MOST_IMAGES ? JUDGE_IMAGES : JUDGE_QUADS;
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                const int slot = (wn_i * NB + nb) * 16 + l16, im = dv.txy.of(slot), rem = slot - im * txy, row = dv.tx.of(rem);
+                image[nb] = (slot < npix) & (n0 + im < g.N) & (y0 + row < g.P) & (x0 + rem - row * g.tx < g.Q) ? im : -1;
+            }
+            bool any = false;
+            judge_sums<MB, NB>(judging, ragged, image, first_image, last_image, [&](int mb, int nb, int i) { return __builtin_fabsf(acc[mb][nb][i]); },
+                               [&](auto in) {
+                                   any = false;
+#pragma unroll
+                                   for (int nb = 0; nb < NB; ++nb) any |= in(nb);
+                                   if (judging == JUDGE_LANE) any = __builtin_amdgcn_ballot_w64(any) != 0;
+                               },
+                               [&](int mb, int i, float m) {
+                                   greatest = __builtin_elementwise_maximum(greatest, m);
+                                   least = __builtin_fminf(least, any & ((kb16 + mb) * 16 + 4 * grp + i < g.K) ? m : FINITE);
+                               });
         }
-        small |= !(least >= line) | !(greatest <= MOST);
+        small |= !(least >= line) | !(greatest <= FINITE);
         fine = __builtin_amdgcn_ballot_w64(small) == 0;
     } else {
         float m = 0.f;
@@ -591,57 +585,56 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) m = __builtin_elementwise_maximum(m, __builtin_fabsf(acc[mb][nb][i]));
-        fine = __builtin_amdgcn_ballot_w64(!(m <= MOST)) == 0;
+        fine = __builtin_amdgcn_ballot_w64(!(m <= FINITE)) == 0;
     }
     // Otherwise each output for itself: sums that are not finite; those whose window has no value that is large enough, and not only
-    // zeros; those of kernels whose sums are too small for it.
+    // zeros; those of kernels whose finite sums are all too small for it.
     if (__builtin_expect(!fine, 0)) {
-        float m1[MB][4];
-        KernelFacts facts[MB][4];
-        if constexpr (TWO)
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb) {
-                const KernelFacts* from = reinterpret_cast<const KernelFacts*>(reinterpret_cast<const float*>(wt + (size_t)total * wstep) + 16 * g.Kb16) +
-                                          (kb16 + mb) * 16 + 4 * (opaque(lane) >> 4);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    m1[mb][i] = largest_sum(mb, i);
-                    facts[mb][i] = {0.f, 0.f};
-                }
-                for (int p = 0; p < own.facts; ++p, from += 16 * g.Kb16)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        facts[mb][i].squares += from[i].squares;
-                        facts[mb][i].small += from[i].small;
-                    }
-            }
+        unsigned window[NB];
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
             const int slot = (wn_i * NB + nb) * 16 + (opaque(lane) & 15);
             const int im = dv.txy.of(slot), rem = slot - im * txy, row = dv.tx.of(rem), col = rem - row * g.tx;
             const bool exists = slot < npix && n0 + im < g.N && y0 + row < g.P && x0 + col < g.Q;
-            unsigned window = 0;
+            window[nb] = 0;
             if constexpr (TWO)
                 if (exists)
                     for (int r = 0; r < g.R; ++r)
                         for (int s = 0; s < g.S; ++s) {
                             const unsigned m = most[(im * g.yh + row * g.esy + r) * g.rowp + col * g.esx + s];
-                            window = m > window ? m : window;
+                            window[nb] = m > window[nb] ? m : window[nb];
                         }
-            const bool lost = TWO && window - 1 < __float_as_uint(HALF_LEAST) - 1;
+            const bool lost = TWO && window[nb] - 1 < __float_as_uint(HALF_LEAST) - 1;
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float own_sum = __builtin_fabsf(acc[mb][nb][i]);
-                    bool bad = lost || !(own_sum <= MOST);
-                    if constexpr (TWO) {
-                        // (a NaN among them: not this output's, whose own sum is finite)
-                        const float m = g.b > 1 ? together(own_sum, image_of(nb)) : m1[mb][i];
-                        bad |= window != 0 && (m < half_line(facts[mb][i].squares, facts[mb][i].small, __uint_as_float(window)) || !(facts[mb][i].squares <= MOST));
-                    }
-                    if (bad && exists && (kb16 + mb) * 16 + 4 * (opaque(lane) >> 4) + i < g.K) again |= 1ull << ((nb * MB + mb) * 4 + i);
-                }
+                for (int i = 0; i < 4; ++i)
+                    if (exists && (lost || !(__builtin_fabsf(acc[mb][nb][i]) <= FINITE)) && (kb16 + mb) * 16 + 4 * (opaque(lane) >> 4) + i < g.K)
+                        again |= 1ull << ((nb * MB + mb) * 4 + i);
+        }
+        if constexpr (TWO) {
+            KernelLine own_line[MB];                        // of kernels l16
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+                own_line[mb] = kernel_line(reinterpret_cast<const KernelFacts*>(reinterpret_cast<const float*>(wt + (size_t)total * wstep) + 16 * g.Kb16) + (kb16 + mb) * 16,
+                                           own.facts, 16 * g.Kb16, opaque(lane));
+            unsigned group = 0;                             // bits of the nb that are judged together
+            judge_sums<MB, NB>(judging, ragged, image, first_image, last_image,
+                               [&](int mb, int nb, int i) { return __builtin_fabsf(acc[mb][nb][i]) <= FINITE ? __builtin_fabsf(acc[mb][nb][i]) : 0.f; },
+                               [&](auto in) {
+                                   group = 0;
+#pragma unroll
+                                   for (int nb = 0; nb < NB; ++nb) group |= in(nb) && window[nb] != 0 ? 1u << nb : 0u;
+                               },
+                               [&](int mb, int i, float m) {
+                                   const int k = 4 * (opaque(lane) >> 4) + i;
+                                   const float norm = __shfl(own_line[mb].norm, k), root = __shfl(own_line[mb].root, k);
+                                   const bool there = (kb16 + mb) * 16 + k < g.K;
+#pragma unroll
+                                   for (int nb = 0; nb < NB; ++nb)
+                                       if (there && (group >> nb & 1) && !(m >= half_line(norm, root, __uint_as_float(window[nb]))))
+                                           again |= 1ull << ((nb * MB + mb) * 4 + i);
+                               });
         }
     }
     // all of them; the second time those that were marked

@@ -14,6 +14,8 @@
 
 #include <type_traits>
 
+#include "wino_transform.h"
+
 namespace iolb {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -207,11 +209,115 @@ __device__ __forceinline__ unsigned quad_other(unsigned v)
 // Sums of uniform, normal, sparse and lognormal inputs by normal, Laplace, sparse and lognormal kernels are 2^4 to 2^12 above the line, whatever n.
 struct KernelFacts { float squares; float small; };          // sum of the scaled elements' squares; how many are small and not zero
 constexpr float HALF_LINE = 0.0625f;
-// A piece of a kernel, up to 128 elements, has at most these squares; where one has more (a few elements far above the sample), its parts are NaN.
-constexpr float HALF_PIECE = 0x1p27f;
-__device__ __forceinline__ float half_line(float squares, float small, float inputs)
+// A piece of a kernel has at most these squares per element that it has room for; where one has more (elements far above the sample), its parts are NaN.
+constexpr float HALF_SQUARES = 0x1p20f;
+constexpr float HALF_PIECE = 128 * HALF_SQUARES;             // direct and 1 x 1 layers
+constexpr float HALF_PIECE_PLANE = 32 * HALF_SQUARES;        // 32 channels of a transformed kernel's plane
+// norm: of the kernel's scaled elements; root: that of how many are small; inputs: the largest
+__device__ __forceinline__ float half_line(float norm, float root, float inputs) { return HALF_LINE * (norm + (root > 0.f ? root * inputs : 0.f)); }
+
+// The largest of four neighbouring lanes' values, where their images agree (NaN where one of them is).
+__device__ __forceinline__ float quad_largest(float v, int image)
 {
-    return HALF_LINE * (__builtin_amdgcn_sqrtf(squares) + (small > 0.f ? __builtin_amdgcn_sqrtf(small) * inputs : 0.f));
+    auto take = [&](auto bit_c) {
+        constexpr int BIT = decltype(bit_c)::value;
+        const float o = __uint_as_float(quad_other<BIT>(__float_as_uint(v)));
+        v = (int)quad_other<BIT>((unsigned)image) == image ? __builtin_elementwise_maximum(v, o) : v;
+    };
+    take(std::integral_constant<int, 0>{});
+    take(std::integral_constant<int, 1>{});
+    return v;
+}
+// The largest of the 16 lanes of a row.
+__device__ __forceinline__ float row_largest(float v)
+{
+    auto take = [&](int o) { v = __builtin_elementwise_maximum(v, __int_as_float(o)); };
+    take(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x121, 0xf, 0xf, false));             // row_ror:1, 2, 4, 8
+    take(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x122, 0xf, 0xf, false));
+    take(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x124, 0xf, 0xf, false));
+    take(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, false));
+    return v;
+}
+// The sums of a kernel that are judged together, in a wave whose lanes l16 hold NB pixels each (one alone is below its line by chance once in some
+// 10^3, and looking closer costs 2 us): of one image a lane's (where NB is less than four its three neighbours' too; where some pixels are no
+// outputs, ragged, all of them); of up to MOST_IMAGES all of each; of more those of four neighbouring pixels that are of one image.
+// image[nb]: -1 where there is no output.
+enum { JUDGE_LANE, JUDGE_IMAGES, JUDGE_QUADS };
+constexpr int MOST_IMAGES = 4;
+constexpr float FINITE = 3.402823466e38f;                    // beyond it a value is not finite
+// begin(in): a group of this lane, in(nb) whether a pixel of its is in it; see(mb, i, largest): of kernel 4 grp + i of block mb the largest sum of
+// the group.  value(mb, nb, i): a sum's magnitude.  Every lane takes part.
+template <int MB, int NB, class Value, class Begin, class See>
+__device__ __forceinline__ void judge_sums(int mode, bool ragged, const int (&image)[NB], int first, int last, Value value, Begin begin, See see)
+{
+    if (mode == JUDGE_LANE) {
+        begin([&](int nb) { return image[nb] >= 0; });
+        float m[MB][4];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                m[mb][i] = 0.f;
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) m[mb][i] = __builtin_elementwise_maximum(m[mb][i], value(mb, nb, i));
+                if constexpr (NB < 4) m[mb][i] = quad_largest(m[mb][i], 0);
+            }
+        if (ragged)
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) m[mb][i] = row_largest(m[mb][i]);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) see(mb, i, m[mb][i]);
+    } else if (mode == JUDGE_IMAGES) {
+#pragma unroll 1
+        for (int im = first; im <= last; ++im) {
+            begin([&](int nb) { return image[nb] == im; });
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float m = 0.f;
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) m = __builtin_elementwise_maximum(m, image[nb] == im ? value(mb, nb, i) : 0.f);
+                    see(mb, i, row_largest(m));
+                }
+        }
+    } else {
+        static_for<NB>([&](auto at_c) {
+            constexpr int at = decltype(at_c)::value;
+            begin([&](int nb) { return nb == at && image[nb] >= 0; });
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) see(mb, i, quad_largest(value(mb, at, i), image[at]));
+        });
+    }
+}
+// What a kernel's pieces tell of it, for kernel lane % 16 of a block of 16: the 2-norm of its scaled elements, the root of how many are small
+// (not finite where the first is not).  from: those of the block's first kernel, `pitch` kernels from piece to piece.
+struct KernelLine { float norm, root; };
+__device__ __forceinline__ KernelLine kernel_line(const KernelFacts* from, int pieces, size_t pitch, int lane)
+{
+    KernelFacts sum = {0.f, 0.f};
+    for (int p0 = lane >> 4; p0 < pieces; p0 += 16) {
+        KernelFacts f[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) f[j] = from[(p0 + 4 * j < pieces ? p0 + 4 * j : 0) * pitch + (lane & 15)];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            sum.squares += p0 + 4 * j < pieces ? f[j].squares : 0.f;
+            sum.small += p0 + 4 * j < pieces ? f[j].small : 0.f;
+        }
+    }
+#pragma unroll
+    for (int d = 16; d < 64; d *= 2) {
+        sum.squares += __shfl_xor(sum.squares, d);
+        sum.small += __shfl_xor(sum.small, d);
+    }
+    return {__builtin_amdgcn_sqrtf(sum.squares), __builtin_amdgcn_sqrtf(sum.small)};
 }
 
 // Two values, scaled already.

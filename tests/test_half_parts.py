@@ -232,6 +232,13 @@ def _halves(x, w):
     x[:, 1::2] *= np.float32(1e-8)
 
 
+def _beside_outliers(x, w):
+    """Beside pixels whose sums are not finite, or computed again for a reason of their own."""
+    _halves(x, w)
+    x[:, 0, ::4, ::3] *= np.float32(1e6)
+    x[0, 2, -1, -1] = np.float32(3e30)
+
+
 def _one_image_of_it(x, w):
     """In one image of the batch only, the others as they are: they do not speak for it."""
     w[:, 0] = 0
@@ -240,7 +247,7 @@ def _one_image_of_it(x, w):
 
 APART = {"identity": _identity, "balanced_1e3": _balanced(1e3), "balanced_1e5": _balanced(1e5), "balanced_1e7": _balanced(1e7), "balanced_1e9": _balanced(1e9),
          "pruned_1e-8": _pruned(1e-8), "pruned_1e-12": _pruned(1e-12), "small_1": _some_small_kernels(1), "small_4": _some_small_kernels(4),
-         "small_7": _some_small_kernels(7), "small_100": _some_small_kernels(100), "last": _last_channels, "halves": _halves, "one_image": _one_image_of_it}
+         "small_7": _some_small_kernels(7), "small_100": _some_small_kernels(100), "last": _last_channels, "halves": _halves, "beside_outliers": _beside_outliers, "one_image": _one_image_of_it}
 
 
 def _conv64(torch, xd, wd, stride, pad):
@@ -256,15 +263,17 @@ def _conv64(torch, xd, wd, stride, pad):
     return y.view(N, K, P, Q)
 
 
-def _each_kernel_by_itself(torch, y, xd, wd, stride, pad):
+def _each_kernel_by_itself(torch, y, xd, wd, stride, pad, each_output=False):
     """Error per image and kernel against the size of its sums (the root of the sum of squared products, which no cancellation makes
-    small).  Sums of n products in fp32, four products before each rounding of a running sum of about that size, are off by some
-    sqrt(n / 4) 2^-24 of it: three times that, for images of one or six outputs, and what goes unmarked, 2^-21; one output four
+    small).  Sums of n products in fp32, a rounding of up to 2^-24 of a running sum of 0.7 of that size in the mean each, are off by some
+    0.7 sqrt(n) 2^-24 of it: three times that, for images of one or six outputs, and what goes unmarked, 2^-21; one output four
     times both.  A cut that is not taken again was 1e-4 and more."""
     ref, size = _conv64(torch, xd, wd, stride, pad), _conv64(torch, xd.double() ** 2, wd.double() ** 2, stride, pad).sqrt()
-    err, lim = (y.double() - ref).abs(), 1.5 * wd[0].numel() ** 0.5 * 2.0 ** -24 + 2.0 ** -21
+    err, lim = (y.double() - ref).abs(), 2.1 * wd[0].numel() ** 0.5 * 2.0 ** -24 + 2.0 ** -21
     rms = lambda a: (a * a).mean((2, 3)).sqrt()  # noqa: E731
     tiny = 2.0 ** -149
+    if each_output:
+        assert bool((err <= 8 * lim * size + tiny).all()), float((err / (lim * size + tiny)).max())
     assert bool((rms(err) <= lim * rms(size) + tiny).all()), float((rms(err) / (lim * rms(size) + tiny)).max())
     assert bool((err.amax((2, 3)) <= 4 * lim * size.amax((2, 3)) + tiny).all()), float((err.amax((2, 3)) / (lim * size.amax((2, 3)) + tiny)).max())
 
@@ -301,7 +310,7 @@ def test_direct_kernels_whose_operands_differ_in_size(gpu, layer, change):  # no
     APART[change](x, w)
     xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
     for y in _in_every_layout(torch, B, xd, wd, stride, pad):
-        _each_kernel_by_itself(torch, y, xd, wd, stride, pad)
+        _each_kernel_by_itself(torch, y, xd, wd, stride, pad, change == "beside_outliers")
     # what another image holds does not change an image's bits
     y = B.conv_direct(xd, wd, stride, pad)
     other = xd.clone()
