@@ -241,7 +241,7 @@ SplitChoice split_choice(const iolb_shape& s, int P, int Q, int pad_w, int layou
     if (s.R == 1 && s.S == 1 && s.pad == 0 && pad_w == 0) {
         iolb::SplitPointGeom g{};
         g.groups = 1; g.images = s.N; g.C = s.C; g.K = g.Ky = s.K; g.HW = g.HWy = P * Q; g.HWin = s.H * s.W; g.Win = s.W; g.Q = Q;
-        g.stride = s.stride; g.hwc = hwc;
+        g.stride = s.stride; g.hwc = hwc; g.per = P * Q; g.pieces = iolb::split_facts(s.C, 1, 4);
         g.in = hwc ? (s.C % 4 ? iolb::SPLIT_IN_SINGLE : iolb::SPLIT_IN_CHANNELS) : s.stride == 1 ? iolb::SPLIT_IN_PIXELS : iolb::SPLIT_IN_SINGLE;
         g.vec_out = hwc && s.K % 4 == 0;
         if (iolb::split_point_faster(s, P, Q, hwc) && iolb::split_point_plan(&g, &cycles)) {
@@ -541,7 +541,7 @@ SplitWino split_wino(const iolb_shape& s, const iolb_tile_config& tile)
     if (runs && n2 * std::max(s.C, s.K) * pitch < (1LL << 31) && s.C <= 32768 && s.K <= 65535) {
         iolb::SplitPointGeom& g = r.g;
         g.groups = (int)n2; g.images = 1; g.C = s.C; g.K = g.Ky = s.K; g.HW = (int)tiles; g.HWy = g.HWin = (int)pitch; g.Win = g.Q = (int)tiles;
-        g.stride = 1; g.in = iolb::SPLIT_IN_PIXELS;
+        g.stride = 1; g.in = iolb::SPLIT_IN_PIXELS; g.per = (int)tiles; g.pieces = (s.C + 31) / 32;
         g.w_image = 1;                                        // kernels per plane; the real distance follows from the plan
         double cycles = 0;
         if (iolb::split_point_plan(&g, &cycles)) {

@@ -201,6 +201,7 @@ struct SplitPointGeom {
     long long w_image;         // 16-byte pieces from one group's kernels to the next
     int hwc, in, vec_out;      // in: how the inputs are read, below
     int raw, m;                // the kernels as the caller holds them, below; tile edge where they are transformed
+    int per, pieces;           // pixels of an image that have one scale; pieces that a kernel's facts come in
 };
 // Inputs read in single floats; four channels at a time (channels innermost, C a multiple of 4, 16-byte aligned); two
 // neighbouring pixels at a time (channels outermost, stride 1; blocks may run on into the next image only where HW is
@@ -212,7 +213,8 @@ constexpr int split_point_pixels(int in) { return in == SPLIT_IN_PIXELS ? 2 : 1;
 #define IOLB_SPLIT_POINT_SHAPES(X) X(1, 2, 4, 1) X(1, 4, 4, 1) X(2, 4, 4, 1) X(3, 4, 4, 1) X(4, 4, 4, 1)
 // Room for a group's kernels in two parts, which they and what undoes their scales do not fill.
 inline long long split_point_weight_bytes(const SplitPointGeom& g) { return (g.C + 31LL) / 32 * g.Kb16 * 3072; }
-// wt: the kernels in two parts, per group [chunk][16-kernel block][part][lane] and behind them what undoes the scales of 16 Kb16 kernels;
+// wt: the kernels in two parts, per group [chunk][16-kernel block][part][lane] and behind them what undoes the scales of 16 Kb16 kernels
+// and their facts, [piece][kernel];
 // w: as the caller holds them (g.raw), for blocks that are taken again.
 hipError_t launch_split_point(const float* x, const void* wt, const float* w, float* y, const SplitPointGeom& g, hipStream_t st);
 

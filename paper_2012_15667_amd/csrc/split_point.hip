@@ -5,7 +5,7 @@
 // A step is 32 channels.  The inputs of chunk t + 1 are split and written to one LDS buffer while chunk t is multiplied
 // from the other; their loads are issued three chunks ahead and kept in registers, two neighbouring pixels per load where
 // the layout has them.  Every pixel has a scale of its own: its image's largest value in the block, from the first 32 channels and a few more, but at
-// most 512 times the largest of the pixel's own sample.  The split's arithmetic is
+// most 512 times the largest of the pixel's own sample.  Sums are judged, and some computed again, as in direct_split.hip.  The split's arithmetic is
 // placed between the matrix instructions, three vector
 // instructions after each, where it costs little (a 16-bit matrix instruction leaves the vector pipeline free; measured:
 // eight vector instructions per 32-cycle matrix instruction 1433 against 1631 TFLOP/s).  wt is not declared restrict on
@@ -33,7 +33,7 @@ namespace {
 
 template <int MB, int NB, int WM, int WN, int IN, bool VPX>
 __global__ void __launch_bounds__(64 * WM * WN, 2)
-split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitPointGeom g, const float* __restrict__ w)
+split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitPointGeom g, const float* __restrict__ w, Divisor by_per)
 {
     constexpr int T = 64 * WM * WN, NPIX = 16 * NB * WN, PLANE = 4 * NPIX * 16, BUF = 2 * PLANE;
     // an input item: CH channels of PX neighbouring pixels
@@ -41,12 +41,13 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
     constexpr int ITEMS = 32 / CH * NPIX / PX, IB = (ITEMS + T - 1) / T;
     extern __shared__ u32x4 lds16[];
     // two buffers, each the h of all pixels and then the l; room that nobody reads; per pixel the largest value in the sample that sets
-    // its scale, and of all its channels, scaled, and that of its image; what undoes the kernels' scales
+    // its scale, and of all its channels, scaled, and that of its image; its scale; what undoes the kernels' scales
     char* const lds = reinterpret_cast<char*>(lds16);
     unsigned* const sample = reinterpret_cast<unsigned*>(lds + 2 * BUF + PLANE + 16);
     unsigned* const most = sample + NPIX;
     unsigned* const images = most + NPIX;
-    float* const kback = reinterpret_cast<float*>(images + NPIX);
+    unsigned* const scales = images + NPIX;
+    float* const kback = reinterpret_cast<float*>(scales + NPIX);
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, grp = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm_i = wave % WM, wn_i = wave / WM;
@@ -62,14 +63,21 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
     const int n0 = group * g.images + __builtin_amdgcn_readfirstlane(pix0 / g.HW);
     const int p0 = __builtin_amdgcn_readfirstlane(pix0 % g.HW);           // ... in image n0
     const long long left_px = (long long)g.images * g.HW - pix0;          // pixels of the group from there on
+    // images that have a scale of their own: which of them, in the block, a pixel is of (of a transformed plane g.HW is all of the batch)
+    const int i0 = __builtin_amdgcn_readfirstlane(pix0 % g.per);
+    const bool two_images = g.per >= NPIX, one_image = i0 + NPIX <= g.per;
+    auto image_in = [&](int px) {
+        const int one = i0 + px >= g.per, any = by_per.of(i0 + px);
+        return two_images ? one : any;
+    };
 
-    const size_t image = (size_t)g.C * g.HWin;
+    const size_t image_floats = (size_t)g.C * g.HWin;
     const int span = __builtin_amdgcn_readfirstlane((p0 + NPIX - 1) / g.HW + 1);              // images the block touches
     const int have = (group + 1) * g.images - n0;
-    const unsigned long long xbase = reinterpret_cast<unsigned long long>(x + (size_t)n0 * image);
+    const unsigned long long xbase = reinterpret_cast<unsigned long long>(x + (size_t)n0 * image_floats);
     // (the builtin returns a signed int: the halves have to be unsigned before they are put together)
     const unsigned xlo = __builtin_amdgcn_readfirstlane((unsigned)xbase), xhi = __builtin_amdgcn_readfirstlane((unsigned)(xbase >> 32));
-    const unsigned range = __builtin_amdgcn_readfirstlane((unsigned)(4 * image * (span < have ? span : have)));
+    const unsigned range = __builtin_amdgcn_readfirstlane((unsigned)(4 * image_floats * (span < have ? span : have)));
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
         reinterpret_cast<void*>((unsigned long long)xhi << 32 | xlo), 0, (int)range, 0x00020000);
 
@@ -217,14 +225,14 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
     barrier();
     static_assert(NPIX <= 64, "a lane per pixel");
     unsigned all = 0;
-    if (span == 1) {
+    if (one_image) {
         all = wave_max(lane < NPIX ? sample[lane] : 0u);
     } else {
-        if (tid < NPIX && tid < left_px) atomicMax(images + (p0 + tid) / g.HW, sample[tid]);
+        if (tid < NPIX && tid < left_px) atomicMax(images + image_in(tid), sample[tid]);
         barrier();
     }
     auto scale_of = [&](int px) {
-        const unsigned m = sample[px], image = span == 1 ? all : images[(p0 + px) / g.HW];
+        const unsigned m = sample[px], image = one_image ? all : images[image_in(px)];
         // (bits of floats: 3 << 23 less is an eighth, 9 << 23 more is 512 times)
         const unsigned eighth = image < 4u << 23 ? 0u : image - (3u << 23), most_m = m + (9u << 23);
         return half_scale_bits(m == 0 ? eighth : image < m ? m : image < most_m ? image : most_m);
@@ -233,7 +241,9 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
     for (int i = 0; i < IB; ++i)
 #pragma unroll
         for (int p = 0; p < PX; ++p) {
-            scale[i][p] = __uint_as_float(scale_of(item_px(i) + p));
+            const unsigned bits = scale_of(item_px(i) + p);
+            scale[i][p] = __uint_as_float(bits);
+            if (exists(i)) scales[item_px(i) + p] = bits;       // (the same from every channel's items)
             top[i][p] = 0.f;
         }
     __builtin_amdgcn_sched_barrier(0);
@@ -285,8 +295,8 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
     }
 
     // each partial sum is complete: write the block once.  Register i of a 16 x 16 block holds channel 4 grp + i of
-    // pixel l16.  Where all sums are finite, and no pixel is too small for its scale, they are only written; otherwise those that
-    // are not, and such a pixel's, are marked, and written a second time.
+    // pixel l16.  Where all sums are finite, no pixel is too small for its scale and no kernel's sums are too small, they are only
+    // written; otherwise outputs for which that is not so are marked, and written a second time.
 #pragma unroll
     for (int i = 0; i < IB; ++i)
 #pragma unroll
@@ -295,28 +305,171 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
     barrier();
     unsigned long long again = 0;
     static_assert(MB * NB * 4 <= 64, "one mark per output");
-    float back[NB];
+    float back[NB], inputs[NB];
     f32x4 kb4[MB];
-    bool lost[NB], any_lost = false;
-    f32x4 zero = {0.f, 0.f, 0.f, 0.f};                      // 0 times a sum that is not finite is NaN
+    bool bad = false;
+    // a line for all kernels, by the largest that they can have
+    const float most_norm = __builtin_amdgcn_sqrtf(g.pieces * (g.raw == SPLIT_RAW_ROWS ? HALF_PIECE : HALF_PIECE_PLANE)), most_root = __builtin_amdgcn_sqrtf((float)g.C);
+    const int last_image = image_in((int)(left_px < NPIX ? left_px : NPIX) - 1);
+    const bool whole = left_px >= NPIX, lane_of_one = one_image || (VPX && g.per % NB == 0);
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
         const int px = pixel_of(nb, l16);
-        back[nb] = half_unscale(scale_of(px));
-        lost[nb] = px < left_px && most[px] - 1 < __float_as_uint(HALF_LEAST) - 1;
-        any_lost |= lost[nb];
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) zero[i] = __builtin_fmaf(px < left_px ? acc[mb][nb][i] : 0.f, 0.f, zero[i]);
+        back[nb] = half_unscale(scales[px]);
+        inputs[nb] = px < left_px ? __uint_as_float(most[px]) : 0.f;
+        bad |= __float_as_uint(inputs[nb]) - 1 < __float_as_uint(HALF_LEAST) - 1;
     }
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) kb4[mb] = *reinterpret_cast<const f32x4*>(kback + (wm_i * MB + mb) * 16 + 4 * grp);
-    const bool finite = __builtin_amdgcn_ballot_w64(any_lost || zero[0] + zero[1] + zero[2] + zero[3] != 0.f) == 0;
-    enum { PLAIN, MARKING, MARKED_ONLY };
-    auto write_y = [&](auto mode_c) {
-        constexpr int MODE = decltype(mode_c)::value;
-        constexpr bool MARKED = MODE == MARKED_ONLY;
+    // Nearly always the lanes hold pixels of one image and one scale each, and all is well.  (This way lies by itself: instructions come from
+    // memory here.  The last blocks of an image, whose last lanes have few pixels, judge those of 16 lanes.)
+    const bool of_one = last_image == 0;
+    bool fine = false;
+    if (__builtin_expect(of_one | (whole & lane_of_one), 1)) {
+        bool other = bad;
+        float input = 0.f, most_sum[MB][4];
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) input = __builtin_fmaxf(input, inputs[nb]);
+        if (whole) {
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) other |= back[nb] != back[0];
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float m = 0.f;
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) m = __builtin_elementwise_maximum(m, __builtin_fabsf(acc[mb][nb][i]));
+                    most_sum[mb][i] = m;
+                }
+        } else {
+            input = row_largest(input);
+            const float first = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(back[0])));
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) other |= (back[nb] != first) & (pixel_of(nb, l16) < left_px);
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float m = 0.f;
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) m = __builtin_elementwise_maximum(m, pixel_of(nb, l16) < left_px ? __builtin_fabsf(acc[mb][nb][i]) : 0.f);
+                    most_sum[mb][i] = row_largest(m);
+                }
+        }
+        const float line = half_line(most_norm, most_root, input);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                other |= (!(most_sum[mb][i] >= line) & ((kb16 + mb) * 16 + 4 * grp + i < g.K)) | !(most_sum[mb][i] <= FINITE);
+        fine = __builtin_amdgcn_ballot_w64(other) == 0;
+    }
+    if (__builtin_expect(!fine, 0)) {
+    int image[NB];
+    float size[NB];
+    const bool ragged = of_one && !whole;
+    const int judging = lane_of_one || of_one ? JUDGE_LANE : last_image < MOST_IMAGES ? JUDGE_IMAGES : JUDGE_QUADS;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        const bool there = pixel_of(nb, l16) < left_px;
+        image[nb] = there ? image_in(pixel_of(nb, l16)) : -1;
+        size[nb] = there ? back[nb] : 0.f;
+    }
+    // Pixels that are judged together have scales of their own: size, a pixel's against that of the brightest of them (0: no output).  The
+    // largest input of them, by that scale, makes the line; where all are zero there is none.
+    auto of_group = [&](const float (&v)[NB], float (&to)[NB]) {
+        float all = 0.f;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) all = __builtin_fmaxf(all, v[nb]);
+        if (NB < 4) all = quad_largest(all, 0);
+        if (ragged) all = row_largest(all);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) to[nb] = 0.f;
+        if (__builtin_expect(judging == JUDGE_LANE, 1)) {
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) to[nb] = all;
+        } else if (judging == JUDGE_QUADS) {
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) to[nb] = quad_largest(v[nb], image[nb]);
+        } else {
+            for (int im = 0; im <= last_image; ++im) {
+                float m = 0.f;
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) m = image[nb] == im ? __builtin_fmaxf(m, v[nb]) : m;
+                m = row_largest(m);
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) to[nb] = image[nb] == im ? m : to[nb];
+            }
+        }
+    };
+    bool lost[NB], zero[NB];
+    {
+        float brightest[NB];
+        of_group(size, brightest);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            lost[nb] = __float_as_uint(inputs[nb]) - 1 < __float_as_uint(HALF_LEAST) - 1;
+            zero[nb] = inputs[nb] == 0.f;
+            size[nb] = size[nb] > 0.f ? size[nb] * half_unscale(__float_as_uint(brightest[nb])) : 0.f;      // (powers of two)
+            inputs[nb] *= size[nb];
+        }
+        float largest[NB];
+        of_group(inputs, largest);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) inputs[nb] = largest[nb];
+    }
+    // whether all is well by that line
+    {
+        float line[NB];
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) line[nb] = inputs[nb] > 0.f ? half_line(most_norm, most_root, inputs[nb]) : 0.f;
+        float least = 0.f;
+        judge_sums<MB, NB>(judging, ragged, image, 0, last_image, [&](int mb, int nb, int i) { return __builtin_fabsf(acc[mb][nb][i]) * size[nb]; },
+                           [&](auto in) {
+                               least = 0.f;
+#pragma unroll
+                               for (int nb = 0; nb < NB; ++nb) least = in(nb) ? line[nb] : least;
+                           },
+                           [&](int mb, int i, float m) { bad |= (!(m >= least) & ((kb16 + mb) * 16 + 4 * grp + i < g.K)) | !(m <= FINITE); });
+    }
+    fine = __builtin_amdgcn_ballot_w64(bad) == 0;
+    // otherwise each output for itself, by its kernel's own line; zero inputs have lost nothing
+    if (__builtin_expect(!fine, 0)) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (image[nb] >= 0 && (lost[nb] || !(__builtin_fabsf(acc[mb][nb][i]) <= FINITE)) && (kb16 + mb) * 16 + 4 * (opaque(lane) >> 4) + i < g.K)
+                        again |= 1ull << ((nb * MB + mb) * 4 + i);
+        KernelLine own_line[MB];                            // of kernels l16
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+            own_line[mb] = kernel_line(reinterpret_cast<const KernelFacts*>(reinterpret_cast<const float*>(group_w + (size_t)nchunks * wstep) + 16 * g.Kb16) + (kb16 + mb) * 16,
+                                       g.pieces, 16 * g.Kb16, opaque(lane));
+        unsigned group = 0;                                 // bits of the nb that are judged together
+        judge_sums<MB, NB>(judging, ragged, image, 0, last_image,
+                           [&](int mb, int nb, int i) { return __builtin_fabsf(acc[mb][nb][i]) <= FINITE ? __builtin_fabsf(acc[mb][nb][i]) * size[nb] : 0.f; },
+                           [&](auto in) {
+                               group = 0;
+#pragma unroll
+                               for (int nb = 0; nb < NB; ++nb) group |= in(nb) && !zero[nb] ? 1u << nb : 0u;
+                           },
+                           [&](int mb, int i, float m) {
+                               const int k = 4 * (opaque(lane) >> 4) + i;
+                               const float norm = __shfl(own_line[mb].norm, k), root = __shfl(own_line[mb].root, k);
+                               const bool there = (kb16 + mb) * 16 + k < g.K;
+#pragma unroll
+                               for (int nb = 0; nb < NB; ++nb)
+                                   if (there && (group >> nb & 1) && !(m >= half_line(norm, root, inputs[nb]))) again |= 1ull << ((nb * MB + mb) * 4 + i);
+                           });
+    }
+    }
+    // all of them; the second time those that were marked
+    auto write_y = [&](auto marked_c) {
+        constexpr bool MARKED = decltype(marked_c)::value;
         const int l16 = opaque(lane) & 15, grp = opaque(lane) >> 4;
         if constexpr (VPX && !MARKED) {
             typedef float vec __attribute__((ext_vector_type(NB), aligned(4)));
@@ -333,12 +486,7 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
                 for (int i = 0; i < 4; ++i) {
                     vec q;
 #pragma unroll
-                    for (int nb = 0; nb < NB; ++nb) {
-                        // (beyond the pixels that exist the inputs are what follows them: not a reason to do anything again)
-                        if (MODE == MARKING && px + nb < left_px && (lost[nb] || !(__builtin_fabsf(acc[mb][nb][i]) <= 3.402823466e38f)))
-                            again |= 1ull << ((nb * MB + mb) * 4 + i);
-                        q[nb] = acc[mb][nb][i] * back[nb] * kb4[mb][i];
-                    }
+                    for (int nb = 0; nb < NB; ++nb) q[nb] = acc[mb][nb][i] * back[nb] * kb4[mb][i];
                     if (k0 + i >= g.K) continue;
                     if (whole) {
                         *reinterpret_cast<vec*>(yp + (size_t)i * g.HWy) = q;
@@ -359,13 +507,7 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) {
                 const int k0 = (kb16 + mb) * 16 + 4 * grp, bit = (nb * MB + mb) * 4;
-                if constexpr (!MARKED) {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        if (MODE == MARKING && (lost[nb] || !(__builtin_fabsf(acc[mb][nb][i]) <= 3.402823466e38f))) again |= 1ull << (bit + i);
-                        acc[mb][nb][i] = acc[mb][nb][i] * back[nb] * kb4[mb][i];
-                    }
-                }
+                if constexpr (!MARKED) acc[mb][nb] = acc[mb][nb] * back[nb] * kb4[mb];
                 if (g.hwc) {
                     float* yp = y + ((size_t)n * g.HW + r) * g.K + k0;
                     if (!MARKED && g.vec_out && k0 + 3 < g.K) {
@@ -384,12 +526,39 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
             }
         }
     };
-    if (finite) {
-        write_y(std::integral_constant<int, PLAIN>{});
-        return;
+    write_y(std::false_type{});
+    if (__builtin_expect(fine || __builtin_amdgcn_ballot_w64(again != 0) == 0, 1)) return;
+
+    // Few marked outputs of an image are sums of their own, a lane one channel in 64 (image by image: what others hold decides nothing).
+    const RawKernels raw(w, g.raw, g.m, group, g.C, g.K);
+    {
+        constexpr int FEW = 16;
+        unsigned long long many = 0;
+        while (const unsigned long long lanes = __builtin_amdgcn_ballot_w64(again != 0)) {
+            const int src = __builtin_ctzll(lanes);
+            const int nb0 = __builtin_amdgcn_readlane((int)(__builtin_ctzll(again | 1ull << 63) / (4 * MB)), src);
+            const int im = image_in(pixel_of(nb0, src & 15));
+            unsigned long long own = 0;
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) own |= image_in(pixel_of(nb, opaque(lane) & 15)) == im ? again & (((1ull << (4 * MB - 1) << 1) - 1) << (nb * MB * 4)) : 0;
+            again &= ~own;
+            if (wave_sum((float)__popcll(own)) > FEW) { many |= own; continue; }
+            while (const unsigned long long left = __builtin_amdgcn_ballot_w64(own != 0)) {
+                const int at = __builtin_ctzll(left);
+                const int bit = __builtin_amdgcn_readlane(__builtin_ctzll(own | 1ull << 63), at);
+                if (lane == at) own &= own - 1;
+                const int k = (kb16 + bit / 4 % MB) * 16 + 4 * (at >> 4) + (bit & 3), q = p0 + pixel_of(bit / (4 * MB), at & 15), r = q % g.HW;
+                const size_t n = n0 + q / g.HW, in = g.stride == 1 ? r : r / g.Q * g.stride * g.Win + r % g.Q * g.stride;
+                const float* xp = x + n * image_floats + (g.hwc ? in * g.C : in);
+                float sum = 0.f;
+                for (int c = lane; c < g.C; c += 64) sum = __builtin_fmaf(xp[(size_t)c * (cstep / 4)], raw.at(k, c), sum);
+                sum = wave_sum(sum);
+                if (lane == at) y[g.hwc ? (n * g.HW + r) * g.K + k : (n * g.Ky + k) * g.HWy + r] = sum;
+            }
+        }
+        again = many;
+        if (__builtin_amdgcn_ballot_w64(again != 0) == 0) return;
     }
-    write_y(std::integral_constant<int, MARKING>{});
-    if (__builtin_amdgcn_ballot_w64(again != 0) == 0) return;
 
     // A wave with a marked output takes its whole block again on the fp32 matrix instructions, which hold their sums in
     // the same registers; the inputs come from memory.
@@ -403,7 +572,6 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    const RawKernels raw(w, g.raw, g.m, group, g.C, g.K);
 #pragma unroll 1
     for (int ch = 0; ch < nchunks; ++ch) {
         float wv[MB][8];
@@ -426,16 +594,16 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
                 for (int mb = 0; mb < MB; ++mb) acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[mb][j], v[j], acc[mb][nb], 0, 0, 0);
         });
     }
-    write_y(std::integral_constant<int, MARKED_ONLY>{});
+    write_y(std::true_type{});
 }
 
 template <int MB, int NB, int WM, int WN, int IN, bool VPX>
 hipError_t launch_one(const float* x, const u32x4* wt, const float* w, float* y, const SplitPointGeom& g, hipStream_t st)
 {
     auto kern = split_point_kernel<MB, NB, WM, WN, IN, VPX>;
-    constexpr size_t NPIX = 16 * NB * WN, shm = 5 * 4 * NPIX * 16 + 16 + 12 * NPIX + 64 * MB * WM;
+    constexpr size_t NPIX = 16 * NB * WN, shm = 5 * 4 * NPIX * 16 + 16 + 16 * NPIX + 64 * MB * WM;
     static_assert(shm <= 64 * 1024, "dynamic LDS without an opt-in");
-    hipLaunchKernelGGL(kern, dim3(g.nbk * g.nbp * g.groups), dim3(64 * WM * WN), shm, st, x, wt, y, g, w);
+    hipLaunchKernelGGL(kern, dim3(g.nbk * g.nbp * g.groups), dim3(64 * WM * WN), shm, st, x, wt, y, g, w, Divisor(g.per));
     return hipGetLastError();
 }
 
@@ -447,7 +615,7 @@ hipError_t launch_split_point(const float* x, const void* wt, const float* w_giv
     const long long npix = 16LL * g.nb * g.wn, span = (g.HW - 1 + npix - 1) / g.HW + 1;
     if (g.Kb16 != g.nbk * g.mb * g.wm || (long long)g.nbp * npix < (long long)g.images * g.HW || (long long)g.images * g.HW >= (1LL << 31) - 1024 ||
         4 * (span < g.images ? span : g.images) * g.C * g.HWin >= (1LL << 31) || g.Kb16 * 16 < g.K ||
-        (long long)g.nbk * g.nbp * g.groups > 0x7fffffffLL)
+        (long long)g.nbk * g.nbp * g.groups > 0x7fffffffLL || g.per < 1 || g.pieces < 1)
         return hipErrorInvalidValue;
     if (g.in == SPLIT_IN_CHANNELS && (!g.hwc || g.C % 4)) return hipErrorInvalidValue;
     if (g.in == SPLIT_IN_PIXELS && (g.hwc || g.stride != 1 || (g.images > 1 && g.HW % split_point_pixels(g.in)))) return hipErrorInvalidValue;

@@ -49,20 +49,31 @@ __device__ __forceinline__ void store_parts(u32x4* to, const unsigned short (&p)
 }
 
 // The piece of eight transformed kernel elements in two fp16 parts, scaled already, of kernel lane % KERNELS and the channels of lane / KERNELS; the
-// lanes that share a kernel, lane % KERNELS, judge it together (of `channels` < 16 some are all small now and then: not judged).  NaN in
-// place of a kernel too small for its scale.
+// lanes that share a kernel, lane % KERNELS, judge it together (of `channels` < 16 some are all small now and then: left to the sums).  NaN in
+// place of a kernel that does not fit its scale.  Returns what the lanes that share a kernel have of it.
 template <int KERNELS>
-__device__ __forceinline__ void store_halves(u32x4* to, const float (&u)[8], int channels)
+__device__ __forceinline__ KernelFacts store_halves(u32x4* to, const float (&u)[8], int channels, float most_squares)
 {
     u32x4 h, l;
     float most = half_eight(u, 1.f, h, l);
+    KernelFacts facts = {0.f, 0.f};
 #pragma unroll
-    for (int d = KERNELS; d < 64; d *= 2) most = __builtin_fmaxf(most, __shfl_xor(most, d));
-    const unsigned poison = channels >= 16 && most != 0.f && most < HALF_LEAST ? 0x7e007e00u : 0u;
+    for (int j = 0; j < 8; ++j) {
+        facts.squares = __builtin_fmaf(u[j], u[j], facts.squares);
+        facts.small += u[j] != 0.f && __builtin_fabsf(u[j]) < HALF_LEAST ? 1.f : 0.f;
+    }
+#pragma unroll
+    for (int d = KERNELS; d < 64; d *= 2) {
+        most = __builtin_fmaxf(most, __shfl_xor(most, d));
+        facts.squares += __shfl_xor(facts.squares, d);
+        facts.small += __shfl_xor(facts.small, d);
+    }
+    const unsigned poison = (channels >= 16 && most != 0.f && most < HALF_LEAST) || !(facts.squares <= most_squares) ? 0x7e007e00u : 0u;
 #pragma unroll
     for (int i = 0; i < 4; ++i) h[i] |= poison;
     to[0] = h;
     to[64] = l;
+    return facts;
 }
 // The channel of spot 0 ... 15 at which kernels are sampled for their scale: two elements of each, g[0][0] and g[2][2], which are also
 // elements of the transformed kernel, times a power of two.
@@ -141,6 +152,8 @@ struct RawKernels {
     {
         return m == 2 ? Mats<2>::L[row][j] : m == 3 ? Mats<3>::L[row][j] : m == 4 ? Mats<4>::L[row][j] : Mats<6>::L[row][j];
     }
+    // (as `accumulate` adds: to the bits of a transformed kernel in memory)
+    static __device__ __forceinline__ float add(float coef, float v, float to) { return coef == 0.f ? to : __builtin_fmaf(coef, v, to); }
     __device__ __forceinline__ float at(int k, int c) const
     {
         if (k >= K || c >= C) return 0.f;
@@ -149,7 +162,7 @@ struct RawKernels {
         const float* t = w + ((size_t)k * C + c) * 9;
         float u = 0.f;
 #pragma unroll
-        for (int j = 0; j < 3; ++j) u += lj[j] * (li[0] * t[j] + (li[1] * t[3 + j] + li[2] * t[6 + j]));
+        for (int j = 0; j < 3; ++j) u = add(lj[j], add(li[2], t[6 + j], add(li[1], t[3 + j], add(li[0], t[j], 0.f))), u);
         return u;
     }
 };

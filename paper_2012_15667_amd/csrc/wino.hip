@@ -62,6 +62,11 @@ kernel_transform(const float* __restrict__ w, float* __restrict__ U, int C, int 
 // wave per row of the planes in turn.  Bound by its stores once the rows of w come through LDS: 512 x 512 kernels in F(2 x 2)
 // (in three parts 25 MB) 30 -> 8 us; gathered by their lanes they cost a cache line per lane and load, in every row of the planes again.
 constexpr int SPLIT_ROW = 32 * 9, SPLIT_ROW_PITCH = SPLIT_ROW + 1;
+// The facts of a plane's kernels, [chunk][16 Kb16], behind what undoes their scales.
+__device__ __forceinline__ KernelFacts* plane_facts(u32x4* plane, int chunks, int Kb16)
+{
+    return reinterpret_cast<KernelFacts*>(reinterpret_cast<float*>(plane + (size_t)128 * chunks * Kb16) + 16 * Kb16);
+}
 template <int M>
 __device__ __forceinline__ void kernel_transform_split_block(const float* __restrict__ w, u32x4* __restrict__ wt, int C, int K, int chunks, int Kb16,
                                                              int block, float* rows, unsigned* scales)
@@ -101,7 +106,9 @@ __device__ __forceinline__ void kernel_transform_split_block(const float* __rest
             const float up = scale * this_up * power_of_two(kernel_up<M>(J));
 #pragma unroll
             for (int c = 0; c < 8; ++c) u[c] = kernel_element<M, J>(lg[c]) * up;
-            store_halves<16>(wt + (size_t)(row * n + J) * chunks * Kb16 * 192 + ((size_t)ch * Kb16 + kb) * 128 + lane, u, C - ch * 32);
+            u32x4* const to = wt + (size_t)(row * n + J) * chunks * Kb16 * 192;
+            const KernelFacts f = store_halves<16>(to + ((size_t)ch * Kb16 + kb) * 128 + lane, u, C - ch * 32, HALF_PIECE_PLANE);
+            if (lane < 16) plane_facts(to, chunks, Kb16)[((size_t)ch * Kb16 + kb) * 16 + lane] = f;
         });
     }
 }
@@ -131,7 +138,8 @@ __device__ __forceinline__ void split_planes_block(const float* __restrict__ U, 
     if (ch == 0 && lane < 16) reinterpret_cast<float*>(to + (size_t)128 * chunks * Kb16)[k] = half_unscale(scale) * (row_down<M>(plane / n) * row_down<M>(plane % n));
 #pragma unroll
     for (int j = 0; j < 8; ++j) u[j] *= __uint_as_float(scale) * up;
-    store_halves<16>(to + ((size_t)ch * Kb16 + kb) * 128 + lane, u, C - ch * 32);
+    const KernelFacts f = store_halves<16>(to + ((size_t)ch * Kb16 + kb) * 128 + lane, u, C - ch * 32, HALF_PIECE_PLANE);
+    if (lane < 16) plane_facts(to, chunks, Kb16)[((size_t)ch * Kb16 + kb) * 16 + lane] = f;
 }
 
 // step 1a: one lane per (c, t); t runs fastest.  VEC (m = 2 or 4, W a multiple of m, x aligned to

@@ -626,7 +626,7 @@ wino_split_weights(const float* __restrict__ w, u32x4* __restrict__ wt, int C, i
             float u[8];
 #pragma unroll
             for (int c = 0; c < 8; ++c) u[c] = kernel_element<M, J>(lg[c]) * up;
-            store_halves<32>(wt + (((size_t)(row * n + J) * chunks + ch) * Kb32 + kb) * 128 + lane, u, C - ch * 16);
+            store_halves<32>(wt + (((size_t)(row * n + J) * chunks + ch) * Kb32 + kb) * 128 + lane, u, C - ch * 16, 3e38f);
         });
     }
 }
@@ -663,7 +663,7 @@ wino_split_given(const float* __restrict__ U, u32x4* __restrict__ wt, int C, int
         u[c] = U[exists ? ((size_t)plane * rows + c0 + c) * cols + k : 0];
         u[c] = exists ? u[c] * up : 0.f;
     }
-    store_halves<32>(wt + (((size_t)plane * chunks + ch) * Kb32 + kb) * 128 + lane, u, C - ch * 16);
+    store_halves<32>(wt + (((size_t)plane * chunks + ch) * Kb32 + kb) * 128 + lane, u, C - ch * 16, 3e38f);
 }
 
 template <int M, int TB, int Z, int COLS, int PARTS>

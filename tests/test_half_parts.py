@@ -317,3 +317,57 @@ def test_direct_kernels_whose_operands_differ_in_size(gpu, layer, change):  # no
     other[N - 1] *= 1e-20
     other[N - 1, 1:] = 0
     assert torch.equal(B.conv_direct(other, wd, stride, pad)[:N - 1], y[:N - 1])
+
+
+@pytest.mark.parametrize("layout,layer", [(o, n) for n in [(12, 768, 17, 17, 192, 1), (70, 515, 7, 5, 500, 1), (4, 300, 61, 61, 450, 2)] for o in ("chw", "hwc")] +
+                         [("hwc", (90, 256, 1, 1, 400, 1)), ("hwc", (11, 81, 3, 5, 70, 1))])
+@pytest.mark.parametrize("change", list(APART))
+def test_pointwise_kernels_whose_operands_differ_in_size(gpu, layer, layout, change):  # noqa: F811
+    torch, B = gpu
+    N, C, H, W, K, stride = layer
+    lay = B.LAYOUT_HWC if layout == "hwc" else B.LAYOUT_CHW
+    assert B.iolb_route(B.make_shape(N, C, H, W, K, 1, 1, stride, 0), lay)[0] == B.ROUTE_SPLIT
+    x, w = (a.copy() for a in make_inputs(N, C, H, W, K, 1, 1, "u11", "he", seed=C + K))
+    APART[change](x, w)
+    wd = torch.from_numpy(w).cuda()
+
+    def run(a):
+        if layout == "chw":
+            return B.conv_direct(a, wd, stride, 0)
+        return B.conv_direct_layout(a.permute(0, 2, 3, 1).contiguous(), wd, stride, 0, lay).permute(0, 3, 1, 2)
+
+    xd = torch.from_numpy(x).cuda()
+    y = run(xd)
+    _each_kernel_by_itself(torch, y, xd, wd, stride, 0, change == "beside_outliers")
+    other = xd.clone()
+    other[N - 1] *= 1e-20
+    other[N - 1, 1:] = 0
+    assert torch.equal(run(other)[:N - 1], y[:N - 1])
+
+
+# root mean square per image and kernel, of the kernel's outputs in that image (of 4 x 4 outputs and more): a fifth of the guards of single outputs
+# (GUARD_WINO); a cut that is not taken again was 1e-3 and more
+WINO_EACH = {2: 1e-5, 3: 6e-5, 4: 1e-4, 6: 1.2e-4}
+
+
+def _winograd_each(torch, B, run, xd, wd, m, pad):
+    from tests.test_split_kernels import _winograd_ref
+    ref = _winograd_ref(torch, xd, wd, pad)
+    rms = lambda a: (a * a).mean((2, 3)).sqrt()  # noqa: E731
+    y = run(xd)
+    err = rms(y.double() - ref)
+    assert bool((err <= WINO_EACH[m] * rms(ref) + 2.0 ** -149).all()), float((err / (rms(ref) + 2.0 ** -149)).max())
+
+
+@pytest.mark.parametrize("m,N,C,H,W,K", [(2, 64, 512, 7, 7, 512), (3, 33, 525, 7, 8, 485), (4, 9, 277, 35, 37, 233), (6, 5, 284, 29, 30, 497),
+                                          (4, 128, 512, 5, 5, 512), (6, 100, 512, 4, 4, 512), (2, 96, 516, 13, 13, 516)])
+@pytest.mark.parametrize("change", [c for c in APART if c != "one_image"])
+def test_winograd_product_kernels_whose_operands_differ_in_size(gpu, m, N, C, H, W, K, change):  # noqa: F811
+    torch, B = gpu
+    assert B.iolb_route(B.make_shape(N, C, H, W, K, algo=B.WINO_ALGO[m]))[0] == B.ROUTE_SPLIT
+    x, w = (a.copy() for a in make_inputs(N, C, H, W, K, 3, 3, "u11", "he", seed=m + C))
+    APART[change](x, w)
+    xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+    U = B.winograd_transform_kernels(wd, m)[0]
+    _winograd_each(torch, B, lambda a: B.conv_winograd(a, wd, m), xd, wd, m, 1)
+    _winograd_each(torch, B, lambda a: B.conv_winograd_pre(a, U, K, m), xd, wd, m, 1)
