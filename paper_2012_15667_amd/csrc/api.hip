@@ -541,7 +541,7 @@ SplitWino split_wino(const iolb_shape& s, const iolb_tile_config& tile)
     if (runs && n2 * std::max(s.C, s.K) * pitch < (1LL << 31) && s.C <= 32768 && s.K <= 65535) {
         iolb::SplitPointGeom& g = r.g;
         g.groups = (int)n2; g.images = 1; g.C = s.C; g.K = g.Ky = s.K; g.HW = (int)tiles; g.HWy = g.HWin = (int)pitch; g.Win = g.Q = (int)tiles;
-        g.stride = 1; g.in = iolb::SPLIT_IN_PIXELS; g.per = (int)tiles; g.pieces = (s.C + 31) / 32;
+        g.stride = 1; g.in = iolb::SPLIT_IN_PIXELS; g.per = w.th * w.tw; g.pieces = (s.C + 31) / 32;
         g.w_image = 1;                                        // kernels per plane; the real distance follows from the plan
         double cycles = 0;
         if (iolb::split_point_plan(&g, &cycles)) {
