@@ -529,8 +529,8 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
     barrier();
     if (__builtin_amdgcn_readfirstlane(*any) == 0) return;
 
-    // The block again on the fp32 matrix instructions, from the same inputs; three parts hold all of a kernel, two do
-    // unless they are not finite: then the caller's own is read.
+    // The block again on the fp32 matrix instructions, from the same inputs; three parts hold all of a kernel, of two the caller's own is
+    // read: they may have lost what the block is taken again for.
     clear();
     xs = 1.f;
 #pragma unroll 1
@@ -542,22 +542,10 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
             const char* vplane = lds + plane * (TB * 64);
             float w[8];
             if constexpr (TWO) {
-                u32x4 f[PARTS];
-                load_u(f, unit_at(u, s));
-                const f16x8 h = __builtin_bit_cast(f16x8, f[0]), l = __builtin_bit_cast(f16x8, f[1]);
-                const float back = kback[32 * z + l32] * (row_down<M>(plane / n) * row_down<M>(plane % n));
-                bool whole = true;
+                // (opaque: nothing of it is computed, and kept in scalar registers, through the loop above)
+                const RawKernels kernels(w_raw, raw, M, opaque(plane), opaque(g.C), opaque(g.K));
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    w[j] = ((float)h[j] + (float)l[j]) * back;
-                    whole = whole && __builtin_fabsf(w[j]) <= 3.402823466e38f;
-                }
-                if (!whole) {
-                    // (opaque: nothing of it is computed, and kept in scalar registers, through the loop above)
-                    const RawKernels kernels(w_raw, raw, M, opaque(plane), opaque(g.C), opaque(g.K));
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) w[j] = kernels.at(kb * Z + 32 * z + l32, 16 * s + 8 * half + j);
-                }
+                for (int j = 0; j < 8; ++j) w[j] = kernels.at(kb * Z + 32 * z + l32, 16 * s + 8 * half + j);
             } else {
                 u32x4 f[PARTS];
                 load_u(f, unit_at(u, s));

@@ -375,3 +375,22 @@ def test_winograd_product_kernels_whose_operands_differ_in_size(gpu, m, N, C, H,
     U = B.winograd_transform_kernels(wd, m)[0]
     _winograd_each(torch, B, lambda a: B.conv_winograd(a, wd, m), xd, wd, m, 1)
     _winograd_each(torch, B, lambda a: B.conv_winograd_pre(a, U, K, m), xd, wd, m, 1)
+
+
+@pytest.mark.parametrize("m,N,C,H,W,K", [(4, 16, 100, 64, 64, 64), (2, 8, 130, 56, 56, 128)])
+def test_fused_winograd_blocks_taken_again_read_the_callers_kernels(gpu, m, N, C, H, W, K):  # noqa: F811
+    """A corner too small for its image's scale has its blocks taken again; its sums are of the last channels alone, whose weights the parts
+    have lost beside those of the other channels."""
+    torch, B = gpu
+    from tests.test_split_kernels import _runs_fused, _winograd_ref
+    x, w = (a.copy() for a in make_inputs(N, C, H, W, K, 3, 3, "u11", "he", seed=m))
+    n = C % 16
+    x[:, :, :9, :9] *= np.float32(1e-7)
+    x[:, :-n, :9, :9] = 0
+    w[::2, -n:] *= np.float32(1e-9)
+    xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+    ref = _winograd_ref(torch, xd, wd, 1)[:, :, :4, :4]
+    U = B.winograd_transform_kernels(wd, m)[0]
+    for y in (_runs_fused(B, lambda: B.conv_winograd(xd, wd, m)), _runs_fused(B, lambda: B.conv_winograd_pre(xd, U, K, m))):
+        err = (y[:, :, :4, :4].double() - ref).abs().amax((2, 3))
+        assert bool((err <= 8 * WINO_EACH[m] * ref.abs().amax((2, 3))).all()), float((err / ref.abs().amax((2, 3))).max())
