@@ -124,7 +124,8 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
     const int im_bytes = g.yh * g.rowb, plane = g.b * im_bytes, group_bytes = split_planes(PARTS) * plane, buf_bytes = CH8 * group_bytes;
     // (two parts: l lies `plane` bytes after h)
     float* const kback = reinterpret_cast<float*>(lds + g.nbuf * buf_bytes);     // TWO: what undoes the scales of the block's kernels
-    int* const koff = reinterpret_cast<int*>(kback + (TWO ? 16 * MB * WM : 0));  // [4 * steps]
+    KernelLine* const lines = reinterpret_cast<KernelLine*>(kback + (TWO ? 16 * MB * WM : 0));           // TWO: of the kernels, where asked for
+    int* const koff = reinterpret_cast<int*>(lines + (TWO ? 16 * MB * WM : 0));  // [4 * steps]
     uint2* const table = reinterpret_cast<uint2*>(koff + ((4 * steps + 1) & ~1));      // [items]
     // TWO: the largest value of each staged pixel over the channels, scaled; of each image in the sample (one image: of each wave)
     unsigned* const most = reinterpret_cast<unsigned*>(table + items);
@@ -531,29 +532,16 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
             brightest = most[i] > brightest ? most[i] : brightest;
         }
         const float inputs = __uint_as_float(wave_max(brightest));
-        // Whether all sums are finite and no kernel's too small, by the largest of kernels and inputs: mostly so, and then they are only written.
-        const float line = half_line(__builtin_amdgcn_sqrtf(own.facts * HALF_PIECE), __builtin_amdgcn_sqrtf((float)(C * RS)), inputs);
-        float least = FINITE, greatest = 0.f;
+        // Whether all sums are finite and no kernel's too small, by the largest input: mostly so, and then they are only written.
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) kb4[mb] = *reinterpret_cast<const f32x4*>(kback + (wm_i * MB + mb) * 16 + 4 * grp);
+        // First by a line for all kernels, then by each one's own.  A kernel's sums that are judged together: judge_sums.
+        bool bad;
         ragged = (y0 + g.ty > g.P) | (x0 + g.tx > g.Q) | (n0 + g.b > g.N);
         // (The way of most workgroups lies by itself: instructions come from memory here.  Slots beyond the pixels of a whole block of one image
         // hold the last of them again.)
-        if (__builtin_expect((g.b == 1) & !ragged, 1)) {
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    float m = 0.f;
-#pragma unroll
-                    for (int nb = 0; nb < NB; ++nb) m = __builtin_elementwise_maximum(m, __builtin_fabsf(acc[mb][nb][i]));
-                    if constexpr (NB < 4) m = quad_largest(m, 0);
-                    greatest = __builtin_elementwise_maximum(greatest, m);
-                    least = __builtin_fminf(least, (kb16 + mb) * 16 + 4 * grp + i < g.K ? m : FINITE);
-                }
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) image[nb] = 0;
-        } else {
+        const bool whole = (g.b == 1) & !ragged;
+        if (__builtin_expect(!whole, 0)) {
             first_image = dv.txy.of(wn_i * NB * 16 < npix ? wn_i * NB * 16 : npix - 1);
             last_image = dv.txy.of((wn_i + 1) * NB * 16 < npix ? (wn_i + 1) * NB * 16 - 1 : npix - 1);
             judging = g.b == 1 ? JUDGE_LANE : last_image - first_image < MOST_IMAGES ? JUDGE_IMAGES : JUDGE_QUADS;
@@ -562,21 +550,45 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
                 const int slot = (wn_i * NB + nb) * 16 + l16, im = dv.txy.of(slot), rem = slot - im * txy, row = dv.tx.of(rem);
                 image[nb] = (slot < npix) & (n0 + im < g.N) & (y0 + row < g.P) & (x0 + rem - row * g.tx < g.Q) ? im : -1;
             }
-            bool any = false;
-            judge_sums<MB, NB>(judging, ragged, image, first_image, last_image, [&](int mb, int nb, int i) { return __builtin_fabsf(acc[mb][nb][i]); },
-                               [&](auto in) {
-                                   any = false;
-#pragma unroll
-                                   for (int nb = 0; nb < NB; ++nb) any |= in(nb);
-                                   if (judging == JUDGE_LANE) any = __builtin_amdgcn_ballot_w64(any) != 0;
-                               },
-                               [&](int mb, int i, float m) {
-                                   greatest = __builtin_elementwise_maximum(greatest, m);
-                                   least = __builtin_fminf(least, any & ((kb16 + mb) * 16 + 4 * grp + i < g.K) ? m : FINITE);
-                               });
         }
-        small |= !(least >= line) | !(greatest <= FINITE);
-        fine = __builtin_amdgcn_ballot_w64(small) == 0;
+        const float all_kernels = HALF_LINE * (__builtin_amdgcn_sqrtf(own.facts * HALF_PIECE) + __builtin_amdgcn_sqrtf((float)(C * RS)) * inputs);
+        auto all_well = [&](auto closer_c) {
+            constexpr bool closer = decltype(closer_c)::value;
+            bad = small;
+            auto see = [&](int mb, int i, float m) {
+                const float line = closer ? line_of(lines[(wm_i * MB + mb) * 16 + 4 * grp + i], inputs) : all_kernels;
+                bad |= (!(m >= line) & ((kb16 + mb) * 16 + 4 * grp + i < g.K)) | !(m <= FINITE);
+            };
+            if (__builtin_expect(whole, 1)) {
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        float m = 0.f;
+#pragma unroll
+                        for (int nb = 0; nb < NB; ++nb) m = __builtin_elementwise_maximum(m, __builtin_fabsf(acc[mb][nb][i]));
+                        if constexpr (NB < 4) m = quad_largest(m, 0);
+                        see(mb, i, m);
+                    }
+            } else {
+                bool any = false;
+                judge_sums<MB, NB>(judging, ragged, image, first_image, last_image, [&](int mb, int nb, int i) { return __builtin_fabsf(acc[mb][nb][i]); },
+                                   [&](auto in) {
+                                       any = false;
+#pragma unroll
+                                       for (int nb = 0; nb < NB; ++nb) any |= in(nb);
+                                       if (judging == JUDGE_LANE) any = __builtin_amdgcn_ballot_w64(any) != 0;
+                                   },
+                                   [&](int mb, int i, float m) { see(mb, i, any || !(m <= FINITE) ? m : FINITE); });
+            }
+            return __builtin_amdgcn_ballot_w64(bad) == 0;
+        };
+        fine = all_well(std::false_type{});
+        if (__builtin_expect(!fine, 0)) {
+            wave_lines<MB>(reinterpret_cast<const KernelFacts*>(reinterpret_cast<const float*>(wt + (size_t)total * wstep) + 16 * g.Kb16) + kb16 * 16, own.facts,
+                           16 * g.Kb16, lane, lines + wm_i * (16 * MB));
+            fine = all_well(std::true_type{});
+        }
     } else {
         float m = 0.f;
 #pragma unroll
@@ -590,34 +602,38 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
     // Otherwise each output for itself: sums that are not finite; those whose window has no value that is large enough, and not only
     // zeros; those of kernels whose finite sums are all too small for it.
     if (__builtin_expect(!fine, 0)) {
-        unsigned window[NB];
+        const int l16 = opaque(lane) & 15, grp = opaque(lane) >> 4;
+        unsigned window[NB], exists = 0;
+        int corner[NB];
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
-            const int slot = (wn_i * NB + nb) * 16 + (opaque(lane) & 15);
-            const int im = dv.txy.of(slot), rem = slot - im * txy, row = dv.tx.of(rem), col = rem - row * g.tx;
-            const bool exists = slot < npix && n0 + im < g.N && y0 + row < g.P && x0 + col < g.Q;
+            const int slot = (wn_i * NB + nb) * 16 + l16, im = dv.txy.of(slot), rem = slot - im * txy, row = dv.tx.of(rem), col = rem - row * g.tx;
+            const bool there = (slot < npix) & (n0 + im < g.N) & (y0 + row < g.P) & (x0 + col < g.Q);
+            exists |= there ? 1u << nb : 0u;
+            image[nb] = there ? im : -1;
+            corner[nb] = there ? (im * g.yh + row * g.esy) * g.rowp + col * g.esx : 0;
             window[nb] = 0;
-            if constexpr (TWO)
-                if (exists)
-                    for (int r = 0; r < g.R; ++r)
-                        for (int s = 0; s < g.S; ++s) {
-                            const unsigned m = most[(im * g.yh + row * g.esy + r) * g.rowp + col * g.esx + s];
-                            window[nb] = m > window[nb] ? m : window[nb];
-                        }
+        }
+        if constexpr (TWO)
+            for (int r = 0; r < g.R; ++r)
+                for (int s = 0; s < g.S; ++s)
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) {
+                        const unsigned m = most[corner[nb] + r * g.rowp + s];
+                        window[nb] = m > window[nb] ? m : window[nb];
+                    }
+        const int kernels = g.K - kb16 * 16 - 4 * grp;      // that exist from this lane's first on
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
             const bool lost = TWO && window[nb] - 1 < __float_as_uint(HALF_LEAST) - 1;
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    if (exists && (lost || !(__builtin_fabsf(acc[mb][nb][i]) <= FINITE)) && (kb16 + mb) * 16 + 4 * (opaque(lane) >> 4) + i < g.K)
+                    if ((exists >> nb & 1) & (lost | !(__builtin_fabsf(acc[mb][nb][i]) <= FINITE)) & (mb * 16 + i < kernels))
                         again |= 1ull << ((nb * MB + mb) * 4 + i);
         }
         if constexpr (TWO) {
-            KernelLine own_line[MB];                        // of kernels l16
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
-                own_line[mb] = kernel_line(reinterpret_cast<const KernelFacts*>(reinterpret_cast<const float*>(wt + (size_t)total * wstep) + 16 * g.Kb16) + (kb16 + mb) * 16,
-                                           own.facts, 16 * g.Kb16, opaque(lane));
             unsigned group = 0;                             // bits of the nb that are judged together
             judge_sums<MB, NB>(judging, ragged, image, first_image, last_image,
                                [&](int mb, int nb, int i) { return __builtin_fabsf(acc[mb][nb][i]) <= FINITE ? __builtin_fabsf(acc[mb][nb][i]) : 0.f; },
@@ -627,13 +643,11 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
                                    for (int nb = 0; nb < NB; ++nb) group |= in(nb) && window[nb] != 0 ? 1u << nb : 0u;
                                },
                                [&](int mb, int i, float m) {
-                                   const int k = 4 * (opaque(lane) >> 4) + i;
-                                   const float norm = __shfl(own_line[mb].norm, k), root = __shfl(own_line[mb].root, k);
-                                   const bool there = (kb16 + mb) * 16 + k < g.K;
+                                   if (mb * 16 + i >= kernels) return;
+                                   const KernelLine line = lines[(wm_i * MB + mb) * 16 + 4 * grp + i];
 #pragma unroll
                                    for (int nb = 0; nb < NB; ++nb)
-                                       if (there && (group >> nb & 1) && !(m >= half_line(norm, root, __uint_as_float(window[nb]))))
-                                           again |= 1ull << ((nb * MB + mb) * 4 + i);
+                                       if ((group >> nb & 1) & !(m >= line_of(line, __uint_as_float(window[nb])))) again |= 1ull << ((nb * MB + mb) * 4 + i);
                                });
         }
     }

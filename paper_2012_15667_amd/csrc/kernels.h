@@ -129,10 +129,10 @@ inline int split_batches(const SplitGeom& g)
 __host__ __device__ constexpr int split_pixel_bytes(int parts) { return parts == 2 ? 16 : 48; }
 __host__ __device__ constexpr int split_planes(int parts) { return parts == 2 ? 2 : 1; }
 // buffers of the input tile, offsets of the matrix steps' units, table of the input tile's elements, whole 16 bytes; of two parts
-// also the kernels' scales, the pixels' largest values and the images'
+// also the kernels' scales and lines, the pixels' largest values and the images'
 __host__ __device__ inline int split_two_bytes(const SplitGeom& g)
 {
-    return g.parts == 2 ? 64 * g.mb * g.wm + 4 * g.halo + 4 * (g.b > 4 ? g.b : 4) : 0;
+    return g.parts == 2 ? 64 * g.mb * g.wm + 128 * g.mb * g.wm + 4 * g.halo + 4 * (g.b > 4 ? g.b : 4) : 0;
 }
 __host__ __device__ inline int split_tables_bytes(const SplitGeom& g)
 {

@@ -204,18 +204,93 @@ __device__ __forceinline__ unsigned quad_other(unsigned v)
 // the lost ones may be all of the sum.  So sums are judged when they are there, per kernel.  Scaled, an operand below HALF_LEAST is off by up to
 // 2^-25: those of the inputs by the kernel's elements, those of the kernel (`small` of them) by up to the largest input add an error of
 // 2^-25 (|kernel| + sqrt(small) inputs), |.| the 2-norm, in the root mean square and sqrt(n) times that at worst.  Sums of a kernel of which
-// none is 2^21 times that (a few pixels' of one image: one sum alone may be small by chance) are computed again: unmarked errors
-// of this kind are 2^-21 of the largest of those sums, and no more than sqrt(n) 2^-21, which is less than the n 2^-24 of n sums in fp32 from 64 products on.
-// Sums of uniform, normal, sparse and lognormal inputs by normal, Laplace, sparse and lognormal kernels are 2^4 to 2^12 above the line, whatever n.
+// none is 2^20 times that (a few pixels' of one image: one sum alone may be small by chance) are computed again: unmarked errors
+// of this kind are 2^-21 of the largest of those sums in the root mean square, and no more than sqrt(n) 2^-20, which is less than the n 2^-24 of n
+// sums in fp32 from 256 products on.  Sums of uniform, normal, sparse and lognormal inputs by normal, Laplace, sparse and lognormal kernels
+// are 2^5 to 2^13 above the line, whatever n.
 struct KernelFacts { float squares; float small; };          // sum of the scaled elements' squares; how many are small and not zero
-constexpr float HALF_LINE = 0.0625f;
-// A piece of a kernel has at most these squares per element that it has room for; where one has more (elements far above the sample), its parts are NaN.
-constexpr float HALF_SQUARES = 0x1p20f;
+struct KernelLine { float norm, root; };                     // what the line of a kernel follows from
+constexpr float HALF_LINE = 0.03125f;
+__device__ __forceinline__ KernelLine kernel_line(const KernelFacts& f, float line = HALF_LINE)
+{
+    return {line * __builtin_amdgcn_sqrtf(f.squares), line * __builtin_amdgcn_sqrtf(f.small)};
+}
+// (inputs: the largest)
+__device__ __forceinline__ float line_of(const KernelLine& k, float inputs) { return k.norm + (k.root > 0.f ? k.root * inputs : 0.f); }
+// A piece of a kernel has at most these squares per element that it has room for (where it has more, elements far above the sample, its parts
+// are NaN): so there is a line for all kernels that asks for nothing that is not known, which sums are compared with first.
+constexpr float HALF_SQUARES = 0x1p26f;
 constexpr float HALF_PIECE = 128 * HALF_SQUARES;             // direct and 1 x 1 layers
 constexpr float HALF_PIECE_PLANE = 32 * HALF_SQUARES;        // 32 channels of a transformed kernel's plane
-// norm: of the kernel's scaled elements; root: that of how many are small; inputs: the largest
-__device__ __forceinline__ float half_line(float norm, float root, float inputs) { return HALF_LINE * (norm + (root > 0.f ? root * inputs : 0.f)); }
-
+// The facts of a wave's 16 MB kernels, which come in pieces `pitch` kernels apart, and their lines to LDS; every lane takes part.
+template <int MB>
+__device__ __forceinline__ void wave_lines(const KernelFacts* from, int pieces, size_t pitch, int lane, KernelLine* lines)
+{
+    KernelFacts sum[MB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) sum[mb] = {0.f, 0.f};
+#pragma unroll 4
+    for (int p = lane >> 4; p < pieces; p += 4)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            const KernelFacts f = from[p * pitch + mb * 16 + (lane & 15)];
+            sum[mb].squares += f.squares;
+            sum[mb].small += f.small;
+        }
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+#pragma unroll
+        for (int d = 16; d < 64; d *= 2) {
+            sum[mb].squares += __shfl_xor(sum[mb].squares, d);
+            sum[mb].small += __shfl_xor(sum[mb].small, d);
+        }
+        if (lane < 16) lines[mb * 16 + lane] = kernel_line(sum[mb]);
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
+// The facts of kernel thread % Z, which come in pieces `pitch` kernels apart, are added up by GROUPS = T / Z threads, a share each: the
+// first EARLY of its pieces are loaded early.
+template <int EARLY>
+struct FactsShare {
+    const KernelFacts* from;
+    int piece, pieces, by;
+    size_t pitch;
+    KernelFacts early[EARLY];
+    __device__ __forceinline__ void load(const KernelFacts* at, int first, int groups, int count, size_t step)
+    {
+        from = at; piece = first; by = groups; pieces = count; pitch = step;
+#pragma unroll
+        for (int j = 0; j < EARLY; ++j) early[j] = from[(piece + j * by < pieces ? piece + j * by : 0) * pitch];
+    }
+    __device__ __forceinline__ KernelFacts sum() const
+    {
+        KernelFacts all = {0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < EARLY; ++j) {
+            all.squares += piece + j * by < pieces ? early[j].squares : 0.f;
+            all.small += piece + j * by < pieces ? early[j].small : 0.f;
+        }
+#pragma unroll 4
+        for (int p = piece + EARLY * by; p < pieces; p += by) {
+            const KernelFacts f = from[p * pitch];
+            all.squares += f.squares;
+            all.small += f.small;
+        }
+        return all;
+    }
+};
+// ... and the shares of all of them, in order.
+template <int Z, int GROUPS>
+__device__ __forceinline__ KernelFacts all_shares(const KernelFacts* shares, int kernel)
+{
+    KernelFacts all = shares[kernel];
+#pragma unroll
+    for (int j = 1; j < GROUPS; ++j) {
+        all.squares += shares[j * Z + kernel].squares;
+        all.small += shares[j * Z + kernel].small;
+    }
+    return all;
+}
 // The largest of four neighbouring lanes' values, where their images agree (NaN where one of them is).
 __device__ __forceinline__ float quad_largest(float v, int image)
 {
@@ -240,9 +315,10 @@ __device__ __forceinline__ float row_largest(float v)
 }
 // The sums of a kernel that are judged together, in a wave whose lanes l16 hold NB pixels each (one alone is below its line by chance once in some
 // 10^3, and looking closer costs 2 us): of one image a lane's (where NB is less than four its three neighbours' too; where some pixels are no
-// outputs, ragged, all of them); of up to MOST_IMAGES all of each; of more those of four neighbouring pixels that are of one image.
+// outputs, ragged, all of them); of up to MOST_IMAGES all of each; of more those of four neighbouring pixels that are of one image.  Mixed: a
+// lane's pixels that are of one image, several such groups.
 // image[nb]: -1 where there is no output.
-enum { JUDGE_LANE, JUDGE_IMAGES, JUDGE_QUADS };
+enum { JUDGE_LANE, JUDGE_IMAGES, JUDGE_QUADS, JUDGE_MIXED };
 constexpr int MOST_IMAGES = 4;
 constexpr float FINITE = 3.402823466e38f;                    // beyond it a value is not finite
 // begin(in): a group of this lane, in(nb) whether a pixel of its is in it; see(mb, i, largest): of kernel 4 grp + i of block mb the largest sum of
@@ -285,6 +361,20 @@ __device__ __forceinline__ void judge_sums(int mode, bool ragged, const int (&im
                     see(mb, i, row_largest(m));
                 }
         }
+    } else if (mode == JUDGE_MIXED) {
+        static_for<NB>([&](auto at_c) {
+            constexpr int at = decltype(at_c)::value;
+            begin([&](int nb) { return nb == at && image[nb] >= 0; });
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float m = 0.f;
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) m = __builtin_elementwise_maximum(m, image[nb] == image[at] ? value(mb, nb, i) : 0.f);
+                    see(mb, i, m);
+                }
+        });
     } else {
         static_for<NB>([&](auto at_c) {
             constexpr int at = decltype(at_c)::value;
@@ -296,30 +386,6 @@ __device__ __forceinline__ void judge_sums(int mode, bool ragged, const int (&im
         });
     }
 }
-// What a kernel's pieces tell of it, for kernel lane % 16 of a block of 16: the 2-norm of its scaled elements, the root of how many are small
-// (not finite where the first is not).  from: those of the block's first kernel, `pitch` kernels from piece to piece.
-struct KernelLine { float norm, root; };
-__device__ __forceinline__ KernelLine kernel_line(const KernelFacts* from, int pieces, size_t pitch, int lane)
-{
-    KernelFacts sum = {0.f, 0.f};
-    for (int p0 = lane >> 4; p0 < pieces; p0 += 16) {
-        KernelFacts f[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) f[j] = from[(p0 + 4 * j < pieces ? p0 + 4 * j : 0) * pitch + (lane & 15)];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            sum.squares += p0 + 4 * j < pieces ? f[j].squares : 0.f;
-            sum.small += p0 + 4 * j < pieces ? f[j].small : 0.f;
-        }
-    }
-#pragma unroll
-    for (int d = 16; d < 64; d *= 2) {
-        sum.squares += __shfl_xor(sum.squares, d);
-        sum.small += __shfl_xor(sum.small, d);
-    }
-    return {__builtin_amdgcn_sqrtf(sum.squares), __builtin_amdgcn_sqrtf(sum.small)};
-}
-
 // Two values, scaled already.
 __device__ __forceinline__ void half_pair(float a, float b, unsigned& h, unsigned& l)
 {

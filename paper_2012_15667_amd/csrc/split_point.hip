@@ -41,13 +41,16 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
     constexpr int ITEMS = 32 / CH * NPIX / PX, IB = (ITEMS + T - 1) / T;
     extern __shared__ u32x4 lds16[];
     // two buffers, each the h of all pixels and then the l; room that nobody reads; per pixel the largest value in the sample that sets
-    // its scale, and of all its channels, scaled, and that of its image; its scale; what undoes the kernels' scales
+    // its scale, and of all its channels, scaled, and that of its image; its scale; what undoes the kernels' scales;
+    // shares of their facts, then their lines
     char* const lds = reinterpret_cast<char*>(lds16);
     unsigned* const sample = reinterpret_cast<unsigned*>(lds + 2 * BUF + PLANE + 16);
     unsigned* const most = sample + NPIX;
     unsigned* const images = most + NPIX;
     unsigned* const scales = images + NPIX;
     float* const kback = reinterpret_cast<float*>(scales + NPIX);
+    KernelFacts* const shares = reinterpret_cast<KernelFacts*>(kback + 16 * MB * WM);
+    KernelLine* const lines = reinterpret_cast<KernelLine*>(shares);
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, grp = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm_i = wave % WM, wn_i = wave / WM;
@@ -199,7 +202,14 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
     }
     static_assert(16 * MB * WM <= T && 3 * NPIX <= T, "one kernel, one of the pixels' three values per thread");
     float my_kback = 0.f;
-    if (tid < 16 * MB * WM) my_kback = reinterpret_cast<const float*>(group_w + (size_t)nchunks * wstep)[kb * (16 * MB * WM) + tid];
+    constexpr int Z = 16 * MB * WM;
+    const float* const group_scales = reinterpret_cast<const float*>(group_w + (size_t)nchunks * wstep);
+    if (tid < Z) my_kback = group_scales[kb * Z + tid];
+    // Blocks of several images whose lanes hold pixels of more than one judge single sums, by each kernel's own line (which others ask for
+    // only where one for all kernels does not do).
+    const bool of_one_image = i0 + (left_px < NPIX ? (int)left_px : NPIX) <= g.per, lane_of_one = of_one_image || (VPX && g.per % NB == 0);
+    FactsShare<16> share;
+    if (!lane_of_one) share.load(reinterpret_cast<const KernelFacts*>(group_scales + 16 * g.Kb16) + kb * Z + tid % Z, tid / Z, T / Z, g.pieces, 16 * g.Kb16);
     load_x(xv[1], 1);
     load_a(a0);
     if (tid < 3 * NPIX) sample[tid] = 0;                    // (most and images follow)
@@ -221,9 +231,11 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
             }
             if (exists(i) && m && item_px(i) + p < left_px) atomicMax(sample + item_px(i) + p, m);
         }
-    if (tid < 16 * MB * WM) kback[tid] = my_kback;
+    if (tid < Z) kback[tid] = my_kback;
+    if (!lane_of_one && tid < T / Z * Z) shares[tid] = share.sum();
     barrier();
     static_assert(NPIX <= 64, "a lane per pixel");
+    if (!lane_of_one && tid < Z) lines[tid] = kernel_line(all_shares<Z, T / Z>(shares, tid));
     unsigned all = 0;
     if (one_image) {
         all = wave_max(lane < NPIX ? sample[lane] : 0u);
@@ -308,10 +320,9 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
     float back[NB], inputs[NB];
     f32x4 kb4[MB];
     bool bad = false;
-    // a line for all kernels, by the largest that they can have
-    const float most_norm = __builtin_amdgcn_sqrtf(g.pieces * (g.raw == SPLIT_RAW_ROWS ? HALF_PIECE : HALF_PIECE_PLANE)), most_root = __builtin_amdgcn_sqrtf((float)g.C);
-    const int last_image = image_in((int)(left_px < NPIX ? left_px : NPIX) - 1);
-    const bool whole = left_px >= NPIX, lane_of_one = one_image || (VPX && g.per % NB == 0);
+    const float all_norm = HALF_LINE * __builtin_amdgcn_sqrtf(g.pieces * (g.raw == SPLIT_RAW_ROWS ? HALF_PIECE : HALF_PIECE_PLANE)), all_root = HALF_LINE * __builtin_amdgcn_sqrtf((float)g.C);
+    auto kernel_exists = [&](int mb, int i) { return (kb16 + mb) * 16 + 4 * grp + i < g.K; };
+    const bool whole = left_px >= NPIX;
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
         const int px = pixel_of(nb, l16);
@@ -321,55 +332,104 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
     }
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) kb4[mb] = *reinterpret_cast<const f32x4*>(kback + (wm_i * MB + mb) * 16 + 4 * grp);
-    // Nearly always the lanes hold pixels of one image and one scale each, and all is well.  (This way lies by itself: instructions come from
-    // memory here.  The last blocks of an image, whose last lanes have few pixels, judge those of 16 lanes.)
-    const bool of_one = last_image == 0;
-    bool fine = false;
-    if (__builtin_expect(of_one | (whole & lane_of_one), 1)) {
-        bool other = bad;
-        float input = 0.f, most_sum[MB][4];
+    // Nearly always a lane's pixels are judged together, or where they are of several images each by itself, and all is well.  (This way lies by
+    // itself: instructions come from memory here.  The last block of an image, whose last lanes have few pixels, judges those of 16 lanes.)
+    auto all_well = [&](auto closer_c) {
+        constexpr bool CLOSER = decltype(closer_c)::value;
+        auto line_at = [&](int mb, int i, float input) {
+            return CLOSER ? line_of(lines[(wm_i * MB + mb) * 16 + 4 * grp + i], input) : all_norm + all_root * input;
+        };
+        if (__builtin_expect(VPX | of_one_image, 1)) {
+            bool other = bad, apart = false;                // apart: pixels of two images
+            float input = 0.f;
+            const float first = of_one_image & !whole ? __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(back[0]))) : back[0];
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) input = __builtin_fmaxf(input, inputs[nb]);
-        if (whole) {
+            for (int nb = 0; nb < NB; ++nb) {
+                input = __builtin_fmaxf(input, inputs[nb]);
+                other |= (back[nb] != first) & (pixel_of(nb, l16) < left_px);
+            }
+            if (of_one_image & !whole) input = row_largest(input);
+            // (a lane of two images: each one's pixels; of more, single ones)
+            bool of_first[NB], of_last[NB];
+            if (!lane_of_one) {
+                const bool two = g.per >= NB - 1;
+                other = bad;
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) other |= back[nb] != back[0];
+                for (int nb = 0; nb < NB; ++nb) {
+                    const bool there = pixel_of(nb, l16) < left_px;
+                    of_first[nb] = there & (two ? image_in(pixel_of(nb, l16)) == image_in(pixel_of(0, l16)) : nb == 0);
+                    of_last[nb] = there & !of_first[nb];
+                    other |= (of_first[nb] & (back[nb] != back[0])) | (of_last[nb] & (back[nb] != back[NB - 1])) | (!two & (nb > 0) & (nb + 1 < NB) & there);
+                    apart |= of_last[nb];
+                }
+            }
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     float m = 0.f;
+                    if (lane_of_one & whole) {
 #pragma unroll
-                    for (int nb = 0; nb < NB; ++nb) m = __builtin_elementwise_maximum(m, __builtin_fabsf(acc[mb][nb][i]));
-                    most_sum[mb][i] = m;
+                        for (int nb = 0; nb < NB; ++nb) m = __builtin_elementwise_maximum(m, __builtin_fabsf(acc[mb][nb][i]));
+                        other |= !(m <= FINITE);
+                    } else if (lane_of_one) {
+#pragma unroll
+                        for (int nb = 0; nb < NB; ++nb) m = __builtin_elementwise_maximum(m, pixel_of(nb, l16) < left_px ? __builtin_fabsf(acc[mb][nb][i]) : 0.f);
+                        if (of_one_image) m = row_largest(m);
+                        other |= !(m <= FINITE);
+                    } else {
+                        float last = 0.f;
+#pragma unroll
+                        for (int nb = 0; nb < NB; ++nb) {
+                            m = __builtin_elementwise_maximum(m, of_first[nb] ? __builtin_fabsf(acc[mb][nb][i]) : 0.f);
+                            last = __builtin_elementwise_maximum(last, of_last[nb] ? __builtin_fabsf(acc[mb][nb][i]) : 0.f);
+                        }
+                        other |= !(m <= FINITE) | !(last <= FINITE);
+                        m = apart && last < m ? last : m;
+                    }
+                    other |= !(m >= line_at(mb, i, input)) & kernel_exists(mb, i) & (input > 0.f);
                 }
+            return __builtin_amdgcn_ballot_w64(other) == 0;
+        } else if constexpr (!VPX) {
+            bool other = bad, same[NB][NB];
+            float input = 0.f;
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                input = __builtin_fmaxf(input, inputs[nb]);
+#pragma unroll
+                for (int o = 0; o < NB; ++o) {
+                    same[nb][o] = (image_in(pixel_of(o, l16)) == image_in(pixel_of(nb, l16))) & (pixel_of(o, l16) < left_px);
+                    other |= (back[nb] != back[o]) & same[nb][o];
+                }
+            }
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float line = line_at(mb, i, input);
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) {
+                        float m = 0.f;
+#pragma unroll
+                        for (int o = 0; o < NB; ++o) m = __builtin_elementwise_maximum(m, same[nb][o] ? __builtin_fabsf(acc[mb][o][i]) : 0.f);
+                        other |= ((!(m >= line) & kernel_exists(mb, i) & (inputs[nb] > 0.f)) | !(m <= FINITE)) & same[nb][nb];
+                    }
+                }
+            return __builtin_amdgcn_ballot_w64(other) == 0;
         } else {
-            input = row_largest(input);
-            const float first = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(back[0])));
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) other |= (back[nb] != first) & (pixel_of(nb, l16) < left_px);
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    float m = 0.f;
-#pragma unroll
-                    for (int nb = 0; nb < NB; ++nb) m = __builtin_elementwise_maximum(m, pixel_of(nb, l16) < left_px ? __builtin_fabsf(acc[mb][nb][i]) : 0.f);
-                    most_sum[mb][i] = row_largest(m);
-                }
+            return false;
         }
-        const float line = half_line(most_norm, most_root, input);
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                other |= (!(most_sum[mb][i] >= line) & ((kb16 + mb) * 16 + 4 * grp + i < g.K)) | !(most_sum[mb][i] <= FINITE);
-        fine = __builtin_amdgcn_ballot_w64(other) == 0;
+    };
+    bool fine = lane_of_one ? all_well(std::false_type{}) : false;
+    if (__builtin_expect(!fine, 0)) {
+        if (lane_of_one) wave_lines<MB>(reinterpret_cast<const KernelFacts*>(group_scales + 16 * g.Kb16) + kb16 * 16, g.pieces, 16 * g.Kb16, lane, lines + wm_i * (16 * MB));
+        fine = all_well(std::true_type{});
     }
     if (__builtin_expect(!fine, 0)) {
     int image[NB];
     float size[NB];
-    const bool ragged = of_one && !whole;
-    const int judging = lane_of_one || of_one ? JUDGE_LANE : last_image < MOST_IMAGES ? JUDGE_IMAGES : JUDGE_QUADS;
+    const bool ragged = of_one_image && !whole;
+    const int judging = lane_of_one ? JUDGE_LANE : JUDGE_MIXED;
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
         const bool there = pixel_of(nb, l16) < left_px;
@@ -385,22 +445,14 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
         if (NB < 4) all = quad_largest(all, 0);
         if (ragged) all = row_largest(all);
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) to[nb] = 0.f;
-        if (__builtin_expect(judging == JUDGE_LANE, 1)) {
+        for (int nb = 0; nb < NB; ++nb) {
+            float mine = all;
+            if (judging == JUDGE_MIXED) {
+                mine = 0.f;
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) to[nb] = all;
-        } else if (judging == JUDGE_QUADS) {
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) to[nb] = quad_largest(v[nb], image[nb]);
-        } else {
-            for (int im = 0; im <= last_image; ++im) {
-                float m = 0.f;
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb) m = image[nb] == im ? __builtin_fmaxf(m, v[nb]) : m;
-                m = row_largest(m);
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb) to[nb] = image[nb] == im ? m : to[nb];
+                for (int other = 0; other < NB; ++other) mine = image[other] == image[nb] ? __builtin_fmaxf(mine, v[other]) : mine;
             }
+            to[nb] = mine;
         }
     };
     bool lost[NB], zero[NB];
@@ -419,23 +471,8 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) inputs[nb] = largest[nb];
     }
-    // whether all is well by that line
+    // otherwise each output for itself; zero inputs have lost nothing
     {
-        float line[NB];
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) line[nb] = inputs[nb] > 0.f ? half_line(most_norm, most_root, inputs[nb]) : 0.f;
-        float least = 0.f;
-        judge_sums<MB, NB>(judging, ragged, image, 0, last_image, [&](int mb, int nb, int i) { return __builtin_fabsf(acc[mb][nb][i]) * size[nb]; },
-                           [&](auto in) {
-                               least = 0.f;
-#pragma unroll
-                               for (int nb = 0; nb < NB; ++nb) least = in(nb) ? line[nb] : least;
-                           },
-                           [&](int mb, int i, float m) { bad |= (!(m >= least) & ((kb16 + mb) * 16 + 4 * grp + i < g.K)) | !(m <= FINITE); });
-    }
-    fine = __builtin_amdgcn_ballot_w64(bad) == 0;
-    // otherwise each output for itself, by its kernel's own line; zero inputs have lost nothing
-    if (__builtin_expect(!fine, 0)) {
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -444,13 +481,8 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
                 for (int i = 0; i < 4; ++i)
                     if (image[nb] >= 0 && (lost[nb] || !(__builtin_fabsf(acc[mb][nb][i]) <= FINITE)) && (kb16 + mb) * 16 + 4 * (opaque(lane) >> 4) + i < g.K)
                         again |= 1ull << ((nb * MB + mb) * 4 + i);
-        KernelLine own_line[MB];                            // of kernels l16
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-            own_line[mb] = kernel_line(reinterpret_cast<const KernelFacts*>(reinterpret_cast<const float*>(group_w + (size_t)nchunks * wstep) + 16 * g.Kb16) + (kb16 + mb) * 16,
-                                       g.pieces, 16 * g.Kb16, opaque(lane));
         unsigned group = 0;                                 // bits of the nb that are judged together
-        judge_sums<MB, NB>(judging, ragged, image, 0, last_image,
+        judge_sums<MB, NB>(judging, ragged, image, 0, 0,
                            [&](int mb, int nb, int i) { return __builtin_fabsf(acc[mb][nb][i]) <= FINITE ? __builtin_fabsf(acc[mb][nb][i]) * size[nb] : 0.f; },
                            [&](auto in) {
                                group = 0;
@@ -459,11 +491,11 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
                            },
                            [&](int mb, int i, float m) {
                                const int k = 4 * (opaque(lane) >> 4) + i;
-                               const float norm = __shfl(own_line[mb].norm, k), root = __shfl(own_line[mb].root, k);
-                               const bool there = (kb16 + mb) * 16 + k < g.K;
+                               if ((kb16 + mb) * 16 + k >= g.K) return;
+                               const KernelLine line = lines[(wm_i * MB + mb) * 16 + k];
 #pragma unroll
                                for (int nb = 0; nb < NB; ++nb)
-                                   if (there && (group >> nb & 1) && !(m >= half_line(norm, root, inputs[nb]))) again |= 1ull << ((nb * MB + mb) * 4 + i);
+                                   if ((group >> nb & 1) & !(m >= line_of(line, inputs[nb]))) again |= 1ull << ((nb * MB + mb) * 4 + i);
                            });
     }
     }
@@ -601,7 +633,7 @@ template <int MB, int NB, int WM, int WN, int IN, bool VPX>
 hipError_t launch_one(const float* x, const u32x4* wt, const float* w, float* y, const SplitPointGeom& g, hipStream_t st)
 {
     auto kern = split_point_kernel<MB, NB, WM, WN, IN, VPX>;
-    constexpr size_t NPIX = 16 * NB * WN, shm = 5 * 4 * NPIX * 16 + 16 + 16 * NPIX + 64 * MB * WM;
+    constexpr size_t NPIX = 16 * NB * WN, shm = 5 * 4 * NPIX * 16 + 16 + 16 * NPIX + 64 * MB * WM + 512 * WM * WN;
     static_assert(shm <= 64 * 1024, "dynamic LDS without an opt-in");
     hipLaunchKernelGGL(kern, dim3(g.nbk * g.nbp * g.groups), dim3(64 * WM * WN), shm, st, x, wt, y, g, w, Divisor(g.per));
     return hipGetLastError();

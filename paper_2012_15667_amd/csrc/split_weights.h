@@ -50,8 +50,8 @@ __device__ __forceinline__ void store_parts(u32x4* to, const unsigned short (&p)
 
 // The piece of eight transformed kernel elements in two fp16 parts, scaled already, of kernel lane % KERNELS and the channels of lane / KERNELS; the
 // lanes that share a kernel, lane % KERNELS, judge it together (of `channels` < 16 some are all small now and then: left to the sums).  NaN in
-// place of a kernel that does not fit its scale.  Returns what the lanes that share a kernel have of it.
-template <int KERNELS>
+// place of a kernel too small for its scale, or with larger squares (of what is returned).  Returns what the elements of the lane, or (SHARED) of all lanes that share the kernel, tell of it.
+template <int KERNELS, bool SHARED>
 __device__ __forceinline__ KernelFacts store_halves(u32x4* to, const float (&u)[8], int channels, float most_squares)
 {
     u32x4 h, l;
@@ -60,17 +60,19 @@ __device__ __forceinline__ KernelFacts store_halves(u32x4* to, const float (&u)[
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         facts.squares = __builtin_fmaf(u[j], u[j], facts.squares);
-        facts.small += u[j] != 0.f && __builtin_fabsf(u[j]) < HALF_LEAST ? 1.f : 0.f;
+        facts.small += magnitude(u[j]) - 1 < __float_as_uint(HALF_LEAST) - 1 ? 1.f : 0.f;       // (zero comes last)
     }
 #pragma unroll
     for (int d = KERNELS; d < 64; d *= 2) {
         most = __builtin_fmaxf(most, __shfl_xor(most, d));
-        facts.squares += __shfl_xor(facts.squares, d);
-        facts.small += __shfl_xor(facts.small, d);
+        if constexpr (SHARED) {
+            facts.squares += __shfl_xor(facts.squares, d);
+            facts.small += __shfl_xor(facts.small, d);
+        }
     }
-    const unsigned poison = (channels >= 16 && most != 0.f && most < HALF_LEAST) || !(facts.squares <= most_squares) ? 0x7e007e00u : 0u;
+    const bool fits = (channels < 16 || most == 0.f || most >= HALF_LEAST) && facts.squares <= most_squares;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) h[i] |= poison;
+    for (int i = 0; i < 4; ++i) h[i] |= fits ? 0u : 0x7e007e00u;
     to[0] = h;
     to[64] = l;
     return facts;
@@ -124,7 +126,18 @@ __device__ __forceinline__ float row_up(int row)
     static_for<M + 2>([&](auto r) { if (row == decltype(r)::value) up = power_of_two(kernel_up<M>(decltype(r)::value)); });
     return up;
 }
-// ... and back.
+// The weight of its sums in an output.
+template <int M>
+__device__ __forceinline__ float row_weight(int row)
+{
+    float weight = 0.f;
+    static_for<M + 2>([&](auto r) {
+        constexpr float of_row = plane_weight<M>(decltype(r)::value);
+        if (row == decltype(r)::value) weight = of_row;
+    });
+    return weight;
+}
+// What brings it back.
 template <int M>
 __device__ __forceinline__ float row_down(int row)
 {
@@ -159,7 +172,11 @@ struct RawKernels {
         if (k >= K || c >= C) return 0.f;
         if (raw == SPLIT_RAW_ROWS) return w[(size_t)k * C + c];
         if (raw == SPLIT_RAW_PLANES) return w[((size_t)plane * ((C + 15) / 16 * 16) + c) * ((K + 31) / 32 * 32) + k];
-        const float* t = w + ((size_t)k * C + c) * 9;
+        return of(w + ((size_t)k * C + c) * 9);
+    }
+    // (of nine taps)
+    __device__ __forceinline__ float of(const float* t) const
+    {
         float u = 0.f;
 #pragma unroll
         for (int j = 0; j < 3; ++j) u = add(lj[j], add(li[2], t[6 + j], add(li[1], t[3 + j], add(li[0], t[j], 0.f))), u);

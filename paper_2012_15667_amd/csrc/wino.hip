@@ -107,7 +107,7 @@ __device__ __forceinline__ void kernel_transform_split_block(const float* __rest
 #pragma unroll
             for (int c = 0; c < 8; ++c) u[c] = kernel_element<M, J>(lg[c]) * up;
             u32x4* const to = wt + (size_t)(row * n + J) * chunks * Kb16 * 192;
-            const KernelFacts f = store_halves<16>(to + ((size_t)ch * Kb16 + kb) * 128 + lane, u, C - ch * 32, HALF_PIECE_PLANE);
+            const KernelFacts f = store_halves<16, true>(to + ((size_t)ch * Kb16 + kb) * 128 + lane, u, C - ch * 32, HALF_PIECE_PLANE);
             if (lane < 16) plane_facts(to, chunks, Kb16)[((size_t)ch * Kb16 + kb) * 16 + lane] = f;
         });
     }
@@ -138,7 +138,7 @@ __device__ __forceinline__ void split_planes_block(const float* __restrict__ U, 
     if (ch == 0 && lane < 16) reinterpret_cast<float*>(to + (size_t)128 * chunks * Kb16)[k] = half_unscale(scale) * (row_down<M>(plane / n) * row_down<M>(plane % n));
 #pragma unroll
     for (int j = 0; j < 8; ++j) u[j] *= __uint_as_float(scale) * up;
-    const KernelFacts f = store_halves<16>(to + ((size_t)ch * Kb16 + kb) * 128 + lane, u, C - ch * 32, HALF_PIECE_PLANE);
+    const KernelFacts f = store_halves<16, true>(to + ((size_t)ch * Kb16 + kb) * 128 + lane, u, C - ch * 32, HALF_PIECE_PLANE);
     if (lane < 16) plane_facts(to, chunks, Kb16)[((size_t)ch * Kb16 + kb) * 16 + lane] = f;
 }
 

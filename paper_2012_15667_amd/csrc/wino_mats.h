@@ -84,6 +84,30 @@ constexpr float power_of_two(int e)
     for (; e < 0; ++e) p *= 0.5f;
     return p;
 }
+// Largest factor with which sums of plane row (or column) `row`, of kernels brought to size as above, enter an output: of plane (i, j)
+// plane_weight(i) plane_weight(j).
+template <int M>
+constexpr float plane_weight(int row)
+{
+    float most = 0.f;
+    for (int r = 0; r < M; ++r) {
+        const float a = Mats<M>::A[r][row] < 0.f ? -Mats<M>::A[r][row] : Mats<M>::A[r][row];
+        most = a > most ? a : most;
+    }
+    return most * power_of_two(-kernel_up<M>(row));
+}
+// Factor from inputs to their transform, in the root mean square and at most: the squares of B's rows, added up.
+template <int M>
+constexpr float input_growth()
+{
+    float most = 0.f;
+    for (int r = 0; r < M + 2; ++r) {
+        float sum = 0.f;
+        for (int j = 0; j < M + 2; ++j) sum += Mats<M>::B[r][j] * Mats<M>::B[r][j];
+        most = sum > most ? sum : most;
+    }
+    return most;                                             // (a root each for rows and columns)
+}
 
 }  // namespace iolb
 

@@ -95,14 +95,18 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
     // What a transform rounds off is not less than what V's parts lose, at most 2^-25, where a window has a value of 2^-5 and 2^-2.
     constexpr int TOP = M == 4 ? 3 : 7;
     constexpr float LEAST = M == 4 ? 0.03125f : 0.25f;
+    // Sums are judged as split_mfma.h tells, the outputs of a sub-domain together: unmarked errors are 2^-21 of the largest of them, 2^-18 in
+    // F(4 x 4) (in the root mean square; the transforms round off 2^-22 and 2^-19).
+    constexpr float LINE = M == 4 ? HALF_LINE / 8 : HALF_LINE;
     extern __shared__ u32x4 lds16[];
     char* const lds = reinterpret_cast<char*>(lds16);
     // behind the buffers: whether a block is taken again; what undoes the kernels' scales; per image of the block the largest value of the
-    // sample that sets its scale; per sub-domain the largest value of its windows, scaled
+    // sample that sets its scale; per sub-domain the largest value of its windows, scaled; what the kernels' lines follow from
     int* const any = reinterpret_cast<int*>(lds + wino_split_buffers(M, TB));
     float* const kback = reinterpret_cast<float*>(any + 4);
     unsigned* const sample = reinterpret_cast<unsigned*>(kback + Z);
     unsigned* const most = sample + TB;
+    KernelLine* const lines = reinterpret_cast<KernelLine*>(most + TB);
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
@@ -357,7 +361,8 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
     // writes and reads two kernels at once and 32 tiles reach every bank once; a thread then owns whole (kernel, tile) pairs.
     constexpr int PAIRS = 32 * TB / 512;
     static_assert(ZB * PAIRS <= 32, "one mark per pair");
-    unsigned again = 0;                                      // pairs whose sums are not all finite
+    unsigned again = 0;                                      // pairs that are taken again
+    bool again_root = false;                                 // (the second time: and once more those below what their kernel's small elements may have lost)
     auto finish = [&](auto marked_c) {
         constexpr bool MARKED = decltype(marked_c)::value;   // the second time: marked pairs only
         float* const m = reinterpret_cast<float*>(lds);
@@ -380,10 +385,11 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
             int img, ti, tj;
             place(t, img, ti, tj);
             const int h0 = ti * M, w0 = tj * M;
-            float back = 1.f;
+            float back = 1.f, input = 0.f;
             bool lost = false;
             if constexpr (TWO) {
                 back = half_unscale(half_scale_bits<TOP>(sample[t < g.tiles ? img - img0 : 0]));
+                input = __uint_as_float(most[tl]);
                 lost = most[tl] - 1 < __float_as_uint(LEAST) - 1;
             }
 #pragma unroll
@@ -417,11 +423,28 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
                     if (t >= g.tiles || k >= g.K) continue;
                     if constexpr (MARKED) {
                         if (!(again >> bit & 1)) continue;
+                        if (TWO && again_root) {
+                            float largest = 0.f;
+#pragma unroll
+                            for (int r = 0; r < M; ++r)
+#pragma unroll
+                                for (int j = 0; j < M; ++j) largest = __builtin_elementwise_maximum(largest, __builtin_fabsf(o[r][j]));
+                            // (sums that are not finite are what they are)
+                            if (!(largest < lines[32 * z + kl].root * input * back * kback[32 * z + kl])) again &= ~(1u << bit);
+                        }
                     } else {
-                        // every plane enters one of the corners, with a factor that is not zero
-                        if (lost || !(__builtin_fabsf(o[0][0]) <= 3.402823466e38f && __builtin_fabsf(o[0][M - 1]) <= 3.402823466e38f &&
-                              __builtin_fabsf(o[M - 1][0]) <= 3.402823466e38f && __builtin_fabsf(o[M - 1][M - 1]) <= 3.402823466e38f))
-                            again |= 1u << bit;
+                        // (every plane enters an output)
+                        float largest = 0.f;
+#pragma unroll
+                        for (int r = 0; r < M; ++r)
+#pragma unroll
+                            for (int j = 0; j < M; ++j) largest = __builtin_elementwise_maximum(largest, __builtin_fabsf(o[r][j]));
+                        bool bad = lost || !(largest <= FINITE);
+                        if constexpr (TWO) {
+                            const KernelLine line = lines[32 * z + kl];
+                            bad |= input > 0.f && !(largest >= line_of(line, input));
+                        }
+                        if (bad) again |= 1u << bit;
                         if constexpr (TWO) {
                             const float kscale = kback[32 * z + kl];
 #pragma unroll
@@ -461,11 +484,14 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
         load_x(first, 0);
         // for the sample beside the first stage a value of each sub-domain from other channels, a wave four of them; the kernels' scales
         float spread = 0.f, my_kback = 0.f;
+        FactsShare<2> share;                                   // (of the kernels' facts, a piece per stage)
         if constexpr (TWO) {
             const int sc = wave * g.C >> 3;
             const unsigned long long have = __builtin_amdgcn_ballot_w64(sc + (lane >> 4) < g.C) & rowok[1] & colok[0];
             spread = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rx, (int)((by_lane(have) ? xoff : OUTSIDE) + 4), wino_split_offset<COLS>(g, sc, 1), 0));
-            if (tid < Z) my_kback = reinterpret_cast<const float*>(reinterpret_cast<const char*>(wt) + (size_t)PL * pstride)[kb * Z + tid];
+            const float* const scales = reinterpret_cast<const float*>(reinterpret_cast<const char*>(wt) + (size_t)PL * pstride);
+            if (tid < Z) my_kback = scales[kb * Z + tid];
+            share.load(reinterpret_cast<const KernelFacts*>(scales + 32 * g.Kb32) + kb * Z + tid % Z, tid / Z, 512 / Z, nst, 32 * g.Kb32);
         }
         static_range<0, D>([&](auto uc) {
             constexpr int u = decltype(uc)::value;
@@ -494,7 +520,16 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
                 atomicMax(sample + image_in, largest);
             }
             if (tid < Z) kback[tid] = my_kback;
+            // (in the buffer that the second stage goes to)
+            KernelFacts* const shares = reinterpret_cast<KernelFacts*>(lds + VBUF);
+            static_assert(VBUF >= 512 * (int)sizeof(KernelFacts), "room for the shares");
+            shares[tid] = share.sum();
             barrier();
+            if (tid < Z) {
+                const KernelLine line = kernel_line(all_shares<Z, 512 / Z>(shares, tid), LINE);
+                constexpr float growth = input_growth<M>();
+                lines[tid] = {line.norm, growth * line.root};
+            }
             xs = __uint_as_float(half_scale_bits<TOP>(sample[image_in]));
         }
         transform(first, lds);
@@ -529,49 +564,125 @@ wino_split_kernel(const float* __restrict__ x, const u32x4* wt, float* __restric
     barrier();
     if (__builtin_amdgcn_readfirstlane(*any) == 0) return;
 
-    // The block again on the fp32 matrix instructions, from the same inputs; three parts hold all of a kernel, of two the caller's own is
-    // read: they may have lost what the block is taken again for.
-    clear();
+    // The block again on the fp32 matrix instructions, from the same inputs.  Three parts hold all of a kernel, and so do two of most, unless they
+    // are not finite: the caller's own is read then.  Sums that are below what the kernel's small elements may have lost are taken
+    // once more, all of their kernels read from the caller's.
     xs = 1.f;
+#pragma unroll 1
+    for (bool careful = false;; careful = true) {
+    clear();
 #pragma unroll 1
     for (int s = 0; s < nst; ++s) {
         load_x(wx, s);
         transform(wx, lds);
         barrier();
-        auto unit = [&](int u, int plane, int z, f32x16 (&c)[TBB]) {
-            const char* vplane = lds + plane * (TB * 64);
-            float w[8];
-            if constexpr (TWO) {
-                // (opaque: nothing of it is computed, and kept in scalar registers, through the loop above)
-                const RawKernels kernels(w_raw, raw, M, opaque(plane), opaque(g.C), opaque(g.K));
-#pragma unroll
-                for (int j = 0; j < 8; ++j) w[j] = kernels.at(kb * Z + 32 * z + l32, 16 * s + 8 * half + j);
-            } else {
-                u32x4 f[PARTS];
-                load_u(f, unit_at(u, s));
-                kept_eight(f[0], f[1], f[PARTS - 1], w);
-            }
+        auto multiply4 = [&](int plane, int four, const float* w, f32x16 (&c)[TBB]) {
 #pragma unroll
             for (int t = 0; t < TBB; ++t) {
-                float v[8];
-                fetch(v, vplane, t);
+                const f32x4 v = *reinterpret_cast<const f32x4*>(lds + plane * (TB * 64) + r0 + four * (TB * 16) + t * 512);
 #pragma unroll
-                for (int j = 0; j < 8; ++j) c[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[j], v[j], c[t], 0, 0, 0);
+                for (int j = 0; j < 4; ++j) c[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[j], v[j], c[t], 0, 0, 0);
             }
         };
-        static_range<0, FP * ZB>([&](auto uc) {
-            constexpr int u = decltype(uc)::value;
-            unit(u, wave * FP + u / ZB, u % ZB, acc[u / ZB][u % ZB]);
-        });
-        if constexpr (LP != 0)
-            if (has_extra) unit(UNITS - 1, xplane, xzb, accx);
+        if constexpr (TWO) {
+            static_range<0, ZB>([&](auto zc) {
+                constexpr int z = decltype(zc)::value;
+#pragma unroll 1
+                for (int four = 0; four < 2; ++four) {
+                    const int lane2 = opaque(lane), k = kb * Z + 32 * z + (lane2 & 31), c0 = 16 * s + 8 * (lane2 >> 5) + 4 * four;
+                    float taps[4][9];
+                    if (careful && raw == SPLIT_RAW_TAPS)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+#pragma unroll
+                            for (int i = 0; i < 9; ++i) {
+                                const bool exists = k < g.K && c0 + j < g.C;
+                                taps[j][i] = w_raw[exists ? ((size_t)k * g.C + c0 + j) * 9 + i : 0];
+                                taps[j][i] = exists ? taps[j][i] : 0.f;
+                            }
+                    auto unit = [&](int plane, f32x16 (&c)[TBB]) {
+                        // (opaque: nothing of it is computed, and kept in scalar registers, through the loop above)
+                        const int pl = __builtin_amdgcn_readfirstlane(opaque(plane + (four >> 1)));
+                        const RawKernels kernels(w_raw, raw, M, pl, opaque(g.C), opaque(g.K));
+                        float w[4];
+                        bool whole = !careful;
+                        if (!careful) {
+                            const unsigned at = (unsigned)(s * g.Kb32 + kb * ZB + z) * UNIT + (unsigned)pl * pstride;
+                            const u32x2 h = __builtin_amdgcn_raw_buffer_load_b64(ru, lane * 16 + 8 * four, (int)at, 0), l = __builtin_amdgcn_raw_buffer_load_b64(ru, lane * 16 + 8 * four + 1024, (int)at, 0);
+                            const float back = kback[32 * z + l32] * (row_down<M>(pl / n) * row_down<M>(pl % n));
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) {
+                                // (a bit_cast of an element of a vector reads its first one)
+                                const unsigned hb = h[j / 2], lb = l[j / 2];
+                                const f16x2 hj = __builtin_bit_cast(f16x2, hb), lj = __builtin_bit_cast(f16x2, lb);
+                                w[j] = ((float)hj[j % 2] + (float)lj[j % 2]) * back;
+                                whole = whole && __builtin_fabsf(w[j]) <= FINITE;
+                            }
+                        }
+                        if (!whole)
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) w[j] = careful && raw == SPLIT_RAW_TAPS ? kernels.of(taps[j]) : kernels.at(k, c0 + j);
+                        multiply4(plane, four, w, c);
+                    };
+                    static_range<0, FP>([&](auto pc) { unit(wave * FP + decltype(pc)::value, acc[decltype(pc)::value][z]); });
+                    if constexpr (LP != 0)
+                        if (has_extra && xzb == z) unit(xplane, accx);
+                }
+            });
+        } else {
+            auto unit = [&](int u, int plane, f32x16 (&c)[TBB]) {
+                u32x4 f[PARTS];
+                float w[8];
+                load_u(f, unit_at(u, s));
+                kept_eight(f[0], f[1], f[PARTS - 1], w);
+                multiply4(plane, 0, w, c);
+                multiply4(plane, 1, w + 4, c);
+            };
+            static_range<0, FP * ZB>([&](auto uc) {
+                constexpr int u = decltype(uc)::value;
+                unit(u, wave * FP + u / ZB, acc[u / ZB][u % ZB]);
+            });
+            if constexpr (LP != 0)
+                if (has_extra) unit(UNITS - 1, xplane, accx);
+        }
         barrier();
     }
+    if (tid == 0) *any = 0;
+    again_root = !careful;
     finish(std::true_type{});
+    if (!TWO || careful) return;
+    barrier();
+    if (again) *any = 1;
+    barrier();
+    if (__builtin_amdgcn_readfirstlane(*any) == 0) return;
+    }
+}
+
+// What a lane's elements of a kernel in a plane tell, by the weight of its sums in an output.
+__device__ __forceinline__ void add_weighted(KernelFacts& to, const KernelFacts& f, float weight)
+{
+    to.squares = __builtin_fmaf(weight * weight, f.squares, to.squares);
+    to.small = __builtin_fmaf(weight * weight, f.small, to.small);
+}
+// All of a kernel's 16 channels, rows[row of planes][channels' half, kernel], in a fixed order.
+template <int M>
+__device__ __forceinline__ void store_facts(const KernelFacts (&rows)[M + 2][64], KernelFacts* to)
+{
+    __syncthreads();
+    if (threadIdx.x >= 32) return;
+    KernelFacts all = {0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < M + 2; ++i)
+#pragma unroll
+        for (int half = 0; half < 64; half += 32) {
+            all.squares += rows[i][half + threadIdx.x].squares;
+            all.small += rows[i][half + threadIdx.x].small;
+        }
+    to[threadIdx.x] = all;
 }
 
 // Kernels in two or three parts in the order of the kernel above: [plane][16 channels][32 kernels][part][lane][8 channels], and behind two
-// parts what undoes the scales of 32 Kb32 kernels.
+// parts what undoes the scales of 32 Kb32 kernels, and their facts, [16 channels][kernel].
 // One workgroup per 16 channels of 32 kernels of w[K][C][3][3], a wave per row of the planes in turn.
 template <int M, int PARTS>
 __global__ void __launch_bounds__(256)
@@ -583,6 +694,7 @@ wino_split_weights(const float* __restrict__ w, u32x4* __restrict__ wt, int C, i
     const int kb = blockIdx.x % Kb32, ch = blockIdx.x / Kb32;
     const int have = C - ch * 16 < 16 ? (C - ch * 16) * 9 : LEN;
     __shared__ unsigned scales[32];
+    __shared__ KernelFacts rows_facts[n][64];
     float some[8];                                          // each kernel's scale, the same in all of its workgroups
 #pragma unroll
     for (int j = 0; j < 8; ++j) some[j] = PARTS == 2 ? sampled_value(w, kb * 32 + wave * 8 + j, K, C, lane) : 0.f;
@@ -600,7 +712,8 @@ wino_split_weights(const float* __restrict__ w, u32x4* __restrict__ wt, int C, i
     for (int row = wave; row < n; row += 4) {
         float lg[8][3];                                     // this row of L g, for each channel
         kernel_row<M>(row, mine, lg);
-        const float this_up = row_up<M>(row);
+        const float this_up = row_up<M>(row), this_weight = PARTS == 2 ? row_weight<M>(row) : 0.f;
+        KernelFacts facts = {0.f, 0.f};
         static_for<n>([&](auto j) {
             constexpr int J = decltype(j)::value;
             if constexpr (PARTS == 3) {
@@ -610,55 +723,74 @@ wino_split_weights(const float* __restrict__ w, u32x4* __restrict__ wt, int C, i
                 store_parts(wt + (((size_t)(row * n + J) * chunks + ch) * Kb32 + kb) * 192 + lane, p);
                 return;
             }
-            const float up = __uint_as_float(scale) * this_up * power_of_two(kernel_up<M>(J));
+            constexpr float to_size = power_of_two(kernel_up<M>(J));
+            const float up = __uint_as_float(scale) * this_up * to_size;
             float u[8];
 #pragma unroll
             for (int c = 0; c < 8; ++c) u[c] = kernel_element<M, J>(lg[c]) * up;
-            store_halves<32>(wt + (((size_t)(row * n + J) * chunks + ch) * Kb32 + kb) * 128 + lane, u, C - ch * 16, 3e38f);
+            const KernelFacts f = store_halves<32, false>(wt + (((size_t)(row * n + J) * chunks + ch) * Kb32 + kb) * 128 + lane, u, C - ch * 16, 3e38f);
+            constexpr float weight = plane_weight<M>(J);
+            add_weighted(facts, f, this_weight * weight);
         });
+        if constexpr (PARTS == 2) rows_facts[row][lane] = facts;
     }
+    if constexpr (PARTS == 2)
+        store_facts<M>(rows_facts, reinterpret_cast<KernelFacts*>(reinterpret_cast<float*>(wt + (size_t)n * n * chunks * Kb32 * 128) + 32 * Kb32) + ((size_t)ch * Kb32 + kb) * 32);
 }
 
-// The same, to the same bits, from a caller's U[plane][C rounded up to 16][K rounded up to 32]: one lane per 16-byte piece.
+// The same, to the same bits, from a caller's U[plane][C rounded up to 16][K rounded up to 32]: a wave per row of the planes.
 template <int M, int PARTS>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(64 * (M + 2))
 wino_split_given(const float* __restrict__ U, u32x4* __restrict__ wt, int C, int K, int chunks, int Kb32)
 {
     constexpr int n = M + 2;
-    const long long id = (long long)blockIdx.x * 256 + threadIdx.x, per = (long long)chunks * Kb32 * 64;
-    const int plane = (int)(id / per), in = (int)(id % per);
-    if (plane >= n * n) return;
-    const int lane = in & 63, kb = (in >> 6) % Kb32, ch = (in >> 6) / Kb32;
+    __shared__ KernelFacts rows_facts[n][64];
+    const int lane = threadIdx.x & 63, row = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int kb = blockIdx.x % Kb32, ch = blockIdx.x / Kb32;
     const int k = kb * 32 + (lane & 31), c0 = ch * 16 + (lane >> 5) * 8;
     const int rows = (C + 15) / 16 * 16, cols = (K + 31) / 32 * 32;
-    if constexpr (PARTS == 3) {
-        unsigned short p[3][8];
+    const unsigned scale = PARTS == 2 ? scale_of_given<M, 32>(U, k, K, C, rows, cols, lane) : 0u;
+    if (PARTS == 2 && ch == 0 && threadIdx.x < 32) reinterpret_cast<float*>(wt + (size_t)n * n * chunks * Kb32 * 128)[k] = half_unscale(scale);
+    KernelFacts facts = {0.f, 0.f};
+    float v[n][8];
+#pragma unroll
+    for (int j = 0; j < n; ++j)
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
-            const float v = k < K && c0 + c < C ? U[((size_t)plane * rows + c0 + c) * cols + k] : 0.f;
-            split_kept(v, p[0][c], p[1][c], p[2][c]);
+            const bool exists = k < K && c0 + c < C;
+            v[j][c] = U[exists ? ((size_t)(row * n + j) * rows + c0 + c) * cols + k : 0];
+            v[j][c] = exists ? v[j][c] : 0.f;
         }
-        store_parts(wt + (((size_t)plane * chunks + ch) * Kb32 + kb) * 192 + lane, p);
-        return;
-    }
-    const unsigned scale = scale_of_given<M, 32>(U, k, K, C, rows, cols, lane);
-    if (plane == 0 && ch == 0 && lane < 32) reinterpret_cast<float*>(wt + (size_t)n * n * chunks * Kb32 * 128)[k] = half_unscale(scale);
-    const float up = __uint_as_float(scale) * row_up<M>(plane / n) * row_up<M>(plane % n);
-    float u[8];
+    const float this_up = row_up<M>(row), this_weight = PARTS == 2 ? row_weight<M>(row) : 0.f;
+    static_for<n>([&](auto j) {
+        constexpr int J = decltype(j)::value;
+        const size_t piece = ((size_t)(row * n + J) * chunks + ch) * Kb32 + kb;
+        if constexpr (PARTS == 3) {
+            unsigned short p[3][8];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        const bool exists = k < K && c0 + c < C;
-        u[c] = U[exists ? ((size_t)plane * rows + c0 + c) * cols + k : 0];
-        u[c] = exists ? u[c] * up : 0.f;
-    }
-    store_halves<32>(wt + (((size_t)plane * chunks + ch) * Kb32 + kb) * 128 + lane, u, C - ch * 16, 3e38f);
+            for (int c = 0; c < 8; ++c) split_kept(v[J][c], p[0][c], p[1][c], p[2][c]);
+            store_parts(wt + piece * 192 + lane, p);
+            return;
+        }
+        constexpr float to_size = power_of_two(kernel_up<M>(J));
+            const float up = __uint_as_float(scale) * this_up * to_size;
+        float u[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) u[c] = v[J][c] * up;
+        const KernelFacts f = store_halves<32, false>(wt + piece * 128 + lane, u, C - ch * 16, 3e38f);
+        constexpr float weight = plane_weight<M>(J);
+        add_weighted(facts, f, this_weight * weight);
+    });
+    if constexpr (PARTS == 2) rows_facts[row][lane] = facts;
+    if constexpr (PARTS == 2)
+        store_facts<M>(rows_facts, reinterpret_cast<KernelFacts*>(reinterpret_cast<float*>(wt + (size_t)n * n * chunks * Kb32 * 128) + 32 * Kb32) + ((size_t)ch * Kb32 + kb) * 32);
 }
 
 template <int M, int TB, int Z, int COLS, int PARTS>
 hipError_t launch_one(const float* x, const u32x4* wt, const float* w, int raw, float* y, const WinoSplitGeom& g, hipStream_t st)
 {
     auto kern = wino_split_kernel<M, TB, Z, COLS, PARTS>;
-    constexpr size_t shm = wino_split_buffers(M, TB) + 16 + 4 * Z + 8 * TB;
+    constexpr size_t shm = wino_split_buffers(M, TB) + 16 + 4 * Z + 8 * TB + 8 * Z;
     static_assert(shm <= 160 * 1024, "LDS");
     if (shm > 64 * 1024) {
         const hipError_t e = allow_large_lds((const void*)kern);
@@ -672,13 +804,12 @@ hipError_t launch_one(const float* x, const u32x4* wt, const float* w, int raw, 
 
 hipError_t launch_wino_split_weights(const float* w, bool given, void* wt, const WinoSplitGeom& g, hipStream_t st)
 {
-    const long long pieces = (long long)g.chunks * g.Kb32 * 64, n = g.m + 2;
-    const long long blocks = given ? (pieces * n * n + 255) / 256 : (long long)g.chunks * g.Kb32;
-    if (pieces >= (1LL << 31) || blocks > 0x7fffffffLL || g.chunks * 16LL < g.C || g.Kb32 * 32LL < g.K) return hipErrorInvalidValue;
+    const long long blocks = (long long)g.chunks * g.Kb32;
+    if (blocks >= (1LL << 25) || g.chunks * 16LL < g.C || g.Kb32 * 32LL < g.K) return hipErrorInvalidValue;
     u32x4* o = static_cast<u32x4*>(wt);
 #define IOLB_CASE(M_, P_)                                                                                                                       \
     if (g.m == M_ && g.parts == P_) {                                                                                                           \
-        if (given) hipLaunchKernelGGL((wino_split_given<M_, P_>), dim3((unsigned)blocks), dim3(256), 0, st, w, o, g.C, g.K, g.chunks, g.Kb32);  \
+        if (given) hipLaunchKernelGGL((wino_split_given<M_, P_>), dim3((unsigned)blocks), dim3(64 * (M_ + 2)), 0, st, w, o, g.C, g.K, g.chunks, g.Kb32);  \
         else       hipLaunchKernelGGL((wino_split_weights<M_, P_>), dim3((unsigned)blocks), dim3(256), 0, st, w, o, g.C, g.K, g.chunks, g.Kb32); \
         return hipGetLastError();                                                                                                               \
     }
