@@ -714,15 +714,27 @@ split_conv_kernel(const float* __restrict__ x, const u32x4* wt, float* y, SplitG
                 if (lane == at) mine &= mine - 1;
                 const int nb = bit / (4 * MB), k = (kb16 + bit / 4 % MB) * 16 + 4 * (at >> 4) + (bit & 3);
                 const int rem = (wn_i * NB + nb) * 16 + (at & 15) - image * txy, row = rem / g.tx, n = n0 + image, py = y0 + row, px = x0 + rem % g.tx;
+                // (a lane takes every 64th of channels and taps, eight at a time: the latency of their loads is what this costs)
+                const float *xp = x + (size_t)n * C * g.H * g.W, *wp1 = own.w + (size_t)k * C * RS;
+                const int gy1 = py * g.stride - g.pad, gx1 = px * g.stride - g.pad_w;
                 float sum = 0.f;
-                for (int r = 0; r < g.R; ++r)
-                    for (int s = 0; s < g.S; ++s) {
-                        const int gy = py * g.stride - g.pad + r, gx = px * g.stride - g.pad_w + s;
-                        if (gy < 0 || gy >= g.H || gx < 0 || gx >= g.W) continue;
-                        const float* xp = x + (size_t)n * C * g.H * g.W + (g.hwc ? ((size_t)gy * g.W + gx) * C : (size_t)gy * g.W + gx);
-                        const float* wp1 = own.w + (size_t)k * C * RS + (own.transposed ? s * g.R + r : r * g.S + s);
-                        for (int c = lane; c < C; c += 64) sum = __builtin_fmaf(xp[(size_t)c * (cstep / 4)], wp1[(size_t)c * RS], sum);
+#pragma unroll 1
+                for (int e0 = lane; e0 < RS * C; e0 += 8 * 64) {
+                    float v[8], u[8];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const int e = e0 + 64 * j, c = e / RS, tap = e - c * RS;                     // as the kernel lies
+                        const int r = own.transposed ? tap % g.R : tap / g.S, s = own.transposed ? tap / g.R : tap - r * g.S;
+                        const int gy = gy1 + r, gx = gx1 + s;
+                        const bool inside = (e < RS * C) & (gy >= 0) & (gy < g.H) & (gx >= 0) & (gx < g.W);
+                        v[j] = xp[inside ? (size_t)c * (cstep / 4) + (g.hwc ? ((size_t)gy * g.W + gx) * C : (size_t)gy * g.W + gx) : 0];
+                        v[j] = inside ? v[j] : 0.f;
+                        u[j] = wp1[inside ? e : 0];
+                        u[j] = inside ? u[j] : 0.f;
                     }
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) sum = __builtin_fmaf(v[j], u[j], sum);
+                }
                 sum = wave_sum(sum);
                 if (lane == at) y[g.hwc ? (((size_t)n * g.P + py) * g.Q + px) * g.K + k : ((size_t)n * g.K + k) * PQ + (size_t)py * g.Q + px] = sum;
             }

@@ -583,7 +583,15 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
                 const size_t n = n0 + q / g.HW, in = g.stride == 1 ? r : r / g.Q * g.stride * g.Win + r % g.Q * g.stride;
                 const float* xp = x + n * image_floats + (g.hwc ? in * g.C : in);
                 float sum = 0.f;
-                for (int c = lane; c < g.C; c += 64) sum = __builtin_fmaf(xp[(size_t)c * (cstep / 4)], raw.at(k, c), sum);
+                // (eight loads at a time: their latency is what this costs)
+#pragma unroll 1
+                for (int c0 = lane; c0 < g.C; c0 += 8 * 64) {
+                    float v[8];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) v[j] = xp[(size_t)(c0 + 64 * j < g.C ? c0 + 64 * j : 0) * (cstep / 4)];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) sum = __builtin_fmaf(c0 + 64 * j < g.C ? v[j] : 0.f, raw.at(k, c0 + 64 * j), sum);
+                }
                 sum = wave_sum(sum);
                 if (lane == at) y[g.hwc ? (n * g.HW + r) * g.K + k : (n * g.Ky + k) * g.HWy + r] = sum;
             }
