@@ -313,10 +313,15 @@ __device__ __forceinline__ float row_largest(float v)
     take(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, false));
     return v;
 }
+// What the lane before and the lane after hold (of a row of 16; 0 at its ends).
+__device__ __forceinline__ float lane_before(float v) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x111, 0xf, 0xf, false)); }
+__device__ __forceinline__ float lane_after(float v) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x101, 0xf, 0xf, false)); }
+// Which neighbours' pixels a lane of two images takes to its first and last ones: of its image, and of one scale (`scales` at either end).
+struct Joins { bool before, after; };
 // The sums of a kernel that are judged together, in a wave whose lanes l16 hold NB pixels each (one alone is below its line by chance once in some
 // 10^3, and looking closer costs 2 us): of one image a lane's (where NB is less than four its three neighbours' too; where some pixels are no
 // outputs, ragged, all of them); of up to MOST_IMAGES all of each; of more those of four neighbouring pixels that are of one image.  Mixed: a
-// lane's pixels that are of one image, several such groups.
+// lane's pixels that are of one image, several such groups, and those of the lanes beside it that `joins` allows.
 // image[nb]: -1 where there is no output.
 enum { JUDGE_LANE, JUDGE_IMAGES, JUDGE_QUADS, JUDGE_MIXED };
 constexpr int MOST_IMAGES = 4;
@@ -324,7 +329,7 @@ constexpr float FINITE = 3.402823466e38f;                    // beyond it a valu
 // begin(in): a group of this lane, in(nb) whether a pixel of its is in it; see(mb, i, largest): of kernel 4 grp + i of block mb the largest sum of
 // the group.  value(mb, nb, i): a sum's magnitude.  Every lane takes part.
 template <int MB, int NB, class Value, class Begin, class See>
-__device__ __forceinline__ void judge_sums(int mode, bool ragged, const int (&image)[NB], int first, int last, Value value, Begin begin, See see)
+__device__ __forceinline__ void judge_sums(int mode, bool ragged, const int (&image)[NB], int first, int last, Value value, Begin begin, See see, Joins joins = {})
 {
     if (mode == JUDGE_LANE) {
         begin([&](int nb) { return image[nb] >= 0; });
@@ -362,19 +367,27 @@ __device__ __forceinline__ void judge_sums(int mode, bool ragged, const int (&im
                 }
         }
     } else if (mode == JUDGE_MIXED) {
-        static_for<NB>([&](auto at_c) {
-            constexpr int at = decltype(at_c)::value;
-            begin([&](int nb) { return nb == at && image[nb] >= 0; });
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    float m = 0.f;
+            for (int i = 0; i < 4; ++i) {
+                float m[NB];
 #pragma unroll
-                    for (int nb = 0; nb < NB; ++nb) m = __builtin_elementwise_maximum(m, image[nb] == image[at] ? value(mb, nb, i) : 0.f);
-                    see(mb, i, m);
+                for (int at = 0; at < NB; ++at) {
+                    m[at] = 0.f;
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) m[at] = __builtin_elementwise_maximum(m[at], image[nb] == image[at] ? value(mb, nb, i) : 0.f);
                 }
-        });
+                const float before = lane_before(m[NB - 1]), after = lane_after(m[0]);
+                static_for<NB>([&](auto at_c) {
+                    constexpr int at = decltype(at_c)::value;
+                    begin([&](int nb) { return nb == at && image[nb] >= 0; });
+                    float all = m[at];
+                    if (joins.before & (image[at] == image[0])) all = __builtin_elementwise_maximum(all, before);
+                    if (joins.after & (image[at] == image[NB - 1])) all = __builtin_elementwise_maximum(all, after);
+                    see(mb, i, all);
+                });
+            }
     } else {
         static_for<NB>([&](auto at_c) {
             constexpr int at = decltype(at_c)::value;

@@ -349,8 +349,8 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
                 other |= (back[nb] != first) & (pixel_of(nb, l16) < left_px);
             }
             if (of_one_image & !whole) input = row_largest(input);
-            // (a lane of two images: each one's pixels; of more, single ones)
-            bool of_first[NB], of_last[NB];
+            // (a lane of two images: each one's pixels, and those of the lanes beside it; of more, single ones)
+            bool of_first[NB], of_last[NB], before = false, after = false;
             if (!lane_of_one) {
                 const bool two = g.per >= NB - 1;
                 other = bad;
@@ -362,6 +362,13 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
                     other |= (of_first[nb] & (back[nb] != back[0])) | (of_last[nb] & (back[nb] != back[NB - 1])) | (!two & (nb > 0) & (nb + 1 < NB) & there);
                     apart |= of_last[nb];
                 }
+                before = apart & (l16 > 0) & (image_in(pixel_of(0, l16) - 1) == image_in(pixel_of(0, l16)));
+                after = apart & (l16 < 15) & (pixel_of(NB, l16) < left_px) & (image_in(pixel_of(NB, l16)) == image_in(pixel_of(NB - 1, l16)));
+                const float there[4] = {lane_before(back[NB - 1]), lane_after(back[0]), lane_before(input), lane_after(input)};
+                before &= there[0] == back[0];
+                after &= there[1] == back[NB - 1];
+                if (before) input = __builtin_fmaxf(input, there[2]);
+                if (after) input = __builtin_fmaxf(input, there[3]);
             }
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
@@ -385,6 +392,9 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
                             last = __builtin_elementwise_maximum(last, of_last[nb] ? __builtin_fabsf(acc[mb][nb][i]) : 0.f);
                         }
                         other |= !(m <= FINITE) | !(last <= FINITE);
+                        const float from = lane_before(apart ? last : m), to = lane_after(m);
+                        if (before) m = __builtin_elementwise_maximum(m, from);
+                        if (after) last = __builtin_elementwise_maximum(last, to);
                         m = apart && last < m ? last : m;
                     }
                     other |= !(m >= line_at(mb, i, input)) & kernel_exists(mb, i) & (input > 0.f);
@@ -438,6 +448,7 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
     }
     // Pixels that are judged together have scales of their own: size, a pixel's against that of the brightest of them (0: no output).  The
     // largest input of them, by that scale, makes the line; where all are zero there is none.
+    Joins joins = {};
     auto of_group = [&](const float (&v)[NB], float (&to)[NB]) {
         float all = 0.f;
 #pragma unroll
@@ -454,11 +465,26 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
             }
             to[nb] = mine;
         }
+        if (judging == JUDGE_MIXED) {
+            const float before = lane_before(to[NB - 1]), after = lane_after(to[0]);
+#pragma unroll
+            for (int nb = NB - 1; nb >= 0; --nb) {
+                if (joins.before & (image[nb] == image[0])) to[nb] = __builtin_fmaxf(to[nb], before);
+                if (joins.after & (image[nb] == image[NB - 1])) to[nb] = __builtin_fmaxf(to[nb], after);
+            }
+        }
     };
     bool lost[NB], zero[NB];
     {
         float brightest[NB];
         of_group(size, brightest);
+        if (VPX && judging == JUDGE_MIXED) {
+            const int l16 = opaque(lane) & 15, px0 = pixel_of(0, l16), px1 = pixel_of(NB, l16);
+            const float before = lane_before(brightest[NB - 1]), after = lane_after(brightest[0]);
+            const bool apart = image[NB - 1] != image[0];
+            joins.before = apart & (l16 > 0) & (image[0] >= 0) & (before == brightest[0]) && image_in(px0 - 1) == image[0];
+            joins.after = apart & (l16 < 15) & (px1 < left_px) & (after == brightest[NB - 1]) && image_in(px1) == image[NB - 1];
+        }
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
             lost[nb] = __float_as_uint(inputs[nb]) - 1 < __float_as_uint(HALF_LEAST) - 1;
@@ -496,7 +522,8 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
 #pragma unroll
                                for (int nb = 0; nb < NB; ++nb)
                                    if ((group >> nb & 1) & !(m >= line_of(line, inputs[nb]))) again |= 1ull << ((nb * MB + mb) * 4 + i);
-                           });
+                           },
+                           joins);
     }
     }
     // all of them; the second time those that were marked
