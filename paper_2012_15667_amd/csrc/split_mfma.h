@@ -319,7 +319,7 @@ __device__ __forceinline__ float lane_after(float v) { return __int_as_float(__b
 // Which neighbours' pixels a lane of two images takes to its first and last ones: of its image, and of one scale (`scales` at either end).
 struct Joins { bool before, after; };
 // The sums of a kernel that are judged together, in a wave whose lanes l16 hold NB pixels each (one alone is below its line by chance once in some
-// 10^3, and looking closer costs 2 us): of one image a lane's (where NB is less than four its three neighbours' too; where some pixels are no
+// 10^3, and looking closer costs 2 us): of one image a lane's (where NB is less than four its three neighbours' too, of several images, first < last, those of its own; where some pixels are no
 // outputs, ragged, all of them); of up to MOST_IMAGES all of each; of more those of four neighbouring pixels that are of one image.  Mixed: a
 // lane's pixels that are of one image, several such groups, and those of the lanes beside it that `joins` allows.
 // image[nb]: -1 where there is no output.
@@ -341,7 +341,7 @@ __device__ __forceinline__ void judge_sums(int mode, bool ragged, const int (&im
                 m[mb][i] = 0.f;
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb) m[mb][i] = __builtin_elementwise_maximum(m[mb][i], value(mb, nb, i));
-                if constexpr (NB < 4) m[mb][i] = quad_largest(m[mb][i], 0);
+                if constexpr (NB < 4) m[mb][i] = quad_largest(m[mb][i], first < last ? image[0] : 0);
             }
         if (ragged)
 #pragma unroll

@@ -349,6 +349,13 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
                 other |= (back[nb] != first) & (pixel_of(nb, l16) < left_px);
             }
             if (of_one_image & !whole) input = row_largest(input);
+            // (fewer than four: with the three lanes beside it, as below; all of one scale, then)
+            const int mine = of_one_image ? 0 : image_in(pixel_of(0, l16));
+            if (NB < 4 && lane_of_one) {
+                const bool there = pixel_of(0, l16) < left_px;
+                other |= there & (quad_largest(there ? back[0] : 0.f, mine) != back[0]);
+                input = quad_largest(input, mine);
+            }
             // (a lane of two images: each one's pixels, and those of the lanes beside it; of more, single ones)
             bool of_first[NB], of_last[NB], before = false, after = false;
             if (!lane_of_one) {
@@ -378,10 +385,12 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
                     if (lane_of_one & whole) {
 #pragma unroll
                         for (int nb = 0; nb < NB; ++nb) m = __builtin_elementwise_maximum(m, __builtin_fabsf(acc[mb][nb][i]));
+                        if (NB < 4) m = quad_largest(m, mine);
                         other |= !(m <= FINITE);
                     } else if (lane_of_one) {
 #pragma unroll
                         for (int nb = 0; nb < NB; ++nb) m = __builtin_elementwise_maximum(m, pixel_of(nb, l16) < left_px ? __builtin_fabsf(acc[mb][nb][i]) : 0.f);
+                        if (NB < 4) m = quad_largest(m, mine);
                         if (of_one_image) m = row_largest(m);
                         other |= !(m <= FINITE);
                     } else {
@@ -453,7 +462,7 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
         float all = 0.f;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) all = __builtin_fmaxf(all, v[nb]);
-        if (NB < 4) all = quad_largest(all, 0);
+        if (NB < 4) all = quad_largest(all, of_one_image ? 0 : image[0]);
         if (ragged) all = row_largest(all);
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
@@ -508,7 +517,7 @@ split_point_kernel(const float* __restrict__ x, const u32x4* wt, float* y, Split
                     if (image[nb] >= 0 && (lost[nb] || !(__builtin_fabsf(acc[mb][nb][i]) <= FINITE)) && (kb16 + mb) * 16 + 4 * (opaque(lane) >> 4) + i < g.K)
                         again |= 1ull << ((nb * MB + mb) * 4 + i);
         unsigned group = 0;                                 // bits of the nb that are judged together
-        judge_sums<MB, NB>(judging, ragged, image, 0, 0,
+        judge_sums<MB, NB>(judging, ragged, image, 0, !of_one_image,
                            [&](int mb, int nb, int i) { return __builtin_fabsf(acc[mb][nb][i]) <= FINITE ? __builtin_fabsf(acc[mb][nb][i]) * size[nb] : 0.f; },
                            [&](auto in) {
                                group = 0;

@@ -364,7 +364,8 @@ def _winograd_each(torch, B, run, xd, wd, m, pad):
 
 
 @pytest.mark.parametrize("m,N,C,H,W,K", [(2, 64, 512, 7, 7, 512), (3, 33, 525, 7, 8, 485), (4, 9, 277, 35, 37, 233), (6, 5, 284, 29, 30, 497),
-                                          (4, 128, 512, 5, 5, 512), (6, 100, 512, 4, 4, 512), (2, 96, 516, 13, 13, 516)])
+                                          (4, 128, 512, 5, 5, 512), (6, 100, 512, 4, 4, 512), (2, 96, 516, 13, 13, 516),
+                                          (6, 11, 272, 8, 7, 128), (2, 40, 272, 4, 5, 64)])
 @pytest.mark.parametrize("change", list(APART))
 def test_winograd_product_kernels_whose_operands_differ_in_size(gpu, m, N, C, H, W, K, change):  # noqa: F811
     torch, B = gpu
