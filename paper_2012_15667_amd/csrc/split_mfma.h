@@ -291,6 +291,21 @@ __device__ __forceinline__ KernelFacts all_shares(const KernelFacts* shares, int
     }
     return all;
 }
+// v and what the lane 16 or 32 further holds, both in either lane: their sum or maximum is that of the two.
+struct LanePair { float a, b; };
+template <int APART>
+__device__ __forceinline__ LanePair lanes_apart(float v)
+{
+    static_assert(APART == 16 || APART == 32);
+    const unsigned u = __float_as_uint(v);
+    if constexpr (APART == 16) {
+        const auto p = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+        return {__uint_as_float(p[0]), __uint_as_float(p[1])};
+    } else {
+        const auto p = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+        return {__uint_as_float(p[0]), __uint_as_float(p[1])};
+    }
+}
 // The largest of four neighbouring lanes' values, where their images agree (NaN where one of them is).
 __device__ __forceinline__ float quad_largest(float v, int image)
 {

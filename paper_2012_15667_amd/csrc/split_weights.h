@@ -62,14 +62,19 @@ __device__ __forceinline__ KernelFacts store_halves(u32x4* to, const float (&u)[
         facts.squares = __builtin_fmaf(u[j], u[j], facts.squares);
         facts.small += magnitude(u[j]) - 1 < __float_as_uint(HALF_LEAST) - 1 ? 1.f : 0.f;       // (zero comes last)
     }
-#pragma unroll
-    for (int d = KERNELS; d < 64; d *= 2) {
-        most = __builtin_fmaxf(most, __shfl_xor(most, d));
+    auto share = [&](auto apart_c) {
+        constexpr int APART = decltype(apart_c)::value;
+        const LanePair m = lanes_apart<APART>(most);
+        most = __builtin_fmaxf(m.a, m.b);
         if constexpr (SHARED) {
-            facts.squares += __shfl_xor(facts.squares, d);
-            facts.small += __shfl_xor(facts.small, d);
+            const LanePair q = lanes_apart<APART>(facts.squares), s = lanes_apart<APART>(facts.small);
+            facts.squares = q.a + q.b;
+            facts.small = s.a + s.b;
         }
-    }
+    };
+    static_assert(KERNELS == 16 || KERNELS == 32);
+    if constexpr (KERNELS == 16) share(std::integral_constant<int, 16>{});
+    share(std::integral_constant<int, 32>{});
     const bool fits = (channels < 16 || most == 0.f || most >= HALF_LEAST) && facts.squares <= most_squares;
 #pragma unroll
     for (int i = 0; i < 4; ++i) h[i] |= fits ? 0u : 0x7e007e00u;
