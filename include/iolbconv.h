@@ -98,10 +98,16 @@ typedef struct iolb_bounds_out {
  * (this call, conv_direct_layout with cfg NULL, conv_direct_pad2, conv_direct_noalloc; the products of conv_winograd,
  * conv_winograd_pad, and conv_winograd_ws / _pre with cfg NULL): every operand as the sum of two fp16 parts under a
  * scale taken from the data, three products of parts, or, for few channels and small layers, as the sum of three bf16 parts,
- * six products; fp32 sums -- no less precise than fp32 products.  Their blocks are not tiles of the enumeration;
- * a caller-supplied tile always runs on the fp32 kernels.  Outputs that the parts cannot hold (infinities, NaN, operands or
- * sums near the end of the range, values far from what a sample of the image has as its largest) are computed again in fp32: what
- * fp32 sums give, in up to ten times the layer's time where many are such. */
+ * six products; fp32 sums.  Their blocks are not tiles of the enumeration; a caller-supplied tile always runs on the fp32 kernels.
+ * Precision.  Three parts: no less than fp32 products.  Two parts, n = C R S: to the rounding of fp32 sums two errors add.  Parts hold an
+ * operand to 2^-23 of it and their smallest product is left out: 2^-21 |x| |w| per product at most.  And operands below 2^-10 (Winograd F(4x4): 2^-4) of a
+ * sample's largest value lose more; that is at most 2^-21 in the root mean square, sqrt(n) 2^-20 at worst, of the largest of the sums of the
+ * same kernel that are judged together: those of a few neighbouring output pixels of one image (Winograd: of the sums of a plane, and
+ * 2^-18).  Where no sum of them is large enough for that, they are computed again in fp32, as are outputs that the parts cannot hold
+ * (infinities, NaN, operands or sums near the end of the range).  So a single output is less precise than an fp32 sum only where it is
+ * far smaller than its neighbours of the same kernel and its window holds values far below the largest of theirs.  What is computed
+ * again costs time: 1.1 - 1.5 times the layer's where few outputs are, up to twelve times where most are (one huge value in every image,
+ * channels and kernels scaled by 1e3 and 1e-3 against each other). */
 int conv_direct(const float* x, const float* w, float* y,
                 int N, int C, int H, int W, int K, int R, int S, int stride, int pad);
 

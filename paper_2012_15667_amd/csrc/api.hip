@@ -208,8 +208,9 @@ int check_config(const iolb_shape& s, const iolb_tile_config& cfg)
 
 // ---- direct layers on the 16-bit matrix cores, operands in parts -------------------------------
 // Which kernel a layer without a caller-supplied tile runs on.  The choice and the block depend on the layer alone
-// (not on the entry point nor on the tile it was tuned; the tensor layout changes addresses only), so that every entry
-// point gives the same bits for the same layer, whatever was called before.
+// (not on the entry point nor on the tile it was tuned), so that every entry point gives the same bits for the same
+// layer and layout, whatever was called before.  The layout is part of it for 1 x 1 kernels only: with channels innermost
+// they take the split kernel where the other layouts may keep the fp32 tile.
 struct SplitChoice {
     enum { NONE, CONV, POINT } kind = NONE;
     iolb::SplitGeom conv{};

@@ -21,9 +21,9 @@
 // computed, from what the weights' launch tells of it.  The scales and one barrier more cost 1.2 us of a workgroup's life, the look at
 // the kernels' sums 0.3 - 0.5 (64 -> 64 at 56 x 56, batch 32 33.4 and 34.3 us, 256 -> 256, batch 64 602 and 605; with each kernel's own line
 // there always, by v_dot2 beside the matrix instructions, 36.3 and 609).  Measured whole calls, three
-// bf16 parts / two fp16 parts: 3x3, 256 -> 256 at 56 x 56, batch 64 927 / 605 us (392 TFLOP/s of fp32 products; register-only 646),
-// 64 -> 64 at 56 x 56, batch 32 50 / 38, 128 -> 256 at 28 x 28, stride 2 57 / 42, 5x5, 96 -> 256 at 27 x 27, batch 16, channels
-// innermost 76 / 58; 80 drawn layers 1.17 in the mean.
+// bf16 parts / two fp16 parts: 3x3, 256 -> 256 at 56 x 56, batch 64 927 / 595 us (398 TFLOP/s of fp32 products; register-only 646),
+// 64 -> 64 at 56 x 56, batch 32 50 / 35, 128 -> 256 at 28 x 28, stride 2 57 / 41, 5x5, 96 -> 256 at 27 x 27, batch 16, channels
+// innermost 76 / 57; 80 drawn layers 1.17 in the mean.
 // What bounds it: the matrix cores are busy 0.6 of the cycles; the rest is LDS reads (85 bytes per clock and unit), weight loads (24
 // through the L2) and the first loads and last stores of a round.  Twice the items per batch of staging: equal.
 // With three parts (whole call on the fp32 instructions 1900 us, 934 - 953) measured on that layer: blocks of 32 x 112 per wave 1041 us (kernel),

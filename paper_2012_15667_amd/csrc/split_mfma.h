@@ -134,8 +134,8 @@ __device__ __forceinline__ void kept_eight(const u32x4& h, const u32x4& m, const
 // the same sum, if that one's partner is not far smaller than its own.  So a group of operands that enter the same sums together (an
 // output's window, a kernel's taps and channels) has to hold at least one of 2^-2, or only zeros, and a kernel's sums have to
 // reach a line (below) that tells whether what counts in them was cut; where they do not, outputs are computed again, too.  That is slow where it
-// happens: 64 -> 64 at 56 x 56, batch 32, with one value of each image 1e5 times the others 35 -> 176 us, with a quarter of each image
-// 1e-5 of the rest 175, nine in ten values zero 36 (in three bf16 parts, whatever the finite values, 51).
+// happens: 64 -> 64 at 56 x 56, batch 32, with one value of each image 1e5 times the others 35 -> 184 us, with a quarter of each image
+// 1e-5 of the rest 182, nine in ten values zero 36 (in three bf16 parts, whatever the finite values, 51).
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 constexpr int HALF_TOP = 9;                                  // sample below 2^9

@@ -29,14 +29,15 @@ bool split_derive(SplitGeom* g)
     if ((long long)g->nbk * g->nbx * g->nby * g->nbn > 0x7fffffffLL) return false;
     // kernels of 3 MiB and more do not stay in an L2 of 4 MiB beside the inputs: then an XCD works on one channel block
     // at a time (512 -> 512 at 28 x 28, 14 MB of kernels: 1140 -> 1118 us; 256 -> 256 at 56 x 56, 3.5 MB: 1068 -> 1052;
-    // 256 -> 512 at 28 x 28: equal)
+    // 256 -> 512 at 28 x 28: equal).  Measured with three parts; the bytes are those of three parts in two as well, half as much
+    // again as these take, so that in two parts the line lies at 2 MiB.
     g->k_outer = g->nbk > 1 && split_weight_bytes(*g) >= (3LL << 20);
     g->nbuf = split_chunks(*g) > 1 ? 2 : 1;
     if (g->b * g->tx * g->ty > 16 * g->nb * g->wn) return false;
     if (4LL * g->b * g->C * g->H * g->W >= (1LL << 31)) return false;
     g->cstep = g->hwc ? 4 : 4 * g->H * g->W;
     if (split_chunks(*g) > 1 && split_batches(*g) > split_steps(*g)) return false;
-    // Sixteen lanes read 16 bytes each of consecutive pixels, 48 bytes apart: that covers every LDS bank once.  A row
+    // Sixteen lanes read 16 bytes each of consecutive pixels, 48 bytes apart (16 in two parts): that covers every LDS bank once.  A row
     // pitch that is congruent to the bytes of a tile row modulo the 256 bytes of the banks keeps it so across a row
     // end; taken where it does not cost a resident workgroup.
     const int px = split_pixel_bytes(g->parts);
@@ -309,8 +310,8 @@ bool split_point_faster(const iolb_shape& s, int P, int Q, bool hwc)
 
 // Sums of fewer channels keep three bf16 parts, whose error is smaller there (F(2 x 2), 16 channels 1.0e-7 against 1.3e-7, 48 1.7e-7 and
 // 1.9e-7; F(4 x 4) 3.7e-7 and 5.4e-7, 1.2e-6 and 1.3e-6; from 64 on that of two fp16 parts is), and which are up to 12 % faster there;
-// so do a few more in a single round of workgroups, where the sample of two parts costs more than its products save (64 -> 64 at 28 x 28,
-// batch 8, F(2 x 2) 13.1 and 13.3 us).
+// so do a few more in a single round of workgroups, where the sample of two parts costs more than its products save (40 drawn layers of
+// 64 - 94 channels in one round, two parts against three: F(2 x 2) 1.00 - 1.10 times the time, F(4 x 4) 0.97 - 1.19; 1.034 in the mean).
 constexpr int WINO_TWO_LEAST = 64, WINO_TWO_SMALL = 96;
 
 // Modelled time of a call: the kernels' transform, and per round of workgroups first loads and stores and a stage of 16

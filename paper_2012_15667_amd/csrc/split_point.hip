@@ -5,8 +5,11 @@
 // A step is 32 channels.  The inputs of chunk t + 1 are split and written to one LDS buffer while chunk t is multiplied
 // from the other; their loads are issued three chunks ahead and kept in registers, two neighbouring pixels per load where
 // the layout has them.  Every pixel has a scale of its own: its image's largest value in the block, from the first 32 channels and a few more, but at
-// most 512 times the largest of the pixel's own sample.  Sums are judged, and some computed again, as in direct_split.hip.  The split's arithmetic is
-// placed between the matrix instructions, three vector
+// most 512 times the largest of the pixel's own sample.  Sums are judged, and some computed again, as in direct_split.hip: those of a lane's
+// four pixels together, or where these are of two images (a plane of 7 x 7 sub-domains) those of one with the pixels of the lane beside it.
+// One to three alone are below their line so often that nearly every wave looked closer: product of 512 -> 512 at 14 x 14, batch 64, F(2 x 2)
+// 113 us, with the lane beside it 103, without lines per kernel 91; all of 768 -> 192 at 17 x 17 35.1 and, without, 34.0.  The split's
+// arithmetic is placed between the matrix instructions, three vector
 // instructions after each, where it costs little (a 16-bit matrix instruction leaves the vector pipeline free; measured:
 // eight vector instructions per 32-cycle matrix instruction 1433 against 1631 TFLOP/s).  wt is not declared restrict on
 // purpose: loads of memory known not to change were moved down past the barrier to their use, which undid the prefetch.

@@ -9,7 +9,8 @@
 //
 // Two parts: inputs are scaled before their transform, per image of the block by a sample of its first stage and a few channels more;
 // kernels per kernel, their planes brought to the same size.  A sub-domain whose windows are all too small for the scale, like a sum that
-// is not finite, has its block taken again.
+// is not finite, has its block taken again; so has one of whose sums in a plane none reaches the line of its kernel (split_mfma.h), from the
+// parts, and where these do not hold the kernel, from the caller's.  Lines and looking at them cost 1 us of 50 (256 -> 256 at 14 x 14).
 //
 // What bounds it, F(4 x 4), 32 x 64, 128 -> 128 at 112 x 112, batch 64: of the 46 us that a block lives, 10 pass before its first product
 // and 9 after its last, with one block on a unit; a stage takes 3.4, 1.7 of them products and waiting for kernel parts (147 KB from the L2), the rest
@@ -17,11 +18,12 @@
 // bf16 parts / this: that layer 859 / 581 / 496 us (119 TFLOP/s of the planes' products), F(4 x 4) 256 -> 256 at 14 x 14 87 / 60 / 52,
 // F(2 x 2) 64 -> 64 at 28 x 28, batch 8 (three parts) 19.8 / 13.2.
 // Channel sums through LDS two at a time, and no division by the planes' scales: 506 -> 496.
-// Registers: F(4 x 4), 32 x 64 has 251, three parts 256 and spill 5 (24 bytes a lane; 13 and 44 where columns are read one by one).
-// A block with a sum that is not finite is taken again by all its waves, stage by stage without overlap: one NaN adds the time of one
-// such block (256 -> 256 at 14 x 14 64 -> 155 us, 64 -> 64 at 28 x 28, batch 8 14.9 -> 25.5, where the fp32 kernels took 94 and 20.5 whatever the
-// values), all NaN takes 2.1 - 2.8 times as long (128 -> 128 at 112 x 112 600 -> 1690 us, fp32 kernel 860).  With the next stage's inputs
-// and the next unit's kernels on their way that was 133, 24.1 and 1427, but one or two more registers were spilled and large finite layers took 0.5 %
+// Registers: F(4 x 4), 32 x 64 has 253 and spills 47 - 62 scalar ones, most of them of what is taken again; three parts 256 and spill 5
+// vector ones (24 bytes a lane; 13 and 44 where columns are read one by one).
+// A block that is taken again is so by all its waves, stage by stage without overlap: one such block adds its time (256 -> 256 at 14 x 14, F(4 x 4)
+// 52 -> 178 us, 128 -> 128 at 56 x 56, batch 8, F(2 x 2) 35 -> 101), and where the caller's kernels are read in it, which is not tuned, several
+// times that (channels and kernels balanced by 1e3: 490 and 390).  With three parts, of which one NaN cost 64 -> 155 us: the next stage's inputs
+// and the next unit's kernels on their way in it gave 133, but one or two more registers were spilled and large finite layers took 0.5 %
 // longer: not kept.
 // Measured and not kept: four waves of twice the planes each; transform and loads spread between the matrix instructions
 // of every wave in place of the two phases below (F(4 x 4), 256 -> 256 at 56 x 56 521 -> 666: 26 registers spilled);

@@ -1,5 +1,6 @@
 """Operands in two fp16 parts (split_mfma.h): what their scales, taken from samples, do not fit is computed again in fp32, image by
-image and kernel by kernel, and every output keeps the error bound of a sum in fp32."""
+image and kernel by kernel.  Outputs keep the error bound of a sum in fp32 beside what parts may lose of the largest of the few sums of a
+kernel that are judged together; the tests say which bound they hold outputs to."""
 import ctypes
 
 import numpy as np
@@ -12,6 +13,7 @@ from tests.test_split_kernels import _bound, gpu  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
+# (These four run in three bf16 parts, which hold every value: the same data through the other kind of parts.  Layers in two parts: TWO_PARTS.)
 # N, C, H, W, K, R, stride, pad: whole images in a block, parts of one, a window of one row and of one pixel, chunks of 16 and 32
 LAYERS = [(6, 48, 7, 7, 40, 3, 1, 1), (3, 72, 30, 31, 64, 3, 1, 1), (5, 64, 16, 15, 130, 3, 2, 1), (2, 40, 40, 40, 24, 5, 1, 2)]
 
@@ -247,7 +249,8 @@ def _one_image_of_it(x, w):
 
 APART = {"identity": _identity, "balanced_1e3": _balanced(1e3), "balanced_1e5": _balanced(1e5), "balanced_1e7": _balanced(1e7), "balanced_1e9": _balanced(1e9),
          "pruned_1e-8": _pruned(1e-8), "pruned_1e-12": _pruned(1e-12), "small_1": _some_small_kernels(1), "small_4": _some_small_kernels(4),
-         "small_7": _some_small_kernels(7), "small_100": _some_small_kernels(100), "last": _last_channels, "halves": _halves, "beside_outliers": _beside_outliers, "one_image": _one_image_of_it}
+         "small_7": _some_small_kernels(7), "small_100": _some_small_kernels(100), "last": _last_channels, "halves": _halves,
+         "beside_outliers": _beside_outliers, "one_image": _one_image_of_it}
 
 
 def _conv64(torch, xd, wd, stride, pad):

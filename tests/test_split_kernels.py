@@ -25,7 +25,9 @@ def gpu():
 def _bound(x, w, stride, pad, ref_of=conv_ref):
     """Largest error of a sum of products taken in three bf16 parts, per output: a running sum is rounded six times per
     step of four (tap, eight channels) units and every rounding, inside the instruction too, is at most 2^-23 of the sum
-    of magnitudes so far (twice 2^-24: truncation is allowed for); the products left out add 3 * 2^-24."""
+    of magnitudes so far (twice 2^-24: truncation is allowed for); the products left out add 3 * 2^-24.  Layers in two fp16 parts round half as often
+    (three products a step) and lose 2^-21 of each product at most, 4 of the 16 units that stand beside the steps here: the bound holds
+    for them with half to spare."""
     C, RS = w.shape[1], w.shape[2] * w.shape[3]
     steps = -(-C // 8) * RS
     return (12 * steps + 16) * 2.0 ** -23 * ref_of(np.abs(x), np.abs(w), stride, pad)
@@ -159,7 +161,9 @@ def test_single_products_have_fp32_precision(gpu, layer):
     products of parts three are left out: m l and l m, each at most 2^-8 2^-16 of it, and l l: 2^-23.  The other six are
     added in five roundings of at most 2^-23 of the sum (truncation allowed for); the partial sums exceed the product by
     no more than 2^-7 of it.  A product left out beside these, h l, l h or m m, breaks it (computed on the CPU with such a
-    split: 0.12 of the bound with the six, 10 to 19 times the bound without one of those)."""
+    split: 0.12 of the bound with the six, 10 to 19 times the bound without one of those).  The third layer runs in two fp16
+    parts: each operand is held to 2^-23 of it, l l, at most 2^-22, is left out, and the sum is rounded once beside what is far smaller: 4.5 of
+    the six 2^-23; 0.8 * 2^-24 in the mean."""
     torch, B = gpu
     N, C, H, W, K, R, pad = layer
     assert B.iolb_route(B.make_shape(N, C, H, W, K, R, R, 1, pad))[0] == B.ROUTE_SPLIT
